@@ -202,11 +202,9 @@ hipError_t launch_calib_unpack(const Dims& d, const uint8_t* state, const lq_cal
 struct RotLayout {
     size_t off_X, off_M, off_G;  // Omega, momentum, gradient of the last step (r x r each)
     size_t off_E1, off_E2;       // N x r and r x K quantisation errors of the rotated factors (last step)
-    size_t off_ax;               // per-wavefront row maxima of Omega^T R, [4 * nkb][r]
-    size_t off_lp;               // partial sums of E1^2 (nlb), then of E2^2 (r * nkb)
-    size_t off_gp;               // partials of the gradient, [workgroup][r][r]
-    size_t off_tmp;              // scratch matrices of the update
-    int nlb, nkb, n_lp;
+    size_t off_ax;               // row maxima of Omega^T R, one set per workgroup
+    size_t off_lp;               // partial sums of E1^2, then of E2^2, one per workgroup
+    size_t off_gp;               // parts of the gradient, [workgroup][r][r]
     size_t total;
 };
 RotLayout rot_layout(const Dims& d);

@@ -6,77 +6,82 @@
 // ascending (the codes depend on their rounding); the rounding has zero derivative (App. B.2), so
 //     G = -2/(N r) L^T E1 - 2/(r K) R E2^T
 // and the update is the Cayley SGD with momentum of the work the paper cites for it (Li et al. 2020, Algorithm 1).
-// Five launches per step, no atomics, every sum in a fixed order:
-//   rot_zl_kernel     one thread per row of L: the row of Z1 in blocks of 32 columns (twice with a per-row scale: row
-//                     maximum, then codes), E1, partial sums of E1^2
-//   rot_zr_kernel     one thread per column of R: the column of Z2 (stored in E2's place), per-wavefront row maxima
-//   rot_qr_kernel     E2 = deq(Q2(Z2)) - Z2 in place, partial sums of E2^2 (row-scaled Q2 only: with block scales
-//                     rot_zr_kernel forms E2 itself and a step is four launches)
-//   rot_grad_kernel   partials of L^T E1 and R E2^T over strided 16-deep slices of N and K
-//   rot_cayley_kernel one workgroup: G, loss, momentum, the skew-symmetric W, step length, the fixed-point passes
+// Four launches per step (three with block-scaled Q2), no atomics, every sum in a fixed order:
+//   rot_z_kernel      64 rows of L (or columns of R) per workgroup turn: Z1 / Z2 on the fp32 matrix instruction, E1 / E2,
+//                     their part of G, partial sums of squares.  A row of Z2 runs over all of K, so with one scale per row
+//                     the first launch only leaves the row maxima of Z2 and a second, small one forms E2 and its part of G
+//   rot_sum_kernel    G from the workgroups' parts (fp64), the loss
+//   rot_cayley_kernel one workgroup: momentum, the skew-symmetric W, step length, the fixed-point passes
+//
+// v_mfma_f32_16x16x4_f32 is, bit for bit, four fused multiply-adds in ascending order of its contraction index (checked
+// against fma chains on random operands over 2^+-12 and on subnormal products), so it evaluates the chains that
+// define Z1 and Z2.  One step on 11200 x 64 and 64 x 2240 factors took 202 us with one thread per row or column
+// (44 + 9 workgroups, Omega read from LDS for every fourth multiply-add; the update alone 66 us on one CU's vector ALUs).
 #include <mutex>
 
-#include "lq_internal.h"
 #include <type_traits>
+
+#include "lq_internal.h"
 
 namespace lq {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int ROT_TPB = 256;
-constexpr int ROT_GRAD_WGS = 64;   // slices the two contractions of the gradient are dealt to
-constexpr int ROT_TMP = 3;         // r x r scratch matrices of the update kernel
+
+// How the 64-row groups of L and the 64-column groups of R are dealt to workgroups.  Every workgroup leaves one r x r part
+// of the gradient, so their number is capped: at rank 64 by what LQ_ROT_STATIC_SCRATCH_BYTES holds, at the others by
+// the traffic of rot_sum_kernel (128 parts of rank 128 are 8 MB).
+struct RotSplit {
+    int gL, gR;   // groups
+    int wL, wR;   // workgroups that form E1 and E2
+    int wM;       // workgroups that leave row maxima of Z2 (row kinds)
+};
+static RotSplit rot_split(const Dims& d)
+{
+    const int cap = d.r <= 32 ? 256 : d.r == 64 ? 112 : 128;
+    RotSplit w;
+    w.gL = (int)(d.N / 64);
+    w.gR = (int)(d.K / 64);
+    const int per = (w.gL + w.gR + cap - 1) / cap;
+    w.wL = (w.gL + per - 1) / per;
+    w.wR = w.gR < cap - w.wL ? w.gR : cap - w.wL;
+    if (w.wR < 1) w.wR = 1;
+    w.wM = w.gR < 256 ? w.gR : 256;
+    return w;
+}
 
 RotLayout rot_layout(const Dims& d)
 {
     RotLayout rl;
+    const RotSplit w = rot_split(d);
     const size_t rr = (size_t)d.r * d.r * 4;
-    rl.nlb = (int)((d.N + ROT_TPB - 1) / ROT_TPB);
-    rl.nkb = (int)((d.K + ROT_TPB - 1) / ROT_TPB);
     size_t o = 0;
     rl.off_X = o;   o = align256(o + rr);
     rl.off_M = o;   o = align256(o + rr);
     rl.off_G = o;   o = align256(o + rr);
     rl.off_E1 = o;  o = align256(o + (size_t)d.N * d.r * 4);
     rl.off_E2 = o;  o = align256(o + (size_t)d.r * d.K * 4);
-    rl.off_ax = o;  o = align256(o + (size_t)rl.nkb * 4 * d.r * 4);
-    rl.n_lp = rl.nlb + d.r * rl.nkb;
-    rl.off_lp = o;  o = align256(o + (size_t)rl.n_lp * 4);
-    rl.off_gp = o;  o = align256(o + (size_t)ROT_GRAD_WGS * rr);
-    rl.off_tmp = o; o = align256(o + (size_t)ROT_TMP * rr);
+    rl.off_ax = o;  o = align256(o + (size_t)w.wM * d.r * 4);
+    rl.off_lp = o;  o = align256(o + (size_t)(w.wL + w.wR) * 4);
+    rl.off_gp = o;  o = align256(o + (size_t)(w.wL + w.wR) * rr);
     rl.total = o;
     return rl;
 }
 
-// Maximum over the 64 lanes (in every lane) on the data-parallel-primitive path.
+// Maximum over a row of 16 lanes (in each of them), on the data-parallel-primitive path.
 template <int CTRL>
 __device__ __forceinline__ float rot_dpp_max(float v)
 {
     const int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false);
     return fmaxf(v, __int_as_float(o));
 }
-__device__ __forceinline__ float rot_wave_max(float v)
+__device__ __forceinline__ float rot_max16(float v)
 {
-    v = rot_dpp_max<0xB1>(v);   // quad_perm [1,0,3,2]
-    v = rot_dpp_max<0x4E>(v);   // quad_perm [2,3,0,1]
-    v = rot_dpp_max<0x141>(v);  // row_half_mirror
-    v = rot_dpp_max<0x140>(v);  // row_mirror
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
-}
-
-// Sum over the workgroup (256 threads), valid in thread 0.
-__device__ __forceinline__ float rot_block_sum(float v, float* red)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
-    const int tid = threadIdx.x;
-    if ((tid & 63) == 0) red[tid >> 6] = v;
-    __syncthreads();
-    return red[0] + red[1] + red[2] + red[3];
+    v = rot_dpp_max<0xB1>(v);     // quad_perm [1,0,3,2]
+    v = rot_dpp_max<0x4E>(v);     // quad_perm [2,3,0,1]
+    v = rot_dpp_max<0x141>(v);    // row_half_mirror
+    return rot_dpp_max<0x140>(v); // row_mirror
 }
 
 // Q2, the format lq_pack_weights gives L and R (App. A.3).  Row kinds carry one fp32 scale per row: 0 symmetric integers
@@ -87,20 +92,6 @@ struct RotQ {
     float top;  // row kinds: qmax or 448
     int bits;   // MXINT
 };
-
-// Maximum over the lane's half of the wavefront (lanes 0..31 | 32..63 = one block of 32 columns).
-__device__ __forceinline__ float rot_half_max(float v, int lane)
-{
-    v = rot_dpp_max<0xB1>(v);
-    v = rot_dpp_max<0x4E>(v);
-    v = rot_dpp_max<0x141>(v);
-    v = rot_dpp_max<0x140>(v);
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    return lane < 32 ? fmaxf(r0, r1) : fmaxf(r2, r3);
-}
 
 // Row kinds: scale amax / top, codes against top / amax (an all-zero row: scale 1).
 __device__ __forceinline__ void rot_scale(float amax, float top, float& s, float& inv)
@@ -155,378 +146,415 @@ __device__ __forceinline__ float rot_err_block(float z, int e, const RotQ& q)
     return __builtin_ldexpf(c, e - frac) - z;
 }
 
-// BW neighbouring entries of the thread's row (or column) of Z: z[c] = sum_i a(i) * Om[i][j0 + c], each an fma chain over
-// ascending i.  The rank index is the loop (four rows of Omega per turn, broadcast from LDS), the BW running sums are the
-// registers: the thread's own operand a(i) is read again for every block of columns (L1-resident) instead of being held,
-// so the register count does not grow with the rank (a first version that held the row spilled at ranks 96 and 128).
-template <int R, int BW, typename AOP>
-__device__ __forceinline__ void rot_chain_block(AOP a, const float* om, int j0, float (&z)[BW])
-{
-#pragma unroll
-    for (int c = 0; c < BW; ++c) z[c] = 0.f;
-    float av[4], an[4];
-    a(0, av);
-#pragma unroll 1
-    for (int i = 0; i < R; i += 4) {
-        a(i + 4 < R ? i + 4 : i, an);  // the next turn's operand, requested before this turn's arithmetic
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int c = 0; c < BW; c += 4) {
-                const v4f w = *(const v4f*)(om + (i + u) * R + j0 + c);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) z[c + t] = __builtin_fmaf(av[u], w[t], z[c + t]);
-            }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) av[u] = an[u];
-    }
-}
+struct RotZParams {
+    const float* L;
+    const float* R;
+    const float* X;    // Omega
+    int N, K;
+    RotSplit w;
+    RotQ q;
+    float *oL, *oR;    // E1, E2 (ROT_OUT: the rotated factors)
+    float* ax;         // row maxima of Z2, [wM][r]
+    float* lp;         // sums of squares, [wL + wR]
+    float* gp;         // parts of the gradient, [wL + wR][r][r]
+    float c1, c2;
+};
 
-// One thread per row n of L.  OUTZ: write Z1 = L Omega itself (the rotated factor) instead of its quantisation error.
-// QK: 0 integer rows, 1 FP8 rows (one scale per row: the chains run twice, row maximum first), 2 block kinds (a block
-// of 32 columns is one pass of the chains).
-template <int R, bool OUTZ, int QK>
-__global__ __launch_bounds__(ROT_TPB) void rot_zl_kernel(const float* __restrict__ L, const float* __restrict__ X, int N,
-                                                        RotQ q, float* __restrict__ out, float* __restrict__ lp)
-{
-    constexpr int BW = R < 32 ? R : 32;
-    extern __shared__ __attribute__((aligned(16))) float om[];
-    __shared__ float red[4];
-    for (int i = threadIdx.x; i < R * R; i += ROT_TPB) om[i] = X[i];
-    __syncthreads();
-    const int n = blockIdx.x * ROT_TPB + threadIdx.x;
-    const bool ok = n < N;
-    const float* lrow = L + (size_t)(ok ? n : 0) * R;  // rows past N recompute row 0 and store nothing
-    auto aop = [&](int i, float (&av)[4]) {
-        const v4f v = *(const v4f*)(lrow + i);
-        av[0] = v[0]; av[1] = v[1]; av[2] = v[2]; av[3] = v[3];
-    };
-    float* orow = out + (size_t)(ok ? n : 0) * R;
-    float z[BW];
-    float sq = 0.f;
-    if constexpr (OUTZ) {
-#pragma unroll 1
-        for (int j0 = 0; j0 < R; j0 += BW) {
-            rot_chain_block<R, BW>(aop, om, j0, z);
-            if (ok) {
-#pragma unroll
-                for (int c = 0; c < BW; c += 4) *(v4f*)(orow + j0 + c) = v4f{z[c], z[c + 1], z[c + 2], z[c + 3]};
-            }
-        }
-    } else {
-        float s = 1.f, inv = 1.f;
-        if constexpr (QK != 2) {
-            float amax = 0.f;
-#pragma unroll 1
-            for (int j0 = 0; j0 < R; j0 += BW) {
-                rot_chain_block<R, BW>(aop, om, j0, z);
-#pragma unroll
-                for (int c = 0; c < BW; ++c) amax = fmaxf(amax, fabsf(z[c]));
-            }
-            rot_scale(amax, q.top, s, inv);
-        }
-#pragma unroll 1
-        for (int j0 = 0; j0 < R; j0 += BW) {
-            rot_chain_block<R, BW>(aop, om, j0, z);  // (row kinds: the same chains, the same bits as in the first pass)
-            int eb = 0;
-            if constexpr (QK == 2) {
-                float amax = 0.f;
-#pragma unroll
-                for (int c = 0; c < BW; ++c) amax = fmaxf(amax, fabsf(z[c]));
-                eb = rot_block_exp(amax, q);
-            }
-#pragma unroll
-            for (int c = 0; c < BW; ++c) {
-                if constexpr (QK == 2) z[c] = rot_err_block(z[c], eb, q);
-                else z[c] = rot_err<QK>(z[c], s, inv, q.top);
-                sq = __builtin_fmaf(z[c], z[c], sq);
-            }
-            if (ok) {
-#pragma unroll
-                for (int c = 0; c < BW; c += 4) *(v4f*)(orow + j0 + c) = v4f{z[c], z[c + 1], z[c + 2], z[c + 3]};
-            }
-        }
-        const float tot = rot_block_sum(ok ? sq : 0.f, red);
-        if (threadIdx.x == 0) lp[blockIdx.x] = tot;
-    }
-}
+// ROT_OUT: write Z1 and Z2.  ROT_FIRST (row kinds): E1 and its part of G; row maxima of Z2.  ROT_SECOND: E2 and its part
+// of G.  ROT_BOTH (block kinds): E1, E2 and their parts of G.
+enum { ROT_OUT, ROT_FIRST, ROT_SECOND, ROT_BOTH };
 
-// One thread per column k of R: the column of Z2 = Omega^T R.  OUTZ: written to out[j][k] as it is.  Otherwise, row kinds
-// of Q2: Z2 is written and the maximum magnitude of every row j over the wavefront's 64 columns is left in
-// ax[4 * block + wavefront][j] (rot_qr_kernel finishes the job); block kinds: a block is 32 lanes of one row, so the error
-// is formed here, written to out, and its squares are summed into lp[block].
-template <int R, bool OUTZ, int QK>
-__global__ __launch_bounds__(ROT_TPB) void rot_zr_kernel(const float* __restrict__ Rm, const float* __restrict__ X, int K,
-                                                        RotQ q, float* __restrict__ out, float* __restrict__ ax,
-                                                        float* __restrict__ lp)
+// LDS strides in floats, chosen for conflict-free operand reads: lane (l15, q) reads Omega[4 s + q][l15], so q has to move
+// by 16 banks; it reads row l15, column 4 s + q of the staged factor and, in the second contraction, row 16 s + 4 q + u,
+// column l15 of the factor and the error: a stride of 4 modulo 16 serves both.
+template <int R> constexpr int rot_sx() { return R % 32 ? R : R + 16; }
+template <int R> constexpr int rot_sl() { return R + 4; }
+template <int R> constexpr int rot_z_lds() { return (R * rot_sx<R>() + 2 * 64 * rot_sl<R>() + 6 * R) * 4; }
+
+// A workgroup turn is a group of 64 rows of L (columns of R, transposed on the way into LDS): each of the 4 wavefronts
+// forms 16 rows of Z (R / 16 tiles of 16 x 16: lane (l15, q) holds rows 4 q + i, column l15), quantises them in registers,
+// and leaves the error in LDS, from where each wavefront contracts one quadrant of G over the 64 rows; the quadrant stays in
+// registers over all turns.
+// QK: 0 integer rows, 1 FP8 rows (one scale per row), 2 block kinds.
+template <int R, int MODE, int QK>
+__global__ __launch_bounds__(ROT_TPB) void rot_z_kernel(RotZParams p)
 {
-    constexpr int BW = R < 32 ? R : 32;
-    extern __shared__ __attribute__((aligned(16))) float om[];
-    __shared__ float red[4];
-    for (int i = threadIdx.x; i < R * R; i += ROT_TPB) om[i] = X[i];
-    __syncthreads();
-    const int k = blockIdx.x * ROT_TPB + threadIdx.x;
-    const bool ok = k < K;
-    // buffer loads: the row offset i * K travels in a scalar register and all loads share one vector offset; a column
-    // past K reads finite in-range data of the next row (zeros past the end of the descriptor), and nothing computed
-    // from it is stored or enters a maximum
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)Rm, 0, R * K * 4, 0x00020000);
-    auto aop = [&](int i, float (&av)[4]) {
+    constexpr int T = R / 16, H = T > 1 ? T / 2 : 1, SX = rot_sx<R>(), SL = rot_sl<R>();
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    float* Xs = lds;                 // Omega
+    float* Ls = Xs + R * SX;         // the group's rows of L / columns of R
+    float* Es = Ls + 64 * SL;        // their errors
+    float* red = Es + 64 * SL;       // [4][R] column maxima per wavefront; then scale[R], 1 / scale[R] of the rows of Z2
+    float* sc = red + 4 * R;
+    const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nL = MODE == ROT_SECOND ? 0 : p.w.wL;
+    const bool left = (int)blockIdx.x < nL;
+    const int wg = left ? blockIdx.x : blockIdx.x - nL;
+    const int nwg = left ? p.w.wL : (int)gridDim.x - nL;
+    const int ngroups = left ? p.w.gL : p.w.gR;
+    const bool maxima = MODE == ROT_FIRST && !left;  // only the row maxima of Z2 are wanted
+    const int K = p.K;
+
+    for (int e = tid; e < R * R / 4; e += ROT_TPB) {
+        const int row = e / (R / 4), c = e - row * (R / 4);
+        *(v4f*)(Xs + row * SX + 4 * c) = *(const v4f*)(p.X + 4 * e);
+    }
+    if constexpr (MODE == ROT_SECOND) {  // scales of the rows of Z2
+        constexpr int SLICES = ROT_TPB / R < 4 ? ROT_TPB / R : 4;
+        const int sl = tid / R, j = tid - sl * R;
+        if (sl < SLICES) {
+            float m = 0.f;
+#pragma unroll 8
+            for (int i = sl; i < p.w.wM; i += SLICES) m = fmaxf(m, p.ax[(size_t)i * R + j]);
+            red[sl * R + j] = m;
+        }
+        __syncthreads();
+        if (tid < R) {
+            float m = red[tid];
+            for (int i = 1; i < SLICES; ++i) m = fmaxf(m, red[i * R + tid]);
+            float s, inv;
+            rot_scale(m, p.q.top, s, inv);
+            sc[tid] = s;
+            sc[R + tid] = inv;
+        }
+    }
+    v4f g[H][H];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) av[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, k * 4, (i + u) * K * 4, 0));
-    };
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    float z[BW];
+    for (int a = 0; a < H; ++a)
+#pragma unroll
+        for (int b = 0; b < H; ++b) g[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
+    float mx[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) mx[t] = 0.f;
     float sq = 0.f;
-#pragma unroll 1
-    for (int j0 = 0; j0 < R; j0 += BW) {
-        rot_chain_block<R, BW>(aop, om, j0, z);
+    const int ha = wave >> 1, hb = wave & 1;
+
+    for (int grp = wg; grp < ngroups; grp += nwg) {
+        __syncthreads();  // the previous turn's contraction has read Ls and Es
+        if (left) {
+            const float* src = p.L + (size_t)grp * 64 * R;
 #pragma unroll
-        for (int c = 0; c < BW; ++c) {
-            float o = z[c];
-            if constexpr (!OUTZ) {
-                if constexpr (QK != 2) {
-                    const float m = rot_wave_max(ok ? fabsf(o) : 0.f);
-                    if (lane == 0) ax[(size_t)(blockIdx.x * 4 + wave) * R + j0 + c] = m;
-                } else {
-                    const int eb = rot_block_exp(rot_half_max(ok ? fabsf(o) : 0.f, lane), q);
-                    o = rot_err_block(o, eb, q);
-                    if (ok) sq = __builtin_fmaf(o, o, sq);
+            for (int e = 0; e < 64 * R / 4 / ROT_TPB; ++e) {
+                const int f = tid + e * ROT_TPB, row = f / (R / 4), c = f - row * (R / 4);
+                *(v4f*)(Ls + row * SL + 4 * c) = *(const v4f*)(src + 4 * f);
+            }
+        } else {
+            const float* src = p.R + (size_t)grp * 64;
+#pragma unroll
+            for (int e = 0; e < 64 * R / 4 / ROT_TPB; ++e) {
+                const int f = tid + e * ROT_TPB, i = f >> 4, c = f & 15;
+                const v4f v = *(const v4f*)(src + (size_t)i * K + 4 * c);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) Ls[(4 * c + u) * SL + i] = v[u];
+            }
+        }
+        __syncthreads();
+        v4f z[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) z[t] = v4f{0.f, 0.f, 0.f, 0.f};
+        {
+            const float* ap = Ls + (16 * wave + l15) * SL + q;
+            const float* bp = Xs + q * SX + l15;
+#pragma unroll 4
+            for (int s = 0; s < R / 4; ++s) {
+                const float a = ap[4 * s];
+#pragma unroll
+                for (int t = 0; t < T; ++t) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bp[4 * s * SX + 16 * t], z[t], 0, 0, 0);
+            }
+        }
+        float* dl = p.oL + (size_t)(grp * 64 + 16 * wave + 4 * q) * R + l15;  // row 4 q + i, column 16 t + l15
+        float* dr = p.oR + (size_t)l15 * K + grp * 64 + 16 * wave + 4 * q;    // row 16 t + l15, columns 4 q ..
+        if constexpr (MODE != ROT_OUT) {
+            if (maxima) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    float m = fmaxf(fmaxf(fabsf(z[t][0]), fabsf(z[t][1])), fmaxf(fabsf(z[t][2]), fabsf(z[t][3])));
+                    mx[t] = fmaxf(mx[t], m);
                 }
+                continue;
             }
-            if (ok) out[(size_t)(j0 + c) * K + k] = o;
+            if (left) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (QK == 2) {
+#pragma unroll
+                        for (int t = 0; t < T; t += 2) {  // (block kinds have rank >= 32: T is even)
+                            const int t1 = t + 1 < T ? t + 1 : t;
+                            const int eb = rot_block_exp(rot_max16(fmaxf(fabsf(z[t][i]), fabsf(z[t1][i]))), p.q);
+                            z[t][i] = rot_err_block(z[t][i], eb, p.q);
+                            if (t1 > t) z[t1][i] = rot_err_block(z[t1][i], eb, p.q);
+                        }
+                    } else {
+                        float m = 0.f, s, inv;
+#pragma unroll
+                        for (int t = 0; t < T; ++t) m = fmaxf(m, fabsf(z[t][i]));
+                        rot_scale(rot_max16(m), p.q.top, s, inv);
+#pragma unroll
+                        for (int t = 0; t < T; ++t) z[t][i] = rot_err<QK>(z[t][i], s, inv, p.q.top);
+                    }
+                }
+            } else if constexpr (QK == 2) {  // a block is 32 rows of the group: this wavefront's 16 and its neighbour's
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    float m = fmaxf(fmaxf(fabsf(z[t][0]), fabsf(z[t][1])), fmaxf(fabsf(z[t][2]), fabsf(z[t][3])));
+                    m = fmaxf(m, __shfl_xor(m, 16));
+                    m = fmaxf(m, __shfl_xor(m, 32));
+                    mx[t] = m;
+                    red[wave * R + 16 * t + l15] = m;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const int eb = rot_block_exp(fmaxf(mx[t], red[(wave ^ 1) * R + 16 * t + l15]), p.q);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) z[t][i] = rot_err_block(z[t][i], eb, p.q);
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) z[t][i] = rot_err<QK>(z[t][i], sc[16 * t + l15], sc[R + 16 * t + l15], p.q.top);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            if (left) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dl[i * R + 16 * t] = z[t][i];
+            } else {
+                *(v4f*)(dr + (size_t)16 * t * K) = z[t];
+            }
+        }
+        if constexpr (MODE != ROT_OUT) {
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sq = __builtin_fmaf(z[t][i], z[t][i], sq);
+                    Es[(16 * wave + 4 * q + i) * SL + 16 * t + l15] = z[t][i];
+                }
+            __syncthreads();
+            if (T > 1 || wave == 0) {
+                const float* ap = Ls + 4 * q * SL + 16 * H * ha + l15;
+                const float* bp = Es + 4 * q * SL + 16 * H * hb + l15;
+#pragma unroll 2
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        float av[H], bv[H];
+#pragma unroll
+                        for (int a = 0; a < H; ++a) av[a] = ap[(16 * s + u) * SL + 16 * a];
+#pragma unroll
+                        for (int b = 0; b < H; ++b) bv[b] = bp[(16 * s + u) * SL + 16 * b];
+#pragma unroll
+                        for (int a = 0; a < H; ++a)
+#pragma unroll
+                            for (int b = 0; b < H; ++b) g[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], g[a][b], 0, 0, 0);
+                    }
+            }
         }
     }
-    if constexpr (!OUTZ && QK == 2) {
-        const float tot = rot_block_sum(sq, red);
-        if (threadIdx.x == 0) lp[blockIdx.x] = tot;
-    }
-}
-
-// E2 = deq(Q2(Z2)) - Z2 in place; grid (column blocks, r).
-__global__ __launch_bounds__(ROT_TPB) void rot_qr_kernel(float* __restrict__ E2, const float* __restrict__ ax, int K, int r,
-                                                        int nparts, RotQ q, float* __restrict__ lp)
-{
-    __shared__ float red[4];
-    const int j = blockIdx.y;
-    float amax = 0.f;
-    for (int p = 0; p < nparts; ++p) amax = fmaxf(amax, ax[(size_t)p * r + j]);
-    float s, inv;
-    rot_scale(amax, q.top, s, inv);
-    const int k = blockIdx.x * ROT_TPB + threadIdx.x;
-    float sq = 0.f;
-    if (k < K) {
-        const float z = E2[(size_t)j * K + k];
-        const float e = q.kind == 0 ? rot_err<0>(z, s, inv, q.top) : rot_err<1>(z, s, inv, q.top);
-        E2[(size_t)j * K + k] = e;
-        sq = e * e;
-    }
-    const float tot = rot_block_sum(sq, red);
-    if (threadIdx.x == 0) lp[(size_t)j * gridDim.x + blockIdx.x] = tot;
-}
-
-// Partials of  c1 L^T E1 + c2 R E2^T  (r x r): workgroup w takes the 16-deep slices w, w + gridDim.x, ... of the
-// contraction over N, then of the one over K.  Thread (ty, tx) of 16 x 16 owns entries (ty + 16 a, tx + 16 b).
-template <int T>
-__global__ __launch_bounds__(ROT_TPB) void rot_grad_kernel(const float* __restrict__ L, const float* __restrict__ E1,
-                                                          const float* __restrict__ Rm, const float* __restrict__ E2, int N,
-                                                          int K, float c1, float c2, float* __restrict__ gp)
-{
-    constexpr int R = 16 * T;
-    __shared__ float As[16][R];
-    __shared__ float Bs[16][R];
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-    float acc[T][T];
+    if constexpr (MODE != ROT_OUT) {
+        if (maxima) {
 #pragma unroll
-    for (int a = 0; a < T; ++a)
-#pragma unroll
-        for (int b = 0; b < T; ++b) acc[a][b] = 0.f;
-    auto contract = [&]() {
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float av[T], bv[T];
-#pragma unroll
-            for (int a = 0; a < T; ++a) av[a] = As[kk][ty + 16 * a];
-#pragma unroll
-            for (int b = 0; b < T; ++b) bv[b] = Bs[kk][tx + 16 * b];
-#pragma unroll
-            for (int a = 0; a < T; ++a)
-#pragma unroll
-                for (int b = 0; b < T; ++b) acc[a][b] = __builtin_fmaf(av[a], bv[b], acc[a][b]);
+            for (int t = 0; t < T; ++t) {
+                float m = fmaxf(mx[t], __shfl_xor(mx[t], 16));
+                m = fmaxf(m, __shfl_xor(m, 32));
+                if (q == 0) red[wave * R + 16 * t + l15] = m;
+            }
+            __syncthreads();
+            if (tid < R) p.ax[(size_t)wg * R + tid] = fmaxf(fmaxf(red[tid], red[R + tid]), fmaxf(red[2 * R + tid], red[3 * R + tid]));
+            return;
         }
-    };
-    for (int n0 = blockIdx.x * 16; n0 < N; n0 += gridDim.x * 16) {  // rows n0 .. n0+15 of L and E1 (zero past N)
-        __syncthreads();
-        for (int e = tid; e < 16 * R; e += ROT_TPB) {
-            const int rr = e / R, i = e - rr * R;
-            const bool ok = n0 + rr < N;
-            As[rr][i] = ok ? L[(size_t)(n0 + rr) * R + i] : 0.f;
-            Bs[rr][i] = ok ? c1 * E1[(size_t)(n0 + rr) * R + i] : 0.f;
-        }
-        __syncthreads();
-        contract();
-    }
-    for (int k0 = blockIdx.x * 16; k0 < K; k0 += gridDim.x * 16) {  // columns k0 .. k0+15 of R and E2 (K is a multiple of 64)
-        __syncthreads();
-        for (int e = tid; e < 16 * R; e += ROT_TPB) {
-            const int i = e >> 4, kk = e & 15;
-            As[kk][i] = Rm[(size_t)i * K + k0 + kk];
-            Bs[kk][i] = c2 * E2[(size_t)i * K + k0 + kk];
-        }
-        __syncthreads();
-        contract();
-    }
-    float* o = gp + (size_t)blockIdx.x * R * R;
+        const int part = left ? wg : p.w.wL + wg;
+        const float c = left ? p.c1 : p.c2;
+        if (T > 1 || wave == 0) {
+            float* o = p.gp + (size_t)part * R * R + (16 * H * ha + 4 * q) * R + 16 * H * hb + l15;
 #pragma unroll
-    for (int a = 0; a < T; ++a)
+            for (int a = 0; a < H; ++a)
 #pragma unroll
-        for (int b = 0; b < T; ++b) o[(ty + 16 * a) * R + tx + 16 * b] = acc[a][b];
+                for (int b = 0; b < H; ++b)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[(16 * a + i) * R + 16 * b] = c * g[a][b][i];
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_down(sq, o);
+        __syncthreads();
+        if (lane == 0) red[wave] = sq;
+        __syncthreads();
+        if (tid == 0) p.lp[part] = (red[0] + red[1]) + (red[2] + red[3]);
+    }
 }
 
 struct RotStepParams {
     float* X;          // Omega
     float* M;          // momentum
     float* G;          // gradient of this step
-    const float* gp;   // its partials
-    const float* lp;   // partial sums of E1^2 (nlb) then of E2^2
-    float* tmp;        // ROT_TMP scratch matrices
+    const float* gp;   // its parts, [parts][r][r]
+    const float* lp;   // partial sums of E1^2 (wL) then of E2^2
     float* loss;       // may be null
-    int r, nlb, n_lp, nparts;
+    int r, wL, parts;
     float inv1, inv2;  // 1 / (N r), 1 / (r K)
     float lr, beta, eps, q, grad_scale;
     int s;
 };
 
-// The update, one workgroup of 1024 threads.  Three r x r work matrices and Omega; as many as fit sit in a 60 KB LDS pool
-// (all four up to rank 32, three at rank 64, one at rank 96), the rest in the state's scratch area in global memory:
-// the code addresses both through generic pointers.  Every phase reads what earlier phases wrote; __syncthreads orders
-// those accesses within the workgroup.
-// T = entries per thread and dimension in the r-deep products: thread (ty, tx) of 32 x 32 owns entries (ty + 32 a, tx + 32 b),
-// so one k step loads T + T operands for T * T multiply-adds (rank 16 and 32: T = 1, 64: 2, 96: 3, 128: 4).
-// ALL_LDS (rank <= 32): everything sits in the pool and the compiler sees plain LDS addresses.
-constexpr int ROT_POOL = 15360;  // floats
-template <int T, bool ALL_LDS>
-__global__ __launch_bounds__(1024) void rot_cayley_kernel(RotStepParams p)
+// G = grad_scale * (sum of the parts), 64 entries per workgroup, the parts dealt to its 4 wavefronts (all of a thread's loads
+// are independent); the last workgroup sums the loss.  A launch of its own: read by the single workgroup of the
+// update, the parts (1.8 MB at rank 64) would pass through one CU.
+__global__ __launch_bounds__(ROT_TPB) void rot_sum_kernel(RotStepParams p)
 {
-    __shared__ __attribute__((aligned(16))) float pool[ROT_POOL];
-    __shared__ double red[16];
-    __shared__ float bc;
-    const int r = p.r, rr = r * r, tid = threadIdx.x;
-    const int ty = tid >> 5, tx = tid & 31;
-    __builtin_assume(r % 16 == 0 && r >= 16);
-    // priority: W (read by every product of the second half), then the operands of the passes, then Omega
-    float *W, *T1, *T2, *Xl;
-    if constexpr (ALL_LDS) {
-        W = pool;
-        T1 = pool + rr;
-        T2 = pool + 2 * rr;
-        Xl = pool + 3 * rr;
-    } else {
-        const int fit = ROT_POOL / rr;
-        W = 0 < fit ? pool : p.tmp;
-        T1 = 1 < fit ? pool + rr : p.tmp + rr;
-        T2 = 2 < fit ? pool + 2 * rr : p.tmp + 2 * rr;
-        Xl = 3 < fit ? pool + 3 * rr : p.X;
-    }
-    // W: first beta M - G, then Wh, then W = Wh - Wh^T in place;  T1: A = (beta M - G) X^T, later Y;
-    // T2: X^T (for A), B = X^T A, later X + Y
-    auto block_sum = [&](double v) -> double {
+    __shared__ double red[4][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rr = p.r * p.r;
+    if (blockIdx.x == gridDim.x - 1) {
+        double a = 0.0, b = 0.0;
+        for (int i = tid; i < p.parts; i += ROT_TPB) (i < p.wL ? a : b) += (double)p.lp[i];
+        double v = a * (double)p.inv1 + b * (double)p.inv2;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
+        if (lane == 0) red[wave][0] = v;
         __syncthreads();
-        if ((tid & 63) == 0) red[tid >> 6] = v;
-        __syncthreads();
-        double t = 0.0;
-        for (int w = 0; w < 16; ++w) t += red[w];
-        return t;
-    };
-    // C(i, j) = sum_k A(i, k) B(k, j), each entry an fma chain over ascending k; out(i, j, value) stores it
-    auto product = [&](auto A, auto B, auto out) {
-        float acc[T][T];
+        if (tid == 0 && p.loss) *p.loss = (float)((red[0][0] + red[1][0]) + (red[2][0] + red[3][0]));
+        return;
+    }
+    const int e = blockIdx.x * 64 + lane;
+    double g = 0.0;
+#pragma unroll 16
+    for (int w = wave; w < p.parts; w += 4) g += (double)p.gp[(size_t)w * rr + e];
+    red[wave][lane] = g;
+    __syncthreads();
+    if (wave == 0) p.G[e] = (float)((double)p.grad_scale * ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])));
+}
+
+// The update, one workgroup.  Every r x r product runs on the fp32 matrix instruction: wavefront w owns NT neighbouring
+// 16 x 16 tiles of one row of tiles.  Its left operand W (a row of tiles of the skew-symmetric matrix) stays in registers
+// over all products that use it; Omega and the right operand sit in LDS.  The contraction index is dealt so that lane
+// (l15, q) takes k = 16 s + 4 q + u in step (s, u): a left operand is then one 16-byte read per s, and with row strides
+// of 4 modulo 16 floats all reads of either operand are free of bank conflicts.
+template <int R> constexpr int rot_nt() { return R == 128 ? 4 : R == 96 ? 3 : 1; }
+template <int R> constexpr int rot_cayley_threads() { return (R / 16) * (R / 16) / rot_nt<R>() * 64; }
+template <int R> constexpr int rot_cayley_lds() { return 2 * R * (R + 4) * 4; }
+template <int R>
+__global__ __launch_bounds__(rot_cayley_threads<R>()) void rot_cayley_kernel(RotStepParams p)
+{
+    constexpr int T = R / 16, NT = rot_nt<R>(), S = R + 4, NTHR = rot_cayley_threads<R>(), NWV = NTHR / 64;
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ double red[NWV];
+    float* Xs = lds;
+    float* Ts = lds + R * S;
+    const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rb = wave / (T / NT), cb = (wave % (T / NT)) * NT;  // row of tiles, first column of tiles
+    typedef v4f Left[T];
+    Left va;
 #pragma unroll
-        for (int a = 0; a < T; ++a)
+    for (int s = 0; s < T; ++s) {
+        const size_t o = (size_t)(16 * rb + l15) * R + 16 * s + 4 * q;
+        const v4f m = *(const v4f*)(p.M + o), g = *(const v4f*)(p.G + o);
 #pragma unroll
-            for (int b = 0; b < T; ++b) acc[a][b] = 0.f;
-        const bool live = ty < r && tx < r;  // (rank 16 leaves three quarters of the workgroup idle)
-        if (live) {
-#pragma unroll 8
-            for (int k = 0; k < r; ++k) {
-                float av[T], bv[T];
+        for (int u = 0; u < 4; ++u) va[s][u] = p.beta * m[u] - g[u];
+    }
+    for (int e = tid; e < R * R / 4; e += NTHR) {
+        const int row = e / (R / 4), c = e - row * (R / 4);
+        *(v4f*)(Xs + row * S + 4 * c) = *(const v4f*)(p.X + 4 * e);
+    }
+    __syncthreads();
+    auto product = [&](auto left, auto right, v4f (&acc)[NT]) {
 #pragma unroll
-                for (int a = 0; a < T; ++a) av[a] = A(ty + 32 * a, k);
+        for (int t = 0; t < NT; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int b = 0; b < T; ++b) bv[b] = B(k, tx + 32 * b);
+        for (int s = 0; s < T; ++s) {
+            const v4f a = left(s);
+            v4f b[NT];
 #pragma unroll
-                for (int a = 0; a < T; ++a)
+            for (int t = 0; t < NT; ++t) b[t] = right(s, t);
 #pragma unroll
-                    for (int b = 0; b < T; ++b) acc[a][b] = __builtin_fmaf(av[a], bv[b], acc[a][b]);
-            }
+            for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int a = 0; a < T; ++a)
-#pragma unroll
-                for (int b = 0; b < T; ++b) out(ty + 32 * a, tx + 32 * b, acc[a][b]);
+                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[t][u], acc[t], 0, 0, 0);
         }
     };
-    // loss (before the update) and gradient from their partials
-    {
-        double a = 0.0, b = 0.0;
-        for (int i = tid; i < p.nlb; i += 1024) a += (double)p.lp[i];
-        for (int i = p.nlb + tid; i < p.n_lp; i += 1024) b += (double)p.lp[i];
-        const double ta = block_sum(a), tb = block_sum(b);
-        if (tid == 0 && p.loss) *p.loss = (float)(ta * (double)p.inv1 + tb * (double)p.inv2);
-    }
-    for (int e = tid; e < rr; e += 1024) {
-        double g = 0.0;
-#pragma unroll 16
-        for (int w = 0; w < ROT_GRAD_WGS; ++w) g += (double)p.gp[(size_t)w * rr + e];  // 16 loads in flight at a time
-        const float gf = (float)((double)p.grad_scale * g);
-        p.G[e] = gf;
-        W[e] = p.beta * p.M[e] - gf;
-        const float x = p.X[e];
-        if (ALL_LDS || Xl != p.X) Xl[e] = x;
-        const int i = e / r, j = e - i * r;
-        T2[j * r + i] = x;  // X^T: the product below then reads rows, not columns (in LDS a column read is a 32-way bank conflict)
-    }
+    auto cols = [&](const float* m, int s, int j0) {  // entries (16 s + 4 q + u, j0 + l15)
+        v4f v;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = m[(16 * s + 4 * q + u) * S + j0 + l15];
+        return v;
+    };
+    auto rows = [&](const float* m, int s, int i0) { return *(const v4f*)(m + (i0 + l15) * S + 16 * s + 4 * q); };  // entries (i0 + l15, 16 s + 4 q + u)
+    auto put = [&](const v4f (&d)[NT]) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Ts[(16 * rb + 4 * q + i) * S + 16 * (cb + t) + l15] = d[t][i];
+    };
+    v4f A[NT], d[NT];
+    product([&](int s) { return va[s]; }, [&](int s, int t) { return rows(Xs, s, 16 * (cb + t)); }, A);      // A = (beta M - G) X^T
+    put(A);
     __syncthreads();
-    product([&](int i, int k) { return W[i * r + k]; }, [&](int k, int j) { return T2[k * r + j]; },
-            [&](int i, int j, float v) { T1[i * r + j] = v; });                       // A = (beta M - G) X^T
+    product([&](int s) { return cols(Xs, s, 16 * rb); }, [&](int s, int t) { return cols(Ts, s, 16 * (cb + t)); }, d);  // B = X^T A
     __syncthreads();
-    product([&](int i, int k) { return Xl[k * r + i]; }, [&](int k, int j) { return T1[k * r + j]; },
-            [&](int i, int j, float v) { T2[i * r + j] = v; });                       // B = X^T A
+    put(d);
     __syncthreads();
-    product([&](int i, int k) { return Xl[i * r + k]; }, [&](int k, int j) { return T2[k * r + j]; },
-            [&](int i, int j, float v) { W[i * r + j] = T1[i * r + j] - 0.5f * v; });  // Wh = A - 1/2 X B
+    product([&](int s) { return rows(Xs, s, 16 * rb); }, [&](int s, int t) { return cols(Ts, s, 16 * (cb + t)); }, d);  // X B
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d[t][i] = A[t][i] - 0.5f * d[t][i];                                      // Wh
+    __syncthreads();
+    put(d);
     __syncthreads();
     double n2 = 0.0;
-    for (int e = tid; e < rr; e += 1024) {  // W = Wh - Wh^T, each pair (i, j), (j, i) by the thread of its upper entry
-        const int i = e / r, j = e - i * r;
-        if (i > j) continue;
-        const float w = W[e] - W[j * r + i];
-        W[e] = w;
-        W[j * r + i] = -w;
-        if (i < j) n2 += 2.0 * (double)w * (double)w;
+#pragma unroll
+    for (int s = 0; s < T; ++s) {                                                                           // W = Wh - Wh^T
+        const v4f a = rows(Ts, s, 16 * rb), b = cols(Ts, s, 16 * rb);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            va[s][u] = a[u] - b[u];
+            n2 += (double)va[s][u] * (double)va[s][u];
+        }
     }
-    const double nrm2 = block_sum(n2);      // (its barriers also order W's stores before the reads below)
-    if (tid == 0) {
-        const float lim = 2.f * p.q / ((float)sqrt(nrm2) + p.eps);
-        bc = p.lr < lim ? p.lr : lim;
-    }
+    if (cb != 0) n2 = 0.0;  // the T / NT wavefronts of a row of tiles hold the same part of W
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n2 += __shfl_down(n2, o);
+    if (lane == 0) red[wave] = n2;
     __syncthreads();
-    const float alpha = bc;
-    product([&](int i, int k) { return W[i * r + k]; }, [&](int k, int j) { return Xl[k * r + j]; },
-            [&](int i, int j, float v) {                                               // M = W X;  Y = X + alpha M
-                p.M[i * r + j] = v;
-                T1[i * r + j] = __builtin_fmaf(alpha, v, Xl[i * r + j]);
-            });
-    for (int it = 0; it < p.s; ++it) {      // Y <- X + alpha/2 W (X + Y); Y is dead once X + Y is formed, so it is updated in place
+    double nrm2 = 0.0;
+    for (int w = 0; w < NWV; ++w) nrm2 += red[w];
+    const float lim = 2.f * p.q / ((float)sqrt(nrm2) + p.eps);
+    const float alpha = p.lr < lim ? p.lr : lim;
+    v4f x[NT], y[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[t][i] = Xs[(16 * rb + 4 * q + i) * S + 16 * (cb + t) + l15];
+    auto store = [&](float* dst, const v4f (&v)[NT]) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dst[(16 * rb + 4 * q + i) * R + 16 * (cb + t) + l15] = v[t][i];
+    };
+    product([&](int s) { return va[s]; }, [&](int s, int t) { return cols(Xs, s, 16 * (cb + t)); }, d);      // M = W X;  Y = X + alpha M
+    store(p.M, d);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[t][i] = __builtin_fmaf(alpha, d[t][i], x[t][i]);
+    for (int it = 0; it < p.s; ++it) {                                                                      // Y <- X + alpha/2 W (X + Y)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d[t][i] = x[t][i] + y[t][i];
         __syncthreads();
-        for (int e = tid; e < rr; e += 1024) T2[e] = Xl[e] + T1[e];
+        put(d);
         __syncthreads();
-        product([&](int i, int k) { return W[i * r + k]; }, [&](int k, int j) { return T2[k * r + j]; },
-                [&](int i, int j, float v) { T1[i * r + j] = __builtin_fmaf(0.5f * alpha, v, Xl[i * r + j]); });
+        product([&](int s) { return va[s]; }, [&](int s, int t) { return cols(Ts, s, 16 * (cb + t)); }, d);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[t][i] = __builtin_fmaf(0.5f * alpha, d[t][i], x[t][i]);
     }
-    __syncthreads();
-    for (int e = tid; e < rr; e += 1024) p.X[e] = T1[e];
+    store(p.X, y);
 }
 
 __global__ __launch_bounds__(ROT_TPB) void rot_init_kernel(float* X, float* M, const float* X0, const float* M0, int r)
@@ -555,51 +583,61 @@ static RotQ rot_q2(const Dims& d)
     return q;
 }
 
-template <int R, bool OUTZ>
-static void rot_launch_z(const Dims& d, const RotLayout& rl, const RotQ& q, const float* L, const float* Rm, const float* X,
-                         float* o1, float* o2, float* ax, float* lp, hipStream_t s)
+// Kernels whose LDS exceeds the 64 KB a launch may use without asking: asked once per device and kernel, so that later
+// calls (which a caller may capture in a graph) only launch.
+template <auto KERNEL>
+static void rot_ask_lds(int bytes)
 {
-    const size_t lds = (size_t)R * R * 4;
-    auto go = [&](auto qk) {
-        constexpr int BQ = decltype(qk)::value;
-        if constexpr (R == 128) {  // Omega alone fills the 64 KB a launch may use without asking for more
-            // once per device and kernel pair, so that later calls (which a caller may capture in a graph) only launch
-            static bool asked[64] = {false};
-            int dev = 0;
-            if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-            if (!asked[dev]) {
-                (void)hipFuncSetAttribute((const void*)rot_zl_kernel<R, OUTZ, BQ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                (void)hipFuncSetAttribute((const void*)rot_zr_kernel<R, OUTZ, BQ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                asked[dev] = true;
-            }
-        }
-        hipLaunchKernelGGL((rot_zl_kernel<R, OUTZ, BQ>), dim3(rl.nlb), dim3(ROT_TPB), lds, s, L, X, (int)d.N, q, o1, lp);
-        hipLaunchKernelGGL((rot_zr_kernel<R, OUTZ, BQ>), dim3(rl.nkb), dim3(ROT_TPB), lds, s, Rm, X, (int)d.K, q, o2, ax,
-                           lp ? lp + rl.nlb : nullptr);
-    };
-    // (the rotated factors themselves do not depend on Q2: one instantiation serves both)
-    if (OUTZ || q.kind == 0)
-        go(std::integral_constant<int, 0>{});
-    else if (q.kind == 1)
-        go(std::integral_constant<int, 1>{});
-    else if constexpr (R >= 32)
-        go(std::integral_constant<int, 2>{});
+    static bool asked[64] = {false};
+    if (bytes <= 65536) return;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+    if (asked[dev]) return;
+    (void)hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    asked[dev] = true;
 }
 
-template <bool OUTZ>
-static void rot_dispatch_z(const Dims& d, const RotLayout& rl, const RotQ& q, const float* L, const float* Rm, const float* X,
-                           float* o1, float* o2, float* ax, float* lp, hipStream_t s)
+template <int R, int MODE, int QK>
+static void rot_launch_z(const RotZParams& p, int grid, hipStream_t s)
 {
-    switch (d.r) {
-        case 16: rot_launch_z<16, OUTZ>(d, rl, q, L, Rm, X, o1, o2, ax, lp, s); break;
-        case 32: rot_launch_z<32, OUTZ>(d, rl, q, L, Rm, X, o1, o2, ax, lp, s); break;
-        case 64: rot_launch_z<64, OUTZ>(d, rl, q, L, Rm, X, o1, o2, ax, lp, s); break;
-        case 96: rot_launch_z<96, OUTZ>(d, rl, q, L, Rm, X, o1, o2, ax, lp, s); break;
-        default: rot_launch_z<128, OUTZ>(d, rl, q, L, Rm, X, o1, o2, ax, lp, s); break;
+    rot_ask_lds<rot_z_kernel<R, MODE, QK>>(rot_z_lds<R>());
+    hipLaunchKernelGGL((rot_z_kernel<R, MODE, QK>), dim3(grid), dim3(ROT_TPB), rot_z_lds<R>(), s, p);
+}
+
+template <int R>
+static void rot_launch_errors(const RotZParams& p, hipStream_t s)
+{
+    if (p.q.kind == 0) {
+        rot_launch_z<R, ROT_FIRST, 0>(p, p.w.wL + p.w.wM, s);
+        rot_launch_z<R, ROT_SECOND, 0>(p, p.w.wR, s);
+    } else if (p.q.kind == 1) {
+        rot_launch_z<R, ROT_FIRST, 1>(p, p.w.wL + p.w.wM, s);
+        rot_launch_z<R, ROT_SECOND, 1>(p, p.w.wR, s);
+    } else if constexpr (R >= 32) {
+        rot_launch_z<R, ROT_BOTH, 2>(p, p.w.wL + p.w.wR, s);
     }
 }
 
-// Partial results of a step (row maxima, loss and gradient partials, the update's work matrices) for callers that
+template <int R>
+static void rot_launch_cayley(const RotStepParams& p, hipStream_t s)
+{
+    rot_ask_lds<rot_cayley_kernel<R>>(rot_cayley_lds<R>());
+    hipLaunchKernelGGL((rot_cayley_kernel<R>), dim3(1), dim3(rot_cayley_threads<R>()), rot_cayley_lds<R>(), s, p);
+}
+
+template <typename F>
+static void rot_dispatch(int r, F f)
+{
+    switch (r) {
+        case 16: f(std::integral_constant<int, 16>{}); break;
+        case 32: f(std::integral_constant<int, 32>{}); break;
+        case 64: f(std::integral_constant<int, 64>{}); break;
+        case 96: f(std::integral_constant<int, 96>{}); break;
+        default: f(std::integral_constant<int, 128>{}); break;
+    }
+}
+
+// Partial results of a step (row maxima, loss and gradient partials) for callers that
 // cannot allocate: one array per device, held until the process ends.  Every element a step reads it has written before
 // in that same step, so nothing needs clearing between calls; two steps that overlap on one GPU would race on it.
 static __device__ __align__(256) uint8_t scratch[LQ_ROT_STATIC_SCRATCH_BYTES];
@@ -652,63 +690,69 @@ hipError_t launch_rot_step_static(const Dims& d, const float* L, const float* Rm
     return rot_step_launches(d, L, Rm, state, part, cs, loss, s);
 }
 
+static RotZParams rot_z_params(const Dims& d, const float* L, const float* Rm, const float* X, float* oL, float* oR)
+{
+    RotZParams p;
+    p.L = L;
+    p.R = Rm;
+    p.X = X;
+    p.N = (int)d.N;
+    p.K = (int)d.K;
+    p.w = rot_split(d);
+    p.q = rot_q2(d);
+    p.oL = oL;
+    p.oR = oR;
+    p.ax = p.lp = p.gp = nullptr;
+    p.c1 = (float)(-2.0 / ((double)d.N * d.r));
+    p.c2 = (float)(-2.0 / ((double)d.r * (double)d.K));
+    return p;
+}
+
 static hipError_t rot_step_launches(const Dims& d, const float* L, const float* Rm, uint8_t* state, uint8_t* part,
                                     const lq_cayley* cs, float* loss, hipStream_t s)
 {
     const RotLayout rl = rot_layout(d);
-    float* X = (float*)(state + rl.off_X);
-    float* E1 = (float*)(state + rl.off_E1);
-    float* E2 = (float*)(state + rl.off_E2);
-    float* ax = (float*)part;
-    float* lp = (float*)(part + (rl.off_lp - rl.off_ax));
-    float* gp = (float*)(part + (rl.off_gp - rl.off_ax));
-    const int N = (int)d.N, K = (int)d.K, r = d.r;
-    const RotQ q = rot_q2(d);
-    rot_dispatch_z<false>(d, rl, q, L, Rm, X, E1, E2, ax, lp, s);
-    if (q.kind <= 1)
-        hipLaunchKernelGGL(rot_qr_kernel, dim3(rl.nkb, r), dim3(ROT_TPB), 0, s, E2, ax, K, r, rl.nkb * 4, q, lp + rl.nlb);
-    const float c1 = (float)(-2.0 / ((double)N * r)), c2 = (float)(-2.0 / ((double)r * K));
-    switch (r >> 4) {
-        case 1: hipLaunchKernelGGL(rot_grad_kernel<1>, dim3(ROT_GRAD_WGS), dim3(ROT_TPB), 0, s, L, E1, Rm, E2, N, K, c1, c2, gp); break;
-        case 2: hipLaunchKernelGGL(rot_grad_kernel<2>, dim3(ROT_GRAD_WGS), dim3(ROT_TPB), 0, s, L, E1, Rm, E2, N, K, c1, c2, gp); break;
-        case 4: hipLaunchKernelGGL(rot_grad_kernel<4>, dim3(ROT_GRAD_WGS), dim3(ROT_TPB), 0, s, L, E1, Rm, E2, N, K, c1, c2, gp); break;
-        case 6: hipLaunchKernelGGL(rot_grad_kernel<6>, dim3(ROT_GRAD_WGS), dim3(ROT_TPB), 0, s, L, E1, Rm, E2, N, K, c1, c2, gp); break;
-        default: hipLaunchKernelGGL(rot_grad_kernel<8>, dim3(ROT_GRAD_WGS), dim3(ROT_TPB), 0, s, L, E1, Rm, E2, N, K, c1, c2, gp); break;
-    }
+    RotZParams z = rot_z_params(d, L, Rm, (float*)(state + rl.off_X), (float*)(state + rl.off_E1), (float*)(state + rl.off_E2));
+    z.ax = (float*)part;
+    z.lp = (float*)(part + (rl.off_lp - rl.off_ax));
+    z.gp = (float*)(part + (rl.off_gp - rl.off_ax));
     RotStepParams p;
-    p.X = X;
+    p.X = (float*)(state + rl.off_X);
     p.M = (float*)(state + rl.off_M);
     p.G = (float*)(state + rl.off_G);
-    p.gp = gp;
-    p.lp = lp;
-    p.tmp = (float*)(part + (rl.off_tmp - rl.off_ax));
+    p.gp = z.gp;
+    p.lp = z.lp;
     p.loss = loss;
-    p.r = r;
-    p.nlb = rl.nlb;
-    p.n_lp = q.kind <= 1 ? rl.n_lp : rl.nlb + rl.nkb;
-    p.nparts = ROT_GRAD_WGS;
-    p.inv1 = (float)(1.0 / ((double)N * r));
-    p.inv2 = (float)(1.0 / ((double)r * K));
+    p.r = d.r;
+    p.wL = z.w.wL;
+    p.parts = z.w.wL + z.w.wR;
+    p.inv1 = (float)(1.0 / ((double)d.N * d.r));
+    p.inv2 = (float)(1.0 / ((double)d.r * (double)d.K));
     p.lr = cs->lr;
     p.beta = cs->beta;
     p.eps = cs->eps;
     p.q = cs->q;
     p.grad_scale = cs->grad_scale;
     p.s = cs->s;
-    switch ((r + 31) >> 5) {
-        case 1: hipLaunchKernelGGL((rot_cayley_kernel<1, true>), dim3(1), dim3(1024), 0, s, p); break;
-        case 2: hipLaunchKernelGGL((rot_cayley_kernel<2, false>), dim3(1), dim3(1024), 0, s, p); break;
-        case 3: hipLaunchKernelGGL((rot_cayley_kernel<3, false>), dim3(1), dim3(1024), 0, s, p); break;
-        default: hipLaunchKernelGGL((rot_cayley_kernel<4, false>), dim3(1), dim3(1024), 0, s, p); break;
-    }
+    rot_dispatch(d.r, [&](auto rank) {
+        constexpr int R = decltype(rank)::value;
+        rot_launch_errors<R>(z, s);
+        hipLaunchKernelGGL(rot_sum_kernel, dim3(R * R / 64 + 1), dim3(ROT_TPB), 0, s, p);
+        rot_launch_cayley<R>(p, s);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_rot_apply(const Dims& d, const float* L, const float* Rm, const uint8_t* state, float* Lr, float* Rr,
                             hipStream_t s)
 {
-    const RotLayout rl = rot_layout(d);
-    rot_dispatch_z<true>(d, rl, rot_q2(d), L, Rm, (const float*)(state + rl.off_X), Lr, Rr, nullptr, nullptr, s);
+    const RotZParams p = rot_z_params(d, L, Rm, (const float*)(state + rot_layout(d).off_X), Lr, Rr);
+    // (the rotated factors do not depend on Q2 and leave no parts: every group has a workgroup of its own)
+    rot_dispatch(d.r, [&](auto rank) {
+        RotZParams z = p;
+        z.w.wL = z.w.gL;
+        rot_launch_z<decltype(rank)::value, ROT_OUT, 0>(z, z.w.gL + z.w.gR, s);
+    });
     return hipGetLastError();
 }
 
