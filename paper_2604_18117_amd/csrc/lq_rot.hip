@@ -7,9 +7,9 @@
 //     G = -2/(N r) L^T E1 - 2/(r K) R E2^T
 // and the update is the Cayley SGD with momentum of the work the paper cites for it (Li et al. 2020, Algorithm 1).
 // Four launches per step (three with block-scaled Q2), no atomics, every sum in a fixed order:
-//   rot_z_kernel      64 rows of L (or columns of R) per workgroup turn: Z1 / Z2 on the fp32 matrix instruction, E1 / E2,
-//                     their part of G, partial sums of squares.  A row of Z2 runs over all of K, so with one scale per row
-//                     the first launch only leaves the row maxima of Z2 and a second, small one forms E2 and its part of G
+//   rot_z_kernel      128 rows of L (or columns of R) per workgroup turn (64 at ranks 96 and 128): Z1 / Z2 on the fp32
+//                     matrix instruction, E1 / E2, their part of G, partial sums of squares.  A row of Z2 runs over all of
+//                     K, so with one scale per row a small launch before it leaves the row maxima of Z2
 //   rot_sum_kernel    G from the workgroups' parts (fp64), the loss
 //   rot_cayley_kernel one workgroup: momentum, the skew-symmetric W, step length, the fixed-point passes
 //
@@ -29,25 +29,26 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int ROT_TPB = 256;
 
-// How the 64-row groups of L and the 64-column groups of R are dealt to workgroups.  Every workgroup leaves one r x r part
-// of the gradient, so their number is capped: at rank 64 by what LQ_ROT_STATIC_SCRATCH_BYTES holds, at the others by
-// the traffic of rot_sum_kernel (128 parts of rank 128 are 8 MB).
+// How groups of rows of L and of columns of R are dealt to workgroups.  Every workgroup leaves one r x r part of the
+// gradient, so their number is capped: at rank 64 by what LQ_ROT_STATIC_SCRATCH_BYTES holds, at the others by the traffic of
+// rot_sum_kernel (128 parts of rank 128 are 8 MB).  Up to rank 64 a group is 128 rows, 8 wavefronts: two wavefronts
+// per SIMD hide each other's LDS and barrier waits; Omega and two groups of 128 rows do not fit the LDS at ranks 96 and 128.
 struct RotSplit {
     int gL, gR;   // groups
     int wL, wR;   // workgroups that form E1 and E2
-    int wM;       // workgroups that leave row maxima of Z2 (row kinds)
+    int wM;       // workgroups that leave row maxima of Z2 (row kinds), 64 columns a turn
 };
 static RotSplit rot_split(const Dims& d)
 {
-    const int cap = d.r <= 32 ? 256 : d.r == 64 ? 112 : 128;
+    const int cap = d.r <= 32 ? 256 : d.r == 64 ? 112 : 128, rows = d.r <= 64 ? 128 : 64;
     RotSplit w;
-    w.gL = (int)(d.N / 64);
-    w.gR = (int)(d.K / 64);
+    w.gL = (int)((d.N + rows - 1) / rows);
+    w.gR = (int)((d.K + rows - 1) / rows);
     const int per = (w.gL + w.gR + cap - 1) / cap;
     w.wL = (w.gL + per - 1) / per;
     w.wR = w.gR < cap - w.wL ? w.gR : cap - w.wL;
     if (w.wR < 1) w.wR = 1;
-    w.wM = w.gR < 256 ? w.gR : 256;
+    w.wM = (int)(d.K / 64) < 256 ? (int)(d.K / 64) : 256;
     return w;
 }
 
@@ -160,48 +161,47 @@ struct RotZParams {
     float c1, c2;
 };
 
-// ROT_OUT: write Z1 and Z2.  ROT_FIRST (row kinds): E1 and its part of G; row maxima of Z2.  ROT_SECOND: E2 and its part
-// of G.  ROT_BOTH (block kinds): E1, E2 and their parts of G.
-enum { ROT_OUT, ROT_FIRST, ROT_SECOND, ROT_BOTH };
+// ROT_OUT: write Z1 and Z2.  ROT_MAX (row kinds): row maxima of Z2.  ROT_ERR: E1, E2 and their parts of G.
+enum { ROT_OUT, ROT_MAX, ROT_ERR };
 
 // LDS strides in floats, chosen for conflict-free operand reads: lane (l15, q) reads Omega[4 s + q][l15], so q has to move
 // by 16 banks; it reads row l15, column 4 s + q of the staged factor and, in the second contraction, row 16 s + 4 q + u,
 // column l15 of the factor and the error: a stride of 4 modulo 16 serves both.
 template <int R> constexpr int rot_sx() { return R % 32 ? R : R + 16; }
 template <int R> constexpr int rot_sl() { return R + 4; }
-template <int R> constexpr int rot_z_lds() { return (R * rot_sx<R>() + 2 * 64 * rot_sl<R>() + 6 * R) * 4; }
+template <int R, int NWV> constexpr int rot_z_lds() { return (R * rot_sx<R>() + 2 * 16 * NWV * rot_sl<R>() + (NWV + 2) * R) * 4; }
 
-// A workgroup turn is a group of 64 rows of L (columns of R, transposed on the way into LDS): each of the 4 wavefronts
-// forms 16 rows of Z (R / 16 tiles of 16 x 16: lane (l15, q) holds rows 4 q + i, column l15), quantises them in registers,
-// and leaves the error in LDS, from where each wavefront contracts one quadrant of G over the 64 rows; the quadrant stays in
-// registers over all turns.
+// A workgroup turn is a group of 16 * NWV rows of L (columns of R, transposed on the way into LDS): each wavefront forms 16
+// rows of Z (R / 16 tiles of 16 x 16: lane (l15, q) holds rows 4 q + i, column l15), quantises them in registers, and
+// leaves the error in LDS, from where each of 4 wavefronts contracts one quadrant of G over their 64 rows; the quadrant
+// stays in registers over all turns, and 8 wavefronts add their two halves at the end.
 // QK: 0 integer rows, 1 FP8 rows (one scale per row), 2 block kinds.
-template <int R, int MODE, int QK>
-__global__ __launch_bounds__(ROT_TPB) void rot_z_kernel(RotZParams p)
+template <int R, int MODE, int QK, int NWV>
+__global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
 {
     constexpr int T = R / 16, H = T > 1 ? T / 2 : 1, SX = rot_sx<R>(), SL = rot_sl<R>();
+    constexpr int NTHR = 64 * NWV, ROWS = 16 * NWV;
     extern __shared__ __attribute__((aligned(16))) float lds[];
     float* Xs = lds;                 // Omega
     float* Ls = Xs + R * SX;         // the group's rows of L / columns of R
-    float* Es = Ls + 64 * SL;        // their errors
-    float* red = Es + 64 * SL;       // [4][R] column maxima per wavefront; then scale[R], 1 / scale[R] of the rows of Z2
-    float* sc = red + 4 * R;
+    float* Es = Ls + ROWS * SL;      // their errors
+    float* red = Es + ROWS * SL;     // [NWV][R] column maxima per wavefront
+    float* sc = red + NWV * R;       // scale[R], 1 / scale[R] of the rows of Z2
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nL = MODE == ROT_SECOND ? 0 : p.w.wL;
+    const int nL = MODE == ROT_MAX ? 0 : p.w.wL;
     const bool left = (int)blockIdx.x < nL;
     const int wg = left ? blockIdx.x : blockIdx.x - nL;
-    const int nwg = left ? p.w.wL : (int)gridDim.x - nL;
-    const int ngroups = left ? p.w.gL : p.w.gR;
-    const bool maxima = MODE == ROT_FIRST && !left;  // only the row maxima of Z2 are wanted
+    const int nwg = left ? nL : (int)gridDim.x - nL;
+    const int nrows = left ? p.N : p.K;
     const int K = p.K;
 
-    for (int e = tid; e < R * R / 4; e += ROT_TPB) {
+    for (int e = tid; e < R * R / 4; e += NTHR) {
         const int row = e / (R / 4), c = e - row * (R / 4);
         *(v4f*)(Xs + row * SX + 4 * c) = *(const v4f*)(p.X + 4 * e);
     }
-    if constexpr (MODE == ROT_SECOND) {  // scales of the rows of Z2
-        constexpr int SLICES = ROT_TPB / R < 4 ? ROT_TPB / R : 4;
+    if (MODE == ROT_ERR && QK != 2 && !left) {  // scales of the rows of Z2
+        constexpr int SLICES = NTHR / R < NWV ? NTHR / R : NWV;
         const int sl = tid / R, j = tid - sl * R;
         if (sl < SLICES) {
             float m = 0.f;
@@ -228,23 +228,27 @@ __global__ __launch_bounds__(ROT_TPB) void rot_z_kernel(RotZParams p)
 #pragma unroll
     for (int t = 0; t < T; ++t) mx[t] = 0.f;
     float sq = 0.f;
-    const int ha = wave >> 1, hb = wave & 1;
+    const int ha = (wave >> 1) & 1, hb = wave & 1, hg = wave >> 2;  // quadrant of G, half of the group it is contracted over
 
-    for (int grp = wg; grp < ngroups; grp += nwg) {
+    for (int row0 = wg * ROWS; row0 < nrows; row0 += nwg * ROWS) {
+        // the last group of 128 may be half (N and K are multiples of 64): the upper wavefronts then work on
+        // zeros and store nothing
+        const bool live = NWV == 4 || row0 + 64 * hg < nrows;
         __syncthreads();  // the previous turn's contraction has read Ls and Es
         if (left) {
-            const float* src = p.L + (size_t)grp * 64 * R;
+            const float* src = p.L + (size_t)row0 * R;
+            const int n = (nrows - row0) * (R / 4);
 #pragma unroll
-            for (int e = 0; e < 64 * R / 4 / ROT_TPB; ++e) {
-                const int f = tid + e * ROT_TPB, row = f / (R / 4), c = f - row * (R / 4);
-                *(v4f*)(Ls + row * SL + 4 * c) = *(const v4f*)(src + 4 * f);
+            for (int e = 0; e < ROWS * R / 4 / NTHR; ++e) {
+                const int f = tid + e * NTHR, row = f / (R / 4), c = f - row * (R / 4);
+                *(v4f*)(Ls + row * SL + 4 * c) = f < n ? *(const v4f*)(src + 4 * f) : v4f{0.f, 0.f, 0.f, 0.f};
             }
         } else {
-            const float* src = p.R + (size_t)grp * 64;
+            const float* src = p.R + row0;
 #pragma unroll
-            for (int e = 0; e < 64 * R / 4 / ROT_TPB; ++e) {
-                const int f = tid + e * ROT_TPB, i = f >> 4, c = f & 15;
-                const v4f v = *(const v4f*)(src + (size_t)i * K + 4 * c);
+            for (int e = 0; e < ROWS * R / 4 / NTHR; ++e) {
+                const int f = tid + e * NTHR, i = f / (ROWS / 4), c = f & (ROWS / 4 - 1);
+                const v4f v = row0 + 4 * c < nrows ? *(const v4f*)(src + (size_t)i * K + 4 * c) : v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int u = 0; u < 4; ++u) Ls[(4 * c + u) * SL + i] = v[u];
             }
@@ -263,17 +267,15 @@ __global__ __launch_bounds__(ROT_TPB) void rot_z_kernel(RotZParams p)
                 for (int t = 0; t < T; ++t) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bp[4 * s * SX + 16 * t], z[t], 0, 0, 0);
             }
         }
-        float* dl = p.oL + (size_t)(grp * 64 + 16 * wave + 4 * q) * R + l15;  // row 4 q + i, column 16 t + l15
-        float* dr = p.oR + (size_t)l15 * K + grp * 64 + 16 * wave + 4 * q;    // row 16 t + l15, columns 4 q ..
-        if constexpr (MODE != ROT_OUT) {
-            if (maxima) {
+        float* dl = p.oL + (size_t)(row0 + 16 * wave + 4 * q) * R + l15;  // row 4 q + i, column 16 t + l15
+        float* dr = p.oR + (size_t)l15 * K + row0 + 16 * wave + 4 * q;    // row 16 t + l15, columns 4 q ..
+        if constexpr (MODE == ROT_MAX) {
 #pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    float m = fmaxf(fmaxf(fabsf(z[t][0]), fabsf(z[t][1])), fmaxf(fabsf(z[t][2]), fabsf(z[t][3])));
-                    mx[t] = fmaxf(mx[t], m);
-                }
-                continue;
-            }
+            for (int t = 0; t < T; ++t)
+                mx[t] = fmaxf(mx[t], fmaxf(fmaxf(fabsf(z[t][0]), fabsf(z[t][1])), fmaxf(fabsf(z[t][2]), fabsf(z[t][3]))));
+            continue;
+        }
+        if constexpr (MODE == ROT_ERR) {
             if (left) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -319,14 +321,15 @@ __global__ __launch_bounds__(ROT_TPB) void rot_z_kernel(RotZParams p)
         }
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            if (left) {
+            if (!live) {
+            } else if (left) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) dl[i * R + 16 * t] = z[t][i];
             } else {
                 *(v4f*)(dr + (size_t)16 * t * K) = z[t];
             }
         }
-        if constexpr (MODE != ROT_OUT) {
+        if constexpr (MODE == ROT_ERR) {
 #pragma unroll
             for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -335,9 +338,9 @@ __global__ __launch_bounds__(ROT_TPB) void rot_z_kernel(RotZParams p)
                     Es[(16 * wave + 4 * q + i) * SL + 16 * t + l15] = z[t][i];
                 }
             __syncthreads();
-            if (T > 1 || wave == 0) {
-                const float* ap = Ls + 4 * q * SL + 16 * H * ha + l15;
-                const float* bp = Es + 4 * q * SL + 16 * H * hb + l15;
+            if (T > 1 || (wave & 3) == 0) {
+                const float* ap = Ls + (64 * hg + 4 * q) * SL + 16 * H * ha + l15;
+                const float* bp = Es + (64 * hg + 4 * q) * SL + 16 * H * hb + l15;
 #pragma unroll 2
                 for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -355,35 +358,48 @@ __global__ __launch_bounds__(ROT_TPB) void rot_z_kernel(RotZParams p)
             }
         }
     }
-    if constexpr (MODE != ROT_OUT) {
-        if (maxima) {
+    if constexpr (MODE == ROT_MAX) {
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                float m = fmaxf(mx[t], __shfl_xor(mx[t], 16));
-                m = fmaxf(m, __shfl_xor(m, 32));
-                if (q == 0) red[wave * R + 16 * t + l15] = m;
-            }
-            __syncthreads();
-            if (tid < R) p.ax[(size_t)wg * R + tid] = fmaxf(fmaxf(red[tid], red[R + tid]), fmaxf(red[2 * R + tid], red[3 * R + tid]));
-            return;
+        for (int t = 0; t < T; ++t) {
+            float m = fmaxf(mx[t], __shfl_xor(mx[t], 16));
+            m = fmaxf(m, __shfl_xor(m, 32));
+            if (q == 0) red[wave * R + 16 * t + l15] = m;
         }
+        __syncthreads();
+        if (tid < R) p.ax[(size_t)wg * R + tid] = fmaxf(fmaxf(red[tid], red[R + tid]), fmaxf(red[2 * R + tid], red[3 * R + tid]));
+    }
+    if constexpr (MODE == ROT_ERR) {
         const int part = left ? wg : p.w.wL + wg;
         const float c = left ? p.c1 : p.c2;
-        if (T > 1 || wave == 0) {
-            float* o = p.gp + (size_t)part * R * R + (16 * H * ha + 4 * q) * R + 16 * H * hb + l15;
-#pragma unroll
-            for (int a = 0; a < H; ++a)
-#pragma unroll
-                for (int b = 0; b < H; ++b)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) o[(16 * a + i) * R + 16 * b] = c * g[a][b][i];
-        }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) sq += __shfl_down(sq, o);
         __syncthreads();
         if (lane == 0) red[wave] = sq;
+        const bool owner = T > 1 || (wave & 3) == 0;
+        v4f* other = (v4f*)Es + (wave & 3) * H * H * 64 + lane;
+        if (NWV == 8 && hg == 1 && owner) {
+#pragma unroll
+            for (int a = 0; a < H; ++a)
+#pragma unroll
+                for (int b = 0; b < H; ++b) other[(a * H + b) * 64] = g[a][b];
+        }
         __syncthreads();
-        if (tid == 0) p.lp[part] = (red[0] + red[1]) + (red[2] + red[3]);
+        if (hg == 0 && owner) {
+            float* o = p.gp + (size_t)part * R * R + (16 * H * ha + 4 * q) * R + 16 * H * hb + l15;
+#pragma unroll
+            for (int a = 0; a < H; ++a)
+#pragma unroll
+                for (int b = 0; b < H; ++b) {
+                    if constexpr (NWV == 8) g[a][b] += other[(a * H + b) * 64];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[(16 * a + i) * R + 16 * b] = c * g[a][b][i];
+                }
+        }
+        if (tid == 0) {
+            float v = 0.f;
+            for (int w = 0; w < NWV; ++w) v += red[w];
+            p.lp[part] = v;
+        }
     }
 }
 
@@ -597,25 +613,25 @@ static void rot_ask_lds(int bytes)
     asked[dev] = true;
 }
 
-template <int R, int MODE, int QK>
+template <int R, int MODE, int QK, int NWV>
 static void rot_launch_z(const RotZParams& p, int grid, hipStream_t s)
 {
-    rot_ask_lds<rot_z_kernel<R, MODE, QK>>(rot_z_lds<R>());
-    hipLaunchKernelGGL((rot_z_kernel<R, MODE, QK>), dim3(grid), dim3(ROT_TPB), rot_z_lds<R>(), s, p);
+    constexpr int lds = rot_z_lds<R, NWV>();
+    rot_ask_lds<rot_z_kernel<R, MODE, QK, NWV>>(lds);
+    hipLaunchKernelGGL((rot_z_kernel<R, MODE, QK, NWV>), dim3(grid), dim3(64 * NWV), lds, s, p);
 }
 
 template <int R>
 static void rot_launch_errors(const RotZParams& p, hipStream_t s)
 {
-    if (p.q.kind == 0) {
-        rot_launch_z<R, ROT_FIRST, 0>(p, p.w.wL + p.w.wM, s);
-        rot_launch_z<R, ROT_SECOND, 0>(p, p.w.wR, s);
-    } else if (p.q.kind == 1) {
-        rot_launch_z<R, ROT_FIRST, 1>(p, p.w.wL + p.w.wM, s);
-        rot_launch_z<R, ROT_SECOND, 1>(p, p.w.wR, s);
-    } else if constexpr (R >= 32) {
-        rot_launch_z<R, ROT_BOTH, 2>(p, p.w.wL + p.w.wR, s);
-    }
+    constexpr int NWV = R <= 64 ? 8 : 4;  // (rot_split's group)
+    if (p.q.kind <= 1) rot_launch_z<R, ROT_MAX, 0, 4>(p, p.w.wM, s);
+    if (p.q.kind == 0)
+        rot_launch_z<R, ROT_ERR, 0, NWV>(p, p.w.wL + p.w.wR, s);
+    else if (p.q.kind == 1)
+        rot_launch_z<R, ROT_ERR, 1, NWV>(p, p.w.wL + p.w.wR, s);
+    else if constexpr (R >= 32)
+        rot_launch_z<R, ROT_ERR, 2, NWV>(p, p.w.wL + p.w.wR, s);
 }
 
 template <int R>
@@ -747,11 +763,12 @@ hipError_t launch_rot_apply(const Dims& d, const float* L, const float* Rm, cons
                             hipStream_t s)
 {
     const RotZParams p = rot_z_params(d, L, Rm, (const float*)(state + rot_layout(d).off_X), Lr, Rr);
-    // (the rotated factors do not depend on Q2 and leave no parts: every group has a workgroup of its own)
+    // (the rotated factors do not depend on Q2 and leave no parts: every group of 64 has a workgroup of its own)
     rot_dispatch(d.r, [&](auto rank) {
         RotZParams z = p;
-        z.w.wL = z.w.gL;
-        rot_launch_z<decltype(rank)::value, ROT_OUT, 0>(z, z.w.gL + z.w.gR, s);
+        z.w.gL = z.w.wL = (int)(d.N / 64);
+        z.w.gR = (int)(d.K / 64);
+        rot_launch_z<decltype(rank)::value, ROT_OUT, 0, 4>(z, z.w.gL + z.w.gR, s);
     });
     return hipGetLastError();
 }
