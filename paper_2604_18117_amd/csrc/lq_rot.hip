@@ -205,8 +205,13 @@ __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
         const int sl = tid / R, j = tid - sl * R;
         if (sl < SLICES) {
             float m = 0.f;
-#pragma unroll 8
-            for (int i = sl; i < p.w.wM; i += SLICES) m = fmaxf(m, p.ax[(size_t)i * R + j]);
+            for (int i = sl; i < p.w.wM; i += 8 * SLICES) {  // (a maximum may see the last set more than once)
+                float f[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) f[k] = p.ax[(size_t)(i + k * SLICES < p.w.wM ? i + k * SLICES : p.w.wM - 1) * R + j];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) m = fmaxf(m, f[k]);
+            }
             red[sl * R + j] = m;
         }
         __syncthreads();
@@ -436,8 +441,13 @@ __global__ __launch_bounds__(ROT_TPB) void rot_sum_kernel(RotStepParams p)
     }
     const int e = blockIdx.x * 64 + lane;
     double g = 0.0;
-#pragma unroll 16
-    for (int w = wave; w < p.parts; w += 4) g += (double)p.gp[(size_t)w * rr + e];
+    for (int w = wave; w < p.parts; w += 64) {  // 16 loads in flight; a part past the last is the last one again, not added
+        float f[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) f[k] = p.gp[(size_t)(w + 4 * k < p.parts ? w + 4 * k : p.parts - 1) * rr + e];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) g += w + 4 * k < p.parts ? (double)f[k] : 0.0;
+    }
     red[wave][lane] = g;
     __syncthreads();
     if (wave == 0) p.G[e] = (float)((double)p.grad_scale * ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])));
