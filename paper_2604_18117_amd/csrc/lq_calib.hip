@@ -1,33 +1,41 @@
 // Data-free calibration of the low-rank factors (Section 3.2, Eq. 4; gradients of App. B.2): one Adam step on
 //     loss(L, R) = mean ( Q1(W + L R) - W - L R )^2
 // for the main quantiser Q1 of the configuration: INT4 in groups of 64 | 128 along K with fp32 scales, SINT4 blocks with
-// FP16 scales, MXFP4 or MXINT4 (blocks of 32, E8M0 scale).  Four launches per step:
-//   calib_err_kernel   V = W + L R (fp32 FMA chain over ascending j), E = deq(Q1(V)) - V, partial sums of E^2
-//   calib_grad_l_kernel  grad_L = -2/(N K) E R^T      (fp32 MFMA, contraction split over the wavefronts of a workgroup)
-//   calib_grad_r_kernel  partials of L^T E over row ranges
-//   calib_adam_kernel    grad_R = -2/(N K) * (sum of the partials), Adam update of L and R, loss = sum of its partials / (N K)
+// FP16 scales, MXFP4 or MXINT4 (blocks of 32, E8M0 scale).  Two launches per step:
+//   calib_err_kernel   V = W + L R (fp32 FMA chain over ascending j), E = deq(Q1(V)) - V, partial sums of E^2, and the
+//                      tile's parts of grad_L = -2/(N K) E R^T and grad_R = -2/(N K) L^T E while E is in the LDS
+//   calib_adam_kernel  sums the parts, Adam update of L and R, loss = sum of its partials / (N K)
 // No atomics: every sum has a fixed order, so a step is reproducible bit for bit.
+#include <utility>
+
 #include "lq_internal.h"
 
 namespace lq {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// column groups a wavefront of calib_err_kernel owns one of: the INT scale groups, or 64-chunks (two MX blocks)
-static int calib_groups(const Dims& d) { return (d.mx || d.mxi) ? d.C64 : d.G; }
-
-// Row ranges the contraction of grad_R = L^T E is split into (each range a multiple of 16 rows): enough workgroups
-// (K / 32 per range) to fill the device, at most 16 ranges.
-static int calib_splits(const Dims& d)
+// A workgroup owns 128 columns of W and a run of row blocks of 64 rows (128 at rank 64, whose LDS image leaves no room for a
+// second workgroup per CU: 8 wavefronts instead of 4).  Each leaves one r x 128 part of grad_R for its run and one
+// 64 x r part of grad_L per row block and column block.  The runs are as long as they can be with every workgroup slot
+// of the device still taken (two per CU up to rank 32), so that grad_R has few parts.
+constexpr int CALIB_COLS = 128;
+static constexpr int calib_waves(int r) { return r == 64 ? 8 : 4; }
+struct CalibSplit {
+    int cblocks;    // column blocks = parts of grad_L
+    int rblocks;    // row blocks
+    int splits;     // runs of row blocks = parts of grad_R
+    int per;        // row blocks per run
+};
+static CalibSplit calib_split(const Dims& d)
 {
-    const int blocks = (int)(d.N / 16), per = (int)(d.K / 32);
-    int best = 1;
-    for (int s = 1; s <= 16; ++s) {
-        if (blocks % s) continue;
-        best = s;
-        if (s * per >= 256) break;
-    }
-    return best;
+    CalibSplit c;
+    const int rows = 16 * calib_waves(d.r), slots = d.r <= 32 ? 512 : 256;
+    c.cblocks = (int)((d.K + CALIB_COLS - 1) / CALIB_COLS);
+    c.rblocks = (int)((d.N + rows - 1) / rows);
+    const int want = slots > c.cblocks ? slots / c.cblocks : 1;
+    c.per = (c.rblocks + want - 1) / want;
+    c.splits = (c.rblocks + c.per - 1) / c.per;
+    return c;
 }
 
 CalibLayout calib_layout(const Dims& d)
@@ -44,35 +52,33 @@ CalibLayout calib_layout(const Dims& d)
     cl.off_gL = o; o = align256(o + nl);
     cl.off_gR = o; o = align256(o + nr);
     cl.off_E = o;  o = align256(o + (size_t)d.N * d.K * 4);
-    cl.n_lp = (int)(d.N / 16) * ((calib_groups(d) + 3) / 4) * 4;  // one partial per wavefront of calib_err_kernel
+    const CalibSplit c = calib_split(d);
+    cl.n_lp = c.cblocks * c.splits;  // one partial per workgroup of calib_err_kernel
     cl.off_lp = o; o = align256(o + (size_t)cl.n_lp * 4);
-    cl.off_gRp = o; o = align256(o + (size_t)calib_splits(d) * nr);
+    cl.off_gLp = o; o = align256(o + (size_t)c.cblocks * nl);
+    cl.off_gRp = o; o = align256(o + (size_t)c.splits * nr);
     cl.total = o;
     return cl;
 }
 
-// Maximum over the 64 lanes, returned in every lane: four cross-lane steps inside each row of 16 lanes on the
-// vector ALU's data-parallel-primitive path (no LDS traffic), then the four row results through scalar registers.
+// Maximum over a row of 16 lanes, in each of them, on the vector ALU's data-parallel-primitive path (no LDS traffic).
 template <int CTRL>
 __device__ __forceinline__ float dpp_max(float v)
 {
-    const int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false);
-    return fmaxf(v, __int_as_float(o));
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true)));
 }
-// HALF = false: maximum over the wavefront; HALF = true: over the lane's half (lanes 0..31 | 32..63 = one MX block)
-template <bool HALF>
-__device__ __forceinline__ float wave_max_f(float v, int lane)
+__device__ __forceinline__ float row16_max(float v)
 {
-    v = dpp_max<0xB1>(v);   // quad_perm [1,0,3,2]
-    v = dpp_max<0x4E>(v);   // quad_perm [2,3,0,1]
-    v = dpp_max<0x141>(v);  // row_half_mirror
-    v = dpp_max<0x140>(v);  // row_mirror
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    if constexpr (HALF) return lane < 32 ? fmaxf(r0, r1) : fmaxf(r2, r3);
-    return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
+    v = dpp_max<0xB1>(v);       // quad_perm [1,0,3,2]
+    v = dpp_max<0x4E>(v);       // quad_perm [2,3,0,1]
+    v = dpp_max<0x141>(v);      // row_half_mirror
+    return dpp_max<0x140>(v);   // row_mirror
+}
+// The value lane N of each row of 16 lanes holds, in all 16.
+template <int N>
+__device__ __forceinline__ float row16_lane(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xF, 0xF, true));  // row_newbcast
 }
 
 // MX block scales and elements (App. A.3), the arithmetic of the MX pack kernels:
@@ -103,80 +109,158 @@ __device__ __forceinline__ float wave_sum_f(float v)
     return v;
 }
 
-// A workgroup owns 16 rows of W and four consecutive K groups, one per wavefront; lane = column within a 64-chunk.
-// The 16 x r block of L sits in LDS (uniform-address reads broadcast), the r values of R for the lane's column(s)
-// stream through registers four rows of R at a time.  Many small workgroups: the loop is a chain of L2 round
-// trips, hidden by occupancy.
-// Q: 0 INT4 groups of 64 * GC (fp32 scale), 1 SINT4 blocks, 2 MXFP4, 3 MXINT4 (1..3: GC = 1; 2, 3: two blocks of 32 per wavefront).
-template <int GC, int Q>
-__global__ __launch_bounds__(256) void calib_err_kernel(const float* W, const float* L, const float* R, float* E, float* lp,
-                                                        int N, int K, int r)
+// f(0), f(1), ... with the argument as a compile-time constant
+template <typename F, int... k>
+__device__ __forceinline__ void for_constants(F f, std::integer_sequence<int, k...>)
 {
-    extern __shared__ __attribute__((aligned(16))) float sL[];  // [16][r]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int G = K / (64 * GC), GQ = (G + 3) / 4;
-    const int n0 = (blockIdx.x / GQ) * 16;
-    for (int i = tid * 4; i < 16 * r; i += 256 * 4) *(v4f*)&sL[i] = *(const v4f*)&L[(size_t)n0 * r + i];
-    __syncthreads();
+    (f(std::integral_constant<int, k>{}), ...);
+}
+
+struct CalibParams {
+    const float *W, *L, *R;
+    float* E;
+    float* lp;
+    float *gLp, *gRp;
+    int N, K;
+    CalibSplit c;
+};
+
+// LDS images.  L and E, row strides of 4 modulo 16 floats: the 16-byte operand reads (row l15, four columns at 4 q) and the
+// reads of a column over rows 16 s + 4 q + u are free of bank conflicts.  R is read over rows 4 s + q as well: rows of
+// 128 floats, the column's bits 4..5 exchanged by the row's bits 0..1 and bits 2..3 by the row's bits 2..3.
+__device__ __forceinline__ int calib_rs(int row, int col) { return row * CALIB_COLS + (col ^ (16 * (row & 3)) ^ (row & 12)); }
+template <int R> constexpr int calib_lds() { return (16 * calib_waves(R) * (R + 4 + CALIB_COLS + 4) + R * CALIB_COLS) * 4; }
+
+// All three products on v_mfma_f32_16x16x4_f32 (lane (l15, q) holds rows 4 q + i, column l15 of a 16 x 16 result tile).
+// The instruction is, bit for bit, four fused multiply-adds in ascending order of its contraction index, so V = W + L R with
+// W as the initial accumulator is exactly the chain that defines V.  Each wavefront owns 16 rows x 128 columns of
+// the tile for V, the quantiser (row maxima by lane exchange inside 16 lanes) and grad_L, and 128 / NWV columns of all the
+// block's rows for grad_R; E passes through the LDS between them (and to memory, written once).
+// 3456 x 1152 at rank 32: 15-17.6 us (20 + 8.2 + 8.1 us as three kernels, with E read back twice).  Memory is 44 MB of that
+// (W, E and 12 MB of gradient parts: 9 us at 5 TB/s), the matrix pipe is busy 4.9 us and the vector ALU 3 us; the rest is
+// that all workgroups are resident at once and go through the same phases together.
+// GT: 16-column tiles per scale group (4: 64 values, 8: 128, 2: MX block of 32).
+// Q: 0 INT4 groups (fp32 scale), 1 SINT4 blocks, 2 MXFP4, 3 MXINT4.
+template <int R, int Q, int GT>
+__global__ __launch_bounds__(64 * calib_waves(R), calib_waves(R) == 4 && R > 64 ? 1 : 2) void calib_err_kernel(CalibParams p)
+{
+    constexpr int NWV = calib_waves(R), NTHR = 64 * NWV, ROWS = 16 * NWV, T = R / 16, CT = 8 / NWV;
+    constexpr int SL = R + 4, SC = CALIB_COLS + 4;
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    float* Rs = lds;                 // [R][128]   the column block of R (calib_rs)
+    float* Ls = Rs + R * CALIB_COLS;       // [ROWS][SL] the row block of L
+    float* Es = Ls + ROWS * SL;      // [ROWS][SC]
+    const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cb = blockIdx.x % p.c.cblocks, split = blockIdx.x / p.c.cblocks;
+    const int N = p.N, K = p.K, col0 = cb * CALIB_COLS;
+    const int ncol = K - col0 < CALIB_COLS ? K - col0 : CALIB_COLS;  // 128, or 64 in the last block
+
+    // (an out-of-range column of the last block is loaded from the block's first columns and replaced by zero)
+    constexpr int NR = R * CALIB_COLS / 4 / NTHR, NL = ROWS * R / 4 / NTHR;
+    v4f rv[NR];
+#pragma unroll
+    for (int e = 0; e < NR; ++e) {
+        const int f = tid + e * NTHR, row = f / (CALIB_COLS / 4), c = 4 * (f % (CALIB_COLS / 4));
+        rv[e] = *(const v4f*)(p.R + (size_t)row * K + col0 + (c < ncol ? c : c - 64));
+    }
+    v4f gr[T][CT];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) gr[t][c] = v4f{0.f, 0.f, 0.f, 0.f};
     float lsum = 0.f;
-    const int g = (blockIdx.x % GQ) * 4 + wave;
-    if (g < G) {
-        const int col0 = g * GC * 64 + lane;
-        float v[16][GC];
+    const int rb_end = (split + 1) * p.c.per < p.c.rblocks ? (split + 1) * p.c.per : p.c.rblocks;
+    for (int rb = split * p.c.per; rb < rb_end; ++rb) {
+        const int row0 = rb * ROWS, wrow = row0 + 16 * wave;
+        const bool live = wrow < N;  // (N is a multiple of 64: only the upper half of a 128-row block can be missing)
+        // everything this block needs from memory is requested before anything is waited for
+        v4f v[8];
+        const float* wp = p.W + (size_t)((live ? wrow : row0) + 4 * q) * K + col0 + l15;
+        if (ncol == CALIB_COLS) {
 #pragma unroll
-        for (int row = 0; row < 16; ++row)
+            for (int t = 0; t < 8; ++t)
 #pragma unroll
-            for (int c = 0; c < GC; ++c) v[row][c] = W[(size_t)(n0 + row) * K + col0 + c * 64];
-        // 16 rows of R at a time: all their loads are in flight together (one L2 round trip per 16 rank indices)
-        for (int j = 0; j < r; j += 16) {
-            float rj[16][GC];
+                for (int i = 0; i < 4; ++i) v[t][i] = wp[(size_t)i * K + 16 * t];
+        } else {
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj)
+            for (int t = 0; t < 8; ++t)
 #pragma unroll
-                for (int c = 0; c < GC; ++c) rj[jj][c] = R[(size_t)(j + jj) * K + col0 + c * 64];
+                for (int i = 0; i < 4; ++i) v[t][i] = t < 4 ? wp[(size_t)i * K + 16 * t] : 0.f;
+        }
+        v4f lv[NL];
+        {
+            const float* src = p.L + (size_t)row0 * R;
+            const int n = (N - row0) * (R / 4);
 #pragma unroll
-            for (int row = 0; row < 16; ++row) {
-#pragma unroll
-                for (int j4 = 0; j4 < 16; j4 += 4) {
-                    const v4f l4 = *(const v4f*)&sL[row * r + j + j4];
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-                        for (int c = 0; c < GC; ++c) v[row][c] = __builtin_fmaf(l4[jj], rj[j4 + jj][c], v[row][c]);
-                }
+            for (int e = 0; e < NL; ++e) {
+                const int f = tid + e * NTHR;
+                lv[e] = *(const v4f*)(src + 4 * (NWV == 4 || f < n ? f : f - n));
             }
         }
-        float amax[16];
+        __syncthreads();  // the previous block's products have read Ls and Es
+        if (rb == split * p.c.per) {
 #pragma unroll
-        for (int row = 0; row < 16; ++row) {
-            float a = 0.f;
-#pragma unroll
-            for (int c = 0; c < GC; ++c) a = fmaxf(a, fabsf(v[row][c]));
-            amax[row] = wave_max_f<(Q >= 2)>(a, lane);
+            for (int e = 0; e < NR; ++e) {
+                const int f = tid + e * NTHR, row = f / (CALIB_COLS / 4), c = 4 * (f % (CALIB_COLS / 4));
+                *(v4f*)(Rs + calib_rs(row, c)) = c < ncol ? rv[e] : v4f{0.f, 0.f, 0.f, 0.f};
+            }
         }
-        // INT / SINT4 scales need correctly rounded divisions: done once for the 16 rows (lane l works on row l % 16,
-        // the rows then read their pair back through scalar registers) instead of once per row by all lanes
+#pragma unroll
+        for (int e = 0; e < NL; ++e) {
+            const int f = tid + e * NTHR, row = f / (R / 4), c = f - row * (R / 4);
+            *(v4f*)(Ls + row * SL + 4 * c) = NWV == 4 || row0 + row < N ? lv[e] : v4f{0.f, 0.f, 0.f, 0.f};
+        }
+        if (NWV == 8 && !live) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) v[t] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+        __syncthreads();
+        {
+            const float* ap = Ls + (16 * wave + l15) * SL + q;
+#pragma unroll 8
+            for (int s = 0; s < R / 4; ++s) {
+                const float a = ap[4 * s];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) v[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Rs[calib_rs(4 * s + q, 16 * t + l15)], v[t], 0, 0, 0);
+            }
+        }
+        float* ep = p.E + (size_t)(wrow + 4 * q) * K + col0 + l15;
+        float* es = Es + (16 * wave + 4 * q) * SC + l15;
+        constexpr int NG = 8 / GT;  // scale groups side by side; a lane holds 4 rows of each
+        float am[NG][4];
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float a = 0.f;
+#pragma unroll
+                for (int t = g * GT; t < (g + 1) * GT; ++t) a = fmaxf(a, fabsf(v[t][i]));
+                am[g][i] = row16_max(a);
+            }
+        // INT / SINT4 scales need correctly rounded divisions: the 16 lanes that share a row's maxima share the work, lane
+        // 4 g + i dividing for (g, i) and handing the result to the others (two divisions per lane instead of 2 * 4 * NG)
         float sv = 1.0f, iv = 1.0f;
         if constexpr (Q <= 1) {
-            float am = amax[0];
+            float a = am[0][0];
 #pragma unroll
-            for (int row = 1; row < 16; ++row) am = (lane & 15) == row ? amax[row] : am;
+            for (int k = 1; k < 4 * NG; ++k) a = (l15 & (4 * NG - 1)) == k ? am[k >> 2][k & 3] : a;
             if constexpr (Q == 1) {
-                sv = f16_bits_value(sint4_scale(am, &iv));
+                sv = f16_bits_value(sint4_scale(a, &iv));
             } else {  // branch-free: an all-zero group takes scale 1
-                const float sd = __fdiv_rn(am, 7.0f), id = __fdiv_rn(7.0f, am);
-                sv = am == 0.0f ? 1.0f : sd;
-                iv = am == 0.0f ? 1.0f : id;
+                const float sd = __fdiv_rn(a, 7.0f), id = __fdiv_rn(7.0f, a);
+                sv = a == 0.0f ? 1.0f : sd;
+                iv = a == 0.0f ? 1.0f : id;
             }
         }
-#pragma unroll
-        for (int row = 0; row < 16; ++row) {
-            const float a = amax[row];
+        auto finish = [&](auto k_) {  // scale group k >> 2, row k & 3
+            constexpr int k = decltype(k_)::value, g = k >> 2, i = k & 3;
+            const float a = am[g][i];
             float s = 1.0f, inv = 1.0f;
             uint32_t eb = 0u;
             if constexpr (Q <= 1) {
-                s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sv), row));
-                inv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(iv), row));
+                s = row16_lane<k>(sv);
+                inv = row16_lane<k>(iv);
             } else if constexpr (Q == 2) {
                 eb = mxfp4_scale_byte(a);
                 s = e8m0_as_float(eb);
@@ -184,126 +268,102 @@ __global__ __launch_bounds__(256) void calib_err_kernel(const float* W, const fl
                 eb = (__float_as_uint(a) >> 23) & 0xFFu;
             }
 #pragma unroll
-            for (int c = 0; c < GC; ++c) {
+            for (int t = g * GT; t < (g + 1) * GT; ++t) {
                 float deq;
                 if constexpr (Q <= 1) {
-                    float q = rintf(__fmul_rn(v[row][c], inv));
-                    q = fminf(fmaxf(q, -7.0f), 7.0f);
-                    deq = __fmul_rn(q, s);
+                    float c = rintf(__fmul_rn(v[t][i], inv));
+                    c = fminf(fmaxf(c, -7.0f), 7.0f);
+                    deq = __fmul_rn(c, s);
                 } else if constexpr (Q == 2) {
-                    const uint32_t code = a != 0.0f ? (__builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, v[row][c], 0.0f, s, 0) & 0xFu) : 0u;
+                    const uint32_t code = a != 0.0f ? (__builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, v[t][i], 0.0f, s, 0) & 0xFu) : 0u;
                     deq = __fmul_rn(e2m1_value(code), s);
                 } else {
-                    deq = mxint4_round(v[row][c], eb);
+                    deq = mxint4_round(v[t][i], eb);
                 }
-                const float e = __fsub_rn(deq, v[row][c]);
-                E[(size_t)(n0 + row) * K + col0 + c * 64] = e;
-                lsum = __fadd_rn(lsum, __fmul_rn(e, e));
+                const float e = __fsub_rn(deq, v[t][i]);
+                v[t][i] = e;
+                lsum = __builtin_fmaf(e, e, lsum);
+                es[i * SC + 16 * t] = e;
+            }
+        };
+        for_constants(finish, std::make_integer_sequence<int, 4 * NG>{});
+        if (live) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ep[(size_t)i * K + 16 * t] = v[t][i];
+            if (ncol == CALIB_COLS) {
+#pragma unroll
+                for (int t = 4; t < 8; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) ep[(size_t)i * K + 16 * t] = v[t][i];
             }
         }
+        // grad_L of the wavefront's own 16 rows: contraction over the block's columns, column 16 s + 4 q + u in step (s, u)
+        {
+            v4f gl[T];
+#pragma unroll
+            for (int t = 0; t < T; ++t) gl[t] = v4f{0.f, 0.f, 0.f, 0.f};
+            const float* ap = Es + (16 * wave + l15) * SC + 4 * q;
+#pragma unroll 2
+            for (int s = 0; s < CALIB_COLS / 16; ++s) {
+                const v4f a = *(const v4f*)(ap + 16 * s);
+                v4f b[T];
+#pragma unroll
+                for (int t = 0; t < T; ++t) b[t] = *(const v4f*)(Rs + calib_rs(16 * t + l15, 16 * s + 4 * q));
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int t = 0; t < T; ++t) gl[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[t][u], gl[t], 0, 0, 0);
+            }
+            if (live) {
+                float* o = p.gLp + ((size_t)cb * N + wrow + 4 * q) * R + l15;
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[i * R + 16 * t] = gl[t][i];
+            }
+        }
+        __syncthreads();  // every wavefront's rows of E are in the LDS
+        // grad_R of the wavefront's columns: contraction over the block's rows, row 16 s + 4 q + u in step (s, u)
+        {
+            const float* ap = Ls + 4 * q * SL + l15;
+            const float* bp = Es + 4 * q * SC + wave * 16 * CT + l15;
+#pragma unroll 2
+            for (int s = 0; s < ROWS / 16; ++s)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    float a[T], b[CT];
+#pragma unroll
+                    for (int t = 0; t < T; ++t) a[t] = ap[(16 * s + u) * SL + 16 * t];
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) b[c] = bp[(16 * s + u) * SC + 16 * c];
+#pragma unroll
+                    for (int t = 0; t < T; ++t)
+#pragma unroll
+                        for (int c = 0; c < CT; ++c) gr[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[c], gr[t][c], 0, 0, 0);
+                }
+        }
+    }
+    const int c0 = wave * 16 * CT;
+    if (c0 < ncol) {
+        float* o = p.gRp + ((size_t)split * R + 4 * q) * K + col0 + c0 + l15;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[(size_t)(16 * t + i) * K + 16 * c] = gr[t][c][i];
     }
     lsum = wave_sum_f(lsum);
-    if (lane == 0) lp[blockIdx.x * 4 + wave] = lsum;
-}
-
-// Gradient products on v_mfma_f32_16x16x4_f32 (fp32 in, fp32 accumulate): lane l supplies A[row l%16][k slot l/16] and
-// B[col l%16][k slot l/16]; the four values a lane holds per 16-deep slice feed four MFMAs (the k order inside a slice
-// is permuted the same way for both operands).  The contraction is split over the wavefronts of a workgroup (slices
-// w, w + WAVES, ...) and the partial tiles are summed through LDS in wavefront order.  NT = r / 16.
-//
-// grad_L = scale * E R^T: a workgroup owns 16 rows of E and all r columns, so E is read once.
-template <int NT>
-__global__ __launch_bounds__(512) void calib_grad_l_kernel(const float* E, const float* R, float* gL, int K, float scale)
-{
-    constexpr int WAVES = 8;
-    __shared__ __attribute__((aligned(16))) float s_acc[WAVES][NT][64][4];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int row = lane & 15, q = lane >> 4;
-    const int m0 = blockIdx.x * 16;
-    v4f acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
-    const float* ap = E + (size_t)(m0 + row) * K + 4 * q;
-    const float* bp = R + (size_t)row * K + 4 * q;
-    for (int kk = wave * 16; kk < K; kk += WAVES * 16) {
-        const v4f a4 = *(const v4f*)(ap + kk);
-        v4f b4[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) b4[t] = *(const v4f*)(bp + (size_t)t * 16 * K + kk);
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[i], b4[t][i], acc[t], 0, 0, 0);
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) *(v4f*)&s_acc[wave][t][lane][0] = acc[t];
     __syncthreads();
-    // wavefront w finishes tiles w, w + WAVES, ...
-    for (int t = wave; t < NT; t += WAVES) {
-        v4f s = *(const v4f*)&s_acc[0][t][lane][0];
-#pragma unroll
-        for (int w = 1; w < WAVES; ++w) {
-            const v4f o = *(const v4f*)&s_acc[w][t][lane][0];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] = __fadd_rn(s[i], o[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) gL[(size_t)(m0 + 4 * q + i) * (NT * 16) + t * 16 + row] = __fmul_rn(scale, s[i]);
-    }
-}
-
-// Partial grad_R = L^T E over a range of rows: a workgroup owns 32 columns of E (whole 128-byte lines per row), all r
-// rows of the result, and the rows [split * rows_per, (split + 1) * rows_per) of the contraction; the partial goes to
-// part[split][r][K] and the Adam kernel adds the splits in order (and applies the scale).
-template <int NT, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void calib_grad_r_kernel(const float* L, const float* E, float* part, int K, int rows_per)
-{
-    constexpr int r = NT * 16;
-    __shared__ __attribute__((aligned(16))) float s_acc[WAVES][NT * 2][64][4];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int row = lane & 15, q = lane >> 4;
-    const int ct = K >> 5;
-    const int n0 = ((int)blockIdx.x % ct) * 32, split = (int)blockIdx.x / ct;
-    const size_t base = (size_t)split * rows_per;
-    v4f acc[NT][2];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t][0] = acc[t][1] = v4f{0.f, 0.f, 0.f, 0.f};
-    const float* ap = L + (base + 4 * q) * r + row;
-    const float* bp = E + (base + 4 * q) * K + n0 + row;
-    for (int kk = wave * 16; kk < rows_per; kk += WAVES * 16) {
-        float a4[NT][4], b4[2][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) a4[t][i] = ap[(size_t)(kk + i) * r + t * 16];
-            b4[0][i] = bp[(size_t)(kk + i) * K];
-            b4[1][i] = bp[(size_t)(kk + i) * K + 16];
-        }
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[t][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[t][i], b4[h][i], acc[t][h], 0, 0, 0);
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) *(v4f*)&s_acc[wave][t * 2 + h][lane][0] = acc[t][h];
+    if (lane == 0) Es[wave] = lsum;
     __syncthreads();
-    for (int th = wave; th < NT * 2; th += WAVES) {
-        v4f s = *(const v4f*)&s_acc[0][th][lane][0];
+    if (tid == 0) {
+        float v = Es[0];
 #pragma unroll
-        for (int w = 1; w < WAVES; ++w) {
-            const v4f o = *(const v4f*)&s_acc[w][th][lane][0];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] = __fadd_rn(s[i], o[i]);
-        }
-        const int t = th >> 1, h = th & 1;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) part[((size_t)split * r + t * 16 + 4 * q + i) * K + n0 + h * 16 + row] = s[i];
+        for (int w = 1; w < NWV; ++w) v = __fadd_rn(v, Es[w]);
+        p.lp[blockIdx.x] = v;
     }
 }
 
@@ -311,35 +371,40 @@ struct AdamParams {
     float lr, b1, b2, eps, ic1, ic2;  // ic = 1 / (1 - beta^t)
 };
 
-// One thread per parameter: the N x r values of L, then the r x K values of R.  Block 0 also sums the loss partials
-// (thread-strided, a fixed shuffle tree per wavefront, then the four wavefronts in order).
-__global__ __launch_bounds__(256) void calib_adam_kernel(float* L, float* mL, float* vL, const float* gL, size_t nL, float* R,
-                                                         float* mR, float* vR, float* gR, const float* gR_part, int splits,
-                                                         float gscale, size_t nR, AdamParams a, const float* lp, int n_lp,
-                                                         float inv_count, float* loss)
+// One thread per parameter: the N x r values of L, then the r x K values of R; the parts of its gradient are added in order
+// and scaled.  Block 0 also sums the loss partials (thread-strided, a fixed shuffle tree per wavefront, then the four
+// wavefronts in order).
+struct AdamArrays {
+    float *p, *m, *v, *g;
+    const float* part;
+    int parts;
+    size_t n;
+};
+__global__ __launch_bounds__(256) void calib_adam_kernel(AdamArrays aL, AdamArrays aR, float gscale, AdamParams a, const float* lp,
+                                                         int n_lp, float inv_count, float* loss)
 {
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx < nL + nR) {
-        const bool isL = idx < nL;
-        const size_t i = isL ? idx : idx - nL;
-        float* p = isL ? L : R;
-        float* m = isL ? mL : mR;
-        float* v = isL ? vL : vR;
-        float g;
-        if (isL) {
-            g = gL[i];
-        } else {  // grad_R: the row-range partials in order, then the scale
-            float sum = gR_part[i];
-            for (int sp = 1; sp < splits; ++sp) sum = __fadd_rn(sum, gR_part[(size_t)sp * nR + i]);
-            g = __fmul_rn(gscale, sum);
-            gR[i] = g;
+    if (idx < aL.n + aR.n) {
+        const bool isL = idx < aL.n;
+        const AdamArrays& x = isL ? aL : aR;
+        const size_t i = isL ? idx : idx - aL.n;
+        const float m0 = x.m[i], v0 = x.v[i], p0 = x.p[i];
+        float sum = 0.f;
+        for (int sp = 0; sp < x.parts; sp += 16) {  // 16 loads in flight; a part past the last is the last one again, not added
+            float f[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) f[k] = x.part[(size_t)(sp + k < x.parts ? sp + k : x.parts - 1) * x.n + i];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) sum = __fadd_rn(sum, sp + k < x.parts ? f[k] : 0.f);
         }
-        const float mm = __fadd_rn(__fmul_rn(a.b1, m[i]), __fmul_rn(1.0f - a.b1, g));
-        const float vv = __fadd_rn(__fmul_rn(a.b2, v[i]), __fmul_rn(1.0f - a.b2, __fmul_rn(g, g)));
-        m[i] = mm;
-        v[i] = vv;
+        const float g = __fmul_rn(gscale, sum);
+        x.g[i] = g;
+        const float mm = __fadd_rn(__fmul_rn(a.b1, m0), __fmul_rn(1.0f - a.b1, g));
+        const float vv = __fadd_rn(__fmul_rn(a.b2, v0), __fmul_rn(1.0f - a.b2, __fmul_rn(g, g)));
+        x.m[i] = mm;
+        x.v[i] = vv;
         const float den = __fadd_rn(__fsqrt_rn(__fmul_rn(vv, a.ic2)), a.eps);
-        p[i] = __fsub_rn(p[i], __fdiv_rn(__fmul_rn(a.lr, __fmul_rn(mm, a.ic1)), den));
+        x.p[i] = __fsub_rn(p0, __fdiv_rn(__fmul_rn(a.lr, __fmul_rn(mm, a.ic1)), den));
     }
     if (loss && blockIdx.x == 0) {  // block-uniform
         __shared__ float s_part[4];
@@ -354,69 +419,106 @@ __global__ __launch_bounds__(256) void calib_adam_kernel(float* L, float* mL, fl
     }
 }
 
-__global__ __launch_bounds__(256) void calib_zero_kernel(float* p, size_t n)
+// Copies (or zero fills) of whole sections, all in one launch; every length is a multiple of 4 floats and every section
+// starts 16-byte aligned.
+constexpr int CALIB_MAX_PARTS = 9;
+struct CalibCopy {
+    v4f* dst[CALIB_MAX_PARTS];
+    const v4f* src[CALIB_MAX_PARTS];  // null: zeros
+    size_t end[CALIB_MAX_PARTS];      // running sums of the lengths, in v4f
+    int n;
+};
+__global__ __launch_bounds__(256) void calib_copy_kernel(CalibCopy c)
 {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0.f;
+    size_t begin = 0;
+    for (int k = 0; k < c.n; ++k) {
+        if (i < c.end[k]) {
+            if (i >= begin) c.dst[k][i - begin] = c.src[k] ? c.src[k][i - begin] : v4f{0.f, 0.f, 0.f, 0.f};
+            return;
+        }
+        begin = c.end[k];
+    }
+}
+static void calib_copy_add(CalibCopy& c, void* dst, const void* src, size_t bytes)
+{
+    c.dst[c.n] = (v4f*)dst;
+    c.src[c.n] = (const v4f*)src;
+    c.end[c.n] = (c.n ? c.end[c.n - 1] : 0) + bytes / 16;
+    ++c.n;
+}
+static hipError_t calib_copy_run(const CalibCopy& c, hipStream_t s)
+{
+    if (c.n == 0) return hipSuccess;
+    hipLaunchKernelGGL(calib_copy_kernel, dim3((unsigned)((c.end[c.n - 1] + 255) / 256)), dim3(256), 0, s, c);
+    return hipGetLastError();
 }
 
 hipError_t launch_calib_init(const Dims& d, const float* L, const float* R, uint8_t* state, hipStream_t s)
 {
     const CalibLayout cl = calib_layout(d);
-    const size_t nl = (size_t)d.N * d.r * 4, nr = (size_t)d.r * d.K * 4;
-    hipError_t e = hipMemcpyAsync(state + cl.off_L, L, nl, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-    e = hipMemcpyAsync(state + cl.off_R, R, nr, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-    // moments start at zero (one contiguous range: mL, vL, mR, vR); a kernel, so that the call can be captured in a graph
-    const size_t nz = (cl.off_gL - cl.off_mL) / 4;
-    hipLaunchKernelGGL(calib_zero_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, s, (float*)(state + cl.off_mL), nz);
-    return hipGetLastError();
+    CalibCopy c;
+    c.n = 0;
+    calib_copy_add(c, state + cl.off_L, L, (size_t)d.N * d.r * 4);
+    calib_copy_add(c, state + cl.off_R, R, (size_t)d.r * d.K * 4);
+    calib_copy_add(c, state + cl.off_mL, nullptr, cl.off_gL - cl.off_mL);  // moments start at zero (one contiguous range: mL, vL, mR, vR)
+    return calib_copy_run(c, s);
+}
+
+// Kernels whose LDS exceeds the 64 KB a launch may use without asking: asked once per device and kernel, so that later
+// calls (which a caller may capture in a graph) only launch.
+template <auto KERNEL>
+static void calib_launch_err(const CalibParams& p, int waves, int lds, hipStream_t s)
+{
+    if (lds > 65536) {
+        static bool asked[64] = {false};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+        if (!asked[dev]) {
+            (void)hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            asked[dev] = true;
+        }
+    }
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)(p.c.cblocks * p.c.splits)), dim3(64 * waves), lds, s, p);
+}
+
+template <int R>
+static void calib_err(const Dims& d, const CalibParams& p, hipStream_t s)
+{
+    constexpr int lds = calib_lds<R>(), waves = calib_waves(R);
+    if (d.mxi)
+        calib_launch_err<calib_err_kernel<R, 3, 2>>(p, waves, lds, s);
+    else if (d.mx)
+        calib_launch_err<calib_err_kernel<R, 2, 2>>(p, waves, lds, s);
+    else if (d.ga)
+        calib_launch_err<calib_err_kernel<R, 1, 4>>(p, waves, lds, s);
+    else if (d.g == 64)
+        calib_launch_err<calib_err_kernel<R, 0, 4>>(p, waves, lds, s);
+    else
+        calib_launch_err<calib_err_kernel<R, 0, 8>>(p, waves, lds, s);
 }
 
 hipError_t launch_calib_step(const Dims& d, const float* W, uint8_t* state, int step, const lq_adam* ad, float* loss,
                              hipStream_t s)
 {
     const CalibLayout cl = calib_layout(d);
-    float* L = (float*)(state + cl.off_L);
-    float* R = (float*)(state + cl.off_R);
-    float* gL = (float*)(state + cl.off_gL);
-    float* gR = (float*)(state + cl.off_gR);
-    float* E = (float*)(state + cl.off_E);
-    float* lp = (float*)(state + cl.off_lp);
-    const int N = (int)d.N, K = (int)d.K, r = d.r;
-    const unsigned lds = (unsigned)(16 * r * sizeof(float));
-    const dim3 grid((unsigned)((N / 16) * ((calib_groups(d) + 3) / 4))), block(256);
-    if (d.mxi)
-        hipLaunchKernelGGL((calib_err_kernel<1, 3>), grid, block, lds, s, W, L, R, E, lp, N, K, r);
-    else if (d.mx)
-        hipLaunchKernelGGL((calib_err_kernel<1, 2>), grid, block, lds, s, W, L, R, E, lp, N, K, r);
-    else if (d.ga)
-        hipLaunchKernelGGL((calib_err_kernel<1, 1>), grid, block, lds, s, W, L, R, E, lp, N, K, r);
-    else if (d.g == 64)
-        hipLaunchKernelGGL((calib_err_kernel<1, 0>), grid, block, lds, s, W, L, R, E, lp, N, K, r);
-    else
-        hipLaunchKernelGGL((calib_err_kernel<2, 0>), grid, block, lds, s, W, L, R, E, lp, N, K, r);
-    const float cg = (float)(-2.0 / ((double)N * (double)K));
-    // grad_L (N x r): one workgroup per 16 rows of E
-    const dim3 gl_grid((unsigned)(N / 16)), gl_block(512);
-    switch (r >> 4) {
-        case 1: hipLaunchKernelGGL((calib_grad_l_kernel<1>), gl_grid, gl_block, 0, s, E, R, gL, K, cg); break;
-        case 2: hipLaunchKernelGGL((calib_grad_l_kernel<2>), gl_grid, gl_block, 0, s, E, R, gL, K, cg); break;
-        case 4: hipLaunchKernelGGL((calib_grad_l_kernel<4>), gl_grid, gl_block, 0, s, E, R, gL, K, cg); break;
-        case 6: hipLaunchKernelGGL((calib_grad_l_kernel<6>), gl_grid, gl_block, 0, s, E, R, gL, K, cg); break;
-        default: hipLaunchKernelGGL((calib_grad_l_kernel<8>), gl_grid, gl_block, 0, s, E, R, gL, K, cg); break;
-    }
-    // grad_R (r x K): partials over row ranges
-    const int splits = calib_splits(d), rows_per = N / splits;
-    float* gRp = (float*)(state + cl.off_gRp);
-    const dim3 gr_grid((unsigned)((K / 32) * splits));
-    switch (r >> 4) {
-        case 1: hipLaunchKernelGGL((calib_grad_r_kernel<1, 8>), gr_grid, dim3(512), 0, s, L, E, gRp, K, rows_per); break;
-        case 2: hipLaunchKernelGGL((calib_grad_r_kernel<2, 8>), gr_grid, dim3(512), 0, s, L, E, gRp, K, rows_per); break;
-        case 4: hipLaunchKernelGGL((calib_grad_r_kernel<4, 8>), gr_grid, dim3(512), 0, s, L, E, gRp, K, rows_per); break;
-        case 6: hipLaunchKernelGGL((calib_grad_r_kernel<6, 4>), gr_grid, dim3(256), 0, s, L, E, gRp, K, rows_per); break;
-        default: hipLaunchKernelGGL((calib_grad_r_kernel<8, 4>), gr_grid, dim3(256), 0, s, L, E, gRp, K, rows_per); break;
+    CalibParams p;
+    p.W = W;
+    p.L = (float*)(state + cl.off_L);
+    p.R = (float*)(state + cl.off_R);
+    p.E = (float*)(state + cl.off_E);
+    p.lp = (float*)(state + cl.off_lp);
+    p.gLp = (float*)(state + cl.off_gLp);
+    p.gRp = (float*)(state + cl.off_gRp);
+    p.N = (int)d.N;
+    p.K = (int)d.K;
+    p.c = calib_split(d);
+    switch (d.r) {
+        case 16: calib_err<16>(d, p, s); break;
+        case 32: calib_err<32>(d, p, s); break;
+        case 64: calib_err<64>(d, p, s); break;
+        case 96: calib_err<96>(d, p, s); break;
+        default: calib_err<128>(d, p, s); break;
     }
     AdamParams a;
     a.lr = ad->lr;
@@ -425,10 +527,13 @@ hipError_t launch_calib_step(const Dims& d, const float* W, uint8_t* state, int 
     a.eps = ad->eps;
     a.ic1 = (float)(1.0 / (1.0 - pow((double)ad->beta1, (double)step)));
     a.ic2 = (float)(1.0 / (1.0 - pow((double)ad->beta2, (double)step)));
-    const size_t nL = (size_t)N * r, nR = (size_t)r * K;
-    hipLaunchKernelGGL(calib_adam_kernel, dim3((unsigned)((nL + nR + 255) / 256)), dim3(256), 0, s, L, (float*)(state + cl.off_mL),
-                       (float*)(state + cl.off_vL), gL, nL, R, (float*)(state + cl.off_mR), (float*)(state + cl.off_vR), gR, gRp,
-                       splits, cg, nR, a, lp, cl.n_lp, (float)(1.0 / ((double)N * (double)K)), loss);
+    const size_t nL = (size_t)d.N * d.r, nR = (size_t)d.r * d.K;
+    const AdamArrays aL = {(float*)(state + cl.off_L), (float*)(state + cl.off_mL), (float*)(state + cl.off_vL),
+                           (float*)(state + cl.off_gL), p.gLp, p.c.cblocks, nL};
+    const AdamArrays aR = {(float*)(state + cl.off_R), (float*)(state + cl.off_mR), (float*)(state + cl.off_vR),
+                           (float*)(state + cl.off_gR), p.gRp, p.c.splits, nR};
+    hipLaunchKernelGGL(calib_adam_kernel, dim3((unsigned)((nL + nR + 255) / 256)), dim3(256), 0, s, aL, aR,
+                       (float)(-2.0 / ((double)d.N * (double)d.K)), a, p.lp, cl.n_lp, (float)(1.0 / ((double)d.N * (double)d.K)), loss);
     return hipGetLastError();
 }
 
@@ -436,16 +541,22 @@ hipError_t launch_calib_unpack(const Dims& d, const uint8_t* state, const lq_cal
 {
     const CalibLayout cl = calib_layout(d);
     const size_t nl = (size_t)d.N * d.r * 4, nr = (size_t)d.r * d.K * 4;
-    struct { float* dst; size_t off, bytes; } parts[] = {
+    const struct { float* dst; size_t off, bytes; } parts[CALIB_MAX_PARTS] = {
         {out->L, cl.off_L, nl},   {out->R, cl.off_R, nr},   {out->mL, cl.off_mL, nl}, {out->vL, cl.off_vL, nl},
         {out->mR, cl.off_mR, nr}, {out->vR, cl.off_vR, nr}, {out->gL, cl.off_gL, nl}, {out->gR, cl.off_gR, nr},
         {out->E, cl.off_E, (size_t)d.N * d.K * 4}};
+    CalibCopy c;
+    c.n = 0;
     for (auto& p : parts) {
         if (!p.dst) continue;
-        hipError_t e = hipMemcpyAsync(p.dst, state + p.off, p.bytes, hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return e;
+        if ((uintptr_t)p.dst % 16) {  // (the views' alignment is the caller's)
+            const hipError_t e = hipMemcpyAsync(p.dst, state + p.off, p.bytes, hipMemcpyDeviceToDevice, s);
+            if (e != hipSuccess) return e;
+        } else {
+            calib_copy_add(c, p.dst, state + p.off, p.bytes);
+        }
     }
-    return hipSuccess;
+    return calib_copy_run(c, s);
 }
 
 }  // namespace lq

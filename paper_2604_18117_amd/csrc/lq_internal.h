@@ -188,9 +188,10 @@ struct CalibLayout {
     size_t off_mL, off_vL, off_mR, off_vR;  // Adam moments (contiguous, in this order)
     size_t off_gL, off_gR;     // gradients of the last step
     size_t off_E;              // N x K  deq(Q1(W + L R)) - (W + L R) of the last step
-    size_t off_lp;             // partial sums of E^2, one per wavefront
+    size_t off_lp;             // partial sums of E^2, one per workgroup
     int n_lp;
-    size_t off_gRp;            // partials of L^T E over row ranges, [range][r][K]
+    size_t off_gLp;            // parts of E R^T, [column block][N][r]
+    size_t off_gRp;            // parts of L^T E, [run of row blocks][r][K]
     size_t total;
 };
 CalibLayout calib_layout(const Dims& d);
