@@ -196,7 +196,6 @@ lq_status lq_pack_weights(const lq_config* cfg, const float* W, const float* L, 
     hipError_t e = d.mxi ? launch_pack_mxi(d, cfg->residual_from_quantized, W, L, R, (uint8_t*)packed, (hipStream_t)stream)
                    : d.mx ? launch_pack_mx(d, cfg->residual_from_quantized, W, L, R, (uint8_t*)packed, (hipStream_t)stream)
                         : launch_pack_int(d, cfg->residual_from_quantized, W, L, R, (uint8_t*)packed, (hipStream_t)stream);
-    if (e == hipSuccess) e = launch_write_tag((uint8_t*)packed, make_tag(d, LQ_BLOB_PACKED, 0), (hipStream_t)stream);
     return e == hipSuccess ? LQ_OK : LQ_ERR_DEVICE;
 }
 

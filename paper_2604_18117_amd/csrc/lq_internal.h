@@ -232,8 +232,6 @@ static inline int panel_width(int tilesN, int C64, int chunk_row_bytes = 32)
     return pw < 1 ? 1 : pw > tilesN ? tilesN : pw;
 }
 
-hipError_t launch_write_tag(uint8_t* blob, const BlobTag& t, hipStream_t s);
-
 // ---- device helpers ----------------------------------------------------------------------
 #if defined(__HIPCC__)
 // header of an activation blob, written by the first workgroup of the kernel that fills the blob

@@ -16,7 +16,7 @@
 // returns NaN, not 448, above 464).
 #include <type_traits>
 
-#include "lq_internal.h"
+#include "lq_pack.h"
 
 namespace lq {
 
@@ -115,64 +115,35 @@ __device__ __forceinline__ float e8m0_inverse(uint32_t E)  // 2^(127-E), exact (
 {
     return __uint_as_float((254u - E) << 23);
 }
-__device__ __forceinline__ double e8m0_double(uint32_t E) { return __builtin_ldexp(1.0, (int)E - 127); }
-
-__device__ __forceinline__ float wmax64(float v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 
 // ---------------------------------------------------------------------------------------------
 // pack
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void mx_fill_kernel(uint8_t* p, size_t n, uint8_t v)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = v;
-}
+// Q2 of a row of L or R: E4M3 with one fp32 scale
+struct PackFp8Rows {
+    __device__ void scale(float amax, float* s, float* inv) const { fp8_scales(amax, s, inv); }
+    template <typename V>
+    __device__ uint32_t quad(V v, float inv) const
+    {
+        return fp8_quad(__fmul_rn(v[0], inv), __fmul_rn(v[1], inv), __fmul_rn(v[2], inv), __fmul_rn(v[3], inv));
+    }
+    __device__ size_t r_offset(int j, int k, int r) const { return mx_rq_offset(j, k, r); }
+};
 
-// Ks: row length of the source; K: row length of the layout (Ks rounded up to 128, the rest zero codes)
-__global__ __launch_bounds__(256) void mx_pack_r_kernel(const float* R, int Ks, int K, int r, uint8_t* r8, float* sr)
+// MXFP8e4 factors: one thread per (row, block of 32).  Rows of R, blocks along K, into the activation kernel's operand order;
+// then rows of L, blocks along the rank, into the forward's.
+// (Ks: row length of R's source; K: of the layout, a multiple of 128: blocks past the source are zero)
+__global__ __launch_bounds__(256) void mxb_pack_rows_kernel(const float* L, const float* R, int N, int K, int Ks, int r, int rp,
+                                                            uint8_t* lcodes, uint8_t* lscales, uint8_t* rcodes, uint8_t* rscales)
 {
-    __shared__ float red[4];
-    const int j = blockIdx.x, tid = threadIdx.x;
-    float a = 0.f;
-    for (int k = tid; k < Ks; k += 256) a = fmaxf(a, fabsf(R[(size_t)j * Ks + k]));
-    a = wmax64(a);
-    if ((tid & 63) == 0) red[tid >> 6] = a;
-    __syncthreads();
-    a = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    float s, inv;
-    fp8_scales(a, &s, &inv);
-    if (tid == 0) sr[j] = s;
-    for (int k = tid; k < K; k += 256)
-        r8[mx_rq_offset(j, k, r)] = k < Ks ? (uint8_t)fp8_byte(__fmul_rn(R[(size_t)j * Ks + k], inv)) : (uint8_t)0;
-}
-
-__global__ __launch_bounds__(256) void mx_pack_l_kernel(const float* L, int N, int r, int rp, uint8_t* l8, float* sl)
-{
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
-    float a = 0.f;
-    for (int j = 0; j < r; ++j) a = fmaxf(a, fabsf(L[(size_t)n * r + j]));
-    float s, inv;
-    fp8_scales(a, &s, &inv);
-    sl[n] = s;
-    for (int j = 0; j < rp; ++j)
-        l8[(size_t)n * rp + j] = (j < r) ? (uint8_t)fp8_byte(__fmul_rn(L[(size_t)n * r + j], inv)) : (uint8_t)0;
-}
-
-// MXFP8e4 factors: one thread per (row, block of 32).  mode 0: rows of R, blocks along K, into the
-// activation kernel's operand order; mode 1: rows of L, blocks along the rank, into the forward's.
-// (src_len: row length of the source; len: of the layout, a multiple of 128 for R: blocks past the source are zero)
-__global__ __launch_bounds__(256) void mxb_pack_rows_kernel(const float* A, int rows, int len, int src_len, int mode, int r,
-                                                            int rp, uint8_t* codes, uint8_t* scales)
-{
-    const int nb = len >> 5;
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t nr = (size_t)r * (K >> 5);
+    const int mode = idx < nr ? 0 : 1;
+    if (mode) idx -= nr;
+    const int nb = mode ? r >> 5 : K >> 5, rows = mode ? N : r, src_len = mode ? r : Ks;
     if (idx >= (size_t)rows * nb) return;
+    const float* A = mode ? L : R;
+    uint8_t *codes = mode ? lcodes : rcodes, *scales = mode ? lscales : rscales;
     const int row = (int)(idx / nb), b = (int)(idx % nb);
     const bool in_src = 32 * b < src_len;
     const float* v = A + (size_t)row * src_len + 32 * b;
@@ -194,61 +165,54 @@ __global__ __launch_bounds__(256) void mxb_pack_rows_kernel(const float* A, int 
         scales[mxb_scale_offset(row, b)] = (uint8_t)E;
 }
 
-// one wavefront per (n, 64-chunk): lane = k % 64, two blocks of 32.  from_q: 0 = unquantised factors,
-// 1 = E4M3 codes with fp32 row scales, 2 = MXFP8e4 codes with E8M0 block scales (sl, sr hold le, re).
-__global__ __launch_bounds__(256) void mx_pack_p_kernel(const float* W, const float* L, const float* R, int N, int Ks, int K,
-                                                        int r, int rp, int from_q, const uint8_t* l8, const float* sl,
-                                                        const uint8_t* r8, const float* sr, uint8_t* pc, uint8_t* pe)
-{
-    const int lane = threadIdx.x & 63;
-    const int C64 = K >> 6, CQ = (C64 + 3) >> 2;  // layout chunks; a chunk past the source row (k >= Ks) is all zero
-    const size_t wid = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (wid >= (size_t)N * C64) return;
-    const int n = (int)(wid / C64), c = (int)(wid % C64);
-    const int k = c * 64 + lane;
-    double d = 0.0;
-    const int rr = k < Ks ? r : 0;
-    for (int j = 0; j < rr; ++j) {
-        if (from_q == 3) {  // MXFP6e2 factors
-            const uint8_t* le = (const uint8_t*)sl;
-            const uint8_t* re = (const uint8_t*)sr;
-            const double lh = (double)e2m3_value(fp6_get(l8 + mx6_lt_slot(n, j >> 5, rp), j & 31)) * e8m0_double(le[mxb_scale_offset(n, j >> 5)]);
-            const double rh = (double)e2m3_value(fp6_get(r8 + mx6_rq_slot(j, k >> 5, r), k & 31)) * e8m0_double(re[mxb_re_offset(j, k >> 5, r)]);
-            d = fma(lh, rh, d);
-            continue;
-        }
-        if (from_q == 2) {  // element * 2^e is exact in fp64, and so is the product of two of them
-            const uint8_t* le = (const uint8_t*)sl;
-            const uint8_t* re = (const uint8_t*)sr;
-            const double lh = (double)fp8_value(l8[mxb_frag8_offset(n, j, rp)]) * e8m0_double(le[mxb_scale_offset(n, j >> 5)]);
-            const double rh = (double)fp8_value(r8[mxb_rq_offset(j, k, r)]) * e8m0_double(re[mxb_re_offset(j, k >> 5, r)]);
-            d = fma(lh, rh, d);
-            continue;
-        }
-        float lh, rh;
-        if (from_q) {
-            lh = __fmul_rn(fp8_value(l8[(size_t)n * rp + j]), sl[n]);
-            rh = __fmul_rn(fp8_value(r8[mx_rq_offset(j, k, r)]), sr[j]);
-        } else {
-            lh = L[(size_t)n * r + j];
-            rh = R[(size_t)j * Ks + k];
-        }
-        d = fma((double)lh, (double)rh, d);
+// Residual of a 64-chunk (two blocks of 32): MXFP4 codes and E8M0 bytes.  KIND of the factors: 0 as given, 1 E4M3 codes with
+// fp32 row scales, 2 MXFP8e4 and 3 MXFP6e2 codes with E8M0 block scales (sl, sr hold le, re; element * 2^e is exact in fp32).
+template <int KIND>
+struct PackMxResidual {
+    const float *L, *R;
+    const uint8_t* l8;
+    const float* sl;
+    const uint8_t* r8;
+    const float* sr;
+    uint8_t *pc, *pe;
+    int Ks, C64, r, rp;
+    __device__ float lhat(int n, int j) const
+    {
+        if constexpr (KIND == 0) return L[(size_t)n * r + j];
+        if constexpr (KIND == 1) return __fmul_rn(fp8_value(l8[(size_t)n * rp + j]), sl[n]);
+        const float s = e8m0_value(((const uint8_t*)sl)[mxb_scale_offset(n, j >> 5)]);
+        if constexpr (KIND == 2) return __fmul_rn(fp8_value(l8[mxb_frag8_offset(n, j, rp)]), s);
+        return __fmul_rn(e2m3_value(fp6_get(l8 + mx6_lt_slot(n, j >> 5, rp), j & 31)), s);
     }
-    const float P = k < Ks ? (float)((double)W[(size_t)n * Ks + k] - d) : 0.0f;
-    float a = fabsf(P);
+    __device__ float rhat(int j, int k) const
+    {
+        if constexpr (KIND == 0) return R[(size_t)j * Ks + k];
+        if constexpr (KIND == 1) return __fmul_rn(fp8_value(r8[mx_rq_offset(j, k, r)]), sr[j]);
+        const float s = e8m0_value(((const uint8_t*)sr)[mxb_re_offset(j, k >> 5, r)]);
+        if constexpr (KIND == 2) return __fmul_rn(fp8_value(r8[mxb_rq_offset(j, k, r)]), s);
+        return __fmul_rn(e2m3_value(fp6_get(r8 + mx6_rq_slot(j, k >> 5, r), k & 31)), s);
+    }
+    __device__ void encode(int n, int c, const float (&P)[1][16], int q) const
+    {
+        float a = pack_amax(P[0]);
+        a = fmaxf(a, __shfl_xor(a, 16));  // lanes q, q ^ 1 hold the block
+        const uint32_t E = e8m0_of(a);
+        const float s = e8m0_value(E);
+        uint32_t w[2] = {0u, 0u};
+        if (a != 0.0f) {
 #pragma unroll
-    for (int o = 16; o >= 1; o >>= 1) a = fmaxf(a, __shfl_xor(a, o, 64));  // amax of the 32-block (half wave)
-    const uint32_t E = e8m0_of(a);
-    uint32_t code = 0;
-    if (a != 0.0f) code = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, P, 0.0f, e8m0_value(E), 0) & 0xFu;
-    uint32_t w = code << (4 * (lane & 7));
-    w |= __shfl_xor(w, 1, 64);
-    w |= __shfl_xor(w, 2, 64);
-    w |= __shfl_xor(w, 4, 64);
-    if ((lane & 7) == 0) *(uint32_t*)(pc + mx_code_offset(n, k, C64)) = w;
-    if ((lane & 31) == 0) pe[mx_scale_offset(n, c, lane >> 5, CQ)] = (uint8_t)E;
-}
+            for (int d = 0; d < 2; ++d) {
+                w[d] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w[d], P[0][8 * d], P[0][8 * d + 1], s, 0);
+                w[d] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w[d], P[0][8 * d + 2], P[0][8 * d + 3], s, 1);
+                w[d] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w[d], P[0][8 * d + 4], P[0][8 * d + 5], s, 2);
+                w[d] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w[d], P[0][8 * d + 6], P[0][8 * d + 7], s, 3);
+            }
+        }
+        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+        *(u2*)(pc + mx_code_offset(n, c * 64 + 16 * q, C64)) = u2{w[0], w[1]};
+        if ((q & 1) == 0) pe[mx_scale_offset(n, c, q >> 1, (C64 + 3) >> 2)] = (uint8_t)E;
+    }
+};
 
 hipError_t launch_pack_mx(const Dims& d, int from_q, const float* W, const float* L, const float* R, uint8_t* packed,
                           hipStream_t s)
@@ -259,34 +223,40 @@ hipError_t launch_pack_mx(const Dims& d, int from_q, const float* W, const float
     uint8_t* r8 = packed + pl.off_rq;
     float* sr = (float*)(packed + pl.off_sr);
     const int N = (int)d.N, K = (int)d.K, Ks = (int)d.Ks;
-    const size_t pe_bytes = (size_t)(N / 32) * ((d.C64 + 3) / 4) * 256;
-    hipLaunchKernelGGL(mx_fill_kernel, dim3((unsigned)((pe_bytes + 255) / 256)), dim3(256), 0, s, packed + pl.off_sw,
-                       pe_bytes, (uint8_t)127);
-    if (d.smooth) {  // reciprocals of the smoothing vector start at 1
-        const hipError_t e = launch_set_smoothing(d, nullptr, packed, s);
+    uint8_t *pc = packed + pl.off_pq, *pe = packed + pl.off_sw;
+    PackFill fill;
+    fill.n = 0;
+    fill.blob = (uint32_t*)packed;
+    fill.tag = make_tag(d, LQ_BLOB_PACKED, 0);
+    if (d.C64 % 4) fill.add(pe, (size_t)(N / 32) * ((d.C64 + 3) / 4) * 256, 0x7F7F7F7Fu);  // padding chunks of the last quad: 2^0
+    if (d.smooth) fill.add(packed + pl.off_rg, (size_t)K * 4, 0x3F800000u);                 // reciprocals start at 1
+    if (d.mxb) {  // padding of the rank to 64: zero codes, scale 2^0
+        if (d.rp != d.r) fill.add(l8, (size_t)N * d.rp, 0u);
+        fill.add(sl, (size_t)N * 8, 0x7F7F7F7Fu);
+    }
+    hipError_t e = launch_pack_fill(fill, s);
+    if (e != hipSuccess) return e;
+    if (!d.mxb) {
+        pack_row_factors(PackFp8Rows{}, L, R, N, Ks, K, d.r, d.rp, l8, sl, r8, sr, s);
+    } else if (d.r > 0 && d.mxb_elem == 6) {
+        e = launch_pack_rows_mx6(d, L, R, packed, s);
         if (e != hipSuccess) return e;
+    } else if (d.r > 0) {
+        const size_t nt = (size_t)d.r * (K / 32) + (size_t)N * (d.r / 32);
+        hipLaunchKernelGGL(mxb_pack_rows_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, L, R, N, K, Ks, d.r, d.rp, l8, (uint8_t*)sl,
+                           r8, (uint8_t*)sr);
     }
-    if (d.mxb) {
-        // padding of the rank to 64: zero codes, scale 2^0
-        const size_t lq_bytes = (size_t)N * d.rp, le_bytes = (size_t)N * 8;
-        if (lq_bytes) hipLaunchKernelGGL(mx_fill_kernel, dim3((unsigned)((lq_bytes + 255) / 256)), dim3(256), 0, s, l8, lq_bytes, (uint8_t)0);
-        hipLaunchKernelGGL(mx_fill_kernel, dim3((unsigned)((le_bytes + 255) / 256)), dim3(256), 0, s, (uint8_t*)sl, le_bytes, (uint8_t)127);
-        if (d.r > 0 && d.mxb_elem == 6) {
-            const hipError_t e = launch_pack_rows_mx6(d, L, R, packed, s);
-            if (e != hipSuccess) return e;
-        } else if (d.r > 0) {
-            const size_t nr = (size_t)d.r * (K / 32), nl = (size_t)N * (d.r / 32);
-            hipLaunchKernelGGL(mxb_pack_rows_kernel, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, s, R, d.r, K, Ks, 0, d.r, d.rp, r8, (uint8_t*)sr);
-            hipLaunchKernelGGL(mxb_pack_rows_kernel, dim3((unsigned)((nl + 255) / 256)), dim3(256), 0, s, L, N, d.r, d.r, 1, d.r, d.rp, l8, (uint8_t*)sl);
-        }
-    } else {
-        if (d.r > 0) hipLaunchKernelGGL(mx_pack_r_kernel, dim3(d.r), dim3(256), 0, s, R, Ks, K, d.r, r8, sr);
-        hipLaunchKernelGGL(mx_pack_l_kernel, dim3((N + 255) / 256), dim3(256), 0, s, d.r > 0 ? L : (const float*)nullptr, N,
-                           d.r, d.rp, l8, sl);
-    }
-    const size_t waves = (size_t)N * d.C64;
-    hipLaunchKernelGGL(mx_pack_p_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, W, L, R, N, Ks, K, d.r, d.rp,
-                       (from_q && d.mxb) ? (d.mxb_elem == 6 ? 3 : 2) : from_q, l8, sl, r8, sr, packed + pl.off_pq, packed + pl.off_sw);
+    auto residual = [&](auto kind) {
+        pack_residual<1>(PackMxResidual<decltype(kind)::value>{L, R, l8, sl, r8, sr, pc, pe, Ks, d.C64, d.r, d.rp}, W, N, Ks, d.r, d.C64, s);
+    };
+    if (!from_q || d.r == 0)
+        residual(std::integral_constant<int, 0>{});
+    else if (!d.mxb)
+        residual(std::integral_constant<int, 1>{});
+    else if (d.mxb_elem == 8)
+        residual(std::integral_constant<int, 2>{});
+    else
+        residual(std::integral_constant<int, 3>{});
     return hipGetLastError();
 }
 

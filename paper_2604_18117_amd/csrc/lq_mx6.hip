@@ -74,13 +74,18 @@ __device__ __forceinline__ v6u fp6_block_from_bf16(v32bf h, float sc)
 // ---------------------------------------------------------------------------------------------
 // offline packing of the factors: one thread per (row, block of 32)
 // ---------------------------------------------------------------------------------------------
-// (src_len: row length of the source; len: of the layout, a multiple of 128 for R: blocks past the source are zero)
-__global__ __launch_bounds__(256) void mx6_pack_rows_kernel(const float* A, int rows, int len, int src_len, int mode, int r,
-                                                            int rp, uint8_t* slots, uint8_t* scales)
+// Rows of R, then rows of L.  (Ks: row length of R's source; K: of the layout, a multiple of 128: blocks past the source are zero)
+__global__ __launch_bounds__(256) void mx6_pack_rows_kernel(const float* L, const float* R, int N, int K, int Ks, int r, int rp,
+                                                            uint8_t* lslots, uint8_t* lscales, uint8_t* rslots, uint8_t* rscales)
 {
-    const int nb = len >> 5;
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t nr = (size_t)r * (K >> 5);
+    const int mode = idx < nr ? 0 : 1;
+    if (mode) idx -= nr;
+    const int nb = mode ? r >> 5 : K >> 5, rows = mode ? N : r, src_len = mode ? r : Ks;
     if (idx >= (size_t)rows * nb) return;
+    const float* A = mode ? L : R;
+    uint8_t *slots = mode ? lslots : rslots, *scales = mode ? lscales : rscales;
     const int row = (int)(idx / nb), b = (int)(idx % nb);
     float v[32];
     float a = 0.f;
@@ -107,11 +112,9 @@ hipError_t launch_pack_rows_mx6(const Dims& d, const float* L, const float* R, u
     const PackedLayout pl = packed_layout(d);
     if (d.r == 0) return hipSuccess;
     const int N = (int)d.N, K = (int)d.K;
-    const size_t nr = (size_t)d.r * (K / 32), nl = (size_t)N * (d.r / 32);
-    hipLaunchKernelGGL(mx6_pack_rows_kernel, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, s, R, d.r, K, (int)d.Ks, 0, d.r, d.rp,
-                       packed + pl.off_rq, packed + pl.off_sr);
-    hipLaunchKernelGGL(mx6_pack_rows_kernel, dim3((unsigned)((nl + 255) / 256)), dim3(256), 0, s, L, N, d.r, d.r, 1, d.r, d.rp,
-                       packed + pl.off_lq, packed + pl.off_sl);
+    const size_t nt = (size_t)d.r * (K / 32) + (size_t)N * (d.r / 32);
+    hipLaunchKernelGGL(mx6_pack_rows_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, L, R, N, K, (int)d.Ks, d.r, d.rp,
+                       packed + pl.off_lq, packed + pl.off_sl, packed + pl.off_rq, packed + pl.off_sr);
     return hipGetLastError();
 }
 

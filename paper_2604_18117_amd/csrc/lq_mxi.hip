@@ -18,7 +18,7 @@
 // product's accumulators.
 //
 // Contract beyond the general one: block maxima are zero or lie in [2^-100, 2^120].
-#include "lq_internal.h"
+#include "lq_pack.h"
 
 #include <type_traits>
 
@@ -78,26 +78,23 @@ __device__ __forceinline__ float mxint_value(int code, uint32_t field, int bits)
     return ldexpf((float)code, ((int)field - 127) - (bits - 2));
 }
 
-__global__ __launch_bounds__(256) void mxi_fill_kernel(uint8_t* p, size_t n, uint8_t v)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 // ---------------------------------------------------------------------------------------------
 // offline packing
 // ---------------------------------------------------------------------------------------------
-// Factors: one thread per (row, block of 32).  mode 0: rows of R, blocks along K; mode 1: rows of L,
-// blocks along the rank.  Stores the dequantised elements as bf16 in operand order and the E8M0 bytes
-// row-major.
-__global__ __launch_bounds__(256) void mxi_pack_rows_kernel(const float* A, int rows, int len, int mode, int bits,
-                                                            int r, int rp, uint8_t* vals, uint8_t* ebytes)
+// Factors: one thread per (row, block of 32).  Rows of R, blocks along K, then rows of L, blocks along the rank.
+// Stores the dequantised elements as bf16 in operand order and the E8M0 bytes row-major.
+__global__ __launch_bounds__(256) void mxi_pack_rows_kernel(const float* L, const float* R, int N, int K, int bits, int r, int rp,
+                                                            uint8_t* lvals, uint8_t* lebytes, uint8_t* rvals, uint8_t* rebytes)
 {
-    const int nb = len >> 5;
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t nr = (size_t)r * (K >> 5);
+    const int mode = idx < nr ? 0 : 1;
+    if (mode) idx -= nr;
+    const int nb = mode ? r >> 5 : K >> 5, rows = mode ? N : r;
     if (idx >= (size_t)rows * nb) return;
+    uint8_t *vals = mode ? lvals : rvals, *ebytes = mode ? lebytes : rebytes;
     const int row = (int)(idx / nb), b = (int)(idx % nb);
-    const float* v = A + (size_t)row * len + 32 * b;
+    const float* v = (mode ? L : R) + (size_t)row * (mode ? r : K) + 32 * b;
     float a = 0.f;
     for (int i = 0; i < 32; ++i) a = fmaxf(a, fabsf(v[i]));
     const uint32_t field = exp_field(a);
@@ -110,42 +107,37 @@ __global__ __launch_bounds__(256) void mxi_pack_rows_kernel(const float* A, int 
     }
 }
 
-// Residual and its MXINT4 codes: one wavefront per (n, 64-chunk), lane = k % 64 (two blocks of 32).
-__global__ __launch_bounds__(256) void mxi_pack_p_kernel(const float* W, const float* L, const float* R, int N, int K,
-                                                         int r, int rp, int from_q, const uint8_t* lv,
-                                                         const uint8_t* rv, uint8_t* pq, uint8_t* pe)
-{
-    const int lane = threadIdx.x & 63;
-    const int C64 = K >> 6, CQ = (C64 + 3) >> 2;
-    const size_t wid = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (wid >= (size_t)N * C64) return;
-    const int n = (int)(wid / C64), c = (int)(wid % C64);
-    const int k = c * 64 + lane;
-    double d = 0.0;
-    for (int j = 0; j < r; ++j) {
-        double lh, rh;
-        if (from_q) {  // the dequantised elements, exact in bf16
-            lh = (double)bf16_value(*(const uint16_t*)(lv + mxi_lt_offset(n, j, rp)));
-            rh = (double)bf16_value(*(const uint16_t*)(rv + mxi_rq_offset(j, k, r)));
-        } else {
-            lh = (double)L[(size_t)n * r + j];
-            rh = (double)R[(size_t)j * K + k];
-        }
-        d = fma(lh, rh, d);
+// Residual of a 64-chunk (two blocks of 32): MXINT4 codes and scale bytes.  Factors: the dequantised elements (exact in
+// bf16) or, from_q = 0, as given.
+struct PackMxiResidual {
+    const float *L, *R;
+    const uint8_t *lv, *rv;
+    uint8_t *pq, *pe;
+    int K, r, rp, from_q;
+    __device__ float lhat(int n, int j) const
+    {
+        return from_q ? bf16_value(*(const uint16_t*)(lv + mxi_lt_offset(n, j, rp))) : L[(size_t)n * r + j];
     }
-    const float P = (float)((double)W[(size_t)n * K + k] - d);
-    float a = fabsf(P);
+    __device__ float rhat(int j, int k) const
+    {
+        return from_q ? bf16_value(*(const uint16_t*)(rv + mxi_rq_offset(j, k, r))) : R[(size_t)j * K + k];
+    }
+    __device__ void encode(int n, int c, const float (&P)[1][16], int q) const
+    {
+        float a = pack_amax(P[0]);
+        a = fmaxf(a, __shfl_xor(a, 16));  // lanes q, q ^ 1 hold the block
+        const uint32_t field = exp_field(a);
+        uint32_t w[2] = {0u, 0u};
 #pragma unroll
-    for (int o = 16; o >= 1; o >>= 1) a = fmaxf(a, __shfl_xor(a, o, 64));  // block of 32 = half a wavefront
-    const uint32_t field = exp_field(a);
-    const int q = mxint_code(P, field, 4);
-    uint32_t w = nib_put(lane & 7, q < 0 ? 1u : 0u, (uint32_t)(q < 0 ? -q : q));
-    w |= __shfl_xor(w, 1, 64);
-    w |= __shfl_xor(w, 2, 64);
-    w |= __shfl_xor(w, 4, 64);
-    if ((lane & 7) == 0) *(uint32_t*)(pq + mxi_frag_offset(n, k, C64)) = w;
-    if ((lane & 31) == 0) pe[mxi_scale_offset(n, c, lane >> 5, CQ)] = (uint8_t)(field + 7);
-}
+        for (int e = 0; e < 16; ++e) {
+            const int code = mxint_code(P[0][e], field, 4);
+            w[e >> 3] |= nib_put(e & 7, code < 0 ? 1u : 0u, (uint32_t)(code < 0 ? -code : code));
+        }
+        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+        *(u2*)(pq + mxi_frag_offset(n, c * 64 + 16 * q, K >> 6)) = u2{w[0], w[1]};
+        if ((q & 1) == 0) pe[mxi_scale_offset(n, c, q >> 1, ((K >> 6) + 3) >> 2)] = (uint8_t)(field + 7);
+    }
+};
 
 struct MxiPackedPtrs {
     uint8_t *pq, *pe, *lv, *le, *rv, *re;
@@ -162,24 +154,20 @@ hipError_t launch_pack_mxi(const Dims& d, int from_q, const float* W, const floa
 {
     const MxiPackedPtrs pp = mxi_packed_ptrs(d, packed);
     const int N = (int)d.N, K = (int)d.K;
-    // scale bytes of the padding chunks of the last quad: 2^0
-    const size_t pe_bytes = (size_t)(N / 32) * ((d.C64 + 3) / 4) * 256;
-    if (d.smooth) {  // reciprocals of the smoothing vector start at 1
-        const hipError_t e = launch_set_smoothing(d, nullptr, packed, s);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(mxi_fill_kernel, dim3((unsigned)((pe_bytes + 255) / 256)), dim3(256), 0, s, pp.pe, pe_bytes,
-                       (uint8_t)127);
+    PackFill fill;
+    fill.n = 0;
+    fill.blob = (uint32_t*)packed;
+    fill.tag = make_tag(d, LQ_BLOB_PACKED, 0);
+    if (d.C64 % 4) fill.add(pp.pe, (size_t)(N / 32) * ((d.C64 + 3) / 4) * 256, 0x7F7F7F7Fu);        // padding chunks of the last quad: 2^0
+    if (d.smooth) fill.add(packed + packed_layout(d).off_rg, (size_t)K * 4, 0x3F800000u);            // reciprocals start at 1
+    const hipError_t e = launch_pack_fill(fill, s);
+    if (e != hipSuccess) return e;
     if (d.r > 0) {
-        const size_t nr = (size_t)d.r * (K / 32), nl = (size_t)N * (d.r / 32);
-        hipLaunchKernelGGL(mxi_pack_rows_kernel, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, s, R, d.r, K, 0,
-                           d.bw_bits, d.r, d.rp, pp.rv, pp.re);
-        hipLaunchKernelGGL(mxi_pack_rows_kernel, dim3((unsigned)((nl + 255) / 256)), dim3(256), 0, s, L, N, d.r, 1,
-                           d.bw_bits, d.r, d.rp, pp.lv, pp.le);
+        const size_t nt = (size_t)d.r * (K / 32) + (size_t)N * (d.r / 32);
+        hipLaunchKernelGGL(mxi_pack_rows_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, L, R, N, K, d.bw_bits, d.r, d.rp, pp.lv,
+                           pp.le, pp.rv, pp.re);
     }
-    const size_t waves = (size_t)N * d.C64;
-    hipLaunchKernelGGL(mxi_pack_p_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, W, L, R, N, K, d.r, d.rp,
-                       from_q, pp.lv, pp.rv, pp.pq, pp.pe);
+    pack_residual<1>(PackMxiResidual{L, R, pp.lv, pp.rv, pp.pq, pp.pe, K, d.r, d.rp, from_q}, W, N, K, d.r, d.C64, s);
     return hipGetLastError();
 }
 

@@ -4,16 +4,9 @@
 //   (SINT4-style blocks, App. A.3), or the literal SINT4 blocks: 64 values, FP16 scale.  Also the inverse
 //   views used by tests.
 // Quantiser: s = amax / qmax, code = rne(v * (qmax / amax)), symmetric range, all-zero -> s = 1.
-#include "lq_internal.h"
+#include "lq_pack.h"
 
 namespace lq {
-
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 
 __device__ __forceinline__ void scale_pair(float amax, float qmax, float* s, float* inv)
 {
@@ -41,115 +34,98 @@ __device__ __forceinline__ size_t rq_offset(int j, int k, int r)
     return ((size_t)((size_t)c * (r >> 4) + (j >> 4)) * 64 + (j & 15) + 16 * kq) * 16 + (k & 15);
 }
 
-// ---- Q2(R): one workgroup per row j ------------------------------------------------------
-__global__ __launch_bounds__(256) void pack_r_kernel(const float* R, int K, int r, float qmax,
-                                                     int8_t* rq, float* sr)
-{
-    __shared__ float red[4];
-    const int j = blockIdx.x, tid = threadIdx.x;
-    float a = 0.f;
-    for (int k = tid; k < K; k += 256) a = fmaxf(a, fabsf(R[(size_t)j * K + k]));
-    a = wave_max(a);
-    if ((tid & 63) == 0) red[tid >> 6] = a;
-    __syncthreads();
-    a = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    float s, inv;
-    scale_pair(a, qmax, &s, &inv);
-    if (tid == 0) sr[j] = s;
-    for (int k = tid; k < K; k += 256)
-        rq[rq_offset(j, k, r)] = (int8_t)quant_code(R[(size_t)j * K + k], inv, qmax);
-}
+// Q2 of a row of L or R
+struct PackIntRows {
+    float qmax;
+    __device__ void scale(float amax, float* s, float* inv) const { scale_pair(amax, qmax, s, inv); }
+    template <typename V>
+    __device__ uint32_t quad(V v, float inv) const
+    {
+        uint32_t w = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w |= (uint32_t)(quant_code(v[i], inv, qmax) & 0xFF) << (8 * i);
+        return w;
+    }
+    __device__ size_t r_offset(int j, int k, int r) const { return rq_offset(j, k, r); }
+};
 
-// ---- Q2(L): one thread per row n ---------------------------------------------------------
-__global__ __launch_bounds__(256) void pack_l_kernel(const float* L, int N, int r, int rp,
-                                                     float qmax, int8_t* lq, float* sl)
-{
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
-    float a = 0.f;
-    for (int j = 0; j < r; ++j) a = fmaxf(a, fabsf(L[(size_t)n * r + j]));
-    float s, inv;
-    scale_pair(a, qmax, &s, &inv);
-    sl[n] = s;
-    for (int j = 0; j < rp; ++j)
-        lq[(size_t)n * rp + j] = (j < r) ? (int8_t)quant_code(L[(size_t)n * r + j], inv, qmax) : (int8_t)0;
-}
-
-// ---- residual + Q1: one wavefront per (n, group) -------------------------------------------
+// Residual of a scale group of GC chunks: dequantised (from_q) or given factors; Q1 = INT4, fp32 scale (times 2^6, lq_internal.h)
+// or SINT4's FP16 scale (stored as its bits; codes against the stored scale).
 template <int GC>
-__global__ __launch_bounds__(256) void pack_p_kernel(const float* W, const float* L, const float* R,
-                                                     int N, int K, int r, int rp, int from_q,
-                                                     const int8_t* lq, const float* sl,
-                                                     const int8_t* rq, const float* sr,
-                                                     uint8_t* pq, float* swT, int ga)
-{
-    const int lane = threadIdx.x & 63;
-    const int G = K / (64 * GC), C64 = K >> 6;
-    const size_t wid = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (wid >= (size_t)N * G) return;
-    const int n = (int)(wid / G), gi = (int)(wid % G);
-    float P[GC];
-    float a = 0.f;
+struct PackIntResidual {
+    const float *L, *R;
+    const int8_t* lq;
+    const float* sl;
+    const int8_t* rq;
+    const float* sr;
+    uint8_t* pq;
+    float* swT;
+    int N, K, r, rp, from_q, ga;
+    __device__ float lhat(int n, int j) const { return from_q ? (float)lq[(size_t)n * rp + j] * sl[n] : L[(size_t)n * r + j]; }
+    __device__ float rhat(int j, int k) const { return from_q ? (float)rq[rq_offset(j, k, r)] * sr[j] : R[(size_t)j * K + k]; }
+    __device__ void encode(int n, int g, const float (&P)[GC][16], int q) const
+    {
+        float a = pack_amax(P[0]);
+        if constexpr (GC == 2) a = fmaxf(a, pack_amax(P[1]));
+        a = fmaxf(a, __shfl_xor(a, 16));
+        a = fmaxf(a, __shfl_xor(a, 32));
+        float s, inv;
+        if (ga) {
+            const uint32_t bits = sint4_scale(a, &inv);
+            if (q == 0) ((uint32_t*)swT)[(size_t)g * N + n] = bits;
+        } else {
+            scale_pair(a, 7.0f, &s, &inv);
+            if (q == 0) swT[(size_t)g * N + n] = ldexpf(s, 6);
+        }
 #pragma unroll
-    for (int cc = 0; cc < GC; ++cc) {
-        const int k = (gi * GC + cc) * 64 + lane;
-        double d = 0.0;
-        for (int j = 0; j < r; ++j) {
-            float lh, rh;
-            if (from_q) {
-                lh = (float)lq[(size_t)n * rp + j] * sl[n];
-                rh = (float)rq[rq_offset(j, k, r)] * sr[j];
-            } else {
-                lh = L[(size_t)n * r + j];
-                rh = R[(size_t)j * K + k];
+        for (int cc = 0; cc < GC; ++cc) {
+            // 16 six-bit fields = dwords 3 (q % 2) .. 3 (q % 2) + 2 of the operand of K half q / 2
+            uint32_t w[3] = {0u, 0u, 0u};
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const uint64_t v = (uint64_t)f6_field(quant_code(P[cc][e], inv, 7.0f)) << ((6 * e) & 31);
+                w[(6 * e) >> 5] |= (uint32_t)v;
+                if (((6 * e) & 31) > 26) w[((6 * e) >> 5) + 1] |= (uint32_t)(v >> 32);
             }
-            d = fma((double)lh, (double)rh, d);
+            uint8_t* ch = pq + f6_chunk_offset(n, (g * GC + cc) * 64, K >> 6);
+            const int slot = (n & 31) + 32 * (q >> 1);
+            typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+            if (q & 1) {
+                *(uint32_t*)(ch + f6_dword_offset(slot, 3)) = w[0];
+                *(u2*)(ch + f6_dword_offset(slot, 4)) = u2{w[1], w[2]};
+            } else {
+                *(u2*)(ch + f6_dword_offset(slot, 0)) = u2{w[0], w[1]};
+                *(uint32_t*)(ch + f6_dword_offset(slot, 2)) = w[2];
+            }
         }
-        P[cc] = (float)((double)W[(size_t)n * K + k] - d);
-        a = fmaxf(a, fabsf(P[cc]));
     }
-    a = wave_max(a);
-    float s, inv;
-    if (ga) {  // FP16 scale, stored as its bits; codes against the stored scale
-        const uint32_t bits = sint4_scale(a, &inv);
-        if (lane == 0) ((uint32_t*)swT)[(size_t)gi * N + n] = bits;
-    } else {
-        scale_pair(a, 7.0f, &s, &inv);
-        if (lane == 0) swT[(size_t)gi * N + n] = ldexpf(s, 6);
-    }
-#pragma unroll
-    for (int cc = 0; cc < GC; ++cc) {
-        const int k = (gi * GC + cc) * 64 + lane;
-        const int q = quant_code(P[cc], inv, 7.0f);
-        // 6-bit fields: lane (half = lane / 32, i = lane % 32) owns bits 6i .. 6i+5 of its half's 192-bit operand;
-        // the six dwords of a half are OR-reduced over its 32 lanes
-        const int i = lane & 31, bit = 6 * i;
-        const uint64_t v = (uint64_t)f6_field(q) << (bit & 31);
-        uint32_t mine = 0u;
-#pragma unroll
-        for (int dd = 0; dd < 6; ++dd) {
-            uint32_t w = (bit >> 5) == dd ? (uint32_t)v : (bit >> 5) + 1 == dd ? (uint32_t)(v >> 32) : 0u;
-#pragma unroll
-            for (int o = 16; o >= 1; o >>= 1) w |= __shfl_xor(w, o, 64);
-            if (i == dd) mine = w;
+};
+
+__global__ __launch_bounds__(256) void pack_fill_kernel(PackFill f)
+{
+    write_tag(f.blob, f.tag);
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    size_t begin = 0;
+    for (int k = 0; k < f.n; ++k) {
+        if (i < f.end[k]) {
+            f.p[k][i - begin] = f.v[k];
+            return;
         }
-        if (i < 6) *(uint32_t*)(pq + f6_chunk_offset(n, k, C64) + f6_dword_offset((n & 31) + 32 * (lane >> 5), i)) = mine;
+        begin = f.end[k];
     }
 }
-
-// blob header (offline packing: a launch of its own; the activation kernels write theirs themselves)
-__global__ void write_tag_kernel(uint32_t* dst, BlobTag t) { write_tag(dst, t); }
-hipError_t launch_write_tag(uint8_t* blob, const BlobTag& t, hipStream_t s)
+hipError_t launch_pack_fill(const PackFill& f, hipStream_t s)
 {
-    hipLaunchKernelGGL(write_tag_kernel, dim3(1), dim3(64), 0, s, (uint32_t*)blob, t);
+    const size_t n = f.n ? f.end[f.n - 1] : 1;
+    hipLaunchKernelGGL(pack_fill_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, f);
     return hipGetLastError();
 }
 
-// reciprocals of the smoothing vector (gamma == nullptr: ones)
+// reciprocals of the smoothing vector
 __global__ __launch_bounds__(256) void smooth_recip_kernel(const float* gamma, int Ks, int K, float* rg)
 {
     const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k < K) rg[k] = (gamma && k < Ks) ? __fdiv_rn(1.0f, gamma[k]) : 1.0f;  // (k >= Ks: layout padding)
+    if (k < K) rg[k] = k < Ks ? __fdiv_rn(1.0f, gamma[k]) : 1.0f;  // (k >= Ks: layout padding)
 }
 
 hipError_t launch_set_smoothing(const Dims& d, const float* gamma, uint8_t* packed, hipStream_t s)
@@ -171,27 +147,18 @@ hipError_t launch_pack_int(const Dims& d, int from_q, const float* W, const floa
     uint8_t* pq = packed + pl.off_pq;
     float* swT = (float*)(packed + pl.off_sw);
     const int N = (int)d.N, K = (int)d.K;
-    if (d.r > 0) {
-        hipLaunchKernelGGL(pack_r_kernel, dim3(d.r), dim3(256), 0, s, R, K, d.r, (float)d.qmax_bw, rq, sr);
-        hipLaunchKernelGGL(pack_l_kernel, dim3((N + 255) / 256), dim3(256), 0, s, L, N, d.r, d.rp,
-                           (float)d.qmax_bw, lq, sl);
-    } else {
-        // no branch: sl must still hold finite values (the forward multiplies 0 by it)
-        hipLaunchKernelGGL(pack_l_kernel, dim3((N + 255) / 256), dim3(256), 0, s, (const float*)nullptr, N, 0, 0,
-                           1.0f, lq, sl);
-    }
-    if (d.smooth) {
-        const hipError_t e = launch_set_smoothing(d, nullptr, packed, s);
-        if (e != hipSuccess) return e;
-    }
-    const size_t waves = (size_t)N * d.G;
-    const unsigned blocks = (unsigned)((waves + 3) / 4);
+    PackFill fill;
+    fill.n = 0;
+    fill.blob = (uint32_t*)packed;
+    fill.tag = make_tag(d, LQ_BLOB_PACKED, 0);
+    if (d.smooth) fill.add(packed + pl.off_rg, (size_t)K * 4, 0x3F800000u);  // reciprocals of the smoothing vector start at 1
+    const hipError_t e = launch_pack_fill(fill, s);
+    if (e != hipSuccess) return e;
+    pack_row_factors(PackIntRows{(float)d.qmax_bw}, L, R, N, K, K, d.r, d.rp, (uint8_t*)lq, sl, (uint8_t*)rq, sr, s);
     if (d.g == 64)
-        hipLaunchKernelGGL(pack_p_kernel<1>, dim3(blocks), dim3(256), 0, s, W, L, R, N, K, d.r, d.rp, from_q, lq,
-                           sl, rq, sr, pq, swT, d.ga ? 1 : 0);
+        pack_residual<1>(PackIntResidual<1>{L, R, lq, sl, rq, sr, pq, swT, N, K, d.r, d.rp, from_q, d.ga ? 1 : 0}, W, N, K, d.r, d.G, s);
     else
-        hipLaunchKernelGGL(pack_p_kernel<2>, dim3(blocks), dim3(256), 0, s, W, L, R, N, K, d.r, d.rp, from_q, lq,
-                           sl, rq, sr, pq, swT, 0);
+        pack_residual<2>(PackIntResidual<2>{L, R, lq, sl, rq, sr, pq, swT, N, K, d.r, d.rp, from_q, 0}, W, N, K, d.r, d.G, s);
     return hipGetLastError();
 }
 
