@@ -246,17 +246,26 @@ hipError_t launch_unpack_act_mxi(const Dims& d, const uint8_t* act, int64_t M, c
 }
 
 // ---------------------------------------------------------------------------------------------
-// activation kernel.  Same decomposition as the other families (16 token rows per workgroup, lane =
-// (row l%16, 16-value quarter l/16 of each 64-chunk), chunks dealt round-robin to 4 wavefronts), but
-// every scale is local to a block of 32, so there is no pass over the whole row before coding: the row
-// is streamed through a few chunk slots and K is not limited by the register file.
+// activation kernel.  Every scale is local to a block of 32, so there is no pass over the whole row before coding: the row
+// is streamed and K is not limited by the register file.  A workgroup is ROWG x KW wavefronts; wavefront (rg, w) owns RPW
+// groups of 16 token rows and the chunks c = w mod KW of K; lane l works on row l%16 of each group and on the 16-value
+// quarter l/16 of a 64-chunk.
+//
+// What bounds it: the dequantised R (2 r K bytes) passes through every workgroup, at rank 128 several times the bytes of X.
+// Large batches (ROWG = 2) copy each super-step of KW chunks of it to LDS once per workgroup, directly and one super-step
+// ahead, and a fragment read from there serves RPW groups of rows; small ones (ROWG = 1) have each wavefront read its own
+// chunks' fragments from the L2 while it codes X.  X is requested two super-steps ahead.  Chain of 16384 x 1152 -> 4608 -> 1152 at
+// rank 128: first activation step 31.5 -> 21.7 us, step from codes 60.7 -> 30.9 us (16 rows and four wavefronts per workgroup
+// before, R straight from the L2); 64 rows of 4608, rank 128: 19.5 -> 16.0 us.
+// T's sums run over a wavefront's chunks in ascending order and then over the wavefronts; the same sizes take the same
+// form in the step from codes, so a hand-off gives the bits of the two-call path.
 // ---------------------------------------------------------------------------------------------
 struct MxiActParams {
     const void* X;
     const int8_t* cb;    // from-codes variant: M x K MXINT8 codes of a quantized hand-off, row-major
     const uint8_t* cbe;  // ... and their E8M0 bytes, M x K/32
     int64_t ldx;
-    int M, K, C64, CQ, r, rp;
+    int M, Mp, K, C64, CQ, r, rp;
     const uint8_t* rv;
     uint8_t* xq;
     uint8_t* xe;
@@ -329,84 +338,129 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)  // upper halv
 // FROMC: the branch half of the step alone, from the MXINT8 codes of a quantized hand-off (the producing layer's
 // epilogue has already written this layer's main codes and scales): 16 code bytes and a scale byte replace the 16 values
 // of X, code * 2^(s-6) is the dequantised bf16 element; the contraction and the re-quantisation are the same code.
-template <bool BF16IN, int NJB, bool SM = false, bool FROMC = false>
-__global__ __launch_bounds__(256) void mxi_act_kernel(MxiActParams p)
+template <bool BF16IN, int NJB, bool SM, bool FROMC, int RPW, int ROWG, int KW, bool DBG>
+__global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams p)
 {
     write_tag(p.tag_dst, p.tag);
     constexpr bool BF16 = BF16IN && !SM;  // representation of a chunk in registers
     constexpr int NJA = NJB > 0 ? NJB : 1;
-    constexpr int PF = 2;  // 64-chunks in flight per wavefront (measured: 2 beats 4, 6, 8 -- fewer registers, more resident workgroups)
-    __shared__ float s_acc[4][NJA][64][4];
+    constexpr int NG = RPW * ROWG;               // groups of 16 rows per workgroup
+    constexpr int RCHUNK = NJB * 2048;           // bytes of R per 64-chunk
+    constexpr int RBUF = KW * RCHUNK;            // ... per super-step
+    constexpr bool STAGE = NJB > 0 && ROWG > 1;  // R goes through LDS
+    constexpr int RED = NG * KW * NJA * 1024;    // partial sums of the wavefronts of a row group
+    constexpr int LDS_BYTES = NJB == 0 ? 16 : STAGE && 2 * RBUF > RED ? 2 * RBUF : RED;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wid & (KW - 1), rgrp = wid / KW;
     const int r16 = lane & 15, kq = lane >> 4;
-    const int row = blockIdx.x * 16 + r16;
-    const bool row_ok = row < p.M;
+    const int row0 = blockIdx.x * (16 * NG) + rgrp * (16 * RPW);  // first row of this wavefront
     const int C64 = p.C64;
-    const int nmy = (C64 - wave + 3) >> 2;  // chunks of this wavefront: c = wave + 4 * ci, ci < nmy
+    const int Mp = p.Mp;
+    const int nss = (C64 + KW - 1) / KW;
 
-    // No scale spans more than a block of 32, so the row is streamed: PF chunks are in flight, a slot
-    // is refilled as soon as its chunk has been coded.
-    MxiChunk<BF16> xc[PF];
-    auto load_x = [&](MxiChunk<BF16>& ch, size_t koff, bool ok) {
-        if constexpr (FROMC) {  // 16 code bytes in w[0..3], the block's scale byte in w[4]
-            static_assert(!FROMC || (BF16IN && !SM), "the from-codes variant reuses the packed chunk registers");
-            v4i a = {0, 0, 0, 0};
-            uint32_t e = 0u;
-            if (ok) {
-                a = *(const v4i*)(p.cb + (size_t)row * p.K + koff);
-                e = p.cbe[(size_t)row * (p.K >> 5) + (koff >> 5)];
+    // Rows past M count as zeros, chunks past the end are clamped and not used: the loads are unconditional (the wait
+    // below counts them).  Groups past Mp (the last workgroup) are not stored.
+    struct XSet { MxiChunk<BF16> g[RPW]; };
+    XSet xs[2];
+    auto load_x = [&](XSet& st, int ss) {
+        int c = KW * ss + wave;
+        c = c < C64 ? c : C64 - 1;
+#pragma unroll
+        for (int g = 0; g < RPW; ++g) {
+            MxiChunk<BF16>& ch = st.g[g];
+            int row = row0 + 16 * g + r16;
+            row = row < p.M ? row : p.M - 1;
+            const size_t koff = (size_t)c * 64 + kq * 16;
+            if constexpr (FROMC) {  // 16 code bytes in w[0..3], the block's scale byte in w[4]
+                static_assert(!FROMC || (BF16IN && !SM), "the from-codes variant reuses the packed chunk registers");
+                const v4i a = *(const v4i*)(p.cb + (size_t)row * p.K + koff);
+                ch.w[0] = a[0]; ch.w[1] = a[1]; ch.w[2] = a[2]; ch.w[3] = a[3];
+                ch.w[4] = p.cbe[(size_t)row * (p.K >> 5) + (koff >> 5)];
+            } else if constexpr (SM)
+                smooth_load<BF16IN, 16>(ch.v, p.X, (size_t)row * p.ldx + koff, p.rg + koff, true);
+            else
+                ch.load(p.X, (size_t)row * p.ldx + koff, true);
+        }
+    };
+    // R of super-step ss -> LDS buffer: lane l of an instruction writes 16 bytes at 16 l behind the wave-uniform address
+    constexpr int RI = RBUF / 1024 / (KW * ROWG);  // 1 KB instructions per wavefront
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc((void*)p.rv, 0, C64 * RCHUNK, 0x00020000);
+    auto load_r = [&](int ss) {
+        if constexpr (STAGE) {
+#pragma unroll
+            for (int i = 0; i < RI; ++i) {
+                const int piece = wid * RI + i;              // of RBUF / 1024
+                int c = KW * ss + piece / (RCHUNK / 1024);    // (a chunk past the end is clamped: fetched, not used)
+                c = c < C64 ? c : C64 - 1;
+                uint8_t* dst = lds + (ss & 1) * RBUF + piece * 1024;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_r, (__attribute__((address_space(3))) void*)dst, 16, lane * 16,
+                                                         c * RCHUNK + (piece % (RCHUNK / 1024)) * 1024, 0, 0);
             }
-            ch.w[0] = a[0]; ch.w[1] = a[1]; ch.w[2] = a[2]; ch.w[3] = a[3];
-            ch.w[4] = e;
-        } else if constexpr (SM)
-            smooth_load<BF16IN, 16>(ch.v, p.X, (size_t)row * p.ldx + koff, p.rg + koff, ok);
-        else
-            ch.load(p.X, (size_t)row * p.ldx + koff, ok);
+        }
     };
-#pragma unroll
-    for (int i = 0; i < PF; ++i) load_x(xc[i], (size_t)(wave + 4 * i) * 64 + kq * 16, row_ok && i < nmy);
-    // dequantised R fragments (bf16): first chunk now, later ones one chunk ahead.  Two register sets up to rank 64; one
-    // above (refilled right after the chunk's MFMAs): a second set of 64 or more registers would halve the occupancy
-    constexpr int RB = NJB > 4 ? 1 : 2;
-    v4i bvs[RB][NJA][2];
-    auto load_r = [&](int slot, int ci) {
-        int c = wave + 4 * ci;
-        c = c < C64 ? c : C64 - 1;  // clamped: a fragment past the end is fetched but not used
-#pragma unroll
-        for (int jb = 0; jb < NJB; ++jb)
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                bvs[slot][jb][u] = *(const v4i*)(p.rv + ((((size_t)((size_t)c * NJB + jb) * 2 + u) * 64 + lane) * 16));
-    };
-    load_r(0, 0);
 
-    v4f acc[NJA];
+    v4f acc[RPW][NJA];
 #pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) acc[jb] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int g = 0; g < RPW; ++g)
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb) acc[g][jb] = v4f{0.f, 0.f, 0.f, 0.f};
 
-    for (int base = 0; base < nmy; base += PF) {
+    // One super-step: request R of the next one, code this one's X, request X of the one after the next, multiply.
+    auto step = [&](XSet& st, int ss) {
+        const int c = KW * ss + wave;
+        const bool have = c < C64;  // wave-uniform
+        // fragment pairs of R read ahead: an LDS round trip is longer than a pair's products, an L2 round trip much longer
+        constexpr int RD = NJA < (STAGE ? 3 : 4) ? NJA : STAGE ? 3 : 4;
+        v4i rf[RD][2];
+        auto read_pair = [&](int jb) {
 #pragma unroll
-    for (int sl = 0; sl < PF; ++sl) {
-        const int ci = base + sl;
-        const int c = wave + 4 * ci;
-        if constexpr (RB == 2) load_r((sl + 1) & 1, ci + 1);
-        if (ci < nmy) {  // wave-uniform
+            for (int u = 0; u < 2; ++u) {
+                if constexpr (STAGE)
+                    rf[jb % RD][u] = *(const v4i*)(lds + (ss & 1) * RBUF + wave * RCHUNK + lane * 16 + (jb * 2 + u) * 1024);
+                else
+                    rf[jb % RD][u] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_r, lane * 16, (have ? c : 0) * RCHUNK + (jb * 2 + u) * 1024, 0));
+            }
+        };
+        load_r(ss + 1);
+        if constexpr (NJB > 0 && !STAGE) {
+#pragma unroll
+            for (int jb = 0; jb < RD; ++jb) read_pair(jb);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        v4i au[RPW][2];
+#pragma unroll
+        for (int g = 0; g < RPW; ++g) {
+            MxiChunk<BF16> ch = st.g[g];
+            const int row = row0 + 16 * g + r16;
+            const bool row_ok = row < p.M;
+            if (row0 + 16 * g + 16 > p.M && !row_ok) {  // only in the last workgroup
+                if constexpr (BF16) {
+#pragma unroll
+                    for (int d = 0; d < 8; ++d) ch.w[d] = 0u;
+                } else {
+#pragma unroll
+                    for (int d = 0; d < 16; ++d) ch.v[d] = 0.f;
+                }
+            }
             uint32_t field;
             if constexpr (FROMC) {
-                field = xc[sl].w[4];
+                field = ch.w[4];
             } else {
                 float m = 0.f;
                 if constexpr (BF16) {
                     // |bf16| is monotonic in its low 15 bits: packed unsigned 16-bit max, two values per op
                     us2 m2 = {0, 0};
 #pragma unroll
-                    for (int d = 0; d < 8; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, xc[sl].w[d] & 0x7FFF7FFFu));
+                    for (int d = 0; d < 8; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, ch.w[d] & 0x7FFF7FFFu));
                     const uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
                     m = __uint_as_float(mm << 16);
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(xc[sl].get(i)));
+                    for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(ch.get(i)));
                 }
                 const float ab = fmaxf(m, __shfl_xor(m, 16, 64));  // block of 32 = lanes kq, kq ^ 1
                 field = exp_field(ab);
@@ -422,12 +476,12 @@ __global__ __launch_bounds__(256) void mxi_act_kernel(MxiActParams p)
                         uint32_t sum = 0u - 0xFB000000u;
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
-                            const float x = xc[sl].get(8 * h + e);
+                            const float x = ch.get(8 * h + e);
                             const uint32_t mb = __float_as_uint(__fadd_rn(fminf(__fmul_rn(fabsf(x), inv4), 7.0f), 8388608.0f));
                             const int sh = e < 4 ? 8 * e : 8 * ((e - 5) & 3) + 4;
                             sum += mb << sh;
                         }
-                        const uint32_t* w = &xc[sl].w[4 * h];
+                        const uint32_t* w = &ch.w[4 * h];
                         const uint32_t s03 = __builtin_amdgcn_perm(w[1], w[0], 0x07050301u);
                         const uint32_t s47 = __builtin_amdgcn_perm(w[3], w[2], 0x07050301u);
                         pk[h] = sum | (s03 & 0x80808080u) | ((s47 >> 4) & 0x08080808u);
@@ -435,15 +489,17 @@ __global__ __launch_bounds__(256) void mxi_act_kernel(MxiActParams p)
                 } else {
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const float x = xc[sl].get(i);
+                        const float x = ch.get(i);
                         const uint32_t mg = __float_as_uint(__fadd_rn(fminf(__fmul_rn(fabsf(x), inv4), 7.0f), 8388608.0f)) & 7u;
                         pk[i >> 3] |= nib_put(i & 7, __float_as_uint(x) >> 31, mg);
                     }
                 }
                 // lane (row, kq): block kq>>1 of the chunk, K half-block h = kq&1 -> dwords 2*(kq>>1), +1 of lane (row, h)
                 uint8_t* dst = p.xq + ((size_t)((size_t)(row >> 5) * C64 + c) * 64 + (row & 31) + 32 * (kq & 1)) * 16 + (kq >> 1) * 8;
-                *(uint2*)dst = make_uint2(pk[0], pk[1]);
-                if ((kq & 1) == 0) p.xe[mxi_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)(field + 7u);
+                if (have && row0 + 16 * g < Mp) {
+                    *(uint2*)dst = make_uint2(pk[0], pk[1]);
+                    if ((kq & 1) == 0) p.xe[mxi_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)(field + 7u);
+                }
             }
             if (NJB > 0) {
                 // ---- branch: MXINT8 of the same block, kept as dequantised bf16
@@ -452,108 +508,178 @@ __global__ __launch_bounds__(256) void mxi_act_kernel(MxiActParams p)
                     const float step = field >= 7u ? __uint_as_float((field - 6u) << 23) : 0.0f;
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
-                        v8[i] = __fmul_rn((float)(int)(int8_t)((xc[sl].w[i >> 2] >> (8 * (i & 3))) & 0xFFu), step);
+                        v8[i] = __fmul_rn((float)(int)(int8_t)((ch.w[i >> 2] >> (8 * (i & 3))) & 0xFFu), step);
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) v8[i] = mxint8_round(xc[sl].get(i), field);
+                    for (int i = 0; i < 16; ++i) v8[i] = mxint8_round(ch.get(i), field);
                 }
-                v4i au[2];
-#pragma unroll
+                #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) au[u][d] = (int)bf16_pair(v8[8 * u + 2 * d], v8[8 * u + 2 * d + 1]);
-                if (p.dbg_xb && row_ok) {
+                    for (int d = 0; d < 4; ++d) au[g][u][d] = (int)bf16_pair(v8[8 * u + 2 * d], v8[8 * u + 2 * d + 1]);
+                if (DBG && p.dbg_xb && row_ok && have) {
                     uint32_t cb[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
                         cb[i >> 2] |= ((uint32_t)(int)ldexpf(v8[i], 6 - ((int)field - 127)) & 0xFFu) << (8 * (i & 3));
                     *(v4i*)(p.dbg_xb + (size_t)row * p.K + c * 64 + kq * 16) = v4i{(int)cb[0], (int)cb[1], (int)cb[2], (int)cb[3]};
                 }
-                if (p.dbg_xbe && row_ok && (kq & 1) == 0) p.dbg_xbe[(size_t)row * (p.K >> 5) + 2 * c + (kq >> 1)] = (uint8_t)field;
+                if (DBG && p.dbg_xbe && row_ok && have && (kq & 1) == 0) p.dbg_xbe[(size_t)row * (p.K >> 5) + 2 * c + (kq >> 1)] = (uint8_t)field;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (STAGE || NJB == 0) {
+            load_x(st, ss + 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (NJB > 0) {
+            if (have) {
+                if constexpr (STAGE) {
 #pragma unroll
-                for (int jb = 0; jb < NJB; ++jb)
+                    for (int jb = 0; jb < RD; ++jb) read_pair(jb);
+                }
+#pragma unroll
+                for (int jb = 0; jb < NJB; ++jb) {
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int u = 0; u < 2; ++u)
-                        acc[jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, au[u]),
-                                                                         __builtin_bit_cast(v8bf, bvs[sl % RB][jb][u]), acc[jb], 0, 0, 0);
+#pragma unroll
+                        for (int g = 0; g < RPW; ++g)
+                            acc[g][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, au[g][u]),
+                                                                                 __builtin_bit_cast(v8bf, rf[jb % RD][u]), acc[g][jb], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (jb + RD < NJB) read_pair(jb + RD);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (STAGE) {
+                // this wavefront's share of R for the next super-step has arrived once at most the loads issued after it are
+                // outstanding: X of super-step ss + 2, at least two per row group
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * RPW) : "memory");
+            } else {
+                load_x(st, ss + 2);  // (behind the fragments: loads return in order)
             }
         }
-        if constexpr (RB == 1) load_r(0, ci + 1);
-        // refill the slot with the chunk PF positions further on
-        load_x(xc[sl], (size_t)(c + 4 * PF) * 64 + kq * 16, row_ok && ci + PF < nmy);
+    };
+    load_x(xs[0], 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_r(0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_x(xs[1], 1);
+    if constexpr (STAGE) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * RPW) : "memory");
     }
+    int ss = 0;
+    for (; ss + 1 < nss; ss += 2) {
+        step(xs[0], ss);
+        step(xs[1], ss + 1);
     }
-    if constexpr (!FROMC) {   // padding chunk of the last quad (at most one per wavefront): its scale bytes must be valid E8M0 values (2^0)
-        const int c = wave + 4 * nmy;
-        if (c < 4 * p.CQ && (kq & 1) == 0) p.xe[mxi_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)127;
-    }
-    if (NJB == 0) return;
-
+    if (ss < nss) step(xs[0], ss);
+    if constexpr (!FROMC) {   // padding chunks of the last quad: their scale bytes must be valid E8M0 values (2^0)
+        const int c = C64 + wave;
+        if (c < 4 * p.CQ && (kq & 1) == 0) {
 #pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) *(v4f*)&s_acc[wave][jb][lane][0] = acc[jb];
-    __syncthreads();
-    if (wave != 0) return;
-
-    // lane holds column j = jb*16 + lane%16 of the intermediate for token rows 4*kq + i
-    float T[NJA][4];
-#pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) {
-        v4f sum = *(const v4f*)&s_acc[0][jb][lane][0];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) {
-            const v4f o = *(const v4f*)&s_acc[w][jb][lane][0];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) sum[i] = __fadd_rn(sum[i], o[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            T[jb][i] = sum[i];
-            const int grow = blockIdx.x * 16 + 4 * kq + i;
-            if (grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = sum[i];
+            for (int g = 0; g < RPW; ++g)
+                if (row0 + 16 * g < Mp) p.xe[mxi_scale_offset(row0 + 16 * g + r16, c, kq >> 1, p.CQ)] = (uint8_t)127;
         }
     }
-    // re-quantise to MXINT8 per token and per block of 32 along the rank (two 16-column groups)
-    const int BR = p.r >> 5;
+    if constexpr (NJB > 0) {
+        const int BR = p.r >> 5;
+        constexpr int NBB = (NJB + 1) / 2;   // blocks of 32 along the rank
+        if constexpr (STAGE) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last super-step's request (clamped, unused) has landed
+            __syncthreads();
+        }
+        v4f* red = (v4f*)lds;                // [row group][wavefront][jb][lane]
 #pragma unroll
-    for (int bb = 0; bb < (NJB + 1) / 2; ++bb) {
+        for (int g = 0; g < RPW; ++g)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float tm = fmaxf(fabsf(T[2 * bb][i]), fabsf(T[(2 * bb + 1) % NJA][i]));
+            for (int jb = 0; jb < NJB; ++jb) red[(((rgrp * RPW + g) * KW + wave) * NJB + jb) * 64 + lane] = acc[g][jb];
+        __syncthreads();
+        // one (row group, block of 32 of the rank) per wavefront at a time: sum over the wavefronts, re-quantise to
+        // MXINT8; the lane holds columns (2 bb + h) * 16 + lane%16 of the intermediate for token rows 4*kq + i
+        for (int task = wid; task < NG * NBB; task += KW * ROWG) {
+            const int g = task / NBB, bb = task - g * NBB;
+            const int rbase = blockIdx.x * (16 * NG) + 16 * g;
+            if (rbase >= Mp) continue;
+            float T[2][4];
 #pragma unroll
-            for (int o = 8; o >= 1; o >>= 1) tm = fmaxf(tm, __shfl_xor(tm, o, 64));
-            const int grow = blockIdx.x * 16 + 4 * kq + i;
-            const uint32_t field = exp_field(tm);
-            if (r16 == 0) p.te[(size_t)grow * BR + bb] = (uint8_t)field;
+            for (int h = 0; h < 2; ++h) {
+                v4f sum = red[(g * KW * NJB + 2 * bb + h) * 64 + lane];
 #pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const float v = mxint8_round(T[(2 * bb + g) % NJA][i], field);
-                *(uint16_t*)(p.tv + mxi_lt_offset(grow, (2 * bb + g) * 16 + r16, p.rp)) = (uint16_t)(__float_as_uint(v) >> 16);
+                for (int w = 1; w < KW; ++w) {
+                    const v4f o = red[((g * KW + w) * NJB + 2 * bb + h) * 64 + lane];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sum[i] = __fadd_rn(sum[i], o[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    T[h][i] = sum[i];
+                    const int grow = rbase + 4 * kq + i;
+                    if (DBG && grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + (2 * bb + h) * 16 + r16] = sum[i];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float tm = fmaxf(fabsf(T[0][i]), fabsf(T[1][i]));
+#pragma unroll
+                for (int o = 8; o >= 1; o >>= 1) tm = fmaxf(tm, __shfl_xor(tm, o, 64));
+                const int grow = rbase + 4 * kq + i;
+                const uint32_t field = exp_field(tm);
+                if (r16 == 0) p.te[(size_t)grow * BR + bb] = (uint8_t)field;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float v = mxint8_round(T[h][i], field);
+                    *(uint16_t*)(p.tv + mxi_lt_offset(grow, (2 * bb + h) * 16 + r16, p.rp)) = (uint16_t)(__float_as_uint(v) >> 16);
+                }
             }
         }
     }
 }
 
-template <bool BF16, int NJB, bool SM>
-static hipError_t mxi_act_launch(const MxiActParams& p, int64_t Mp, hipStream_t s)
+// Rows per workgroup: 64 (two groups of 32, R through LDS), 32 (two groups of 16, R through LDS) or 16 (eight wavefronts along
+// K, each reading its R from the L2).  More rows per workgroup mean fewer bytes of R, as long as the workgroups still cover
+// most of the 256 compute units; below that the short chain of the 16-row form wins, and with few columns of R its traffic
+// does not matter.  Measured (us, bf16 X, act / from codes; 64-, 32-, 16-row form):
+//   16384 x 4608, rank 128: 58.6 / 30.9, 73.7 / 44.7, 90.0 / 54.2      16384 x 4608, rank 64: 49.6 / 22.8, 53.7 / 27.7, 65.6 / 35.5
+//    8192 x 2240, rank  64: 25.2 / 11.9, 18.4 /  9.6, 19.8 / 11.2      16384 x 1152, rank 32: 17.4 /  8.1, 15.9 /  8.3, 18.4 / 10.4
+//    1024 x 4608, rank 128: 46.0 / 28.4, 30.5 / 20.9, 18.2 / 15.1       8192 x 1152, rank 32: 14.1 /  7.9, 10.5 /  7.8,  9.8 /  7.9
+static int mxi_act_rows(int r, int64_t Mp)
 {
-    hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM>), dim3((unsigned)(Mp / 16)), dim3(256), 0, s, p);
+    if (r >= 64 && Mp >= 64 * 192) return 64;
+    if (Mp >= (r >= 64 ? 32 * 192 : 32 * 384) && r > 0) return 32;
+    return 16;
+}
+
+template <bool BF16, int NJB, bool SM, bool FROMC, bool DBG>
+static hipError_t mxi_act_launch2(const MxiActParams& p, hipStream_t s)
+{
+    switch (mxi_act_rows(p.r, p.Mp)) {
+        case 64: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 2, 2, 4, DBG>), dim3((unsigned)((p.Mp + 63) / 64)), dim3(512), 0, s, p); break;
+        case 32: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 2, 4, DBG>), dim3((unsigned)(p.Mp / 32)), dim3(512), 0, s, p); break;
+        default: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 1, 8, DBG>), dim3((unsigned)(p.Mp / 16)), dim3(512), 0, s, p); break;
+    }
     return hipGetLastError();
 }
-template <bool BF16, bool SM>
-static hipError_t mxi_act_rank2(const MxiActParams& p, int64_t Mp, hipStream_t s)
+template <bool BF16, int NJB, bool SM, bool FROMC>
+static hipError_t mxi_act_launch(const MxiActParams& p, hipStream_t s)
+{
+    if constexpr (!FROMC) {
+        if (p.dbg_xb || p.dbg_xbe || p.dbg_T) return mxi_act_launch2<BF16, NJB, SM, FROMC, true>(p, s);
+    }
+    return mxi_act_launch2<BF16, NJB, SM, FROMC, false>(p, s);
+}
+template <bool BF16, bool SM, bool FROMC>
+static hipError_t mxi_act_rank(const MxiActParams& p, hipStream_t s)
 {
     switch (p.r) {
-        case 0: return mxi_act_launch<BF16, 0, SM>(p, Mp, s);
-        case 32: return mxi_act_launch<BF16, 2, SM>(p, Mp, s);
-        case 64: return mxi_act_launch<BF16, 4, SM>(p, Mp, s);
-        case 96: return mxi_act_launch<BF16, 6, SM>(p, Mp, s);
-        default: return mxi_act_launch<BF16, 8, SM>(p, Mp, s);
+        case 0: return mxi_act_launch<BF16, 0, SM, FROMC>(p, s);
+        case 32: return mxi_act_launch<BF16, 2, SM, FROMC>(p, s);
+        case 64: return mxi_act_launch<BF16, 4, SM, FROMC>(p, s);
+        case 96: return mxi_act_launch<BF16, 6, SM, FROMC>(p, s);
+        default: return mxi_act_launch<BF16, 8, SM, FROMC>(p, s);
     }
-}
-template <bool BF16>
-static hipError_t mxi_act_rank(const MxiActParams& p, int64_t Mp, hipStream_t s)
-{
-    return p.rg ? mxi_act_rank2<BF16, true>(p, Mp, s) : mxi_act_rank2<BF16, false>(p, Mp, s);
 }
 
 // The branch half of the activation step from the codes of a quantized hand-off (see mxi_act_kernel, FROMC).
@@ -568,6 +694,7 @@ hipError_t launch_branch_from_codes_mxi(const Dims& d, const uint8_t* packed, co
     p.cb = (const int8_t*)codes;
     p.cbe = codes + handoff_codes_bytes(d, M);
     p.M = (int)M;
+    p.Mp = (int)al.Mp;
     p.K = (int)d.K;
     p.C64 = d.C64;
     p.CQ = (d.C64 + 3) / 4;
@@ -578,15 +705,8 @@ hipError_t launch_branch_from_codes_mxi(const Dims& d, const uint8_t* packed, co
     p.xe = act + al.off_sx;
     p.tv = act + al.off_tq;
     p.te = act + al.off_st;
-    const unsigned grid = (unsigned)(al.Mp / 16);
-    switch (d.r) {
-        case 32: hipLaunchKernelGGL((mxi_act_kernel<true, 2, false, true>), dim3(grid), dim3(256), 0, s, p); break;
-        case 64: hipLaunchKernelGGL((mxi_act_kernel<true, 4, false, true>), dim3(grid), dim3(256), 0, s, p); break;
-        case 96: hipLaunchKernelGGL((mxi_act_kernel<true, 6, false, true>), dim3(grid), dim3(256), 0, s, p); break;
-        case 128: hipLaunchKernelGGL((mxi_act_kernel<true, 8, false, true>), dim3(grid), dim3(256), 0, s, p); break;
-        default: break;  // rank 0: the next layer has no branch, its blob is complete after the producing layer's epilogue
-    }
-    return hipGetLastError();
+    if (d.r == 0) return hipSuccess;  // the next layer has no branch: its blob is complete after the producing layer's epilogue
+    return mxi_act_rank<true, false, true>(p, s);
 }
 
 hipError_t launch_quantize_act_mxi(const Dims& d, int x_dtype, const uint8_t* packed, const void* X, int64_t M,
@@ -602,6 +722,7 @@ hipError_t launch_quantize_act_mxi(const Dims& d, int x_dtype, const uint8_t* pa
     p.cbe = nullptr;
     p.ldx = ldx;
     p.M = (int)M;
+    p.Mp = (int)al.Mp;
     p.K = (int)d.K;
     p.C64 = d.C64;
     p.CQ = (d.C64 + 3) / 4;
@@ -616,7 +737,8 @@ hipError_t launch_quantize_act_mxi(const Dims& d, int x_dtype, const uint8_t* pa
     p.dbg_xbe = dbg ? dbg->xbe : nullptr;
     p.dbg_T = dbg ? dbg->T : nullptr;
     p.rg = d.smooth ? (const float*)(packed + pl.off_rg) : nullptr;
-    return x_dtype == LQ_BF16 ? mxi_act_rank<true>(p, al.Mp, s) : mxi_act_rank<false>(p, al.Mp, s);
+    if (d.smooth) return x_dtype == LQ_BF16 ? mxi_act_rank<true, true, false>(p, s) : mxi_act_rank<false, true, false>(p, s);
+    return x_dtype == LQ_BF16 ? mxi_act_rank<true, false, false>(p, s) : mxi_act_rank<false, false, false>(p, s);
 }
 
 // ---------------------------------------------------------------------------------------------

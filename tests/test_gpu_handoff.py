@@ -73,6 +73,8 @@ def _run(oracle, M, K1, N1, N2, r1, r2, bw, seed, with_y):
     (64, 64, 128, 64, 0, 0, 8, False),          # no branch on either side
     (200, 320, 192, 320, 32, 0, 8, False),
     (1, 128, 64, 64, 32, 32, 8, True),
+    (6145, 64, 320, 64, 32, 64, 8, False),      # the step from codes on 32-row workgroups
+    (12290, 64, 576, 64, 32, 128, 4, False),    # ... and on 64-row workgroups, the last one partly past M
 ])
 def test_handoff_equals_the_two_call_path(oracle, M, K1, N1, N2, r1, r2, bw, with_y):
     _run(oracle, M, K1, N1, N2, r1, r2, bw, 40 + M, with_y)

@@ -185,3 +185,13 @@ def test_full_size_sampled_rows(oracle, name):
     rng = np.random.default_rng(1)
     rows = np.sort(np.concatenate([[0, layer.M - 1], rng.choice(layer.M, 14, replace=False)]))
     _compare(oracle, layer, X, W, L, R, rows=rows)
+
+
+# rows per workgroup of the activation step: 64 from 12288 rows at rank >= 64; 32 from 6144 rows (rank 32: 12288); last workgroup partly or wholly past M
+@pytest.mark.parametrize("M,K,r,bw,xd", [(6143, 320, 64, 8, "bf16"), (6113, 320, 64, 8, "bf16"), (12281, 448, 128, 4, "bf16"), (12289, 64, 96, 8, "f32"),
+                                         (12287, 576, 32, 8, "bf16"), (6150, 1152, 96, 8, "f32")])
+def test_activation_row_forms(oracle, M, K, r, bw, xd):
+    layer = wl.Layer("t", M, K, 64, r, "mxi", 32, bw, 8, xd, seed=M + r)
+    X, W, L, R = wl.make_inputs(layer)
+    rows = np.unique(np.concatenate([np.arange(M - 70, M), np.arange(40), np.arange(0, M, 997)]))
+    _compare(oracle, layer, X, W, L, R, rows=rows)
