@@ -650,6 +650,184 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_int_kernel(FwdParams p)
     }
 }
 
+// Small layers: a wavefront (a workgroup of its own) per tile of NRB*32 x NCB*32 outputs.  Where the 128 x 256 tiles leave most
+// of the chip idle, the time of a call is one tile's serial chain of steps; here a step is 1 to 4 products and 16 to 64 FMAs instead of
+// 8 and 128, nothing is shared between wavefronts (no LDS staging, no barriers), and both operand streams are requested
+// DEPTH steps ahead straight into the registers the products read.  Bounded by that chain for a few tiles (64 x 1152 -> 3456:
+// 9.2 -> 3.7 us, 64 x 4608 -> 1152: 22.5 -> 5.9 us) and by the operands' L2 traffic, 13-16 TB/s, for many.  Same sums in the same
+// order as fwd_tile.
+template <int GC, int NK, int NRB, int NCB, bool DBG, bool GA>
+__global__ __launch_bounds__(64, 2) void fwd_int_small_kernel(FwdParams p)
+{
+    typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    constexpr int RSRC_FLAGS = 0x00020000;
+    constexpr int NKA = NK > 0 ? NK : 1;
+    constexpr int STEP_REGS = 6 * GC * (NRB + NCB) + NCB + (GA ? NRB : 0);
+    constexpr int DEPTH = (NCB == 1 ? 150 : GA ? 80 : 105) / STEP_REGS;  // steps in flight
+    constexpr int ROW = 64 * NCB + 16;      // bytes per staged output row (pad: no bank conflicts)
+    __shared__ __attribute__((aligned(16))) uint8_t stage[32 * ROW];
+
+    const int lane = threadIdx.x, half = lane >> 5, l32 = lane & 31;
+    // row blocks fastest: the tiles that read one column block's weights run together on one XCD
+    const int tile = xcd_order(blockIdx.x, p.tilesM * p.tilesN);
+    const int tile_n = tile / p.tilesM, rb0 = (tile - tile_n * p.tilesM) * NRB;
+    const int G = p.G, C64 = p.C64;
+    const uint32_t lane16 = (uint32_t)lane * 16u, lane8 = 1024u + (uint32_t)lane * 8u;
+
+    int rbc[NRB];  // row blocks past the end are clamped; their results are not stored
+#pragma unroll
+    for (int i = 0; i < NRB; ++i) rbc[i] = rb0 + i < p.nrb ? rb0 + i : p.nrb - 1;
+    __amdgpu_buffer_rsrc_t rs_x[NRB];
+#pragma unroll
+    for (int i = 0; i < NRB; ++i)
+        rs_x[i] = __builtin_amdgcn_make_buffer_rsrc((void*)(p.xq + (size_t)rbc[i] * C64 * F6_CHUNK), 0, C64 * F6_CHUNK, RSRC_FLAGS);
+    const int cb0 = tile_n * NCB, col0 = cb0 * 32;  // (N is a multiple of 64)
+    const __amdgpu_buffer_rsrc_t rs_p = __builtin_amdgcn_make_buffer_rsrc((void*)(p.pq + (size_t)cb0 * C64 * F6_CHUNK), 0, NCB * C64 * F6_CHUNK, RSRC_FLAGS);
+    const __amdgpu_buffer_rsrc_t rs_s = __builtin_amdgcn_make_buffer_rsrc((void*)(p.swT + col0), 0, (G * p.N - col0) * 4, RSRC_FLAGS);
+
+    struct Step { Op6 a[NRB][GC], b[NCB][GC]; float sw[NCB]; int sx[NRB]; };
+    auto load_op = [&](Op6& o, const __amdgpu_buffer_rsrc_t& rs, int chunk) {
+        o = op6(__builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs, lane16, chunk * F6_CHUNK, 0)),
+                __builtin_bit_cast(v2i, (u2)__builtin_amdgcn_raw_buffer_load_b64(rs, lane8, chunk * F6_CHUNK, 0)));
+    };
+    auto load = [&](Step& t, int step) {  // (steps past the end are clamped: fetched, not used)
+        const int g = step < G ? step : G - 1;
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) t.sw[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_s, l32 * 4 + j * 128, g * p.N * 4, 0));
+        if constexpr (GA) {
+#pragma unroll
+            for (int i = 0; i < NRB; ++i)
+                t.sx[i] = (int)p.sxg[(((size_t)g * p.tiles128 + (rbc[i] >> 2)) * 32 + l32) * 4 + (rbc[i] & 3)];
+        }
+#pragma unroll
+        for (int cc = 0; cc < GC; ++cc) {
+#pragma unroll
+            for (int j = 0; j < NCB; ++j) load_op(t.b[j][cc], rs_p, j * C64 + g * GC + cc);
+#pragma unroll
+            for (int i = 0; i < NRB; ++i) load_op(t.a[i][cc], rs_x[i], g * GC + cc);
+        }
+    };
+    Step st[DEPTH];
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) load(st[i], i);
+    // epilogue operands
+    float sl[NCB];
+    v4i lqf[NCB][NKA];
+#pragma unroll
+    for (int j = 0; j < NCB; ++j) {
+        sl[j] = p.sl[col0 + j * 32 + l32];
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) lqf[j][kk] = *(const v4i*)(p.lq + (size_t)(col0 + j * 32 + l32) * p.rp + kk * 32 + half * 16);
+    }
+
+    v16f t[NRB][NCB];
+#pragma unroll
+    for (int i = 0; i < NRB; ++i)
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) t[i][j] = v16f{0};
+    auto fold = [&](Step& c, int g) {
+#pragma unroll
+        for (int i = 0; i < NRB; ++i)
+#pragma unroll
+            for (int j = 0; j < NCB; ++j) {
+                v16f d = {0};
+#pragma unroll
+                for (int cc = 0; cc < GC; ++cc)
+                    d = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(op8(c.a[i][cc]), op8(c.b[j][cc]), d, 2, 2, 0, 0, 0, 0);
+                if constexpr (GA) {  // exact products of the FP16 block scales; K half 1 of the operands is zero
+                    const v4i as = {c.sx[i], 0, 0, 0};
+                    const v4i bs = {half ? 0 : __float_as_int(c.sw[j]), 0, 0, 0};
+                    const v16f P = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, as), __builtin_bit_cast(v8h, bs), v16f{0}, 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) t[i][j][e] = __builtin_fmaf(d[e], P[e], t[i][j][e]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) t[i][j][e] = __builtin_fmaf(d[e], c.sw[j], t[i][j][e]);
+                }
+                if (DBG) {
+                    if (p.dbg_acc) {
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const int row = (rb0 + i) * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+                            if (row < p.M) p.dbg_acc[((size_t)row * p.N + col0 + j * 32 + l32) * G + g] = (int)(d[e] * 64.0f);
+                        }
+                    }
+                }
+            }
+    };
+    int g0 = 0;
+    for (; g0 + DEPTH <= G; g0 += DEPTH) {
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) {
+            fold(st[i], g0 + i);
+            load(st[i], g0 + i + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < DEPTH - 1; ++i)
+        if (g0 + i < G) fold(st[i], g0 + i);
+
+    // ---- epilogue (as in fwd_tile): rank-r expansion, scales, sum, bf16; a 32 x 32 block at a time through LDS
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const int rows_valid = p.M - rb0 * 32 < NRB * 32 ? p.M - rb0 * 32 : NRB * 32;
+    const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(p.Y + (size_t)(rb0 * 32) * p.ldy + col0), 0, (int)((rows_valid - 1) * p.ldy * 2 + NCB * 64), RSRC_FLAGS);
+#pragma unroll
+    for (int i = 0; i < NRB; ++i) {
+        v4i tqf[NKA];
+        v4f sxv[4], stv[4];
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) tqf[kk] = *(const v4i*)(p.tq + (size_t)(rbc[i] * 32 + l32) * p.rp + kk * 32 + half * 16);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {  // rows 8*q + 4*half + 0..3
+            stv[q] = *(const v4f*)(p.st + rbc[i] * 32 + 8 * q + 4 * half);
+            if constexpr (!GA) sxv[q] = *(const v4f*)(p.sx + rbc[i] * 32 + 8 * q + 4 * half);
+        }
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) {
+            v16i a2 = {0};
+#pragma unroll
+            for (int kk = 0; kk < NK; ++kk) a2 = __builtin_amdgcn_mfma_i32_32x32x32_i8(tqf[kk], lqf[j][kk], a2, 0, 0, 0);
+            float y[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float ybr = __fmul_rn(__fmul_rn((float)a2[e], stv[e >> 2][e & 3]), sl[j]);
+                y[e] = GA ? __builtin_fmaf(t[i][j][e], 64.0f, ybr) : __builtin_fmaf(sxv[e >> 2][e & 3], t[i][j][e], ybr);
+            }
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+                const bf16x2 h = __builtin_convertvector(f32x2{y[e], y[e + 1]}, bf16x2);
+                const uint32_t w = __builtin_bit_cast(uint32_t, h);
+                const int o = (8 * (e >> 2) + 4 * half + (e & 3)) * ROW + j * 64 + l32 * 2;
+                *(uint16_t*)(stage + o) = (uint16_t)(w & 0xFFFFu);
+                *(uint16_t*)(stage + o + ROW) = (uint16_t)(w >> 16);
+            }
+            if (DBG) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int row = (rb0 + i) * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+                    if (row < p.M) {
+                        if (p.dbg_acc2) p.dbg_acc2[(size_t)row * p.N + col0 + j * 32 + l32] = a2[e];
+                        if (p.dbg_y32) p.dbg_y32[(size_t)row * p.N + col0 + j * 32 + l32] = y[e];
+                    }
+                }
+            }
+        }
+        // read back row-wise (LDS operations of one wavefront complete in order): 4 NCB lanes per row of 64 NCB bytes
+        constexpr int LR = 4 * NCB, RP = 64 / LR;
+#pragma unroll
+        for (int q = 0; q < 32 / RP; ++q) {
+            const int row = q * RP + lane / LR, seg = (lane % LR) * 16;
+            const v4i o = *(const v4i*)(stage + row * ROW + seg);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, o), rs_y, (i * 32 + row) * (int)p.ldy * 2 + seg, 0, 0);
+        }
+    }
+}
+
 // Workgroup slots of the device: two workgroups (of 256 registers per lane) per compute unit.
 static int workgroup_slots()
 {
@@ -668,6 +846,26 @@ template <int GC, int NK, bool DBG, bool GA = false>
 static hipError_t launch_cfg(const FwdParams& p0, hipStream_t s)
 {
     FwdParams p = p0;
+    // Small layers, by the number T of 32 x 32 tiles (the device holds 2048 wavefronts of these kernels): one tile to a
+    // wavefront while that leaves no SIMD with two, larger ones as the L2 traffic of the operands (3, 2.25 and 1.5 KB per tile
+    // and 64-chunk) begins to count, the 128 x 256 tiles once they occupy enough of the chip.  The SINT4-block kernel of
+    // those is the slower one, so the line lies higher.  us, 1 x 1 / 2 x 1 / 2 x 2 / 128 x 256:
+    //   64-deep   T =  108 (   64 x 1152 -> 3456):  3.7 /  4.7 /  6.6 /  9.2      SINT4   T =  140 (  64 x 2240 -> 2240):  6.0 /  9.4 / 14.3 / 20.5
+    //             T =  840 ( 128 x 2240 -> 6720):   8.7 /  7.6 / 12.4 / 15.2              T = 1120 ( 512 x 2240 -> 2240): 13.5 / 13.1 / 15.7 / 22.4
+    //             T = 1728 ( 512 x 1152 -> 3456):   8.8 /  8.0 /  8.0 / 10.2              T = 6720 (3072 x 2240 -> 2240):    - /    - / 31.3 / 36.6
+    //             T = 4620 ( 700 x 2240 -> 6720):     - /    - / 19.7 / 22.9              T = 8960 (4096 x 2240 -> 2240):    - /    - / 43.8 / 41.2
+    //             T = 6720 (3072 x 2240 -> 2240):     - /    - / 25.4 / 23.2      128-deep T = 36 (  2 x 4608 -> 1152):   5.9 /  8.0 / 13.2 / 22.4
+    const int64_t T = (int64_t)p.nrb * (p.N / 32);
+    if (T <= (GA ? 7168 : 5120)) {
+        const int rbt = T <= 800 ? 1 : 2, cbt = T <= 1700 ? 1 : 2;
+        p.tilesN = p.N / 32 / cbt;
+        p.tilesM = (p.nrb + rbt - 1) / rbt;
+        dim3 grid((unsigned)(p.tilesM * p.tilesN)), block(64);
+        if (rbt == 1) hipLaunchKernelGGL((fwd_int_small_kernel<GC, NK, 1, 1, DBG, GA>), grid, block, 0, s, p);
+        else if (cbt == 1) hipLaunchKernelGGL((fwd_int_small_kernel<GC, NK, 2, 1, DBG, GA>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((fwd_int_small_kernel<GC, NK, 2, 2, DBG, GA>), grid, block, 0, s, p);
+        return hipGetLastError();
+    }
     p.tilesM = (p.nrb + 3) / 4;
     p.tilesN = (p.N + WN * 64 - 1) / (WN * 64);
     const int slots = workgroup_slots() & ~7;

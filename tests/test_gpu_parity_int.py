@@ -380,3 +380,21 @@ def test_empty_batch_is_a_no_op(oracle, family):
     Y1 = lq.lq_linear_lowrank_fwd(cfg, packed, lq.lq_quantize_act(cfg, packed, X1), 8)
     torch.cuda.synchronize()
     assert tuple(Y1.shape) == (8, N) and bool(torch.isfinite(Y1.float()).all())
+
+
+# Forms of the forward by the number of 32 x 32 tiles: 1 x 1 to 800, 2 x 1 to 1700, 2 x 2 to 5120 (SINT4 blocks 7168), 128 x 256 tiles
+# above; ragged M, an odd number of row blocks, fewer and more steps than are kept in flight.
+@pytest.mark.parametrize("M,K,N,r,g,ag", [
+    (790, 1152, 1024, 32, 64, 0), (397, 1152, 2304, 32, 64, 0), (400, 256, 2304, 16, 128, 0), (1130, 128, 1536, 64, 64, 0),
+    (1100, 2304, 2176, 96, 128, 0), (1129, 1216, 1600, 128, 64, 0), (2340, 64, 2240, 0, 64, 0),
+    (2500, 320, 2176, 32, 64, 0), (2497, 384, 2176, 32, 128, 0), (2600, 128, 2240, 32, 64, 0),
+    (790, 704, 1024, 32, 64, 64), (397, 1152, 2304, 64, 64, 64), (1100, 256, 2176, 0, 64, 64), (3400, 64, 2176, 128, 64, 64), (3500, 192, 2176, 32, 64, 64),
+])
+def test_forward_forms_bit_exact(oracle, M, K, N, r, g, ag):
+    layer = wl.Layer("t", M, K, N, r, "int", g, 8, 8, "bf16", seed=M + N, a_group=ag)
+    X, W, L, R = wl.make_inputs(layer)
+    out_gpu = run_gpu(layer, X, W, L, R, debug=False)
+    rows = np.unique(np.concatenate([np.arange(M - 40, M), np.arange(0, M, 61)]))
+    _, _, out = run_oracle_int(oracle, layer, X[rows], W, L, R, want_acc=False)
+    assert np.array_equal(bf16_to_bits(out_gpu.Y)[rows], out.Y)
+    assert torch.equal(run_gpu(layer, X, W, L, R, debug=True, debug_acc=False).Y, out_gpu.Y)
