@@ -58,6 +58,19 @@ CalibLayout calib_layout(const Dims& d)
     cl.off_gLp = o; o = align256(o + (size_t)c.cblocks * nl);
     cl.off_gRp = o; o = align256(o + (size_t)c.splits * nr);
     cl.total = o;
+    // The size callers are told never falls below that of the first layout (a loss partial per wavefront of 16 rows and a group,
+    // parts of grad_R over up to 16 row ranges): what lq_calib_sizes returned for a layer stays the least it returns.
+    {
+        const size_t blocks = (size_t)d.N / 16, groups = (size_t)((d.mx || d.mxi) ? d.C64 : d.G);
+        size_t parts = 1;
+        for (size_t p = 1; p <= 16; ++p) {
+            if (blocks % p) continue;
+            parts = p;
+            if (p * (d.K / 32) >= 256) break;
+        }
+        const size_t f = align256(align256(cl.off_lp + blocks * ((groups + 3) / 4) * 4 * 4) + parts * nr);
+        if (f > cl.total) cl.total = f;
+    }
     return cl;
 }
 

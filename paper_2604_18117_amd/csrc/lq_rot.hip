@@ -67,6 +67,17 @@ RotLayout rot_layout(const Dims& d)
     rl.off_lp = o;  o = align256(o + (size_t)(w.wL + w.wR) * 4);
     rl.off_gp = o;  o = align256(o + (size_t)(w.wL + w.wR) * rr);
     rl.total = o;
+    // The size callers are told never falls below that of the first layout (row maxima and loss partials per wavefront of 256
+    // rows or columns, 64 parts of the gradient, three r x r work matrices): what lq_rot_sizes returned for a layer stays the least it
+    // returns, and the library's own array takes no configuration that it refused.
+    {
+        const size_t nlb = ((size_t)d.N + 255) / 256, nkb = ((size_t)d.K + 255) / 256;
+        size_t f = align256(rl.off_ax + nkb * 4 * d.r * 4);
+        f = align256(f + (nlb + d.r * nkb) * 4);
+        f = align256(f + 64 * rr);
+        f = align256(f + 3 * rr);
+        if (f > rl.total) rl.total = f;
+    }
     return rl;
 }
 
