@@ -155,12 +155,20 @@ def config_for_layer(layer, smooth: bool = False) -> lq_config:
                        layer.x_dtype, smooth=smooth, a_group=layer.a_group)
 
 
+# The handle of the current stream, straight from the extension: the Stream object that torch.cuda.current_stream() builds
+# around it takes 2.8 us, most of a kernel launch (3.0 us), and two calls per layer at small M are bound by the host.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    return int(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None or _get_device is None or not torch.cuda.is_initialized():
+        return int(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(_get_device())
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def lq_packed_sizes(cfg: lq_config) -> int:
@@ -172,13 +180,13 @@ def lq_packed_sizes(cfg: lq_config) -> int:
 def lq_set_smoothing(cfg: lq_config, packed: torch.Tensor, gamma: torch.Tensor) -> None:
     """gamma: K fp32 CUDA values > 0; stores their reciprocals in the blob (layer packed with smooth=True)."""
     assert gamma.is_cuda and gamma.dtype == torch.float32 and gamma.is_contiguous() and gamma.numel() == cfg.K
-    _check(_lib.lq_set_smoothing(C.byref(cfg), _ptr(gamma), _ptr(packed), packed.numel(), C.c_void_p(_stream())),
+    _check(_lib.lq_set_smoothing(C.byref(cfg), _ptr(gamma), _ptr(packed), packed.numel(), _stream()),
            "lq_set_smoothing")
 
 
 def lq_verify_blob(cfg: lq_config, kind: int, blob: torch.Tensor, M: int = 0) -> None:
     """Raises LqError(LQ_ERR_STALE_BLOB) when the blob's header does not belong to cfg (and M).  Synchronises the stream."""
-    _check(_lib.lq_verify_blob(C.byref(cfg), kind, _ptr(blob), blob.numel(), M, C.c_void_p(_stream())), "lq_verify_blob")
+    _check(_lib.lq_verify_blob(C.byref(cfg), kind, _ptr(blob), blob.numel(), M, _stream()), "lq_verify_blob")
 
 
 def lq_act_sizes(cfg: lq_config, M: int) -> int:
@@ -198,7 +206,7 @@ def lq_pack_weights(cfg: lq_config, W: torch.Tensor, L: Optional[torch.Tensor], 
     if packed is None:
         packed = torch.empty(lq_packed_sizes(cfg), dtype=torch.uint8, device=W.device)
     _check(_lib.lq_pack_weights(C.byref(cfg), _ptr(W), _ptr(L), _ptr(R), _ptr(packed), packed.numel(),
-                                C.c_void_p(_stream())), "lq_pack_weights")
+                                _stream()), "lq_pack_weights")
     return packed
 
 
@@ -217,8 +225,9 @@ def lq_quantize_act(cfg: lq_config, packed: torch.Tensor, X: torch.Tensor, act: 
     (and the parity taps when debug=True)."""
     assert X.is_cuda and X.dim() == 2 and X.stride(1) == 1 and X.shape[1] == cfg.K
     assert X.dtype == (torch.bfloat16 if cfg.x_dtype == LQ_BF16 else torch.float32)
-    assert packed is None or packed.numel() >= lq_packed_sizes(cfg)
     M = X.shape[0]
+    if M == 0:  # (the library looks at no buffer then)
+        assert packed is None or packed.numel() >= lq_packed_sizes(cfg)
     if act is None:
         act = torch.empty(lq_act_sizes(cfg, M), dtype=torch.uint8, device=X.device)
     dbg = None
@@ -232,10 +241,11 @@ def lq_quantize_act(cfg: lq_config, packed: torch.Tensor, X: torch.Tensor, act: 
                         torch.zeros((M, cfg.K // 32), dtype=torch.uint8, device=X.device))
         dbg = lq_act_debug(taps.xb.data_ptr(), taps.sxb.data_ptr(), taps.accT.data_ptr(), taps.T.data_ptr(),
                            taps.xbe.data_ptr())
-    _check(_lib.lq_quantize_act(C.byref(cfg), _ptr(packed), 0 if packed is None else packed.numel(), _ptr(X), M, X.stride(0),
-                                _ptr(act), act.numel(),
-                                C.byref(dbg) if dbg is not None else None, C.c_void_p(_stream())),
-           "lq_quantize_act")
+    st = _lib.lq_quantize_act(C.byref(cfg), _ptr(packed), 0 if packed is None else packed.numel(), _ptr(X), M, X.stride(0),
+                              _ptr(act), act.numel(), C.byref(dbg) if dbg is not None else None, _stream())
+    if st != LQ_OK:
+        assert packed is None or packed.numel() >= lq_packed_sizes(cfg)  # the library's own size check, as an assertion
+        _check(st, "lq_quantize_act")
     return (act, taps) if debug else act
 
 
@@ -261,7 +271,7 @@ def lq_linear_lowrank_fwd(cfg: lq_config, packed: torch.Tensor, act: torch.Tenso
                         torch.zeros((M, cfg.N), dtype=torch.float32, device=act.device))
         dbg = lq_fwd_debug(taps.acc.data_ptr() if debug_acc else None, taps.acc2.data_ptr(), taps.y32.data_ptr())
     _check(_lib.lq_linear_lowrank_fwd(C.byref(cfg), _ptr(packed), packed.numel(), _ptr(act), act.numel(), M, _ptr(Y), Y.stride(0),
-                                      C.byref(dbg) if dbg is not None else None, C.c_void_p(_stream())),
+                                      C.byref(dbg) if dbg is not None else None, _stream()),
            "lq_linear_lowrank_fwd")
     return (Y, taps) if debug else Y
 
@@ -286,7 +296,7 @@ def lq_linear_lowrank_fwd_handoff(cfg: lq_config, packed: torch.Tensor, act: tor
     _check(_lib.lq_linear_lowrank_fwd_handoff(C.byref(cfg), _ptr(packed), packed.numel(), _ptr(act), act.numel(), M, _ptr(Y),
                                               Y.stride(0) if Y is not None else 0,
                                               C.byref(next_cfg), _ptr(act_next), act_next.numel(), _ptr(codes), codes.numel(),
-                                              C.c_void_p(_stream())), "lq_linear_lowrank_fwd_handoff")
+                                              _stream()), "lq_linear_lowrank_fwd_handoff")
     return act_next, codes
 
 
@@ -295,7 +305,7 @@ def lq_branch_from_codes(next_cfg: lq_config, packed_next: torch.Tensor, codes: 
     """Completes act_next (the consumer's intermediate codes and scales) from the hand-off codes."""
     _check(_lib.lq_branch_from_codes(C.byref(next_cfg), _ptr(packed_next), 0 if packed_next is None else packed_next.numel(),
                                      _ptr(codes), codes.numel(), M, _ptr(act_next),
-                                     act_next.numel(), C.c_void_p(_stream())), "lq_branch_from_codes")
+                                     act_next.numel(), _stream()), "lq_branch_from_codes")
     return act_next
 
 
@@ -328,7 +338,7 @@ def lq_unpack_weights(cfg: lq_config, packed: torch.Tensor) -> WeightsView:
     view = lq_weights_view(v.pq.data_ptr(), v.sw.data_ptr() if v.sw is not None else None,
                            v.pe.data_ptr() if v.pe is not None else None, v.lq.data_ptr(), v.sl.data_ptr(),
                            v.rq.data_ptr(), v.sr.data_ptr(), v.le.data_ptr(), v.re.data_ptr())
-    _check(_lib.lq_unpack_weights(C.byref(cfg), _ptr(packed), C.byref(view), C.c_void_p(_stream())),
+    _check(_lib.lq_unpack_weights(C.byref(cfg), _ptr(packed), C.byref(view), _stream()),
            "lq_unpack_weights")
     return v
 
@@ -356,7 +366,7 @@ def lq_unpack_act(cfg: lq_config, act: torch.Tensor, M: int) -> ActView:
     view = lq_act_view(v.xq.data_ptr(), v.sx.data_ptr() if v.sx is not None else None,
                        v.xe.data_ptr() if v.xe is not None else None, v.tq.data_ptr(), v.st.data_ptr(),
                        v.te.data_ptr())
-    _check(_lib.lq_unpack_act(C.byref(cfg), _ptr(act), M, C.byref(view), C.c_void_p(_stream())), "lq_unpack_act")
+    _check(_lib.lq_unpack_act(C.byref(cfg), _ptr(act), M, C.byref(view), _stream()), "lq_unpack_act")
     return v
 
 
@@ -375,7 +385,7 @@ def lq_calib_init(cfg: lq_config, L: torch.Tensor, R: torch.Tensor, state: Optio
     assert tuple(L.shape) == (cfg.N, cfg.rank) and tuple(R.shape) == (cfg.rank, cfg.K), "factor shapes must match cfg"
     if state is None:
         state = torch.empty(lq_calib_sizes(cfg), dtype=torch.uint8, device=L.device)
-    _check(_lib.lq_calib_init(C.byref(cfg), _ptr(L), _ptr(R), _ptr(state), state.numel(), C.c_void_p(_stream())),
+    _check(_lib.lq_calib_init(C.byref(cfg), _ptr(L), _ptr(R), _ptr(state), state.numel(), _stream()),
            "lq_calib_init")
     return state
 
@@ -386,7 +396,7 @@ def lq_calib_step(cfg: lq_config, W: torch.Tensor, state: torch.Tensor, step: in
     assert W.is_cuda and W.dtype == torch.float32 and W.is_contiguous() and tuple(W.shape) == (cfg.N, cfg.K)
     ad = lq_adam(lr, beta1, beta2, eps)
     _check(_lib.lq_calib_step(C.byref(cfg), _ptr(W), _ptr(state), state.numel(), step, C.byref(ad), _ptr(loss),
-                              C.c_void_p(_stream())), "lq_calib_step")
+                              _stream()), "lq_calib_step")
 
 
 def lq_calib_unpack(cfg: lq_config, state: torch.Tensor, names=("L", "R")) -> dict:
@@ -396,7 +406,7 @@ def lq_calib_unpack(cfg: lq_config, state: torch.Tensor, names=("L", "R")) -> di
               "E": (N, K)}
     out = {k: torch.empty(shapes[k], dtype=torch.float32, device=state.device) for k in names}
     view = lq_calib_view(**{k: (out[k].data_ptr() if k in out else None) for k in shapes})
-    _check(_lib.lq_calib_unpack(C.byref(cfg), _ptr(state), C.byref(view), C.c_void_p(_stream())), "lq_calib_unpack")
+    _check(_lib.lq_calib_unpack(C.byref(cfg), _ptr(state), C.byref(view), _stream()), "lq_calib_unpack")
     return out
 
 
@@ -421,7 +431,7 @@ def lq_rot_init(cfg: lq_config, Omega0: Optional[torch.Tensor] = None, Mom0: Opt
         assert t is None or (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous() and tuple(t.shape) == (cfg.rank, cfg.rank))
     if state is None:
         state = torch.empty(lq_rot_sizes(cfg), dtype=torch.uint8, device=device)
-    _check(_lib.lq_rot_init(C.byref(cfg), _ptr(Omega0), _ptr(Mom0), _ptr(state), state.numel(), C.c_void_p(_stream())),
+    _check(_lib.lq_rot_init(C.byref(cfg), _ptr(Omega0), _ptr(Mom0), _ptr(state), state.numel(), _stream()),
            "lq_rot_init")
     return state
 
@@ -433,7 +443,7 @@ def lq_rot_step(cfg: lq_config, L: torch.Tensor, R: torch.Tensor, state: torch.T
     _check_factors(cfg, L, R)
     opt = lq_cayley(lr, beta, eps, q, s, grad_scale)
     _check(_lib.lq_rot_step(C.byref(cfg), _ptr(L), _ptr(R), _ptr(state), state.numel(), C.byref(opt), _ptr(loss),
-                            C.c_void_p(_stream())), "lq_rot_step")
+                            _stream()), "lq_rot_step")
 
 
 def lq_rot_step_static(cfg: lq_config, L: torch.Tensor, R: torch.Tensor, state: torch.Tensor, lr: float = 0.5,
@@ -443,14 +453,14 @@ def lq_rot_step_static(cfg: lq_config, L: torch.Tensor, R: torch.Tensor, state: 
     _check_factors(cfg, L, R)
     opt = lq_cayley(lr, beta, eps, q, s, grad_scale)
     _check(_lib.lq_rot_step_static(C.byref(cfg), _ptr(L), _ptr(R), _ptr(state), state.numel(), C.byref(opt), _ptr(loss),
-                                   C.c_void_p(_stream())), "lq_rot_step_static")
+                                   _stream()), "lq_rot_step_static")
 
 
 def lq_rot_apply(cfg: lq_config, L: torch.Tensor, R: torch.Tensor, state: torch.Tensor):
     """(L Omega, Omega^T R) as new fp32 tensors, for lq_pack_weights."""
     _check_factors(cfg, L, R)
     Lr, Rr = torch.empty_like(L), torch.empty_like(R)
-    _check(_lib.lq_rot_apply(C.byref(cfg), _ptr(L), _ptr(R), _ptr(state), _ptr(Lr), _ptr(Rr), C.c_void_p(_stream())),
+    _check(_lib.lq_rot_apply(C.byref(cfg), _ptr(L), _ptr(R), _ptr(state), _ptr(Lr), _ptr(Rr), _stream()),
            "lq_rot_apply")
     return Lr, Rr
 
@@ -461,5 +471,5 @@ def lq_rot_unpack(cfg: lq_config, state: torch.Tensor, names=("Omega",)) -> dict
     shapes = {"Omega": (r, r), "Mom": (r, r), "G": (r, r), "E1": (N, r), "E2": (r, K)}
     out = {k: torch.empty(shapes[k], dtype=torch.float32, device=state.device) for k in names}
     view = lq_rot_view(**{k: (out[k].data_ptr() if k in out else None) for k in shapes})
-    _check(_lib.lq_rot_unpack(C.byref(cfg), _ptr(state), C.byref(view), C.c_void_p(_stream())), "lq_rot_unpack")
+    _check(_lib.lq_rot_unpack(C.byref(cfg), _ptr(state), C.byref(view), _stream()), "lq_rot_unpack")
     return out
