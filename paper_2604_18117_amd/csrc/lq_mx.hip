@@ -1337,9 +1337,215 @@ __global__ __launch_bounds__(256, 2) void mx_fwd_kernel(MxFwdParams p)
     }
 }
 
+// Small layers: a wavefront (a workgroup of its own) per tile of NRB*32 x NCB*32 outputs.  Where the 128 x 256 tiles leave most of the chip
+// idle, the time of a call is one tile's serial chain of stages; here nothing is shared between wavefronts (no LDS staging, no
+// barriers) and both operand streams are requested DEPTH quads of 64-chunks ahead straight into the registers the products
+// read.  Bounded by that chain for a few tiles (128 x 1152 -> 3456: 7.6 -> 3.2 us, 128 x 4608 -> 1152: 16.2 -> 4.2 us), by the operands'
+// L2 traffic for many.  Same products in the same order as mx_fwd_tile.
+template <int NK, bool DBG, bool BLK, int BFMT, int NRB, int NCB>
+__global__ __launch_bounds__(64, 2) void mx_fwd_small_kernel(MxFwdParams p)
+{
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    constexpr int RSRC_FLAGS = 0x00020000;
+    constexpr int DEPTH = NRB + NCB == 2 ? 4 : 2;  // quads in flight (17 registers per row or column block each)
+    constexpr int ROW = 64 * NCB + 8;              // bytes per staged output row
+    __shared__ __attribute__((aligned(16))) uint8_t stage[32 * ROW];
+
+    const int lane = threadIdx.x, half = lane >> 5, l32 = lane & 31;
+    // row blocks fastest: the tiles that read one column block's weights run together on one XCD
+    const int tiles = p.tilesM * p.tilesN, per = tiles >> 3, rem = tiles & 7, xcd = blockIdx.x & 7;
+    const int tile = xcd * per + (xcd < rem ? xcd : rem) + ((int)blockIdx.x >> 3);
+    const int tile_n = tile / p.tilesM, rb0 = (tile - tile_n * p.tilesM) * NRB, cb0 = tile_n * NCB;
+    const int C64 = p.C64, CQ = p.CQ;
+    const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
+
+    int rbc[NRB];  // row blocks past the end are clamped; their results are not stored
+#pragma unroll
+    for (int i = 0; i < NRB; ++i) rbc[i] = rb0 + i < p.nrb ? rb0 + i : p.nrb - 1;
+    __amdgpu_buffer_rsrc_t rs_x[NRB], rs_xe[NRB];
+#pragma unroll
+    for (int i = 0; i < NRB; ++i) {
+        rs_x[i] = __builtin_amdgcn_make_buffer_rsrc((void*)(p.xc + (size_t)rbc[i] * C64 * 1024), 0, C64 * 1024, RSRC_FLAGS);
+        rs_xe[i] = __builtin_amdgcn_make_buffer_rsrc((void*)(p.xe + (size_t)rbc[i] * CQ * 256), 0, CQ * 256, RSRC_FLAGS);
+    }
+    const __amdgpu_buffer_rsrc_t rs_p = __builtin_amdgcn_make_buffer_rsrc((void*)(p.pc + (size_t)cb0 * C64 * 1024), 0, NCB * C64 * 1024, RSRC_FLAGS);
+    const __amdgpu_buffer_rsrc_t rs_pe = __builtin_amdgcn_make_buffer_rsrc((void*)(p.pe + (size_t)cb0 * CQ * 256), 0, NCB * CQ * 256, RSRC_FLAGS);
+
+    struct Quad { v4i a[NRB][4], b[NCB][4]; int sa[NRB], sb[NCB]; };
+    auto load = [&](Quad& t, int quad) {  // (quads and chunks past the end are clamped: fetched, not used)
+        const int q = quad < CQ ? quad : CQ - 1;
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) t.sa[i] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_xe[i], lane4, q * 256, 0);
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) t.sb[j] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_pe, lane4, (j * CQ + q) * 256, 0);
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) {
+            const int c = 4 * q + cc < C64 ? 4 * q + cc : C64 - 1;
+#pragma unroll
+            for (int j = 0; j < NCB; ++j) t.b[j][cc] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_p, lane16, (j * C64 + c) * 1024, 0));
+#pragma unroll
+            for (int i = 0; i < NRB; ++i) t.a[i][cc] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_x[i], lane16, c * 1024, 0));
+        }
+    };
+    Quad qd[DEPTH];
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) load(qd[i], i);
+
+    v16f t[NRB][NCB];
+#pragma unroll
+    for (int i = 0; i < NRB; ++i)
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) t[i][j] = v16f{0};
+    auto chunk = [&](const Quad& c, auto cc_tag) {
+        constexpr int CC = decltype(cc_tag)::value;
+#pragma unroll
+        for (int i = 0; i < NRB; ++i)
+#pragma unroll
+            for (int j = 0; j < NCB; ++j) {
+                const v4i av = c.a[i][CC], bv = c.b[j][CC];
+                const v8i a8 = {av[0], av[1], av[2], av[3], 0, 0, 0, 0}, b8 = {bv[0], bv[1], bv[2], bv[3], 0, 0, 0, 0};
+                t[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b8, a8, t[i][j], 4, 4, CC, c.sb[j], CC, c.sa[i]);
+            }
+    };
+    auto multiply = [&](const Quad& c, int quad) {
+        chunk(c, std::integral_constant<int, 0>{});
+        chunk(c, std::integral_constant<int, 1>{});  // (the number of chunks is even)
+        if (4 * quad + 2 < C64) {
+            chunk(c, std::integral_constant<int, 2>{});
+            chunk(c, std::integral_constant<int, 3>{});
+        }
+    };
+    int q0 = 0;
+    for (; q0 + DEPTH <= CQ; q0 += DEPTH) {
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) {
+            multiply(qd[i], q0 + i);
+            load(qd[i], q0 + i + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < DEPTH - 1; ++i)
+        if (q0 + i < CQ) multiply(qd[i], q0 + i);
+
+    // ---- branch and epilogue as in mx_fwd_tile
+    if constexpr (BLK) {
+#pragma unroll
+        for (int cc = 0; cc < NK; ++cc) {
+            v8i lb[NCB];
+            int lsc[NCB];
+#pragma unroll
+            for (int j = 0; j < NCB; ++j) {
+                lb[j] = *(const v8i*)(p.l8 + ((size_t)((size_t)(cb0 + j) * NK + cc) * 64 + lane) * 32);
+                lsc[j] = *(const int*)((const uint8_t*)p.sl + ((size_t)(cb0 + j) * 64 + lane) * 4);
+            }
+#pragma unroll
+            for (int i = 0; i < NRB; ++i) {
+                const v8i ta = *(const v8i*)(p.tq8 + ((size_t)((size_t)rbc[i] * NK + cc) * 64 + lane) * 32);
+                const int tsc = *(const int*)((const uint8_t*)p.st + ((size_t)rbc[i] * 64 + lane) * 4);
+#pragma unroll
+                for (int j = 0; j < NCB; ++j) {
+                    if (cc == 0)
+                        t[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(lb[j], ta, t[i][j], BFMT, BFMT, 0, lsc[j], 0, tsc);
+                    else
+                        t[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(lb[j], ta, t[i][j], BFMT, BFMT, 1, lsc[j], 1, tsc);
+                }
+            }
+        }
+    }
+    constexpr int NKF = BLK ? 0 : NK, NKA = NKF > 0 ? NKF : 1;
+    v8i lf[NCB][NKA];
+    v4f slv[NCB][4];
+#pragma unroll
+    for (int j = 0; j < NCB; ++j) {
+#pragma unroll
+        for (int kk = 0; kk < NKF; ++kk) lf[j][kk] = *(const v8i*)(p.l8 + (size_t)((cb0 + j) * 32 + l32) * p.rp + kk * 64 + half * 32);
+        if constexpr (NKF > 0) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) slv[j][g] = *(const v4f*)(p.sl + (cb0 + j) * 32 + 8 * g + 4 * half);
+        }
+    }
+    const int rows_valid = p.M - rb0 * 32 < NRB * 32 ? p.M - rb0 * 32 : NRB * 32;
+    const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(p.Y + (size_t)(rb0 * 32) * p.ldy + cb0 * 32), 0, (int)((rows_valid - 1) * p.ldy * 2 + NCB * 64), RSRC_FLAGS);
+#pragma unroll
+    for (int i = 0; i < NRB; ++i) {
+        v8i tf[NKA];
+        float stl = 0.f;
+        if constexpr (NKF > 0) {
+#pragma unroll
+            for (int kk = 0; kk < NKF; ++kk) tf[kk] = *(const v8i*)(p.tq8 + (size_t)(rbc[i] * 32 + l32) * p.rp + kk * 64 + half * 32);
+            stl = p.st[rbc[i] * 32 + l32];
+        }
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) {
+            v16f a2 = {0};
+#pragma unroll
+            for (int kk = 0; kk < NKF; ++kk)
+                a2 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(lf[j][kk], tf[kk], a2, 0, 0, 0, 0, 0, 0);
+            float y[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                if (BLK) y[e] = t[i][j][e];
+                else if (NK == 0) y[e] = __fadd_rn(t[i][j][e], 0.f);
+                else y[e] = __builtin_fmaf(__fmul_rn(a2[e], stl), slv[j][e >> 2][e & 3], t[i][j][e]);
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const bf16x2 h0 = __builtin_convertvector(f32x2{y[4 * g], y[4 * g + 1]}, bf16x2);
+                const bf16x2 h1 = __builtin_convertvector(f32x2{y[4 * g + 2], y[4 * g + 3]}, bf16x2);
+                *(v2i*)(stage + l32 * ROW + half * 8 + j * 64 + g * 16) = v2i{__builtin_bit_cast(int, h0), __builtin_bit_cast(int, h1)};
+            }
+            if (DBG) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int row = (rb0 + i) * 32 + l32, col = (cb0 + j) * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+                    if (row < p.M && p.dbg_y32) p.dbg_y32[(size_t)row * p.N + col] = y[e];
+                }
+            }
+        }
+        // read back row-wise (LDS operations of one wavefront complete in order): 4 NCB lanes per row of 64 NCB bytes
+        constexpr int LR = 4 * NCB, RP = 64 / LR;
+#pragma unroll
+        for (int q = 0; q < 32 / RP; ++q) {
+            const int row = q * RP + lane / LR, seg = (lane % LR) * 16;
+            const v2i lo = *(const v2i*)(stage + row * ROW + seg), hi = *(const v2i*)(stage + row * ROW + seg + 8);
+            const v4i o = {lo[0], lo[1], hi[0], hi[1]};
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, o), rs_y, (i * 32 + row) * (int)p.ldy * 2 + seg, 0, 0);
+        }
+    }
+}
+
+template <int NK, bool DBG, bool BLK, int BFMT>
+static void mx_fwd_small_launch(MxFwdParams p, int rbt, int cbt, hipStream_t s)
+{
+    p.tilesN = p.N / 32 / cbt;
+    p.tilesM = (p.nrb + rbt - 1) / rbt;
+    const dim3 grid((unsigned)(p.tilesM * p.tilesN)), block(64);
+    if (rbt == 1) hipLaunchKernelGGL((mx_fwd_small_kernel<NK, DBG, BLK, BFMT, 1, 1>), grid, block, 0, s, p);
+    else if (cbt == 1) hipLaunchKernelGGL((mx_fwd_small_kernel<NK, DBG, BLK, BFMT, 2, 1>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((mx_fwd_small_kernel<NK, DBG, BLK, BFMT, 2, 2>), grid, block, 0, s, p);
+}
+
 template <int NK, bool BLK, int BFMT = 0>
 static void mx_fwd_launch(const MxFwdParams& p, hipStream_t s)
 {
+    // Small layers, by the number T of 32 x 32 tiles (the device holds 2048 wavefronts of these kernels): one tile to a
+    // wavefront while that leaves no SIMD with two, larger ones as the L2 traffic of the operands (2, 1.5 and 1 KB per tile and
+    // 64-chunk) begins to count, the 128 x 256 tiles once they occupy enough of the chip.  us, 1 x 1 / 2 x 1 / 2 x 2 / 128 x 256:
+    //   T =  108 (   2 x 1152 -> 3456): 2.7 / 3.3 / 4.3 /  7.5        T = 1728 ( 512 x 1152 -> 3456):  6.6 /  5.7 /  5.8 /  8.0
+    //   T =  720 ( 300 x 1152 -> 2304): 3.7 / 3.7 / 4.1 /  7.2        T = 2304 (2048 x 4608 -> 1152): 18.2 / 15.0 / 15.2 / 17.2
+    //   T = 1080 ( 300 x 1152 -> 3456): 5.2 / 4.7 / 5.3 /  7.9        T = 3500 ( 300 x 2240 -> 11200): 17.4 / 12.6 / 11.2 / 12.7
+    //   T =  576 ( 512 x 4608 -> 1152): 6.1 / 8.8 / 11.0 / 16.5       T = 4608 (4096 x 4608 -> 1152): 53.1 / 31.8 / 22.1 / 18.7
+    const int64_t T = (int64_t)p.nrb * (p.N / 32);
+    if (T <= 3584) {
+        const int rbt = T <= 800 ? 1 : 2, cbt = T <= 2000 ? 1 : 2;
+        if (p.dbg_y32) mx_fwd_small_launch<NK, true, BLK, BFMT>(p, rbt, cbt, s);
+        else mx_fwd_small_launch<NK, false, BLK, BFMT>(p, rbt, cbt, s);
+        return;
+    }
     dim3 grid((unsigned)(p.n_full + 2 * (p.tilesM * p.tilesN - p.n_full))), block(256);
     if (p.dbg_y32)
         hipLaunchKernelGGL((mx_fwd_kernel<NK, true, BLK, BFMT>), grid, block, 0, s, p);

@@ -182,3 +182,18 @@ def test_long_rows_are_streamed(oracle, M, K, N, r, xd, sm):
     layer = wl.Layer("t", M, K, N, r, "mx", 32, 8, 8, xd, outlier_scale=10.0, n_outliers=8, seed=K)
     X, W, L, R = wl.make_inputs(layer)
     _compare(oracle, layer, X, W, L, R, gamma=smoothing_vector(X, W) if sm else None)
+
+
+# Forms of the forward by the number of 32 x 32 tiles: 1 x 1 to 800, 2 x 1 to 2000, 2 x 2 to 3584, 128 x 256 tiles above; ragged M, an odd
+# number of row blocks, fewer and more quads of chunks than are kept in flight, a last quad of two chunks.
+@pytest.mark.parametrize("fam,bw,M,K,N,r", [
+    ("mx", 8, 790, 1152, 1024, 32), ("mx", 8, 397, 640, 2304, 64), ("mx", 8, 1100, 1152, 2176, 128), ("mx", 8, 1700, 128, 2176, 32),
+    ("mxb", 8, 397, 1152, 2304, 96), ("mxb", 8, 1129, 192, 1600, 64), ("mxb", 6, 790, 2240, 1024, 64), ("mxb", 6, 1130, 704, 2112, 128),
+    ("mxb", 6, 1700, 256, 2176, 64), ("mx", 8, 401, 320, 2304, 0),
+])
+def test_forward_forms(oracle, fam, bw, M, K, N, r):
+    from tests import test_gpu_parity_mxb as mxb
+    layer = wl.Layer("t", M, K, N, r, fam, 32, bw, bw, "bf16", seed=M + N)
+    X, W, L, R = wl.make_inputs(layer)
+    rows = np.unique(np.concatenate([np.arange(M - 40, M), np.arange(0, M, 61)]))
+    (_compare if fam == "mx" else mxb._compare)(oracle, layer, X, W, L, R, rows=rows)
