@@ -778,6 +778,59 @@ __device__ __forceinline__ v8i mxi_expand8(v4i p)  // 32 nibbles -> 32 FP8 subno
     return o;
 }
 
+// Hand-off codes of 8 consecutive channels (k0 = this layer's channel = the next layer's k) of one token, given as bf16: a
+// block of 32 of the next layer's K axis is the 4 lanes that differ in the two low lane bits.  Codes as in the activation
+// kernel: shared exponent from the block maximum, MXINT4 main codes (sign-magnitude nibbles), MXINT8 branch codes.
+__device__ __forceinline__ void mxi_handoff_emit(const MxiFwdParams& p, const v4i v, const int row, const int k0)
+{
+                    const uint32_t w[4] = {(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
+                    us2 m2 = {0, 0};
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, w[d] & 0x7FFF7FFFu));
+                    uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
+                    float am = __uint_as_float(mm << 16);
+                    am = fmaxf(am, __shfl_xor(am, 1, 64));
+                    am = fmaxf(am, __shfl_xor(am, 2, 64));
+                    const uint32_t field = exp_field(am);
+                    const float inv4 = field >= 2u ? __uint_as_float((256u - field) << 23) : 0.0f;   // 2^(2-s)
+                    const float to8 = field >= 7u ? __uint_as_float((260u - field) << 23) : 0.0f;    // 2^(6-s)
+                    // Both codes by one fused multiply-add each: scaling by a power of two is exact, so fma(x, 2^-step, magic)
+                    // rounds the scaled value to the nearest integer (ties to even) in one step -- the same integer the
+                    // activation kernel reaches by rounding on the block's grid and scaling afterwards -- and leaves it in
+                    // the low mantissa bits of the magic number.  Clamping after the rounding equals clamping before it.
+                    uint32_t sum = 0u - 0xFB000000u, c8[2];
+                    uint32_t ub[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float x = __uint_as_float((e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16));
+                        const uint32_t mb = __float_as_uint(fminf(__builtin_fmaf(fabsf(x), inv4, 8388608.0f), 8388615.0f));
+                        const int sh = e < 4 ? 8 * e : 8 * ((e - 5) & 3) + 4;
+                        sum += mb << sh;
+                        // 1.5 * 2^23 + code, code in [-127, 127]: the low byte is the two's-complement MXINT8 code
+                        ub[e] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(x, to8, 12582912.0f), 12582785.0f, 12583039.0f));
+                    }
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t lo = __builtin_amdgcn_perm(ub[4 * h + 1], ub[4 * h], 0x0c0c0400u);      // bytes 0 of two dwords
+                        const uint32_t hi = __builtin_amdgcn_perm(ub[4 * h + 3], ub[4 * h + 2], 0x04000c0cu);  // ... in the upper half
+                        c8[h] = lo | hi;
+                    }
+                    const uint32_t s03 = __builtin_amdgcn_perm(w[1], w[0], 0x07050301u);
+                    const uint32_t s47 = __builtin_amdgcn_perm(w[3], w[2], 0x07050301u);
+                    const uint32_t pk = sum | (s03 & 0x80808080u) | ((s47 >> 4) & 0x08080808u);
+    if (row < p.nrb * 32) {
+        *(uint32_t*)(p.ho_xq + mxi_frag_offset(row, k0, p.ho_C64)) = pk;
+        *(uint2*)(p.ho_cb + (size_t)row * p.N + k0) = make_uint2(c8[0], c8[1]);
+        if ((k0 & 31) == 0) {
+            p.ho_xe[mxi_scale_offset(row, k0 >> 6, (k0 >> 5) & 1, p.ho_CQ)] = (uint8_t)(field + 7u);
+            p.ho_cbe[(size_t)row * (p.N >> 5) + (k0 >> 5)] = (uint8_t)field;
+            // padding chunks of the next layer's last quad: valid E8M0 bytes (2^0), written with the last real chunk
+            if ((k0 >> 6) == p.ho_C64 - 1)
+                for (int c = p.ho_C64; c < 4 * p.ho_CQ; ++c) p.ho_xe[mxi_scale_offset(row, c, (k0 >> 5) & 1, p.ho_CQ)] = (uint8_t)127;
+        }
+    }
+}
+
 // NK16 = 16-deep chunks of the rank: 0 | 2 | 4 | 6 | 8.  HO: quantized hand-off (Section 4.5): the epilogue also emits
 // the next layer's activation codes from the bf16 values it has just formed; Y itself is optional then.
 template <int NK16, bool DBG, bool HO = false>
@@ -998,61 +1051,8 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
 #pragma unroll
         for (int q = 0; q < 4; ++q) ov[q] = *(const v4i*)(stage + (q * 8 + rd_row) * EPI_ROW + rd_seg * 16);
         if constexpr (HO) {
-            // The lane holds 8 consecutive channels of one token as bf16; a block of 32 channels of the next layer's K
-            // axis is the 4 lanes that differ in the two low lane bits.  Codes as in the activation kernel: shared
-            // exponent from the block maximum, MXINT4 main codes (sign-magnitude nibbles), MXINT8 branch codes.
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = rbase + q * 8 + rd_row;
-                const uint32_t w[4] = {(uint32_t)ov[q][0], (uint32_t)ov[q][1], (uint32_t)ov[q][2], (uint32_t)ov[q][3]};
-                us2 m2 = {0, 0};
-#pragma unroll
-                for (int d = 0; d < 4; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, w[d] & 0x7FFF7FFFu));
-                uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
-                float am = __uint_as_float(mm << 16);
-                am = fmaxf(am, __shfl_xor(am, 1, 64));
-                am = fmaxf(am, __shfl_xor(am, 2, 64));
-                const uint32_t field = exp_field(am);
-                const float inv4 = field >= 2u ? __uint_as_float((256u - field) << 23) : 0.0f;   // 2^(2-s)
-                const float to8 = field >= 7u ? __uint_as_float((260u - field) << 23) : 0.0f;    // 2^(6-s)
-                // Both codes by one fused multiply-add each: scaling by a power of two is exact, so fma(x, 2^-step, magic)
-                // rounds the scaled value to the nearest integer (ties to even) in one step -- the same integer the
-                // activation kernel reaches by rounding on the block's grid and scaling afterwards -- and leaves it in
-                // the low mantissa bits of the magic number.  Clamping after the rounding equals clamping before it.
-                uint32_t sum = 0u - 0xFB000000u, c8[2];
-                uint32_t ub[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float x = __uint_as_float((e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16));
-                    const uint32_t mb = __float_as_uint(fminf(__builtin_fmaf(fabsf(x), inv4, 8388608.0f), 8388615.0f));
-                    const int sh = e < 4 ? 8 * e : 8 * ((e - 5) & 3) + 4;
-                    sum += mb << sh;
-                    // 1.5 * 2^23 + code, code in [-127, 127]: the low byte is the two's-complement MXINT8 code
-                    ub[e] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(x, to8, 12582912.0f), 12582785.0f, 12583039.0f));
-                }
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t lo = __builtin_amdgcn_perm(ub[4 * h + 1], ub[4 * h], 0x0c0c0400u);      // bytes 0 of two dwords
-                    const uint32_t hi = __builtin_amdgcn_perm(ub[4 * h + 3], ub[4 * h + 2], 0x04000c0cu);  // ... in the upper half
-                    c8[h] = lo | hi;
-                }
-                const uint32_t s03 = __builtin_amdgcn_perm(w[1], w[0], 0x07050301u);
-                const uint32_t s47 = __builtin_amdgcn_perm(w[3], w[2], 0x07050301u);
-                const uint32_t pk = sum | (s03 & 0x80808080u) | ((s47 >> 4) & 0x08080808u);
-                if (row < p.nrb * 32) {
-                    const int k0 = cb0 * 32 + rd_seg * 8;   // this layer's channel = the next layer's k
-                    *(uint32_t*)(p.ho_xq + mxi_frag_offset(row, k0, p.ho_C64)) = pk;
-                    *(uint2*)(p.ho_cb + (size_t)row * p.N + k0) = make_uint2(c8[0], c8[1]);
-                    if ((rd_seg & 3) == 0) {
-                        p.ho_xe[mxi_scale_offset(row, k0 >> 6, (k0 >> 5) & 1, p.ho_CQ)] = (uint8_t)(field + 7u);
-                        p.ho_cbe[(size_t)row * (p.N >> 5) + (k0 >> 5)] = (uint8_t)field;
-                        // padding chunks of the next layer's last quad: valid E8M0 bytes (2^0), written by the wavefront
-                        // that owns the last real chunk
-                        if ((k0 >> 6) == p.ho_C64 - 1)
-                            for (int c = p.ho_C64; c < 4 * p.ho_CQ; ++c) p.ho_xe[mxi_scale_offset(row, c, (k0 >> 5) & 1, p.ho_CQ)] = (uint8_t)127;
-                    }
-                }
-            }
+            for (int q = 0; q < 4; ++q) mxi_handoff_emit(p, ov[q], rbase + q * 8 + rd_row, cb0 * 32 + rd_seg * 8);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -1062,9 +1062,191 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
     }
 }
 
+// Small layers: a wavefront (a workgroup of its own) per tile of NRB*32 x NCB*32 outputs.  Where the 128 x 256 tiles leave most of the
+// chip idle, the time of a call is one tile's serial chain of steps; here nothing is shared between wavefronts (no LDS staging, no
+// barriers) and both operand streams are requested DEPTH quads of 64-chunks ahead, as packed nibbles, and expanded in registers.
+// Bounded by that chain for a few tiles (128 x 1152 -> 3456: 10.6 -> 4.2 us, 128 x 4608 -> 1152: 30.3 -> 8.6 us), by the operands' L2
+// traffic for many.  Same products in the same order as mxi_fwd_kernel.  HO: as there.
+template <int NK16, bool DBG, bool HO, int NRB, int NCB>
+__global__ __launch_bounds__(64, 2) void mxi_fwd_small_kernel(MxiFwdParams p)
+{
+    if constexpr (HO) write_tag(p.ho_tag_dst, p.ho_tag);
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    constexpr int RSRC_FLAGS = 0x00020000;
+    constexpr int DEPTH = NRB + NCB == 2 ? 4 : NRB + NCB == 3 ? 2 : 1;  // quads in flight (17 registers per row or column block each)
+    constexpr int ROW = 64 * NCB + 16;                                  // bytes per staged output row
+    __shared__ __attribute__((aligned(16))) uint8_t stage[32 * ROW];
+
+    const int lane = threadIdx.x, half = lane >> 5, l32 = lane & 31;
+    // row blocks fastest: the tiles that read one column block's weights run together on one XCD
+    const int tiles = p.tilesM * p.tilesN, per = tiles >> 3, rem = tiles & 7, xcd = blockIdx.x & 7;
+    const int tile = xcd * per + (xcd < rem ? xcd : rem) + ((int)blockIdx.x >> 3);
+    const int tile_n = tile / p.tilesM, rb0 = (tile - tile_n * p.tilesM) * NRB, cb0 = tile_n * NCB;
+    const int C64 = p.C64, CQ = p.CQ;
+    const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
+
+    int rbc[NRB];  // row blocks past the end are clamped; their results are not stored
+#pragma unroll
+    for (int i = 0; i < NRB; ++i) rbc[i] = rb0 + i < p.nrb ? rb0 + i : p.nrb - 1;
+    __amdgpu_buffer_rsrc_t rs_x[NRB], rs_xe[NRB];
+#pragma unroll
+    for (int i = 0; i < NRB; ++i) {
+        rs_x[i] = __builtin_amdgcn_make_buffer_rsrc((void*)(p.xq + (size_t)rbc[i] * C64 * 1024), 0, C64 * 1024, RSRC_FLAGS);
+        rs_xe[i] = __builtin_amdgcn_make_buffer_rsrc((void*)(p.xe + (size_t)rbc[i] * CQ * 256), 0, CQ * 256, RSRC_FLAGS);
+    }
+    const __amdgpu_buffer_rsrc_t rs_p = __builtin_amdgcn_make_buffer_rsrc((void*)(p.pq + (size_t)cb0 * C64 * 1024), 0, NCB * C64 * 1024, RSRC_FLAGS);
+    const __amdgpu_buffer_rsrc_t rs_pe = __builtin_amdgcn_make_buffer_rsrc((void*)(p.pe + (size_t)cb0 * CQ * 256), 0, NCB * CQ * 256, RSRC_FLAGS);
+
+    struct Chunk { v4i a[NRB], b[NCB]; };
+    struct Quad { Chunk c[4]; int sa[NRB], sb[NCB]; };
+    auto load_scales = [&](Quad& t, int quad) {  // (quads and chunks past the end are clamped: fetched, not used)
+        const int q = quad < CQ ? quad : CQ - 1;
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) t.sa[i] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_xe[i], lane4, q * 256, 0);
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) t.sb[j] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_pe, lane4, (j * CQ + q) * 256, 0);
+    };
+    auto load_chunk = [&](Chunk& t, int chunk) {
+        const int c = chunk < C64 ? chunk : C64 - 1;
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) t.b[j] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_p, lane16, (j * C64 + c) * 1024, 0));
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) t.a[i] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_x[i], lane16, c * 1024, 0));
+    };
+    Quad qd[DEPTH];
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) {
+        load_scales(qd[i], i);
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) load_chunk(qd[i].c[cc], 4 * i + cc);
+    }
+
+    v16f t[NRB][NCB];
+#pragma unroll
+    for (int i = 0; i < NRB; ++i)
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) t[i][j] = v16f{0};
+    // one chunk; its registers are refilled with the chunk DEPTH quads further on as soon as they have been expanded
+    auto chunk = [&](Quad& q, const int (&sa)[NRB], const int (&sb)[NCB], auto cc_tag, int quad) {
+        constexpr int CC = decltype(cc_tag)::value;
+        v8i ae[NRB], be[NCB];
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) ae[i] = mxi_expand8(q.c[CC].a[i]);
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) be[j] = mxi_expand8(q.c[CC].b[j]);
+        load_chunk(q.c[CC], 4 * (quad + DEPTH) + CC);
+        if (4 * quad + CC < C64) {
+#pragma unroll
+            for (int i = 0; i < NRB; ++i)
+#pragma unroll
+                for (int j = 0; j < NCB; ++j)
+                    t[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ae[i], be[j], t[i][j], 0, 0, CC, sa[i], CC, sb[j]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](Quad& q, int quad) {
+        int sa[NRB], sb[NCB];
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) sa[i] = q.sa[i];
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) sb[j] = q.sb[j];
+        load_scales(q, quad + DEPTH);
+        chunk(q, sa, sb, std::integral_constant<int, 0>{}, quad);
+        chunk(q, sa, sb, std::integral_constant<int, 1>{}, quad);
+        chunk(q, sa, sb, std::integral_constant<int, 2>{}, quad);
+        chunk(q, sa, sb, std::integral_constant<int, 3>{}, quad);
+    };
+    int q0 = 0;
+    for (; q0 + DEPTH <= CQ; q0 += DEPTH) {
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) multiply(qd[i], q0 + i);
+    }
+#pragma unroll
+    for (int i = 0; i < DEPTH - 1; ++i)
+        if (q0 + i < CQ) multiply(qd[i], q0 + i);
+
+    // ---- rank-r expansion and epilogue as in mxi_fwd_kernel
+#pragma unroll
+    for (int ch = 0; ch < NK16; ++ch) {
+        v4i lf[NCB];
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) lf[j] = *(const v4i*)(p.lv + ((size_t)((size_t)(cb0 + j) * NK16 + ch) * 64 + lane) * 16);
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) {
+            const v4i tf = *(const v4i*)(p.tv + ((size_t)((size_t)rbc[i] * NK16 + ch) * 64 + lane) * 16);
+#pragma unroll
+            for (int j = 0; j < NCB; ++j)
+                t[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, tf), __builtin_bit_cast(v8bf, lf[j]), t[i][j], 0, 0, 0);
+        }
+    }
+    const bool have_y = !HO || p.Y;
+    const int rows_valid = p.M - rb0 * 32 < NRB * 32 ? p.M - rb0 * 32 : NRB * 32;
+    const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
+        have_y ? (void*)(p.Y + (size_t)(rb0 * 32) * p.ldy + cb0 * 32) : (void*)p.ho_xq, 0,
+        have_y ? (int)((rows_valid - 1) * p.ldy * 2 + NCB * 64) : 0, RSRC_FLAGS);
+#pragma unroll
+    for (int i = 0; i < NRB; ++i) {
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) {
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+                const bf16x2 h = __builtin_convertvector(f32x2{t[i][j][e], t[i][j][e + 1]}, bf16x2);
+                const uint32_t w = __builtin_bit_cast(uint32_t, h);
+                const int o = (8 * (e >> 2) + 4 * half + (e & 3)) * ROW + j * 64 + l32 * 2;
+                *(uint16_t*)(stage + o) = (uint16_t)(w & 0xFFFFu);
+                *(uint16_t*)(stage + o + ROW) = (uint16_t)(w >> 16);
+            }
+            if (DBG) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int row = (rb0 + i) * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+                    if (row < p.M && p.dbg_y32) p.dbg_y32[(size_t)row * p.N + (cb0 + j) * 32 + l32] = t[i][j][e];
+                }
+            }
+        }
+        // read back row-wise (LDS operations of one wavefront complete in order): 4 NCB lanes per row of 64 NCB bytes
+        constexpr int LR = 4 * NCB, RP = 64 / LR;
+#pragma unroll
+        for (int q = 0; q < 32 / RP; ++q) {
+            const int row = q * RP + lane / LR, seg = (lane % LR) * 16;
+            const v4i o = *(const v4i*)(stage + row * ROW + seg);
+            if constexpr (HO) mxi_handoff_emit(p, o, (rb0 + i) * 32 + row, cb0 * 32 + seg / 2);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, o), rs_y, (i * 32 + row) * (int)p.ldy * 2 + seg, 0, 0);
+        }
+    }
+}
+
+template <int NK16, bool DBG, bool HO>
+static void mxi_fwd_small_launch(MxiFwdParams p, int rbt, int cbt, hipStream_t s)
+{
+    p.tilesN = p.N / 32 / cbt;
+    p.tilesM = (p.nrb + rbt - 1) / rbt;
+    const dim3 grid((unsigned)(p.tilesM * p.tilesN)), block(64);
+    if (rbt == 1) hipLaunchKernelGGL((mxi_fwd_small_kernel<NK16, DBG, HO, 1, 1>), grid, block, 0, s, p);
+    else if (cbt == 1) hipLaunchKernelGGL((mxi_fwd_small_kernel<NK16, DBG, HO, 2, 1>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((mxi_fwd_small_kernel<NK16, DBG, HO, 2, 2>), grid, block, 0, s, p);
+}
+
 template <int NK16>
 static void mxi_fwd_launch(const MxiFwdParams& p, hipStream_t s)
 {
+    // Small layers, by the number T of 32 x 32 tiles (the device holds 2048 wavefronts of these kernels): one tile to a
+    // wavefront, larger ones as the L2 traffic of the operands (2, 1.5 and 1 KB per tile and 64-chunk) begins to count, the
+    // 128 x 256 tiles once they occupy enough of the chip.  us, 1 x 1 / 2 x 1 / 2 x 2 / 128 x 256:
+    //   T =  108 (   2 x 1152 -> 3456): 3.7 / 4.7 / 6.6 / 10.4        T = 3360 ( 512 x 2240 -> 6720): 17.6 / 13.7 / 14.4 / 19.5
+    //   T =  144 ( 128 x 4608 -> 1152): 8.6 / 13.1 / 19.3 / 30.3      T = 5076 (1500 x 1152 -> 3456): 15.7 / 13.4 / 12.0 / 13.5
+    //   T = 1152 (1024 x 4608 -> 1152): 14.2 / 16.1 / 22.3 / 34.0     T = 6720 (1024 x 2240 -> 6720): 29.9 / 24.3 / 19.4 / 21.4
+    //   T = 1728 ( 512 x 1152 -> 3456): 6.9 / 6.3 / 7.8 / 10.9        T = 13440 (2048 x 2240 -> 6720): 53.0 / 41.9 / 35.3 / 30.6
+    const int64_t T = (int64_t)p.nrb * (p.N / 32);
+    if (T <= 7000) {
+        const int rbt = T <= 1400 ? 1 : 2, cbt = T <= 3600 ? 1 : 2;
+        if (p.ho_xq) mxi_fwd_small_launch<NK16, false, true>(p, rbt, cbt, s);
+        else if (p.dbg_y32) mxi_fwd_small_launch<NK16, true, false>(p, rbt, cbt, s);
+        else mxi_fwd_small_launch<NK16, false, false>(p, rbt, cbt, s);
+        return;
+    }
     dim3 grid((unsigned)(p.tilesM * p.tilesN)), block(256);
     if (p.ho_xq)
         hipLaunchKernelGGL((mxi_fwd_kernel<NK16, false, true>), grid, block, 0, s, p);

@@ -73,6 +73,8 @@ def _run(oracle, M, K1, N1, N2, r1, r2, bw, seed, with_y):
     (64, 64, 128, 64, 0, 0, 8, False),          # no branch on either side
     (200, 320, 192, 320, 32, 0, 8, False),
     (1, 128, 64, 64, 32, 32, 8, True),
+    (397, 192, 4032, 64, 32, 32, 8, True),      # the producer's 64 x 32 tiles, an odd number of row blocks
+    (1700, 320, 2240, 64, 32, 64, 4, True),     # ... and its 64 x 64 tiles
     (6145, 64, 320, 64, 32, 64, 8, False),      # the step from codes on 32-row workgroups
     (12290, 64, 576, 64, 32, 128, 4, False),    # ... and on 64-row workgroups, the last one partly past M
 ])

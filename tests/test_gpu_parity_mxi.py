@@ -195,3 +195,14 @@ def test_activation_row_forms(oracle, M, K, r, bw, xd):
     X, W, L, R = wl.make_inputs(layer)
     rows = np.unique(np.concatenate([np.arange(M - 70, M), np.arange(40), np.arange(0, M, 997)]))
     _compare(oracle, layer, X, W, L, R, rows=rows)
+
+
+# Forms of the forward by the number of 32 x 32 tiles: 1 x 1 to 1400, 2 x 1 to 3600, 2 x 2 to 7000, 128 x 256 tiles above; ragged M, an odd
+# number of row blocks, fewer and more quads of chunks than are kept in flight, last quads of one to four chunks.
+@pytest.mark.parametrize("M,K,N,r,bw", [(790, 1152, 1664, 32, 8), (397, 704, 4032, 64, 4), (1130, 320, 2176, 128, 8), (1700, 448, 2176, 96, 4),
+                                        (2300, 64, 2112, 64, 8), (3300, 576, 2176, 32, 8), (401, 2240, 4032, 0, 8)])
+def test_forward_forms(oracle, M, K, N, r, bw):
+    layer = wl.Layer("t", M, K, N, r, "mxi", 32, bw, 8, "bf16", seed=M + N)
+    X, W, L, R = wl.make_inputs(layer)
+    rows = np.unique(np.concatenate([np.arange(M - 40, M), np.arange(0, M, 61)]))
+    _compare(oracle, layer, X, W, L, R, rows=rows)
