@@ -57,17 +57,18 @@ __device__ __forceinline__ v6u fp6_block_from_f32(const float* v, float sc)
         a[j] = v[2 * j];
         b[j] = v[2 * j + 1];
     }
-    const v6u c = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, sc);
+    v6u c = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, sc);
     // The converter writes its six result registers over several passes while still reading its sources,
     // and the register allocator is not told: without the sources being live past it, it has been seen
-    // to place the result on top of the scale register (positions 0 and 1 right, the rest garbage).
-    asm volatile("" : : "v"(a), "v"(b), "v"(sc));
+    // to place the result on top of the scale register (positions 0 and 1 right, the rest garbage).  The result passes
+    // through the statement: one that only reads the sources may be moved ahead of the conversion.
+    asm volatile("" : "+v"(c) : "v"(a), "v"(b), "v"(sc));
     return c;
 }
 __device__ __forceinline__ v6u fp6_block_from_bf16(v32bf h, float sc)
 {
-    const v6u c = __builtin_amdgcn_cvt_scalef32_pk32_fp6_bf16(h, sc);
-    asm volatile("" : : "v"(h), "v"(sc));  // as above
+    v6u c = __builtin_amdgcn_cvt_scalef32_pk32_fp6_bf16(h, sc);
+    asm volatile("" : "+v"(c) : "v"(h), "v"(sc));  // as above
     return c;
 }
 
