@@ -7,10 +7,10 @@
 // SINT4 blocks (App. A.3; template flag GA): the main codes take one FP16 scale per 64-chunk of K instead
 // of one scale per token, sx[m,g] = fp16(amax_g / 7), codes clamp(rne(x * fl(1 / sx))); the branch is unchanged.
 //
-// Decomposition: a workgroup of 4 wavefronts owns 16 token rows; lane l of every wavefront
+// Decomposition: a workgroup of NW = 4 or 8 wavefronts owns 16 token rows; lane l of every wavefront
 // works on row l%16 and on the 16-value quarter l/16 of each 64-deep K chunk, which is
 // exactly the A-operand layout of v_mfma_i32_16x16x64_i8.  The 64-chunks of K are dealt
-// round-robin to the 4 wavefronts, so a whole row block lives in registers between the
+// round-robin to the wavefronts, so a whole row block lives in registers between the
 // amax pass and the quantisation pass: X is read from HBM once.  Rows too long for that (MAXC = 0) are
 // streamed twice through a two-chunk ring instead: once for the amax, once for the codes (the second read
 // comes from the caches: a workgroup's 16 rows are at most a few hundred KB).
@@ -139,26 +139,28 @@ __device__ __forceinline__ void f6_codes16(const float (&v)[16], uint32_t (&out)
     const v16f a = __builtin_shufflevector(ev, ev, 0, 1, 2, 3, 4, 5, 6, 7, -1, -1, -1, -1, -1, -1, -1, -1);
     const v16f b = __builtin_shufflevector(od, od, 0, 1, 2, 3, 4, 5, 6, 7, -1, -1, -1, -1, -1, -1, -1, -1);
     const float sc = 8.0f;
-    const v6u c = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, sc);
+    v6u c = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, sc);
     // The converter writes its result registers over several passes while still reading its sources, and the
-    // register allocator is not told: the sources are kept live past it so that the result cannot land on them.
-    asm volatile("" : : "v"(a), "v"(b), "v"(sc));
+    // register allocator is not told: the sources are kept live past it so that the result cannot land on them.  (The
+    // result passes through the statement: one that only reads the sources may be moved ahead of the conversion.)
+    asm volatile("" : "+v"(c) : "v"(a), "v"(b), "v"(sc));
     out[0] = c[0];
     out[1] = c[1];
     out[2] = c[2];
 }
 
 // BF16IN: element type of X; SM: smoothing variant (X times stored reciprocals, row held as fp32).
-template <bool BF16IN, int MAXC, int NJB, bool SM = false, bool GA = false>
-__global__ __launch_bounds__(256) void act_int_kernel(ActParams p)
+template <bool BF16IN, int MAXC, int NJB, bool SM, bool GA, int NW>
+__global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
 {
     write_tag(p.tag_dst, p.tag);
     constexpr bool BF16 = BF16IN && !SM;  // representation of the row in registers
-    __shared__ float s_amax[4][16];
+    __shared__ float s_amax[NW][16];
     __shared__ float s_sxb[16];
-    __shared__ int s_acc[4][NJB > 0 ? NJB : 1][64][4];  // [wave][j block][lane][4]
+    __shared__ int s_acc[NW][NJB > 0 ? NJB : 1][64][4];  // [wave][j block][lane][4]
+    __shared__ float s_tmax[NW][16];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: with smoothing, whose row is fp32 in registers, 8192 x 2240 took 29.6 us with it in a vector register and takes 18.0
     const int r16 = lane & 15, kq = lane >> 4;
     const int row = blockIdx.x * 16 + r16;
     const bool row_ok = row < p.M;
@@ -167,10 +169,10 @@ __global__ __launch_bounds__(256) void act_int_kernel(ActParams p)
 
     constexpr bool STREAM = MAXC == 0;
     constexpr int NS = STREAM ? 2 : MAXC;            // chunk slots in registers
-    const int nmy = (C64 - wave + 3) >> 2;           // chunks of this wavefront: c = wave + 4 * ci, ci < nmy
+    const int nmy = (C64 - wave + NW - 1) / NW;      // chunks of this wavefront: c = wave + NW * ci, ci < nmy
     XChunk<BF16> xc[NS];
     auto load_x = [&](XChunk<BF16>& ch, int ci) {
-        const int c = wave + 4 * ci;
+        const int c = wave + NW * ci;
         const size_t koff = (size_t)c * 64 + kq * 16;
         if constexpr (SM)
             load_smoothed<BF16IN>(ch, p.X, (size_t)row * p.ldx + koff, p.rg + (c < C64 ? koff : 0), row_ok && c < C64);
@@ -186,15 +188,17 @@ __global__ __launch_bounds__(256) void act_int_kernel(ActParams p)
     constexpr int NJA = NJB > 0 ? NJB : 1;
     v4i bv[2][NJA];
     auto load_rq = [&](v4i (&dst)[NJA], int ci) {
-        int c = wave + 4 * ci;
+        int c = wave + NW * ci;
         c = c < C64 ? c : C64 - 1;  // clamped: a fragment past the end is fetched but not used
 #pragma unroll
         for (int jb = 0; jb < NJB; ++jb) dst[jb] = *(const v4i*)(p.rq + ((size_t)((size_t)c * NJB + jb) * 64 + lane) * 16);
     };
     load_rq(bv[0], 0);
-    float srj[NJA];
+    constexpr int PW = NJB <= 2 ? 1 : NW;        // wavefronts that re-quantise the intermediate
+    constexpr int NT = (NJA + PW - 1) / PW;      // column blocks each of them takes
+    float srj[NT];
 #pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) srj[jb] = p.sr[jb * 16 + r16];
+    for (int t = 0; t < NT; ++t) srj[t] = p.sr[(wave + PW * t < NJB ? wave + PW * t : 0) * 16 + r16];
 
     // ---- per-row amax -------------------------------------------------------------------
     float a = 0.f;
@@ -231,7 +235,8 @@ __global__ __launch_bounds__(256) void act_int_kernel(ActParams p)
     a = fmaxf(a, __shfl_xor(a, 32, 64));
     if (kq == 0) s_amax[wave][r16] = a;
     __syncthreads();
-    a = fmaxf(fmaxf(s_amax[0][r16], s_amax[1][r16]), fmaxf(s_amax[2][r16], s_amax[3][r16]));
+#pragma unroll
+    for (int w = 0; w < NW; ++w) a = fmaxf(a, s_amax[w][r16]);
 
     float s4, inv4, sb, invb;
     scales(a, 7.0f, &s4, &inv4);
@@ -332,7 +337,7 @@ __global__ __launch_bounds__(256) void act_int_kernel(ActParams p)
         for (int ci0 = 0; ci0 < nmy; ci0 += 2) {
 #pragma unroll
             for (int sl = 0; sl < 2; ++sl) {
-                const int ci = ci0 + sl, c = wave + 4 * ci;
+                const int ci = ci0 + sl, c = wave + NW * ci;
                 load_rq(bv[(sl + 1) & 1], ci + 1);
                 if (c < C64) code_chunk(xc[sl], c, sl);  // wave-uniform
                 load_x(xc[sl], ci + 2);
@@ -341,42 +346,40 @@ __global__ __launch_bounds__(256) void act_int_kernel(ActParams p)
     } else {
 #pragma unroll
         for (int ci = 0; ci < NS; ++ci) {
-            const int c = wave + 4 * ci;
+            const int c = wave + NW * ci;
             if (ci + 1 < NS) load_rq(bv[(ci + 1) & 1], ci + 1);
             if (c < C64) code_chunk(xc[ci], c, ci & 1);  // wave-uniform
         }
     }
     if (njb == 0) return;
 
-    // ---- combine the 4 wavefronts' partial accumulators, dequantise, re-quantise ----------
+    // ---- combine the wavefronts' partial accumulators, dequantise, re-quantise.  Up to two column blocks: the first wavefront;
+    // more: wavefront w takes the column blocks w, w + NW, and the row maxima meet in LDS
 #pragma unroll
     for (int jb = 0; jb < NJB; ++jb) *(v4i*)&s_acc[wave][jb][lane][0] = acc[jb];
     __syncthreads();
-    if (wave != 0) return;
+    if (wave >= PW) return;
 
     // lane holds column j = jb*16 + lane%16 and token rows 4*(lane/16) + i
-    float T[NJB > 0 ? NJB : 1][4];
+    float T[NT][4];
     float tmax[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) {
-        {
-            v4i s = *(const v4i*)&s_acc[0][jb][lane][0];
+    for (int t = 0; t < NT; ++t) {
+        const int jb = wave + PW * t;
+        if (jb >= NJB) break;  // wave-uniform
+        v4i s = *(const v4i*)&s_acc[0][jb][lane][0];
 #pragma unroll
-            for (int w = 1; w < 4; ++w) {
-                const v4i o = *(const v4i*)&s_acc[w][jb][lane][0];
-                s += o;
-            }
+        for (int w = 1; w < NW; ++w) s += *(const v4i*)&s_acc[w][jb][lane][0];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int tok = 4 * kq + i;
-                const float tv = __fmul_rn(__fmul_rn((float)s[i], s_sxb[tok]), srj[jb]);
-                T[jb][i] = tv;
-                tmax[i] = fmaxf(tmax[i], fabsf(tv));
-                const int grow = blockIdx.x * 16 + tok;
-                if (grow < p.M) {
-                    if (p.dbg_accT) p.dbg_accT[(size_t)grow * p.r + jb * 16 + r16] = s[i];
-                    if (p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = tv;
-                }
+        for (int i = 0; i < 4; ++i) {
+            const int tok = 4 * kq + i;
+            const float tv = __fmul_rn(__fmul_rn((float)s[i], s_sxb[tok]), srj[t]);
+            T[t][i] = tv;
+            tmax[i] = fmaxf(tmax[i], fabsf(tv));
+            const int grow = blockIdx.x * 16 + tok;
+            if (grow < p.M) {
+                if (p.dbg_accT) p.dbg_accT[(size_t)grow * p.r + jb * 16 + r16] = s[i];
+                if (p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = tv;
             }
         }
     }
@@ -385,43 +388,83 @@ __global__ __launch_bounds__(256) void act_int_kernel(ActParams p)
 #pragma unroll
         for (int o = 8; o >= 1; o >>= 1) tmax[i] = fmaxf(tmax[i], __shfl_xor(tmax[i], o, 64));
     }
+    if constexpr (PW > 1) {
+        if (r16 == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s_tmax[wave][4 * kq + i] = tmax[i];
+        }
+        __syncthreads();  // (every wavefront: PW = NW)
+#pragma unroll
+        for (int w = 0; w < PW; ++w)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tmax[i] = fmaxf(tmax[i], s_tmax[w][4 * kq + i]);
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int grow = blockIdx.x * 16 + 4 * kq + i;
         float stv, invt;
         scales(tmax[i], p.qa, &stv, &invt);
-        if (r16 == 0) p.st[grow] = stv;
 #pragma unroll
-        for (int jb = 0; jb < NJB; ++jb)
-            p.tq[(size_t)grow * p.rp + jb * 16 + r16] = (int8_t)(rne_bits(__fmul_rn(T[jb][i], invt)) & 0xFFu);
-        if (p.rp > p.r && r16 < (p.rp - p.r)) p.tq[(size_t)grow * p.rp + p.r + r16] = 0;
+        for (int t = 0; t < NT; ++t) {
+            const int jb = wave + PW * t;
+            if (jb >= NJB) break;
+            p.tq[(size_t)grow * p.rp + jb * 16 + r16] = (int8_t)(rne_bits(__fmul_rn(T[t][i], invt)) & 0xFFu);
+        }
+        if (wave == 0) {
+            if (r16 == 0) p.st[grow] = stv;
+            if (p.rp > p.r && r16 < (p.rp - p.r)) p.tq[(size_t)grow * p.rp + p.r + r16] = 0;
+        }
     }
 }
 
-template <bool BF16, int MAXC, int NJB, bool SM, bool GA>
+template <bool BF16, int MAXC, int NJB, bool SM, bool GA, int NW>
 static hipError_t launch_one(const ActParams& p, int64_t Mp, hipStream_t s)
 {
-    hipLaunchKernelGGL((act_int_kernel<BF16, MAXC, NJB, SM, GA>), dim3((unsigned)(Mp / 16)), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((act_int_kernel<BF16, MAXC, NJB, SM, GA, NW>), dim3((unsigned)(Mp / 16)), dim3(NW * 64), 0, s, p);
     return hipGetLastError();
 }
 
-template <bool BF16, int MAXC, bool SM, bool GA>
+template <bool BF16, int MAXC, bool SM, bool GA, int NW>
 static hipError_t launch_rank2(const ActParams& p, int64_t Mp, hipStream_t s)
 {
     switch (p.r) {
-        case 0: return launch_one<BF16, MAXC, 0, SM, GA>(p, Mp, s);
-        case 16: return launch_one<BF16, MAXC, 1, SM, GA>(p, Mp, s);
-        case 32: return launch_one<BF16, MAXC, 2, SM, GA>(p, Mp, s);
-        case 64: return launch_one<BF16, MAXC, 4, SM, GA>(p, Mp, s);
-        case 96: return launch_one<BF16, MAXC, 6, SM, GA>(p, Mp, s);
-        default: return launch_one<BF16, MAXC, 8, SM, GA>(p, Mp, s);
+        case 0: return launch_one<BF16, MAXC, 0, SM, GA, NW>(p, Mp, s);
+        case 16: return launch_one<BF16, MAXC, 1, SM, GA, NW>(p, Mp, s);
+        case 32: return launch_one<BF16, MAXC, 2, SM, GA, NW>(p, Mp, s);
+        case 64: return launch_one<BF16, MAXC, 4, SM, GA, NW>(p, Mp, s);
+        case 96: return launch_one<BF16, MAXC, 6, SM, GA, NW>(p, Mp, s);
+        default: return launch_one<BF16, MAXC, 8, SM, GA, NW>(p, Mp, s);
     }
 }
 
-template <bool BF16, int MAXC, bool SM = false>
+template <bool BF16, int MAXC, bool SM, int NW>
 static hipError_t launch_rank(const ActParams& p, int64_t Mp, hipStream_t s)
 {
-    return p.sxg ? launch_rank2<BF16, MAXC, SM, true>(p, Mp, s) : launch_rank2<BF16, MAXC, SM, false>(p, Mp, s);
+    return p.sxg ? launch_rank2<BF16, MAXC, SM, true, NW>(p, Mp, s) : launch_rank2<BF16, MAXC, SM, false, NW>(p, Mp, s);
+}
+
+template <bool BF16, bool SM>
+static hipError_t launch_len(const ActParams& p, int64_t Mp, hipStream_t s)
+{
+    // Eight wavefronts to a workgroup while there is at most one workgroup per compute unit: the time is then one
+    // workgroup's chain (64 x 4608: 12.8 -> 10.8 us, SINT4 64 x 2240: 11.1 -> 9.1, 4096 x 4608: 18.7 -> 16.6); with more
+    // workgroups four are as fast or faster (8192 x 4608: 27.3 against 29.6, 16384 x 1152: 15.7 against 17.3).
+    if (Mp <= 16 * 256) {
+        const int mc = (p.C64 + 7) / 8;
+        if (mc <= 3) return launch_rank<BF16, 3, SM, 8>(p, Mp, s);
+        if (mc <= 5) return launch_rank<BF16, 5, SM, 8>(p, Mp, s);
+        if (mc <= 9) return launch_rank<BF16, 9, SM, 8>(p, Mp, s);
+        return launch_rank<BF16, 0, SM, 8>(p, Mp, s);
+    }
+    // MAXC = 0: the streamed kernel, for rows that do not fit in registers (fp32 representation: beyond 9 chunks per
+    // wavefront, K > 2304; bf16: beyond 18, K > 4608)
+    const int mc = (p.C64 + 3) / 4;
+    if (mc <= 5) return launch_rank<BF16, 5, SM, 4>(p, Mp, s);
+    if (mc <= 9) return launch_rank<BF16, 9, SM, 4>(p, Mp, s);
+    if constexpr (BF16 && !SM) {
+        if (mc <= 18) return launch_rank<BF16, 18, SM, 4>(p, Mp, s);
+    }
+    return launch_rank<BF16, 0, SM, 4>(p, Mp, s);
 }
 
 hipError_t launch_quantize_act_int(const Dims& d, int x_dtype, const uint8_t* packed, const void* X,
@@ -455,23 +498,8 @@ hipError_t launch_quantize_act_int(const Dims& d, int x_dtype, const uint8_t* pa
     p.dbg_accT = dbg ? dbg->accT : nullptr;
     p.dbg_T = dbg ? dbg->T : nullptr;
     p.rg = (const float*)(packed + pl.off_rg);
-    const int maxc = (d.C64 + 3) / 4;
-    // MAXC = 0: the streamed kernel, for rows that do not fit in registers (fp32 representation: beyond 9 chunks per
-    // wavefront, K > 2304; bf16: beyond 18, K > 4608)
-    if (d.smooth) {
-        if (x_dtype == LQ_BF16)
-            return maxc <= 5 ? launch_rank<true, 5, true>(p, al.Mp, s) : maxc <= 9 ? launch_rank<true, 9, true>(p, al.Mp, s) : launch_rank<true, 0, true>(p, al.Mp, s);
-        return maxc <= 5 ? launch_rank<false, 5, true>(p, al.Mp, s) : maxc <= 9 ? launch_rank<false, 9, true>(p, al.Mp, s) : launch_rank<false, 0, true>(p, al.Mp, s);
-    }
-    if (x_dtype == LQ_BF16) {
-        if (maxc <= 5) return launch_rank<true, 5>(p, al.Mp, s);
-        if (maxc <= 9) return launch_rank<true, 9>(p, al.Mp, s);
-        if (maxc <= 18) return launch_rank<true, 18>(p, al.Mp, s);
-        return launch_rank<true, 0>(p, al.Mp, s);
-    }
-    if (maxc <= 5) return launch_rank<false, 5>(p, al.Mp, s);
-    if (maxc <= 9) return launch_rank<false, 9>(p, al.Mp, s);
-    return launch_rank<false, 0>(p, al.Mp, s);
+    if (d.smooth) return x_dtype == LQ_BF16 ? launch_len<true, true>(p, al.Mp, s) : launch_len<false, true>(p, al.Mp, s);
+    return x_dtype == LQ_BF16 ? launch_len<true, false>(p, al.Mp, s) : launch_len<false, false>(p, al.Mp, s);
 }
 
 }  // namespace lq

@@ -398,3 +398,27 @@ def test_forward_forms_bit_exact(oracle, M, K, N, r, g, ag):
     _, _, out = run_oracle_int(oracle, layer, X[rows], W, L, R, want_acc=False)
     assert np.array_equal(bf16_to_bits(out_gpu.Y)[rows], out.Y)
     assert torch.equal(run_gpu(layer, X, W, L, R, debug=True, debug_acc=False).Y, out_gpu.Y)
+
+
+# Activation step: eight wavefronts to a workgroup up to 4096 rows, four above; row lengths at the edges of the register forms (3, 5, 9 chunks
+# per wavefront of eight; 5, 9, 18 of four; fp32 rows 9) and on the streamed form; every rank, fp32 input, SINT4 blocks, smoothing.
+@pytest.mark.parametrize("M,K,r,xd,ag,sm", [
+    (50, 64, 16, "bf16", 0, False), (33, 1536, 16, "bf16", 0, False), (40, 1600, 96, "bf16", 64, False), (47, 2560, 128, "f32", 0, False),
+    (31, 2624, 64, "bf16", 0, True), (18, 4608, 128, "bf16", 0, True), (17, 4672, 96, "f32", 64, True), (4090, 128, 32, "bf16", 64, True),
+    (4097, 1280, 16, "bf16", 0, False), (4100, 1344, 96, "f32", 0, True), (4127, 2304, 128, "bf16", 64, True), (4129, 2368, 64, "f32", 0, False),
+    (4110, 64, 0, "bf16", 0, False), (4111, 192, 96, "bf16", 0, True),
+])
+def test_activation_forms_bit_exact(oracle, M, K, r, xd, ag, sm):
+    layer = wl.Layer("t", M, K, 64, r, "int", 64, 8, 8, xd, outlier_scale=25.0, n_outliers=max(1, K // 100), seed=M + K, a_group=ag)
+    X, W, L, R = wl.make_inputs(layer)
+    gamma = np.exp(np.random.default_rng(K).uniform(-1, 1, K)).astype(np.float32) if sm else None
+    g = run_gpu(layer, X, W, L, R, debug=False, gamma=gamma)
+    rows = np.unique(np.concatenate([np.arange(max(0, M - 40), M), np.arange(0, M, 61)]))
+    Xo = X[rows] if gamma is None else oracle.smooth(X[rows], gamma)
+    _, act, out = run_oracle_int(oracle, layer, Xo, W, L, R, want_acc=False)
+    from paper_2604_18117_amd import binding as lq
+    av = lq.lq_unpack_act(g.cfg, g.act, M)
+    assert np.array_equal(n(av.xq)[rows], act.xq) and np.array_equal(n(av.sx)[rows], act.sx)
+    if r:
+        assert np.array_equal(n(av.tq)[rows], act.tq) and np.array_equal(n(av.st)[rows], act.st)
+    assert np.array_equal(bf16_to_bits(g.Y)[rows], out.Y)
