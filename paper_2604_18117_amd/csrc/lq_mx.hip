@@ -416,7 +416,7 @@ __global__ __launch_bounds__(256) void mx_act_kernel(MxActParams p)
     __shared__ float s_sxb[16];
     __shared__ float s_acc[4][NJB > 0 ? NJB : 1][64][4];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, kq = lane >> 4;
     const int row = blockIdx.x * 16 + r16;
     const bool row_ok = row < p.M;
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(256) void mxb_act_kernel(MxbActParams p)
     constexpr int PF = 2;  // 128-chunks in flight per wavefront: no scale spans more than a block, the row is streamed
     __shared__ float s_acc[4][NJA][64][4];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, q = lane >> 4;
     const int row = blockIdx.x * 16 + r16;
     const bool row_ok = row < p.M;
@@ -829,32 +829,33 @@ __global__ __launch_bounds__(256) void mxb_act_kernel(MxbActParams p)
 #pragma unroll
     for (int jb = 0; jb < NJB; ++jb) *(v4f*)&s_acc[wave][jb][lane][0] = acc[jb];
     __syncthreads();
-    if (wave != 0) return;
-
-    // lane holds column j = jb*16 + lane%16 of the intermediate for token rows 4*q + i
-    float T[NJA][4];
+    // Sum over the wavefronts, re-quantise per token and per block of 32 along the rank: a block (two 16-column groups) to a
+    // wavefront.  The lane holds columns (2 bb + g) * 16 + lane%16 of the intermediate for token rows 4*q + i.
 #pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) {
-        v4f sum = *(const v4f*)&s_acc[0][jb][lane][0];
+    for (int bb0 = 0; bb0 < (NJB + 1) / 2; bb0 += 4) {
+        const int bb = bb0 + wave;
+        if (bb >= (NJB + 1) / 2) break;  // wave-uniform
+        float T[2][4];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
-            const v4f o = *(const v4f*)&s_acc[w][jb][lane][0];
+        for (int g = 0; g < 2; ++g) {
+            const int jb = 2 * bb + g;
+            v4f sum = *(const v4f*)&s_acc[0][jb][lane][0];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) sum[i] = __fadd_rn(sum[i], o[i]);
+            for (int w = 1; w < 4; ++w) {
+                const v4f o = *(const v4f*)&s_acc[w][jb][lane][0];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum[i] = __fadd_rn(sum[i], o[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                T[g][i] = sum[i];
+                const int grow = blockIdx.x * 16 + 4 * q + i;
+                if (grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = sum[i];
+            }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            T[jb][i] = sum[i];
-            const int grow = blockIdx.x * 16 + 4 * q + i;
-            if (grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = sum[i];
-        }
-    }
-    // re-quantise per token and per block of 32 along the rank (two 16-column groups per block)
-#pragma unroll
-    for (int bb = 0; bb < (NJB + 1) / 2; ++bb) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float tm = fmaxf(fabsf(T[2 * bb][i]), fabsf(T[2 * bb + 1][i]));
+            float tm = fmaxf(fabsf(T[0][i]), fabsf(T[1][i]));
 #pragma unroll
             for (int o = 8; o >= 1; o >>= 1) tm = fmaxf(tm, __shfl_xor(tm, o, 64));
             const int grow = blockIdx.x * 16 + 4 * q + i;
@@ -863,9 +864,10 @@ __global__ __launch_bounds__(256) void mxb_act_kernel(MxbActParams p)
             if (r16 == 0) p.te[mxb_scale_offset(grow, bb)] = (uint8_t)E;
 #pragma unroll
             for (int g = 0; g < 2; ++g)
-                p.tq8[mxb_frag8_offset(grow, (2 * bb + g) * 16 + r16, p.rp)] = (uint8_t)fp8_byte(__fmul_rn(T[2 * bb + g][i], inv));
+                p.tq8[mxb_frag8_offset(grow, (2 * bb + g) * 16 + r16, p.rp)] = (uint8_t)fp8_byte(__fmul_rn(T[g][i], inv));
         }
     }
+    if (wave != 3) return;
     // padding of the rank to a multiple of 64: zero codes, scale 2^0
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

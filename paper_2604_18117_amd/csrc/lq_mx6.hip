@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void mx6_act_kernel(Mx6ActParams p)
     __shared__ float s_acc[4][NJA][64][4];
     __shared__ float s_T[16][NJA * 16 + 1];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, q = lane >> 4;
     const int row = blockIdx.x * 16 + r16;
     const bool row_ok = row < p.M;
@@ -376,23 +376,24 @@ __global__ __launch_bounds__(256) void mx6_act_kernel(Mx6ActParams p)
 #pragma unroll
     for (int jb = 0; jb < NJB; ++jb) *(v4f*)&s_acc[wave][jb][lane][0] = acc[jb];
     __syncthreads();
-    if (wave == 0) {
-        // lane holds column j = jb*16 + lane%16 of the intermediate for token rows 4*q + i
+    // sum over the wavefronts, a 16-column group to a wavefront: lane holds column j = jb*16 + lane%16 of the intermediate
+    // for token rows 4*q + i
 #pragma unroll
-        for (int jb = 0; jb < NJB; ++jb) {
-            v4f sum = *(const v4f*)&s_acc[0][jb][lane][0];
+    for (int jb0 = 0; jb0 < NJB; jb0 += 4) {
+        const int jb = jb0 + wave;
+        if (jb >= NJB) break;  // wave-uniform
+        v4f sum = *(const v4f*)&s_acc[0][jb][lane][0];
 #pragma unroll
-            for (int w = 1; w < 4; ++w) {
-                const v4f o = *(const v4f*)&s_acc[w][jb][lane][0];
+        for (int w = 1; w < 4; ++w) {
+            const v4f o = *(const v4f*)&s_acc[w][jb][lane][0];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) sum[i] = __fadd_rn(sum[i], o[i]);
-            }
+            for (int i = 0; i < 4; ++i) sum[i] = __fadd_rn(sum[i], o[i]);
+        }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                s_T[4 * q + i][jb * 16 + r16] = sum[i];
-                const int grow = blockIdx.x * 16 + 4 * q + i;
-                if (grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = sum[i];
-            }
+        for (int i = 0; i < 4; ++i) {
+            s_T[4 * q + i][jb * 16 + r16] = sum[i];
+            const int grow = blockIdx.x * 16 + 4 * q + i;
+            if (grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = sum[i];
         }
     }
     __syncthreads();
