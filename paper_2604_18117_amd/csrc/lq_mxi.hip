@@ -386,19 +386,22 @@ __global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams
         }
     };
     // R of super-step ss -> LDS buffer: lane l of an instruction writes 16 bytes at 16 l behind the wave-uniform address
-    constexpr int RI = RBUF / 1024 / (KW * ROWG);  // 1 KB instructions per wavefront
+    constexpr int RI = RBUF / 1024 / (KW * ROWG);  // 1 KB instructions per wavefront, all of one chunk
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-    const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc((void*)p.rv, 0, C64 * RCHUNK, 0x00020000);
+    auto chunk_r = [&](int c) {  // R of one chunk (a descriptor for all of it would end at 4 GB: K = 2^24 at rank 128 has as much)
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(p.rv + (size_t)c * RCHUNK), 0, RCHUNK, 0x00020000);
+    };
     auto load_r = [&](int ss) {
         if constexpr (STAGE) {
+            static_assert(RCHUNK / 1024 % RI == 0, "a wavefront's share of a super-step lies in one chunk");
+            const int c = KW * ss + wid * RI / (RCHUNK / 1024);    // (a chunk past the end is clamped: fetched, not used)
+            const __amdgpu_buffer_rsrc_t rs_r = chunk_r(c < C64 ? c : C64 - 1);
 #pragma unroll
             for (int i = 0; i < RI; ++i) {
                 const int piece = wid * RI + i;              // of RBUF / 1024
-                int c = KW * ss + piece / (RCHUNK / 1024);    // (a chunk past the end is clamped: fetched, not used)
-                c = c < C64 ? c : C64 - 1;
                 uint8_t* dst = lds + (ss & 1) * RBUF + piece * 1024;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_r, (__attribute__((address_space(3))) void*)dst, 16, lane * 16,
-                                                         c * RCHUNK + (piece % (RCHUNK / 1024)) * 1024, 0, 0);
+                                                         (piece % (RCHUNK / 1024)) * 1024, 0, 0);
             }
         }
     };
@@ -416,13 +419,14 @@ __global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams
         // fragment pairs of R read ahead: an LDS round trip is longer than a pair's products, an L2 round trip much longer
         constexpr int RD = NJA < (STAGE ? 3 : 4) ? NJA : STAGE ? 3 : 4;
         v4i rf[RD][2];
+        const __amdgpu_buffer_rsrc_t rs_r = chunk_r(have ? c : 0);
         auto read_pair = [&](int jb) {
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 if constexpr (STAGE)
                     rf[jb % RD][u] = *(const v4i*)(lds + (ss & 1) * RBUF + wave * RCHUNK + lane * 16 + (jb * 2 + u) * 1024);
                 else
-                    rf[jb % RD][u] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_r, lane * 16, (have ? c : 0) * RCHUNK + (jb * 2 + u) * 1024, 0));
+                    rf[jb % RD][u] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_r, lane * 16, (jb * 2 + u) * 1024, 0));
             }
         };
         load_r(ss + 1);

@@ -206,3 +206,41 @@ def test_forward_forms(oracle, M, K, N, r, bw):
     X, W, L, R = wl.make_inputs(layer)
     rows = np.unique(np.concatenate([np.arange(M - 40, M), np.arange(0, M, 61)]))
     _compare(oracle, layer, X, W, L, R, rows=rows)
+
+
+def test_rows_as_long_as_the_contract_allows():
+    """K = 2^24 at rank 128: the dequantised R is 4 GB.  Everything but the last chunk of X and R is zero, so the intermediate
+    is that of the last chunk alone: the codes of a layer with K = 64."""
+    from paper_2604_18117_amd import binding as lq
+    M, K, N, r = 3, 1 << 24, 64, 128
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    x = torch.randn((M, 64), generator=g, device="cuda").to(torch.bfloat16)
+    Rs = torch.randn((r, 64), generator=g, device="cuda")
+    L = torch.randn((N, r), generator=g, device="cuda")
+
+    def layer(k):
+        cfg = lq.make_config(N, k, r, "mxi", 32, 8, 8)
+        X, R, W = (torch.zeros(s, dtype=t, device="cuda") for s, t in (((M, k), torch.bfloat16), ((r, k), torch.float32), ((N, k), torch.float32)))
+        X[:, -64:], R[:, -64:] = x, Rs
+        packed = lq.lq_pack_weights(cfg, W, L, R)
+        del R, W
+        act = lq.lq_quantize_act(cfg, packed, X)
+        # the step from codes, on the codes the activation step rounds X to
+        codes = torch.zeros(lq.lq_handoff_sizes(cfg, M), dtype=torch.uint8, device="cuda")
+        blocks = X.float().view(M, k // 32, 32)
+        e = torch.frexp(blocks.abs().amax(2))[1].to(torch.int32) - 1
+        q = torch.round(torch.ldexp(blocks, 6 - e[..., None])).clamp(-127, 127).to(torch.int8)
+        q[blocks.abs().amax(2) == 0] = 0
+        codes[:M * k] = q.view(torch.uint8).reshape(-1)
+        scales = codes[codes.numel() - (32 * (k // 32) + 255) // 256 * 256:]
+        scales[:M * (k // 32)] = torch.where(blocks.abs().amax(2) == 0, 0, e + 127).to(torch.uint8).reshape(-1)
+        from_codes = lq.lq_branch_from_codes(cfg, packed, codes, M, torch.full_like(act, 0xFF))
+        views = [lq.lq_unpack_act(cfg, a, M) for a in (act, from_codes)]
+        torch.cuda.synchronize()
+        return [(v.tq.cpu(), v.te.cpu()) for v in views]
+
+    want = layer(64)[0]
+    assert want[0].any()
+    for got in layer(K):
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
