@@ -2,6 +2,8 @@
 // detected here, before any launch, so that all error paths can be exercised without a GPU.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+
 #include "lq_internal.h"
 
 namespace lq {
@@ -137,6 +139,19 @@ ActLayout act_layout(const Dims& d, int64_t M)
     o = align256(o + (d.mxi ? (size_t)al.Mp * (d.r / 32) + 4 : (size_t)al.Mp * (d.mxb ? 8 : 4)));
     al.total = o;
     return al;
+}
+
+int compute_units()
+{
+    static std::atomic<int> cached[64];
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    cus = cached[dev].load(std::memory_order_relaxed);
+    if (cus == 0) {
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+        cached[dev].store(cus, std::memory_order_relaxed);
+    }
+    return cus;
 }
 
 }  // namespace lq

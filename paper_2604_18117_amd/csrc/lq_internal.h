@@ -221,6 +221,8 @@ hipError_t launch_rot_apply(const Dims& d, const float* L, const float* R, const
                             hipStream_t s);
 hipError_t launch_rot_unpack(const Dims& d, const uint8_t* state, const lq_rot_view* out, hipStream_t s);
 
+int compute_units();  // of the current device
+
 // Tile order of the forward kernels: panels of `panel` tile columns (256 channels each), row-major inside a panel; the
 // last panel may be narrower.  The workgroups resident on an XCD at one time then share few weight column blocks: with
 // all tile columns in flight at once, the weight codes of a wide layer (7.5 MB at 2240 x 6720) do not stay in the XCD's

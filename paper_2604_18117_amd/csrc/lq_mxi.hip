@@ -247,18 +247,18 @@ hipError_t launch_unpack_act_mxi(const Dims& d, const uint8_t* act, int64_t M, c
 
 // ---------------------------------------------------------------------------------------------
 // activation kernel.  Every scale is local to a block of 32, so there is no pass over the whole row before coding: the row
-// is streamed and K is not limited by the register file.  A workgroup is ROWG x KW wavefronts; wavefront (rg, w) owns RPW
-// groups of 16 token rows and the chunks c = w mod KW of K; lane l works on row l%16 of each group and on the 16-value
+// is streamed and K is not limited by the register file.  A workgroup is ROWG x 4 wavefronts; wavefront (rg, w) owns RPW
+// groups of 16 token rows and the chunks c = w mod 4 of K; lane l works on row l%16 of each group and on the 16-value
 // quarter l/16 of a 64-chunk.
 //
 // What bounds it: the dequantised R (2 r K bytes) passes through every workgroup, at rank 128 several times the bytes of X.
-// Large batches (ROWG = 2) copy each super-step of KW chunks of it to LDS once per workgroup, directly and one super-step
+// Large batches (ROWG = 2) copy each super-step of 4 chunks of it to LDS once per workgroup, directly and one super-step
 // ahead, and a fragment read from there serves RPW groups of rows; small ones (ROWG = 1) have each wavefront read its own
 // chunks' fragments from the L2 while it codes X.  X is requested two super-steps ahead.  Chain of 16384 x 1152 -> 4608 -> 1152 at
-// rank 128: first activation step 31.5 -> 21.7 us, step from codes 60.7 -> 30.9 us (16 rows and four wavefronts per workgroup
-// before, R straight from the L2); 64 rows of 4608, rank 128: 19.5 -> 16.0 us.
-// T's sums run over a wavefront's chunks in ascending order and then over the wavefronts; the same sizes take the same
-// form in the step from codes, so a hand-off gives the bits of the two-call path.
+// rank 128: first activation step 31.5 -> 20.4 us, step from codes 60.7 -> 31.7 us (without LDS and with R requested a fragment
+// ahead); 64 rows of 4608, rank 128: 19.5 -> 17.6 us.  (Eight wavefronts along K take 16.2 us there, but then T is another sum.)
+// T is defined as four sums, each over the chunks c = w mod 4 in ascending order, added in the order of w: every form forms
+// these, so a token's codes do not depend on the batch it is in, and a hand-off gives the bits of the two-call path.
 // ---------------------------------------------------------------------------------------------
 struct MxiActParams {
     const void* X;
@@ -338,12 +338,13 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)  // upper halv
 // FROMC: the branch half of the step alone, from the MXINT8 codes of a quantized hand-off (the producing layer's
 // epilogue has already written this layer's main codes and scales): 16 code bytes and a scale byte replace the 16 values
 // of X, code * 2^(s-6) is the dequantised bf16 element; the contraction and the re-quantisation are the same code.
-template <bool BF16IN, int NJB, bool SM, bool FROMC, int RPW, int ROWG, int KW, bool DBG>
-__global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams p)
+template <bool BF16IN, int NJB, bool SM, bool FROMC, int RPW, int ROWG, bool DBG>
+__global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
 {
     write_tag(p.tag_dst, p.tag);
     constexpr bool BF16 = BF16IN && !SM;  // representation of a chunk in registers
     constexpr int NJA = NJB > 0 ? NJB : 1;
+    constexpr int KW = 4;                        // wavefronts along K: part of T's order of summation, the same in every form
     constexpr int NG = RPW * ROWG;               // groups of 16 rows per workgroup
     constexpr int RCHUNK = NJB * 2048;           // bytes of R per 64-chunk
     constexpr int RBUF = KW * RCHUNK;            // ... per super-step
@@ -412,27 +413,32 @@ __global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams
 #pragma unroll
         for (int jb = 0; jb < NJB; ++jb) acc[g][jb] = v4f{0.f, 0.f, 0.f, 0.f};
 
+    // Fragment pairs of R, RD ahead of their products: an LDS round trip is longer than a pair's products, an L2 round trip much
+    // longer.  Without STAGE they are requested before X is coded, up to rank 64 a super-step ahead (ROLL; us without / with it: rank 32,
+    // 4096 x 4608 16.5 / 14.7, rank 64 18.7 / 15.8; rank 128, 64 x 1152 7.1 / 7.5; from codes rank 64, 2 x 4608 7.6 / 10.3).
+    constexpr bool ROLL = !STAGE && !FROMC && !SM && NJB <= 4;
+    constexpr int RD = STAGE ? (NJA < 3 ? NJA : 3) : NJA < 4 ? NJA : 4;
+    v4i rf[RD][2];
+    auto read_pair = [&](int ss, int jb) {
+        const int c = KW * ss + wave;  // (past the end: clamped, fetched, not used)
+        const __amdgpu_buffer_rsrc_t rs_r = chunk_r(c < C64 ? c : C64 - 1);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if constexpr (STAGE)
+                rf[jb % RD][u] = *(const v4i*)(lds + (ss & 1) * RBUF + wave * RCHUNK + lane * 16 + (jb * 2 + u) * 1024);
+            else
+                rf[jb % RD][u] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_r, lane * 16, (jb * 2 + u) * 1024, 0));
+        }
+    };
+
     // One super-step: request R of the next one, code this one's X, request X of the one after the next, multiply.
     auto step = [&](XSet& st, int ss) {
         const int c = KW * ss + wave;
         const bool have = c < C64;  // wave-uniform
-        // fragment pairs of R read ahead: an LDS round trip is longer than a pair's products, an L2 round trip much longer
-        constexpr int RD = NJA < (STAGE ? 3 : 4) ? NJA : STAGE ? 3 : 4;
-        v4i rf[RD][2];
-        const __amdgpu_buffer_rsrc_t rs_r = chunk_r(have ? c : 0);
-        auto read_pair = [&](int jb) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                if constexpr (STAGE)
-                    rf[jb % RD][u] = *(const v4i*)(lds + (ss & 1) * RBUF + wave * RCHUNK + lane * 16 + (jb * 2 + u) * 1024);
-                else
-                    rf[jb % RD][u] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_r, lane * 16, (jb * 2 + u) * 1024, 0));
-            }
-        };
         load_r(ss + 1);
-        if constexpr (NJB > 0 && !STAGE) {
+        if constexpr (NJB > 0 && !STAGE && !ROLL) {
 #pragma unroll
-            for (int jb = 0; jb < RD; ++jb) read_pair(jb);
+            for (int jb = 0; jb < RD; ++jb) read_pair(ss, jb);
         }
         __builtin_amdgcn_sched_barrier(0);
         v4i au[RPW][2];
@@ -441,7 +447,9 @@ __global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams
             MxiChunk<BF16> ch = st.g[g];
             const int row = row0 + 16 * g + r16;
             const bool row_ok = row < p.M;
-            if (row0 + 16 * g + 16 > p.M && !row_ok) {  // only in the last workgroup
+            // zeros: a row past M (only in the last workgroup); ROLL: a chunk past the end, whose products are formed (a branch around
+            // them would end the compiler's count of the loads in flight)
+            if ((row0 + 16 * g + 16 > p.M && !row_ok) || (ROLL && !have)) {
                 if constexpr (BF16) {
 #pragma unroll
                     for (int d = 0; d < 8; ++d) ch.w[d] = 0u;
@@ -517,7 +525,7 @@ __global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams
 #pragma unroll
                     for (int i = 0; i < 16; ++i) v8[i] = mxint8_round(ch.get(i), field);
                 }
-                #pragma unroll
+#pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
                     for (int d = 0; d < 4; ++d) au[g][u][d] = (int)bf16_pair(v8[8 * u + 2 * d], v8[8 * u + 2 * d + 1]);
@@ -537,10 +545,10 @@ __global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (NJB > 0) {
-            if (have) {
+            if (ROLL || have) {
                 if constexpr (STAGE) {
 #pragma unroll
-                    for (int jb = 0; jb < RD; ++jb) read_pair(jb);
+                    for (int jb = 0; jb < RD; ++jb) read_pair(ss, jb);
                 }
 #pragma unroll
                 for (int jb = 0; jb < NJB; ++jb) {
@@ -552,7 +560,8 @@ __global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams
                             acc[g][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, au[g][u]),
                                                                                  __builtin_bit_cast(v8bf, rf[jb % RD][u]), acc[g][jb], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (jb + RD < NJB) read_pair(jb + RD);
+                    if (jb + RD < NJB) read_pair(ss, jb + RD);
+                    else if constexpr (ROLL) read_pair(ss + 1, jb + RD - NJB);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -561,13 +570,17 @@ __global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams
                 // outstanding: X of super-step ss + 2, at least two per row group
                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * RPW) : "memory");
             } else {
-                load_x(st, ss + 2);  // (behind the fragments: loads return in order)
+                load_x(st, ss + 2);
             }
         }
     };
     load_x(xs[0], 0);
     __builtin_amdgcn_sched_barrier(0);
     load_r(0);
+    if constexpr (NJB > 0 && ROLL) {
+#pragma unroll
+        for (int jb = 0; jb < RD; ++jb) read_pair(0, jb);
+    }
     __builtin_amdgcn_sched_barrier(0);
     load_x(xs[1], 1);
     if constexpr (STAGE) {
@@ -642,27 +655,43 @@ __global__ __launch_bounds__(ROWG * KW * 64, 2) void mxi_act_kernel(MxiActParams
     }
 }
 
-// Rows per workgroup: 64 (two groups of 32, R through LDS), 32 (two groups of 16, R through LDS) or 16 (eight wavefronts along
-// K, each reading its R from the L2).  More rows per workgroup mean fewer bytes of R, as long as the workgroups still cover
-// most of the 256 compute units; below that the short chain of the 16-row form wins, and with few columns of R its traffic
-// does not matter.  Measured (us, bf16 X, act / from codes; 64-, 32-, 16-row form):
-//   16384 x 4608, rank 128: 58.6 / 30.9, 73.7 / 44.7, 90.0 / 54.2      16384 x 4608, rank 64: 49.6 / 22.8, 53.7 / 27.7, 65.6 / 35.5
-//    8192 x 2240, rank  64: 25.2 / 11.9, 18.4 /  9.6, 19.8 / 11.2      16384 x 1152, rank 32: 17.4 /  8.1, 15.9 /  8.3, 18.4 / 10.4
-//    1024 x 4608, rank 128: 46.0 / 28.4, 30.5 / 20.9, 18.2 / 15.1       8192 x 1152, rank 32: 14.1 /  7.9, 10.5 /  7.8,  9.8 /  7.9
-static int mxi_act_rows(int r, int64_t Mp)
+// Rows per workgroup: 64 (two groups of 32, R through LDS), 32 (two groups of 16, R through LDS) or 16 (each wavefront reads its R
+// from the L2).  All sum T in the same order, so a token's bits depend on none of this.  The forms with R in LDS run one workgroup to
+// a compute unit: they pay where the rounds they take are nearly full and there is R enough (rank times K) for its traffic to
+// count; the step from codes, which reads half as much and codes nothing, is earlier at that point.
+// Measured (us, bf16 X, act / from codes; 64-, 32-, 16-row form):
+//   16384 x 4608, rank 128: 50.4 / 31.7, 61.5 / 45.4, 65.8 / 55.6      16384 x 4608, rank  64: 42.0 / 24.1, 40.0 / 28.5, 47.1 / 37.3
+//   16384 x 1152, rank 128: 20.4 / 12.8, 24.2 / 15.6, 21.5 / 16.3      16384 x 1152, rank  32: 15.8 /  7.5, 14.3 /  7.9, 13.3 /  8.6
+//   10240 x 4608, rank 128: 48.3 / 30.3, 58.6 / 43.0, 49.9 / 42.2       8192 x 4608, rank 128: 47.7 / 30.0, 32.1 / 23.8, 35.5 / 29.6
+//    8192 x 1152, rank 128: 18.9 / 12.1, 12.7 /  8.5, 12.1 /  9.4       8192 x 2240, rank  32: 21.5 /   - , 14.9 /   - , 12.2 /   -
+//    1024 x 4608, rank 128: 46.3 / 27.9, 29.9 / 19.1, 18.1 / 14.0        300 x 1152, rank  64: 14.6 /  8.1,  9.5 /  5.9,  6.5 /  4.6
+static int mxi_act_rows(int r, int64_t K, int64_t Mp, bool from_codes)
 {
-    if (r >= 64 && Mp >= 64 * 192) return 64;
-    if (Mp >= (r >= 64 ? 32 * 192 : 32 * 384) && r > 0) return 32;
-    return 16;
+    const int64_t cus = compute_units();
+    auto full = [&](int rows) {  // the share of its rounds that a form of one workgroup per compute unit fills
+        const int64_t wgs = (Mp + rows - 1) / rows;
+        return (double)wgs / (double)((wgs + cus - 1) / cus * cus);
+    };
+    const bool large = r * K >= 128 * 1152, one_round = Mp <= 32 * cus;  // (of the 32-row form)
+    if (r < 32) return 16;
+    if (from_codes) {
+        if (one_round) return r >= 64 && full(32) >= 0.6 ? 32 : 16;
+        if (full(64) >= (large && r >= 64 ? 0.55 : 0.7)) return 64;
+        return full(32) >= 0.75 ? 32 : 16;
+    }
+    if (!large) return 16;
+    if (r <= 64) return !one_round && full(32) >= 0.85 ? 32 : 16;
+    if (full(64) >= (r * K >= 96 * 4096 ? 0.7 : 0.8)) return 64;
+    return one_round && full(32) >= 0.6 && K >= 2240 ? 32 : 16;
 }
 
 template <bool BF16, int NJB, bool SM, bool FROMC, bool DBG>
 static hipError_t mxi_act_launch2(const MxiActParams& p, hipStream_t s)
 {
-    switch (mxi_act_rows(p.r, p.Mp)) {
-        case 64: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 2, 2, 4, DBG>), dim3((unsigned)((p.Mp + 63) / 64)), dim3(512), 0, s, p); break;
-        case 32: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 2, 4, DBG>), dim3((unsigned)(p.Mp / 32)), dim3(512), 0, s, p); break;
-        default: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 1, 8, DBG>), dim3((unsigned)(p.Mp / 16)), dim3(512), 0, s, p); break;
+    switch (mxi_act_rows(p.r, p.K, p.Mp, FROMC)) {
+        case 64: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 2, 2, DBG>), dim3((unsigned)((p.Mp + 63) / 64)), dim3(512), 0, s, p); break;
+        case 32: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 2, DBG>), dim3((unsigned)(p.Mp / 32)), dim3(512), 0, s, p); break;
+        default: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 1, DBG>), dim3((unsigned)(p.Mp / 16)), dim3(256), 0, s, p); break;
     }
     return hipGetLastError();
 }

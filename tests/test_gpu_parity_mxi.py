@@ -187,9 +187,12 @@ def test_full_size_sampled_rows(oracle, name):
     _compare(oracle, layer, X, W, L, R, rows=rows)
 
 
-# rows per workgroup of the activation step: 64 from 12288 rows at rank >= 64; 32 from 6144 rows (rank 32: 12288); last workgroup partly or wholly past M
+# rows per workgroup of the activation step: 16, and where there is R enough (rank times K) 32 and 64 in batches that fill most of the device;
+# last workgroup partly or wholly past M
 @pytest.mark.parametrize("M,K,r,bw,xd", [(6143, 320, 64, 8, "bf16"), (6113, 320, 64, 8, "bf16"), (12281, 448, 128, 4, "bf16"), (12289, 64, 96, 8, "f32"),
-                                         (12287, 576, 32, 8, "bf16"), (6150, 1152, 96, 8, "f32")])
+                                         (12287, 576, 32, 8, "bf16"), (6150, 1152, 96, 8, "f32"),
+                                         (13281, 1152, 128, 8, "bf16"), (13345, 1600, 96, 4, "f32"), (5130, 2304, 128, 8, "bf16"),
+                                         (5101, 2240, 96, 4, "f32"), (14337, 2304, 64, 8, "bf16"), (14001, 4608, 32, 8, "bf16")])
 def test_activation_row_forms(oracle, M, K, r, bw, xd):
     layer = wl.Layer("t", M, K, 64, r, "mxi", 32, bw, 8, xd, seed=M + r)
     X, W, L, R = wl.make_inputs(layer)
@@ -244,3 +247,41 @@ def test_rows_as_long_as_the_contract_allows():
     assert want[0].any()
     for got in layer(K):
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("fam,g,bw,ag,r", [("mxi", 32, 8, 32, 128), ("mxi", 32, 4, 32, 64), ("mxi", 32, 8, 32, 32), ("mx", 32, 8, 32, 64),
+                                           ("mxb", 32, 8, 32, 128), ("mxb", 32, 6, 32, 64), ("int", 64, 8, 0, 64), ("int", 64, 6, 64, 32)])
+def test_a_token_does_not_depend_on_its_batch(fam, g, bw, ag, r):
+    """A token's codes and outputs are the same bits in every batch, whatever form of the kernels the batch size takes.  Block scales spread
+    over 2^+-10, so that the fp32 sums of the intermediate round."""
+    from paper_2604_18117_amd import binding as lq
+    M, K, N = 13400, 2304, 576
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(r + bw)
+
+    def spread(rows, cols):
+        e = torch.randint(-10, 11, (rows, cols // 32, 1), generator=gen, device="cuda")
+        return torch.ldexp(torch.randn((rows, cols // 32, 32), generator=gen, device="cuda"), e).reshape(rows, cols)
+    cfg = lq.make_config(N, K, r, fam, g, bw, bw if fam == "mxb" else 8, a_group=ag)
+    packed = lq.lq_pack_weights(cfg, spread(N, K) * 0.02, torch.randn((N, r), generator=gen, device="cuda"), spread(r, K))
+    X = spread(M, K).to(torch.bfloat16)
+
+    def run(m):
+        act = lq.lq_quantize_act(cfg, packed, X[:m])
+        v = lq.lq_unpack_act(cfg, act, m)
+        Y = lq.lq_linear_lowrank_fwd(cfg, packed, act, m)
+        parts = [v.tq, v.st, v.te, Y.view(torch.int16)]
+        if fam == "mxi":  # the step from codes too: those that a producer with this output would leave
+            blocks = X[:m].float().view(m, K // 32, 32)
+            e = torch.frexp(blocks.abs().amax(2))[1].to(torch.int32) - 1
+            codes = torch.zeros(lq.lq_handoff_sizes(cfg, m), dtype=torch.uint8, device="cuda")
+            codes[:m * K] = torch.round(torch.ldexp(blocks, 6 - e[..., None])).clamp(-127, 127).to(torch.int8).view(torch.uint8).reshape(-1)
+            mp = (m + 31) // 32 * 32
+            codes[(mp * K + 255) // 256 * 256:][:m * (K // 32)] = (e + 127).to(torch.uint8).reshape(-1)
+            vc = lq.lq_unpack_act(cfg, lq.lq_branch_from_codes(cfg, packed, codes, m, torch.zeros_like(act)), m)
+            assert torch.equal(vc.tq, v.tq) and torch.equal(vc.te, v.te)
+        return parts
+    whole = run(M)
+    for m in (5, 300, 2000, 6200, 8300):
+        for name, a, b in zip(("tq", "st", "te", "Y"), run(m), whole):
+            assert torch.equal(a, b[:m]), (m, name)
