@@ -449,11 +449,15 @@ static hipError_t launch_len(const ActParams& p, int64_t Mp, hipStream_t s)
     // Eight wavefronts to a workgroup while there is at most one workgroup per compute unit: the time is then one
     // workgroup's chain (64 x 4608: 12.8 -> 10.8 us, SINT4 64 x 2240: 11.1 -> 9.1, 4096 x 4608: 18.7 -> 16.6); with more
     // workgroups four are as fast or faster (8192 x 4608: 27.3 against 29.6, 16384 x 1152: 15.7 against 17.3).
-    if (Mp <= 16 * 256) {
+    // Smoothed fp32 rows spill 80 to 95 registers in the nine-chunk form (two multiplicands per value until the row is formed), which
+    // costs more than a second pass over a row of six chunks per wavefront (4096 x 2624 rank 128: streamed 23.7 us, in
+    // registers 28.0; 2 x 2624 rank 16: 10.5, 13.6) and less than one over nine (1024 x 4608 rank 32: 27.3, 24.4).  The other types spill at
+    // rank 128 alone, at most 29 registers, and are within 3 % of the streamed form or faster.
+    if (Mp <= 16 * compute_units()) {
         const int mc = (p.C64 + 7) / 8;
         if (mc <= 3) return launch_rank<BF16, 3, SM, 8>(p, Mp, s);
         if (mc <= 5) return launch_rank<BF16, 5, SM, 8>(p, Mp, s);
-        if (mc <= 9) return launch_rank<BF16, 9, SM, 8>(p, Mp, s);
+        if (mc <= 9 && (BF16 || !SM || mc > 6)) return launch_rank<BF16, 9, SM, 8>(p, Mp, s);
         return launch_rank<BF16, 0, SM, 8>(p, Mp, s);
     }
     // MAXC = 0: the streamed kernel, for rows that do not fit in registers (fp32 representation: beyond 9 chunks per

@@ -401,12 +401,13 @@ def test_forward_forms_bit_exact(oracle, M, K, N, r, g, ag):
 
 
 # Activation step: eight wavefronts to a workgroup up to 4096 rows, four above; row lengths at the edges of the register forms (3, 5, 9 chunks
-# per wavefront of eight; 5, 9, 18 of four; fp32 rows 9) and on the streamed form; every rank, fp32 input, SINT4 blocks, smoothing.
+# per wavefront of eight, smoothed fp32 rows of 6 streamed; 5, 9, 18 of four; fp32 rows 9) and on the streamed form; every rank, fp32 input, SINT4 blocks, smoothing.
 @pytest.mark.parametrize("M,K,r,xd,ag,sm", [
     (50, 64, 16, "bf16", 0, False), (33, 1536, 16, "bf16", 0, False), (40, 1600, 96, "bf16", 64, False), (47, 2560, 128, "f32", 0, False),
     (31, 2624, 64, "bf16", 0, True), (18, 4608, 128, "bf16", 0, True), (17, 4672, 96, "f32", 64, True), (4090, 128, 32, "bf16", 64, True),
     (4097, 1280, 16, "bf16", 0, False), (4100, 1344, 96, "f32", 0, True), (4127, 2304, 128, "bf16", 64, True), (4129, 2368, 64, "f32", 0, False),
     (4110, 64, 0, "bf16", 0, False), (4111, 192, 96, "bf16", 0, True),
+    (33, 2624, 128, "f32", 0, True), (20, 3136, 16, "f32", 64, True), (1000, 3072, 96, "f32", 0, True), (35, 4608, 128, "f32", 0, False),
 ])
 def test_activation_forms_bit_exact(oracle, M, K, r, xd, ag, sm):
     layer = wl.Layer("t", M, K, 64, r, "int", 64, 8, 8, xd, outlier_scale=25.0, n_outliers=max(1, K // 100), seed=M + K, a_group=ag)
