@@ -654,7 +654,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd_int_kernel(FwdParams p)
 // of the chip idle, the time of a call is one tile's serial chain of steps; here a step is 1 to 4 products and 16 to 64 FMAs instead of
 // 8 and 128, nothing is shared between wavefronts (no LDS staging, no barriers), and both operand streams are requested
 // DEPTH steps ahead straight into the registers the products read.  Bounded by that chain for a few tiles (64 x 1152 -> 3456:
-// 9.2 -> 3.7 us, 64 x 4608 -> 1152: 22.5 -> 5.9 us) and by the operands' L2 traffic, 13-16 TB/s, for many.  Same sums in the same
+// 9.5 -> 4.0 us, 64 x 4608 -> 1152: 22.5 -> 5.9 us) and by the operands' L2 traffic, 13-16 TB/s, for many.  Same sums in the same
 // order as fwd_tile.
 template <int GC, int NK, int NRB, int NCB, bool DBG, bool GA>
 __global__ __launch_bounds__(64, 2) void fwd_int_small_kernel(FwdParams p)
@@ -670,9 +670,12 @@ __global__ __launch_bounds__(64, 2) void fwd_int_small_kernel(FwdParams p)
     __shared__ __attribute__((aligned(16))) uint8_t stage[32 * ROW];
 
     const int lane = threadIdx.x, half = lane >> 5, l32 = lane & 31;
-    // row blocks fastest: the tiles that read one column block's weights run together on one XCD
+    // The tiles that share a block of the longer operand run together on one XCD: it is then read from memory once, the shorter one
+    // stays in the L2.  (Row blocks always fastest, 9083 x 4608 -> 576: 46.1 us, now 32.9.)
     const int tile = xcd_order(blockIdx.x, p.tilesM * p.tilesN);
-    const int tile_n = tile / p.tilesM, rb0 = (tile - tile_n * p.tilesM) * NRB;
+    const bool mfast = p.tilesM <= p.tilesN;
+    const int slow = tile / (mfast ? p.tilesM : p.tilesN), fast = tile - slow * (mfast ? p.tilesM : p.tilesN);
+    const int tile_n = mfast ? slow : fast, rb0 = (mfast ? fast : slow) * NRB;
     const int G = p.G, C64 = p.C64;
     const uint32_t lane16 = (uint32_t)lane * 16u, lane8 = 1024u + (uint32_t)lane * 8u;
 
@@ -850,13 +853,20 @@ static hipError_t launch_cfg(const FwdParams& p0, hipStream_t s)
     // wavefront while that leaves no SIMD with two, larger ones as the L2 traffic of the operands (3, 2.25 and 1.5 KB per tile
     // and 64-chunk) begins to count, the 128 x 256 tiles once they occupy enough of the chip.  The SINT4-block kernel of
     // those is the slower one, so the line lies higher.  us, 1 x 1 / 2 x 1 / 2 x 2 / 128 x 256:
-    //   64-deep   T =  108 (   64 x 1152 -> 3456):  3.7 /  4.7 /  6.6 /  9.2      SINT4   T =  140 (  64 x 2240 -> 2240):  6.0 /  9.4 / 14.3 / 20.5
-    //             T =  840 ( 128 x 2240 -> 6720):   8.7 /  7.6 / 12.4 / 15.2              T = 1120 ( 512 x 2240 -> 2240): 13.5 / 13.1 / 15.7 / 22.4
-    //             T = 1728 ( 512 x 1152 -> 3456):   8.8 /  8.0 /  8.0 / 10.2              T = 6720 (3072 x 2240 -> 2240):    - /    - / 31.3 / 36.6
-    //             T = 4620 ( 700 x 2240 -> 6720):     - /    - / 19.7 / 22.9              T = 8960 (4096 x 2240 -> 2240):    - /    - / 43.8 / 41.2
-    //             T = 6720 (3072 x 2240 -> 2240):     - /    - / 25.4 / 23.2      128-deep T = 36 (  2 x 4608 -> 1152):   5.9 /  8.0 / 13.2 / 22.4
+    //   64-deep   T =  216 (  64 x 1152 -> 3456):  4.0 /  5.0 /  6.8 /  9.5      SINT4     T =  140 (  64 x 2240 -> 2240):  6.1 /  9.3 / 14.4 / 20.4
+    //             T =  840 ( 128 x 2240 -> 6720):  8.4 /  7.7 / 10.3 / 15.2                T = 1120 ( 512 x 2240 -> 2240): 12.8 / 12.4 / 15.9 / 20.8
+    //             T = 1728 ( 512 x 1152 -> 3456):  8.5 /  7.7 /  7.7 / 10.1                T = 6720 (3072 x 2240 -> 2240): 55.4 / 53.6 / 31.2 / 37.7
+    //             T = 4608 (4096 x 4608 -> 1152): 54.4 / 48.9 / 32.6 / 38.7                T = 8960 (4096 x 2240 -> 2240): 70.5 / 68.6 / 42.8 / 41.4
+    //             T = 4620 ( 700 x 2240 -> 6720): 32.8 / 29.3 / 20.0 / 22.9      128-deep  T =   36 (   2 x 4608 -> 1152):  6.0 /  8.1 / 12.7 / 22.5
+    //             T = 5652 (5000 x 1152 -> 1152): 21.5 / 17.4 / 13.5 / 14.9                T =  576 ( 512 x 4608 -> 1152): 10.3 / 10.3 / 13.1 / 24.9
+    //             T = 6720 (3072 x 2240 -> 2240): 44.9 / 37.9 / 24.1 / 23.4                T = 5112 (4539 x 4608 -> 1152): 57.0 / 49.8 / 32.2 / 36.1
+    //             T = 6768 (6000 x 1152 -> 1152): 24.9 / 21.1 / 15.4 / 15.1                T = 6912 (2048 x 1152 -> 3456): 26.0 / 23.2 / 15.7 / 14.9
     const int64_t T = (int64_t)p.nrb * (p.N / 32);
-    if (T <= (GA ? 7168 : 5120)) {
+    // Rows of three and four chunks: the 128 x 256 tiles also where one to every second compute unit takes all of them (T = 3312, 2939 x
+    // 256 -> 1152, 128-deep: 6.3 against 5.9; at two chunks, 5.1 against 5.5, they do not serve).
+    const int t128 = ((p.nrb + 3) / 4) * ((p.N + WN * 64 - 1) / (WN * 64));
+    const int line = GA ? 7168 : p.C64 > 2 && p.C64 <= 4 && 2 * t128 <= compute_units() ? 3072 : 5120;
+    if (T <= line) {
         const int rbt = T <= 800 ? 1 : 2, cbt = T <= 1700 ? 1 : 2;
         p.tilesN = p.N / 32 / cbt;
         p.tilesM = (p.nrb + rbt - 1) / rbt;

@@ -1356,10 +1356,13 @@ __global__ __launch_bounds__(64, 2) void mx_fwd_small_kernel(MxFwdParams p)
     __shared__ __attribute__((aligned(16))) uint8_t stage[32 * ROW];
 
     const int lane = threadIdx.x, half = lane >> 5, l32 = lane & 31;
-    // row blocks fastest: the tiles that read one column block's weights run together on one XCD
+    // The tiles that share a block of the longer operand run together on one XCD: it is then read from memory once, the shorter one
+    // stays in the L2.  (Row blocks always fastest, 31515 x 4608 -> 64: 25.2 us, now 15.4.)
     const int tiles = p.tilesM * p.tilesN, per = tiles >> 3, rem = tiles & 7, xcd = blockIdx.x & 7;
     const int tile = xcd * per + (xcd < rem ? xcd : rem) + ((int)blockIdx.x >> 3);
-    const int tile_n = tile / p.tilesM, rb0 = (tile - tile_n * p.tilesM) * NRB, cb0 = tile_n * NCB;
+    const bool mfast = p.tilesM <= p.tilesN;
+    const int slow = tile / (mfast ? p.tilesM : p.tilesN), fast = tile - slow * (mfast ? p.tilesM : p.tilesN);
+    const int rb0 = (mfast ? fast : slow) * NRB, cb0 = (mfast ? slow : fast) * NCB;
     const int C64 = p.C64, CQ = p.CQ;
     const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
 
@@ -1537,12 +1540,14 @@ static void mx_fwd_launch(const MxFwdParams& p, hipStream_t s)
     // Small layers, by the number T of 32 x 32 tiles (the device holds 2048 wavefronts of these kernels): one tile to a
     // wavefront while that leaves no SIMD with two, larger ones as the L2 traffic of the operands (2, 1.5 and 1 KB per tile and
     // 64-chunk) begins to count, the 128 x 256 tiles once they occupy enough of the chip.  us, 1 x 1 / 2 x 1 / 2 x 2 / 128 x 256:
-    //   T =  108 (   2 x 1152 -> 3456): 2.7 / 3.3 / 4.3 /  7.5        T = 1728 ( 512 x 1152 -> 3456):  6.6 /  5.7 /  5.8 /  8.0
-    //   T =  720 ( 300 x 1152 -> 2304): 3.7 / 3.7 / 4.1 /  7.2        T = 2304 (2048 x 4608 -> 1152): 18.2 / 15.0 / 15.2 / 17.2
-    //   T = 1080 ( 300 x 1152 -> 3456): 5.2 / 4.7 / 5.3 /  7.9        T = 3500 ( 300 x 2240 -> 11200): 17.4 / 12.6 / 11.2 / 12.7
-    //   T =  576 ( 512 x 4608 -> 1152): 6.1 / 8.8 / 11.0 / 16.5       T = 4608 (4096 x 4608 -> 1152): 53.1 / 31.8 / 22.1 / 18.7
+    //   T =  108 (   2 x 1152 -> 3456): 3.0 / 3.5 / 4.5 /  7.6        T = 1728 ( 512 x 1152 -> 3456):  6.4 /  5.5 /  5.8 /  8.3
+    //   T =  720 ( 300 x 1152 -> 2304): 4.1 / 4.3 / 4.8 /  7.9        T = 2304 (2048 x 4608 -> 1152): 16.9 / 15.8 / 14.7 / 18.5
+    //   T = 1080 ( 300 x 1152 -> 3456): 5.4 / 4.9 / 5.5 /  8.1        T = 3500 ( 300 x 2240 -> 11200): 16.4 / 12.1 / 10.7 / 12.5
+    //   T =  576 ( 512 x 4608 -> 1152): 6.1 / 7.9 / 9.5 / 17.4        T = 4608 (4096 x 4608 -> 1152): 30.8 / 25.4 / 21.3 / 19.7
     const int64_t T = (int64_t)p.nrb * (p.N / 32);
-    if (T <= 3584) {
+    // More than 80 MB of X codes (a narrow layer): a stream over memory, which the large tiles' requests serve as well or better (37243 x
+    // 4608 -> 64: 18.7 us against 17.9).
+    if (T <= 3584 && (int64_t)p.nrb * p.C64 <= 80000) {
         const int rbt = T <= 800 ? 1 : 2, cbt = T <= 2000 ? 1 : 2;
         if (p.dbg_y32) mx_fwd_small_launch<NK, true, BLK, BFMT>(p, rbt, cbt, s);
         else mx_fwd_small_launch<NK, false, BLK, BFMT>(p, rbt, cbt, s);

@@ -285,3 +285,22 @@ def test_a_token_does_not_depend_on_its_batch(fam, g, bw, ag, r):
     for m in (5, 300, 2000, 6200, 8300):
         for name, a, b in zip(("tq", "st", "te", "Y"), run(m), whole):
             assert torch.equal(a, b[:m]), (m, name)
+
+
+# Layers narrow and wide, long and short: each order of the small forms' tiles, and the large tiles beside them (by the number of tiles, at
+# three and four chunks, above 80 MB of X codes)
+@pytest.mark.parametrize("fam,g,bw,ag,K,N,ms", [("mx", 32, 8, 32, 4608, 64, (33, 700, 20011, 36001)), ("mxb", 32, 6, 32, 576, 192, (40, 9001, 19000)),
+                                                ("mxi", 32, 8, 32, 1152, 192, (65, 5000, 37333, 38000)), ("int", 128, 4, 0, 256, 1152, (70, 900, 2939, 4000, 4700)),
+                                                ("int", 64, 8, 0, 512, 128, (97, 6500, 40000, 41000)), ("int", 64, 6, 64, 192, 4480, (33, 420, 1601, 1700))])
+def test_outputs_do_not_depend_on_the_tiles(fam, g, bw, ag, K, N, ms):
+    from paper_2604_18117_amd import binding as lq
+    r = 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K + N)
+    cfg = lq.make_config(N, K, r, fam, g, bw, bw if fam == "mxb" else 8, a_group=ag)
+    W, L, R = (torch.randn(s, generator=gen, device="cuda") * f for s, f in (((N, K), 0.02), ((N, r), 0.1), ((r, K), 0.1)))
+    packed = lq.lq_pack_weights(cfg, W, L, R)
+    X = (torch.randn((ms[-1], K), generator=gen, device="cuda") * torch.exp2(torch.randint(-8, 9, (1, K), generator=gen, device="cuda"))).to(torch.bfloat16)
+    Y = [lq.lq_linear_lowrank_fwd(cfg, packed, lq.lq_quantize_act(cfg, packed, X[:m]), m).view(torch.int16) for m in ms]
+    for m, y in zip(ms, Y):
+        assert torch.equal(y, Y[-1][:m]), m
