@@ -478,37 +478,24 @@ hipError_t launch_calib_init(const Dims& d, const float* L, const float* R, uint
     return calib_copy_run(c, s);
 }
 
-// Kernels whose LDS exceeds the 64 KB a launch may use without asking: asked once per device and kernel, so that later
-// calls (which a caller may capture in a graph) only launch.
 template <auto KERNEL>
-static void calib_launch_err(const CalibParams& p, int waves, int lds, hipStream_t s)
+static hipError_t calib_launch_err(const CalibParams& p, int waves, int lds, hipStream_t s)
 {
-    if (lds > 65536) {
-        static bool asked[64] = {false};
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-        if (!asked[dev]) {
-            (void)hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            asked[dev] = true;
-        }
-    }
+    const hipError_t e = allow_lds<KERNEL>(lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(KERNEL, dim3((unsigned)(p.c.cblocks * p.c.splits)), dim3(64 * waves), lds, s, p);
+    return hipGetLastError();
 }
 
 template <int R>
-static void calib_err(const Dims& d, const CalibParams& p, hipStream_t s)
+static hipError_t calib_err(const Dims& d, const CalibParams& p, hipStream_t s)
 {
     constexpr int lds = calib_lds<R>(), waves = calib_waves(R);
-    if (d.mxi)
-        calib_launch_err<calib_err_kernel<R, 3, 2>>(p, waves, lds, s);
-    else if (d.mx)
-        calib_launch_err<calib_err_kernel<R, 2, 2>>(p, waves, lds, s);
-    else if (d.ga)
-        calib_launch_err<calib_err_kernel<R, 1, 4>>(p, waves, lds, s);
-    else if (d.g == 64)
-        calib_launch_err<calib_err_kernel<R, 0, 4>>(p, waves, lds, s);
-    else
-        calib_launch_err<calib_err_kernel<R, 0, 8>>(p, waves, lds, s);
+    if (d.mxi) return calib_launch_err<calib_err_kernel<R, 3, 2>>(p, waves, lds, s);
+    if (d.mx) return calib_launch_err<calib_err_kernel<R, 2, 2>>(p, waves, lds, s);
+    if (d.ga) return calib_launch_err<calib_err_kernel<R, 1, 4>>(p, waves, lds, s);
+    if (d.g == 64) return calib_launch_err<calib_err_kernel<R, 0, 4>>(p, waves, lds, s);
+    return calib_launch_err<calib_err_kernel<R, 0, 8>>(p, waves, lds, s);
 }
 
 hipError_t launch_calib_step(const Dims& d, const float* W, uint8_t* state, int step, const lq_adam* ad, float* loss,
@@ -526,13 +513,15 @@ hipError_t launch_calib_step(const Dims& d, const float* W, uint8_t* state, int 
     p.N = (int)d.N;
     p.K = (int)d.K;
     p.c = calib_split(d);
+    hipError_t e;
     switch (d.r) {
-        case 16: calib_err<16>(d, p, s); break;
-        case 32: calib_err<32>(d, p, s); break;
-        case 64: calib_err<64>(d, p, s); break;
-        case 96: calib_err<96>(d, p, s); break;
-        default: calib_err<128>(d, p, s); break;
+        case 16: e = calib_err<16>(d, p, s); break;
+        case 32: e = calib_err<32>(d, p, s); break;
+        case 64: e = calib_err<64>(d, p, s); break;
+        case 96: e = calib_err<96>(d, p, s); break;
+        default: e = calib_err<128>(d, p, s); break;
     }
+    if (e != hipSuccess) return e;  // (the parts in the state are an earlier step's: no update from them)
     AdamParams a;
     a.lr = ad->lr;
     a.b1 = ad->beta1;

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "lq.h"
 
 namespace lq {
@@ -232,6 +234,23 @@ static inline int panel_width(int tilesN, int C64, int chunk_row_bytes = 32)
 {
     const int pw = (int)(((int64_t)2 << 20) / ((int64_t)256 * C64 * chunk_row_bytes));
     return pw < 1 ? 1 : pw > tilesN ? tilesN : pw;
+}
+
+// Kernels whose LDS exceeds the 64 KB a launch may use without asking: asked until it is granted, once per device and kernel, so
+// that later calls (which a caller may capture in a graph) only launch.
+template <auto KERNEL>
+hipError_t allow_lds(int bytes)
+{
+    if (bytes <= 65536) return hipSuccess;
+    static std::atomic<bool> granted[64];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const bool known = dev >= 0 && dev < 64;  // (a device past the table asks every time)
+    if (known && granted[dev].load(std::memory_order_relaxed)) return hipSuccess;
+    e = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess && known) granted[dev].store(true, std::memory_order_relaxed);
+    return e;
 }
 
 // ---- device helpers ----------------------------------------------------------------------

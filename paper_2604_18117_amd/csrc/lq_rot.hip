@@ -620,57 +620,48 @@ static RotQ rot_q2(const Dims& d)
     return q;
 }
 
-// Kernels whose LDS exceeds the 64 KB a launch may use without asking: asked once per device and kernel, so that later
-// calls (which a caller may capture in a graph) only launch.
-template <auto KERNEL>
-static void rot_ask_lds(int bytes)
-{
-    static bool asked[64] = {false};
-    if (bytes <= 65536) return;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-    if (asked[dev]) return;
-    (void)hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    asked[dev] = true;
-}
-
 template <int R, int MODE, int QK, int NWV>
-static void rot_launch_z(const RotZParams& p, int grid, hipStream_t s)
+static hipError_t rot_launch_z(const RotZParams& p, int grid, hipStream_t s)
 {
     constexpr int lds = rot_z_lds<R, NWV>();
-    rot_ask_lds<rot_z_kernel<R, MODE, QK, NWV>>(lds);
+    const hipError_t e = allow_lds<rot_z_kernel<R, MODE, QK, NWV>>(lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((rot_z_kernel<R, MODE, QK, NWV>), dim3(grid), dim3(64 * NWV), lds, s, p);
+    return hipGetLastError();
 }
 
 template <int R>
-static void rot_launch_errors(const RotZParams& p, hipStream_t s)
+static hipError_t rot_launch_errors(const RotZParams& p, hipStream_t s)
 {
     constexpr int NWV = R <= 64 ? 8 : 4;  // (rot_split's group)
-    if (p.q.kind <= 1) rot_launch_z<R, ROT_MAX, 0, 4>(p, p.w.wM, s);
-    if (p.q.kind == 0)
-        rot_launch_z<R, ROT_ERR, 0, NWV>(p, p.w.wL + p.w.wR, s);
-    else if (p.q.kind == 1)
-        rot_launch_z<R, ROT_ERR, 1, NWV>(p, p.w.wL + p.w.wR, s);
-    else if constexpr (R >= 32)
-        rot_launch_z<R, ROT_ERR, 2, NWV>(p, p.w.wL + p.w.wR, s);
+    if (p.q.kind <= 1) {
+        const hipError_t e = rot_launch_z<R, ROT_MAX, 0, 4>(p, p.w.wM, s);
+        if (e != hipSuccess) return e;
+    }
+    if (p.q.kind == 0) return rot_launch_z<R, ROT_ERR, 0, NWV>(p, p.w.wL + p.w.wR, s);
+    if (p.q.kind == 1) return rot_launch_z<R, ROT_ERR, 1, NWV>(p, p.w.wL + p.w.wR, s);
+    if constexpr (R >= 32) return rot_launch_z<R, ROT_ERR, 2, NWV>(p, p.w.wL + p.w.wR, s);
+    return hipErrorInvalidValue;  // (block kinds have rank >= 32)
 }
 
 template <int R>
-static void rot_launch_cayley(const RotStepParams& p, hipStream_t s)
+static hipError_t rot_launch_cayley(const RotStepParams& p, hipStream_t s)
 {
-    rot_ask_lds<rot_cayley_kernel<R>>(rot_cayley_lds<R>());
+    const hipError_t e = allow_lds<rot_cayley_kernel<R>>(rot_cayley_lds<R>());
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((rot_cayley_kernel<R>), dim3(1), dim3(rot_cayley_threads<R>()), rot_cayley_lds<R>(), s, p);
+    return hipGetLastError();
 }
 
 template <typename F>
-static void rot_dispatch(int r, F f)
+static hipError_t rot_dispatch(int r, F f)
 {
     switch (r) {
-        case 16: f(std::integral_constant<int, 16>{}); break;
-        case 32: f(std::integral_constant<int, 32>{}); break;
-        case 64: f(std::integral_constant<int, 64>{}); break;
-        case 96: f(std::integral_constant<int, 96>{}); break;
-        default: f(std::integral_constant<int, 128>{}); break;
+        case 16: return f(std::integral_constant<int, 16>{});
+        case 32: return f(std::integral_constant<int, 32>{});
+        case 64: return f(std::integral_constant<int, 64>{});
+        case 96: return f(std::integral_constant<int, 96>{});
+        default: return f(std::integral_constant<int, 128>{});
     }
 }
 
@@ -771,13 +762,14 @@ static hipError_t rot_step_launches(const Dims& d, const float* L, const float* 
     p.q = cs->q;
     p.grad_scale = cs->grad_scale;
     p.s = cs->s;
-    rot_dispatch(d.r, [&](auto rank) {
+    return rot_dispatch(d.r, [&](auto rank) {  // (stops at the first launch that fails: no update from an earlier step's parts)
         constexpr int R = decltype(rank)::value;
-        rot_launch_errors<R>(z, s);
+        hipError_t e = rot_launch_errors<R>(z, s);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(rot_sum_kernel, dim3(R * R / 64 + 1), dim3(ROT_TPB), 0, s, p);
-        rot_launch_cayley<R>(p, s);
+        e = hipGetLastError();
+        return e != hipSuccess ? e : rot_launch_cayley<R>(p, s);
     });
-    return hipGetLastError();
 }
 
 hipError_t launch_rot_apply(const Dims& d, const float* L, const float* Rm, const uint8_t* state, float* Lr, float* Rr,
@@ -785,13 +777,12 @@ hipError_t launch_rot_apply(const Dims& d, const float* L, const float* Rm, cons
 {
     const RotZParams p = rot_z_params(d, L, Rm, (const float*)(state + rot_layout(d).off_X), Lr, Rr);
     // (the rotated factors do not depend on Q2 and leave no parts: every group of 64 has a workgroup of its own)
-    rot_dispatch(d.r, [&](auto rank) {
+    return rot_dispatch(d.r, [&](auto rank) {
         RotZParams z = p;
         z.w.gL = z.w.wL = (int)(d.N / 64);
         z.w.gR = (int)(d.K / 64);
-        rot_launch_z<decltype(rank)::value, ROT_OUT, 0, 4>(z, z.w.gL + z.w.gR, s);
+        return rot_launch_z<decltype(rank)::value, ROT_OUT, 0, 4>(z, z.w.gL + z.w.gR, s);
     });
-    return hipGetLastError();
 }
 
 hipError_t launch_rot_unpack(const Dims& d, const uint8_t* state, const lq_rot_view* out, hipStream_t s)
