@@ -226,8 +226,6 @@ hipError_t launch_pack_mx(const Dims& d, int from_q, const float* W, const float
     uint8_t *pc = packed + pl.off_pq, *pe = packed + pl.off_sw;
     PackFill fill;
     fill.n = 0;
-    fill.blob = (uint32_t*)packed;
-    fill.tag = make_tag(d, LQ_BLOB_PACKED, 0);
     if (d.C64 % 4) fill.add(pe, (size_t)(N / 32) * ((d.C64 + 3) / 4) * 256, 0x7F7F7F7Fu);  // padding chunks of the last quad: 2^0
     if (d.smooth) fill.add(packed + pl.off_rg, (size_t)K * 4, 0x3F800000u);                 // reciprocals start at 1
     if (d.mxb) {  // padding of the rank to 64: zero codes, scale 2^0
@@ -246,18 +244,15 @@ hipError_t launch_pack_mx(const Dims& d, int from_q, const float* W, const float
         hipLaunchKernelGGL(mxb_pack_rows_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, L, R, N, K, Ks, d.r, d.rp, l8, (uint8_t*)sl,
                            r8, (uint8_t*)sr);
     }
+    e = hipGetLastError();
     auto residual = [&](auto kind) {
-        pack_residual<1>(PackMxResidual<decltype(kind)::value>{L, R, l8, sl, r8, sr, pc, pe, Ks, d.C64, d.r, d.rp}, W, N, Ks, d.r, d.C64, s);
+        return pack_residual<1>(e, PackMxResidual<decltype(kind)::value>{L, R, l8, sl, r8, sr, pc, pe, Ks, d.C64, d.r, d.rp}, W, N, Ks, d.r, d.C64, packed,
+                                make_tag(d, LQ_BLOB_PACKED, 0), s);
     };
-    if (!from_q || d.r == 0)
-        residual(std::integral_constant<int, 0>{});
-    else if (!d.mxb)
-        residual(std::integral_constant<int, 1>{});
-    else if (d.mxb_elem == 8)
-        residual(std::integral_constant<int, 2>{});
-    else
-        residual(std::integral_constant<int, 3>{});
-    return hipGetLastError();
+    if (!from_q || d.r == 0) return residual(std::integral_constant<int, 0>{});
+    if (!d.mxb) return residual(std::integral_constant<int, 1>{});
+    if (d.mxb_elem == 8) return residual(std::integral_constant<int, 2>{});
+    return residual(std::integral_constant<int, 3>{});
 }
 
 // ---------------------------------------------------------------------------------------------

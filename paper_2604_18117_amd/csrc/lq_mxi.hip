@@ -156,8 +156,6 @@ hipError_t launch_pack_mxi(const Dims& d, int from_q, const float* W, const floa
     const int N = (int)d.N, K = (int)d.K;
     PackFill fill;
     fill.n = 0;
-    fill.blob = (uint32_t*)packed;
-    fill.tag = make_tag(d, LQ_BLOB_PACKED, 0);
     if (d.C64 % 4) fill.add(pp.pe, (size_t)(N / 32) * ((d.C64 + 3) / 4) * 256, 0x7F7F7F7Fu);        // padding chunks of the last quad: 2^0
     if (d.smooth) fill.add(packed + packed_layout(d).off_rg, (size_t)K * 4, 0x3F800000u);            // reciprocals start at 1
     const hipError_t e = launch_pack_fill(fill, s);
@@ -167,8 +165,8 @@ hipError_t launch_pack_mxi(const Dims& d, int from_q, const float* W, const floa
         hipLaunchKernelGGL(mxi_pack_rows_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, L, R, N, K, d.bw_bits, d.r, d.rp, pp.lv,
                            pp.le, pp.rv, pp.re);
     }
-    pack_residual<1>(PackMxiResidual{L, R, pp.lv, pp.rv, pp.pq, pp.pe, K, d.r, d.rp, from_q}, W, N, K, d.r, d.C64, s);
-    return hipGetLastError();
+    return pack_residual<1>(hipGetLastError(), PackMxiResidual{L, R, pp.lv, pp.rv, pp.pq, pp.pe, K, d.r, d.rp, from_q}, W, N, K, d.r, d.C64, packed,
+                            make_tag(d, LQ_BLOB_PACKED, 0), s);
 }
 
 // ---------------------------------------------------------------------------------------------

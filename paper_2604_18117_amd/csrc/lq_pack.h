@@ -6,16 +6,14 @@
 
 namespace lq {
 
-// Sections a pack call presets to a constant (padding codes and scales, smoothing reciprocals of 1), all in one launch
-// together with the blob header.  Lengths in dwords.
+// Sections a pack call presets to a constant (padding codes and scales, smoothing reciprocals of 1), all in one launch.
+// Lengths in dwords.
 struct PackFill {
     static constexpr int MAX = 4;
     uint32_t* p[MAX];
     uint32_t v[MAX];
     size_t end[MAX];  // running sums of the lengths
     int n;
-    uint32_t* blob;
-    BlobTag tag;
     void add(void* dst, size_t bytes, uint32_t value)
     {
         if (bytes == 0) return;
@@ -40,8 +38,9 @@ hipError_t launch_pack_fill(const PackFill& f, hipStream_t s);
 // 0.85-1.0 ms for 11200 x 2240 and 6720 x 2240 at rank 64.)
 //
 // F: lhat(n, j) and rhat(j, k) dequantised factors (k inside the source row), encode(n, group, P, q) for the lane's values.
+// The last launch of a pack call: it writes the blob's header too.
 template <int R, int GC, typename F>
-__global__ __launch_bounds__(256) void pack_residual_kernel(F f, const float* W, int Ks, int groups, int per)
+__global__ __launch_bounds__(256) void pack_residual_kernel(F f, const float* W, int Ks, int groups, int per, uint32_t* blob, BlobTag tag)
 {
     typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));  // (W is aligned to its elements only)
     typedef double v4d __attribute__((ext_vector_type(4)));
@@ -96,27 +95,32 @@ __global__ __launch_bounds__(256) void pack_residual_kernel(F f, const float* W,
         }
         f.encode(n, g, P, q);
     }
+    write_tag(blob, tag);  // (ahead of the loop it takes the MXFP8 form at rank 128 from 188 registers to 256, 70 us to 104)
 }
 template <int R, int GC, typename F>
-static void pack_residual_launch(const F& f, const float* W, int N, int Ks, int groups, hipStream_t s)
+static void pack_residual_launch(const F& f, const float* W, int N, int Ks, int groups, uint8_t* blob, const BlobTag& tag, hipStream_t s)
 {
     // runs as long as 2048 workgroups (8 per CU) allow: a run reads its rows' factors once
     const int rb = N / 64, want = 2048 / rb > 1 ? 2048 / rb : 1;
     const int per = (groups + want - 1) / want;
     hipLaunchKernelGGL((pack_residual_kernel<R, GC, F>), dim3((unsigned)(rb * ((groups + per - 1) / per))), dim3(256), 0, s, f, W, Ks,
-                       groups, per);
+                       groups, per, (uint32_t*)blob, tag);
 }
+// (not launched, and the header not written, if the launches before it failed: `before`)
 template <int GC, typename F>
-static void pack_residual(const F& f, const float* W, int N, int Ks, int r, int groups, hipStream_t s)
+static hipError_t pack_residual(hipError_t before, const F& f, const float* W, int N, int Ks, int r, int groups, uint8_t* blob,
+                                const BlobTag& tag, hipStream_t s)
 {
+    if (before != hipSuccess) return before;
     switch (r) {
-        case 0: pack_residual_launch<0, GC>(f, W, N, Ks, groups, s); break;
-        case 16: pack_residual_launch<16, GC>(f, W, N, Ks, groups, s); break;
-        case 32: pack_residual_launch<32, GC>(f, W, N, Ks, groups, s); break;
-        case 64: pack_residual_launch<64, GC>(f, W, N, Ks, groups, s); break;
-        case 96: pack_residual_launch<96, GC>(f, W, N, Ks, groups, s); break;
-        default: pack_residual_launch<128, GC>(f, W, N, Ks, groups, s); break;
+        case 0: pack_residual_launch<0, GC>(f, W, N, Ks, groups, blob, tag, s); break;
+        case 16: pack_residual_launch<16, GC>(f, W, N, Ks, groups, blob, tag, s); break;
+        case 32: pack_residual_launch<32, GC>(f, W, N, Ks, groups, blob, tag, s); break;
+        case 64: pack_residual_launch<64, GC>(f, W, N, Ks, groups, blob, tag, s); break;
+        case 96: pack_residual_launch<96, GC>(f, W, N, Ks, groups, blob, tag, s); break;
+        default: pack_residual_launch<128, GC>(f, W, N, Ks, groups, blob, tag, s); break;
     }
+    return hipGetLastError();
 }
 
 // Maximum magnitude over the lane's values and those of the lanes that hold the rest of its row's block (q ^ 1) or chunk

@@ -103,7 +103,6 @@ struct PackIntResidual {
 
 __global__ __launch_bounds__(256) void pack_fill_kernel(PackFill f)
 {
-    write_tag(f.blob, f.tag);
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     size_t begin = 0;
     for (int k = 0; k < f.n; ++k) {
@@ -116,7 +115,8 @@ __global__ __launch_bounds__(256) void pack_fill_kernel(PackFill f)
 }
 hipError_t launch_pack_fill(const PackFill& f, hipStream_t s)
 {
-    const size_t n = f.n ? f.end[f.n - 1] : 1;
+    if (f.n == 0) return hipSuccess;
+    const size_t n = f.end[f.n - 1];
     hipLaunchKernelGGL(pack_fill_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, f);
     return hipGetLastError();
 }
@@ -149,17 +149,15 @@ hipError_t launch_pack_int(const Dims& d, int from_q, const float* W, const floa
     const int N = (int)d.N, K = (int)d.K;
     PackFill fill;
     fill.n = 0;
-    fill.blob = (uint32_t*)packed;
-    fill.tag = make_tag(d, LQ_BLOB_PACKED, 0);
     if (d.smooth) fill.add(packed + pl.off_rg, (size_t)K * 4, 0x3F800000u);  // reciprocals of the smoothing vector start at 1
-    const hipError_t e = launch_pack_fill(fill, s);
+    hipError_t e = launch_pack_fill(fill, s);
     if (e != hipSuccess) return e;
     pack_row_factors(PackIntRows{(float)d.qmax_bw}, L, R, N, K, K, d.r, d.rp, (uint8_t*)lq, sl, (uint8_t*)rq, sr, s);
+    e = hipGetLastError();
+    const BlobTag tag = make_tag(d, LQ_BLOB_PACKED, 0);
     if (d.g == 64)
-        pack_residual<1>(PackIntResidual<1>{L, R, lq, sl, rq, sr, pq, swT, N, K, d.r, d.rp, from_q, d.ga ? 1 : 0}, W, N, K, d.r, d.G, s);
-    else
-        pack_residual<2>(PackIntResidual<2>{L, R, lq, sl, rq, sr, pq, swT, N, K, d.r, d.rp, from_q, 0}, W, N, K, d.r, d.G, s);
-    return hipGetLastError();
+        return pack_residual<1>(e, PackIntResidual<1>{L, R, lq, sl, rq, sr, pq, swT, N, K, d.r, d.rp, from_q, d.ga ? 1 : 0}, W, N, K, d.r, d.G, packed, tag, s);
+    return pack_residual<2>(e, PackIntResidual<2>{L, R, lq, sl, rq, sr, pq, swT, N, K, d.r, d.rp, from_q, 0}, W, N, K, d.r, d.G, packed, tag, s);
 }
 
 // ---- plain views ----------------------------------------------------------------------------

@@ -62,15 +62,16 @@ CFG = {"int": (512, 256, 64, "int", 64, 8, 8), "int128": (512, 256, 128, "int", 
        "mxb": (512, 256, 96, "mxb", 32, 8, 8), "mxb6": (512, 256, 64, "mxb", 32, 6, 6), "mxi": (512, 256, 128, "mxi", 32, 8, 8)}
 
 
-@pytest.mark.parametrize("call", ["calib_step", "rot_step"])
+@pytest.mark.parametrize("call", ["calib_step", "rot_step", "pack"])
 @pytest.mark.parametrize("cfg", list(CFG))
 def test_nothing_is_launched_after_a_failed_launch(run, call, cfg):
-    """An Adam or Cayley update from parts that were never written, or codes from factors that were never quantised, would spoil the
-    caller's state behind an error status."""
+    """An update from gradient parts that were never written would spoil the caller's state behind an error status; a pack call that failed
+    must not reach its last launch, which writes the blob's header."""
     (st, names, _), = run([(call, CFG[cfg], -1, 0, 0)])
     assert st == 0 and len(names) >= 2
     for k, (st, got, _) in enumerate(run([(call, CFG[cfg], k, 0, 0) for k in range(len(names))])):
         assert st == DEVICE_ERROR and got == names[:k + 1], (k, got)
+    assert call != "pack" or "pack_residual_kernel" in names[-1]
 
 
 @pytest.mark.parametrize("call,cfg", [("calib_step", "int"), ("calib_step", "mx"), ("rot_step", "int"), ("rot_step", "mxi"), ("rot_apply", "mxi")])
