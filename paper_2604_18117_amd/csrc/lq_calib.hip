@@ -443,14 +443,11 @@ struct CalibCopy {
 };
 __global__ __launch_bounds__(256) void calib_copy_kernel(CalibCopy c)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    size_t begin = 0;
-    for (int k = 0; k < c.n; ++k) {
-        if (i < c.end[k]) {
-            if (i >= begin) c.dst[k][i - begin] = c.src[k] ? c.src[k][i - begin] : v4f{0.f, 0.f, 0.f, 0.f};
-            return;
-        }
-        begin = c.end[k];
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < c.end[c.n - 1]; i += (size_t)gridDim.x * 256) {
+        size_t begin = 0;
+        int k = 0;
+        for (; i >= c.end[k]; ++k) begin = c.end[k];
+        c.dst[k][i - begin] = c.src[k] ? c.src[k][i - begin] : v4f{0.f, 0.f, 0.f, 0.f};
     }
 }
 static void calib_copy_add(CalibCopy& c, void* dst, const void* src, size_t bytes)
@@ -463,7 +460,9 @@ static void calib_copy_add(CalibCopy& c, void* dst, const void* src, size_t byte
 static hipError_t calib_copy_run(const CalibCopy& c, hipStream_t s)
 {
     if (c.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(calib_copy_kernel, dim3((unsigned)((c.end[c.n - 1] + 255) / 256)), dim3(256), 0, s, c);
+    // (a launch has fewer than 2^32 threads: an error matrix of 64 GB takes more than one turn)
+    const size_t blocks = (c.end[c.n - 1] + 255) / 256, cap = (size_t)1 << 22;
+    hipLaunchKernelGGL(calib_copy_kernel, dim3((unsigned)(blocks < cap ? blocks : cap)), dim3(256), 0, s, c);
     return hipGetLastError();
 }
 

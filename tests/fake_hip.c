@@ -9,6 +9,7 @@ enum { MAX_KERNELS = 8192, MAX_LAUNCHES = 256 };
 static struct { const void* host; const char* name; } kernels[MAX_KERNELS];
 static int n_kernels, n_launches, n_attrs, fail_launch = -1, fail_attrs, last_error, device;
 static const char* launched[MAX_LAUNCHES];
+static double threads[MAX_LAUNCHES];
 static struct { dim3_ grid, block; size_t lds; void* stream; } call;
 
 void fake_reset(int failing_launch, int failing_attrs, int dev)
@@ -21,6 +22,7 @@ void fake_reset(int failing_launch, int failing_attrs, int dev)
 int fake_launches(void) { return n_launches; }
 int fake_attrs(void) { return n_attrs; }
 const char* fake_launched(int i) { return launched[i]; }
+double fake_threads(int i) { return threads[i]; }
 
 void** __hipRegisterFatBinary(const void* data) { static void* handle; (void)data; return &handle; }
 void __hipUnregisterFatBinary(void** modules) { (void)modules; }
@@ -46,11 +48,14 @@ int __hipPopCallConfiguration(dim3_* grid, dim3_* block, size_t* lds, void** str
 }
 int hipLaunchKernel(const void* f, dim3_ grid, dim3_ block, void** args, size_t lds, void* stream)
 {
-    (void)grid; (void)block; (void)args; (void)lds; (void)stream;
+    (void)args; (void)lds; (void)stream;
     const char* name = "?";
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i].host == f) name = kernels[i].name;
-    if (n_launches < MAX_LAUNCHES) launched[n_launches] = name;
+    if (n_launches < MAX_LAUNCHES) {
+        launched[n_launches] = name;
+        threads[n_launches] = (double)grid.x * grid.y * grid.z * block.x * block.y * block.z;
+    }
     if (n_launches++ == fail_launch) return last_error = 719;
     return 0;
 }
