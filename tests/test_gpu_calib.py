@@ -85,6 +85,30 @@ def test_first_step_matches_oracle(oracle, N, K, r, g, sint4):
     assert np.allclose(_n(a["mL"]), 0.1 * _n(a["gL"]), rtol=1e-6, atol=0)   # first moments after one step: (1 - beta1) g
 
 
+# Workgroups of several row blocks (of 64 rows, 128 at rank 64; the last run shorter, the last block half missing; many column
+# blocks leave few runs) and a last column block of 64 columns.
+@pytest.mark.parametrize("N,K,r,g,sint4", [(320, 16448, 16, 64, False), (832, 5568, 32, 64, True), (320, 16448, 64, 64, False),
+                                           (192, 16448, 128, 64, False), (320, 16512, 32, 128, False), (320, 16448, 32, 32, "mxfp4"),
+                                           (448, 16448, 64, 32, "mxint4"), (192, 16448, 96, 32, "mxint4"), (192, 16448, 128, 32, "mxfp4"),
+                                           (192, 192, 32, 64, False), (64, 320, 64, 32, "mxfp4"), (320, 64, 96, 64, True)])
+def test_first_step_over_row_blocks_and_a_half_column_block(oracle, N, K, r, g, sint4):
+    rng = np.random.default_rng(N + K + r)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    L, R = ((rng.standard_normal(s) * 0.03).astype(np.float32) for s in ((N, r), (r, K)))
+    cfg = _cfg(N, K, r, g, sint4)
+    state = lq.lq_calib_init(cfg, torch.from_numpy(L).cuda(), torch.from_numpy(R).cuda())
+    st = oracle.calib_init(L, R)
+    out, got, loss, _, _ = _check_step(oracle, cfg, W, torch.from_numpy(W).cuda(), state, st, 1, 1e-4, g, sint4)
+    assert np.array_equal(_n(got["E"]), out.E), "E"
+    assert abs(loss - out.loss) <= 1e-5 * out.loss
+    # fp32 chains: a part's 128 columns (or its rows, at most N) and then the parts, each addition within 2^-24 of the sum of magnitudes
+    c = 2.0 / (N * K)
+    E = np.abs(out.E).astype(np.float64)
+    for name, want, mag, terms in (("gL", out.gL, E @ np.abs(R).astype(np.float64).T, 128 + (K + 127) // 128),
+                                   ("gR", out.gR, np.abs(L).astype(np.float64).T @ E, 2 * N)):
+        assert np.all(np.abs(_n(got[name]) - want) <= (terms + 4) * 2.0 ** -24 * c * mag + 1e-30), name
+
+
 @pytest.mark.parametrize("g,kind,lr", [(64, False, 1e-4), (32, "mxfp4", 1e-3)])
 def test_trajectory_matches_oracle(oracle, g, kind, lr):
     N, K, r = 128, 256, 16

@@ -408,6 +408,8 @@ def test_forward_forms_bit_exact(oracle, M, K, N, r, g, ag):
     (4097, 1280, 16, "bf16", 0, False), (4100, 1344, 96, "f32", 0, True), (4127, 2304, 128, "bf16", 64, True), (4129, 2368, 64, "f32", 0, False),
     (4110, 64, 0, "bf16", 0, False), (4111, 192, 96, "bf16", 0, True),
     (33, 2624, 128, "f32", 0, True), (20, 3136, 16, "f32", 64, True), (1000, 3072, 96, "f32", 0, True), (35, 4608, 128, "f32", 0, False),
+    (40, 4736, 0, "bf16", 0, False), (33, 4672, 16, "bf16", 0, False), (20, 5120, 0, "bf16", 64, False), (20, 5632, 16, "bf16", 64, False),
+    (4100, 4672, 16, "bf16", 0, False), (4097, 4736, 0, "bf16", 64, False),
 ])
 def test_activation_forms_bit_exact(oracle, M, K, r, xd, ag, sm):
     layer = wl.Layer("t", M, K, 64, r, "int", 64, 8, 8, xd, outlier_scale=25.0, n_outliers=max(1, K // 100), seed=M + K, a_group=ag)

@@ -90,6 +90,25 @@ def test_mx_branch_formats_as_q2(oracle, q2, bits, N, K, r):
     _compare_step(oracle, lq, N, K, r, bits, seed=N + r, q2=q2, lr=0.5, beta=0.9, s=2, grad_scale=2500.0)
 
 
+# More groups of rows (columns) than workgroups: each takes several turns, some one fewer, the last group of 128 half missing.
+@pytest.mark.parametrize("N,K,r,bits,q2", [(33088, 192, 16, 8, "int"), (64, 33088, 16, 4, "int"), (16448, 1216, 64, 6, "int"),
+                                           (192, 16448, 64, 8, "fp8"), (33088, 320, 32, 8, "mxfp8"), (8256, 1344, 128, 8, "mxfp8"),
+                                           (128, 8384, 96, 4, "mxint"), (16448, 1216, 64, 6, "mxfp6")])
+def test_several_turns_per_workgroup(oracle, N, K, r, bits, q2):
+    from paper_2604_18117_amd import binding as lq
+    _compare_step(oracle, lq, N, K, r, bits, seed=N + K, q2=q2, lr=0.5, beta=0.9, s=2, grad_scale=2500.0)
+    if r <= 64:  # ... and the same bits with the partial results in the library's array
+        L, R, X0, M0 = _case(N, K, r, 5)
+        cfg = _cfg(lq, N, K, r, bits, q2)
+        got = []
+        for step in (lq.lq_rot_step, lq.lq_rot_step_static):
+            state = lq.lq_rot_init(cfg, _d(X0), _d(M0))
+            step(cfg, _d(L), _d(R), state, grad_scale=2500.0)
+            got.append(lq.lq_rot_unpack(cfg, state, ("Omega", "Mom", "G", "E1", "E2")))
+        torch.cuda.synchronize()
+        assert all(torch.equal(got[0][k], got[1][k]) for k in got[0])
+
+
 def test_defaults_identity_start_and_more_passes(oracle):
     """lq_rot_init without matrices starts at the identity with zero momentum; the paper's learning rate with the loss as
     printed (grad_scale 1); s = 5 passes; beta = 0."""
