@@ -413,8 +413,9 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
 
     // Fragment pairs of R, RD ahead of their products: an LDS round trip is longer than a pair's products, an L2 round trip much
     // longer.  Without STAGE they are requested before X is coded, up to rank 64 a super-step ahead (ROLL; us without / with it: rank 32,
-    // 4096 x 4608 16.5 / 14.7, rank 64 18.7 / 15.8; rank 128, 64 x 1152 7.1 / 7.5; from codes rank 64, 2 x 4608 7.6 / 10.3).
-    constexpr bool ROLL = !STAGE && !FROMC && !SM && NJB <= 4;
+    // 4096 x 4608 16.5 / 14.7, rank 64 18.7 / 15.8, smoothed fp32 rank 32, 8192 x 2240 21.0 / 18.5, though 64 x 2240 10.1 / 11.0;
+    // but rank 128, 64 x 1152 7.1 / 7.5, smoothed bf16 rank 64, 4096 x 2240 12.4 / 13.9, from codes rank 64, 2 x 4608 7.6 / 10.3).
+    constexpr bool ROLL = !STAGE && !FROMC && (!SM || !BF16IN) && NJB <= 4;
     constexpr int RD = STAGE ? (NJA < 3 ? NJA : 3) : NJA < 4 ? NJA : 4;
     v4i rf[RD][2];
     auto read_pair = [&](int ss, int jb) {
