@@ -61,3 +61,44 @@ def test_fused_smoothing(oracle, family, M, K, N, r, xd):
     a = run_gpu(layer, X, Ws, L, R, debug=True, debug_acc=False)
     b = run_gpu(layer, X, Ws, L, R, debug=True, debug_acc=False, gamma=gamma)
     assert not np.array_equal(n(a.av.xq), n(b.av.xq))
+
+
+@pytest.mark.parametrize("family,g,bw,ag", [("int", 64, 8, 0), ("int", 128, 4, 0), ("int", 64, 6, 64), ("mx", 32, 8, 32), ("mxb", 32, 8, 32),
+                                            ("mxb", 32, 6, 32), ("mxi", 32, 8, 32)])
+@pytest.mark.parametrize("r", [32, 96, 128])
+def test_packing_runs_of_groups_and_unaligned_sources(oracle, family, g, bw, ag, r):
+    """Workgroups that pack several scale groups of their rows (runs of two and three), and W, L, R that are aligned to
+    their elements only: codes and scales against the oracle, and the same blob from both."""
+    import torch
+    from paper_2604_18117_amd import binding as lq
+    from tests.gpu_util import n
+    if family == "mx" and r == 96:
+        pytest.skip("rank 96 is not a rank of the fp32-scaled FP8 branch")
+    N, K = 4096, 4736
+    layer = wl.Layer("t", 1, K, N, r, family, g, bw, 8 if family != "mxb" else bw, "bf16", seed=N + r, a_group=ag)
+    _, W, L, R = wl.make_inputs(layer)
+    cfg = lq.config_for_layer(layer)
+
+    def shifted(a):
+        t = torch.empty(a.size + 1, dtype=torch.float32, device="cuda")[1:].view(a.shape)
+        return t.copy_(torch.from_numpy(a))
+    blobs = [lq.lq_pack_weights(cfg, *s, packed=torch.zeros(lq.lq_packed_sizes(cfg), dtype=torch.uint8, device="cuda"))
+             for s in ([torch.from_numpy(a).cuda() for a in (W, L, R)], [shifted(a) for a in (W, L, R)])]
+    assert torch.equal(blobs[0], blobs[1])
+    wv = lq.lq_unpack_weights(cfg, blobs[0])
+    rows = np.arange(0, N, 129)  # (a row's codes depend on its own values and on R alone)
+    if family == "int":
+        pk = oracle.pack_int(W[rows], L[rows], R, g, bw, sint4_blocks=ag == 64)
+        assert np.array_equal(n(wv.sw)[rows], pk.sw)
+    elif family == "mx":
+        pk = oracle.pack_mx(W[rows], L[rows], R)
+    elif family == "mxb":
+        pk = oracle.pack_mxb(W[rows], L[rows], R, elem=bw)
+    else:
+        pk = oracle.pack_mxi(W[rows], L[rows], R, bw)
+    if family in ("mx", "mxb"):
+        assert np.array_equal(t_mxb.E2M1[n(wv.pq).view(np.uint8)[rows]], t_mxb.E2M1[pk.pc])
+    else:
+        assert np.array_equal(n(wv.pq)[rows], pk.pq)
+    if family != "int":
+        assert np.array_equal(n(wv.pe)[rows], pk.pe)
