@@ -79,7 +79,7 @@ def bench_calib(args, layer, np, torch, lq, wl):
            "config": {"workload": layer.name + "_calib", "N": N, "K": Kd, "rank": r,
                       "main": {"mx": "MXFP4", "mxb": "MXFP4", "mxi": "MXINT4"}.get(
                           layer.family, "SINT4 blocks" if layer.a_group == 64 else f"INT4 g{layer.g}"),
-                      "launches_per_step": 4},
+                      "launches_per_step": 2},
            "work_per_step": {"flops": flops, "hbm_bytes_error_kernel": hbm, "loss": float(loss.item())}}
     if args.oracle_seconds > 0:
         from oracle import lq_ref
@@ -121,7 +121,7 @@ def bench_rot(args, layer, np, torch, lq, wl):
            "n_gpus": 1, "steps": K, "warmup": args.warmup, "ms_per_step": round(ms_step, 5), "higher_is_better": True,
            "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
            "config": {"workload": layer.name + "_rot", "N": N, "K": Kd, "rank": r, "q2_bits": layer.br_w_bits,
-                      "launches_per_step": 5},
+                      "launches_per_step": 3 if layer.family in ("mxb", "mxi") else 4},  # (row maxima first with one scale per row)
            "work_per_step": {"flops": 2.0 * (2 * 2 + 1) * (N + Kd) * r * r + 2.0 * 8 * r ** 3, "loss": float(loss.item())}}
     if args.oracle_seconds > 0:
         from oracle import lq_ref

@@ -181,7 +181,8 @@ lq_status lq_act_sizes(const lq_config *cfg, int64_t M, size_t *act_bytes);
    X 16-byte aligned).  `packed`: blob written by lq_pack_weights for the same cfg, packed_bytes = the
    bytes the caller holds there (LQ_ERR_BUFFER_TOO_SMALL below lq_packed_sizes; packed may be NULL, and
    packed_bytes is then ignored, when rank == 0 and no smoothing is fused).
-   `act`: device, 256-byte aligned, at least lq_act_sizes(cfg, M) bytes.  dbg may be NULL. */
+   `act`: device, 256-byte aligned, at least lq_act_sizes(cfg, M) bytes.  dbg may be NULL.
+   A token's codes, and its outputs of the forward, are the same bits in every batch. */
 lq_status lq_quantize_act(const lq_config *cfg, const void *packed, size_t packed_bytes, const void *X,
                           int64_t M, int64_t ldx, void *act, size_t act_bytes, const lq_act_debug *dbg,
                           void *stream);
@@ -243,8 +244,9 @@ lq_status lq_unpack_act(const lq_config *cfg, const void *act, int64_t M, const 
    the best rank-r approximation of W (an input here: the singular value decomposition is the caller's).  lq_pack_weights
    forms W - L' R', so it takes L' = -L, R' = R.
    The state blob is device memory owned by the caller (256-byte aligned, at least state_bytes); it holds the factors,
-   Adam's two moments, the last step's gradients and error matrix.  A step is four kernel launches, no atomics, no
-   allocation; results are reproducible bit for bit. */
+   Adam's two moments, the last step's gradients and error matrix, and the parts they are summed from (K / 128 parts
+   of grad_L, each N x r; at most 65536 / K parts of grad_R, each r x K).  A step is two kernel launches, no atomics, no allocation; results are
+   reproducible bit for bit.  After a launch that failed (LQ_ERR_DEVICE) nothing more of the step is launched. */
 typedef struct {
     float lr;      /* the paper uses 1e-4 for INT formats (App. A.2)                  */
     float beta1;   /* Adam as published: 0.9, 0.999, 1e-8; bias-corrected, no decay   */
@@ -291,8 +293,9 @@ lq_status lq_calib_unpack(const lq_config *cfg, const void *state, const lq_cali
    the optimiser: beta, q, s and eps are the cited algorithm's (0.9, 0.5, 2, 1e-8).  With the mean-squared-error loss
    as printed the gradient of a layer-sized problem is of the order of 1e-7 and a step of 0.5 moves Omega by as much;
    grad_scale (1 = as printed) is the caller's handle on that.
-   The state blob is device memory owned by the caller (256-byte aligned, at least state_bytes).  A step is five kernel
-   launches (four with block-scaled formats), no atomics, no allocation; results are reproducible bit for bit. */
+   The state blob is device memory owned by the caller (256-byte aligned, at least state_bytes).  A step is four kernel
+   launches (three with block-scaled formats), no atomics, no allocation; results are reproducible bit for bit.  After a launch
+   that failed (LQ_ERR_DEVICE) nothing more of the step is launched. */
 typedef struct {
     float lr;          /* 0.5 (App. A.2)                                                  */
     float beta;        /* momentum, in [0, 1)                                            */
@@ -320,8 +323,7 @@ lq_status lq_rot_step(const lq_config *cfg, const float *L, const float *R, void
                       const lq_cayley *opt, float *loss, void *stream);
 
 /* For callers that cannot allocate or size a workspace (code under HIP graph capture, tight serving loops, harnesses
-   that forbid hipMalloc): lq_rot_step with the step's partial results (row maxima, loss and gradient partials, the
-   update's work matrices) in an array the library holds on each GPU (LQ_ROT_STATIC_SCRATCH_BYTES, until the process
+   that forbid hipMalloc): lq_rot_step with the step's partial results (row maxima, loss and gradient partials) in an array the library holds on each GPU (LQ_ROT_STATIC_SCRATCH_BYTES, until the process
    ends) instead of in the state blob.  Same arguments, same kernels, same results bit for bit.  Of the state blob only
    the leading sections are used (Omega, momentum, gradient, E1, E2: 3 r^2 + N r + r K floats, each section rounded up to
    256 bytes), so state_bytes may be that small; a blob of lq_rot_sizes bytes always serves.  A configuration whose

@@ -139,7 +139,8 @@ struct CalibParams {
 };
 
 // LDS images.  L and E, row strides of 4 modulo 16 floats: the 16-byte operand reads (row l15, four columns at 4 q) and the
-// reads of a column over rows 16 s + 4 q + u are free of bank conflicts.  R is read over rows 4 s + q as well: rows of
+// reads of a column over rows 16 s + 4 q + u touch every bank once (the counter shows 0.9 conflict cycles per LDS instruction, with
+// the stores of L and the 16-byte reads' own passes).  R is read over rows 4 s + q as well: rows of
 // 128 floats, the column's bits 4..5 exchanged by the row's bits 0..1 and bits 2..3 by the row's bits 2..3.
 __device__ __forceinline__ int calib_rs(int row, int col) { return row * CALIB_COLS + (col ^ (16 * (row & 3)) ^ (row & 12)); }
 template <int R> constexpr int calib_lds() { return (16 * calib_waves(R) * (R + 4 + CALIB_COLS + 4) + R * CALIB_COLS) * 4; }
