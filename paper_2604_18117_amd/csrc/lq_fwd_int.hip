@@ -832,18 +832,7 @@ __global__ __launch_bounds__(64, 2) void fwd_int_small_kernel(FwdParams p)
 }
 
 // Workgroup slots of the device: two workgroups (of 256 registers per lane) per compute unit.
-static int workgroup_slots()
-{
-    static int cached[64] = {0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 512;
-    if (cached[dev] == 0) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-        cached[dev] = 2 * cus;
-    }
-    return cached[dev];
-}
+static int workgroup_slots() { return 2 * compute_units(); }
 
 template <int GC, int NK, bool DBG, bool GA = false>
 static hipError_t launch_cfg(const FwdParams& p0, hipStream_t s)

@@ -1539,6 +1539,7 @@ static void mx_fwd_launch(const MxFwdParams& p, hipStream_t s)
     //   T =  720 ( 300 x 1152 -> 2304): 4.1 / 4.3 / 4.8 /  7.9        T = 2304 (2048 x 4608 -> 1152): 16.9 / 15.8 / 14.7 / 18.5
     //   T = 1080 ( 300 x 1152 -> 3456): 5.4 / 4.9 / 5.5 /  8.1        T = 3500 ( 300 x 2240 -> 11200): 16.4 / 12.1 / 10.7 / 12.5
     //   T =  576 ( 512 x 4608 -> 1152): 6.1 / 7.9 / 9.5 / 17.4        T = 4608 (4096 x 4608 -> 1152): 30.8 / 25.4 / 21.3 / 19.7
+    //                                                               T = 3492 (3100 x 4608 -> 1152): 25.5 / 19.8 / 17.3 / 19.2
     const int64_t T = (int64_t)p.nrb * (p.N / 32);
     // More than 80 MB of X codes (a narrow layer): a stream over memory, which the large tiles' requests serve as well or better (37243 x
     // 4608 -> 64: 18.7 us against 17.9).
@@ -1555,18 +1556,7 @@ static void mx_fwd_launch(const MxFwdParams& p, hipStream_t s)
         hipLaunchKernelGGL((mx_fwd_kernel<NK, false, BLK, BFMT>), grid, block, 0, s, p);
 }
 
-static int mx_workgroup_slots()  // two workgroups (of up to 256 registers per lane) per compute unit
-{
-    static int cached[64] = {0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 512;
-    if (cached[dev] == 0) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-        cached[dev] = 2 * cus;
-    }
-    return cached[dev];
-}
+static int mx_workgroup_slots() { return 2 * compute_units(); }  // two workgroups (of up to 256 registers per lane) per compute unit
 
 hipError_t launch_fwd_mx(const Dims& d, const uint8_t* packed, const uint8_t* act, int64_t M, uint16_t* Y, int64_t ldy,
                          const lq_fwd_debug* dbg, hipStream_t s)
