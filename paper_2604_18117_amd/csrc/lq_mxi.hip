@@ -810,6 +810,34 @@ __device__ __forceinline__ v8i mxi_expand8(v4i p)  // 32 nibbles -> 32 FP8 subno
     return o;
 }
 
+// Both codes of eight values (bf16 pairs) by one fused multiply-add each: scaling by a power of two is exact, so fma(x, 2^-step, magic)
+// rounds the scaled value to the nearest integer (ties to even) in one step -- the same integer the
+// activation kernel reaches by rounding on the block's grid and scaling afterwards -- and leaves it in
+// the low mantissa bits of the magic number.  Clamping after the rounding equals clamping before it.
+__device__ __forceinline__ void mxi_handoff_codes(const uint32_t* w, const float inv4, const float to8, uint32_t& pk, uint32_t* c8)
+{
+    uint32_t sum = 0u - 0xFB000000u;
+    uint32_t ub[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float x = __uint_as_float((e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16));
+        const uint32_t mb = __float_as_uint(fminf(__builtin_fmaf(fabsf(x), inv4, 8388608.0f), 8388615.0f));
+        const int sh = e < 4 ? 8 * e : 8 * ((e - 5) & 3) + 4;
+        sum += mb << sh;
+        // 1.5 * 2^23 + code, code in [-127, 127]: the low byte is the two's-complement MXINT8 code
+        ub[e] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(x, to8, 12582912.0f), 12582785.0f, 12583039.0f));
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t lo = __builtin_amdgcn_perm(ub[4 * h + 1], ub[4 * h], 0x0c0c0400u);      // bytes 0 of two dwords
+        const uint32_t hi = __builtin_amdgcn_perm(ub[4 * h + 3], ub[4 * h + 2], 0x04000c0cu);  // ... in the upper half
+        c8[h] = lo | hi;
+    }
+    const uint32_t s03 = __builtin_amdgcn_perm(w[1], w[0], 0x07050301u);
+    const uint32_t s47 = __builtin_amdgcn_perm(w[3], w[2], 0x07050301u);
+    pk = sum | (s03 & 0x80808080u) | ((s47 >> 4) & 0x08080808u);
+}
+
 // Hand-off codes of 8 consecutive channels (k0 = this layer's channel = the next layer's k) of one token, given as bf16: a
 // block of 32 of the next layer's K axis is the 4 lanes that differ in the two low lane bits.  Codes as in the activation
 // kernel: shared exponent from the block maximum, MXINT4 main codes (sign-magnitude nibbles), MXINT8 branch codes.
@@ -826,30 +854,8 @@ __device__ __forceinline__ void mxi_handoff_emit(const MxiFwdParams& p, const v4
                     const uint32_t field = exp_field(am);
                     const float inv4 = field >= 2u ? __uint_as_float((256u - field) << 23) : 0.0f;   // 2^(2-s)
                     const float to8 = field >= 7u ? __uint_as_float((260u - field) << 23) : 0.0f;    // 2^(6-s)
-                    // Both codes by one fused multiply-add each: scaling by a power of two is exact, so fma(x, 2^-step, magic)
-                    // rounds the scaled value to the nearest integer (ties to even) in one step -- the same integer the
-                    // activation kernel reaches by rounding on the block's grid and scaling afterwards -- and leaves it in
-                    // the low mantissa bits of the magic number.  Clamping after the rounding equals clamping before it.
-                    uint32_t sum = 0u - 0xFB000000u, c8[2];
-                    uint32_t ub[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float x = __uint_as_float((e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16));
-                        const uint32_t mb = __float_as_uint(fminf(__builtin_fmaf(fabsf(x), inv4, 8388608.0f), 8388615.0f));
-                        const int sh = e < 4 ? 8 * e : 8 * ((e - 5) & 3) + 4;
-                        sum += mb << sh;
-                        // 1.5 * 2^23 + code, code in [-127, 127]: the low byte is the two's-complement MXINT8 code
-                        ub[e] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(x, to8, 12582912.0f), 12582785.0f, 12583039.0f));
-                    }
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const uint32_t lo = __builtin_amdgcn_perm(ub[4 * h + 1], ub[4 * h], 0x0c0c0400u);      // bytes 0 of two dwords
-                        const uint32_t hi = __builtin_amdgcn_perm(ub[4 * h + 3], ub[4 * h + 2], 0x04000c0cu);  // ... in the upper half
-                        c8[h] = lo | hi;
-                    }
-                    const uint32_t s03 = __builtin_amdgcn_perm(w[1], w[0], 0x07050301u);
-                    const uint32_t s47 = __builtin_amdgcn_perm(w[3], w[2], 0x07050301u);
-                    const uint32_t pk = sum | (s03 & 0x80808080u) | ((s47 >> 4) & 0x08080808u);
+                    uint32_t pk, c8[2];
+                    mxi_handoff_codes(w, inv4, to8, pk, c8);
     if (row < p.nrb * 32) {
         *(uint32_t*)(p.ho_xq + mxi_frag_offset(row, k0, p.ho_C64)) = pk;
         *(uint2*)(p.ho_cb + (size_t)row * p.N + k0) = make_uint2(c8[0], c8[1]);
@@ -861,6 +867,37 @@ __device__ __forceinline__ void mxi_handoff_emit(const MxiFwdParams& p, const v4
                 for (int c = p.ho_C64; c < 4 * p.ho_CQ; ++c) p.ho_xe[mxi_scale_offset(row, c, (k0 >> 5) & 1, p.ho_CQ)] = (uint8_t)127;
         }
     }
+}
+
+// The same from the registers of mxi_fwd_kernel: a row block of 32 tokens and 64 channels (one chunk of the next layer's K); lane (row, h)
+// holds channels 16 h .. 16 h + 15 of both blocks of 32 as bf16 pairs, which is how the activation kernel holds them: one 16-byte store of
+// main codes (1 KB contiguous per wavefront), one of branch codes per block, and each lane half writes one block's scale bytes.
+__device__ __forceinline__ void mxi_handoff_rows(const MxiFwdParams& p, const uint32_t (&w)[2][8], const int rb, const int cb0, const int lane)
+{
+    const int half = lane >> 5, row = rb * 32 + (lane & 31), c = cb0 >> 1;
+    uint32_t field[2], pk[4];
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+        us2 m2 = {0, 0};
+#pragma unroll
+        for (int d = 0; d < 8; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, w[blk][d] & 0x7FFF7FFFu));
+        const uint32_t mm = (uint32_t)(m2[0] > m2[1] ? m2[0] : m2[1]) << 16;
+        const auto sw = __builtin_amdgcn_permlane32_swap(mm, mm, false, false);  // both halves of the row in every lane
+        field[blk] = exp_field(fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])));
+        const float inv4 = field[blk] >= 2u ? __uint_as_float((256u - field[blk]) << 23) : 0.0f;   // 2^(2-s)
+        const float to8 = field[blk] >= 7u ? __uint_as_float((260u - field[blk]) << 23) : 0.0f;    // 2^(6-s)
+        uint32_t c8[4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) mxi_handoff_codes(&w[blk][4 * h], inv4, to8, pk[2 * blk + h], &c8[2 * h]);
+        *(v4i*)(p.ho_cb + (size_t)row * p.N + (cb0 + blk) * 32 + 16 * half) = v4i{(int)c8[0], (int)c8[1], (int)c8[2], (int)c8[3]};
+    }
+    *(v4i*)(p.ho_xq + ((size_t)((size_t)rb * p.ho_C64 + c) * 64 + lane) * 16) = v4i{(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
+    const uint32_t f = half ? field[1] : field[0];
+    p.ho_xe[mxi_scale_offset(row, c, half, p.ho_CQ)] = (uint8_t)(f + 7u);
+    p.ho_cbe[(size_t)row * (p.N >> 5) + cb0 + half] = (uint8_t)f;
+    // padding chunks of the next layer's last quad: valid E8M0 bytes (2^0), written with the last real chunk
+    if (c == p.ho_C64 - 1)
+        for (int cc = p.ho_C64; cc < 4 * p.ho_CQ; ++cc) p.ho_xe[mxi_scale_offset(row, cc, half, p.ho_CQ)] = (uint8_t)127;
 }
 
 // NK16 = 16-deep chunks of the rank: 0 | 2 | 4 | 6 | 8.  HO: quantized hand-off (Section 4.5): the epilogue also emits
@@ -892,6 +929,10 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
     const int C64 = p.C64, CQ = p.CQ;
 
     const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
+    // The weights are the first operand, and lane l32 of it takes row c(l32) of its block of 32: the accumulator of row 8 g + 4 h + i is
+    // register 4 g + i of the lanes of half h, so with c(8 g + 4 h + i) = 16 h + 4 g + i a lane ends up with one token and 16
+    // consecutive channels of it -- 32 bytes of Y, and the unit in which the next layer's codes are laid out.
+    const uint32_t lanep = (uint32_t)((l32 & 3) + ((l32 >> 3) << 2) + (((l32 >> 2) & 1) << 4) + 32 * half);
     int rbs = rb0 + wave;  // row block staged by this wavefront
     rbs = rbs < p.nrb ? rbs : p.nrb - 1;
     const uint8_t* xq_base = p.xq + (size_t)rbs * C64 * 1024;
@@ -922,7 +963,7 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
     auto load_b = [&](BStage& b, int step) {
         const int st = step < C64 ? step : C64 - 1;
 #pragma unroll
-        for (int cbi = 0; cbi < 2; ++cbi) b.v[cbi] = *(const v4i*)(pq_base[cbi] + (size_t)st * 1024 + lane16);
+        for (int cbi = 0; cbi < 2; ++cbi) b.v[cbi] = *(const v4i*)(pq_base[cbi] + (size_t)st * 1024 + lanep * 16u);
     };
     struct Scales { int a[4]; int b[2]; };
     auto load_s = [&](Scales& sc, int quad) {
@@ -930,7 +971,7 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
 #pragma unroll
         for (int rbi = 0; rbi < 4; ++rbi) sc.a[rbi] = *(const int*)(xe_base[rbi] + (size_t)q * 256 + lane4);
 #pragma unroll
-        for (int cbi = 0; cbi < 2; ++cbi) sc.b[cbi] = *(const int*)(pe_base[cbi] + (size_t)q * 256 + lane4);
+        for (int cbi = 0; cbi < 2; ++cbi) sc.b[cbi] = *(const int*)(pe_base[cbi] + (size_t)q * 256 + lanep * 4u);
     };
 
     v16f t[4][2];
@@ -964,8 +1005,8 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
             if (rbi + 1 < 4) af[(rbi + 1) & 1] = lds_a(rbi + 1);
 #pragma unroll
             for (int cbi = 0; cbi < 2; ++cbi)
-                t[rbi][cbi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[rbi & 1], bu[PAR][cbi], t[rbi][cbi], 0, 0, SEL,
-                                                                             sc.a[rbi], SEL, sc.b[cbi]);
+                t[rbi][cbi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bu[PAR][cbi], af[rbi & 1], t[rbi][cbi], 0, 0, SEL,
+                                                                             sc.b[cbi], SEL, sc.a[rbi]);
             if (rbi == 0) {
                 store_a(a, buf ^ 1);
                 load_a(a, s + 3);
@@ -1022,74 +1063,93 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
 
     if (!active) return;
 
-    // ---- rank-r expansion on the bf16 MFMA, accumulated on top of the main product --------------
-#pragma unroll
-    for (int ch = 0; ch < NK16; ++ch) {
-        v4i lf[2];
-#pragma unroll
-        for (int cbi = 0; cbi < 2; ++cbi) lf[cbi] = *(const v4i*)(p.lv + ((size_t)((size_t)(cb0 + cbi) * NK16 + ch) * 64 + lane) * 16);
+    // ---- rank-r expansion on the bf16 MFMA, accumulated on top of the main product: operands of BD chunks of the rank requested
+    // ahead (the registers of the K loop's operands are free; with each chunk's requested at its turn these products took 10500
+    // cycles at rank 128, of which the matrix core needs 2048)
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    constexpr int RSRC_FLAGS = 0x00020000, BD = NK16 < 3 ? NK16 : 3;
+    if constexpr (NK16 > 0) {
+        const __amdgpu_buffer_rsrc_t rs_l = __builtin_amdgcn_make_buffer_rsrc((void*)(p.lv + (size_t)cb0 * NK16 * 1024), 0, 2 * NK16 * 1024, RSRC_FLAGS);
+        __amdgpu_buffer_rsrc_t rs_t[4];
 #pragma unroll
         for (int rbi = 0; rbi < 4; ++rbi) {
             int rb = rb0 + rbi;
             rb = rb < p.nrb ? rb : p.nrb - 1;
-            const v4i tf = *(const v4i*)(p.tv + ((size_t)((size_t)rb * NK16 + ch) * 64 + lane) * 16);
+            rs_t[rbi] = __builtin_amdgcn_make_buffer_rsrc((void*)(p.tv + (size_t)rb * NK16 * 1024), 0, NK16 * 1024, RSRC_FLAGS);
+        }
+        v8bf lf[BD][2], tf[BD][4];
+        auto load_branch = [&](int ch) {
 #pragma unroll
             for (int cbi = 0; cbi < 2; ++cbi)
-                t[rbi][cbi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, tf), __builtin_bit_cast(v8bf, lf[cbi]),
-                                                                     t[rbi][cbi], 0, 0, 0);
+                lf[ch % BD][cbi] = __builtin_bit_cast(v8bf, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_l, lanep * 16u, (cbi * NK16 + ch) * 1024, 0));
+#pragma unroll
+            for (int rbi = 0; rbi < 4; ++rbi)
+                tf[ch % BD][rbi] = __builtin_bit_cast(v8bf, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_t[rbi], lane16, ch * 1024, 0));
+        };
+#pragma unroll
+        for (int ch = 0; ch < BD; ++ch) load_branch(ch);
+#pragma unroll
+        for (int ch = 0; ch < NK16; ++ch) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int rbi = 0; rbi < 4; ++rbi)
+#pragma unroll
+                for (int cbi = 0; cbi < 2; ++cbi)
+                    t[rbi][cbi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf[ch % BD][cbi], tf[ch % BD][rbi], t[rbi][cbi], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ch + BD < NK16) load_branch(ch + BD);
         }
     }
 
-    // ---- epilogue: bf16, transposed through the wavefront's own LDS slice, full-line stores ------
+    // ---- epilogue: bf16; with the hand-off the next layer's codes straight from the registers; Y transposed through the wavefront's
+    // own LDS slice, full-line stores ------
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     uint8_t* stage = lds + wave * EPI_WAVE;
-    const int wr_off = (4 * half) * EPI_ROW + l32 * 2;
+    const int wr_off = l32 * EPI_ROW + half * 32;
     const int rd_row = lane >> 3, rd_seg = lane & 7;
     // The stores are buffer stores through a descriptor that ends with the wavefront's 128 bytes of the tile's last valid
-    // row (rows past M are out of range and dropped by the hardware; without Y the descriptor is empty): no branch, so
+    // row (rows past M are out of range and dropped by the hardware): no branch, so
     // the compiler can count the stores and need not wait for them when it waits for an older load.
-    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
     const int rows_valid = p.M - rb0 * 32 < 128 ? p.M - rb0 * 32 : 128;
     const bool have_y = !HO || p.Y;
     const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
         have_y ? (void*)(p.Y + (size_t)(rb0 * 32) * p.ldy + cb0 * 32) : (void*)p.ho_xq, 0,
-        have_y ? (int)((rows_valid - 1) * p.ldy * 2 + 128) : 0, 0x00020000);
+        have_y ? (int)((rows_valid - 1) * p.ldy * 2 + 128) : 0, RSRC_FLAGS);
     uint32_t yoff = (uint32_t)(rd_row * (int)p.ldy * 2 + rd_seg * 16);
     const uint32_t ystep = (uint32_t)(8 * (int)p.ldy * 2);
     v4i ov[4];
 #pragma unroll
     for (int rbi = 0; rbi < 4; ++rbi) {
-        const int rbase = (rb0 + rbi) * 32;
+        uint32_t w[2][8];
 #pragma unroll
         for (int cbi = 0; cbi < 2; ++cbi) {
 #pragma unroll
-            for (int i = 0; i < 16; i += 2) {
-                const bf16x2 h = __builtin_convertvector(f32x2{t[rbi][cbi][i], t[rbi][cbi][i + 1]}, bf16x2);
-                const uint32_t w = __builtin_bit_cast(uint32_t, h);
-                const int o = wr_off + (8 * (i >> 2) + (i & 3)) * EPI_ROW + cbi * 64;
-                *(uint16_t*)(stage + o) = (uint16_t)(w & 0xFFFFu);
-                *(uint16_t*)(stage + o + EPI_ROW) = (uint16_t)(w >> 16);
-            }
+            for (int i = 0; i < 16; i += 2)
+                w[cbi][i >> 1] = __builtin_bit_cast(uint32_t, (bf16x2)__builtin_convertvector(f32x2{t[rbi][cbi][i], t[rbi][cbi][i + 1]}, bf16x2));
             if (DBG) {
-                const int col = (cb0 + cbi) * 32 + l32;
+                const int row = (rb0 + rbi) * 32 + l32;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int row = rbase + 8 * (i >> 2) + 4 * half + (i & 3);
-                    if (row < p.M && p.dbg_y32) p.dbg_y32[(size_t)row * p.N + col] = t[rbi][cbi][i];
-                }
+                for (int i = 0; i < 16; ++i)
+                    if (row < p.M && p.dbg_y32) p.dbg_y32[(size_t)row * p.N + (cb0 + cbi) * 32 + 16 * half + i] = t[rbi][cbi][i];
             }
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) ov[q] = *(const v4i*)(stage + (q * 8 + rd_row) * EPI_ROW + rd_seg * 16);
         if constexpr (HO) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) mxi_handoff_emit(p, ov[q], rbase + q * 8 + rd_row, cb0 * 32 + rd_seg * 8);
+            if (rb0 + rbi < p.nrb) mxi_handoff_rows(p, w, rb0 + rbi, cb0, lane);
         }
+        if (have_y) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, ov[q]), rs_y, yoff, 0, 0);
-            yoff += ystep;
+            for (int cbi = 0; cbi < 2; ++cbi)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    *(v4i*)(stage + wr_off + cbi * 64 + h * 16) = v4i{(int)w[cbi][4 * h], (int)w[cbi][4 * h + 1], (int)w[cbi][4 * h + 2], (int)w[cbi][4 * h + 3]};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ov[q] = *(const v4i*)(stage + (q * 8 + rd_row) * EPI_ROW + rd_seg * 16);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, ov[q]), rs_y, yoff, 0, 0);
+                yoff += ystep;
+            }
         }
     }
 }
