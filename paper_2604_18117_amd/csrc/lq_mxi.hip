@@ -900,32 +900,32 @@ __device__ __forceinline__ void mxi_handoff_rows(const MxiFwdParams& p, const ui
         for (int cc = p.ho_C64; cc < 4 * p.ho_CQ; ++cc) p.ho_xe[mxi_scale_offset(row, cc, half, p.ho_CQ)] = (uint8_t)127;
 }
 
+namespace mxif {
+constexpr int RBT = 4, NBUF = 4;              // row blocks of a tile, LDS buffers of the activation stream (one 64-chunk each)
+constexpr int EPI_ROW = 144, EPI_WAVE = 32 * EPI_ROW;
+constexpr int LDS_MAIN = NBUF * RBT * 2048;   // [buffer][row block][part][lane][16 B]
+constexpr int LDS_BYTES = LDS_MAIN > 4 * EPI_WAVE ? LDS_MAIN : 4 * EPI_WAVE;
+}  // namespace mxif
+
+// One tile of 128 rows: WN = 4 wavefronts side by side of 128 x 64 outputs each, or, for a last column of tiles of at most 128 channels,
+// 2 x 2 wavefronts of 64 x 64 (side by side two of the four would have no columns).  Bounded by the 8-bit matrix rate inside the K loop
+// (two wavefronts per SIMD keep it busy as long as their loads arrive), by instruction latency around it.  The fences in the loop
+// hold every load two steps ahead of its use: left to itself the compiler sank them to the end of their step and waited for all of
+// them in the next (16384 x 4608 -> 1152 rank 128: 79.6 us, with the fences and the narrow tiles last 66.3; 16384 x 1152 -> 3456 70.4
+// -> 59.4; 16384 x 1152 -> 1152 26.2 -> 22.7; 5000 x 2240 -> 6720 67.6 -> 63.3).
 // NK16 = 16-deep chunks of the rank: 0 | 2 | 4 | 6 | 8.  HO: quantized hand-off (Section 4.5): the epilogue also emits
 // the next layer's activation codes from the bf16 values it has just formed; Y itself is optional then.
-template <int NK16, bool DBG, bool HO = false>
-__global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
+template <int NK16, bool DBG, bool HO, int WN>
+__device__ __forceinline__ void mxi_fwd_tile(const MxiFwdParams& p, uint8_t* lds, const int rb0, const int tile_n)
 {
-    if constexpr (HO) write_tag(p.ho_tag_dst, p.ho_tag);
-    constexpr int RBT = 4;
-    constexpr int EPI_ROW = 144, EPI_WAVE = 32 * EPI_ROW;
-    constexpr int LDS_MAIN = 2 * RBT * 2048;  // [buffer][row block][part][lane][16 B]
-    constexpr int LDS_BYTES = LDS_MAIN > 4 * EPI_WAVE ? LDS_MAIN : 4 * EPI_WAVE;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
-
+    using namespace mxif;
+    constexpr int NRB = WN == 4 ? 4 : 2;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-
-    // XCD-aware tile order: workgroup ids are dealt round-robin to the 8 XCDs, each gets one run of tiles
-    const int tiles = p.tilesM * p.tilesN;
-    const int per = tiles >> 3, rem = tiles & 7;
-    const int xcd = blockIdx.x & 7, loc = blockIdx.x >> 3;
-    const int tile = xcd * per + (xcd < rem ? xcd : rem) + loc;
-    int tile_m, tile_n;
-    panel_tile(tile, p.tilesM, p.tilesN, p.panel, tile_m, tile_n);
-    const int rb0 = tile_m * RBT;
-    const int cb0 = tile_n * 8 + wave * 2;
-    const bool active = (cb0 * 32 < p.N) && (rb0 < p.nrb);
+    const int rw = NRB * (wave / WN), rbw = rb0 + rw;   // this wavefront's first row block, in the tile and in the layer
+    const int cb0 = tile_n * 8 + (wave % WN) * 2;
+    const bool active = (cb0 * 32 < p.N) && (rbw < p.nrb);
     const int C64 = p.C64, CQ = p.CQ;
 
     const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
@@ -935,23 +935,27 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
     const uint32_t lanep = (uint32_t)((l32 & 3) + ((l32 >> 3) << 2) + (((l32 >> 2) & 1) << 4) + 32 * half);
     int rbs = rb0 + wave;  // row block staged by this wavefront
     rbs = rbs < p.nrb ? rbs : p.nrb - 1;
-    const uint8_t* xq_base = p.xq + (size_t)rbs * C64 * 1024;
     const int cbw = (cb0 * 32 < p.N) ? cb0 : 0;  // wavefronts past the last column read block 0 (unused)
-    const uint8_t* pq_base[2] = {p.pq + (size_t)cbw * C64 * 1024, p.pq + (size_t)(cbw + 1) * C64 * 1024};
-    const uint8_t* pe_base[2] = {p.pe + (size_t)cbw * CQ * 256, p.pe + (size_t)(cbw + 1) * CQ * 256};
-    const uint8_t* xe_base[4];
+    // The streams are read with buffer loads: a wave-uniform descriptor and step offset in scalar registers, the lane offset shared
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    constexpr int RSRC_FLAGS = 0x00020000;
+    auto rsrc = [](const void* base, size_t bytes) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, RSRC_FLAGS); };
+    const __amdgpu_buffer_rsrc_t rs_x = rsrc(p.xq + (size_t)rbs * C64 * 1024, (size_t)C64 * 1024);
+    const __amdgpu_buffer_rsrc_t rs_p[2] = {rsrc(p.pq + (size_t)cbw * C64 * 1024, (size_t)C64 * 1024), rsrc(p.pq + (size_t)(cbw + 1) * C64 * 1024, (size_t)C64 * 1024)};
+    const __amdgpu_buffer_rsrc_t rs_pe[2] = {rsrc(p.pe + (size_t)cbw * CQ * 256, (size_t)CQ * 256), rsrc(p.pe + (size_t)(cbw + 1) * CQ * 256, (size_t)CQ * 256)};
+    __amdgpu_buffer_rsrc_t rs_xe[NRB];
 #pragma unroll
-    for (int rbi = 0; rbi < 4; ++rbi) {
-        int rb = rb0 + rbi;
+    for (int rbi = 0; rbi < NRB; ++rbi) {
+        int rb = rbw + rbi;
         rb = rb < p.nrb ? rb : p.nrb - 1;
-        xe_base[rbi] = p.xe + (size_t)rb * CQ * 256;
+        rs_xe[rbi] = rsrc(p.xe + (size_t)rb * CQ * 256, (size_t)CQ * 256);
     }
 
     // Steps (and quads of steps) past the end are clamped instead of predicated: the loads stay
     // unconditional, what they fetch is never used.
     auto load_a = [&](v4i& a, int step) {
         const int st = step < C64 ? step : C64 - 1;
-        a = *(const v4i*)(xq_base + (size_t)st * 1024 + lane16);
+        a = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_x, lane16, st * 1024, 0));
     };
     auto store_a = [&](const v4i& a, int buf) {
         const v8i e = mxi_expand8(a);
@@ -963,20 +967,20 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
     auto load_b = [&](BStage& b, int step) {
         const int st = step < C64 ? step : C64 - 1;
 #pragma unroll
-        for (int cbi = 0; cbi < 2; ++cbi) b.v[cbi] = *(const v4i*)(pq_base[cbi] + (size_t)st * 1024 + lanep * 16u);
+        for (int cbi = 0; cbi < 2; ++cbi) b.v[cbi] = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_p[cbi], lanep * 16u, st * 1024, 0));
     };
-    struct Scales { int a[4]; int b[2]; };
+    struct Scales { int a[NRB]; int b[2]; };
     auto load_s = [&](Scales& sc, int quad) {
         const int q = quad < CQ ? quad : CQ - 1;
 #pragma unroll
-        for (int rbi = 0; rbi < 4; ++rbi) sc.a[rbi] = *(const int*)(xe_base[rbi] + (size_t)q * 256 + lane4);
+        for (int rbi = 0; rbi < NRB; ++rbi) sc.a[rbi] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_xe[rbi], lane4, q * 256, 0);
 #pragma unroll
-        for (int cbi = 0; cbi < 2; ++cbi) sc.b[cbi] = *(const int*)(pe_base[cbi] + (size_t)q * 256 + lanep * 4u);
+        for (int cbi = 0; cbi < 2; ++cbi) sc.b[cbi] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_pe[cbi], lanep * 4u, q * 256, 0);
     };
 
-    v16f t[4][2];
+    v16f t[NRB][2];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NRB; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -984,38 +988,38 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
 
     v8i bu[2][2];  // expanded weight operands: [step parity][column block]
 
-    // One step = one 64-chunk.  On entry: LDS buffer s&1 holds the activation operands of step s,
-    // bu[s&1] the weight operands of step s, `a`/`b` the packed data of step s+1.  During the step the
-    // data of step s+1 is expanded (activations into the other LDS buffer, weights into bu[(s+1)&1])
-    // and the loads of step s+3 are issued into `a`/`b`.  SEL = s % 4 picks the scale byte.
+    // One step = one 64-chunk.  On entry: LDS buffers s & 3 and (s + 1) & 3 hold the activation operands of steps s and s + 1, af[0] the
+    // first of step s, bu[s & 1] its weight operands, `a` / `b` the packed data of steps s + 2 / s + 1.  During the step the activations
+    // of step s + 2 are expanded into their LDS buffer and the weights of step s + 1 into bu[(s + 1) & 1], and the loads of steps
+    // s + 4 and s + 3 are issued.  Operands are read across the step's end: what the barrier there orders is written and read two steps
+    // apart, so nothing waits for it.  SEL = s % 4 picks the scale byte and the buffer.
+    v8i af[2];
+    auto lds_a = [&](int buf, int rbi) -> v8i {
+        const uint8_t* base = lds + (size_t)((buf * RBT + rw + rbi) * 2048) + lane16;
+        const v4i lo = *(const v4i*)(base);
+        const v4i hi = *(const v4i*)(base + 1024);
+        return v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    };
     auto do_step = [&](auto sel, int s, v4i& a, BStage& b, const Scales& sc) {
         constexpr int SEL = decltype(sel)::value;
         constexpr int PAR = SEL & 1;
-        const int buf = PAR;
-        auto lds_a = [&](int rbi) -> v8i {
-            const uint8_t* base = lds + (size_t)((buf * RBT + rbi) * 2048) + lane16;
-            const v4i lo = *(const v4i*)(base);
-            const v4i hi = *(const v4i*)(base + 1024);
-            return v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        };
-        v8i af[2];
-        af[0] = lds_a(0);
 #pragma unroll
-        for (int rbi = 0; rbi < 4; ++rbi) {
-            if (rbi + 1 < 4) af[(rbi + 1) & 1] = lds_a(rbi + 1);
+        for (int rbi = 0; rbi < NRB; ++rbi) {
+            af[(rbi + 1) & 1] = rbi + 1 < NRB ? lds_a(SEL, rbi + 1) : lds_a((SEL + 1) & 3, 0);
 #pragma unroll
             for (int cbi = 0; cbi < 2; ++cbi)
                 t[rbi][cbi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bu[PAR][cbi], af[rbi & 1], t[rbi][cbi], 0, 0, SEL,
                                                                              sc.b[cbi], SEL, sc.a[rbi]);
             if (rbi == 0) {
-                store_a(a, buf ^ 1);
-                load_a(a, s + 3);
+                store_a(a, (SEL + 2) & 3);
+                load_a(a, s + 4);
             }
             if (rbi == 1) {
 #pragma unroll
                 for (int cbi = 0; cbi < 2; ++cbi) bu[PAR ^ 1][cbi] = mxi_expand8(b.v[cbi]);
                 load_b(b, s + 3);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
     };
@@ -1024,66 +1028,68 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
     BStage b0, b1;
     Scales s0, s1;
     load_a(a0, 0);
+    load_a(a1, 1);
     load_b(b0, 0);
     load_s(s0, 0);
     store_a(a0, 0);
+    store_a(a1, 1);
 #pragma unroll
     for (int cbi = 0; cbi < 2; ++cbi) bu[0][cbi] = mxi_expand8(b0.v[cbi]);
     __builtin_amdgcn_sched_barrier(0);
-    load_a(a1, 1);
     load_b(b1, 1);
     load_a(a0, 2);
     load_b(b0, 2);
+    load_a(a1, 3);
     load_s(s1, 1);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
+    af[0] = lds_a(0, 0);
 
     // steps in groups of eight (two quads of chunks): quad q uses scale set q & 1; step s uses the
-    // register set s & 1 (a1/b1 hold step s+1 on entry to an even step)
+    // register sets a(s & 1) and b((s + 1) & 1)
     int s = 0;
     for (; s + 7 < C64; s += 8) {
-        do_step(std::integral_constant<int, 0>{}, s, a1, b1, s0);
-        do_step(std::integral_constant<int, 1>{}, s + 1, a0, b0, s0);
-        do_step(std::integral_constant<int, 2>{}, s + 2, a1, b1, s0);
-        do_step(std::integral_constant<int, 3>{}, s + 3, a0, b0, s0);
+        do_step(std::integral_constant<int, 0>{}, s, a0, b1, s0);
+        do_step(std::integral_constant<int, 1>{}, s + 1, a1, b0, s0);
+        do_step(std::integral_constant<int, 2>{}, s + 2, a0, b1, s0);
+        do_step(std::integral_constant<int, 3>{}, s + 3, a1, b0, s0);
         load_s(s0, (s >> 2) + 2);
-        do_step(std::integral_constant<int, 0>{}, s + 4, a1, b1, s1);
-        do_step(std::integral_constant<int, 1>{}, s + 5, a0, b0, s1);
-        do_step(std::integral_constant<int, 2>{}, s + 6, a1, b1, s1);
-        do_step(std::integral_constant<int, 3>{}, s + 7, a0, b0, s1);
+        do_step(std::integral_constant<int, 0>{}, s + 4, a0, b1, s1);
+        do_step(std::integral_constant<int, 1>{}, s + 5, a1, b0, s1);
+        do_step(std::integral_constant<int, 2>{}, s + 6, a0, b1, s1);
+        do_step(std::integral_constant<int, 3>{}, s + 7, a1, b0, s1);
         load_s(s1, (s >> 2) + 3);
     }
-    if (s < C64) do_step(std::integral_constant<int, 0>{}, s, a1, b1, s0);
-    if (s + 1 < C64) do_step(std::integral_constant<int, 1>{}, s + 1, a0, b0, s0);
-    if (s + 2 < C64) do_step(std::integral_constant<int, 2>{}, s + 2, a1, b1, s0);
-    if (s + 3 < C64) do_step(std::integral_constant<int, 3>{}, s + 3, a0, b0, s0);
-    if (s + 4 < C64) do_step(std::integral_constant<int, 0>{}, s + 4, a1, b1, s1);
-    if (s + 5 < C64) do_step(std::integral_constant<int, 1>{}, s + 5, a0, b0, s1);
-    if (s + 6 < C64) do_step(std::integral_constant<int, 2>{}, s + 6, a1, b1, s1);
+    if (s < C64) do_step(std::integral_constant<int, 0>{}, s, a0, b1, s0);
+    if (s + 1 < C64) do_step(std::integral_constant<int, 1>{}, s + 1, a1, b0, s0);
+    if (s + 2 < C64) do_step(std::integral_constant<int, 2>{}, s + 2, a0, b1, s0);
+    if (s + 3 < C64) do_step(std::integral_constant<int, 3>{}, s + 3, a1, b0, s0);
+    if (s + 4 < C64) do_step(std::integral_constant<int, 0>{}, s + 4, a0, b1, s1);
+    if (s + 5 < C64) do_step(std::integral_constant<int, 1>{}, s + 5, a1, b0, s1);
+    if (s + 6 < C64) do_step(std::integral_constant<int, 2>{}, s + 6, a0, b1, s1);
 
     if (!active) return;
 
     // ---- rank-r expansion on the bf16 MFMA, accumulated on top of the main product: operands of BD chunks of the rank requested
     // ahead (the registers of the K loop's operands are free; with each chunk's requested at its turn these products took 10500
     // cycles at rank 128, of which the matrix core needs 2048)
-    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-    constexpr int RSRC_FLAGS = 0x00020000, BD = NK16 < 3 ? NK16 : 3;
+    constexpr int BD = NK16 < 3 ? NK16 : 3;
     if constexpr (NK16 > 0) {
         const __amdgpu_buffer_rsrc_t rs_l = __builtin_amdgcn_make_buffer_rsrc((void*)(p.lv + (size_t)cb0 * NK16 * 1024), 0, 2 * NK16 * 1024, RSRC_FLAGS);
-        __amdgpu_buffer_rsrc_t rs_t[4];
+        __amdgpu_buffer_rsrc_t rs_t[NRB];
 #pragma unroll
-        for (int rbi = 0; rbi < 4; ++rbi) {
-            int rb = rb0 + rbi;
+        for (int rbi = 0; rbi < NRB; ++rbi) {
+            int rb = rbw + rbi;
             rb = rb < p.nrb ? rb : p.nrb - 1;
             rs_t[rbi] = __builtin_amdgcn_make_buffer_rsrc((void*)(p.tv + (size_t)rb * NK16 * 1024), 0, NK16 * 1024, RSRC_FLAGS);
         }
-        v8bf lf[BD][2], tf[BD][4];
+        v8bf lf[BD][2], tf[BD][NRB];
         auto load_branch = [&](int ch) {
 #pragma unroll
             for (int cbi = 0; cbi < 2; ++cbi)
                 lf[ch % BD][cbi] = __builtin_bit_cast(v8bf, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_l, lanep * 16u, (cbi * NK16 + ch) * 1024, 0));
 #pragma unroll
-            for (int rbi = 0; rbi < 4; ++rbi)
+            for (int rbi = 0; rbi < NRB; ++rbi)
                 tf[ch % BD][rbi] = __builtin_bit_cast(v8bf, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_t[rbi], lane16, ch * 1024, 0));
         };
 #pragma unroll
@@ -1092,7 +1098,7 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
         for (int ch = 0; ch < NK16; ++ch) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int rbi = 0; rbi < 4; ++rbi)
+            for (int rbi = 0; rbi < NRB; ++rbi)
 #pragma unroll
                 for (int cbi = 0; cbi < 2; ++cbi)
                     t[rbi][cbi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf[ch % BD][cbi], tf[ch % BD][rbi], t[rbi][cbi], 0, 0, 0);
@@ -1111,16 +1117,16 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
     // The stores are buffer stores through a descriptor that ends with the wavefront's 128 bytes of the tile's last valid
     // row (rows past M are out of range and dropped by the hardware): no branch, so
     // the compiler can count the stores and need not wait for them when it waits for an older load.
-    const int rows_valid = p.M - rb0 * 32 < 128 ? p.M - rb0 * 32 : 128;
+    const int rows_valid = p.M - rbw * 32 < NRB * 32 ? p.M - rbw * 32 : NRB * 32;
     const bool have_y = !HO || p.Y;
     const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
-        have_y ? (void*)(p.Y + (size_t)(rb0 * 32) * p.ldy + cb0 * 32) : (void*)p.ho_xq, 0,
+        have_y ? (void*)(p.Y + (size_t)(rbw * 32) * p.ldy + cb0 * 32) : (void*)p.ho_xq, 0,
         have_y ? (int)((rows_valid - 1) * p.ldy * 2 + 128) : 0, RSRC_FLAGS);
     uint32_t yoff = (uint32_t)(rd_row * (int)p.ldy * 2 + rd_seg * 16);
     const uint32_t ystep = (uint32_t)(8 * (int)p.ldy * 2);
     v4i ov[4];
 #pragma unroll
-    for (int rbi = 0; rbi < 4; ++rbi) {
+    for (int rbi = 0; rbi < NRB; ++rbi) {
         uint32_t w[2][8];
 #pragma unroll
         for (int cbi = 0; cbi < 2; ++cbi) {
@@ -1128,14 +1134,14 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
             for (int i = 0; i < 16; i += 2)
                 w[cbi][i >> 1] = __builtin_bit_cast(uint32_t, (bf16x2)__builtin_convertvector(f32x2{t[rbi][cbi][i], t[rbi][cbi][i + 1]}, bf16x2));
             if (DBG) {
-                const int row = (rb0 + rbi) * 32 + l32;
+                const int row = (rbw + rbi) * 32 + l32;
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
                     if (row < p.M && p.dbg_y32) p.dbg_y32[(size_t)row * p.N + (cb0 + cbi) * 32 + 16 * half + i] = t[rbi][cbi][i];
             }
         }
         if constexpr (HO) {
-            if (rb0 + rbi < p.nrb) mxi_handoff_rows(p, w, rb0 + rbi, cb0, lane);
+            if (rbw + rbi < p.nrb) mxi_handoff_rows(p, w, rbw + rbi, cb0, lane);
         }
         if (have_y) {
 #pragma unroll
@@ -1151,6 +1157,28 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
                 yoff += ystep;
             }
         }
+    }
+}
+
+template <int NK16, bool DBG, bool HO = false>
+__global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[mxif::LDS_BYTES];
+    if constexpr (HO) write_tag(p.ho_tag_dst, p.ho_tag);
+    // XCD-aware tile order: workgroup ids are dealt round-robin to the 8 XCDs, each gets one run of tiles
+    // of the panel order; a last column of tiles of at most 128 channels comes last of all: half the work each, these tiles fill the
+    // last generation of the grid.
+    auto xcd_order = [](int i, int n) {
+        const int per = n >> 3, rem = n & 7, xcd = i & 7, loc = i >> 3;
+        return xcd * per + (xcd < rem ? xcd : rem) + loc;
+    };
+    const int wide = (p.N + 127) / 256, n_wide = p.tilesM * wide, b = (int)blockIdx.x;
+    if (b < n_wide) {
+        int tile_m, tile_n;
+        panel_tile(xcd_order(b, n_wide), p.tilesM, wide, p.panel < wide ? p.panel : wide, tile_m, tile_n);
+        mxi_fwd_tile<NK16, DBG, HO, 4>(p, lds, tile_m * mxif::RBT, tile_n);
+    } else {
+        mxi_fwd_tile<NK16, DBG, HO, 2>(p, lds, xcd_order(b - n_wide, p.tilesM) * mxif::RBT, wide);
     }
 }
 
