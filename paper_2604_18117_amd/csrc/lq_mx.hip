@@ -956,7 +956,7 @@ constexpr int EPI_ROW = 136, EPI_WAVE = 32 * EPI_ROW;
 constexpr int NBUF = 4;                          // LDS buffers of the activation stream (one stage each)
 constexpr int LDS_MAIN = NBUF * 2 * RBT * 1024;  // [buffer][chunk in stage][row block][lane][16 B]
 constexpr int LDS_BYTES = LDS_MAIN > 4 * EPI_WAVE ? LDS_MAIN : 4 * EPI_WAVE;
-constexpr int LDS_TOTAL = LDS_BYTES + RBT * 32 * 4 + WN * 64 * 4;
+constexpr int LDS_TOTAL = LDS_BYTES + WN * 64 * 4;
 }  // namespace mxf
 
 // One output tile: row blocks rb0 .. rb0 + NRB - 1 (NRB = 4: a whole 128-row tile; 2: a half tile of the grid's last,
@@ -965,12 +965,7 @@ template <int NK, bool DBG, bool BLK, int BFMT, int NRB>
 __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, const int rb0, const int tile_n)
 {
     using namespace mxf;
-    // + the tile's 128 per-token scales of the fp32-scaled branch (read back by every wavefront in the epilogue: an LDS
-    // broadcast read instead of sixteen 1 KB vector-memory loads per wavefront whose lanes all fetch the same 16 bytes)
-    // ... and the tile's 256 per-channel scales of that branch; both are small loads whose round trip would otherwise
-    // open the epilogue
-    float* lds_st = (float*)(lds + LDS_BYTES);
-    float* lds_sl = lds_st + RBT * 32;
+    float* lds_sl = (float*)(lds + LDS_BYTES);  // + the tile's 256 per-channel scales of the fp32-scaled branch
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1099,9 +1094,6 @@ __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, 
         AStage x0, x1;
         load_a(x0, 0);
         load_a(x1, 1);
-        if constexpr (!BLK && NK > 0) {
-            if (lane < 32) lds_st[wave * 32 + lane] = p.st[rbs * 32 + lane];
-        }
         store_a(x0, 0);
         store_a(x1, 1);
         load_a(x0, 2);
@@ -1125,10 +1117,6 @@ __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, 
     load_a(a1, 1);
     load_b(b0, 0);
     load_s(s0, 0);
-    if constexpr (!BLK && NK > 0) {
-        if (lane < 32) lds_st[wave * 32 + lane] = p.st[rbs * 32 + lane];
-        lds_sl[wave * 64 + lane] = p.sl[cbw * 32 + lane];
-    }
     store_a(a0, 0);
     store_a(a1, 1);
     __builtin_amdgcn_sched_barrier(0);
@@ -1161,6 +1149,17 @@ __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, 
     if constexpr (EARLY) {
         load_lf();
         load_tq(0);
+    }
+    // ... and, last, the branch's scales: of this lane's tokens, and of the wavefront's channel `lane`
+    float stl[NRB], sl_lane = 0.f;
+    if constexpr (!BLK && NK > 0) {
+#pragma unroll
+        for (int rbi = 0; rbi < NRB; ++rbi) {
+            int rb = rb0 + rbi;
+            rb = rb < p.nrb ? rb : p.nrb - 1;
+            stl[rbi] = p.st[rb * 32 + l32];
+        }
+        sl_lane = p.sl[cbw * 32 + lane];
     }
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
@@ -1221,6 +1220,7 @@ __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, 
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     uint8_t* stage = lds + wave * EPI_WAVE;
+    if constexpr (!BLK && NK > 0) lds_sl[wave * 64 + lane] = sl_lane;  // (read by this wavefront only)
     v4f slv[2][4];  // channel scales of the branch, in register order
 #pragma unroll
     for (int cbi = 0; cbi < 2; ++cbi) {
@@ -1266,7 +1266,6 @@ __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, 
                 a2[cbi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(lf[cbi][kk], tf[TQ_ALL ? rbi : 0][kk], a2[cbi], 0, 0, 0, 0, 0, 0);
         }
         if (!TQ_ALL && rbi + 1 < NRB) load_tq(rbi + 1);
-        const float stl = (!BLK && NK > 0) ? lds_st[rbi * 32 + l32] : 0.f;  // this lane's token
         float y[2][16];
 #pragma unroll
         for (int cbi = 0; cbi < 2; ++cbi)
@@ -1279,7 +1278,7 @@ __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, 
                 } else {
                     // two vector instructions per output: the scaled branch term enters through a fused multiply-add
                     // (the fp32 result is compared against a sum rounded once, within an accumulation bound)
-                    y[cbi][i] = __builtin_fmaf(__fmul_rn(a2[cbi][i], stl), slv[cbi][i >> 2][i & 3], t[rbi][cbi][i]);
+                    y[cbi][i] = __builtin_fmaf(__fmul_rn(a2[cbi][i], stl[rbi]), slv[cbi][i >> 2][i & 3], t[rbi][cbi][i]);
                 }
             }
 #pragma unroll
