@@ -231,8 +231,8 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
         const uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
         a = __uint_as_float(mm << 16);
     }
-    a = fmaxf(a, __shfl_xor(a, 16, 64));
-    a = fmaxf(a, __shfl_xor(a, 32, 64));
+    a = max_xor16(a);
+    a = max_xor32(a);
     if (kq == 0) s_amax[wave][r16] = a;
     __syncthreads();
 #pragma unroll
@@ -271,8 +271,8 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) ac = fmaxf(ac, fabsf(ch.get(i)));
             }
-            ac = fmaxf(ac, __shfl_xor(ac, 16, 64));
-            ac = fmaxf(ac, __shfl_xor(ac, 32, 64));
+            ac = max_xor16(ac);
+            ac = max_xor32(ac);
             const uint32_t bits = sint4_scale(ac, &inv4);
             if (kq == 0) {
                 p.sxg[sxg_index(row, c, p.tiles128)] = bits;
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
         }
         {
             // Main codes: x * inv rounded to the nearest integer by the FP6 converter (f6_codes16).  Branch codes:
-            // low bytes of x*invb + 1.5*2^23, gathered with byte permutes (bf16 source) or shifts.
+            // low bytes of x*invb + 1.5*2^23, gathered with byte permutes.
             float um[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -293,24 +293,16 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
             }
             f6_codes16(um, pk);
         }
-        if constexpr (BF16) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t tb[8];
+        for (int h = 0; h < 2; ++h) {
+            uint32_t tb[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) tb[e] = rne_bits(__fmul_rn(ch.get(8 * h + e), invb));
+            for (int e = 0; e < 8; ++e) tb[e] = rne_bits(__fmul_rn(ch.get(8 * h + e), invb));
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const uint32_t p01 = __builtin_amdgcn_perm(tb[4 * q + 1], tb[4 * q], 0x0c0c0400u);
-                    const uint32_t p23 = __builtin_amdgcn_perm(tb[4 * q + 3], tb[4 * q + 2], 0x0c0c0400u);
-                    xb4[2 * h + q] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const uint32_t b = rne_bits(__fmul_rn(ch.get(i), invb)) & 0xFFu;
-                xb4[i >> 2] |= b << (8 * (i & 3));
+            for (int q = 0; q < 2; ++q) {
+                const uint32_t p01 = __builtin_amdgcn_perm(tb[4 * q + 1], tb[4 * q], 0x0c0c0400u);
+                const uint32_t p23 = __builtin_amdgcn_perm(tb[4 * q + 3], tb[4 * q + 2], 0x0c0c0400u);
+                xb4[2 * h + q] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
             }
         }
         // the lane's 16 codes are dwords 3*(kq&1) .. +2 of the forward lane (row % 32, K half kq/2): an aligned
@@ -385,8 +377,7 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) tmax[i] = fmaxf(tmax[i], __shfl_xor(tmax[i], o, 64));
+        tmax[i] = max_row16(tmax[i]);
     }
     if constexpr (PW > 1) {
         if (r16 == 0) {

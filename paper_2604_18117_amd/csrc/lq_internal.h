@@ -275,6 +275,31 @@ __device__ __forceinline__ void panel_tile(int tile, int tilesM, int tilesN, int
         tile_n = full + (t - tile_m * w);
     }
 }
+// max(a, a of lane ^ 16) and max(a, a of lane ^ 32): the row-swap instructions hand both halves to every lane without the LDS round trip
+// of a shuffle, which each chunk of an activation step would wait for.
+__device__ __forceinline__ float max_xor16(float a)
+{
+    const auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+    return fmaxf(__uint_as_float(v[0]), __uint_as_float(v[1]));
+}
+__device__ __forceinline__ float max_xor32(float a)
+{
+    const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+    return fmaxf(__uint_as_float(v[0]), __uint_as_float(v[1]));
+}
+// maximum over each row of 16 lanes, in all of them, on the data-parallel-primitive path
+template <int CTRL>
+__device__ __forceinline__ float max_dpp(float v)
+{
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true)));
+}
+__device__ __forceinline__ float max_row16(float v)
+{
+    v = max_dpp<0xB1>(v);       // quad_perm [1,0,3,2]
+    v = max_dpp<0x4E>(v);       // quad_perm [2,3,0,1]
+    v = max_dpp<0x141>(v);      // row_half_mirror
+    return max_dpp<0x140>(v);   // row_mirror
+}
 __device__ __forceinline__ uint32_t nib_lo(uint32_t p) { return p & 0x87878787u; }
 __device__ __forceinline__ uint32_t nib_hi(uint32_t p)
 {

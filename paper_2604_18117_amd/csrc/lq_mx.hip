@@ -485,8 +485,8 @@ __global__ __launch_bounds__(256) void mx_act_kernel(MxActParams p)
             a = fmaxf(a, a16[ci]);
         }
     }
-    a = fmaxf(a, __shfl_xor(a, 16, 64));
-    a = fmaxf(a, __shfl_xor(a, 32, 64));
+    a = max_xor16(a);
+    a = max_xor32(a);
     if (kq == 0) s_amax[wave][r16] = a;
     __syncthreads();
     a = fmaxf(fmaxf(s_amax[0][r16], s_amax[1][r16]), fmaxf(s_amax[2][r16], s_amax[3][r16]));
@@ -505,7 +505,7 @@ __global__ __launch_bounds__(256) void mx_act_kernel(MxActParams p)
     // one 64-chunk: MXFP4 codes and block scales, FP8 branch codes, skinny contraction (am: amax of the lane's 16 values)
     auto code_chunk = [&](const MxChunk<BF16>& ch, const int c, const float am, const int bslot) {
         // MXFP4: block of 32 = this lane's 16 values and its neighbour's (kq ^ 1)
-        const float ab = fmaxf(am, __shfl_xor(am, 16, 64));
+        const float ab = max_xor16(am);
         const uint32_t E = e8m0_of(ab);
         const float sc = e8m0_value(E);
         uint32_t pk[2] = {0u, 0u};
@@ -590,8 +590,7 @@ __global__ __launch_bounds__(256) void mx_act_kernel(MxActParams p)
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) tmax[i] = fmaxf(tmax[i], __shfl_xor(tmax[i], o, 64));
+        tmax[i] = max_row16(tmax[i]);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -768,7 +767,7 @@ __global__ __launch_bounds__(256) void mxb_act_kernel(MxbActParams p)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(xc.get(i)));
                 }
-                const float ab = fmaxf(m, __shfl_xor(m, 16, 64));  // amax of the 32-block (lanes q, q^1)
+                const float ab = max_xor16(m);  // amax of the 32-block (lanes q, q^1)
                 // main codes: MXFP4
                 const uint32_t E4 = e8m0_of(ab);
                 const float sc = e8m0_value(E4);
@@ -798,7 +797,10 @@ __global__ __launch_bounds__(256) void mxb_act_kernel(MxbActParams p)
             if (NJB > 0) {
                 // lane q knows blocks (q>>1) [first half] and 2+(q>>1) [second half]; it must supply block q
                 const uint32_t send = (q == 1) ? Eh[1] : Eh[0];
-                const uint32_t recv = (uint32_t)__shfl_xor((int)send, 48, 64);
+                const auto h32 = __builtin_amdgcn_permlane32_swap(send, send, false, false);  // the value of lane ^ 48, without the LDS
+                const uint32_t o32 = q < 2 ? h32[1] : h32[0];
+                const auto h16 = __builtin_amdgcn_permlane16_swap(o32, o32, false, false);
+                const uint32_t recv = (q & 1) ? h16[0] : h16[1];
                 const int sa = (int)((q == 0) ? Eh[0] : (q == 3) ? Eh[1] : recv);
                 const v8i a8 = {(int)x8[0], (int)x8[1], (int)x8[2], (int)x8[3], (int)x8[4], (int)x8[5], (int)x8[6], (int)x8[7]};
 #pragma unroll
@@ -851,8 +853,7 @@ __global__ __launch_bounds__(256) void mxb_act_kernel(MxbActParams p)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float tm = fmaxf(fabsf(T[0][i]), fabsf(T[1][i]));
-#pragma unroll
-            for (int o = 8; o >= 1; o >>= 1) tm = fmaxf(tm, __shfl_xor(tm, o, 64));
+            tm = max_row16(tm);
             const int grow = blockIdx.x * 16 + 4 * q + i;
             const uint32_t E = e8m0_of_fp8(tm);
             const float inv = e8m0_inverse(E);

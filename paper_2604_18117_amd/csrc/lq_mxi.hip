@@ -473,7 +473,7 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(ch.get(i)));
                 }
-                const float ab = fmaxf(m, __shfl_xor(m, 16, 64));  // block of 32 = lanes kq, kq ^ 1
+                const float ab = max_xor16(m);  // block of 32 = lanes kq, kq ^ 1
                 field = exp_field(ab);
                 // ---- main codes: MXINT4.  code = min(rne(|x| * 2^(2-s)), 7), sign kept apart
                 const float inv4 = field >= 2u ? __uint_as_float((256u - field) << 23) : 0.0f;  // 2^(2-s)
@@ -639,8 +639,7 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float tm = fmaxf(fabsf(T[0][i]), fabsf(T[1][i]));
-#pragma unroll
-                for (int o = 8; o >= 1; o >>= 1) tm = fmaxf(tm, __shfl_xor(tm, o, 64));
+            tm = max_row16(tm);
                 const int grow = rbase + 4 * kq + i;
                 const uint32_t field = exp_field(tm);
                 if (r16 == 0) p.te[(size_t)grow * BR + bb] = (uint8_t)field;
