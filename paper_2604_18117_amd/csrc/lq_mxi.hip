@@ -1356,13 +1356,19 @@ static void mxi_fwd_launch(const MxiFwdParams& p, hipStream_t s)
 {
     // Small layers, by the number T of 32 x 32 tiles (the device holds 2048 wavefronts of these kernels): one tile to a
     // wavefront, larger ones as the L2 traffic of the operands (2, 1.5 and 1 KB per tile and 64-chunk) begins to count, the
-    // 128 x 256 tiles once they occupy enough of the chip.  us, 1 x 1 / 2 x 1 / 2 x 2 / 128 x 256:
-    //   T =  108 (   2 x 1152 -> 3456): 4.0 / 5.0 / 6.8 / 10.6        T = 3360 ( 512 x 2240 -> 6720): 16.9 / 13.2 / 13.0 / 18.8
-    //   T =  144 ( 128 x 4608 -> 1152): 8.9 / 13.3 / 19.1 / 29.4      T = 5076 (1500 x 1152 -> 3456): 14.8 / 12.9 / 11.6 / 12.7
-    //   T = 1152 (1024 x 4608 -> 1152): 13.7 / 15.1 / 20.3 / 30.1     T = 6720 (1024 x 2240 -> 6720): 28.2 / 23.1 / 18.8 / 20.8
-    //   T = 1728 ( 512 x 1152 -> 3456): 6.9 / 6.3 / 7.8 / 11.3        T = 13440 (2048 x 2240 -> 6720): 52.8 / 41.1 / 33.2 / 29.7
-    const int64_t T = (int64_t)p.nrb * (p.N / 32);
-    if (T <= 7000) {
+    // 128 x 256 tiles once they occupy enough of the chip.  us, 1 x 1 / 2 x 1 / 2 x 2:
+    //   T =  108 (   2 x 1152 -> 3456): 4.0 / 5.0 / 6.8               T = 1728 ( 512 x 1152 -> 3456):  6.9 /  6.3 /  7.8
+    //   T =  144 ( 128 x 4608 -> 1152): 8.9 / 13.3 / 19.1             T = 3360 ( 512 x 2240 -> 6720): 16.9 / 13.2 / 13.0
+    //   T = 1152 (1024 x 4608 -> 1152): 13.7 / 15.1 / 20.3            T = 5076 (1500 x 1152 -> 3456): 14.8 / 12.9 / 11.6
+    // 2 x 2 / 128 x 256:
+    //   T = 3456 (1024 x 1152 -> 3456):  9.0 / 11.3                   T = 5076 (1500 x 1152 -> 3456): 12.0 / 12.0
+    //   T = 4320 (1280 x 1152 -> 3456): 11.3 / 11.8                   T = 5652 (5000 x 1152 -> 1152): 11.7 / 11.5
+    //   T = 4620 ( 700 x 2240 -> 6720): 16.7 / 17.1                   T = 6768 (6000 x 4608 -> 1152): 31.6 / 30.0
+    // Up to 12 chunks of K the large tiles' prologue weighs more (T = 6144, 8192 x 512 -> 768: 7.6 / 8.3; T = 6912, 1700 x 768 ->
+    // 4096: 10.1 / 10.7); with the hand-off, whose codes they form in registers, they are ahead earlier (T = 3168, 700 x 1152 -> 4608: 10.8 /
+    // 14.0; T = 4104, 1200 x 1152 -> 3456: 13.7 / 13.5; T = 5652, 5000 x 256 -> 1152: 10.2 / 8.9).
+    const int64_t T = (int64_t)p.nrb * (p.N / 32), line = p.ho_xq ? 4000 : p.C64 <= 12 ? 7000 : 5000;
+    if (T <= line) {
         const int rbt = T <= 1400 ? 1 : 2, cbt = T <= 3600 ? 1 : 2;
         if (p.ho_xq) mxi_fwd_small_launch<NK16, false, true>(p, rbt, cbt, s);
         else if (p.dbg_y32) mxi_fwd_small_launch<NK16, true, false>(p, rbt, cbt, s);

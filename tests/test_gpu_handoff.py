@@ -82,6 +82,12 @@ def test_handoff_equals_the_two_call_path(oracle, M, K1, N1, N2, r1, r2, bw, wit
     _run(oracle, M, K1, N1, N2, r1, r2, bw, 40 + M, with_y)
 
 
+@pytest.mark.parametrize("M,K1,N1,with_y", [(2085, 128, 2112, False), (1999, 192, 2176, True), (2021, 64, 2240, True)])
+def test_handoff_of_large_layers(oracle, M, K1, N1, with_y):
+    """Layers past the small form: codes formed in registers, the last column of 64 and 128 channels as 2 x 2 wavefronts."""
+    _run(oracle, M, K1, N1, 64, 32, 32, 8, M, with_y)
+
+
 def test_handoff_degenerate_blocks(oracle):
     """All-zero tokens (scale byte 0, codes 0) and a producer with an all-zero channel block."""
     from paper_2604_18117_amd import binding as lq

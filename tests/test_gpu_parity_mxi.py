@@ -211,6 +211,14 @@ def test_forward_forms(oracle, M, K, N, r, bw):
     _compare(oracle, layer, X, W, L, R, rows=rows)
 
 
+@pytest.mark.parametrize("M,K,N,r,bw", [(3845, 128, 1856, 32, 8), (3901, 192, 1920, 64, 4), (3840, 320, 1984, 96, 8), (3009, 832, 1728, 128, 8)])
+def test_last_column_of_large_layers(oracle, M, K, N, r, bw):
+    """More tiles than the small form takes, a last column of 64, 128 or 192 channels (the first two as 2 x 2 wavefronts) and a last row of
+    tiles of one to four row blocks."""
+    layer = wl.Layer("t", M, K, N, r, "mxi", 32, bw, 8, "bf16", seed=M)
+    _compare(oracle, layer, *wl.make_inputs(layer))
+
+
 def test_rows_as_long_as_the_contract_allows():
     """K = 2^24 at rank 128: the dequantised R is 4 GB.  Everything but the last chunk of X and R is zero, so the intermediate
     is that of the last chunk alone: the codes of a layer with K = 64."""
