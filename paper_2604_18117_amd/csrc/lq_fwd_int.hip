@@ -830,9 +830,7 @@ __global__ __launch_bounds__(64, 2) void fwd_int_small_kernel(FwdParams p)
         for (int q = 0; q < 32 / RP; ++q) {
             const int row = q * RP + lane / LR, seg = (lane % LR) * 16;
             const v4i o = *(const v4i*)(stage + row * ROW + seg);
-            // (64 x 64 tiles: an output of 3.4 MB and more, stored past the L2 like the large tiles' -- 1024 x 1152 -> 3456 10.0 / 9.3 us, with the
-            // next layer's activation step 19.6 / 19.2, 4096 x 1152 -> 1152 with it 19.1 / 18.3)
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, o), rs_y, (i * 32 + row) * (int)p.ldy * 2 + seg, 0, NRB + NCB == 4 ? STORE_NT : 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, o), rs_y, (i * 32 + row) * (int)p.ldy * 2 + seg, 0, 0);
         }
     }
 }
