@@ -549,10 +549,10 @@ __device__ __forceinline__ void fwd_tile(const FwdParams& p, uint8_t* lds, const
     // rows past M are out of range and dropped by the hardware, so the stores need no branch -- and only stores the
     // compiler can count let it wait for a load issued before them without waiting for the stores themselves (the
     // vector-memory counter retires in order).  Measured: 2240 -> 6720 layer 110 -> 107 us.
-    // They are non-temporal: the output of a layer that fills the grid (9 MB and more) does not fit the XCDs' L2 and would only push
-    // the weight codes out that every row of tiles reads again (activation step and forward, us without / with: 8192 x 1152 -> 3456
-    // 44.1 / 42.1, 8192 x 4608 -> 1152 72.2 / 68.4, 8192 x 2240 -> 11200 195.1 / 188.8; a reader right behind is no slower off:
-    // 8192 x 1152 -> 3456 and the next layer's activation step 56.1 / 55.2, 2048 rows 25.5 / 24.2).
+    // They go through the caches.  Non-temporal, activation step and forward alone take 1 to 10 % less, but the time moves to the kernel that
+    // reads Y: with X written by the kernel before and the next layer's activation step behind (us, cached / non-temporal) 8192 x 2240 -> 11200
+    // 290.1 / 306.2, 8192 x 2240 -> 6720 188.0 / 195.8, 8192 x 1152 -> 4608 93.0 / 97.1; only Y of 10 to 20 MB gain, 1 to 2 %
+    // (2048 x 1152 -> 3456 38.7 / 37.6), and no more than 1 with an elementwise reader.
     const int rows_valid = p.M - rbw * 32 < NRB * 32 ? p.M - rbw * 32 : NRB * 32;
     const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(p.Y + (size_t)(rbw * 32) * p.ldy + cb0 * 32), 0, (int)((rows_valid - 1) * p.ldy * 2 + 128), RSRC_FLAGS);
@@ -609,7 +609,7 @@ __device__ __forceinline__ void fwd_tile(const FwdParams& p, uint8_t* lds, const
         for (int q = 0; q < 4; ++q) ov[q] = *(const v4i*)(stage + (q * 8 + rd_row) * EPI_ROW + rd_seg * 16);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, ov[q]), rs_y, yoff, 0, STORE_NT);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, ov[q]), rs_y, yoff, 0, 0);
             yoff += ystep;
         }
     }

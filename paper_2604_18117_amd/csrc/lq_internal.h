@@ -253,8 +253,6 @@ hipError_t allow_lds(int bytes)
     return e;
 }
 
-constexpr int STORE_NT = 2;  // cache policy of a buffer store: non-temporal
-
 // ---- device helpers ----------------------------------------------------------------------
 #if defined(__HIPCC__)
 // header of an activation blob, written by the first workgroup of the kernel that fills the blob

@@ -1246,9 +1246,10 @@ __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, 
     // The stores are buffer stores through a descriptor that ends with the wavefront's 128 bytes of the tile's last valid
     // row: rows past M are out of range and dropped by the hardware, so the stores need no branch -- and only stores the
     // compiler can count let it wait for a load issued before them without waiting for the stores themselves.
-    // Non-temporal: the output does not fit the XCDs' L2 and would push out the weight codes that every row of tiles reads again
-    // (us without / with: 16384 x 1152 -> 3456 58.2 / 43.5, 2048 x 1152 -> 3456 10.9 / 9.5; followed by the next layer's
-    // activation step, which reads it, 102.6 / 103.6 and 24.5 / 23.4).
+    // They go through the caches: non-temporal stores make activation step and forward alone 1 to 15 % shorter and the kernel that reads Y
+    // longer by as much or more (X written by the kernel before, the next layer's activation step behind, us, cached / non-temporal: 8192 x 2240
+    // -> 11200 219.9 / 235.3, 16384 x 1152 -> 4608 146.1 / 150.2, 16384 x 1152 -> 3456 125.7 / 124.9, 2048 x 1152 -> 3456 37.1 / 36.0; with an
+    // FP6 branch up to 10 % longer).
     const int rows_valid = p.M - rb0 * 32 < NRB * 32 ? p.M - rb0 * 32 : NRB * 32;
     const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(p.Y + (size_t)(rb0 * 32) * p.ldy + cb0 * 32), 0, (int)((rows_valid - 1) * p.ldy * 2 + 128), RSRC_FLAGS);
@@ -1307,7 +1308,7 @@ __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, 
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, ov[q]), rs_y, yoff, 0, STORE_NT);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, ov[q]), rs_y, yoff, 0, 0);
             yoff += ystep;
         }
     }
