@@ -1361,13 +1361,21 @@ static void mxi_fwd_launch(const MxiFwdParams& p, hipStream_t s)
     //   T =  144 ( 128 x 4608 -> 1152): 8.9 / 13.3 / 19.1             T = 3360 ( 512 x 2240 -> 6720): 16.9 / 13.2 / 13.0
     //   T = 1152 (1024 x 4608 -> 1152): 13.7 / 15.1 / 20.3            T = 5076 (1500 x 1152 -> 3456): 14.8 / 12.9 / 11.6
     // 2 x 2 / 128 x 256:
-    //   T = 3456 (1024 x 1152 -> 3456):  9.0 / 11.3                   T = 5076 (1500 x 1152 -> 3456): 12.0 / 12.0
-    //   T = 4320 (1280 x 1152 -> 3456): 11.3 / 11.8                   T = 5652 (5000 x 1152 -> 1152): 11.7 / 11.5
-    //   T = 4620 ( 700 x 2240 -> 6720): 16.7 / 17.1                   T = 6768 (6000 x 4608 -> 1152): 31.6 / 30.0
-    // Up to 12 chunks of K the large tiles' prologue weighs more (T = 6144, 8192 x 512 -> 768: 7.6 / 8.3; T = 6912, 1700 x 768 ->
-    // 4096: 10.1 / 10.7); with the hand-off, whose codes they form in registers, they are ahead earlier (T = 3168, 700 x 1152 -> 4608: 10.8 /
-    // 14.0; T = 4104, 1200 x 1152 -> 3456: 13.7 / 13.5; T = 5652, 5000 x 256 -> 1152: 10.2 / 8.9).
-    const int64_t T = (int64_t)p.nrb * (p.N / 32), line = p.ho_xq ? 4000 : p.C64 <= 12 ? 7000 : 5000;
+    //   T = 5040 (4476 x  896 -> 1152): 10.0 / 10.7                   T = 5076 (1500 x 1152 -> 3456): 12.0 / 12.0
+    //   T = 5696 (11389 x 1024 -> 512): 10.9 / 11.5                   T = 6516 (5762 x  896 -> 1152): 11.5 / 11.1
+    //   T = 5400 (4770 x 2240 -> 1152): 17.7 / 17.3                   T = 6768 (6000 x 4608 -> 1152): 31.6 / 30.0
+    // 12 chunks of K and fewer: the large tiles' prologue weighs more (T = 6144, 8192 x 512 -> 768: 7.6 / 8.3; T = 6912, 1700 x 768 ->
+    // 4096: 10.1 / 10.7).  More large tiles than compute units (the tiles of a layer of 128 channels are half-sized): some units get a
+    // second one, and the call takes a generation more (T = 6396, 17052 x 832 -> 384: 11.4 / 12.6; T = 6990, 37274 x 2240 -> 192: 20.2 /
+    // 28.3; T = 5150, 82394 x 1152 -> 64: 16.5 / 21.4).
+    // With the hand-off, whose codes they form in registers, the large tiles are ahead earlier (T = 3168, 700 x 1152 -> 4608: 10.8 / 14.0; T = 4104,
+    // 1200 x 1152 -> 3456: 13.7 / 13.5; T = 4596, 12238 x 1152 -> 384: 15.5 / 13.8), also past one per compute unit in short rows (T = 5800, 18532
+    // x 896 -> 320: 15.6 / 15.0; 18545 x 2240 -> 320: 21.3 / 23.4), earlier or later by how many wavefronts their last column leaves without
+    // channels (T = 6348, 33847 x 512 -> 192: 12.9 / 14.9; T = 4600, 73590 x 896 -> 64: 16.3 / 17.1, 73577 x 64 -> 64: 11.1 / 9.2).
+    const int64_t T = (int64_t)p.nrb * (p.N / 32);
+    const bool over = (p.N == 128 ? (p.tilesM + 1) / 2 : p.tilesM * p.tilesN) > compute_units();
+    const int over_ho = (p.N & 255) == 192 ? 1 : p.N < 256 ? 12 : 20;  // with the hand-off: chunks from which a second generation counts
+    const int line = p.ho_xq ? (over && p.C64 >= over_ho ? 7000 : 4000) : over || p.C64 <= 12 ? 7000 : p.C64 <= 24 ? 6500 : 5000;
     if (T <= line) {
         const int rbt = T <= 1400 ? 1 : 2, cbt = T <= 3600 ? 1 : 2;
         if (p.ho_xq) mxi_fwd_small_launch<NK16, false, true>(p, rbt, cbt, s);

@@ -77,6 +77,9 @@ def _run(oracle, M, K1, N1, N2, r1, r2, bw, seed, with_y):
     (1700, 320, 2240, 64, 32, 64, 4, True),     # ... and its 64 x 64 tiles
     (6145, 64, 320, 64, 32, 64, 8, False),      # the step from codes on 32-row workgroups
     (12290, 64, 576, 64, 32, 128, 4, False),    # ... and on 64-row workgroups, the last one partly past M
+    (16630, 1280, 320, 64, 32, 32, 4, True),    # small tiles where the large ones number more than the compute units: long rows,
+    (33850, 64, 192, 64, 32, 32, 8, False),     # ... a last column with one wavefront idle,
+    (73590, 768, 64, 64, 32, 32, 8, False),     # ... and two of four
 ])
 def test_handoff_equals_the_two_call_path(oracle, M, K1, N1, N2, r1, r2, bw, with_y):
     _run(oracle, M, K1, N1, N2, r1, r2, bw, 40 + M, with_y)

@@ -200,7 +200,8 @@ def test_activation_row_forms(oracle, M, K, r, bw, xd):
     _compare(oracle, layer, X, W, L, R, rows=rows)
 
 
-# Forms of the forward by the number of 32 x 32 tiles: 1 x 1 to 1400, 2 x 1 to 3600, 2 x 2 to 7000, 128 x 256 tiles above; ragged M, an odd
+# Forms of the forward by the number of 32 x 32 tiles: 1 x 1 to 1400, 2 x 1 to 3600, 2 x 2 to a line between 4000 and 7000 that depends on the
+# rows' length, the hand-off and the number of large tiles, 128 x 256 tiles above; ragged M, an odd
 # number of row blocks, fewer and more quads of chunks than are kept in flight, last quads of one to four chunks.
 @pytest.mark.parametrize("M,K,N,r,bw", [(790, 1152, 1664, 32, 8), (397, 704, 4032, 64, 4), (1130, 320, 2176, 128, 8), (1700, 448, 2176, 96, 4),
                                         (2300, 64, 2112, 64, 8), (3300, 576, 2176, 32, 8), (401, 2240, 4032, 0, 8)])
@@ -296,9 +297,11 @@ def test_a_token_does_not_depend_on_its_batch(fam, g, bw, ag, r):
 
 
 # Layers narrow and wide, long and short: each order of the small forms' tiles, and the large tiles beside them (by the number of tiles, at
-# three and four chunks, above 80 MB of X codes)
+# three and four chunks, above 80 MB of X codes, more large tiles than compute units)
 @pytest.mark.parametrize("fam,g,bw,ag,K,N,ms", [("mx", 32, 8, 32, 4608, 64, (33, 700, 20011, 36001)), ("mxb", 32, 6, 32, 576, 192, (40, 9001, 19000)),
-                                                ("mxi", 32, 8, 32, 1152, 192, (65, 5000, 37333, 38000)), ("int", 128, 4, 0, 256, 1152, (70, 900, 2939, 4000, 4700)),
+                                                ("mxi", 32, 8, 32, 1152, 192, (65, 5000, 37333, 38000)), ("mxi", 32, 8, 32, 896, 320, (40, 16600, 22400, 22401)),
+                                                ("mxi", 32, 4, 32, 896, 1152, (33, 5700, 5762)), ("mxi", 32, 8, 32, 2240, 128, (65, 39000, 40800)),
+                                                ("mxi", 32, 8, 32, 64, 64, (33, 112000, 112100)), ("int", 128, 4, 0, 256, 1152, (70, 900, 2939, 4000, 4700)),
                                                 ("int", 64, 8, 0, 512, 128, (97, 6500, 40000, 41000)), ("int", 64, 6, 64, 192, 4480, (33, 420, 1601, 1700))])
 def test_outputs_do_not_depend_on_the_tiles(fam, g, bw, ag, K, N, ms):
     from paper_2604_18117_amd import binding as lq
