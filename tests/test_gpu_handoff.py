@@ -91,6 +91,13 @@ def test_handoff_of_large_layers(oracle, M, K1, N1, with_y):
     _run(oracle, M, K1, N1, 64, 32, 32, 8, M, with_y)
 
 
+@pytest.mark.parametrize("M,K1,N1,r1,bw,with_y", [(1210, 576, 3456, 128, 4, False), (1243, 704, 3392, 128, 4, True), (1281, 448, 3264, 96, 8, True),
+                                                  (1999, 256, 2176, 0, 8, False), (2021, 384, 2112, 0, 4, True), (32900, 64, 128, 64, 8, True)])
+def test_handoff_of_large_layers_by_rank(oracle, M, K1, N1, r1, bw, with_y):
+    """... at every depth of the branch's operands in flight, without a branch, with one tile column only."""
+    _run(oracle, M, K1, N1, 64, r1, 32, bw, M, with_y)
+
+
 def test_handoff_degenerate_blocks(oracle):
     """All-zero tokens (scale byte 0, codes 0) and a producer with an all-zero channel block."""
     from paper_2604_18117_amd import binding as lq
@@ -112,6 +119,45 @@ def test_handoff_degenerate_blocks(oracle):
     for f in ("xq", "xe", "tq", "te"):
         assert torch.equal(getattr(va, f), getattr(vr, f)), f
     assert not n(va.xq)[:, 32:64].any() and not n(va.xq)[3].any()
+    assert torch.equal(lq.lq_linear_lowrank_fwd(cfg2, pk2, act2, M), lq.lq_linear_lowrank_fwd(cfg2, pk2, act2_ref, M))
+
+
+@pytest.mark.parametrize("M,N1,with_y", [(70, 128, True), (2085, 2112, False), (2085, 2112, True)])
+def test_handoff_degenerate_blocks_of_both_forms(oracle, M, N1, with_y):
+    """All-zero tokens (scale byte 0, codes 0), tokens near both ends of the range, and a producer with an all-zero channel block; in
+    the small form and in the large tiles."""
+    from paper_2604_18117_amd import binding as lq
+    K1, N2, r = 128, 64, 32
+    l1, l2 = _layer("p", M, K1, N1, r, 8, 5), _layer("c", M, N1, N2, r, 8, 6)
+    X, W1, L1, R1 = wl.make_inputs(l1)
+    _, W2, L2, R2 = wl.make_inputs(l2)
+    X[3] = 0.0
+    X[5:15] *= np.float32(2.0 ** -88)     # both ends of the range that block maxima may take
+    X[15:25] *= np.float32(2.0 ** 110)
+    X[30, 1:] = 0.0           # (a token whose outputs are one column of W)
+    X = wl.round_to_bf16(X)
+    W1[32:64] = 0.0
+    L1[32:64] = 0.0           # outputs 32..63 are exactly zero for every token: an all-zero block of the consumer
+    cfg1, pk1 = _pack(lq, l1, W1, L1, R1)
+    cfg2, pk2 = _pack(lq, l2, W2, L2, R2)
+    act1 = lq.lq_quantize_act(cfg1, pk1, wl.to_dev_x(X, "bf16"))
+    Y1 = lq.lq_linear_lowrank_fwd(cfg1, pk1, act1, M)
+    act2_ref = lq.lq_quantize_act(cfg2, pk2, Y1)
+    Yh = torch.full((M, N1), -1, dtype=torch.int16, device="cuda").view(torch.bfloat16) if with_y else None
+    act2, codes = lq.lq_linear_lowrank_fwd_handoff(cfg1, pk1, act1, M, cfg2, Y=Yh)
+    lq.lq_branch_from_codes(cfg2, pk2, codes, M, act2)
+    if with_y:
+        assert torch.equal(Yh, Y1)
+    va, vr = lq.lq_unpack_act(cfg2, act2, M), lq.lq_unpack_act(cfg2, act2_ref, M)
+    for f in ("xq", "xe", "tq", "te"):
+        assert torch.equal(getattr(va, f), getattr(vr, f)), f
+    assert not n(va.xq)[:, 32:64].any() and not n(va.xq)[3].any()
+    ho = oracle.handoff_mxi(bf16_to_bits(Y1), oracle.pack_mxi(W2, L2, R2, 8))
+    assert np.array_equal(n(va.xq), ho.xq) and np.array_equal(n(va.xe), ho.xe)
+    Mp = (M + 31) // 32 * 32
+    cb, off = n(codes[:Mp * N1]).view(np.int8).reshape(Mp, N1)[:M], (Mp * N1 + 255) // 256 * 256
+    cbe = n(codes[off:off + Mp * (N1 // 32)]).reshape(Mp, N1 // 32)[:M]
+    assert np.array_equal(cb, ho.xb) and np.array_equal(cbe, ho.xbe)
     assert torch.equal(lq.lq_linear_lowrank_fwd(cfg2, pk2, act2, M), lq.lq_linear_lowrank_fwd(cfg2, pk2, act2_ref, M))
 
 

@@ -220,6 +220,17 @@ def test_last_column_of_large_layers(oracle, M, K, N, r, bw):
     _compare(oracle, layer, *wl.make_inputs(layer))
 
 
+# The large tiles' loop takes its chunks in groups of eight and every shorter tail by calls of its own: 4, 6 and 7 chunks and 8 + 4, 8 + 6, 8 + 7
+# (the others are in the cases above); rank 0, and layers of which the last column is all there is.
+@pytest.mark.parametrize("M,K,N,r,bw", [(3845, 256, 1856, 0, 8), (3901, 384, 1920, 128, 4), (3841, 448, 1984, 96, 8), (3841, 768, 1984, 32, 8),
+                                        (6989, 896, 960, 0, 8), (6989, 960, 960, 64, 4), (56001, 448, 128, 32, 8), (112100, 64, 64, 128, 4),
+                                        (112100, 256, 64, 0, 8)])
+def test_large_tiles_tails_and_ranks(oracle, M, K, N, r, bw):
+    layer = wl.Layer("t", M, K, N, r, "mxi", 32, bw, 8, "bf16", seed=M + K)
+    rows = np.unique(np.concatenate([np.arange(M - 140, M), np.arange(130), np.arange(0, M, 61)]))
+    _compare(oracle, layer, *wl.make_inputs(layer), rows=rows)
+
+
 def test_rows_as_long_as_the_contract_allows():
     """K = 2^24 at rank 128: the dequantised R is 4 GB.  Everything but the last chunk of X and R is zero, so the intermediate
     is that of the last chunk alone: the codes of a layer with K = 64."""
