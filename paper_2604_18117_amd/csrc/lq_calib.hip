@@ -74,19 +74,6 @@ CalibLayout calib_layout(const Dims& d)
     return cl;
 }
 
-// Maximum over a row of 16 lanes, in each of them, on the vector ALU's data-parallel-primitive path (no LDS traffic).
-template <int CTRL>
-__device__ __forceinline__ float dpp_max(float v)
-{
-    return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true)));
-}
-__device__ __forceinline__ float row16_max(float v)
-{
-    v = dpp_max<0xB1>(v);       // quad_perm [1,0,3,2]
-    v = dpp_max<0x4E>(v);       // quad_perm [2,3,0,1]
-    v = dpp_max<0x141>(v);      // row_half_mirror
-    return dpp_max<0x140>(v);   // row_mirror
-}
 // The value lane N of each row of 16 lanes holds, in all 16.
 template <int N>
 __device__ __forceinline__ float row16_lane(float v)
@@ -250,7 +237,7 @@ __global__ __launch_bounds__(64 * calib_waves(R), calib_waves(R) == 4 && R > 64 
                 float a = 0.f;
 #pragma unroll
                 for (int t = g * GT; t < (g + 1) * GT; ++t) a = fmaxf(a, fabsf(v[t][i]));
-                am[g][i] = row16_max(a);
+                am[g][i] = max_row16(a);
             }
         // INT / SINT4 scales need correctly rounded divisions: the 16 lanes that share a row's maxima share the work, lane
         // 4 g + i dividing for (g, i) and handing the result to the others (two divisions per lane instead of 2 * 4 * NG)
@@ -301,8 +288,9 @@ __global__ __launch_bounds__(64 * calib_waves(R), calib_waves(R) == 4 && R > 64 
             }
         };
         for_constants(finish, std::make_integer_sequence<int, 4 * NG>{});
-        // E is not read again in a step: non-temporal, it leaves W and the gradient parts in the caches (3456 x 1152, rank 32: 21.8 -> 21.1 us
-        // per step, 11200 x 2240 88.5 -> 86.2, 4608 x 1152 rank 128 73.2 -> 71.0)
+        // E is not read again in a step: non-temporal, it leaves W and the gradient parts in the caches (us per step, steps back
+        // to back, cached / non-temporal: 3456 x 1152 rank 32 23.8 / 22.3, rank 64 31.5 / 31.1, 4608 x 1152 rank 128 72.6 / 71.3, 11200 x 2240 rank 32
+        // 77.6 / 75.6, rank 64 138.9 / 134.6)
         if (live) {
 #pragma unroll
             for (int t = 0; t < 4; ++t)

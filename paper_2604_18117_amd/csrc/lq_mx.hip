@@ -1089,7 +1089,7 @@ __device__ __forceinline__ void mx_fwd_tile(const MxFwdParams& p, uint8_t* lds, 
     };
 
     // A wavefront whose columns lie past N (the last tile column of a layer whose width is no multiple of 256) only stages
-    // its row block of the activation codes and the token scales, barrier for barrier with the others: no matrix work, no
+    // its row block of the activation codes, barrier for barrier with the others: no matrix work, no
     // weight or scale loads that would compete with the wavefront it shares a SIMD with.
     if (cb0 * 32 >= p.N) {  // wave-uniform
         AStage x0, x1;

@@ -639,7 +639,7 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float tm = fmaxf(fabsf(T[0][i]), fabsf(T[1][i]));
-            tm = max_row16(tm);
+                tm = max_row16(tm);
                 const int grow = rbase + 4 * kq + i;
                 const uint32_t field = exp_field(tm);
                 if (r16 == 0) p.te[(size_t)grow * BR + bb] = (uint8_t)field;

@@ -81,21 +81,6 @@ RotLayout rot_layout(const Dims& d)
     return rl;
 }
 
-// Maximum over a row of 16 lanes (in each of them), on the data-parallel-primitive path.
-template <int CTRL>
-__device__ __forceinline__ float rot_dpp_max(float v)
-{
-    const int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false);
-    return fmaxf(v, __int_as_float(o));
-}
-__device__ __forceinline__ float rot_max16(float v)
-{
-    v = rot_dpp_max<0xB1>(v);     // quad_perm [1,0,3,2]
-    v = rot_dpp_max<0x4E>(v);     // quad_perm [2,3,0,1]
-    v = rot_dpp_max<0x141>(v);    // row_half_mirror
-    return rot_dpp_max<0x140>(v); // row_mirror
-}
-
 // Q2, the format lq_pack_weights gives L and R (App. A.3).  Row kinds carry one fp32 scale per row: 0 symmetric integers
 // of qmax, 1 FP8 E4M3 (largest magnitude 448).  Block kinds carry an E8M0 scale per 32 values along the row: 2 MXFP8e4,
 // 3 MXFP6e2, 4 MXINT of `bits`.
@@ -299,7 +284,7 @@ __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
 #pragma unroll
                         for (int t = 0; t < T; t += 2) {  // (block kinds have rank >= 32: T is even)
                             const int t1 = t + 1 < T ? t + 1 : t;
-                            const int eb = rot_block_exp(rot_max16(fmaxf(fabsf(z[t][i]), fabsf(z[t1][i]))), p.q);
+                            const int eb = rot_block_exp(max_row16(fmaxf(fabsf(z[t][i]), fabsf(z[t1][i]))), p.q);
                             z[t][i] = rot_err_block(z[t][i], eb, p.q);
                             if (t1 > t) z[t1][i] = rot_err_block(z[t1][i], eb, p.q);
                         }
@@ -307,7 +292,7 @@ __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
                         float m = 0.f, s, inv;
 #pragma unroll
                         for (int t = 0; t < T; ++t) m = fmaxf(m, fabsf(z[t][i]));
-                        rot_scale(rot_max16(m), p.q.top, s, inv);
+                        rot_scale(max_row16(m), p.q.top, s, inv);
 #pragma unroll
                         for (int t = 0; t < T; ++t) z[t][i] = rot_err<QK>(z[t][i], s, inv, p.q.top);
                     }
