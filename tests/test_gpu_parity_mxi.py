@@ -212,7 +212,8 @@ def test_forward_forms(oracle, M, K, N, r, bw):
     _compare(oracle, layer, X, W, L, R, rows=rows)
 
 
-@pytest.mark.parametrize("M,K,N,r,bw", [(3845, 128, 1856, 32, 8), (3901, 192, 1920, 64, 4), (3840, 320, 1984, 96, 8), (3009, 832, 1728, 128, 8)])
+@pytest.mark.parametrize("M,K,N,r,bw", [(3845, 128, 1856, 32, 8), (3901, 192, 1920, 64, 4), (3840, 320, 1984, 96, 8), (3009, 832, 1728, 128, 8),
+                                        (3969, 832, 1728, 128, 8)])
 def test_last_column_of_large_layers(oracle, M, K, N, r, bw):
     """More tiles than the small form takes, a last column of 64, 128 or 192 channels (the first two as 2 x 2 wavefronts) and a last row of
     tiles of one to four row blocks."""
