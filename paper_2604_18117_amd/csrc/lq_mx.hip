@@ -1539,11 +1539,11 @@ static void mx_fwd_launch(const MxFwdParams& p, hipStream_t s)
     // Small layers, by the number T of 32 x 32 tiles (the device holds 2048 wavefronts of these kernels): one tile to a
     // wavefront while that leaves no SIMD with two, larger ones as the L2 traffic of the operands (2, 1.5 and 1 KB per tile and
     // 64-chunk) begins to count, the 128 x 256 tiles once they occupy enough of the chip.  us, 1 x 1 / 2 x 1 / 2 x 2 / 128 x 256:
-    //   T =  108 (   2 x 1152 -> 3456): 3.0 / 3.5 / 4.5 /  7.6        T = 1728 ( 512 x 1152 -> 3456):  6.4 /  5.5 /  5.8 /  8.3
-    //   T =  720 ( 300 x 1152 -> 2304): 4.1 / 4.3 / 4.8 /  7.9        T = 2304 (2048 x 4608 -> 1152): 16.9 / 15.8 / 14.7 / 18.5
-    //   T = 1080 ( 300 x 1152 -> 3456): 5.4 / 4.9 / 5.5 /  8.1        T = 3500 ( 300 x 2240 -> 11200): 16.4 / 12.1 / 10.7 / 12.5
-    //   T =  576 ( 512 x 4608 -> 1152): 6.1 / 7.9 / 9.5 / 17.4        T = 4608 (4096 x 4608 -> 1152): 30.8 / 25.4 / 21.3 / 19.7
-    //                                                               T = 3492 (3100 x 4608 -> 1152): 25.5 / 19.8 / 17.3 / 19.2
+    //   T =  108 (   2 x 1152 -> 3456): 3.0 / 3.5 / 4.5 /  7.5        T = 1728 ( 512 x 1152 -> 3456):  6.4 /  5.5 /  5.8 /  7.8
+    //   T =  720 ( 300 x 1152 -> 2304): 4.1 / 4.3 / 4.8 /  7.6        T = 2304 (2048 x 4608 -> 1152): 16.9 / 15.8 / 14.7 / 17.5
+    //   T = 1080 ( 300 x 1152 -> 3456): 5.4 / 4.9 / 5.5 /  7.8        T = 3500 ( 300 x 2240 -> 11200): 16.4 / 12.1 / 10.7 / 11.7
+    //   T =  576 ( 512 x 4608 -> 1152): 6.1 / 7.9 / 9.5 / 16.9        T = 4608 (4096 x 4608 -> 1152): 30.8 / 25.4 / 21.3 / 18.6
+    //                                                               T = 3492 (3100 x 4608 -> 1152): 25.5 / 19.8 / 17.3 / 18.0
     const int64_t T = (int64_t)p.nrb * (p.N / 32);
     // More than 80 MB of X codes (a narrow layer): a stream over memory, which the large tiles' requests serve as well or better (37243 x
     // 4608 -> 64: 18.7 us against 17.9).

@@ -909,9 +909,9 @@ constexpr int LDS_BYTES = LDS_MAIN > 4 * EPI_WAVE ? LDS_MAIN : 4 * EPI_WAVE;
 // One tile of 128 rows: WN = 4 wavefronts side by side of 128 x 64 outputs each, or, for a last column of tiles of at most 128 channels,
 // 2 x 2 wavefronts of 64 x 64 (side by side two of the four would have no columns).  Bounded by the 8-bit matrix rate inside the K loop
 // (two wavefronts per SIMD keep it busy as long as their loads arrive), by instruction latency around it.  The fences in the loop
-// hold every load two steps ahead of its use: left to itself the compiler sank them to the end of their step and waited for all of
-// them in the next (16384 x 4608 -> 1152 rank 128: 79.6 us, with the fences and the narrow tiles last 66.3; 16384 x 1152 -> 3456 70.4
-// -> 59.4; 16384 x 1152 -> 1152 26.2 -> 22.7; 5000 x 2240 -> 6720 67.6 -> 63.3).
+// hold every load two steps ahead of its use: left to itself the compiler sinks them to the end of their step and waits for all of
+// them in the next (us without the fences / without the narrow tiles / as it is: 16384 x 4608 -> 1152 rank 128 75.7 / 74.5 / 68.4, 16384 x
+// 1152 -> 3456 74.9 / 67.3 / 67.5, 16384 x 1152 -> 1152 25.6 / 25.3 / 23.5, 5000 x 2240 -> 6720 69.5 / 64.9 / 65.2).
 // NK16 = 16-deep chunks of the rank: 0 | 2 | 4 | 6 | 8.  HO: quantized hand-off (Section 4.5): the epilogue also emits
 // the next layer's activation codes from the bf16 values it has just formed; Y itself is optional then.
 template <int NK16, bool DBG, bool HO, int WN>
