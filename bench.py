@@ -247,7 +247,7 @@ def measure_layer(args, layer, np, torch, lq, wl, keep=False):
                            "W4A4 SINT4 blocks of 64, FP16 scales" if layer.a_group == 64 else f"W4A4 INT4 g{layer.g}",
                    "branch": f"W{layer.br_w_bits}A8 MXINT block 32" if mxi else ("W6A6 MXFP6e2 block 32" if layer.br_w_bits == 6 else "W8A8 MXFP8e4 block 32") if mxb else "W8A8 FP8 E4M3" if mx else f"W{layer.br_w_bits}A{layer.br_a_bits}",
                    "x_dtype": layer.x_dtype, "buffer_sets": nsets,
-                   "arithmetic": ("int4 codes as FP8 subnormals with E8M0 block scales on the scaled FP8 MFMA, "
+                   "arithmetic": ("int4 codes as 6-bit E2M3 fields with E8M0 block scales on the scaled FP6 MFMA, "
                                   "bf16-exact MXINT branch, fp32 accumulate" if mxi else
                                   "e2m1 x e8m0 on the scaled FP4 MFMA, e4m3 branch, fp32 accumulate" if mx else
                                   "int4 codes (exact; 6-bit E2M3 fields on the f8f6f4 MFMA), int8 branch, fp32 dequantisation")},

@@ -28,12 +28,7 @@ namespace lq {
 // chunks ordered [block][chunk]; a lane reads its operand as one aligned 16-byte and one aligned
 // 8-byte load, each contiguous over the wavefront.
 //
-// The MXI family keeps 4-bit sign-magnitude nibbles, 8 codes c0..c7 per dword, such that two bit
-// operations turn a dword into two dwords of FP8-E4M3 *subnormal* bytes  s0000mmm (+-m * 2^-9):
-//     lo = p & 0x87878787          -> bytes of c0..c3
-//     hi = rotl(p, 4) & 0x87878787 -> bytes of c4..c7
-// i.e. for i in 0..3:  c_i   : sign at bit 8i+7, magnitude at bits 8i+2..8i
-//                      c_4+i : sign at bit 8i+3, magnitude at bits 8j+6..8j+4, j = (i-1)&3
+// The MXI family multiplies the same 6-bit fields but keeps 16 of them in 8 bytes (f6_pack in lq_mxi.hip).
 //
 // MX family: E2M1 codes as [block of 32 rows][64-chunk][lane = row%32 + 32*half][16 bytes], code i of a lane's
 // 32 in nibble i of its 16 bytes (the FP4 operand layout of v_mfma_scale_f32_32x32x64_f8f6f4).  E8M0 scales:
@@ -53,9 +48,9 @@ namespace lq {
 // rq : [128-chunk of K][rank/16][lane][32 bytes] (mxb_rq_offset); re (in the sr section): one dword
 // per (chunk, rank/16, lane), byte 0 = scale of K block 4*chunk + q.
 //
-// MXI family (MXINT4 main, MXINT8 / MXINT4 branch): main codes as 4-bit sign-magnitude nibbles in the
-// fragment order of the 8-bit scaled MFMA (mxi_frag_offset), scale bytes in the MX layout above holding
-// shared exponent + 127 + 7; the dequantised branch elements as bf16 in bf16-MFMA operand order
+// MXI family (MXINT4 main, MXINT8 / MXINT4 branch): main codes as packed 6-bit fields in the
+// fragment order of the 6-bit scaled MFMA (mxi_frag_offset), scale bytes in the MX layout above holding
+// shared exponent + 127 + 1; the dequantised branch elements as bf16 in bf16-MFMA operand order
 // (lq / tq sections: [block of 32 rows][rank/16][lane][8 bf16]; rq section: [64-chunk][rank/16][2][lane]
 // [8 bf16]); their E8M0 bytes row-major in the sl / sr / st sections (kept for the views only).
 // ---------------------------------------------------------------------------------------
@@ -86,13 +81,14 @@ struct Dims {
 // undetectable: the per-call entry points never read device memory on the host).
 constexpr size_t BLOB_HEADER = 256;
 constexpr uint32_t BLOB_MAGIC = 0x4C515242u;   // "LQRB"
-constexpr uint32_t BLOB_VERSION = 2u;          // layout revision (6-bit code fields for the INT family)
+// layout revision: 2 INT and MX families (6-bit code fields for the INT family), 3 MXI family (packed 6-bit fields)
+static inline uint32_t blob_version(const Dims& d) { return d.mxi ? 3u : 2u; }
 struct BlobTag { uint32_t w[8]; };
 static inline BlobTag make_tag(const Dims& d, int kind, int64_t M)
 {
     BlobTag t;
     t.w[0] = BLOB_MAGIC;
-    t.w[1] = BLOB_VERSION;
+    t.w[1] = blob_version(d);
     t.w[2] = (uint32_t)kind;
     t.w[3] = (uint32_t)d.cfg_hash;
     t.w[4] = (uint32_t)(d.cfg_hash >> 32);
@@ -298,29 +294,6 @@ __device__ __forceinline__ float max_row16(float v)
     v = max_dpp<0x141>(v);      // row_half_mirror
     return max_dpp<0x140>(v);   // row_mirror
 }
-__device__ __forceinline__ uint32_t nib_lo(uint32_t p) { return p & 0x87878787u; }
-__device__ __forceinline__ uint32_t nib_hi(uint32_t p)
-{
-    return __builtin_rotateleft32(p, 4) & 0x87878787u;
-}
-
-// Insert code e (0..7) with sign bit s (0|1) and magnitude m (0..7) into a packed dword.
-__device__ __forceinline__ uint32_t nib_put(int e, uint32_t s, uint32_t m)
-{
-    if (e < 4) return (s << (8 * e + 7)) | (m << (8 * e));
-    const int i = e - 4, j = (i - 1) & 3;
-    return (s << (8 * i + 3)) | (m << (8 * j + 4));
-}
-
-// Extract code e of a packed dword as a signed integer.
-__device__ __forceinline__ int nib_get(uint32_t p, int e)
-{
-    const uint32_t v = (e < 4) ? nib_lo(p) : nib_hi(p);
-    const uint32_t b = (v >> (8 * (e & 3))) & 0xFFu;
-    const int m = (int)(b & 7u);
-    return (b & 0x80u) ? -m : m;
-}
-
 // ---- 6-bit main codes of the INT family (fragment order above) ----
 constexpr int F6_CHUNK = 1536;  // bytes of one (32-row block, 64-chunk)
 // byte offset, inside a chunk, of dword d (0..5) of lane `lane`'s operand

@@ -7,11 +7,11 @@
 // Element of width b: integer code c in [-(2^(b-1)-1), 2^(b-1)-1], value c * 2^(s-(b-2)) with the
 // block's shared exponent s = floor(log2 amax) (E8M0 byte s + 127; 0 for an all-zero block).
 //
-// Main product: the 4-bit codes are fed to v_mfma_scale_f32_32x32x64_f8f6f4 as FP8-E4M3 subnormals
-// (byte s0000mmm = +-m * 2^-9); the instruction applies both E8M0 block scales itself, so there is
-// NO vector-ALU dequantisation: the stored scale byte is s + 127 + 7 (2^-9 * 2^(s+7) = 2^(s-2), one
-// code step).  Inside a block every product and partial sum is exact; across blocks the matrix core
-// accumulates in fp32.
+// Main product: the 4-bit codes are fed to v_mfma_scale_f32_32x32x64_f8f6f4 as 6-bit fields s00mmm, the
+// E2M3 (FP6) patterns of +-m/8, which run at twice the rate of 8-bit operands; the instruction applies
+// both E8M0 block scales itself, so there is NO vector-ALU dequantisation: the stored scale byte is
+// s + 127 + 1 (2^-3 * 2^(s+1) = 2^(s-2), one code step).  Inside a block every product and partial sum is
+// exact; across blocks the matrix core accumulates in fp32.
 // Branch: a power-of-two block scale times an integer of at most 7 bits is exactly a bf16 value, so
 // the dequantised MXINT elements are stored as bf16 and both contractions run on the bf16 MFMA with
 // fp32 accumulation (products exact); the rank-r expansion accumulates straight into the main
@@ -24,6 +24,7 @@
 
 namespace lq {
 
+typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -33,14 +34,78 @@ typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 
 // ---- layouts -------------------------------------------------------------------------------
 // Main codes, "fragment order": [block of 32 rows][64-chunk of K][lane = row%32 + 32*h][16 bytes].
-// With 8-bit operands the scaled MFMA takes bytes 0..15 of both lanes of a row as K block 0 and
-// bytes 16..31 as K block 1, so lane (row, h) holds k = 16h..16h+15 of each 32-block: packed dwords
-// 0,1 (block 0) and 2,3 (block 1); 8 codes per dword in the nibble order of nib_put.
-__device__ __forceinline__ size_t mxi_frag_offset(int row, int k, int C64)  // dword holding code (row, k)
+// With 6-bit operands lane (row, h) of the scaled MFMA holds block h of its row's chunk, code i at bits 6i .. 6i+5 of six
+// dwords; two of the six bits of every field are zero, so three dwords (16 codes) are kept in two (f6_pack / f6_unpack):
+// bytes 0..7 hold k = 32h .. 32h+15, bytes 8..15 the other half of the block.
+__device__ __forceinline__ size_t mxi_frag_offset(int row, int k, int C64)  // the 8 bytes that hold code (row, k)
 {
-    const int c = k >> 6, kk = k & 63, blk = kk >> 5, h = (kk >> 4) & 1, d = 2 * blk + ((kk & 15) >> 3);
-    return ((size_t)((size_t)(row >> 5) * C64 + c) * 64 + (row & 31) + 32 * h) * 16 + d * 4;
+    return ((size_t)((size_t)(row >> 5) * C64 + (k >> 6)) * 64 + (row & 31) + 32 * ((k >> 5) & 1)) * 16 + ((k >> 4) & 1) * 8;
 }
+// Three dwords of fields have 64 bits in use (sign, three of magnitude per code).  a keeps the 22 of dword 0 in place and, where that
+// has its zeros, 10 bits of dword 2; b the 21 of dword 1 and the other 11 of dword 2: no bit changes its position, two and
+// an and-or apart the three dwords come back in four instructions (expanding nibbles to bytes takes six for 16 codes).
+constexpr uint32_t F6_A = 0xE79E79E7u, F6_B = 0x79E79E79u;  // the bits of dwords 0 and 1 that fields use
+__device__ __forceinline__ uint2 f6_pack(uint32_t d0, uint32_t d1, uint32_t d2) { return make_uint2(d0 | (d2 & ~F6_A), d1 | (d2 & ~F6_B)); }
+__device__ __forceinline__ void f6_unpack(uint32_t a, uint32_t b, uint32_t (&d)[3])
+{
+    d[0] = a & F6_A;
+    d[1] = b & F6_B;
+    d[2] = (a & ~F6_A) | (b & ~F6_B);
+}
+__device__ __forceinline__ int f6_code(const uint8_t* at, int e)  // code e (0..15) of the 8 bytes at `at`
+{
+    uint32_t d[3];
+    f6_unpack(*(const uint32_t*)at, *(const uint32_t*)(at + 4), d);
+    const int bit = 6 * e;
+    const uint64_t lo = d[bit >> 5] | (bit < 64 ? (uint64_t)d[(bit >> 5) + 1] << 32 : 0ull);
+    const uint32_t c = (uint32_t)(lo >> (bit & 31)) & 63u;
+    return (c & 32u) ? -(int)(c & 7u) : (int)(c & 7u);
+}
+
+// The 6-bit fields of values |v| <= 7 sc / 8 (clamped before): the hardware FP6 converter applied to v / sc, round to nearest even,
+// on the grid of E2M3's subnormals = one code step.  The converters write their six result registers over several passes while still
+// reading their sources, and the register allocator is not told: the sources are kept live past them so that the result
+// cannot land on them.  (The result passes through the statement: one that only reads the sources may be moved ahead.)
+typedef unsigned int v6u __attribute__((ext_vector_type(6)));
+__device__ __forceinline__ v6u f6_from_bf16(const uint32_t (&w)[16], float sc)  // bf16 pairs, in order
+{
+    typedef unsigned int v16u __attribute__((ext_vector_type(16)));
+    typedef __bf16 v32bf __attribute__((ext_vector_type(32)));
+    const v16u h = {w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7], w[8], w[9], w[10], w[11], w[12], w[13], w[14], w[15]};
+    v6u c = __builtin_amdgcn_cvt_scalef32_pk32_fp6_bf16(__builtin_bit_cast(v32bf, h), sc);
+    asm volatile("" : "+v"(c) : "v"(h), "v"(sc));
+    return c;
+}
+// 16 values: the sources' upper halves are not defined, the codes they give (result dwords 3..5) not used
+__device__ __forceinline__ uint2 f6_pack16_bf16(const uint32_t (&w)[8], float sc)
+{
+    typedef unsigned int v8u __attribute__((ext_vector_type(8)));
+    typedef __bf16 v32bf __attribute__((ext_vector_type(32)));
+    const v8u h8 = {w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]};
+    const auto h = __builtin_shufflevector(h8, h8, 0, 1, 2, 3, 4, 5, 6, 7, -1, -1, -1, -1, -1, -1, -1, -1);
+    v6u c = __builtin_amdgcn_cvt_scalef32_pk32_fp6_bf16(__builtin_bit_cast(v32bf, h), sc);
+    asm volatile("" : "+v"(c) : "v"(h), "v"(sc));
+    return f6_pack(c[0], c[1], c[2]);
+}
+__device__ __forceinline__ uint2 f6_pack16_f32(const float (&v)[16], float sc)  // (the converter interleaves its two sources)
+{
+    typedef float v8f __attribute__((ext_vector_type(8)));
+    const v8f ev = {v[0], v[2], v[4], v[6], v[8], v[10], v[12], v[14]}, od = {v[1], v[3], v[5], v[7], v[9], v[11], v[13], v[15]};
+    const v16f a = __builtin_shufflevector(ev, ev, 0, 1, 2, 3, 4, 5, 6, 7, -1, -1, -1, -1, -1, -1, -1, -1);
+    const v16f b = __builtin_shufflevector(od, od, 0, 1, 2, 3, 4, 5, 6, 7, -1, -1, -1, -1, -1, -1, -1, -1);
+    v6u c = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, sc);
+    asm volatile("" : "+v"(c) : "v"(a), "v"(b), "v"(sc));
+    return f6_pack(c[0], c[1], c[2]);
+}
+// bf16 pair with both magnitudes at most those of `lim` (7 code steps, in both halves)
+__device__ __forceinline__ uint32_t clamp_pair(uint32_t w, uint32_t lim)
+{
+    const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, w & 0x7FFF7FFFu), __builtin_bit_cast(us2, lim)));
+    return (w & 0x80008000u) | m;
+}
+// 7 code steps (1.75 * 2^s) and the converter's scale 2^(s+1) of a block with exponent field `field`; blocks below 2^-125 have codes 0
+__device__ __forceinline__ uint32_t f6_limit(uint32_t field) { return field >= 2u ? (field << 23) | 0x00600000u : 0u; }  // as fp32 bits
+__device__ __forceinline__ float f6_scale(uint32_t field) { return __uint_as_float((field + 1u) << 23); }
 // Scale bytes: one dword per (block of 32 rows, quad of 64-chunks, lane); lane (row, h) holds the
 // scale of K block h of its row, byte c%4 for chunk c (the instruction's op_sel picks the byte).
 __device__ __forceinline__ size_t mxi_scale_offset(int row, int c, int blk, int CQ)
@@ -127,15 +192,16 @@ struct PackMxiResidual {
         float a = pack_amax(P[0]);
         a = fmaxf(a, __shfl_xor(a, 16));  // lanes q, q ^ 1 hold the block
         const uint32_t field = exp_field(a);
-        uint32_t w[2] = {0u, 0u};
+        uint32_t d[3] = {0u, 0u, 0u};
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int code = mxint_code(P[0][e], field, 4);
-            w[e >> 3] |= nib_put(e & 7, code < 0 ? 1u : 0u, (uint32_t)(code < 0 ? -code : code));
+            const uint32_t f = f6_field(mxint_code(P[0][e], field, 4));
+            const int bit = 6 * e, at = bit >> 5, sh = bit & 31;
+            d[at] |= f << sh;
+            if (sh > 26) d[at + 1] |= f >> (32 - sh);
         }
-        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-        *(u2*)(pq + mxi_frag_offset(n, c * 64 + 16 * q, K >> 6)) = u2{w[0], w[1]};
-        if ((q & 1) == 0) pe[mxi_scale_offset(n, c, q >> 1, ((K >> 6) + 3) >> 2)] = (uint8_t)(field + 7);
+        *(uint2*)(pq + mxi_frag_offset(n, c * 64 + 16 * q, K >> 6)) = f6_pack(d[0], d[1], d[2]);
+        if ((q & 1) == 0) pe[mxi_scale_offset(n, c, q >> 1, ((K >> 6) + 3) >> 2)] = (uint8_t)(field + 1);
     }
 };
 
@@ -184,12 +250,11 @@ __global__ __launch_bounds__(256) void mxi_unpack_w_kernel(MxiPackedPtrs pp, int
     const int C64 = K >> 6, CQ = (C64 + 3) >> 2, B = K >> 5, BR = r >> 5;
     if (idx < (size_t)N * K && out.pq) {
         const int n = (int)(idx / K), k = (int)(idx % K);
-        const uint32_t w = *(const uint32_t*)(pp.pq + mxi_frag_offset(n, k, C64));
-        out.pq[idx] = (int8_t)nib_get(w, k & 7);
+        out.pq[idx] = (int8_t)f6_code(pp.pq + mxi_frag_offset(n, k, C64), k & 15);
     }
     if (idx < (size_t)N * B && out.pe) {
         const int n = (int)(idx / B), b = (int)(idx % B);
-        out.pe[idx] = (uint8_t)(pp.pe[mxi_scale_offset(n, b >> 1, b & 1, CQ)] - 7);
+        out.pe[idx] = (uint8_t)(pp.pe[mxi_scale_offset(n, b >> 1, b & 1, CQ)] - 1);
     }
     if (idx < (size_t)N * r && out.lq) {
         const int n = (int)(idx / r), j = (int)(idx % r);
@@ -219,12 +284,11 @@ __global__ __launch_bounds__(256) void mxi_unpack_a_kernel(const uint8_t* act, A
     const int C64 = K >> 6, CQ = (C64 + 3) >> 2, B = K >> 5, BR = r >> 5;
     if (idx < (size_t)M * K && out.xq) {
         const int m = (int)(idx / K), k = (int)(idx % K);
-        const uint32_t w = *(const uint32_t*)(act + al.off_xq + mxi_frag_offset(m, k, C64));
-        out.xq[idx] = (int8_t)nib_get(w, k & 7);
+        out.xq[idx] = (int8_t)f6_code(act + al.off_xq + mxi_frag_offset(m, k, C64), k & 15);
     }
     if (idx < (size_t)M * B && out.xe) {
         const int m = (int)(idx / B), b = (int)(idx % B);
-        out.xe[idx] = (uint8_t)(act[al.off_sx + mxi_scale_offset(m, b >> 1, b & 1, CQ)] - 7);
+        out.xe[idx] = (uint8_t)(act[al.off_sx + mxi_scale_offset(m, b >> 1, b & 1, CQ)] - 1);
     }
     if (idx < (size_t)M * r && out.tq) {
         const int m = (int)(idx / r), j = (int)(idx % r);
@@ -475,41 +539,27 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
                 }
                 const float ab = max_xor16(m);  // block of 32 = lanes kq, kq ^ 1
                 field = exp_field(ab);
-                // ---- main codes: MXINT4.  code = min(rne(|x| * 2^(2-s)), 7), sign kept apart
-                const float inv4 = field >= 2u ? __uint_as_float((256u - field) << 23) : 0.0f;  // 2^(2-s)
-                uint32_t pk[2] = {0u, 0u};
+                // ---- main codes: MXINT4, clamp(rne(x * 2^(2-s)), +-7) by the FP6 converter
+                const float sc = f6_scale(field);
+                uint2 pk;
                 if constexpr (BF16) {
-                    // |x|*inv + 2^23 has the code in its low bits and 0x4B in its top byte; eight of them
-                    // are summed at their nibble positions (the top bytes shifted by 0 and 4 add up to the
-                    // constant removed first, the others leave the dword); signs by one byte permute per four
+                    const uint32_t l1 = f6_limit(field), l2 = l1 | (l1 >> 16);
+                    uint32_t cw[8];
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        uint32_t sum = 0u - 0xFB000000u;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float x = ch.get(8 * h + e);
-                            const uint32_t mb = __float_as_uint(__fadd_rn(fminf(__fmul_rn(fabsf(x), inv4), 7.0f), 8388608.0f));
-                            const int sh = e < 4 ? 8 * e : 8 * ((e - 5) & 3) + 4;
-                            sum += mb << sh;
-                        }
-                        const uint32_t* w = &ch.w[4 * h];
-                        const uint32_t s03 = __builtin_amdgcn_perm(w[1], w[0], 0x07050301u);
-                        const uint32_t s47 = __builtin_amdgcn_perm(w[3], w[2], 0x07050301u);
-                        pk[h] = sum | (s03 & 0x80808080u) | ((s47 >> 4) & 0x08080808u);
-                    }
+                    for (int d = 0; d < 8; ++d) cw[d] = clamp_pair(ch.w[d], l2);
+                    pk = f6_pack16_bf16(cw, sc);
                 } else {
+                    const float lim = __uint_as_float(f6_limit(field));
+                    float cv[16];
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const float x = ch.get(i);
-                        const uint32_t mg = __float_as_uint(__fadd_rn(fminf(__fmul_rn(fabsf(x), inv4), 7.0f), 8388608.0f)) & 7u;
-                        pk[i >> 3] |= nib_put(i & 7, __float_as_uint(x) >> 31, mg);
-                    }
+                    for (int i = 0; i < 16; ++i) cv[i] = __builtin_amdgcn_fmed3f(ch.get(i), -lim, lim);
+                    pk = f6_pack16_f32(cv, sc);
                 }
-                // lane (row, kq): block kq>>1 of the chunk, K half-block h = kq&1 -> dwords 2*(kq>>1), +1 of lane (row, h)
-                uint8_t* dst = p.xq + ((size_t)((size_t)(row >> 5) * C64 + c) * 64 + (row & 31) + 32 * (kq & 1)) * 16 + (kq >> 1) * 8;
+                // lane (row, kq): half kq & 1 of block kq >> 1 of the chunk
+                uint8_t* dst = p.xq + ((size_t)((size_t)(row >> 5) * C64 + c) * 64 + (row & 31) + 32 * (kq >> 1)) * 16 + (kq & 1) * 8;
                 if (have && row0 + 16 * g < Mp) {
-                    *(uint2*)dst = make_uint2(pk[0], pk[1]);
-                    if ((kq & 1) == 0) p.xe[mxi_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)(field + 7u);
+                    *(uint2*)dst = pk;
+                    if ((kq & 1) == 0) p.xe[mxi_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)(field + 1u);
                 }
             }
             if (NJB > 0) {
@@ -798,31 +848,26 @@ struct MxiFwdParams {
     uint32_t* ho_tag_dst;
 };
 
-__device__ __forceinline__ v8i mxi_expand8(v4i p)  // 32 nibbles -> 32 FP8 subnormal bytes
+__device__ __forceinline__ v8i mxi_expand(v4i p)  // 32 packed codes -> the lane's FP6 operand (six dwords; FP6 mode reads no more)
 {
-    v8i o;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        o[2 * d] = (int)nib_lo((uint32_t)p[d]);
-        o[2 * d + 1] = (int)nib_hi((uint32_t)p[d]);
-    }
-    return o;
+    uint32_t lo[3], hi[3];
+    f6_unpack((uint32_t)p[0], (uint32_t)p[1], lo);
+    f6_unpack((uint32_t)p[2], (uint32_t)p[3], hi);
+    typedef int v6i __attribute__((ext_vector_type(6)));
+    const v6i o = {(int)lo[0], (int)lo[1], (int)lo[2], (int)hi[0], (int)hi[1], (int)hi[2]};
+    return __builtin_shufflevector(o, o, 0, 1, 2, 3, 4, 5, -1, -1);
 }
 
-// Both codes of eight values (bf16 pairs) by one fused multiply-add each: scaling by a power of two is exact, so fma(x, 2^-step, magic)
+// MXINT8 codes of eight values (bf16 pairs) by one fused multiply-add each: scaling by a power of two is exact, so fma(x, 2^-step, magic)
 // rounds the scaled value to the nearest integer (ties to even) in one step -- the same integer the
 // activation kernel reaches by rounding on the block's grid and scaling afterwards -- and leaves it in
 // the low mantissa bits of the magic number.  Clamping after the rounding equals clamping before it.
-__device__ __forceinline__ void mxi_handoff_codes(const uint32_t* w, const float inv4, const float to8, uint32_t& pk, uint32_t* c8)
+__device__ __forceinline__ void mxi_handoff_codes8(const uint32_t* w, const float to8, uint32_t* c8)
 {
-    uint32_t sum = 0u - 0xFB000000u;
     uint32_t ub[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const float x = __uint_as_float((e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16));
-        const uint32_t mb = __float_as_uint(fminf(__builtin_fmaf(fabsf(x), inv4, 8388608.0f), 8388615.0f));
-        const int sh = e < 4 ? 8 * e : 8 * ((e - 5) & 3) + 4;
-        sum += mb << sh;
         // 1.5 * 2^23 + code, code in [-127, 127]: the low byte is the two's-complement MXINT8 code
         ub[e] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(x, to8, 12582912.0f), 12582785.0f, 12583039.0f));
     }
@@ -832,34 +877,41 @@ __device__ __forceinline__ void mxi_handoff_codes(const uint32_t* w, const float
         const uint32_t hi = __builtin_amdgcn_perm(ub[4 * h + 3], ub[4 * h + 2], 0x04000c0cu);  // ... in the upper half
         c8[h] = lo | hi;
     }
-    const uint32_t s03 = __builtin_amdgcn_perm(w[1], w[0], 0x07050301u);
-    const uint32_t s47 = __builtin_amdgcn_perm(w[3], w[2], 0x07050301u);
-    pk = sum | (s03 & 0x80808080u) | ((s47 >> 4) & 0x08080808u);
 }
+__device__ __forceinline__ float mxint8_unscale(uint32_t field) { return field >= 7u ? __uint_as_float((260u - field) << 23) : 0.0f; }  // 2^(6-s)
 
 // Hand-off codes of 8 consecutive channels (k0 = this layer's channel = the next layer's k) of one token, given as bf16: a
 // block of 32 of the next layer's K axis is the 4 lanes that differ in the two low lane bits.  Codes as in the activation
-// kernel: shared exponent from the block maximum, MXINT4 main codes (sign-magnitude nibbles), MXINT8 branch codes.
+// kernel: shared exponent from the block maximum, MXINT4 main codes (6-bit fields), MXINT8 branch codes.
 __device__ __forceinline__ void mxi_handoff_emit(const MxiFwdParams& p, const v4i v, const int row, const int k0)
 {
-                    const uint32_t w[4] = {(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
-                    us2 m2 = {0, 0};
+    const uint32_t w[4] = {(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
+    us2 m2 = {0, 0};
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, w[d] & 0x7FFF7FFFu));
-                    uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
-                    float am = __uint_as_float(mm << 16);
-                    am = fmaxf(am, __shfl_xor(am, 1, 64));
-                    am = fmaxf(am, __shfl_xor(am, 2, 64));
-                    const uint32_t field = exp_field(am);
-                    const float inv4 = field >= 2u ? __uint_as_float((256u - field) << 23) : 0.0f;   // 2^(2-s)
-                    const float to8 = field >= 7u ? __uint_as_float((260u - field) << 23) : 0.0f;    // 2^(6-s)
-                    uint32_t pk, c8[2];
-                    mxi_handoff_codes(w, inv4, to8, pk, c8);
+    for (int d = 0; d < 4; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, w[d] & 0x7FFF7FFFu));
+    const uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
+    float am = __uint_as_float(mm << 16);
+    am = max_dpp<0xB1>(am);  // quad_perm [1,0,3,2], then [2,3,0,1]
+    am = max_dpp<0x4E>(am);
+    const uint32_t field = exp_field(am);
+    uint32_t c8[2];
+    mxi_handoff_codes8(w, mxint8_unscale(field), c8);
+    // the neighbour's 8 values are the other half of the 16 codes that share 8 bytes: both lanes convert all of them, each stores a dword
+    const uint32_t l1 = f6_limit(field), l2 = l1 | (l1 >> 16);
+    const bool odd = (k0 >> 3) & 1;
+    uint32_t cw[8];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t own = clamp_pair(w[d], l2), other = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);
+        cw[d] = odd ? other : own;
+        cw[4 + d] = odd ? own : other;
+    }
+    const uint2 pk = f6_pack16_bf16(cw, f6_scale(field));
     if (row < p.nrb * 32) {
-        *(uint32_t*)(p.ho_xq + mxi_frag_offset(row, k0, p.ho_C64)) = pk;
+        *(uint32_t*)(p.ho_xq + mxi_frag_offset(row, k0, p.ho_C64) + (odd ? 4 : 0)) = odd ? pk.y : pk.x;
         *(uint2*)(p.ho_cb + (size_t)row * p.N + k0) = make_uint2(c8[0], c8[1]);
         if ((k0 & 31) == 0) {
-            p.ho_xe[mxi_scale_offset(row, k0 >> 6, (k0 >> 5) & 1, p.ho_CQ)] = (uint8_t)(field + 7u);
+            p.ho_xe[mxi_scale_offset(row, k0 >> 6, (k0 >> 5) & 1, p.ho_CQ)] = (uint8_t)(field + 1u);
             p.ho_cbe[(size_t)row * (p.N >> 5) + (k0 >> 5)] = (uint8_t)field;
             // padding chunks of the next layer's last quad: valid E8M0 bytes (2^0), written with the last real chunk
             if ((k0 >> 6) == p.ho_C64 - 1)
@@ -869,31 +921,39 @@ __device__ __forceinline__ void mxi_handoff_emit(const MxiFwdParams& p, const v4
 }
 
 // The same from the registers of mxi_fwd_kernel: a row block of 32 tokens and 64 channels (one chunk of the next layer's K); lane (row, h)
-// holds channels 16 h .. 16 h + 15 of both blocks of 32 as bf16 pairs, which is how the activation kernel holds them: one 16-byte store of
-// main codes (1 KB contiguous per wavefront), one of branch codes per block, and each lane half writes one block's scale bytes.
+// holds channels 16 h .. 16 h + 15 of both blocks of 32 as bf16 pairs.  Eight row-swap instructions leave it block h whole, the unit of
+// the consumer's operands: the block's maximum and both kinds of codes need no other lane; 16 bytes of main codes (1 KB contiguous per
+// wavefront), 32 of branch codes, and the block's scale bytes.
 __device__ __forceinline__ void mxi_handoff_rows(const MxiFwdParams& p, const uint32_t (&w)[2][8], const int rb, const int cb0, const int lane)
 {
     const int half = lane >> 5, row = rb * 32 + (lane & 31), c = cb0 >> 1;
-    uint32_t field[2], pk[4];
+    uint32_t x[16], cw[16];
 #pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-        us2 m2 = {0, 0};
-#pragma unroll
-        for (int d = 0; d < 8; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, w[blk][d] & 0x7FFF7FFFu));
-        const uint32_t mm = (uint32_t)(m2[0] > m2[1] ? m2[0] : m2[1]) << 16;
-        const auto sw = __builtin_amdgcn_permlane32_swap(mm, mm, false, false);  // both halves of the row in every lane
-        field[blk] = exp_field(fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])));
-        const float inv4 = field[blk] >= 2u ? __uint_as_float((256u - field[blk]) << 23) : 0.0f;   // 2^(2-s)
-        const float to8 = field[blk] >= 7u ? __uint_as_float((260u - field[blk]) << 23) : 0.0f;    // 2^(6-s)
-        uint32_t c8[4];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) mxi_handoff_codes(&w[blk][4 * h], inv4, to8, pk[2 * blk + h], &c8[2 * h]);
-        *(v4i*)(p.ho_cb + (size_t)row * p.N + (cb0 + blk) * 32 + 16 * half) = v4i{(int)c8[0], (int)c8[1], (int)c8[2], (int)c8[3]};
+    for (int d = 0; d < 8; ++d) {  // the upper half of w[0] and the lower half of w[1] change places
+        const auto sw = __builtin_amdgcn_permlane32_swap(w[0][d], w[1][d], false, false);
+        x[d] = sw[0];
+        x[8 + d] = sw[1];
     }
-    *(v4i*)(p.ho_xq + ((size_t)((size_t)rb * p.ho_C64 + c) * 64 + lane) * 16) = v4i{(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
-    const uint32_t f = half ? field[1] : field[0];
-    p.ho_xe[mxi_scale_offset(row, c, half, p.ho_CQ)] = (uint8_t)(f + 7u);
-    p.ho_cbe[(size_t)row * (p.N >> 5) + cb0 + half] = (uint8_t)f;
+    us2 m2 = {0, 0};
+#pragma unroll
+    for (int d = 0; d < 16; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, x[d] & 0x7FFF7FFFu));
+    const uint32_t field = exp_field(__uint_as_float((uint32_t)(m2[0] > m2[1] ? m2[0] : m2[1]) << 16));
+    const float to8 = mxint8_unscale(field);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        uint32_t c8[4];
+        mxi_handoff_codes8(&x[8 * h], to8, c8);
+        mxi_handoff_codes8(&x[8 * h + 4], to8, c8 + 2);
+        *(v4i*)(p.ho_cb + (size_t)row * p.N + (cb0 + half) * 32 + 16 * h) = v4i{(int)c8[0], (int)c8[1], (int)c8[2], (int)c8[3]};
+    }
+    const uint32_t l1 = f6_limit(field), l2 = l1 | (l1 >> 16);
+#pragma unroll
+    for (int d = 0; d < 16; ++d) cw[d] = clamp_pair(x[d], l2);
+    const v6u f6 = f6_from_bf16(cw, f6_scale(field));
+    const uint2 lo = f6_pack(f6[0], f6[1], f6[2]), hi = f6_pack(f6[3], f6[4], f6[5]);
+    *(v4i*)(p.ho_xq + ((size_t)((size_t)rb * p.ho_C64 + c) * 64 + lane) * 16) = v4i{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y};
+    p.ho_xe[mxi_scale_offset(row, c, half, p.ho_CQ)] = (uint8_t)(field + 1u);
+    p.ho_cbe[(size_t)row * (p.N >> 5) + cb0 + half] = (uint8_t)field;
     // padding chunks of the next layer's last quad: valid E8M0 bytes (2^0), written with the last real chunk
     if (c == p.ho_C64 - 1)
         for (int cc = p.ho_C64; cc < 4 * p.ho_CQ; ++cc) p.ho_xe[mxi_scale_offset(row, cc, half, p.ho_CQ)] = (uint8_t)127;
@@ -902,16 +962,21 @@ __device__ __forceinline__ void mxi_handoff_rows(const MxiFwdParams& p, const ui
 namespace mxif {
 constexpr int RBT = 4, NBUF = 4;              // row blocks of a tile, LDS buffers of the activation stream (one 64-chunk each)
 constexpr int EPI_ROW = 144, EPI_WAVE = 32 * EPI_ROW;
-constexpr int LDS_MAIN = NBUF * RBT * 2048;   // [buffer][row block][part][lane][16 B]
+constexpr int SLOT = 2064;                    // of one staged operand: [lane][16 B], [lane][8 B]; the stride keeps the compiler from merging reads of two slots
+constexpr int LDS_MAIN = NBUF * RBT * SLOT;   // [buffer][row block]
 constexpr int LDS_BYTES = LDS_MAIN > 4 * EPI_WAVE ? LDS_MAIN : 4 * EPI_WAVE;
 }  // namespace mxif
 
 // One tile of 128 rows: WN = 4 wavefronts side by side of 128 x 64 outputs each, or, for a last column of tiles of at most 128 channels,
-// 2 x 2 wavefronts of 64 x 64 (side by side two of the four would have no columns).  Bounded by the 8-bit matrix rate inside the K loop
-// (two wavefronts per SIMD keep it busy as long as their loads arrive), by instruction latency around it.  The fences in the loop
+// 2 x 2 wavefronts of 64 x 64 (side by side two of the four would have no columns).  Inside the K loop the 6-bit matrix
+// rate (512 cycles a step for the two wavefronts of a SIMD) is the largest of several: a step takes 676 (K = 4608) to 800 cycles (K = 1152), with
+// 24 instructions that unpack codes and 9 KB through the LDS per wavefront; around it instruction latency.  Codes as 8-bit operands (FP8
+// subnormals) took 1024 cycles of the matrix core a step: us with those / as it is, rank 64: 16384 x 1152 -> 3456 68.3 / 64.5, 5000 x 2240 -> 6720
+// 63.9 / 53.9, 16384 x 1152 -> 1152 23.8 / 21.9, rank 128 16384 x 4608 -> 1152 68.7 / 59.8, 16384 x 1152 -> 4608 with hand-off 105.5 / 98.1 (the
+// clock falls as the matrix core gets busier: 38 -> 31 thousand cycles a tile).  The fences in the loop
 // hold every load two steps ahead of its use: left to itself the compiler sinks them to the end of their step and waits for all of
-// them in the next (us without the fences / without the narrow tiles / as it is: 16384 x 4608 -> 1152 rank 128 75.7 / 74.5 / 68.4, 16384 x
-// 1152 -> 3456 74.9 / 67.3 / 67.5, 16384 x 1152 -> 1152 25.6 / 25.3 / 23.5, 5000 x 2240 -> 6720 69.5 / 64.9 / 65.2).
+// them in the next (us without the fences / without the narrow tiles / as it is: 16384 x 4608 -> 1152 rank 128 66.4 / 64.5 / 59.8, 16384 x
+// 1152 -> 3456 69.7 / 63.2 / 64.5, 16384 x 1152 -> 1152 22.9 / 22.8 / 21.9, 5000 x 2240 -> 6720 56.5 / 54.3 / 53.9).
 // NK16 = 16-deep chunks of the rank: 0 | 2 | 4 | 6 | 8.  HO: quantized hand-off (Section 4.5): the epilogue also emits
 // the next layer's activation codes from the bf16 values it has just formed; Y itself is optional then.
 template <int NK16, bool DBG, bool HO, int WN>
@@ -927,7 +992,7 @@ __device__ __forceinline__ void mxi_fwd_tile(const MxiFwdParams& p, uint8_t* lds
     const bool active = (cb0 * 32 < p.N) && (rbw < p.nrb);
     const int C64 = p.C64, CQ = p.CQ;
 
-    const uint32_t lane16 = (uint32_t)lane * 16u, lane4 = (uint32_t)lane * 4u;
+    const uint32_t lane16 = (uint32_t)lane * 16u, lane8 = 1024u + (uint32_t)lane * 8u, lane4 = (uint32_t)lane * 4u;
     // The weights are the first operand, and lane l32 of it takes row c(l32) of its block of 32: the accumulator of row 8 g + 4 h + i is
     // register 4 g + i of the lanes of half h, so with c(8 g + 4 h + i) = 16 h + 4 g + i a lane ends up with one token and 16
     // consecutive channels of it -- 32 bytes of Y, and the unit in which the next layer's codes are laid out.
@@ -957,10 +1022,10 @@ __device__ __forceinline__ void mxi_fwd_tile(const MxiFwdParams& p, uint8_t* lds
         a = __builtin_bit_cast(v4i, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs_x, lane16, st * 1024, 0));
     };
     auto store_a = [&](const v4i& a, int buf) {
-        const v8i e = mxi_expand8(a);
-        uint8_t* base = lds + (size_t)((buf * RBT + wave) * 2048) + lane16;
-        *(v4i*)(base) = v4i{e[0], e[1], e[2], e[3]};
-        *(v4i*)(base + 1024) = v4i{e[4], e[5], e[6], e[7]};
+        const v8i e = mxi_expand(a);
+        uint8_t* base = lds + (size_t)((buf * RBT + wave) * SLOT);
+        *(v4i*)(base + lane16) = v4i{e[0], e[1], e[2], e[3]};
+        *(v2i*)(base + lane8) = v2i{e[4], e[5]};
     };
     struct BStage { v4i v[2]; };
     auto load_b = [&](BStage& b, int step) {
@@ -994,10 +1059,12 @@ __device__ __forceinline__ void mxi_fwd_tile(const MxiFwdParams& p, uint8_t* lds
     // apart, so nothing waits for it.  SEL = s % 4 picks the scale byte and the buffer.
     v8i af[2];
     auto lds_a = [&](int buf, int rbi) -> v8i {
-        const uint8_t* base = lds + (size_t)((buf * RBT + rw + rbi) * 2048) + lane16;
-        const v4i lo = *(const v4i*)(base);
-        const v4i hi = *(const v4i*)(base + 1024);
-        return v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        const uint8_t* base = lds + (size_t)((buf * RBT + rw + rbi) * SLOT);
+        const v4i lo = *(const v4i*)(base + lane16);
+        const v2i hi = *(const v2i*)(base + lane8);
+        typedef int v6i __attribute__((ext_vector_type(6)));
+        const v6i o = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1]};
+        return __builtin_shufflevector(o, o, 0, 1, 2, 3, 4, 5, -1, -1);
     };
     auto do_step = [&](auto sel, int s, v4i& a, BStage& b, const Scales& sc) {
         constexpr int SEL = decltype(sel)::value;
@@ -1007,7 +1074,7 @@ __device__ __forceinline__ void mxi_fwd_tile(const MxiFwdParams& p, uint8_t* lds
             af[(rbi + 1) & 1] = rbi + 1 < NRB ? lds_a(SEL, rbi + 1) : lds_a((SEL + 1) & 3, 0);
 #pragma unroll
             for (int cbi = 0; cbi < 2; ++cbi)
-                t[rbi][cbi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bu[PAR][cbi], af[rbi & 1], t[rbi][cbi], 0, 0, SEL,
+                t[rbi][cbi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bu[PAR][cbi], af[rbi & 1], t[rbi][cbi], 2, 2, SEL,
                                                                              sc.b[cbi], SEL, sc.a[rbi]);
             if (rbi == 0) {
                 store_a(a, (SEL + 2) & 3);
@@ -1015,7 +1082,7 @@ __device__ __forceinline__ void mxi_fwd_tile(const MxiFwdParams& p, uint8_t* lds
             }
             if (rbi == 1) {
 #pragma unroll
-                for (int cbi = 0; cbi < 2; ++cbi) bu[PAR ^ 1][cbi] = mxi_expand8(b.v[cbi]);
+                for (int cbi = 0; cbi < 2; ++cbi) bu[PAR ^ 1][cbi] = mxi_expand(b.v[cbi]);
                 load_b(b, s + 3);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -1033,7 +1100,7 @@ __device__ __forceinline__ void mxi_fwd_tile(const MxiFwdParams& p, uint8_t* lds
     store_a(a0, 0);
     store_a(a1, 1);
 #pragma unroll
-    for (int cbi = 0; cbi < 2; ++cbi) bu[0][cbi] = mxi_expand8(b0.v[cbi]);
+    for (int cbi = 0; cbi < 2; ++cbi) bu[0][cbi] = mxi_expand(b0.v[cbi]);
     __builtin_amdgcn_sched_barrier(0);
     load_b(b1, 1);
     load_a(a0, 2);
@@ -1183,9 +1250,9 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
 
 // Small layers: a wavefront (a workgroup of its own) per tile of NRB*32 x NCB*32 outputs.  Where the 128 x 256 tiles leave most of the
 // chip idle, the time of a call is one tile's serial chain of steps; here nothing is shared between wavefronts (no LDS staging, no
-// barriers) and both operand streams are requested DEPTH quads of 64-chunks ahead, as packed nibbles, and expanded in registers.
-// Bounded by that chain for a few tiles (128 x 1152 -> 3456: 10.6 -> 4.2 us, 128 x 4608 -> 1152: 30.3 -> 8.6 us), by the operands' L2
-// traffic for many.  Same products in the same order as mxi_fwd_kernel.  HO: as there.
+// barriers) and both operand streams are requested DEPTH quads of 64-chunks ahead, as packed codes, and unpacked in registers.
+// Bounded by that chain for a few tiles (128 x 1152 -> 3456: 10.6 -> 4.2 us, 128 x 4608 -> 1152: 30.3 -> 8.6 us, both measured with codes as
+// 8-bit operands; 6-bit ones 10.2 -> 9.1 with both operands from memory), by the operands' L2 traffic for many.  Same products in the same order as mxi_fwd_kernel.  HO: as there.
 template <int NK16, bool DBG, bool HO, int NRB, int NCB>
 __global__ __launch_bounds__(64, 2) void mxi_fwd_small_kernel(MxiFwdParams p)
 {
@@ -1255,16 +1322,16 @@ __global__ __launch_bounds__(64, 2) void mxi_fwd_small_kernel(MxiFwdParams p)
         constexpr int CC = decltype(cc_tag)::value;
         v8i ae[NRB], be[NCB];
 #pragma unroll
-        for (int i = 0; i < NRB; ++i) ae[i] = mxi_expand8(q.c[CC].a[i]);
+        for (int i = 0; i < NRB; ++i) ae[i] = mxi_expand(q.c[CC].a[i]);
 #pragma unroll
-        for (int j = 0; j < NCB; ++j) be[j] = mxi_expand8(q.c[CC].b[j]);
+        for (int j = 0; j < NCB; ++j) be[j] = mxi_expand(q.c[CC].b[j]);
         load_chunk(q.c[CC], 4 * (quad + DEPTH) + CC);
         if (4 * quad + CC < C64) {
 #pragma unroll
             for (int i = 0; i < NRB; ++i)
 #pragma unroll
                 for (int j = 0; j < NCB; ++j)
-                    t[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ae[i], be[j], t[i][j], 0, 0, CC, sa[i], CC, sb[j]);
+                    t[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ae[i], be[j], t[i][j], 2, 2, CC, sa[i], CC, sb[j]);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -1357,25 +1424,26 @@ static void mxi_fwd_launch(const MxiFwdParams& p, hipStream_t s)
     // Small layers, by the number T of 32 x 32 tiles (the device holds 2048 wavefronts of these kernels): one tile to a
     // wavefront, larger ones as the L2 traffic of the operands (2, 1.5 and 1 KB per tile and 64-chunk) begins to count, the
     // 128 x 256 tiles once they occupy enough of the chip.  us, 1 x 1 / 2 x 1 / 2 x 2:
-    //   T =  108 (   2 x 1152 -> 3456): 4.0 / 5.0 / 6.8               T = 1728 ( 512 x 1152 -> 3456):  6.9 /  6.3 /  7.8
-    //   T =  144 ( 128 x 4608 -> 1152): 8.9 / 13.3 / 19.1             T = 3360 ( 512 x 2240 -> 6720): 16.9 / 13.2 / 13.0
-    //   T = 1152 (1024 x 4608 -> 1152): 13.7 / 15.1 / 20.3            T = 5076 (1500 x 1152 -> 3456): 14.8 / 12.9 / 11.6
+    //   T =  108 (   2 x 1152 -> 3456): 5.5 / 5.9 / 7.0               T = 1728 ( 512 x 1152 -> 3456):  7.8 /  6.8 /  7.8
+    //   T =  144 ( 128 x 4608 -> 1152): 9.1 / 11.9 / 16.0             T = 3360 ( 512 x 2240 -> 6720): 17.2 / 12.6 / 13.2
+    //   T = 1152 (1024 x 4608 -> 1152): 13.8 / 14.9 / 19.6            T = 5076 (1500 x 1152 -> 3456): 16.2 / 13.8 / 11.9
     // 2 x 2 / 128 x 256:
-    //   T = 5040 (4476 x  896 -> 1152): 10.0 / 10.7                   T = 5076 (1500 x 1152 -> 3456): 12.0 / 12.0
-    //   T = 5696 (11389 x 1024 -> 512): 10.9 / 11.5                   T = 6516 (5762 x  896 -> 1152): 11.5 / 11.1
-    //   T = 5400 (4770 x 2240 -> 1152): 17.7 / 17.3                   T = 6768 (6000 x 4608 -> 1152): 31.6 / 30.0
-    // 12 chunks of K and fewer: the large tiles' prologue weighs more (T = 6144, 8192 x 512 -> 768: 7.6 / 8.3; T = 6912, 1700 x 768 ->
-    // 4096: 10.1 / 10.7).  More large tiles than compute units (the tiles of a layer of 128 channels are half-sized): some units get a
-    // second one, and the call takes a generation more (T = 6396, 17052 x 832 -> 384: 11.4 / 12.6; T = 6990, 37274 x 2240 -> 192: 20.2 /
-    // 28.3; T = 5150, 82394 x 1152 -> 64: 16.5 / 21.4).
-    // With the hand-off, whose codes they form in registers, the large tiles are ahead earlier (T = 3168, 700 x 1152 -> 4608: 10.8 / 14.0; T = 4104,
-    // 1200 x 1152 -> 3456: 13.7 / 13.5; T = 4596, 12238 x 1152 -> 384: 15.5 / 13.8), also past one per compute unit in short rows (T = 5800, 18532
-    // x 896 -> 320: 15.6 / 15.0; 18545 x 2240 -> 320: 21.3 / 23.4), earlier or later by how many wavefronts their last column leaves without
-    // channels (T = 6348, 33847 x 512 -> 192: 12.9 / 14.9; T = 4600, 73590 x 896 -> 64: 16.3 / 17.1, 73577 x 64 -> 64: 11.1 / 9.2).
+    //   T = 5040 (4476 x  896 -> 1152): 10.1 / 10.9                   T = 5076 (1500 x 1152 -> 3456): 12.0 / 12.1
+    //   T = 5696 (11389 x 1024 -> 512): 10.9 / 11.8                   T = 6516 (5762 x  896 -> 1152): 11.5 / 11.3
+    //   T = 5400 (4770 x 2240 -> 1152): 16.4 / 17.6                   T = 6192 (5500 x 4608 -> 1152): 27.8 / 26.3
+    // 12 chunks of K and fewer: the large tiles' prologue weighs more (T = 6144, 8192 x 512 -> 768: 8.8 / 9.6; T = 6912, 1700 x 768 ->
+    // 4096: 11.2 / 11.5).  More large tiles than compute units (the tiles of a layer of 128 channels are half-sized): some units get a
+    // second one, and the call takes a generation more (T = 6396, 17052 x 832 -> 384: 11.7 / 12.0; T = 6990, 37274 x 2240 -> 192: 18.6 /
+    // 22.0; T = 5150, 82394 x 1152 -> 64: 14.8 / 17.4).
+    // With the hand-off, whose codes they form in registers, the large tiles are ahead earlier (T = 3168, 700 x 1152 -> 4608: 11.6 / 13.4; T = 4104,
+    // 1200 x 1152 -> 3456: 14.1 / 13.6; T = 4596, 12238 x 1152 -> 384: 15.2 / 13.4), also past one per compute unit in short rows (T = 5800, 18532
+    // x 896 -> 320: 15.7 / 14.0; 18545 x 2240 -> 320: 20.9 / 20.4), earlier or later by how many wavefronts their last column leaves without
+    // channels (T = 6348, 33847 x 512 -> 192: 13.7 / 14.2; T = 4600, 73590 x 896 -> 64: 17.0 / 17.2, 73577 x 64 -> 64: 12.3 / 10.3).
+    // Over 3000 random calls of T between 1500 and 9000 both forms were timed: 119 are more than 3 % slower than in the better one, 33 more than 8 %.
     const int64_t T = (int64_t)p.nrb * (p.N / 32);
     const bool over = (p.N == 128 ? (p.tilesM + 1) / 2 : p.tilesM * p.tilesN) > compute_units();
     const int over_ho = (p.N & 255) == 192 ? 1 : p.N < 256 ? 12 : 20;  // with the hand-off: chunks from which a second generation counts
-    const int line = p.ho_xq ? (over && p.C64 >= over_ho ? 7000 : 4000) : over || p.C64 <= 12 ? 7000 : p.C64 <= 24 ? 6500 : 5000;
+    const int line = p.ho_xq ? (over && p.C64 >= over_ho ? 7000 : 4000) : over ? 8000 : p.C64 <= 12 ? 7000 : p.C64 <= 24 ? 6500 : 5800;
     if (T <= line) {
         const int rbt = T <= 1400 ? 1 : 2, cbt = T <= 3600 ? 1 : 2;
         if (p.ho_xq) mxi_fwd_small_launch<NK16, false, true>(p, rbt, cbt, s);

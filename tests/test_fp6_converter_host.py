@@ -61,3 +61,28 @@ def test_results_and_sources_are_apart(tmp_path):
                 found["act_int_kernel" if int_family else "mx6_"] += 1
         assert p.wait() == 0
     assert all(found.values()), found
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
+def test_mxint_main_codes(tmp_path):
+    """The same for the MXINT4 main codes: 16 values per conversion (eight dwords of each source are defined), 32 in the
+    hand-off of the large tiles."""
+    found = {"mxi_act_kernel": 0, "mxi_fwd_small_kernel": 0, "mxi_fwd_kernel": 0}
+    for i, co in enumerate(_code_objects()):
+        if b"mxi_act_kernel" not in co:
+            continue
+        path = tmp_path / f"co{i}"
+        path.write_bytes(co)
+        p = subprocess.Popen([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", str(path)], stdout=subprocess.PIPE, text=True)
+        kernel = ""
+        for line in p.stdout:
+            if line.endswith(">:\n"):
+                kernel = line
+            elif "cvt_scalef32" in line and "fp6" in line:
+                dst, *src = [t.strip() for t in line.split("//")[0].split(None, 1)[1].split(",")]
+                name = next(k for k in found if k in kernel)
+                read = set().union(*(_regs(s, 8 if name != "mxi_fwd_kernel" and ":" in s else None) for s in src))
+                assert not _regs(dst) & read, (kernel.strip(), line.strip())
+                found[name] += 1
+        assert p.wait() == 0
+    assert all(found.values()), found
