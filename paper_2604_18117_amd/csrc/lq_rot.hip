@@ -6,12 +6,13 @@
 // ascending (the codes depend on their rounding); the rounding has zero derivative (App. B.2), so
 //     G = -2/(N r) L^T E1 - 2/(r K) R E2^T
 // and the update is the Cayley SGD with momentum of the work the paper cites for it (Li et al. 2020, Algorithm 1).
-// Four launches per step (three with block-scaled Q2), no atomics, every sum in a fixed order:
+// Four launches per step up to rank 32, five above (one less with block-scaled Q2), no atomics, every sum in a fixed order:
 //   rot_z_kernel      128 rows of L (or columns of R) per workgroup turn (64 at ranks 96 and 128): Z1 / Z2 on the fp32
 //                     matrix instruction, E1 / E2, their part of G, partial sums of squares.  A row of Z2 runs over all of
 //                     K, so with one scale per row a small launch before it leaves the row maxima of Z2
 //   rot_sum_kernel    G from the workgroups' parts (fp64), the loss
-//   rot_cayley_kernel one workgroup: momentum, the skew-symmetric W, step length, the fixed-point passes
+//   rot_cayley_kernel one workgroup: momentum, the skew-symmetric W, step length, the fixed-point passes; from rank 64 on
+//                     rot_wh_kernel and rot_update_kernel, a workgroup per 16 columns of Omega
 //
 // v_mfma_f32_16x16x4_f32 is, bit for bit, four fused multiply-adds in ascending order of its contraction index (checked
 // against fma chains on random operands over 2^+-12 and on subnormal products), so it evaluates the chains that
@@ -409,6 +410,7 @@ struct RotStepParams {
     float* M;          // momentum
     float* G;          // gradient of this step
     const float* gp;   // its parts, [parts][r][r]
+    float* Wh;         // r x r between the two launches of the update (over the first part, which has been added by then)
     const float* lp;   // partial sums of E1^2 (wL) then of E2^2
     float* loss;       // may be null
     int r, wL, parts;
@@ -449,25 +451,30 @@ __global__ __launch_bounds__(ROT_TPB) void rot_sum_kernel(RotStepParams p)
     if (wave == 0) p.G[e] = (float)((double)p.grad_scale * ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])));
 }
 
-// The update, one workgroup.  Every r x r product runs on the fp32 matrix instruction: wavefront w owns NT neighbouring
-// 16 x 16 tiles of one row of tiles.  Its left operand W (a row of tiles of the skew-symmetric matrix) stays in registers
-// over all products that use it; Omega and the right operand sit in LDS.  The contraction index is dealt so that lane
-// (l15, q) takes k = 16 s + 4 q + u in step (s, u): a left operand is then one 16-byte read per s, and with row strides
-// of 4 modulo 16 floats all reads of either operand are free of bank conflicts.
-template <int R> constexpr int rot_nt() { return R == 128 ? 4 : R == 96 ? 3 : 1; }
-template <int R> constexpr int rot_cayley_threads() { return (R / 16) * (R / 16) / rot_nt<R>() * 64; }
-template <int R> constexpr int rot_cayley_lds() { return 2 * R * (R + 4) * 4; }
+// The update.  Every r x r product runs on the fp32 matrix instruction; the contraction index is dealt so that lane
+// (l15, q) takes k = 16 s + 4 q + u in step (s, u): an operand read along its rows is one 16-byte read per s.
+//
+// Up to rank 32: one workgroup, a wavefront per 16 x 16 tile.  Its left operand W (a row of tiles of the skew-symmetric matrix)
+// stays in registers over all products that use it; Omega and the right operand sit in LDS, with row strides
+// of 4 modulo 16 floats, so that all reads of either operand are free of bank conflicts.
+template <int R> constexpr int rot_cayley_threads() { return (R / 16) * (R / 16) * 64; }
+template <int N>
+__device__ __forceinline__ float rot_step_length(const RotStepParams& p, const double* parts)  // of |W|^2
+{
+    double nrm2 = 0.0;
+    for (int w = 0; w < N; ++w) nrm2 += parts[w];
+    const float lim = 2.f * p.q / ((float)sqrt(nrm2) + p.eps);
+    return p.lr < lim ? p.lr : lim;
+}
 template <int R>
 __global__ __launch_bounds__(rot_cayley_threads<R>()) void rot_cayley_kernel(RotStepParams p)
 {
-    constexpr int T = R / 16, NT = rot_nt<R>(), S = R + 4, NTHR = rot_cayley_threads<R>(), NWV = NTHR / 64;
-    extern __shared__ __attribute__((aligned(16))) float lds[];
+    constexpr int T = R / 16, S = R + 4, NTHR = rot_cayley_threads<R>(), NWV = NTHR / 64;
+    __shared__ __attribute__((aligned(16))) float Xs[R * S], Ts[R * S];
     __shared__ double red[NWV];
-    float* Xs = lds;
-    float* Ts = lds + R * S;
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rb = wave / (T / NT), cb = (wave % (T / NT)) * NT;  // row of tiles, first column of tiles
+    const int rb = wave / T, cb = wave % T;  // row and column of tiles
     typedef v4f Left[T];
     Left va;
 #pragma unroll
@@ -482,20 +489,15 @@ __global__ __launch_bounds__(rot_cayley_threads<R>()) void rot_cayley_kernel(Rot
         *(v4f*)(Xs + row * S + 4 * c) = *(const v4f*)(p.X + 4 * e);
     }
     __syncthreads();
-    auto product = [&](auto left, auto right, v4f (&acc)[NT]) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+    auto product = [&](auto left, auto right) {
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < T; ++s) {
-            const v4f a = left(s);
-            v4f b[NT];
+            const v4f a = left(s), b = right(s);
 #pragma unroll
-            for (int t = 0; t < NT; ++t) b[t] = right(s, t);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[t][u], acc[t], 0, 0, 0);
+            for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[u], acc, 0, 0, 0);
         }
+        return acc;
     };
     auto cols = [&](const float* m, int s, int j0) {  // entries (16 s + 4 q + u, j0 + l15)
         v4f v;
@@ -504,25 +506,20 @@ __global__ __launch_bounds__(rot_cayley_threads<R>()) void rot_cayley_kernel(Rot
         return v;
     };
     auto rows = [&](const float* m, int s, int i0) { return *(const v4f*)(m + (i0 + l15) * S + 16 * s + 4 * q); };  // entries (i0 + l15, 16 s + 4 q + u)
-    auto put = [&](const v4f (&d)[NT]) {
+    auto put = [&](const v4f& d) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Ts[(16 * rb + 4 * q + i) * S + 16 * (cb + t) + l15] = d[t][i];
+        for (int i = 0; i < 4; ++i) Ts[(16 * rb + 4 * q + i) * S + 16 * cb + l15] = d[i];
     };
-    v4f A[NT], d[NT];
-    product([&](int s) { return va[s]; }, [&](int s, int t) { return rows(Xs, s, 16 * (cb + t)); }, A);      // A = (beta M - G) X^T
+    const v4f A = product([&](int s) { return va[s]; }, [&](int s) { return rows(Xs, s, 16 * cb); });             // A = (beta M - G) X^T
     put(A);
     __syncthreads();
-    product([&](int s) { return cols(Xs, s, 16 * rb); }, [&](int s, int t) { return cols(Ts, s, 16 * (cb + t)); }, d);  // B = X^T A
+    v4f d = product([&](int s) { return cols(Xs, s, 16 * rb); }, [&](int s) { return cols(Ts, s, 16 * cb); });    // B = X^T A
     __syncthreads();
     put(d);
     __syncthreads();
-    product([&](int s) { return rows(Xs, s, 16 * rb); }, [&](int s, int t) { return cols(Ts, s, 16 * (cb + t)); }, d);  // X B
+    d = product([&](int s) { return rows(Xs, s, 16 * rb); }, [&](int s) { return cols(Ts, s, 16 * cb); });        // X B
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) d[t][i] = A[t][i] - 0.5f * d[t][i];                                      // Wh
+    for (int i = 0; i < 4; ++i) d[i] = A[i] - 0.5f * d[i];                                                       // Wh
     __syncthreads();
     put(d);
     __syncthreads();
@@ -536,47 +533,162 @@ __global__ __launch_bounds__(rot_cayley_threads<R>()) void rot_cayley_kernel(Rot
             n2 += (double)va[s][u] * (double)va[s][u];
         }
     }
-    if (cb != 0) n2 = 0.0;  // the T / NT wavefronts of a row of tiles hold the same part of W
+    if (cb != 0) n2 = 0.0;  // the T wavefronts of a row of tiles hold the same part of W
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) n2 += __shfl_down(n2, o);
     if (lane == 0) red[wave] = n2;
     __syncthreads();
-    double nrm2 = 0.0;
-    for (int w = 0; w < NWV; ++w) nrm2 += red[w];
-    const float lim = 2.f * p.q / ((float)sqrt(nrm2) + p.eps);
-    const float alpha = p.lr < lim ? p.lr : lim;
-    v4f x[NT], y[NT];
+    const float alpha = rot_step_length<NWV>(p, red);
+    v4f x, y;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int i = 0; i < 4; ++i) x[i] = Xs[(16 * rb + 4 * q + i) * S + 16 * cb + l15];
+    auto store = [&](float* dst, const v4f& v) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[t][i] = Xs[(16 * rb + 4 * q + i) * S + 16 * (cb + t) + l15];
-    auto store = [&](float* dst, const v4f (&v)[NT]) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) dst[(16 * rb + 4 * q + i) * R + 16 * (cb + t) + l15] = v[t][i];
+        for (int i = 0; i < 4; ++i) dst[(16 * rb + 4 * q + i) * R + 16 * cb + l15] = v[i];
     };
-    product([&](int s) { return va[s]; }, [&](int s, int t) { return cols(Xs, s, 16 * (cb + t)); }, d);      // M = W X;  Y = X + alpha M
+    d = product([&](int s) { return va[s]; }, [&](int s) { return cols(Xs, s, 16 * cb); });                       // M = W X;  Y = X + alpha M
     store(p.M, d);
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) y[t][i] = __builtin_fmaf(alpha, d[t][i], x[t][i]);
+    for (int i = 0; i < 4; ++i) y[i] = __builtin_fmaf(alpha, d[i], x[i]);
     for (int it = 0; it < p.s; ++it) {                                                                      // Y <- X + alpha/2 W (X + Y)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) d[t][i] = x[t][i] + y[t][i];
         __syncthreads();
-        put(d);
+        put(x + y);
         __syncthreads();
-        product([&](int s) { return va[s]; }, [&](int s, int t) { return cols(Ts, s, 16 * (cb + t)); }, d);
+        d = product([&](int s) { return va[s]; }, [&](int s) { return cols(Ts, s, 16 * cb); });
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) y[t][i] = __builtin_fmaf(0.5f * alpha, d[t][i], x[t][i]);
+        for (int i = 0; i < 4; ++i) y[i] = __builtin_fmaf(0.5f * alpha, d[i], x[i]);
     }
     store(p.X, y);
+}
+
+// From rank 64 on: one compute unit's matrix rate would bound the update (12 r^3 operations), so every 16 columns of Omega have a
+// workgroup, with a wavefront per 16 x 16 tile of them: columns of Wh need no other columns of anything that is computed, nor do
+// columns of the fixed-point passes once W is there.  W = Wh - Wh^T and its norm need all of Wh, so there are two launches with Wh in
+// memory between them.  A workgroup requests everything it reads at once, straight into operand registers; only its own 16
+// columns pass through the LDS between products.  The sums are those of the one workgroup.  us
+// per step, one workgroup / this: 11200 x 64 and 64 x 2240 32.9 / 27.9, 3456 x 128 and 128 x 1152 (blocks) 88.4 / 48.0, 2304 x 96 and
+// 96 x 1152 (blocks) 47.0 / 32.3; the update alone 12.9 / 8.1 at rank 64, 60.4 / 19.4 at 128, of which the matrix cores take 5.8.  Up to rank
+// 32 the one workgroup (4.0) is ahead of two launches.
+template <int R>
+struct RotCols {  // 16 columns of an r x r matrix in the LDS, between two products: entry (k, column l15)
+    static constexpr int S = 20;  // row stride in floats: q moves by 16 banks
+    float (&m)[R * S];
+    __device__ __forceinline__ v4f get(int s, int l15, int q) const
+    {
+        v4f v;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = m[(16 * s + 4 * q + u) * S + l15];
+        return v;
+    }
+    __device__ __forceinline__ void put(const v4f& d, int rb, int l15, int q)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[(16 * rb + 4 * q + i) * S + l15] = d[i];
+    }
+};
+template <int R>
+struct RotSlab {  // left operands of a wavefront's row of tiles, from a row-major matrix in memory: entries (i0 + l15, 16 s + 4 q + u) or, transposed, their mirror
+    v4f v[R / 16];
+    __device__ __forceinline__ void rows(const float* m, int i0, int l15, int q)
+    {
+#pragma unroll
+        for (int s = 0; s < R / 16; ++s) v[s] = *(const v4f*)(m + (size_t)(i0 + l15) * R + 16 * s + 4 * q);
+    }
+    __device__ __forceinline__ void cols(const float* m, int i0, int l15, int q)
+    {
+#pragma unroll
+        for (int s = 0; s < R / 16; ++s)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[s][u] = m[(size_t)(16 * s + 4 * q + u) * R + i0 + l15];
+    }
+    template <typename F>
+    __device__ __forceinline__ v4f times(F right) const
+    {
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < R / 16; ++s) {
+            const v4f b = right(s);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v[s][u], b[u], acc, 0, 0, 0);
+        }
+        return acc;
+    }
+};
+
+template <int R>
+__global__ __launch_bounds__(R * 4) void rot_wh_kernel(RotStepParams p)  // Wh = A - 1/2 X (X^T A), A = (beta M - G) X^T
+{
+    __shared__ float as[R * RotCols<R>::S], bs[R * RotCols<R>::S];
+    const int lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4, cb = blockIdx.x;
+    const int rb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    RotSlab<R> m, g, xj, xt, xr;
+    m.rows(p.M, 16 * rb, l15, q);
+    g.rows(p.G, 16 * rb, l15, q);
+    xj.rows(p.X, 16 * cb, l15, q);
+    xt.cols(p.X, 16 * rb, l15, q);
+    xr.rows(p.X, 16 * rb, l15, q);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < R / 16; ++s)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m.v[s][u] = p.beta * m.v[s][u] - g.v[s][u];
+    RotCols<R> ac{as}, bc{bs};
+    const v4f A = m.times([&](int s) { return xj.v[s]; });
+    ac.put(A, rb, l15, q);
+    __syncthreads();
+    bc.put(xt.times([&](int s) { return ac.get(s, l15, q); }), rb, l15, q);
+    __syncthreads();
+    const v4f d = xr.times([&](int s) { return bc.get(s, l15, q); });
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p.Wh[(16 * rb + 4 * q + i) * R + 16 * cb + l15] = A[i] - 0.5f * d[i];
+}
+
+template <int R>
+__global__ __launch_bounds__(R * 4) void rot_update_kernel(RotStepParams p)
+{
+    constexpr int T = R / 16;
+    __shared__ float ts[2][R * RotCols<R>::S];
+    __shared__ double red[T];
+    const int lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4, cb = blockIdx.x;
+    const int rb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t tile = (size_t)(16 * rb + 4 * q) * R + 16 * cb + l15;
+    RotSlab<R> w, wt, xj;
+    w.rows(p.Wh, 16 * rb, l15, q);
+    wt.cols(p.Wh, 16 * rb, l15, q);
+    xj.cols(p.X, 16 * cb, l15, q);
+    v4f x, y;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = p.X[tile + (size_t)i * R];
+    __builtin_amdgcn_sched_barrier(0);
+    double n2 = 0.0;  // (every workgroup forms the whole norm, in the same order)
+#pragma unroll
+    for (int s = 0; s < T; ++s)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            w.v[s][u] -= wt.v[s][u];
+            n2 += (double)w.v[s][u] * (double)w.v[s][u];
+        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n2 += __shfl_down(n2, o);
+    if (lane == 0) red[rb] = n2;
+    v4f d = w.times([&](int s) { return xj.v[s]; });  // M = W X;  Y = X + alpha M
+    __syncthreads();                                 // (a wavefront's X is in registers by then: the columns stored below are this workgroup's own)
+    const float alpha = rot_step_length<T>(p, red);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        p.M[tile + (size_t)i * R] = d[i];
+        y[i] = __builtin_fmaf(alpha, d[i], x[i]);
+    }
+    for (int it = 0; it < p.s; ++it) {               // Y <- X + alpha/2 W (X + Y); two buffers: a pass overwrites what the pass before the last read
+        RotCols<R> tc{ts[it & 1]};
+        tc.put(x + y, rb, l15, q);
+        __syncthreads();
+        d = w.times([&](int s) { return tc.get(s, l15, q); });
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i] = __builtin_fmaf(0.5f * alpha, d[i], x[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p.X[tile + (size_t)i * R] = y[i];
 }
 
 __global__ __launch_bounds__(ROT_TPB) void rot_init_kernel(float* X, float* M, const float* X0, const float* M0, int r)
@@ -632,9 +744,14 @@ static hipError_t rot_launch_errors(const RotZParams& p, hipStream_t s)
 template <int R>
 static hipError_t rot_launch_cayley(const RotStepParams& p, hipStream_t s)
 {
-    const hipError_t e = allow_lds<rot_cayley_kernel<R>>(rot_cayley_lds<R>());
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((rot_cayley_kernel<R>), dim3(1), dim3(rot_cayley_threads<R>()), rot_cayley_lds<R>(), s, p);
+    if constexpr (R <= 32) {
+        hipLaunchKernelGGL((rot_cayley_kernel<R>), dim3(1), dim3(rot_cayley_threads<R>()), 0, s, p);
+    } else {
+        hipLaunchKernelGGL((rot_wh_kernel<R>), dim3(R / 16), dim3(R * 4), 0, s, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((rot_update_kernel<R>), dim3(R / 16), dim3(R * 4), 0, s, p);
+    }
     return hipGetLastError();
 }
 
@@ -734,6 +851,7 @@ static hipError_t rot_step_launches(const Dims& d, const float* L, const float* 
     p.M = (float*)(state + rl.off_M);
     p.G = (float*)(state + rl.off_G);
     p.gp = z.gp;
+    p.Wh = z.gp;
     p.lp = z.lp;
     p.loss = loss;
     p.r = d.r;

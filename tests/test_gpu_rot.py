@@ -240,3 +240,12 @@ def test_search_lowers_the_loss_and_keeps_the_product(oracle):
     P0 = L.astype(np.float64) @ R.astype(np.float64)
     P1 = Lr.cpu().numpy().astype(np.float64) @ Rr.cpu().numpy().astype(np.float64)
     assert np.abs(P1 - P0).max() < 2e-3 * np.abs(P0).max()
+
+
+@pytest.mark.parametrize("r,q2", [(64, "int"), (96, "mxint"), (128, "mxfp8")])
+@pytest.mark.parametrize("s", [0, 1, 5])
+def test_update_split_over_columns(oracle, r, q2, s):
+    """From rank 64 on every 16 columns of Omega have a workgroup: no fixed-point pass, one, and more than the two buffers
+    that the passes alternate between; the smallest factors."""
+    from paper_2604_18117_amd import binding as lq
+    _compare_step(oracle, lq, 64, 64, r, 8, seed=r + s, q2=q2, lr=0.5, beta=0.9, s=s, grad_scale=500.0)
