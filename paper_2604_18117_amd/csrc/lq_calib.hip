@@ -74,13 +74,6 @@ CalibLayout calib_layout(const Dims& d)
     return cl;
 }
 
-// The value lane N of each row of 16 lanes holds, in all 16.
-template <int N>
-__device__ __forceinline__ float row16_lane(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xF, 0xF, true));  // row_newbcast
-}
-
 // MX block scales and elements (App. A.3), the arithmetic of the MX pack kernels:
 // MXFP4: scale byte floor(log2 amax) - 2 + 127 clamped at 0; E2M1 element by the hardware converter (nearest even, saturating)
 __device__ __forceinline__ uint32_t mxfp4_scale_byte(float amax)

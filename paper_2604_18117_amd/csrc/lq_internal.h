@@ -294,6 +294,12 @@ __device__ __forceinline__ float max_row16(float v)
     v = max_dpp<0x141>(v);      // row_half_mirror
     return max_dpp<0x140>(v);   // row_mirror
 }
+// The value lane N of each row of 16 lanes holds, in all 16.
+template <int N>
+__device__ __forceinline__ float row16_lane(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xF, 0xF, true));  // row_newbcast
+}
 // ---- 6-bit main codes of the INT family (fragment order above) ----
 constexpr int F6_CHUNK = 1536;  // bytes of one (32-row block, 64-chunk)
 // byte offset, inside a chunk, of dword d (0..5) of lane `lane`'s operand

@@ -9,7 +9,7 @@
 // Four launches per step up to rank 32, five above (one less with block-scaled Q2), no atomics, every sum in a fixed order:
 //   rot_z_kernel      128 rows of L (or columns of R) per workgroup turn (64 at ranks 96 and 128): Z1 / Z2 on the fp32
 //                     matrix instruction, E1 / E2, their part of G, partial sums of squares.  A row of Z2 runs over all of
-//                     K, so with one scale per row a small launch before it leaves the row maxima of Z2
+//                     K, so with one scale per row a small launch before it, rot_max_kernel, leaves the row maxima of Z2
 //   rot_sum_kernel    G from the workgroups' parts (fp64), the loss
 //   rot_cayley_kernel one workgroup: momentum, the skew-symmetric W, step length, the fixed-point passes; from rank 64 on
 //                     rot_wh_kernel and rot_update_kernel, a workgroup per 16 columns of Omega
@@ -37,8 +37,9 @@ constexpr int ROT_TPB = 256;
 struct RotSplit {
     int gL, gR;   // groups
     int wL, wR;   // workgroups that form E1 and E2
-    int wM;       // workgroups that leave row maxima of Z2 (row kinds), 64 columns a turn
+    int wM;       // workgroups that leave row maxima of Z2 (row kinds), rot_max_cols columns a turn
 };
+static constexpr int rot_max_cols(int r) { return r <= 32 ? 64 : 16; }  // (rot_max_kernel)
 static RotSplit rot_split(const Dims& d)
 {
     const int cap = d.r <= 32 ? 256 : d.r == 64 ? 112 : 128, rows = d.r <= 64 ? 128 : 64;
@@ -49,7 +50,8 @@ static RotSplit rot_split(const Dims& d)
     w.wL = (w.gL + per - 1) / per;
     w.wR = w.gR < cap - w.wL ? w.gR : cap - w.wL;
     if (w.wR < 1) w.wR = 1;
-    w.wM = (int)(d.K / 64) < 256 ? (int)(d.K / 64) : 256;
+    const int sets = (int)d.K / rot_max_cols(d.r);
+    w.wM = sets < 256 ? sets : 256;
     return w;
 }
 
@@ -120,6 +122,15 @@ __device__ __forceinline__ float rot_err(float z, float s, float inv, float top)
     }
 }
 
+template <typename F>
+__device__ __forceinline__ void for_rows(F f)  // f(0) .. f(3) with the argument as a compile-time constant
+{
+    f(std::integral_constant<int, 0>{});
+    f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 3>{});
+}
+
 // Block kinds: the shared exponent floor(log2 amax) - (largest element exponent: 8 for E4M3, 2 for E2M3, 0 for MXINT),
 // kept in [-127, 127]; an all-zero block: -127.
 __device__ __forceinline__ int rot_block_exp(float amax, const RotQ& q)
@@ -158,17 +169,21 @@ struct RotZParams {
     float c1, c2;
 };
 
-// ROT_OUT: write Z1 and Z2.  ROT_MAX (row kinds): row maxima of Z2.  ROT_ERR: E1, E2 and their parts of G.
-enum { ROT_OUT, ROT_MAX, ROT_ERR };
+// ROT_OUT: write Z1 and Z2.  ROT_ERR: E1, E2 and their parts of G.
+enum { ROT_OUT, ROT_ERR };
 
 // LDS strides in floats, chosen for conflict-free operand reads: lane (l15, q) reads Omega[4 s + q][l15], so q has to move
-// by 16 banks; it reads row l15, column 4 s + q of the staged factor and, in the second contraction, row 16 s + 4 q + u,
-// column l15 of the factor and the error: a stride of 4 modulo 16 serves both.
+// by 16 banks; it reads row l15, column 4 s + q of the staged rows of L and, in the second contraction, row 16 s + 4 q + u,
+// column l15 of them and of the error: a stride of 4 modulo 16 serves both.  Columns of R are staged as they lie in memory, rows of
+// 16 NWV values: column l15 of row 4 s + q and, in the second contraction, 16 bytes (16 s + 4 q ..) of row l15 (transposed on the
+// way in, their stores met 8 to a bank: 9340 cycles from a workgroup's start to its first product at rank 64, 2700 for rows of L).
 template <int R> constexpr int rot_sx() { return R % 32 ? R : R + 16; }
 template <int R> constexpr int rot_sl() { return R + 4; }
-template <int R, int NWV> constexpr int rot_z_lds() { return (R * rot_sx<R>() + 2 * 16 * NWV * rot_sl<R>() + (NWV + 2) * R) * 4; }
+template <int NWV> constexpr int rot_sr() { return 16 * NWV + 16; }
+template <int R, int NWV> constexpr int rot_stage() { return 16 * NWV * rot_sl<R>() > R * rot_sr<NWV>() ? 16 * NWV * rot_sl<R>() : R * rot_sr<NWV>(); }
+template <int R, int NWV> constexpr int rot_z_lds() { return (R * rot_sx<R>() + rot_stage<R, NWV>() + 16 * NWV * rot_sl<R>() + (NWV + 2) * R) * 4; }
 
-// A workgroup turn is a group of 16 * NWV rows of L (columns of R, transposed on the way into LDS): each wavefront forms 16
+// A workgroup turn is a group of 16 * NWV rows of L (columns of R): each wavefront forms 16
 // rows of Z (R / 16 tiles of 16 x 16: lane (l15, q) holds rows 4 q + i, column l15), quantises them in registers, and
 // leaves the error in LDS, from where each of 4 wavefronts contracts one quadrant of G over their 64 rows; the quadrant
 // stays in registers over all turns, and 8 wavefronts add their two halves at the end.
@@ -176,59 +191,95 @@ template <int R, int NWV> constexpr int rot_z_lds() { return (R * rot_sx<R>() + 
 template <int R, int MODE, int QK, int NWV>
 __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
 {
-    constexpr int T = R / 16, H = T > 1 ? T / 2 : 1, SX = rot_sx<R>(), SL = rot_sl<R>();
+    constexpr int T = R / 16, H = T > 1 ? T / 2 : 1, SX = rot_sx<R>(), SL = rot_sl<R>(), SR = rot_sr<NWV>();
     constexpr int NTHR = 64 * NWV, ROWS = 16 * NWV;
     extern __shared__ __attribute__((aligned(16))) float lds[];
     float* Xs = lds;                 // Omega
     float* Ls = Xs + R * SX;         // the group's rows of L / columns of R
-    float* Es = Ls + ROWS * SL;      // their errors
+    float* Es = Ls + rot_stage<R, NWV>();  // their errors
     float* red = Es + ROWS * SL;     // [NWV][R] column maxima per wavefront
     float* sc = red + NWV * R;       // scale[R], 1 / scale[R] of the rows of Z2
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nL = MODE == ROT_MAX ? 0 : p.w.wL;
+    const int nL = p.w.wL;
     const bool left = (int)blockIdx.x < nL;
     const int wg = left ? blockIdx.x : blockIdx.x - nL;
     const int nwg = left ? nL : (int)gridDim.x - nL;
     const int nrows = left ? p.N : p.K;
     const int K = p.K;
 
-    for (int e = tid; e < R * R / 4; e += NTHR) {
-        const int row = e / (R / 4), c = e - row * (R / 4);
-        *(v4f*)(Xs + row * SX + 4 * c) = *(const v4f*)(p.X + 4 * e);
+    // the group's rows of L or columns of R: requested a turn ahead, the first with everything else a workgroup needs at its start
+    constexpr int NX = R * R / 4 / NTHR > 0 ? R * R / 4 / NTHR : 1, NG = ROWS * R / 4 / NTHR;
+    v4f xv[NX], lv[NG];
+    // (buffer loads: rows and columns past the end are out of range and read as zeros, without a branch the other side would wait at)
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    auto load_group = [&](int row0) {
+        const int n = nrows - row0 < ROWS ? nrows - row0 : ROWS;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(left ? p.L + (size_t)row0 * R : p.R + row0), 0, (left ? n * R : (R - 1) * K + n) * 4, 0x00020000);
+#pragma unroll
+        for (int e = 0; e < NG; ++e) {
+            const int f = tid + e * NTHR, i = f / (ROWS / 4), c = f & (ROWS / 4 - 1);
+            const uint32_t off = left ? 16u * f : 4 * c < n ? 4u * (uint32_t)(i * K + 4 * c) : ~0u;
+            lv[e] = __builtin_bit_cast(v4f, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+        }
+    };
+    if (wg * ROWS < nrows) load_group(wg * ROWS);
+    {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)p.X, 0, R * R * 4, 0x00020000);
+#pragma unroll
+        for (int e = 0; e < NX; ++e)
+            xv[e] = __builtin_bit_cast(v4f, (u4)__builtin_amdgcn_raw_buffer_load_b128(rs, 16u * (tid + e * NTHR), 0, 0));
     }
-    if (MODE == ROT_ERR && QK != 2 && !left) {  // scales of the rows of Z2
-        constexpr int SLICES = NTHR / R < NWV ? NTHR / R : NWV;
-        const int sl = tid / R, j = tid - sl * R;
-        if (sl < SLICES) {
-            float m = 0.f;
-            for (int i = sl; i < p.w.wM; i += 8 * SLICES) {  // (a maximum may see the last set more than once)
-                float f[8];
+    if (MODE == ROT_ERR && QK != 2 && !left) {  // scales of the rows of Z2, four rows to a thread
+        constexpr int SLICES = NTHR / (R / 4), PER = SLICES >= 256 ? 1 : 256 / SLICES < 8 ? 256 / SLICES : 8;
+        constexpr bool LANES = (R & (R - 1)) == 0;  // the lanes of a wavefront that hold the same rows are a power of two apart
+        constexpr int SETS = LANES ? NWV : SLICES;  // left to reduce through the LDS
+        const int sl = tid / (R / 4), j = 4 * (tid - sl * (R / 4));
+        v4f m = {0.f, 0.f, 0.f, 0.f};
+        for (int i = sl; i < p.w.wM; i += PER * SLICES) {  // (a maximum may see the last set more than once)
+            v4f f[PER];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) f[k] = p.ax[(size_t)(i + k * SLICES < p.w.wM ? i + k * SLICES : p.w.wM - 1) * R + j];
+            for (int k = 0; k < PER; ++k) f[k] = *(const v4f*)(p.ax + (size_t)(i + k * SLICES < p.w.wM ? i + k * SLICES : p.w.wM - 1) * R + j);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) m = fmaxf(m, f[k]);
+            for (int k = 0; k < PER; ++k)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) m[u] = fmaxf(m[u], f[k][u]);
+        }
+        // (the errors' buffer is not in use yet; a thread past the last whole slice, at rank 96, has nothing to add)
+        if constexpr (LANES) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if constexpr (R <= 16) m[u] = max_dpp<0x124>(m[u]);  // rotations within 16 lanes by 4 and by 8
+                if constexpr (R <= 32) m[u] = max_dpp<0x128>(m[u]);
+                if constexpr (R <= 64) m[u] = max_xor16(m[u]);
+                m[u] = max_xor32(m[u]);
             }
-            red[sl * R + j] = m;
+            if (lane < R / 4) *(v4f*)(Es + wave * R + j) = m;
+        } else if (sl < SLICES) {
+            *(v4f*)(Es + sl * R + j) = m;
         }
         __syncthreads();
         if (tid < R) {
-            float m = red[tid];
-            for (int i = 1; i < SLICES; ++i) m = fmaxf(m, red[i * R + tid]);
+            float a = Es[tid];
+#pragma unroll
+            for (int i = 1; i < SETS; ++i) a = fmaxf(a, Es[i * R + tid]);
             float s, inv;
-            rot_scale(m, p.q.top, s, inv);
+            rot_scale(a, p.q.top, s, inv);
             sc[tid] = s;
             sc[R + tid] = inv;
         }
+    }
+#pragma unroll
+    for (int e = 0; e < NX; ++e) {
+        const int f = tid + e * NTHR, row = f / (R / 4), c = f - row * (R / 4);
+        if (f < R * R / 4) *(v4f*)(Xs + row * SX + 4 * c) = xv[e];
     }
     v4f g[H][H];
 #pragma unroll
     for (int a = 0; a < H; ++a)
 #pragma unroll
         for (int b = 0; b < H; ++b) g[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
-    float mx[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) mx[t] = 0.f;
     float sq = 0.f;
     const int ha = (wave >> 1) & 1, hb = wave & 1, hg = wave >> 2;  // quadrant of G, half of the group it is contracted over
 
@@ -238,49 +289,56 @@ __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
         const bool live = NWV == 4 || row0 + 64 * hg < nrows;
         __syncthreads();  // the previous turn's contraction has read Ls and Es
         if (left) {
-            const float* src = p.L + (size_t)row0 * R;
-            const int n = (nrows - row0) * (R / 4);
 #pragma unroll
-            for (int e = 0; e < ROWS * R / 4 / NTHR; ++e) {
+            for (int e = 0; e < NG; ++e) {
                 const int f = tid + e * NTHR, row = f / (R / 4), c = f - row * (R / 4);
-                *(v4f*)(Ls + row * SL + 4 * c) = f < n ? *(const v4f*)(src + 4 * f) : v4f{0.f, 0.f, 0.f, 0.f};
+                *(v4f*)(Ls + row * SL + 4 * c) = lv[e];
             }
         } else {
-            const float* src = p.R + row0;
 #pragma unroll
-            for (int e = 0; e < ROWS * R / 4 / NTHR; ++e) {
+            for (int e = 0; e < NG; ++e) {
                 const int f = tid + e * NTHR, i = f / (ROWS / 4), c = f & (ROWS / 4 - 1);
-                const v4f v = row0 + 4 * c < nrows ? *(const v4f*)(src + (size_t)i * K + 4 * c) : v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int u = 0; u < 4; ++u) Ls[(4 * c + u) * SL + i] = v[u];
+                *(v4f*)(Ls + i * SR + 4 * c) = lv[e];
             }
         }
+        if (row0 + nwg * ROWS < nrows) load_group(row0 + nwg * ROWS);
         __syncthreads();
         v4f z[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) z[t] = v4f{0.f, 0.f, 0.f, 0.f};
         {
-            const float* ap = Ls + (16 * wave + l15) * SL + q;
             const float* bp = Xs + q * SX + l15;
+            auto chain = [&](const float* ap, auto step) {
 #pragma unroll 4
-            for (int s = 0; s < R / 4; ++s) {
-                const float a = ap[4 * s];
+                for (int s = 0; s < R / 4; ++s) {
+                    const float a = ap[s * decltype(step)::value];
 #pragma unroll
-                for (int t = 0; t < T; ++t) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bp[4 * s * SX + 16 * t], z[t], 0, 0, 0);
-            }
+                    for (int t = 0; t < T; ++t) z[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bp[4 * s * SX + 16 * t], z[t], 0, 0, 0);
+                }
+            };
+            if (left) chain(Ls + (16 * wave + l15) * SL + q, std::integral_constant<int, 4>{});
+            else chain(Ls + q * SR + 16 * wave + l15, std::integral_constant<int, 4 * SR>{});
         }
         float* dl = p.oL + (size_t)(row0 + 16 * wave + 4 * q) * R + l15;  // row 4 q + i, column 16 t + l15
         float* dr = p.oR + (size_t)l15 * K + row0 + 16 * wave + 4 * q;    // row 16 t + l15, columns 4 q ..
-        if constexpr (MODE == ROT_MAX) {
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-                mx[t] = fmaxf(mx[t], fmaxf(fmaxf(fabsf(z[t][0]), fabsf(z[t][1])), fmaxf(fabsf(z[t][2]), fabsf(z[t][3]))));
-            continue;
-        }
         if constexpr (MODE == ROT_ERR) {
             if (left) {
+                // (a row's maximum is in 16 lanes: lane i & 3 divides for row i and hands both factors to the others)
+                float sv = 1.f, iv = 1.f;
+                if constexpr (QK != 2) {
+                    float rm[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                    for (int i = 0; i < 4; ++i) {
+                        rm[i] = 0.f;
+#pragma unroll
+                        for (int t = 0; t < T; ++t) rm[i] = fmaxf(rm[i], fabsf(z[t][i]));
+                        rm[i] = max_row16(rm[i]);
+                    }
+                    const float lo = l15 & 1 ? rm[1] : rm[0], hi = l15 & 1 ? rm[3] : rm[2];
+                    rot_scale(l15 & 2 ? hi : lo, p.q.top, sv, iv);
+                }
+                for_rows([&](auto row) {
+                    constexpr int i = decltype(row)::value;
                     if constexpr (QK == 2) {
 #pragma unroll
                         for (int t = 0; t < T; t += 2) {  // (block kinds have rank >= 32: T is even)
@@ -290,15 +348,13 @@ __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
                             if (t1 > t) z[t1][i] = rot_err_block(z[t1][i], eb, p.q);
                         }
                     } else {
-                        float m = 0.f, s, inv;
-#pragma unroll
-                        for (int t = 0; t < T; ++t) m = fmaxf(m, fabsf(z[t][i]));
-                        rot_scale(max_row16(m), p.q.top, s, inv);
+                        const float s = row16_lane<i>(sv), inv = row16_lane<i>(iv);
 #pragma unroll
                         for (int t = 0; t < T; ++t) z[t][i] = rot_err<QK>(z[t][i], s, inv, p.q.top);
                     }
-                }
+                });
             } else if constexpr (QK == 2) {  // a block is 32 rows of the group: this wavefront's 16 and its neighbour's
+                float mx[T];
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
                     float m = fmaxf(fmaxf(fabsf(z[t][0]), fabsf(z[t][1])), fmaxf(fabsf(z[t][2]), fabsf(z[t][3])));
@@ -341,50 +397,54 @@ __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
                 }
             __syncthreads();
             if (T > 1 || (wave & 3) == 0) {
-                const float* ap = Ls + (64 * hg + 4 * q) * SL + 16 * H * ha + l15;
                 const float* bp = Es + (64 * hg + 4 * q) * SL + 16 * H * hb + l15;
+                auto contract = [&](auto left_operand) {  // row 16 s + 4 q + u in step (s, u)
 #pragma unroll 2
-                for (int s = 0; s < 4; ++s)
+                    for (int s = 0; s < 4; ++s) {
+                        v4f av[H];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        float av[H], bv[H];
+                        for (int a = 0; a < H; ++a) av[a] = left_operand(s, a);
 #pragma unroll
-                        for (int a = 0; a < H; ++a) av[a] = ap[(16 * s + u) * SL + 16 * a];
+                        for (int u = 0; u < 4; ++u) {
+                            float bv[H];
 #pragma unroll
-                        for (int b = 0; b < H; ++b) bv[b] = bp[(16 * s + u) * SL + 16 * b];
+                            for (int b = 0; b < H; ++b) bv[b] = bp[(16 * s + u) * SL + 16 * b];
 #pragma unroll
-                        for (int a = 0; a < H; ++a)
+                            for (int a = 0; a < H; ++a)
 #pragma unroll
-                            for (int b = 0; b < H; ++b) g[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], g[a][b], 0, 0, 0);
+                                for (int b = 0; b < H; ++b) g[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a][u], bv[b], g[a][b], 0, 0, 0);
+                        }
                     }
+                };
+                if (left) {
+                    const float* ap = Ls + (64 * hg + 4 * q) * SL + 16 * H * ha + l15;
+                    contract([&](int s, int a) {
+                        v4f v;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) v[u] = ap[(16 * s + u) * SL + 16 * a];
+                        return v;
+                    });
+                } else {
+                    const float* ap = Ls + (16 * H * ha + l15) * SR + 64 * hg + 4 * q;
+                    contract([&](int s, int a) { return *(const v4f*)(ap + 16 * a * SR + 16 * s); });
+                }
             }
         }
-    }
-    if constexpr (MODE == ROT_MAX) {
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            float m = fmaxf(mx[t], __shfl_xor(mx[t], 16));
-            m = fmaxf(m, __shfl_xor(m, 32));
-            if (q == 0) red[wave * R + 16 * t + l15] = m;
-        }
-        __syncthreads();
-        if (tid < R) p.ax[(size_t)wg * R + tid] = fmaxf(fmaxf(red[tid], red[R + tid]), fmaxf(red[2 * R + tid], red[3 * R + tid]));
     }
     if constexpr (MODE == ROT_ERR) {
         const int part = left ? wg : p.w.wL + wg;
         const float c = left ? p.c1 : p.c2;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sq += __shfl_down(sq, o);
-        __syncthreads();
-        if (lane == 0) red[wave] = sq;
         const bool owner = T > 1 || (wave & 3) == 0;
-        v4f* other = (v4f*)Es + (wave & 3) * H * H * 64 + lane;
+        v4f* other = (v4f*)Xs + (wave & 3) * H * H * 64 + lane;  // (Omega has been read)
         if (NWV == 8 && hg == 1 && owner) {
 #pragma unroll
             for (int a = 0; a < H; ++a)
 #pragma unroll
                 for (int b = 0; b < H; ++b) other[(a * H + b) * 64] = g[a][b];
         }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_down(sq, o);
+        if (lane == 0) red[wave] = sq;
         __syncthreads();
         if (hg == 0 && owner) {
             float* o = p.gp + (size_t)part * R * R + (16 * H * ha + 4 * q) * R + 16 * H * hb + l15;
@@ -405,6 +465,43 @@ __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
     }
 }
 
+// Row maxima of Z2 (row kinds), ahead of rot_z_kernel: a wavefront per 16 columns of R and 16 rows of Z2, both operands straight
+// into registers.  Latency alone bounds it: through the LDS, 64
+// columns to a workgroup of four wavefronts, it took 5.2 us at rank 64 and 13.5 at 128, now 3.3 and 5.5.  Up to rank 32 a workgroup takes 64 columns (3.6 / 2.6 us at rank 32): rot_z_kernel reads a set of maxima
+// per workgroup, and above that many sets would cost it more than the columns side by side save here.
+template <int R>
+__global__ __launch_bounds__(4 * R * (rot_max_cols(R) / 16)) void rot_max_kernel(RotZParams p)
+{
+    constexpr int T = R / 16, G = rot_max_cols(R) / 16;
+    __shared__ float red[G][R];
+    const int lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = wave % T, g = wave / T;
+    float a[R / 4], b[R / 4], m = 0.f;
+#pragma unroll
+    for (int s = 0; s < R / 4; ++s) b[s] = p.X[(4 * s + q) * R + 16 * t + l15];
+    for (int c0 = 16 * (G * (int)blockIdx.x + g); c0 < p.K; c0 += 16 * G * (int)gridDim.x) {
+#pragma unroll
+        for (int s = 0; s < R / 4; ++s) a[s] = p.R[(size_t)(4 * s + q) * p.K + c0 + l15];
+        v4f z = {0.f, 0.f, 0.f, 0.f};  // rows: columns c0 + 4 q + i of R, column: row 16 t + l15 of Z2
+#pragma unroll
+        for (int s = 0; s < R / 4; ++s) z = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], z, 0, 0, 0);
+        m = fmaxf(m, fmaxf(fmaxf(fabsf(z[0]), fabsf(z[1])), fmaxf(fabsf(z[2]), fabsf(z[3]))));
+    }
+    m = max_xor32(max_xor16(m));
+    if constexpr (G == 1) {
+        if (q == 0) p.ax[(size_t)blockIdx.x * R + 16 * t + l15] = m;
+    } else {
+        if (q == 0) red[g][16 * t + l15] = m;
+        __syncthreads();
+        if (threadIdx.x < R) {
+            m = red[0][threadIdx.x];
+#pragma unroll
+            for (int i = 1; i < G; ++i) m = fmaxf(m, red[i][threadIdx.x]);
+            p.ax[(size_t)blockIdx.x * R + threadIdx.x] = m;
+        }
+    }
+}
+
 struct RotStepParams {
     float* X;          // Omega
     float* M;          // momentum
@@ -419,36 +516,44 @@ struct RotStepParams {
     int s;
 };
 
-// G = grad_scale * (sum of the parts), 64 entries per workgroup, the parts dealt to its 4 wavefronts (all of a thread's loads
-// are independent); the last workgroup sums the loss.  A launch of its own: read by the single workgroup of the
-// update, the parts (1.8 MB at rank 64) would pass through one CU.
-__global__ __launch_bounds__(ROT_TPB) void rot_sum_kernel(RotStepParams p)
+// G = grad_scale * (sum of the parts), 64 entries per workgroup, the parts dealt to its W wavefronts, D loads of a thread in
+// flight (16 wavefronts, or 4 where the parts are few); the last workgroup sums the loss.  A launch of its own: read by the
+// workgroups of the update, the parts (1.8 MB at rank 64) would pass through each of their compute units.
+template <int W, int D>
+__global__ __launch_bounds__(64 * W) void rot_sum_kernel(RotStepParams p)
 {
-    __shared__ double red[4][64];
+    __shared__ double red[W][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rr = p.r * p.r;
-    if (blockIdx.x == gridDim.x - 1) {
+    double v = 0.0;
+    const bool of_loss = blockIdx.x == gridDim.x - 1;
+    if (of_loss) {
         double a = 0.0, b = 0.0;
-        for (int i = tid; i < p.parts; i += ROT_TPB) (i < p.wL ? a : b) += (double)p.lp[i];
-        double v = a * (double)p.inv1 + b * (double)p.inv2;
+        for (int i = tid; i < p.parts; i += 64 * W) (i < p.wL ? a : b) += (double)p.lp[i];
+        v = a * (double)p.inv1 + b * (double)p.inv2;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
-        if (lane == 0) red[wave][0] = v;
-        __syncthreads();
-        if (tid == 0 && p.loss) *p.loss = (float)((red[0][0] + red[1][0]) + (red[2][0] + red[3][0]));
-        return;
-    }
-    const int e = blockIdx.x * 64 + lane;
-    double g = 0.0;
-    for (int w = wave; w < p.parts; w += 64) {  // 16 loads in flight; a part past the last is the last one again, not added
-        float f[16];
+    } else {
+        const float* gp = p.gp + blockIdx.x * 64 + lane;
+        for (int w = wave; w < p.parts; w += D * W) {  // (a part past the last is the last one again, not added)
+            float f[D];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) f[k] = p.gp[(size_t)(w + 4 * k < p.parts ? w + 4 * k : p.parts - 1) * rr + e];
+            for (int k = 0; k < D; ++k) f[k] = gp[(size_t)(w + W * k < p.parts ? w + W * k : p.parts - 1) * rr];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) g += w + 4 * k < p.parts ? (double)f[k] : 0.0;
+            for (int k = 0; k < D; ++k) v += w + W * k < p.parts ? (double)f[k] : 0.0;
+        }
     }
-    red[wave][lane] = g;
+    red[wave][lane] = v;
     __syncthreads();
-    if (wave == 0) p.G[e] = (float)((double)p.grad_scale * ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])));
+    if (of_loss) {
+        if (tid == 0 && p.loss) {
+            for (int w = 1; w < W; ++w) v += red[w][0];
+            *p.loss = (float)v;
+        }
+    } else if (wave == 0) {
+#pragma unroll
+        for (int w = 1; w < W; ++w) v += red[w][lane];
+        p.G[blockIdx.x * 64 + lane] = (float)((double)p.grad_scale * v);
+    }
 }
 
 // The update.  Every r x r product runs on the fp32 matrix instruction; the contraction index is dealt so that lane
@@ -732,7 +837,8 @@ static hipError_t rot_launch_errors(const RotZParams& p, hipStream_t s)
 {
     constexpr int NWV = R <= 64 ? 8 : 4;  // (rot_split's group)
     if (p.q.kind <= 1) {
-        const hipError_t e = rot_launch_z<R, ROT_MAX, 0, 4>(p, p.w.wM, s);
+        hipLaunchKernelGGL((rot_max_kernel<R>), dim3(p.w.wM), dim3(4 * R * (rot_max_cols(R) / 16)), 0, s, p);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (p.q.kind == 0) return rot_launch_z<R, ROT_ERR, 0, NWV>(p, p.w.wL + p.w.wR, s);
@@ -869,7 +975,8 @@ static hipError_t rot_step_launches(const Dims& d, const float* L, const float* 
         constexpr int R = decltype(rank)::value;
         hipError_t e = rot_launch_errors<R>(z, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(rot_sum_kernel, dim3(R * R / 64 + 1), dim3(ROT_TPB), 0, s, p);
+        if (p.parts > 64) hipLaunchKernelGGL((rot_sum_kernel<16, 8>), dim3(R * R / 64 + 1), dim3(1024), 0, s, p);
+        else hipLaunchKernelGGL((rot_sum_kernel<4, 16>), dim3(R * R / 64 + 1), dim3(256), 0, s, p);
         e = hipGetLastError();
         return e != hipSuccess ? e : rot_launch_cayley<R>(p, s);
     });
