@@ -14,28 +14,39 @@ namespace lq {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// A workgroup owns 128 columns of W and a run of row blocks of 64 rows (128 at rank 64, whose LDS image leaves no room for a
-// second workgroup per CU: 8 wavefronts instead of 4).  Each leaves one r x 128 part of grad_R for its run and one
-// 64 x r part of grad_L per row block and column block.  The runs are as long as they can be with every workgroup slot
-// of the device still taken (two per CU up to rank 32), so that grad_R has few parts.
+// A workgroup owns 128 columns of W and a run of row blocks of 16 rows per wavefront.  It leaves one r x 128 part of grad_R
+// for its run and one part of grad_L, 16 rows x r, per wavefront and row block.  The runs are as long as they can be with
+// every workgroup slot of the device still taken, so that grad_R has few parts.  Up to rank 64 a workgroup has 8 wavefronts
+// (half the parts of grad_R that two workgroups of 4 on the same compute unit leave), or 4 where that shortens
+// the longest chain of strips on a compute unit (us a step, 8 / 4: 1152 x 1152 rank 64 23.9 / 19.8; at equal chains 3456 x 1152 rank 64
+// 29.9 / 31.7); from rank 96 on the LDS holds 4.
 constexpr int CALIB_COLS = 128;
-static constexpr int calib_waves(int r) { return r == 64 ? 8 : 4; }
 struct CalibSplit {
+    int waves;      // wavefronts per workgroup
     int cblocks;    // column blocks = parts of grad_L
     int rblocks;    // row blocks
     int splits;     // runs of row blocks = parts of grad_R
     int per;        // row blocks per run
 };
-static CalibSplit calib_split(const Dims& d)
+static CalibSplit calib_split(const Dims& d, int waves, int slots)
 {
     CalibSplit c;
-    const int rows = 16 * calib_waves(d.r), slots = d.r <= 32 ? 512 : 256;
+    const int rows = 16 * waves;
+    c.waves = waves;
     c.cblocks = (int)((d.K + CALIB_COLS - 1) / CALIB_COLS);
     c.rblocks = (int)((d.N + rows - 1) / rows);
     const int want = slots > c.cblocks ? slots / c.cblocks : 1;
     c.per = (c.rblocks + want - 1) / want;
     c.splits = (c.rblocks + c.per - 1) / c.per;
     return c;
+}
+static CalibSplit calib_split(const Dims& d)
+{
+    if (d.r > 64) return calib_split(d, 4, 256);
+    // (two workgroups of 4 wavefronts share a compute unit up to rank 32; at rank 64 the LDS holds one)
+    const CalibSplit c8 = calib_split(d, 8, 256), c4 = calib_split(d, 4, d.r <= 32 ? 512 : 256);
+    const int chain8 = 8 * c8.per, chain4 = (c4.cblocks * c4.splits > 256 ? 8 : 4) * c4.per;
+    return chain4 < chain8 && (d.r <= 32 || c4.per == 1) ? c4 : c8;
 }
 
 CalibLayout calib_layout(const Dims& d)
@@ -84,9 +95,9 @@ __device__ __forceinline__ uint32_t mxfp4_scale_byte(float amax)
 __device__ __forceinline__ float e8m0_as_float(uint32_t E) { return E ? __uint_as_float(E << 23) : __uint_as_float(0x00400000u); }
 __device__ __forceinline__ float e2m1_value(uint32_t c)  // 1 sign, 2 exponent (bias 1), 1 mantissa bit
 {
-    const uint32_t m = c & 7u;
-    const float mag = m < 2u ? 0.5f * (float)m : ldexpf(1.0f + 0.5f * (float)(m & 1u), (int)(m >> 1) - 1);
-    return (c & 8u) ? -mag : mag;
+    const uint32_t m = c & 7u;  // (branch-free: a code from 2 on is the top of a float's bits)
+    const uint32_t mag = m < 2u ? (m ? 0x3F000000u : 0u) : (m << 22) + (126u << 23);
+    return __uint_as_float(mag | (c & 8u) << 28);
 }
 // MXINT4: shared exponent = the fp32 exponent field of amax; code = clamp(rne(v 2^(2 - s)), -7, 7), value = code 2^(s - 2)
 __device__ __forceinline__ float mxint4_round(float v, uint32_t field)
@@ -118,110 +129,140 @@ struct CalibParams {
     CalibSplit c;
 };
 
-// LDS images.  L and E, row strides of 4 modulo 16 floats: the 16-byte operand reads (row l15, four columns at 4 q) and the
-// reads of a column over rows 16 s + 4 q + u touch every bank once (the counter shows 0.9 conflict cycles per LDS instruction, with
-// the stores of L and the 16-byte reads' own passes).  R is read over rows 4 s + q as well: rows of
-// 128 floats, the column's bits 4..5 exchanged by the row's bits 0..1 and bits 2..3 by the row's bits 2..3.
-__device__ __forceinline__ int calib_rs(int row, int col) { return row * CALIB_COLS + (col ^ (16 * (row & 3)) ^ (row & 12)); }
-template <int R> constexpr int calib_lds() { return (16 * calib_waves(R) * (R + 4 + CALIB_COLS + 4) + R * CALIB_COLS) * 4; }
+// LDS images: R as a [r][SC] block shared by the workgroup, L as [16][SL] and E as [16][SC] per wavefront, row strides of 4
+// modulo 16 floats: 16-byte reads along a row, 16-byte reads of 16 rows at one column and reads of one column over
+// rows 4 q + u each touch every bank once per 16 lanes.
+constexpr int CALIB_SC = CALIB_COLS + 4;
+// (Behind the loop the same memory takes 32 rank indexes of every wavefront's grad_R.)
+constexpr int calib_lds(int r, int waves, bool one)
+{
+    const int images = r * CALIB_SC + waves * 16 * (r + 4 + CALIB_SC), sums = waves * (r < 32 ? r : 32) * CALIB_SC;
+    return (one || images > sums ? images : sums) * 4;
+}
+
+// Orders a wavefront's own LDS stores before its lanes' reads of each other's values (the LDS serves a wavefront in order).
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_sched_barrier(0); }
+
+// The maximum over the 8 lanes of each half row.
+__device__ __forceinline__ float max_row8(float v)
+{
+    v = max_dpp<0xB1>(v);        // quad_perm [1,0,3,2]
+    v = max_dpp<0x4E>(v);        // quad_perm [2,3,0,1]
+    return max_dpp<0x141>(v);    // row_half_mirror
+}
 
 // All three products on v_mfma_f32_16x16x4_f32 (lane (l15, q) holds rows 4 q + i, column l15 of a 16 x 16 result tile).
 // The instruction is, bit for bit, four fused multiply-adds in ascending order of its contraction index, so V = W + L R with
-// W as the initial accumulator is exactly the chain that defines V.  Each wavefront owns 16 rows x 128 columns of
-// the tile for V, the quantiser (row maxima by lane exchange inside 16 lanes) and grad_L, and 128 / NWV columns of all the
-// block's rows for grad_R; E passes through the LDS between them (and to memory, written once).
-// 3456 x 1152 at rank 32: 15-17.6 us (20 + 8.2 + 8.1 us as three kernels, with E read back twice).  Memory is 44 MB of that
-// (W, E and 12 MB of gradient parts: 9 us at 5 TB/s), the matrix pipe is busy 4.9 us and the vector ALU 3 us; the rest is
-// that all workgroups are resident at once and go through the same phases together.
+// W as the initial accumulator is exactly the chain that defines V.  A wavefront works alone on strips of 16 rows x 128
+// columns: tile (h, u) of the eight holds columns 64 h + 4 l15 + u, so W, E and the rows of R move 16 bytes per lane.
+// ONE (runs of one row block): E and L of all strips lie in the LDS, and behind a barrier every wavefront sums grad_R for its
+// own 128 / NWV columns.  Otherwise V's registers are, as they lie, the second operand of grad_R (contraction over the strip's
+// rows, row 4 q + u in step u), which a wavefront sums over its run in registers; grad_L (contraction over columns) takes E through
+// the wavefront's own part of the LDS; there is no barrier inside the run, so wavefronts drift apart and one's loads
+// and stores lie beside another's products, and the next strip is requested as soon as the strip's registers are free.  The sum
+// over the wavefronts behind the run moves 16 r x 128 floats through the LDS: a run of one block is shorter without it.
+// What bounds it: all wavefronts of a short run load, multiply and store at the same time (3456 x 1152 at rank 32: 44 MB, 9 us at 5 TB/s,
+// then 5.7 us of the matrix unit); long runs the matrix unit.  Against one kernel form with barriers between all phases,
+// dword loads and stores and E read back for grad_R (us a step): 3456 x 1152 rank 16 16.3 -> 14.5, rank 32 22.1 -> 19.8, rank 64
+// 30.5 -> 29.9, 4608 x 1152 MXFP4 rank 32 34.0 -> 28.6, 11200 x 2240 rank 16 54.3 -> 46.3, rank 32 75.0 -> 69.2, rank 64 134.4 -> 118.2,
+// rank 128 254.5 -> 214.4.  A run of one strip in the other form: 3456 x 1152 rank 32 20.1, rank 64 31.4.
 // GT: 16-column tiles per scale group (4: 64 values, 8: 128, 2: MX block of 32).
 // Q: 0 INT4 groups (fp32 scale), 1 SINT4 blocks, 2 MXFP4, 3 MXINT4.
-template <int R, int Q, int GT>
-__global__ __launch_bounds__(64 * calib_waves(R), calib_waves(R) == 4 && R > 64 ? 1 : 2) void calib_err_kernel(CalibParams p)
+template <int R, int Q, int GT, int NWV, bool ONE>
+__global__ __launch_bounds__(64 * NWV, R > 64 || (R == 64 && NWV == 4) ? 1 : 2) void calib_err_kernel(CalibParams p)
 {
-    constexpr int NWV = calib_waves(R), NTHR = 64 * NWV, ROWS = 16 * NWV, T = R / 16, CT = 8 / NWV;
-    constexpr int SL = R + 4, SC = CALIB_COLS + 4;
+    constexpr int NTHR = 64 * NWV, T = R / 16, SL = R + 4, SC = CALIB_SC;
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    float* Rs = lds;                 // [R][128]   the column block of R (calib_rs)
-    float* Ls = Rs + R * CALIB_COLS;       // [ROWS][SL] the row block of L
-    float* Es = Ls + ROWS * SL;      // [ROWS][SC]
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float* Rs = lds;                                   // [R][SC]      the column block of R
+    float* Es = Rs + R * SC + wave * 16 * SC;          // [16][SC]     the wavefront's strip of E
+    float* Ls = Rs + R * SC + NWV * 16 * SC + wave * 16 * SL;  // [16][SL] its rows of L
     const int cb = blockIdx.x % p.c.cblocks, split = blockIdx.x / p.c.cblocks;
     const int N = p.N, K = p.K, col0 = cb * CALIB_COLS;
-    const int ncol = K - col0 < CALIB_COLS ? K - col0 : CALIB_COLS;  // 128, or 64 in the last block
+    const bool full = K - col0 >= CALIB_COLS;          // else the last block, of 64 columns
+    const int ncol = full ? CALIB_COLS : 64;
 
     // (an out-of-range column of the last block is loaded from the block's first columns and replaced by zero)
-    constexpr int NR = R * CALIB_COLS / 4 / NTHR, NL = ROWS * R / 4 / NTHR;
+    constexpr int NR = R * CALIB_COLS / 4 / NTHR;
     v4f rv[NR];
 #pragma unroll
     for (int e = 0; e < NR; ++e) {
         const int f = tid + e * NTHR, row = f / (CALIB_COLS / 4), c = 4 * (f % (CALIB_COLS / 4));
         rv[e] = *(const v4f*)(p.R + (size_t)row * K + col0 + (c < ncol ? c : c - 64));
     }
+    v4f w[2][4], lv[T];
+    // (wave-uniform bases with one 32-bit offset per lane: 64-bit lane addresses of every row would not fit beside grad_R)
+    const uint32_t wo = 4u * ((uint32_t)(4 * q) * (uint32_t)K + (uint32_t)(4 * l15));
+    auto request = [&](int wrow) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float* wp = p.W + (size_t)(wrow + i) * K + col0 + (full ? 64 * h : 0);
+                w[h][i] = *(const v4f*)((const char*)wp + wo);
+            }
+    };
+    auto request_l = [&](int wrow) {
+#pragma unroll
+        for (int e = 0; e < T; ++e) lv[e] = *(const v4f*)((const char*)(p.L + (size_t)wrow * R + 256 * e) + (uint32_t)(16 * lane));
+    };
+    auto store_l = [&] {
+#pragma unroll
+        for (int e = 0; e < T; ++e) {
+            const int f = lane + e * 64, row = f / (R / 4), c = f - row * (R / 4);
+            *(v4f*)(Ls + row * SL + 4 * c) = lv[e];
+        }
+    };
+    constexpr int ROWS = 16 * NWV;
+    int wrow = split * p.c.per * ROWS + 16 * wave;
+    const int run_end = (split + 1) * p.c.per * ROWS, row_end = run_end < N ? run_end : N;
+    const bool any = wrow < row_end;
+    if (any) {
+        request(wrow);
+        request_l(wrow);
+    }
+#pragma unroll
+    for (int e = 0; e < NR; ++e) {
+        const int f = tid + e * NTHR, row = f / (CALIB_COLS / 4), c = 4 * (f % (CALIB_COLS / 4));
+        *(v4f*)(Rs + row * SC + c) = c < ncol ? rv[e] : v4f{0.f, 0.f, 0.f, 0.f};
+    }
+    constexpr int CT = ONE ? 8 / NWV : 8;  // 16-column tiles of grad_R a wavefront sums
     v4f gr[T][CT];
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int c = 0; c < CT; ++c) gr[t][c] = v4f{0.f, 0.f, 0.f, 0.f};
     float lsum = 0.f;
-    const int rb_end = (split + 1) * p.c.per < p.c.rblocks ? (split + 1) * p.c.per : p.c.rblocks;
-    for (int rb = split * p.c.per; rb < rb_end; ++rb) {
-        const int row0 = rb * ROWS, wrow = row0 + 16 * wave;
-        const bool live = wrow < N;  // (N is a multiple of 64: only the upper half of a 128-row block can be missing)
-        // everything this block needs from memory is requested before anything is waited for
+    if (any) {
+        store_l();
+    } else if constexpr (ONE) {  // a strip past N is zeros in grad_R
+#pragma unroll
+        for (int e = 0; e < T; ++e) lv[e] = v4f{0.f, 0.f, 0.f, 0.f};
+        store_l();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *(v4f*)(Es + (2 * i + (lane >> 5)) * SC + 4 * (lane & 31)) = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+    __syncthreads();
+    for (; wrow < row_end; wrow = ONE ? row_end : wrow + ROWS) {
         v4f v[8];
-        const float* wp = p.W + (size_t)((live ? wrow : row0) + 4 * q) * K + col0 + l15;
-        if (ncol == CALIB_COLS) {
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
+        for (int t = 0; t < 8; ++t)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[t][i] = wp[(size_t)i * K + 16 * t];
-        } else {
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[t][i] = t < 4 ? wp[(size_t)i * K + 16 * t] : 0.f;
-        }
-        v4f lv[NL];
+            for (int i = 0; i < 4; ++i) v[t][i] = t < 4 || full ? w[t >> 2][i][t & 3] : 0.f;
+        wave_lds_fence();
         {
-            const float* src = p.L + (size_t)row0 * R;
-            const int n = (N - row0) * (R / 4);
-#pragma unroll
-            for (int e = 0; e < NL; ++e) {
-                const int f = tid + e * NTHR;
-                lv[e] = *(const v4f*)(src + 4 * (NWV == 4 || f < n ? f : f - n));
-            }
-        }
-        __syncthreads();  // the previous block's products have read Ls and Es
-        if (rb == split * p.c.per) {
-#pragma unroll
-            for (int e = 0; e < NR; ++e) {
-                const int f = tid + e * NTHR, row = f / (CALIB_COLS / 4), c = 4 * (f % (CALIB_COLS / 4));
-                *(v4f*)(Rs + calib_rs(row, c)) = c < ncol ? rv[e] : v4f{0.f, 0.f, 0.f, 0.f};
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < NL; ++e) {
-            const int f = tid + e * NTHR, row = f / (R / 4), c = f - row * (R / 4);
-            *(v4f*)(Ls + row * SL + 4 * c) = NWV == 4 || row0 + row < N ? lv[e] : v4f{0.f, 0.f, 0.f, 0.f};
-        }
-        if (NWV == 8 && !live) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) v[t] = v4f{0.f, 0.f, 0.f, 0.f};
-        }
-        __syncthreads();
-        {
-            const float* ap = Ls + (16 * wave + l15) * SL + q;
-#pragma unroll 8
+            const float* ap = Ls + l15 * SL + q;
+            const float* bp = Rs + q * SC + 4 * l15;
+#pragma unroll 4
             for (int s = 0; s < R / 4; ++s) {
                 const float a = ap[4 * s];
+                const v4f b0 = *(const v4f*)(bp + 4 * s * SC), b1 = *(const v4f*)(bp + 4 * s * SC + 64);
 #pragma unroll
-                for (int t = 0; t < 8; ++t) v[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Rs[calib_rs(4 * s + q, 16 * t + l15)], v[t], 0, 0, 0);
+                for (int t = 0; t < 8; ++t) v[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, t < 4 ? b0[t & 3] : b1[t & 3], v[t], 0, 0, 0);
             }
         }
-        float* ep = p.E + (size_t)(wrow + 4 * q) * K + col0 + l15;
-        float* es = Es + (16 * wave + 4 * q) * SC + l15;
-        constexpr int NG = 8 / GT;  // scale groups side by side; a lane holds 4 rows of each
+        constexpr int NG = GT == 8 ? 1 : 2, NT = 8 / NG;  // scale groups a lane has values of (4 rows of each), its tiles in each
         float am[NG][4];
 #pragma unroll
         for (int g = 0; g < NG; ++g)
@@ -229,8 +270,8 @@ __global__ __launch_bounds__(64 * calib_waves(R), calib_waves(R) == 4 && R > 64 
             for (int i = 0; i < 4; ++i) {
                 float a = 0.f;
 #pragma unroll
-                for (int t = g * GT; t < (g + 1) * GT; ++t) a = fmaxf(a, fabsf(v[t][i]));
-                am[g][i] = max_row16(a);
+                for (int t = g * NT; t < (g + 1) * NT; ++t) a = fmaxf(a, fabsf(v[t][i]));
+                am[g][i] = GT == 2 ? max_row8(a) : max_row16(a);
             }
         // INT / SINT4 scales need correctly rounded divisions: the 16 lanes that share a row's maxima share the work, lane
         // 4 g + i dividing for (g, i) and handing the result to the others (two divisions per lane instead of 2 * 4 * NG)
@@ -262,7 +303,7 @@ __global__ __launch_bounds__(64 * calib_waves(R), calib_waves(R) == 4 && R > 64 
                 eb = (__float_as_uint(a) >> 23) & 0xFFu;
             }
 #pragma unroll
-            for (int t = g * GT; t < (g + 1) * GT; ++t) {
+            for (int t = g * NT; t < (g + 1) * NT; ++t) {
                 float deq;
                 if constexpr (Q <= 1) {
                     float c = rintf(__fmul_rn(v[t][i], inv));
@@ -277,89 +318,133 @@ __global__ __launch_bounds__(64 * calib_waves(R), calib_waves(R) == 4 && R > 64 
                 const float e = __fsub_rn(deq, v[t][i]);
                 v[t][i] = e;
                 lsum = __builtin_fmaf(e, e, lsum);
-                es[i * SC + 16 * t] = e;
             }
+            if constexpr (Q == 2) __builtin_amdgcn_sched_barrier(0);  // (interleaved, the element decodings take 50 registers more)
         };
         for_constants(finish, std::make_integer_sequence<int, 4 * NG>{});
         // E is not read again in a step: non-temporal, it leaves W and the gradient parts in the caches (us per step, steps back
         // to back, cached / non-temporal: 3456 x 1152 rank 32 23.8 / 22.3, rank 64 31.5 / 31.1, 4608 x 1152 rank 128 72.6 / 71.3, 11200 x 2240 rank 32
         // 77.6 / 75.6, rank 64 138.9 / 134.6)
-        if (live) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) __builtin_nontemporal_store(v[t][i], ep + (size_t)i * K + 16 * t);
-            if (ncol == CALIB_COLS) {
-#pragma unroll
-                for (int t = 4; t < 8; ++t)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) __builtin_nontemporal_store(v[t][i], ep + (size_t)i * K + 16 * t);
+            for (int i = 0; i < 4; ++i) {
+                const v4f e = {v[4 * h][i], v[4 * h + 1][i], v[4 * h + 2][i], v[4 * h + 3][i]};
+                *(v4f*)(Es + (4 * q + i) * SC + 64 * h + 4 * l15) = e;
+                if (h == 0 || full) __builtin_nontemporal_store(e, (v4f*)((char*)(p.E + (size_t)(wrow + i) * K + col0 + 64 * h) + wo));
             }
+        __builtin_amdgcn_sched_barrier(0);
+        // grad_R: contraction over the strip's rows, row 4 q + u in step u
+        if constexpr (!ONE) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const float a = Ls[(4 * q + u) * SL + 16 * t + l15];
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) gr[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, v[c][u], gr[t][c], 0, 0, 0);
+                }
         }
-        // grad_L of the wavefront's own 16 rows: contraction over the block's columns, column 16 s + 4 q + u in step (s, u)
+        const bool more = !ONE && wrow + ROWS < row_end;
+        constexpr bool LATE = R == 64 && NWV == 8;  // (no registers left for the rows of L under grad_L; they come from the L2)
+        if (more) {
+            request(wrow + ROWS);
+            if (!LATE) request_l(wrow + ROWS);
+        }
+        wave_lds_fence();
+        // grad_L of the strip's rows: contraction over the block's columns, column 16 s + 4 q + u in step (s, u); R first, so that
+        // a lane ends with four consecutive rank indexes of its row
         {
             v4f gl[T];
 #pragma unroll
             for (int t = 0; t < T; ++t) gl[t] = v4f{0.f, 0.f, 0.f, 0.f};
-            const float* ap = Es + (16 * wave + l15) * SC + 4 * q;
-#pragma unroll 2
+            const float* ap = Es + l15 * SC + 4 * q;
+            const float* bp = Rs + l15 * SC + 4 * q;
+#pragma unroll R == 64 && !ONE ? 1 : 2
             for (int s = 0; s < CALIB_COLS / 16; ++s) {
                 const v4f a = *(const v4f*)(ap + 16 * s);
                 v4f b[T];
 #pragma unroll
-                for (int t = 0; t < T; ++t) b[t] = *(const v4f*)(Rs + calib_rs(16 * t + l15, 16 * s + 4 * q));
+                for (int t = 0; t < T; ++t) b[t] = *(const v4f*)(bp + 16 * t * SC + 16 * s);
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
 #pragma unroll
-                    for (int t = 0; t < T; ++t) gl[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[t][u], gl[t], 0, 0, 0);
+                    for (int t = 0; t < T; ++t) gl[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[t][u], a[u], gl[t], 0, 0, 0);
             }
-            if (live) {
-                float* o = p.gLp + ((size_t)cb * N + wrow + 4 * q) * R + l15;
+#pragma unroll
+            for (int t = 0; t < T; ++t) *(v4f*)((char*)(p.gLp + ((size_t)cb * N + wrow) * R + 16 * t) + 4u * (uint32_t)(l15 * R + 4 * q)) = gl[t];
+        }
+        if (more && LATE) request_l(wrow + ROWS);
+        if (more) store_l();  // (grad_R has read the strip's rows of L)
+        wave_lds_fence();     // the strip's reads of Es come before the next one's stores
+    }
+    if constexpr (ONE) {
+        // one strip per wavefront: grad_R of the wavefront's columns over all the block's rows, row 16 s + 4 q + u in step (s, u);
+        // E first, so that a lane ends with four consecutive columns of one rank index
+        __syncthreads();
+        const float* ap = Rs + R * SC + 4 * q * SC + 16 * CT * wave + l15;
+        const float* bp = Rs + R * SC + NWV * 16 * SC + 4 * q * SL + l15;
+#pragma unroll 2
+        for (int s = 0; s < NWV; ++s)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float a[CT], b[T];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) a[c] = ap[(16 * s + u) * SC + 16 * c];
+#pragma unroll
+                for (int t = 0; t < T; ++t) b[t] = bp[(16 * s + u) * SL + 16 * t];
 #pragma unroll
                 for (int t = 0; t < T; ++t)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i * R + 16 * t] = gl[t][i];
+                    for (int c = 0; c < CT; ++c) gr[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], b[t], gr[t][c], 0, 0, 0);
+            }
+        if (16 * CT * wave < ncol) {
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    *(v4f*)(p.gRp + ((size_t)split * R + 16 * t + l15) * K + col0 + 16 * (CT * wave + c) + 4 * q) = gr[t][c];
+        }
+    } else {
+        // the wavefronts' parts of grad_R, added in order, 32 rank indexes at a time (the whole LDS is free by now)
+        constexpr int TR = T < 2 ? T : 2;
+        static_assert(T % TR == 0, "whole turns");
+        float* Gs = lds + wave * 16 * TR * SC;
+        __syncthreads();
+#pragma unroll
+        for (int t0 = 0; t0 < T; t0 += TR) {
+            if (t0) __syncthreads();
+#pragma unroll
+            for (int t = 0; t < TR; ++t)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        *(v4f*)(Gs + (16 * t + 4 * q + i) * SC + 64 * h + 4 * l15) =
+                            v4f{gr[t0 + t][4 * h][i], gr[t0 + t][4 * h + 1][i], gr[t0 + t][4 * h + 2][i], gr[t0 + t][4 * h + 3][i]};
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 16 * TR * CALIB_COLS / 4 / NTHR; ++e) {
+                const int f = tid + e * NTHR, row = f / (CALIB_COLS / 4), c = 4 * (f % (CALIB_COLS / 4));
+                v4f sum = *(const v4f*)(lds + row * SC + c);
+#pragma unroll
+                for (int k = 1; k < NWV; ++k) {
+                    const v4f x = *(const v4f*)(lds + (k * 16 * TR + row) * SC + c);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sum[i] = __fadd_rn(sum[i], x[i]);
+                }
+                if (c < ncol) *(v4f*)(p.gRp + ((size_t)split * R + 16 * t0 + row) * K + col0 + c) = sum;
             }
         }
-        __syncthreads();  // every wavefront's rows of E are in the LDS
-        // grad_R of the wavefront's columns: contraction over the block's rows, row 16 s + 4 q + u in step (s, u)
-        {
-            const float* ap = Ls + 4 * q * SL + l15;
-            const float* bp = Es + 4 * q * SC + wave * 16 * CT + l15;
-#pragma unroll 2
-            for (int s = 0; s < ROWS / 16; ++s)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    float a[T], b[CT];
-#pragma unroll
-                    for (int t = 0; t < T; ++t) a[t] = ap[(16 * s + u) * SL + 16 * t];
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) b[c] = bp[(16 * s + u) * SC + 16 * c];
-#pragma unroll
-                    for (int t = 0; t < T; ++t)
-#pragma unroll
-                        for (int c = 0; c < CT; ++c) gr[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[c], gr[t][c], 0, 0, 0);
-                }
-        }
     }
-    const int c0 = wave * 16 * CT;
-    if (c0 < ncol) {
-        float* o = p.gRp + ((size_t)split * R + 4 * q) * K + col0 + c0 + l15;
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int c = 0; c < CT; ++c)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) o[(size_t)(16 * t + i) * K + 16 * c] = gr[t][c][i];
-    }
-    lsum = wave_sum_f(lsum);
     __syncthreads();
-    if (lane == 0) Es[wave] = lsum;
+    lsum = wave_sum_f(lsum);
+    if (lane == 0) lds[wave] = lsum;
     __syncthreads();
     if (tid == 0) {
-        float v = Es[0];
+        float v = lds[0];
 #pragma unroll
-        for (int w = 1; w < NWV; ++w) v = __fadd_rn(v, Es[w]);
+        for (int k = 1; k < NWV; ++k) v = __fadd_rn(v, lds[k]);
         p.lp[blockIdx.x] = v;
     }
 }
@@ -462,23 +547,28 @@ hipError_t launch_calib_init(const Dims& d, const float* L, const float* R, uint
 }
 
 template <auto KERNEL>
-static hipError_t calib_launch_err(const CalibParams& p, int waves, int lds, hipStream_t s)
+static hipError_t calib_launch_err(const CalibParams& p, int lds, hipStream_t s)
 {
     const hipError_t e = allow_lds<KERNEL>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(KERNEL, dim3((unsigned)(p.c.cblocks * p.c.splits)), dim3(64 * waves), lds, s, p);
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)(p.c.cblocks * p.c.splits)), dim3(64 * p.c.waves), lds, s, p);
     return hipGetLastError();
 }
 
-template <int R>
+template <int R, int NWV, bool ONE>
+static hipError_t calib_err_form(const Dims& d, const CalibParams& p, hipStream_t s)
+{
+    constexpr int lds = calib_lds(R, NWV, ONE);
+    if (d.mxi) return calib_launch_err<calib_err_kernel<R, 3, 2, NWV, ONE>>(p, lds, s);
+    if (d.mx) return calib_launch_err<calib_err_kernel<R, 2, 2, NWV, ONE>>(p, lds, s);
+    if (d.ga) return calib_launch_err<calib_err_kernel<R, 1, 4, NWV, ONE>>(p, lds, s);
+    if (d.g == 64) return calib_launch_err<calib_err_kernel<R, 0, 4, NWV, ONE>>(p, lds, s);
+    return calib_launch_err<calib_err_kernel<R, 0, 8, NWV, ONE>>(p, lds, s);
+}
+template <int R, int NWV>
 static hipError_t calib_err(const Dims& d, const CalibParams& p, hipStream_t s)
 {
-    constexpr int lds = calib_lds<R>(), waves = calib_waves(R);
-    if (d.mxi) return calib_launch_err<calib_err_kernel<R, 3, 2>>(p, waves, lds, s);
-    if (d.mx) return calib_launch_err<calib_err_kernel<R, 2, 2>>(p, waves, lds, s);
-    if (d.ga) return calib_launch_err<calib_err_kernel<R, 1, 4>>(p, waves, lds, s);
-    if (d.g == 64) return calib_launch_err<calib_err_kernel<R, 0, 4>>(p, waves, lds, s);
-    return calib_launch_err<calib_err_kernel<R, 0, 8>>(p, waves, lds, s);
+    return p.c.per == 1 ? calib_err_form<R, NWV, true>(d, p, s) : calib_err_form<R, NWV, false>(d, p, s);
 }
 
 hipError_t launch_calib_step(const Dims& d, const float* W, uint8_t* state, int step, const lq_adam* ad, float* loss,
@@ -498,11 +588,11 @@ hipError_t launch_calib_step(const Dims& d, const float* W, uint8_t* state, int 
     p.c = calib_split(d);
     hipError_t e;
     switch (d.r) {
-        case 16: e = calib_err<16>(d, p, s); break;
-        case 32: e = calib_err<32>(d, p, s); break;
-        case 64: e = calib_err<64>(d, p, s); break;
-        case 96: e = calib_err<96>(d, p, s); break;
-        default: e = calib_err<128>(d, p, s); break;
+        case 16: e = p.c.waves == 8 ? calib_err<16, 8>(d, p, s) : calib_err<16, 4>(d, p, s); break;
+        case 32: e = p.c.waves == 8 ? calib_err<32, 8>(d, p, s) : calib_err<32, 4>(d, p, s); break;
+        case 64: e = p.c.waves == 8 ? calib_err<64, 8>(d, p, s) : calib_err<64, 4>(d, p, s); break;
+        case 96: e = calib_err<96, 4>(d, p, s); break;
+        default: e = calib_err<128, 4>(d, p, s); break;
     }
     if (e != hipSuccess) return e;  // (the parts in the state are an earlier step's: no update from them)
     AdamParams a;

@@ -109,6 +109,15 @@ def test_first_step_over_row_blocks_and_a_half_column_block(oracle, N, K, r, g, 
         assert np.all(np.abs(_n(got[name]) - want) <= (terms + 4) * 2.0 ** -24 * c * mag + 1e-30), name
 
 
+# One row block per workgroup of eight wavefronts (the last block's strips past N missing, the last column block 64 wide), and
+# of four; runs of several blocks with eight.
+@pytest.mark.parametrize("N,K,r,g,sint4", [(1088, 2112, 16, 64, False), (1088, 2112, 32, 64, True), (1088, 2112, 64, 64, False),
+                                           (1088, 2112, 64, 32, "mxfp4"), (1088, 2112, 32, 32, "mxint4"), (1088, 2176, 64, 128, False),
+                                           (192, 320, 64, 64, False), (192, 320, 16, 32, "mxfp4"), (2240, 4672, 64, 32, "mxfp4")])
+def test_first_step_with_strips_past_the_last_row(oracle, N, K, r, g, sint4):
+    test_first_step_over_row_blocks_and_a_half_column_block(oracle, N, K, r, g, sint4)
+
+
 @pytest.mark.parametrize("g,kind,lr", [(64, False, 1e-4), (32, "mxfp4", 1e-3)])
 def test_trajectory_matches_oracle(oracle, g, kind, lr):
     N, K, r = 128, 256, 16
