@@ -347,8 +347,8 @@ __device__ __forceinline__ uint32_t fp6_get(const uint8_t* slot, int i)  // code
 }
 __device__ __forceinline__ float e2m3_value(uint32_t c)  // 1 sign, 2 exponent (bias 1), 3 mantissa bits
 {
-    const int e = (int)(c >> 3) & 3, m = (int)c & 7;
-    const float mag = e ? ldexpf(1.0f + 0.125f * (float)m, e - 1) : 0.125f * (float)m;
+    const uint32_t m = c & 31u;  // (branch-free: a normal code is the top of a float's bits)
+    const float mag = m >= 8u ? __uint_as_float((m << 20) + (126u << 23)) : 0.125f * (float)m;
     return (c & 32u) ? -mag : mag;
 }
 

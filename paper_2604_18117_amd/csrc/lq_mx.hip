@@ -75,6 +75,13 @@ __device__ __forceinline__ uint32_t fp8_quad(float u0, float u1, float u2, float
     return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(u2, u3, lo, true);
 }
 __device__ __forceinline__ float fp8_value(uint32_t byte) { return __builtin_amdgcn_cvt_f32_fp8((int)byte, 0); }
+__device__ __forceinline__ float fp8_value_of(uint32_t quad, int t)  // byte t (a constant)
+{
+    return t == 0   ? __builtin_amdgcn_cvt_f32_fp8((int)quad, 0)
+           : t == 1 ? __builtin_amdgcn_cvt_f32_fp8((int)quad, 1)
+           : t == 2 ? __builtin_amdgcn_cvt_f32_fp8((int)quad, 2)
+                    : __builtin_amdgcn_cvt_f32_fp8((int)quad, 3);
+}
 __device__ __forceinline__ void fp8_scales(float amax, float* s, float* inv)
 {
     if (amax == 0.0f) {
@@ -167,8 +174,19 @@ __global__ __launch_bounds__(256) void mxb_pack_rows_kernel(const float* L, cons
 
 // Residual of a 64-chunk (two blocks of 32): MXFP4 codes and E8M0 bytes.  KIND of the factors: 0 as given, 1 E4M3 codes with
 // fp32 row scales, 2 MXFP8e4 and 3 MXFP6e2 codes with E8M0 block scales (sl, sr hold le, re; element * 2^e is exact in fp32).
+struct PackMxBlock4 {  // four codes and their block's scale byte
+    uint32_t c, e;
+};
+typedef uint32_t u32_bytes __attribute__((aligned(1)));
+// Four E2M3 codes of 24 bits as the E4M3 bytes of their values * 2^-6 (normal and subnormal alike)
+__device__ __forceinline__ uint32_t e4m3_of_fp6(uint32_t c)
+{
+    const uint32_t b = (c & 0x3Fu) | (c & 0xFC0u) << 2 | (c & 0x3F000u) << 4 | (c & 0xFC0000u) << 6;
+    return (b & 0x1F1F1F1Fu) | (b & 0x20202020u) << 2;
+}
 template <int KIND>
 struct PackMxResidual {
+    using Raw = std::conditional_t<KIND == 0, pack_v4f, std::conditional_t<KIND == 1, PackCodes4, PackMxBlock4>>;
     const float *L, *R;
     const uint8_t* l8;
     const float* sl;
@@ -176,21 +194,42 @@ struct PackMxResidual {
     const float* sr;
     uint8_t *pc, *pe;
     int Ks, C64, r, rp;
-    __device__ float lhat(int n, int j) const
+    __device__ void lhat(int n, int j, int q, float (&v)[4]) const
     {
-        if constexpr (KIND == 0) return L[(size_t)n * r + j];
-        if constexpr (KIND == 1) return __fmul_rn(fp8_value(l8[(size_t)n * rp + j]), sl[n]);
-        const float s = e8m0_value(((const uint8_t*)sl)[mxb_scale_offset(n, j >> 5)]);
-        if constexpr (KIND == 2) return __fmul_rn(fp8_value(l8[mxb_frag8_offset(n, j, rp)]), s);
-        return __fmul_rn(e2m3_value(fp6_get(l8 + mx6_lt_slot(n, j >> 5, rp), j & 31)), s);
+        if constexpr (KIND == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = L[(size_t)n * r + j + 4 * i + q];
+        } else if constexpr (KIND <= 2) {
+            const uint4 c = *(const uint4*)(l8 + (KIND == 1 ? (size_t)n * rp + j : mxb_frag8_offset(n, j, rp)));
+            const uint32_t d[4] = {c.x, c.y, c.z, c.w};
+            const float s = KIND == 1 ? sl[n] : e8m0_value(((const uint8_t*)sl)[mxb_scale_offset(n, j >> 5)]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = __fmul_rn(fp8_value(d[i] >> (8 * q) & 0xFFu), s);
+        } else {  // 16 codes in 96 bits, four in 24
+            const uint32_t* p = (const uint32_t*)(l8 + mx6_lt_slot(n, j >> 5, rp) + 12 * ((j & 31) >> 4));
+            const uint32_t w0 = p[0], w1 = p[1], w2 = p[2];
+            const uint32_t d[4] = {w0, w0 >> 24 | w1 << 8, w1 >> 16 | w2 << 16, w2 >> 8};
+            const int E = ((const uint8_t*)sl)[mxb_scale_offset(n, j >> 5)];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = ldexpf(fp8_value(e4m3_of_fp6(d[i]) >> (8 * q) & 0xFFu), E - 121);
+        }
     }
-    __device__ float rhat(int j, int k) const
+    __device__ Raw rload(int j, int k) const
     {
-        if constexpr (KIND == 0) return R[(size_t)j * Ks + k];
-        if constexpr (KIND == 1) return __fmul_rn(fp8_value(r8[mx_rq_offset(j, k, r)]), sr[j]);
-        const float s = e8m0_value(((const uint8_t*)sr)[mxb_re_offset(j, k >> 5, r)]);
-        if constexpr (KIND == 2) return __fmul_rn(fp8_value(r8[mxb_rq_offset(j, k, r)]), s);
-        return __fmul_rn(e2m3_value(fp6_get(r8 + mx6_rq_slot(j, k >> 5, r), k & 31)), s);
+        if constexpr (KIND == 0) return *(const Raw*)(R + (size_t)j * Ks + k);
+        else if constexpr (KIND == 1) return Raw{*(const uint32_t*)(r8 + mx_rq_offset(j, k, r)), sr[j]};
+        else {
+            const uint32_t E = ((const uint8_t*)sr)[mxb_re_offset(j, k >> 5, r)];
+            if constexpr (KIND == 2) return Raw{*(const uint32_t*)(r8 + mxb_rq_offset(j, k, r)), E};
+            else return Raw{*(const u32_bytes*)(r8 + mx6_rq_slot(j, k >> 5, r) + 3 * ((k & 31) >> 2)), E};  // (24 bits of the slot's 192)
+        }
+    }
+    __device__ float rval(const Raw& x, int t) const
+    {
+        if constexpr (KIND == 0) return x[t];
+        else if constexpr (KIND == 1) return __fmul_rn(fp8_value_of(x.c, t), x.s);
+        else if constexpr (KIND == 2) return ldexpf(fp8_value_of(x.c, t), (int)x.e - 127);
+        else return ldexpf(fp8_value_of(e4m3_of_fp6(x.c), t), (int)x.e - 121);
     }
     __device__ void encode(int n, int c, const float (&P)[1][16], int q) const
     {

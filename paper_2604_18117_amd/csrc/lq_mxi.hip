@@ -174,18 +174,36 @@ __global__ __launch_bounds__(256) void mxi_pack_rows_kernel(const float* L, cons
 
 // Residual of a 64-chunk (two blocks of 32): MXINT4 codes and scale bytes.  Factors: the dequantised elements (exact in
 // bf16) or, from_q = 0, as given.
+template <bool FROMQ>
 struct PackMxiResidual {
+    using Raw = std::conditional_t<FROMQ, uint2, pack_v4f>;
     const float *L, *R;
     const uint8_t *lv, *rv;
     uint8_t *pq, *pe;
-    int K, r, rp, from_q;
-    __device__ float lhat(int n, int j) const
+    int K, r, rp;
+    __device__ void lhat(int n, int j, int q, float (&v)[4]) const
     {
-        return from_q ? bf16_value(*(const uint16_t*)(lv + mxi_lt_offset(n, j, rp))) : L[(size_t)n * r + j];
+        if constexpr (FROMQ) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint4 c = *(const uint4*)(lv + mxi_lt_offset(n, j + 8 * h, rp));  // 8 elements; the lane's are q and q + 4
+                v[2 * h] = bf16_value((uint16_t)((q & 2 ? c.y : c.x) >> (16 * (q & 1))));
+                v[2 * h + 1] = bf16_value((uint16_t)((q & 2 ? c.w : c.z) >> (16 * (q & 1))));
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = L[(size_t)n * r + j + 4 * i + q];
+        }
     }
-    __device__ float rhat(int j, int k) const
+    __device__ Raw rload(int j, int k) const
     {
-        return from_q ? bf16_value(*(const uint16_t*)(rv + mxi_rq_offset(j, k, r))) : R[(size_t)j * K + k];
+        if constexpr (FROMQ) return *(const Raw*)(rv + mxi_rq_offset(j, k, r));
+        else return *(const Raw*)(R + (size_t)j * K + k);
+    }
+    __device__ float rval(const Raw& x, int t) const
+    {
+        if constexpr (FROMQ) return bf16_value((uint16_t)((t < 2 ? x.x : x.y) >> (16 * (t & 1))));
+        else return x[t];
     }
     __device__ void encode(int n, int c, const float (&P)[1][16], int q) const
     {
@@ -231,8 +249,11 @@ hipError_t launch_pack_mxi(const Dims& d, int from_q, const float* W, const floa
         hipLaunchKernelGGL(mxi_pack_rows_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, L, R, N, K, d.bw_bits, d.r, d.rp, pp.lv,
                            pp.le, pp.rv, pp.re);
     }
-    return pack_residual<1>(hipGetLastError(), PackMxiResidual{L, R, pp.lv, pp.rv, pp.pq, pp.pe, K, d.r, d.rp, from_q}, W, N, K, d.r, d.C64, packed,
-                            make_tag(d, LQ_BLOB_PACKED, 0), s);
+    auto residual = [&](auto fq) {
+        return pack_residual<1>(hipGetLastError(), PackMxiResidual<decltype(fq)::value>{L, R, pp.lv, pp.rv, pp.pq, pp.pe, K, d.r, d.rp}, W, N, K, d.r, d.C64,
+                                packed, make_tag(d, LQ_BLOB_PACKED, 0), s);
+    };
+    return from_q && d.r > 0 ? residual(std::true_type{}) : residual(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -31,30 +31,56 @@ hipError_t launch_pack_fill(const PackFill& f, hipStream_t s);
 // dequantises them are exact in fp32 in every family, their products in fp64.
 //
 // A workgroup owns 64 rows of W (16 per wavefront) and a run of scale groups (GC chunks of 64 along K).  The product is
-// formed transposed, 16 values of K by 16 rows of W per tile: lane (l15, q) ends up with row n = l15 and, the chunk's
-// K values being dealt to the tiles' rows accordingly, the 16 consecutive values k = 16 q .. 16 q + 15 of every chunk: the
-// block maxima are one or two lane exchanges and the codes leave as whole dwords.  (One wavefront per row and group, a lane
-// per K value, r dependent fp64 multiply-adds with two scattered loads each, took 111 us for 4608 x 1152 at rank 32 and
-// 0.85-1.0 ms for 11200 x 2240 and 6720 x 2240 at rank 64.)
+// formed transposed, 16 values of K by 16 rows of W per tile (result register i of lane (l15, q): tile row q + 4 i, column l15).
+// The chunk's K values are dealt to the tiles so that lane (l15, q) ends up with row n = l15 and the 16 consecutive values
+// k = 16 q .. 16 q + 15 of every chunk (the block maxima are one or two lane exchanges, the codes leave as whole dwords), and
+// that the first operand of the four tiles at one rank index is four consecutive values of a row of R: one load per lane, codes of
+// 8 bits in one dword.  So the wavefronts share nothing: no LDS, no barriers, D rank steps of R in flight across chunks and
+// the next chunk of W requested under the products.  What bounds it is the fp64 matrix rate (64 cycles a product) once three
+// wavefronts per SIMD are there.  Against R staged through the LDS as fp32, a barrier per chunk and its loads waited for in every one
+// (us a pack call): 4608 x 1152 rank 32, groups of 128, 24.5 -> 18.3, 6720 x 2240 rank 64, groups of 64, 80.4 -> 51.3, 11200 x 2240 rank 128 292 -> 143,
+// MXINT4 4608 x 1152 rank 128 105 -> 49, MXFP4 6720 x 2240 rank 128 135 -> 87; MXFP6 factors, whose decoding every wavefront now does for
+// itself, 6720 x 2240 rank 128 114.5 -> 106.3, 3456 x 1152 rank 32 18.3 -> 19.5.  (One wavefront per row and group, a lane per K value: 111 us for the
+// first.)
 //
-// F: lhat(n, j) and rhat(j, k) dequantised factors (k inside the source row), encode(n, group, P, q) for the lane's values.
+// F: lhat(n, j, q, v) dequantised L of row n at j + q, j + q + 4, + 8, + 12 (j a multiple of 16); rload(j, k) row j of R at k .. k + 3 (k inside the source row, a multiple of 4) as stored, rval(raw, t)
+// its dequantised values; encode(n, group, P, q) for the lane's values.
 // The last launch of a pack call: it writes the blob's header too.
+typedef float pack_v4f __attribute__((ext_vector_type(4), aligned(4)));  // (W, L and R are aligned to their elements only)
+struct PackCodes4 {  // four 8-bit codes and their scale
+    uint32_t c;
+    float s;
+};
 template <int R, int GC, typename F>
-__global__ __launch_bounds__(256) void pack_residual_kernel(F f, const float* W, int Ks, int groups, int per, uint32_t* blob, BlobTag tag)
+__global__ __launch_bounds__(256, R < 64 || (R == 64 && sizeof(typename F::Raw) <= 8) ? 3 : 2) void pack_residual_kernel(F f, const float* W, int Ks, int groups, int per, uint32_t* blob, BlobTag tag)
 {
-    typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));  // (W is aligned to its elements only)
     typedef double v4d __attribute__((ext_vector_type(4)));
-    constexpr int S = 80;  // LDS row stride in floats: lane (l15, q) reads row 4 s + q, so q moves by 16 banks
-    constexpr int RS = R > 0 ? R : 1, NB = R <= 64 ? 2 : 1;
-    __shared__ float Rs[NB][RS * S];
+    constexpr int NS = R / 4, DMAX = sizeof(typename F::Raw) > 8 || (GC == 2 && R >= 64) ? 4 : 8, D = NS < DMAX ? NS : DMAX;  // (registers)
+    static_assert(NS == 0 || NS % D == 0, "whole turns of the ring");
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q = lane >> 4, wave = tid >> 6;
     const int runs = (groups + per - 1) / per;
     const int n = (blockIdx.x / runs) * 64 + 16 * wave + l15;
     const int g0 = (blockIdx.x % runs) * per, g1 = g0 + per < groups ? g0 + per : groups;
-    double l[RS / 4 + 1];
+    const int kl = 16 * (l15 & 3) + 4 * (l15 >> 2);  // the lane's K values of a chunk as first operand
+    const int kend = Ks - 64;                        // the last source chunk
+    pack_v4f w[4];
+    auto request = [&](int k0) {
 #pragma unroll
-    for (int s = 0; s < R / 4; ++s) l[s] = (double)f.lhat(n, 4 * s + q);
-    int buf = 0;
+        for (int t = 0; t < 4; ++t) w[t] = *(const pack_v4f*)(W + (size_t)n * Ks + k0 + 16 * q + 4 * t);
+    };
+    const int kfirst = g0 * GC * 64 < kend ? g0 * GC * 64 : kend;  // (a run may be layout padding alone)
+    double l[NS + 1];
+    typename F::Raw rr[D + 1];
+#pragma unroll
+    for (int s = 0; s < NS; s += 4) {
+        float v[4];
+        f.lhat(n, 4 * s, q, v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) l[s + i] = (double)v[i];
+    }
+#pragma unroll
+    for (int s = 0; s < D; ++s) rr[s] = f.rload(4 * s + q, kfirst + kl);
+    if constexpr (R > 0) request(kfirst);
     for (int g = g0; g < g1; ++g) {
         float P[GC][16];
 #pragma unroll
@@ -65,44 +91,58 @@ __global__ __launch_bounds__(256) void pack_residual_kernel(F f, const float* W,
                 for (int e = 0; e < 16; ++e) P[cc][e] = 0.f;
                 continue;
             }
-            v4f w[4];
+            const bool more = k0 < kend && !(g + 1 == g1 && cc + 1 == GC);
+            const int knext = more ? k0 + 64 : k0;
+            if constexpr (R == 0) request(k0);
+            pack_v4f wc[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) w[t] = *(const v4f*)(W + (size_t)n * Ks + k0 + 16 * q + 4 * t);
+            for (int t = 0; t < 4; ++t) wc[t] = w[t];
+            if (R > 0 && more) request(knext);
             v4d d[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) d[t] = v4d{0.0, 0.0, 0.0, 0.0};
             if constexpr (R > 0) {
-                // K value kk of the chunk: tile (kk / 4) % 4, tile row kk / 16 + 4 * (kk % 4)
-                float rv[R / 4];
 #pragma unroll
-                for (int e = 0; e < R / 4; ++e) rv[e] = f.rhat((tid >> 6) + 4 * e, k0 + lane);
-                if constexpr (NB == 1) __syncthreads();
+                for (int s = 0; s < NS; ++s) {
+                    float a[4];
 #pragma unroll
-                for (int e = 0; e < R / 4; ++e)
-                    Rs[buf][((tid >> 6) + 4 * e) * S + 16 * ((lane >> 2) & 3) + (lane >> 4) + 4 * (lane & 3)] = rv[e];
-                __syncthreads();
+                    for (int t = 0; t < 4; ++t) a[t] = f.rval(rr[s % D], t);
+                    rr[s % D] = f.rload(4 * ((s + D) % NS) + q, (s + D < NS ? k0 : knext) + kl);
 #pragma unroll
-                for (int s = 0; s < R / 4; ++s)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        d[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Rs[buf][(4 * s + q) * S + 16 * t + l15], l[s], d[t], 0, 0, 0);
-                buf ^= NB - 1;
+                    for (int t = 0; t < 4; ++t) d[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[t], l[s], d[t], 0, 0, 0);
+                }
             }
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) P[cc][4 * t + i] = (float)((double)w[t][i] - d[t][i]);
+                for (int t = 0; t < 4; ++t) P[cc][4 * i + t] = (float)((double)wc[i][t] - d[t][i]);
         }
         f.encode(n, g, P, q);
     }
-    write_tag(blob, tag);  // (ahead of the loop it takes the MXFP8 form at rank 128 from 188 registers to 256, 70 us to 104)
+    write_tag(blob, tag);
+}
+// Scale groups per run.  A compute unit works through ceil(workgroups / 256) of them, each its chunks and about 0.7 of a chunk's
+// time until its rows' factors and first operands are there; the matrix unit is busy from about 2.5 workgroups per compute unit on.
+// (Runs as long as 2048 workgroups allow, 6720 x 2240 rank 64 takes 59.7 us instead of 54.5, 11200 x 2240 rank 128 169.5 instead of 153.3.)
+static inline int pack_residual_run(int rb, int groups, int gc)
+{
+    int best = 1;
+    int64_t best_cost = 0;
+    for (int per = 1; per <= groups; ++per) {
+        const int64_t wgs = (int64_t)rb * ((groups + per - 1) / per), cost = (wgs + 255) / 256 * (10 * per * gc + 7);
+        if (per > 1 && wgs < 640) break;
+        if (per == 1 || cost < best_cost) {
+            best = per;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
 template <int R, int GC, typename F>
 static void pack_residual_launch(const F& f, const float* W, int N, int Ks, int groups, uint8_t* blob, const BlobTag& tag, hipStream_t s)
 {
-    // runs as long as 2048 workgroups (8 per CU) allow: a run reads its rows' factors once
-    const int rb = N / 64, want = 2048 / rb > 1 ? 2048 / rb : 1;
-    const int per = (groups + want - 1) / want;
+    const int rb = N / 64, want = 2048 / rb > 1 ? 2048 / rb : 1;  // (rank 0 only streams W: 2048 workgroups)
+    const int per = R > 0 ? pack_residual_run(rb, groups, GC) : (groups + want - 1) / want;
     hipLaunchKernelGGL((pack_residual_kernel<R, GC, F>), dim3((unsigned)(rb * ((groups + per - 1) / per))), dim3(256), 0, s, f, W, Ks,
                        groups, per, (uint32_t*)blob, tag);
 }

@@ -4,6 +4,8 @@
 //   (SINT4-style blocks, App. A.3), or the literal SINT4 blocks: 64 values, FP16 scale.  Also the inverse
 //   views used by tests.
 // Quantiser: s = amax / qmax, code = rne(v * (qmax / amax)), symmetric range, all-zero -> s = 1.
+#include <type_traits>
+
 #include "lq_pack.h"
 
 namespace lq {
@@ -51,8 +53,9 @@ struct PackIntRows {
 
 // Residual of a scale group of GC chunks: dequantised (from_q) or given factors; Q1 = INT4, fp32 scale (times 2^6, lq_internal.h)
 // or SINT4's FP16 scale (stored as its bits; codes against the stored scale).
-template <int GC>
+template <int GC, bool FROMQ>
 struct PackIntResidual {
+    using Raw = std::conditional_t<FROMQ, PackCodes4, pack_v4f>;
     const float *L, *R;
     const int8_t* lq;
     const float* sl;
@@ -60,9 +63,29 @@ struct PackIntResidual {
     const float* sr;
     uint8_t* pq;
     float* swT;
-    int N, K, r, rp, from_q, ga;
-    __device__ float lhat(int n, int j) const { return from_q ? (float)lq[(size_t)n * rp + j] * sl[n] : L[(size_t)n * r + j]; }
-    __device__ float rhat(int j, int k) const { return from_q ? (float)rq[rq_offset(j, k, r)] * sr[j] : R[(size_t)j * K + k]; }
+    int N, K, r, rp, ga;
+    __device__ void lhat(int n, int j, int q, float (&v)[4]) const
+    {
+        if constexpr (FROMQ) {
+            const uint4 c = *(const uint4*)(lq + (size_t)n * rp + j);
+            const uint32_t d[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = (float)(int8_t)(d[i] >> (8 * q)) * sl[n];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = L[(size_t)n * r + j + 4 * i + q];
+        }
+    }
+    __device__ Raw rload(int j, int k) const
+    {
+        if constexpr (FROMQ) return Raw{*(const uint32_t*)(rq + rq_offset(j, k, r)), sr[j]};
+        else return *(const Raw*)(R + (size_t)j * K + k);
+    }
+    __device__ float rval(const Raw& x, int t) const
+    {
+        if constexpr (FROMQ) return (float)(int8_t)(x.c >> (8 * t)) * x.s;
+        else return x[t];
+    }
     __device__ void encode(int n, int g, const float (&P)[GC][16], int q) const
     {
         float a = pack_amax(P[0]);
@@ -155,9 +178,15 @@ hipError_t launch_pack_int(const Dims& d, int from_q, const float* W, const floa
     pack_row_factors(PackIntRows{(float)d.qmax_bw}, L, R, N, K, K, d.r, d.rp, (uint8_t*)lq, sl, (uint8_t*)rq, sr, s);
     e = hipGetLastError();
     const BlobTag tag = make_tag(d, LQ_BLOB_PACKED, 0);
-    if (d.g == 64)
-        return pack_residual<1>(e, PackIntResidual<1>{L, R, lq, sl, rq, sr, pq, swT, N, K, d.r, d.rp, from_q, d.ga ? 1 : 0}, W, N, K, d.r, d.G, packed, tag, s);
-    return pack_residual<2>(e, PackIntResidual<2>{L, R, lq, sl, rq, sr, pq, swT, N, K, d.r, d.rp, from_q, 0}, W, N, K, d.r, d.G, packed, tag, s);
+    auto residual = [&](auto gc, auto fq) {
+        constexpr int GC = decltype(gc)::value;
+        return pack_residual<GC>(e, PackIntResidual<GC, decltype(fq)::value>{L, R, lq, sl, rq, sr, pq, swT, N, K, d.r, d.rp, d.ga ? 1 : 0}, W, N, K, d.r, d.G,
+                                 packed, tag, s);
+    };
+    const std::integral_constant<int, 1> one{};
+    const std::integral_constant<int, 2> two{};
+    if (from_q && d.r > 0) return d.g == 64 ? residual(one, std::true_type{}) : residual(two, std::true_type{});
+    return d.g == 64 ? residual(one, std::false_type{}) : residual(two, std::false_type{});
 }
 
 // ---- plain views ----------------------------------------------------------------------------

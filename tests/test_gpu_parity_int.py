@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2604_18117_amd import binding as lq
 from paper_2604_18117_amd import workloads as wl
 from tests.smoothing import smoothing_vector
 from tests.gpu_util import bf16_to_bits, n, run_gpu, run_oracle_int
@@ -425,3 +426,20 @@ def test_activation_forms_bit_exact(oracle, M, K, r, xd, ag, sm):
     if r:
         assert np.array_equal(n(av.tq)[rows], act.tq) and np.array_equal(n(av.st)[rows], act.st)
     assert np.array_equal(bf16_to_bits(g.Y)[rows], out.Y)
+
+
+# Residual of the pack step: runs of one and of several scale groups, every depth of the rank ring, factors as given and quantised.
+@pytest.mark.parametrize("N,K,r,g", [(64, 64, 16, 64), (64, 128, 128, 128), (5120, 1280, 32, 64), (5120, 2560, 64, 128), (5120, 1280, 96, 64),
+                                     (2560, 1280, 128, 128), (2560, 1280, 0, 64)])
+@pytest.mark.parametrize("from_q", [True, False])
+def test_packed_codes_over_runs_of_groups(oracle, N, K, r, g, from_q):
+    rng = np.random.default_rng(N + K + r)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    L, R = ((rng.standard_normal(s) * 0.03).astype(np.float32) for s in ((N, r), (r, K)))
+    cfg = lq.make_config(N, K, r, "int", g, 8, 8, residual_from_quantized=from_q)
+    dL, dR = (torch.from_numpy(a).cuda() if r else None for a in (L, R))
+    packed = lq.lq_pack_weights(cfg, torch.from_numpy(W).cuda(), dL, dR)
+    got = lq.lq_unpack_weights(cfg, packed)
+    torch.cuda.synchronize()
+    want = oracle.pack_int(W, L if r else None, R if r else None, g, 8, residual_from_quantized=from_q)
+    assert np.array_equal(n(got.pq), want.pq) and np.array_equal(n(got.sw), want.sw)
