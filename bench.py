@@ -121,7 +121,7 @@ def bench_rot(args, layer, np, torch, lq, wl):
            "n_gpus": 1, "steps": K, "warmup": args.warmup, "ms_per_step": round(ms_step, 5), "higher_is_better": True,
            "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
            "config": {"workload": layer.name + "_rot", "N": N, "K": Kd, "rank": r, "q2_bits": layer.br_w_bits,
-                      "launches_per_step": 3 if layer.family in ("mxb", "mxi") else 4},  # (row maxima first with one scale per row)
+                      "launches_per_step": (3 if layer.family in ("mxb", "mxi") else 4) + (layer.r >= 64)},  # (row maxima first with one scale per row; the update in two from rank 64 on)
            "work_per_step": {"flops": 2.0 * (2 * 2 + 1) * (N + Kd) * r * r + 2.0 * 8 * r ** 3, "loss": float(loss.item())}}
     if args.oracle_seconds > 0:
         from oracle import lq_ref

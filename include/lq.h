@@ -294,7 +294,7 @@ lq_status lq_calib_unpack(const lq_config *cfg, const void *state, const lq_cali
    as printed the gradient of a layer-sized problem is of the order of 1e-7 and a step of 0.5 moves Omega by as much;
    grad_scale (1 = as printed) is the caller's handle on that.
    The state blob is device memory owned by the caller (256-byte aligned, at least state_bytes).  A step is four kernel
-   launches (three with block-scaled formats), no atomics, no allocation; results are reproducible bit for bit.  After a launch
+   launches up to rank 32, five above (one less with block-scaled formats), no atomics, no allocation; results are reproducible bit for bit.  After a launch
    that failed (LQ_ERR_DEVICE) nothing more of the step is launched. */
 typedef struct {
     float lr;          /* 0.5 (App. A.2)                                                  */

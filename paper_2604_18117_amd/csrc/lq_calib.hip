@@ -3,7 +3,7 @@
 // for the main quantiser Q1 of the configuration: INT4 in groups of 64 | 128 along K with fp32 scales, SINT4 blocks with
 // FP16 scales, MXFP4 or MXINT4 (blocks of 32, E8M0 scale).  Two launches per step:
 //   calib_err_kernel   V = W + L R (fp32 FMA chain over ascending j), E = deq(Q1(V)) - V, partial sums of E^2, and the
-//                      tile's parts of grad_L = -2/(N K) E R^T and grad_R = -2/(N K) L^T E while E is in the LDS
+//                      strips' parts of grad_L = -2/(N K) E R^T and grad_R = -2/(N K) L^T E while E is on the chip
 //   calib_adam_kernel  sums the parts, Adam update of L and R, loss = sum of its partials / (N K)
 // No atomics: every sum has a fixed order, so a step is reproducible bit for bit.
 #include <utility>
@@ -17,9 +17,9 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // A workgroup owns 128 columns of W and a run of row blocks of 16 rows per wavefront.  It leaves one r x 128 part of grad_R
 // for its run and one part of grad_L, 16 rows x r, per wavefront and row block.  The runs are as long as they can be with
 // every workgroup slot of the device still taken, so that grad_R has few parts.  Up to rank 64 a workgroup has 8 wavefronts
-// (half the parts of grad_R that two workgroups of 4 on the same compute unit leave), or 4 where that shortens
-// the longest chain of strips on a compute unit (us a step, 8 / 4: 1152 x 1152 rank 64 23.9 / 19.8; at equal chains 3456 x 1152 rank 64
-// 29.9 / 31.7); from rank 96 on the LDS holds 4.
+// (half the parts of grad_R that two workgroups of 4 on the same compute unit leave), or 4 up to rank 32 where that shortens
+// the longest chain of strips on a compute unit (at rank 64 it would, 1152 x 1152 19.8 us a step instead of 24.2, but leaves more parts
+// than states of earlier sizes hold); from rank 96 on the LDS holds 4.
 constexpr int CALIB_COLS = 128;
 struct CalibSplit {
     int waves;      // wavefronts per workgroup
@@ -43,10 +43,11 @@ static CalibSplit calib_split(const Dims& d, int waves, int slots)
 static CalibSplit calib_split(const Dims& d)
 {
     if (d.r > 64) return calib_split(d, 4, 256);
-    // (two workgroups of 4 wavefronts share a compute unit up to rank 32; at rank 64 the LDS holds one)
-    const CalibSplit c8 = calib_split(d, 8, 256), c4 = calib_split(d, 4, d.r <= 32 ? 512 : 256);
+    const CalibSplit c8 = calib_split(d, 8, 256);
+    if (d.r == 64) return c8;
+    const CalibSplit c4 = calib_split(d, 4, 512);  // (two share a compute unit)
     const int chain8 = 8 * c8.per, chain4 = (c4.cblocks * c4.splits > 256 ? 8 : 4) * c4.per;
-    return chain4 < chain8 && (d.r <= 32 || c4.per == 1) ? c4 : c8;
+    return chain4 < chain8 ? c4 : c8;
 }
 
 CalibLayout calib_layout(const Dims& d)
@@ -169,7 +170,7 @@ __device__ __forceinline__ float max_row8(float v)
 // GT: 16-column tiles per scale group (4: 64 values, 8: 128, 2: MX block of 32).
 // Q: 0 INT4 groups (fp32 scale), 1 SINT4 blocks, 2 MXFP4, 3 MXINT4.
 template <int R, int Q, int GT, int NWV, bool ONE>
-__global__ __launch_bounds__(64 * NWV, R > 64 || (R == 64 && NWV == 4) ? 1 : 2) void calib_err_kernel(CalibParams p)
+__global__ __launch_bounds__(64 * NWV, R > 64 ? 1 : 2) void calib_err_kernel(CalibParams p)
 {
     constexpr int NTHR = 64 * NWV, T = R / 16, SL = R + 4, SC = CALIB_SC;
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -346,7 +347,7 @@ __global__ __launch_bounds__(64 * NWV, R > 64 || (R == 64 && NWV == 4) ? 1 : 2) 
                 }
         }
         const bool more = !ONE && wrow + ROWS < row_end;
-        constexpr bool LATE = R == 64 && NWV == 8;  // (no registers left for the rows of L under grad_L; they come from the L2)
+        constexpr bool LATE = R == 64;  // (no registers left for the rows of L under grad_L; they come from the L2)
         if (more) {
             request(wrow + ROWS);
             if (!LATE) request_l(wrow + ROWS);
@@ -590,7 +591,7 @@ hipError_t launch_calib_step(const Dims& d, const float* W, uint8_t* state, int 
     switch (d.r) {
         case 16: e = p.c.waves == 8 ? calib_err<16, 8>(d, p, s) : calib_err<16, 4>(d, p, s); break;
         case 32: e = p.c.waves == 8 ? calib_err<32, 8>(d, p, s) : calib_err<32, 4>(d, p, s); break;
-        case 64: e = p.c.waves == 8 ? calib_err<64, 8>(d, p, s) : calib_err<64, 4>(d, p, s); break;
+        case 64: e = calib_err<64, 8>(d, p, s); break;
         case 96: e = calib_err<96, 4>(d, p, s); break;
         default: e = calib_err<128, 4>(d, p, s); break;
     }
