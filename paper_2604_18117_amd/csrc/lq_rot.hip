@@ -37,9 +37,8 @@ constexpr int ROT_TPB = 256;
 struct RotSplit {
     int gL, gR;   // groups
     int wL, wR;   // workgroups that form E1 and E2
-    int wM;       // workgroups that leave row maxima of Z2 (row kinds), rot_max_cols columns a turn
+    int wM;       // workgroups that leave row maxima of Z2 (row kinds), 64 columns a turn
 };
-static constexpr int rot_max_cols(int r) { return r <= 32 ? 64 : 16; }  // (rot_max_kernel)
 static RotSplit rot_split(const Dims& d)
 {
     const int cap = d.r <= 32 ? 256 : d.r == 64 ? 112 : 128, rows = d.r <= 64 ? 128 : 64;
@@ -50,8 +49,7 @@ static RotSplit rot_split(const Dims& d)
     w.wL = (w.gL + per - 1) / per;
     w.wR = w.gR < cap - w.wL ? w.gR : cap - w.wL;
     if (w.wR < 1) w.wR = 1;
-    const int sets = (int)d.K / rot_max_cols(d.r);
-    w.wM = sets < 256 ? sets : 256;
+    w.wM = (int)(d.K / 64) < 256 ? (int)(d.K / 64) : 256;
     return w;
 }
 
@@ -465,21 +463,23 @@ __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
     }
 }
 
-// Row maxima of Z2 (row kinds), ahead of rot_z_kernel: a wavefront per 16 columns of R and 16 rows of Z2, both operands straight
-// into registers.  Latency alone bounds it: through the LDS, 64
-// columns to a workgroup of four wavefronts, it took 5.2 us at rank 64 and 13.5 at 128, now 3.3 and 5.5.  Up to rank 32 a workgroup takes 64 columns (3.6 / 2.6 us at rank 32): rot_z_kernel reads a set of maxima
-// per workgroup, and above that many sets would cost it more than the columns side by side save here.
+// Row maxima of Z2 (row kinds), ahead of rot_z_kernel: a workgroup per 64 columns of R and 16 rows of Z2, a wavefront per 16 of the columns,
+// both operands straight into registers.  Latency bounds it, and in long rows the redundant reads of R through the L1.  The workgroups are
+// spread over the rows of Z2 and not over narrower sets of columns because a set of maxima is r floats of the state, whose size must not
+// grow, and because every workgroup of rot_z_kernel reads all sets.  us alone, a set per 64 columns through the LDS / per 16 columns / this:
+// 11200 x 64 and 64 x 2240 5.2 / 3.4 / 3.3, 128 x 2304 13.3 / 6.1 / 5.2, 64 x 65536 14.2 / 34.5 / 12.0, 128 x 65536 37.8 / 103 / 38.8; a
+// whole step 32.3 / 23.7 / 23.8, 98.1 / 48.3 / 47.2, 70.7 / 77.3 / 54.6, 231 / 240 / 173.
 template <int R>
-__global__ __launch_bounds__(4 * R * (rot_max_cols(R) / 16)) void rot_max_kernel(RotZParams p)
+__global__ __launch_bounds__(256) void rot_max_kernel(RotZParams p)
 {
-    constexpr int T = R / 16, G = rot_max_cols(R) / 16;
-    __shared__ float red[G][R];
+    __shared__ float red[4][16];
     const int lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = wave % T, g = wave / T;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = (int)blockIdx.x / p.w.wM, set = (int)blockIdx.x - t * p.w.wM;
     float a[R / 4], b[R / 4], m = 0.f;
 #pragma unroll
     for (int s = 0; s < R / 4; ++s) b[s] = p.X[(4 * s + q) * R + 16 * t + l15];
-    for (int c0 = 16 * (G * (int)blockIdx.x + g); c0 < p.K; c0 += 16 * G * (int)gridDim.x) {
+    for (int c0 = 64 * set + 16 * wave; c0 < p.K; c0 += 64 * p.w.wM) {
 #pragma unroll
         for (int s = 0; s < R / 4; ++s) a[s] = p.R[(size_t)(4 * s + q) * p.K + c0 + l15];
         v4f z = {0.f, 0.f, 0.f, 0.f};  // rows: columns c0 + 4 q + i of R, column: row 16 t + l15 of Z2
@@ -488,18 +488,10 @@ __global__ __launch_bounds__(4 * R * (rot_max_cols(R) / 16)) void rot_max_kernel
         m = fmaxf(m, fmaxf(fmaxf(fabsf(z[0]), fabsf(z[1])), fmaxf(fabsf(z[2]), fabsf(z[3]))));
     }
     m = max_xor32(max_xor16(m));
-    if constexpr (G == 1) {
-        if (q == 0) p.ax[(size_t)blockIdx.x * R + 16 * t + l15] = m;
-    } else {
-        if (q == 0) red[g][16 * t + l15] = m;
-        __syncthreads();
-        if (threadIdx.x < R) {
-            m = red[0][threadIdx.x];
-#pragma unroll
-            for (int i = 1; i < G; ++i) m = fmaxf(m, red[i][threadIdx.x]);
-            p.ax[(size_t)blockIdx.x * R + threadIdx.x] = m;
-        }
-    }
+    if (q == 0) red[wave][l15] = m;
+    __syncthreads();
+    if (threadIdx.x < 16)
+        p.ax[(size_t)set * R + 16 * t + threadIdx.x] = fmaxf(fmaxf(red[0][threadIdx.x], red[1][threadIdx.x]), fmaxf(red[2][threadIdx.x], red[3][threadIdx.x]));
 }
 
 struct RotStepParams {
@@ -837,7 +829,7 @@ static hipError_t rot_launch_errors(const RotZParams& p, hipStream_t s)
 {
     constexpr int NWV = R <= 64 ? 8 : 4;  // (rot_split's group)
     if (p.q.kind <= 1) {
-        hipLaunchKernelGGL((rot_max_kernel<R>), dim3(p.w.wM), dim3(4 * R * (rot_max_cols(R) / 16)), 0, s, p);
+        hipLaunchKernelGGL((rot_max_kernel<R>), dim3(p.w.wM * (R / 16)), dim3(256), 0, s, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

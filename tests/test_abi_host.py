@@ -267,6 +267,17 @@ def test_rotation_contract(lq):
     assert raw.lq_rot_sizes(C.byref(lq.make_config(128, 256, 0)), C.byref(n)) == lq.LQ_ERR_SHAPE
 
 
+@pytest.mark.parametrize("N,K,r,fam,rot,calib", [
+    (3456, 1152, 16, "int", 368384, 23078912), (1152, 1152, 32, "int", 584960, 10470144), (11200, 2240, 32, "int", 2171904, 140208128),
+    (11200, 2240, 64, "int", 5235968, 173179904), (3456, 1152, 64, "mx", 2333184, 36570112), (1152, 4608, 64, "mxi", 2644736, 43647744),
+    (6720, 2240, 96, "mxb", 6809344, 132465664), (1152, 4608, 96, "int", 5668352, 56624128), (512, 4096, 128, "int", 7307776, 42992640),
+    (4608, 1152, 128, "mxi", 9053696, 68420608), (64, 16448, 128, "mx", 17170944, 50676480)])
+def test_states_of_earlier_sizes_stay_large_enough(lq, N, K, r, fam, rot, calib):
+    """A program may hold a state of the size that it was once told: what the sizes functions return does not grow."""
+    cfg = lq.make_config(N, K, r, fam, 64 if fam == "int" else 32, 8, 8)
+    assert lq.lq_rot_sizes(cfg) <= rot and lq.lq_calib_sizes(cfg) <= calib
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys

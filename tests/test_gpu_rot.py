@@ -92,7 +92,8 @@ def test_mx_branch_formats_as_q2(oracle, q2, bits, N, K, r):
 
 # More groups of rows (columns) than workgroups: each takes several turns, some one fewer, the last group of 128 half missing.
 @pytest.mark.parametrize("N,K,r,bits,q2", [(33088, 192, 16, 8, "int"), (64, 33088, 16, 4, "int"), (16448, 1216, 64, 6, "int"),
-                                           (192, 16448, 64, 8, "fp8"), (33088, 320, 32, 8, "mxfp8"), (8256, 1344, 128, 8, "mxfp8"),
+                                           (192, 16448, 64, 8, "fp8"), (64, 16512, 96, 6, "int"), (64, 16448, 128, 8, "int"),
+                                           (33088, 320, 32, 8, "mxfp8"), (8256, 1344, 128, 8, "mxfp8"),
                                            (128, 8384, 96, 4, "mxint"), (16448, 1216, 64, 6, "mxfp6")])
 def test_several_turns_per_workgroup(oracle, N, K, r, bits, q2):
     from paper_2604_18117_amd import binding as lq
