@@ -200,10 +200,14 @@ struct PackMxiResidual {
         if constexpr (FROMQ) return *(const Raw*)(rv + mxi_rq_offset(j, k, r));
         else return *(const Raw*)(R + (size_t)j * K + k);
     }
-    __device__ float rval(const Raw& x, int t) const
+    static constexpr double UNIT = 1.0;
+    __device__ void rval(const Raw& x, float (&v)[4]) const
     {
-        if constexpr (FROMQ) return bf16_value((uint16_t)((t < 2 ? x.x : x.y) >> (16 * (t & 1))));
-        else return x[t];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if constexpr (FROMQ) v[t] = bf16_value((uint16_t)((t < 2 ? x.x : x.y) >> (16 * (t & 1))));
+            else v[t] = x[t];
+        }
     }
     __device__ void encode(int n, int c, const float (&P)[1][16], int q) const
     {

@@ -40,11 +40,12 @@ hipError_t launch_pack_fill(const PackFill& f, hipStream_t s);
 // wavefronts per SIMD are there.  Against R staged through the LDS as fp32, a barrier per chunk and its loads waited for in every one
 // (us a pack call): 4608 x 1152 rank 32, groups of 128, 24.5 -> 18.3, 6720 x 2240 rank 64, groups of 64, 80.4 -> 51.3, 11200 x 2240 rank 128 292 -> 143,
 // MXINT4 4608 x 1152 rank 128 105 -> 49, MXFP4 6720 x 2240 rank 128 135 -> 87; MXFP6 factors, whose decoding every wavefront now does for
-// itself, 6720 x 2240 rank 128 114.5 -> 106.3, 3456 x 1152 rank 32 18.3 -> 19.5.  (One wavefront per row and group, a lane per K value: 111 us for the
+// itself, 6720 x 2240 rank 128 114.5 -> 98.5, rank 96 91.5 -> 76.5, rank 32 38.6 -> 36.8, 3456 x 1152 rank 32 18.5 -> 18.9.  (One wavefront per row and group, a lane per K value: 111 us for the
 // first.)
 //
-// F: lhat(n, j, q, v) dequantised L of row n at j + q, j + q + 4, + 8, + 12 (j a multiple of 16); rload(j, k) row j of R at k .. k + 3 (k inside the source row, a multiple of 4) as stored, rval(raw, t)
-// its dequantised values; encode(n, group, P, q) for the lane's values.
+// F: lhat(n, j, q, v) dequantised L of row n at j + q, j + q + 4, + 8, + 12 (j a multiple of 16); rload(j, k) row j of R at k .. k + 3 (k inside the source row, a multiple of 4) as stored, rval(raw, v)
+// its four dequantised values (UNIT: what lhat and rval together leave out of a product, a power of two that L takes in fp64); encode(n, group, P, q) for the
+// lane's values.
 // The last launch of a pack call: it writes the blob's header too.
 typedef float pack_v4f __attribute__((ext_vector_type(4), aligned(4)));  // (W, L and R are aligned to their elements only)
 struct PackCodes4 {  // four 8-bit codes and their scale
@@ -76,7 +77,7 @@ __global__ __launch_bounds__(256, R < 64 || (R == 64 && sizeof(typename F::Raw) 
         float v[4];
         f.lhat(n, 4 * s, q, v);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) l[s + i] = (double)v[i];
+        for (int i = 0; i < 4; ++i) l[s + i] = (double)v[i] * F::UNIT;
     }
 #pragma unroll
     for (int s = 0; s < D; ++s) rr[s] = f.rload(4 * s + q, kfirst + kl);
@@ -105,8 +106,7 @@ __global__ __launch_bounds__(256, R < 64 || (R == 64 && sizeof(typename F::Raw) 
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
                     float a[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) a[t] = f.rval(rr[s % D], t);
+                    f.rval(rr[s % D], a);
                     rr[s % D] = f.rload(4 * ((s + D) % NS) + q, (s + D < NS ? k0 : knext) + kl);
 #pragma unroll
                     for (int t = 0; t < 4; ++t) d[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[t], l[s], d[t], 0, 0, 0);

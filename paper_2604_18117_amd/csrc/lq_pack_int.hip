@@ -81,10 +81,14 @@ struct PackIntResidual {
         if constexpr (FROMQ) return Raw{*(const uint32_t*)(rq + rq_offset(j, k, r)), sr[j]};
         else return *(const Raw*)(R + (size_t)j * K + k);
     }
-    __device__ float rval(const Raw& x, int t) const
+    static constexpr double UNIT = 1.0;
+    __device__ void rval(const Raw& x, float (&v)[4]) const
     {
-        if constexpr (FROMQ) return (float)(int8_t)(x.c >> (8 * t)) * x.s;
-        else return x[t];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if constexpr (FROMQ) v[t] = (float)(int8_t)(x.c >> (8 * t)) * x.s;
+            else v[t] = x[t];
+        }
     }
     __device__ void encode(int n, int g, const float (&P)[GC][16], int q) const
     {

@@ -178,6 +178,30 @@ def test_wide_dynamic_range_blocks(oracle, elem):
     _compare(oracle, layer, wl.round_to_bf16(X), W, L, R)
 
 
+@pytest.mark.parametrize("elem", [8, 6])
+@pytest.mark.parametrize("r,first", [(32, 0), (32, 1), (64, 0), (96, 2), (128, 0)])
+def test_packed_codes_over_the_whole_range_of_factor_scales(oracle, r, first, elem):
+    """Blocks of R with the largest scale bytes against blocks of L with the smallest (0: 2^-127), the other way round, and between;
+    K with a padding chunk."""
+    from paper_2604_18117_amd import binding as lq
+    N, K = 128, 320
+    rng = np.random.default_rng(r + first)
+    W, L, R = (rng.standard_normal(s).astype(np.float32) for s in ((N, K), (N, r), (r, K)))
+    for b in range(r // 32):
+        eR, eL = [(125, -131), (-131, 125), (60, -66), (0, -6)][(first + b) % 4]
+        R[32 * b:32 * b + 32] *= np.float32(2.0 ** eR)
+        L[:, 32 * b:32 * b + 32] *= np.float32(2.0 ** eL)
+    cfg = lq.make_config(N, K, r, "mxb", 32, elem, elem)
+    got = lq.lq_unpack_weights(cfg, lq.lq_pack_weights(cfg, *(torch.from_numpy(a).cuda() for a in (W, L, R))))
+    pk = oracle.pack_mxb(W, L, R, elem=elem)
+    assert pk.re.max() > 230 or pk.le.max() > 230
+    f8 = oracle.mxb_decode(np.arange(256, dtype=np.uint8), elem)
+    for name, want in (("le", pk.le), ("re", pk.re), ("pe", pk.pe)):
+        assert np.array_equal(n(getattr(got, name)), want), name
+    for name, want, val in (("lq", pk.l8, f8), ("rq", pk.r8, f8), ("pq", pk.pc, E2M1)):
+        assert np.array_equal(val[n(getattr(got, name)).view(np.uint8)], val[want]), name
+
+
 @pytest.mark.parametrize("name", ["c5b_qkv", "c5b_fc2", "c5b6_qkv", "c5b6_fc2", "c4m_qkv"])
 def test_full_size_sampled_rows(oracle, name):
     layer = wl.LAYERS[name]
