@@ -110,10 +110,14 @@ def test_first_step_over_row_blocks_and_a_half_column_block(oracle, N, K, r, g, 
 
 
 # One row block per workgroup of eight wavefronts (the last block's strips past N missing, the last column block 64 wide), and
-# of four; runs of several blocks with eight.
+# of four; runs of several blocks with eight, at every rank that has them and for every quantiser (the last run one block or
+# several, the last block half missing).
 @pytest.mark.parametrize("N,K,r,g,sint4", [(1088, 2112, 16, 64, False), (1088, 2112, 32, 64, True), (1088, 2112, 64, 64, False),
                                            (1088, 2112, 64, 32, "mxfp4"), (1088, 2112, 32, 32, "mxint4"), (1088, 2176, 64, 128, False),
-                                           (192, 320, 64, 64, False), (192, 320, 16, 32, "mxfp4"), (2240, 4672, 64, 32, "mxfp4")])
+                                           (192, 320, 64, 64, False), (192, 320, 16, 32, "mxfp4"), (2240, 4672, 64, 32, "mxfp4"),
+                                           (1856, 2240, 16, 64, False), (1984, 2304, 16, 128, False), (1984, 2240, 16, 64, True),
+                                           (1856, 2240, 16, 32, "mxfp4"), (1984, 2240, 32, 64, False), (1856, 2304, 32, 128, False),
+                                           (1984, 2240, 32, 32, "mxfp4"), (1856, 2240, 32, 32, "mxint4")])
 def test_first_step_with_strips_past_the_last_row(oracle, N, K, r, g, sint4):
     test_first_step_over_row_blocks_and_a_half_column_block(oracle, N, K, r, g, sint4)
 
