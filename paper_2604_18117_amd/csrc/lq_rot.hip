@@ -209,7 +209,8 @@ __global__ __launch_bounds__(64 * NWV) void rot_z_kernel(RotZParams p)
     // the group's rows of L or columns of R: requested a turn ahead, the first with everything else a workgroup needs at its start
     constexpr int NX = R * R / 4 / NTHR > 0 ? R * R / 4 / NTHR : 1, NG = ROWS * R / 4 / NTHR;
     v4f xv[NX], lv[NG];
-    // (buffer loads: rows and columns past the end are out of range and read as zeros, without a branch the other side would wait at)
+    // (buffer loads: rows and columns past the end are out of range and read as zeros, without a branch the other side would wait at; R is
+    // below 2^31 bytes, so offsets and lengths fit)
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
     auto load_group = [&](int row0) {
         const int n = nrows - row0 < ROWS ? nrows - row0 : ROWS;

@@ -250,3 +250,31 @@ def test_update_split_over_columns(oracle, r, q2, s):
     that the passes alternate between; the smallest factors."""
     from paper_2604_18117_amd import binding as lq
     _compare_step(oracle, lq, 64, 64, r, 8, seed=r + s, q2=q2, lr=0.5, beta=0.9, s=s, grad_scale=500.0)
+
+
+@pytest.mark.parametrize("r,q2", [(64, "fp8"), (96, "mxint"), (128, "int")])
+def test_rows_as_long_as_the_contract_allows(oracle, r, q2):
+    """The longest rows that are accepted, R just under 2 GB.  Everything but the last 64 columns of R (whose every row has
+    values) is zero, so the errors, the gradient and the rotated factor are those of a factor of 64 columns."""
+    from paper_2604_18117_amd import binding as lq
+    N, K, k = 64, ((1 << 29) - 1) // r // 64 * 64, 64
+    L, R, X0, M0 = _case(N, k, r, r)
+    L[:] = 0.0                                     # G is R E2^T alone
+    cfg = _cfg(lq, N, K, r, 8, q2)
+    with pytest.raises(lq.LqError):
+        lq.lq_rot_sizes(_cfg(lq, N, K + 64, r, 8, q2))
+    Ld, Rd = _d(L), torch.zeros((r, K), dtype=torch.float32, device="cuda")
+    Rd[:, -k:] = _d(R)
+    state = lq.lq_rot_init(cfg, _d(X0), _d(M0))
+    _, Rr = lq.lq_rot_apply(cfg, Ld, Rd, state)
+    assert np.array_equal(Rr[:, -k:].cpu().numpy(), oracle.rot_apply(L, R, X0)[1])
+    assert not bool(Rr[:, :-k].any())
+    del Rr
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    lq.lq_rot_step(cfg, Ld, Rd, state, loss=loss)
+    got = lq.lq_rot_unpack(cfg, state, ("G", "E2"))
+    ref = oracle.rot_step(L, R, oracle.rot_init(r, X0, M0), bits=8, q2=q2)
+    assert np.array_equal(got["E2"][:, -k:].cpu().numpy(), ref.E2)
+    assert not bool(got["E2"][:, :-k].any())
+    assert float(loss.item()) == pytest.approx(ref.loss * k / K, rel=1e-5)      # means over r x K
+    assert np.abs(got["G"].cpu().numpy() - ref.G * (k / K)).max() <= 1e-5 * np.abs(ref.G).max() * (k / K)
