@@ -19,7 +19,8 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // every workgroup slot of the device still taken, so that grad_R has few parts.  Up to rank 64 a workgroup has 8 wavefronts
 // (half the parts of grad_R that two workgroups of 4 on the same compute unit leave), or 4 up to rank 32 where that shortens
 // the longest chain of strips on a compute unit (at rank 64 it would, 1152 x 1152 19.8 us a step instead of 24.2, but leaves more parts
-// than states of earlier sizes hold); from rank 96 on the LDS holds 4.
+// than states of earlier sizes hold); from rank 96 on the LDS holds 4.  The split decides the size of the state, which a program asks for
+// without a device: it counts the 256 compute units of an MI355X and not those of the current device.
 constexpr int CALIB_COLS = 128;
 struct CalibSplit {
     int waves;      // wavefronts per workgroup

@@ -121,16 +121,17 @@ __global__ __launch_bounds__(256, R < 64 || (R == 64 && sizeof(typename F::Raw) 
     }
     write_tag(blob, tag);
 }
-// Scale groups per run.  A compute unit works through ceil(workgroups / 256) of them, each its chunks and about 0.7 of a chunk's
+// Scale groups per run.  A compute unit works through ceil(workgroups / units) of them, each its chunks and about 0.7 of a chunk's
 // time until its rows' factors and first operands are there; the matrix unit is busy from about 2.5 workgroups per compute unit on.
 // (Runs as long as 2048 workgroups allow, 6720 x 2240 rank 64 takes 59.7 us instead of 54.5, 11200 x 2240 rank 128 169.5 instead of 153.3.)
 static inline int pack_residual_run(int rb, int groups, int gc)
 {
+    const int units = compute_units();
     int best = 1;
     int64_t best_cost = 0;
     for (int per = 1; per <= groups; ++per) {
-        const int64_t wgs = (int64_t)rb * ((groups + per - 1) / per), cost = (wgs + 255) / 256 * (10 * per * gc + 7);
-        if (per > 1 && wgs < 640) break;
+        const int64_t wgs = (int64_t)rb * ((groups + per - 1) / per), cost = (wgs + units - 1) / units * (10 * per * gc + 7);
+        if (per > 1 && 2 * wgs < 5 * units) break;
         if (per == 1 || cost < best_cost) {
             best = per;
             best_cost = cost;
