@@ -282,9 +282,9 @@ lq_status lq_calib_unpack(const lq_config *cfg, const void *state, const lq_cali
    the product (L Omega)(Omega^T R) = L R unchanged.  Q2 is the branch weight format cfg->br_w along the rows of L Omega
    and of Omega^T R, as lq_pack_weights quantises L and R: symmetric integers (INT family) or FP8 E4M3 (MX family with
    the fp32-scaled branch) with one fp32 scale per row, or MXFP8e4 / MXFP6e2 / MXINT8 / MXINT4 blocks of 32 along the row
-   with E8M0 scales; rank >= 16, rank * K < 2^29 (LQ_ERR_UNSUPPORTED
-   above: R is read with 32-bit byte offsets).  The main formats of cfg play no part.  Both products are fp32 fused-multiply-add chains over the rank index, ascending
-   from zero.  The rounding is treated as having zero derivative (App. B.2), so
+   with E8M0 scales; rank >= 16, rank * K < 2^29 (LQ_ERR_UNSUPPORTED above: R is read with 32-bit byte offsets).  The main
+   formats of cfg play no part.  Both products are fp32 fused-multiply-add chains over the rank index, ascending from zero.
+   The rounding is treated as having zero derivative (App. B.2), so
        G = -2/(N r) L^T E1 - 2/(r K) R E2^T ,   E1 = Q2(L Omega) - L Omega,  E2 = Q2(Omega^T R) - Omega^T R ,
    times grad_scale.  The update is the Cayley SGD with momentum of the work the paper cites for it (Li et al. 2020,
    Algorithm 1; X = Omega, Frobenius norm):

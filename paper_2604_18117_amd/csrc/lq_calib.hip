@@ -163,8 +163,8 @@ __device__ __forceinline__ float max_row8(float v)
 // the wavefront's own part of the LDS; there is no barrier inside the run, so wavefronts drift apart and one's loads
 // and stores lie beside another's products, and the next strip is requested as soon as the strip's registers are free.  The sum
 // over the wavefronts behind the run moves 16 r x 128 floats through the LDS: a run of one block is shorter without it.
-// What bounds it: all wavefronts of a short run load, multiply and store at the same time (3456 x 1152 at rank 32: 44 MB, 9 us at 5 TB/s,
-// then 5.7 us of the matrix unit); long runs the matrix unit.  Against one kernel form with barriers between all phases,
+// What bounds it: all wavefronts of a short run load, multiply and store at the same time (3456 x 1152 at rank 32: 40 MB, 8 us at 5 TB/s,
+// then 5.7 us of the matrix unit, busy 38 % of the launch); long runs the matrix unit (11200 x 2240 at rank 64: 63 %).  Against one kernel form with barriers between all phases,
 // dword loads and stores and E read back for grad_R (us a step): 3456 x 1152 rank 16 16.3 -> 14.5, rank 32 22.1 -> 19.8, rank 64
 // 30.5 -> 29.9, 4608 x 1152 MXFP4 rank 32 34.0 -> 28.6, 11200 x 2240 rank 16 54.3 -> 46.3, rank 32 75.0 -> 69.2, rank 64 134.4 -> 118.2,
 // rank 128 254.5 -> 214.4.  A run of one strip in the other form: 3456 x 1152 rank 32 20.1, rank 64 31.4.

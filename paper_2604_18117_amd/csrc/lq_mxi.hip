@@ -994,11 +994,11 @@ constexpr int LDS_BYTES = LDS_MAIN > 4 * EPI_WAVE ? LDS_MAIN : 4 * EPI_WAVE;
 
 // One tile of 128 rows: WN = 4 wavefronts side by side of 128 x 64 outputs each, or, for a last column of tiles of at most 128 channels,
 // 2 x 2 wavefronts of 64 x 64 (side by side two of the four would have no columns).  Inside the K loop the 6-bit matrix
-// rate (512 cycles a step for the two wavefronts of a SIMD) is the largest of several: a step takes 676 (K = 4608) to 800 cycles (K = 1152), with
+// rate (512 cycles a step for the two wavefronts of a SIMD) is the largest of several: a step takes 790 (K = 4608) to 870 cycles (K = 1152), with
 // 24 instructions that unpack codes and 9 KB through the LDS per wavefront; around it instruction latency.  Codes as 8-bit operands (FP8
 // subnormals) took 1024 cycles of the matrix core a step: us with those / as it is, rank 64: 16384 x 1152 -> 3456 68.3 / 64.5, 5000 x 2240 -> 6720
-// 63.9 / 53.9, 16384 x 1152 -> 1152 23.8 / 21.9, rank 128 16384 x 4608 -> 1152 68.7 / 59.8, 16384 x 1152 -> 4608 with hand-off 105.5 / 98.1 (the
-// clock falls as the matrix core gets busier: 38 -> 31 thousand cycles a tile).  The fences in the loop
+// 63.9 / 53.9, 16384 x 1152 -> 1152 23.8 / 21.9, rank 128 16384 x 4608 -> 1152 68.7 / 59.8, 16384 x 1152 -> 4608 with hand-off 105.5 / 98.1 (38 -> 30
+// thousand cycles a tile: prologue 3.0, loop 15.2, branch 4.7, epilogue with the hand-off 7.2).  The fences in the loop
 // hold every load two steps ahead of its use: left to itself the compiler sinks them to the end of their step and waits for all of
 // them in the next (us without the fences / without the narrow tiles / as it is: 16384 x 4608 -> 1152 rank 128 66.4 / 64.5 / 59.8, 16384 x
 // 1152 -> 3456 69.7 / 63.2 / 64.5, 16384 x 1152 -> 1152 22.9 / 22.8 / 21.9, 5000 x 2240 -> 6720 56.5 / 54.3 / 53.9).
@@ -1276,8 +1276,9 @@ __global__ __launch_bounds__(256, 2) void mxi_fwd_kernel(MxiFwdParams p)
 // Small layers: a wavefront (a workgroup of its own) per tile of NRB*32 x NCB*32 outputs.  Where the 128 x 256 tiles leave most of the
 // chip idle, the time of a call is one tile's serial chain of steps; here nothing is shared between wavefronts (no LDS staging, no
 // barriers) and both operand streams are requested DEPTH quads of 64-chunks ahead, as packed codes, and unpacked in registers.
-// Bounded by that chain for a few tiles (128 x 1152 -> 3456: 10.6 -> 4.2 us, 128 x 4608 -> 1152: 30.3 -> 8.6 us, both measured with codes as
-// 8-bit operands; 6-bit ones 10.2 -> 9.1 with both operands from memory), by the operands' L2 traffic for many.  Same products in the same order as mxi_fwd_kernel.  HO: as there.
+// Bounded by that chain for a few tiles (128 x 1152 -> 3456 and 128 x 4608 -> 1152, large tiles / this, both with codes as 8-bit operands: 10.6 /
+// 4.2 and 30.3 / 8.6 us; this with 8-bit / 6-bit operands, calls of one captured graph: 4.1 / 3.8 and 8.4 / 7.4 with the operands in the caches,
+// 5.1 / 4.8 and 10.7 / 9.6 with them from memory), by the operands' L2 traffic for many.  Same products in the same order as mxi_fwd_kernel.  HO: as there.
 template <int NK16, bool DBG, bool HO, int NRB, int NCB>
 __global__ __launch_bounds__(64, 2) void mxi_fwd_small_kernel(MxiFwdParams p)
 {
@@ -1448,23 +1449,26 @@ static void mxi_fwd_launch(const MxiFwdParams& p, hipStream_t s)
 {
     // Small layers, by the number T of 32 x 32 tiles (the device holds 2048 wavefronts of these kernels): one tile to a
     // wavefront, larger ones as the L2 traffic of the operands (2, 1.5 and 1 KB per tile and 64-chunk) begins to count, the
-    // 128 x 256 tiles once they occupy enough of the chip.  us, 1 x 1 / 2 x 1 / 2 x 2:
-    //   T =  108 (   2 x 1152 -> 3456): 5.5 / 5.9 / 7.0               T = 1728 ( 512 x 1152 -> 3456):  7.8 /  6.8 /  7.8
-    //   T =  144 ( 128 x 4608 -> 1152): 9.1 / 11.9 / 16.0             T = 3360 ( 512 x 2240 -> 6720): 17.2 / 12.6 / 13.2
-    //   T = 1152 (1024 x 4608 -> 1152): 13.8 / 14.9 / 19.6            T = 5076 (1500 x 1152 -> 3456): 16.2 / 13.8 / 11.9
+    // 128 x 256 tiles once they occupy enough of the chip.  us, the forward's part of activation step and forward, rank 64, the calls of one
+    // captured graph with all buffers in turn over 800 MB (the codes of X freshly written, the weights from memory); 1 x 1 / 2 x 1 / 2 x 2:
+    //   T =  108 (   2 x 1152 -> 3456):  4.2 /  5.5 /  7.5            T = 1728 ( 512 x 1152 -> 3456):  9.5 /  8.6 / 10.4
+    //   T =  144 ( 128 x 4608 -> 1152): 10.9 / 16.1 / 23.1            T = 3360 ( 512 x 2240 -> 6720): 21.5 / 16.7 / 17.3
+    //   T = 1152 (1024 x 4608 -> 1152): 13.6 / 14.8 / 21.2            T = 5076 (1500 x 1152 -> 3456): 19.0 / 15.9 / 12.9
     // 2 x 2 / 128 x 256:
-    //   T = 5040 (4476 x  896 -> 1152): 10.1 / 10.9                   T = 5076 (1500 x 1152 -> 3456): 12.0 / 12.1
-    //   T = 5696 (11389 x 1024 -> 512): 10.9 / 11.8                   T = 6516 (5762 x  896 -> 1152): 11.5 / 11.3
-    //   T = 5400 (4770 x 2240 -> 1152): 16.4 / 17.6                   T = 6192 (5500 x 4608 -> 1152): 27.8 / 26.3
-    // 12 chunks of K and fewer: the large tiles' prologue weighs more (T = 6144, 8192 x 512 -> 768: 8.8 / 9.6; T = 6912, 1700 x 768 ->
-    // 4096: 11.2 / 11.5).  More large tiles than compute units (the tiles of a layer of 128 channels are half-sized): some units get a
-    // second one, and the call takes a generation more (T = 6396, 17052 x 832 -> 384: 11.7 / 12.0; T = 6990, 37274 x 2240 -> 192: 18.6 /
-    // 22.0; T = 5150, 82394 x 1152 -> 64: 14.8 / 17.4).
-    // With the hand-off, whose codes they form in registers, the large tiles are ahead earlier (T = 3168, 700 x 1152 -> 4608: 11.6 / 13.4; T = 4104,
-    // 1200 x 1152 -> 3456: 14.1 / 13.6; T = 4596, 12238 x 1152 -> 384: 15.2 / 13.4), also past one per compute unit in short rows (T = 5800, 18532
-    // x 896 -> 320: 15.7 / 14.0; 18545 x 2240 -> 320: 20.9 / 20.4), earlier or later by how many wavefronts their last column leaves without
-    // channels (T = 6348, 33847 x 512 -> 192: 13.7 / 14.2; T = 4600, 73590 x 896 -> 64: 17.0 / 17.2, 73577 x 64 -> 64: 12.3 / 10.3).
-    // Over 3000 random calls of T between 1500 and 9000 both forms were timed: 119 are more than 3 % slower than in the better one, 33 more than 8 %.
+    //   T = 5040 (4476 x  896 -> 1152): 11.1 / 11.8                   T = 5076 (1500 x 1152 -> 3456): 13.2 / 13.3
+    //   T = 5696 (11389 x 1024 -> 512): 11.3 / 11.7                   T = 6516 (5762 x  896 -> 1152): 12.6 / 12.4
+    //   T = 5400 (4770 x 2240 -> 1152): 17.6 / 17.3                   T = 6192 (5500 x 4608 -> 1152): 29.5 / 27.2
+    // 12 chunks of K and fewer: the large tiles' prologue weighs more (T = 6144, 8192 x 512 -> 768: 9.5 / 9.9; T = 6912, 1700 x 768 ->
+    // 4096: 12.6 / 12.6).  More large tiles than compute units (the tiles of a layer of 128 channels are half-sized): some units get a
+    // second one, and the call takes a generation more (T = 6396, 17052 x 832 -> 384: 12.1 / 11.9; T = 6990, 37274 x 2240 -> 192: 18.0 /
+    // 21.9; T = 8010, 42700 x 1152 -> 192: 14.3 / 14.7; T = 5150, 82394 x 1152 -> 64: 13.1 / 19.8).
+    // With the hand-off, whose codes they form in registers, the large tiles are ahead earlier (T = 3168, 700 x 1152 -> 4608: 14.8 / 15.3; T = 4104,
+    // 1200 x 1152 -> 3456: 16.0 / 15.2; T = 4596, 12238 x 1152 -> 384: 15.6 / 13.3), also past one per compute unit (T = 5800, 18532 x 896 -> 320: 15.8 /
+    // 13.9; 18545 x 2240 -> 320: 20.4 / 18.5), later by how many wavefronts their last column leaves without
+    // channels (T = 6348, 33847 x 512 -> 192: 13.6 / 13.2; T = 4600, 73590 x 896 -> 64: 13.8 / 14.5, 73577 x 64 -> 64: 11.5 / 9.5).
+    // Over 5965 random calls of T between 1500 and 9000 measured in the same way in both forms, 508 are more than 3 % of the forward slower than
+    // in the better one, 222 more than 8 %; with the lines at 7000 and 5000 instead of 8000 and 5800 589 and 286.  (With everything from
+    // memory the large tiles are ahead earlier, with everything in the caches later.)
     const int64_t T = (int64_t)p.nrb * (p.N / 32);
     const bool over = (p.N == 128 ? (p.tilesM + 1) / 2 : p.tilesM * p.tilesN) > compute_units();
     const int over_ho = (p.N & 255) == 192 ? 1 : p.N < 256 ? 12 : 20;  // with the hand-off: chunks from which a second generation counts

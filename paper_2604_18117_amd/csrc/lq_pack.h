@@ -36,8 +36,8 @@ hipError_t launch_pack_fill(const PackFill& f, hipStream_t s);
 // k = 16 q .. 16 q + 15 of every chunk (the block maxima are one or two lane exchanges, the codes leave as whole dwords), and
 // that the first operand of the four tiles at one rank index is four consecutive values of a row of R: one load per lane, codes of
 // 8 bits in one dword.  So the wavefronts share nothing: no LDS, no barriers, D rank steps of R in flight across chunks and
-// the next chunk of W requested under the products.  What bounds it is the fp64 matrix rate (64 cycles a product) once three
-// wavefronts per SIMD are there.  Against R staged through the LDS as fp32, a barrier per chunk and its loads waited for in every one
+// the next chunk of W requested under the products.  What bounds it: at high ranks the fp64 matrix rate (64 cycles a
+// product; the pipe is busy 61 % at 11200 x 2240 rank 128, 54 % at 6720 x 2240 rank 64), below that how few wavefronts a SIMD has (33 % at 4608 x 1152 rank 32).  Against R staged through the LDS as fp32, a barrier per chunk and its loads waited for in every one
 // (us a pack call): 4608 x 1152 rank 32, groups of 128, 24.5 -> 18.3, 6720 x 2240 rank 64, groups of 64, 80.4 -> 51.3, 11200 x 2240 rank 128 292 -> 143,
 // MXINT4 4608 x 1152 rank 128 105 -> 49, MXFP4 6720 x 2240 rank 128 135 -> 87; MXFP6 factors, whose decoding every wavefront now does for
 // itself, 6720 x 2240 rank 128 114.5 -> 98.5, rank 96 91.5 -> 76.5, rank 32 38.6 -> 36.8, 3456 x 1152 rank 32 18.5 -> 18.9.  (One wavefront per row and group, a lane per K value: 111 us for the
