@@ -178,21 +178,21 @@ struct PackMxBlock4 {  // four codes and their block's scale byte
     uint32_t c, e;
 };
 typedef uint32_t u32_bytes __attribute__((aligned(1)));
-// Four E2M3 codes of 24 bits as the E4M3 bytes of their values * 2^-6 (normal and subnormal alike)
+// Four E2M3 codes of 24 bits (what is above is not looked at) as the E4M3 bytes of their values * 2^-6 (normal and subnormal alike)
 __device__ __forceinline__ uint32_t e4m3_of_fp6(uint32_t c)
 {
     const uint32_t h = (c & 0xFFFu) | (c << 4 & ~0xFFFu);                   // two codes to a half
     const uint32_t b = (h & 0x003F003Fu) | (h << 2 & ~0x003F003Fu);         // a code to a byte, bits 6 and 7 of no meaning
     return (b & 0x1F1F1F1Fu) | (b << 2 & 0x80808080u);
 }
-// ... and as fp32 values times 2^-6, with their block's scale byte E <= 254: the converter multiplies by any 2^(E - 127), 2^-127 among them
-// (checked against ldexp over all codes and scales), and no value has bits below 2^-149.  (With an ldexp per value and ten instructions to spread
-// the codes, us a pack call: 4608 x 1152 rank 32 23.4 / 22.4, 6720 x 2240 rank 64 62.0 / 57.6, rank 96 99.1 / 76.5, rank 128 105.8 / 98.5.)
-__device__ __forceinline__ void fp6_quad(uint32_t c, uint32_t E, float (&v)[4])
+// Four E4M3 codes times 2^(E - 127), E <= 254 their block's scale byte: the converter multiplies by any such power, 2^-127 among them (checked
+// against ldexp over all codes and scales; subnormal results are exact).  Codes of E2M3 give their values times 2^-6.  (With an ldexp per
+// value, and ten instructions to spread the 6-bit codes, every wavefront's decoding of R cost more than reading it decoded from the LDS had: us a pack
+// call, staged / ldexp / this: MXFP6 4608 x 1152 rank 32 21.5 / 22.5 / 20.8, 6720 x 2240 rank 96 92.0 / 99.2 / 78.5, MXFP8 8192 x 9216 rank 32 129 / 138 / 122.)
+__device__ __forceinline__ void fp8_block_quad(uint32_t c, uint32_t E, float (&v)[4])
 {
-    const uint32_t b = e4m3_of_fp6(c);
     const float s = __uint_as_float(E << 23);
-    const auto lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(b, s, false), hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(b, s, true);
+    const auto lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c, s, false), hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c, s, true);
     v[0] = lo[0], v[1] = lo[1], v[2] = hi[0], v[3] = hi[1];
 }
 template <int KIND>
@@ -223,7 +223,7 @@ struct PackMxResidual {
             uint32_t c = 0u;  // the lane's four, in 24 bits
 #pragma unroll
             for (int i = 0; i < 4; ++i) c |= (d[i] >> (6 * q) & 63u) << (6 * i);
-            fp6_quad(c, ((const uint8_t*)sl)[mxb_scale_offset(n, j >> 5)], v);
+            fp8_block_quad(e4m3_of_fp6(c), ((const uint8_t*)sl)[mxb_scale_offset(n, j >> 5)], v);
         }
     }
     __device__ Raw rload(int j, int k) const
@@ -237,16 +237,16 @@ struct PackMxResidual {
         }
     }
     static constexpr double UNIT = KIND == 3 ? 4096.0 : 1.0;
+    static constexpr bool PAD_CHECK = true;
     __device__ void rval(const Raw& x, float (&v)[4]) const
     {
-        if constexpr (KIND == 3) {
-            fp6_quad(x.c, x.e, v);
+        if constexpr (KIND >= 2) {
+            fp8_block_quad(KIND == 3 ? e4m3_of_fp6(x.c) : x.c, x.e, v);
         } else {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 if constexpr (KIND == 0) v[t] = x[t];
-                else if constexpr (KIND == 1) v[t] = __fmul_rn(fp8_value_of(x.c, t), x.s);
-                else v[t] = ldexpf(fp8_value_of(x.c, t), (int)x.e - 127);
+                else v[t] = __fmul_rn(fp8_value_of(x.c, t), x.s);
             }
         }
     }

@@ -201,6 +201,7 @@ struct PackMxiResidual {
         else return *(const Raw*)(R + (size_t)j * K + k);
     }
     static constexpr double UNIT = 1.0;
+    static constexpr bool PAD_CHECK = true;
     __device__ void rval(const Raw& x, float (&v)[4]) const
     {
 #pragma unroll

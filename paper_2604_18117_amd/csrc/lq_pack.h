@@ -2,6 +2,8 @@
 // on the fp64 matrix instruction and handed to the family's encoder, and the kernel that presets blob sections.
 #pragma once
 
+#include <type_traits>
+
 #include "lq_internal.h"
 
 namespace lq {
@@ -37,15 +39,20 @@ hipError_t launch_pack_fill(const PackFill& f, hipStream_t s);
 // that the first operand of the four tiles at one rank index is four consecutive values of a row of R: one load per lane, codes of
 // 8 bits in one dword.  So the wavefronts share nothing: no LDS, no barriers, D rank steps of R in flight across chunks and
 // the next chunk of W requested under the products.  What bounds it: at high ranks the fp64 matrix rate (64 cycles a
-// product; the pipe is busy 61 % at 11200 x 2240 rank 128, 54 % at 6720 x 2240 rank 64), below that how few wavefronts a SIMD has (33 % at 4608 x 1152 rank 32).  Against R staged through the LDS as fp32, a barrier per chunk and its loads waited for in every one
-// (us a pack call): 4608 x 1152 rank 32, groups of 128, 24.5 -> 18.3, 6720 x 2240 rank 64, groups of 64, 80.4 -> 51.3, 11200 x 2240 rank 128 292 -> 143,
-// MXINT4 4608 x 1152 rank 128 105 -> 49, MXFP4 6720 x 2240 rank 128 135 -> 87; MXFP6 factors, whose decoding every wavefront now does for
-// itself, 6720 x 2240 rank 128 114.5 -> 98.5, rank 96 91.5 -> 76.5, rank 32 38.6 -> 36.8, 3456 x 1152 rank 32 18.5 -> 18.9.  (One wavefront per row and group, a lane per K value: 111 us for the
-// first.)
+// product; the pipe is busy 62 % at 11200 x 2240 rank 128, 54 % at 6720 x 2240 rank 64), below that how few wavefronts a SIMD has (34 % at
+// 4608 x 1152 rank 32).  Against R staged through the LDS as fp32, a barrier per chunk and its loads waited for in every one
+// (us a pack call): 4608 x 1152 rank 32, groups of 128, 24.5 -> 17.0, 6720 x 2240 rank 64, groups of 64, 80.4 -> 51.1, 11200 x 2240 rank 128 292 -> 139,
+// MXINT4 4608 x 1152 rank 128 105 -> 50, MXFP4 6720 x 2240 rank 128 135 -> 84; MXFP6 factors, whose decoding every wavefront now does for
+// itself, 6720 x 2240 rank 128 114.7 -> 97.2, rank 96 91.6 -> 78.8, 3456 x 1152 rank 32 18.3 -> 18.3.  Factors as given move 16 bytes of R per lane and
+// rank step, which a workgroup then read once and now reads four times: MX layers up to rank 64 that are small or short of rows take up to 6 %
+// longer (2240 x 1920 rank 32 17.1 -> 18.1, 1664 x 2688 rank 64 33.7 -> 35.7; 6848 x 9344 at rank 16 76 -> 85), the others are faster (6720 x 2240 rank 128
+// 148 -> 88).  (One wavefront per row and group, a lane per K value: 111 us for the first.)
 //
-// F: lhat(n, j, q, v) dequantised L of row n at j + q, j + q + 4, + 8, + 12 (j a multiple of 16); rload(j, k) row j of R at k .. k + 3 (k inside the source row, a multiple of 4) as stored, rval(raw, v)
-// its four dequantised values (UNIT: what lhat and rval together leave out of a product, a power of two that L takes in fp64); encode(n, group, P, q) for the
-// lane's values.
+// F: lhat(n, j, q, v) dequantised L of row n at j + q, j + q + 4, + 8, + 12 (j a multiple of 16); rload(j, k) row j of R at k .. k + 3 (k inside the
+// source row, a multiple of 4) as stored, rval(raw, v) its four dequantised values (UNIT: what lhat and rval together leave out of a product, a
+// power of two that L takes in fp64); encode(n, group, P, q) for the lane's values; PAD_CHECK: the layout may have a chunk of padding behind the
+// source's last one (MX), or has none but the compiler allocates registers better with the check (without it groups of 128 with factors as
+// given spill 12 at rank 32, MXINT takes 4 % longer at ranks 64 and 96).
 // The last launch of a pack call: it writes the blob's header too.
 typedef float pack_v4f __attribute__((ext_vector_type(4), aligned(4)));  // (W, L and R are aligned to their elements only)
 struct PackCodes4 {  // four 8-bit codes and their scale
@@ -56,20 +63,19 @@ template <int R, int GC, typename F>
 __global__ __launch_bounds__(256, R < 64 || (R == 64 && sizeof(typename F::Raw) <= 8) ? 3 : 2) void pack_residual_kernel(F f, const float* W, int Ks, int groups, int per, uint32_t* blob, BlobTag tag)
 {
     typedef double v4d __attribute__((ext_vector_type(4)));
-    constexpr int NS = R / 4, DMAX = sizeof(typename F::Raw) > 8 || (GC == 2 && R >= 64) ? 4 : 8, D = NS < DMAX ? NS : DMAX;  // (registers)
+    constexpr int NS = R / 4, DMAX = (sizeof(typename F::Raw) > 8 && (R > 32 || GC == 2)) || (GC == 2 && R >= 64) ? 4 : 8, D = NS < DMAX ? NS : DMAX;  // (registers)
     static_assert(NS == 0 || NS % D == 0, "whole turns of the ring");
     const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q = lane >> 4, wave = tid >> 6;
     const int runs = (groups + per - 1) / per;
     const int n = (blockIdx.x / runs) * 64 + 16 * wave + l15;
     const int g0 = (blockIdx.x % runs) * per, g1 = g0 + per < groups ? g0 + per : groups;
     const int kl = 16 * (l15 & 3) + 4 * (l15 >> 2);  // the lane's K values of a chunk as first operand
-    const int kend = Ks - 64;                        // the last source chunk
     pack_v4f w[4];
     auto request = [&](int k0) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) w[t] = *(const pack_v4f*)(W + (size_t)n * Ks + k0 + 16 * q + 4 * t);
     };
-    const int kfirst = g0 * GC * 64 < kend ? g0 * GC * 64 : kend;  // (a run may be layout padding alone)
+    const int kfirst = !F::PAD_CHECK || g0 * GC * 64 < Ks ? g0 * GC * 64 : Ks - 64;  // (a run may be layout padding alone)
     double l[NS + 1];
     typename F::Raw rr[D + 1];
 #pragma unroll
@@ -82,42 +88,66 @@ __global__ __launch_bounds__(256, R < 64 || (R == 64 && sizeof(typename F::Raw) 
 #pragma unroll
     for (int s = 0; s < D; ++s) rr[s] = f.rload(4 * s + q, kfirst + kl);
     if constexpr (R > 0) request(kfirst);
-    for (int g = g0; g < g1; ++g) {
+    // A chunk's products.  `more`: the run has a source chunk behind it.  Where the ring holds half a chunk or more, a run's last chunk is code of
+    // its own that requests nothing past it: refilled from the same chunk, as above that, the ring would fetch up to all of R once more, and many
+    // runs are one chunk long (us a pack call, MX: factors as given 2240 x 1920 rank 32 20.9 -> 18.1, 18176 x 5120 rank 32 177 -> 147).
+    constexpr bool OWN_LAST = R <= 32 || (R == 64 && GC == 1 && sizeof(typename F::Raw) <= 8);
+    constexpr bool PAD_INSIDE = F::PAD_CHECK && R <= 64;  // (padding in the same loop, or in one behind it: as three wavefronts of MXFP8 factors fit a SIMD; 5824 x 14848 rank 96 505 -> 353 us)
+    auto products = [&](auto last, bool more, int k0, float (&P)[16]) {
+        constexpr bool LAST = OWN_LAST && decltype(last)::value;
+        if constexpr (OWN_LAST) more = !LAST;
+        const int knext = more ? k0 + 64 : k0;
+        if constexpr (R == 0) request(k0);
+        pack_v4f wc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) wc[t] = w[t];
+        if (R > 0 && more) request(knext);
+        v4d d[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) d[t] = v4d{0.0, 0.0, 0.0, 0.0};
+        if constexpr (R > 0) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                float a[4];
+                f.rval(rr[s % D], a);
+                if (!LAST || s + D < NS) rr[s % D] = f.rload(4 * ((s + D) % NS) + q, (s + D < NS ? k0 : knext) + kl);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) d[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[t], l[s], d[t], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) P[4 * i + t] = (float)((double)wc[i][t] - d[t][i]);
+    };
+    auto group = [&](auto last, bool more, int g) {
         float P[GC][16];
 #pragma unroll
         for (int cc = 0; cc < GC; ++cc) {
             const int k0 = (g * GC + cc) * 64;
-            if (k0 >= Ks) {  // a chunk of layout padding (uniform)
+            if (PAD_INSIDE && k0 >= Ks) {  // a chunk of layout padding (uniform)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) P[cc][e] = 0.f;
                 continue;
             }
-            const bool more = k0 < kend && !(g + 1 == g1 && cc + 1 == GC);
-            const int knext = more ? k0 + 64 : k0;
-            if constexpr (R == 0) request(k0);
-            pack_v4f wc[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) wc[t] = w[t];
-            if (R > 0 && more) request(knext);
-            v4d d[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) d[t] = v4d{0.0, 0.0, 0.0, 0.0};
-            if constexpr (R > 0) {
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    float a[4];
-                    f.rval(rr[s % D], a);
-                    rr[s % D] = f.rload(4 * ((s + D) % NS) + q, (s + D < NS ? k0 : knext) + kl);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) d[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[t], l[s], d[t], 0, 0, 0);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) P[cc][4 * i + t] = (float)((double)wc[i][t] - d[t][i]);
+            if (cc + 1 == GC) products(last, more, k0, P[cc]);
+            else products(std::false_type{}, true, k0, P[cc]);
         }
         f.encode(n, g, P, q);
+    };
+    const int gs = F::PAD_CHECK && Ks / (64 * GC) < g1 ? Ks / (64 * GC) : g1;  // (past the run's last source group)
+    int g = g0;
+    if constexpr (OWN_LAST) {
+        for (; g < gs - 1; ++g) group(std::false_type{}, true, g);
+        for (; g < g1; ++g) group(std::true_type{}, false, g);
+    } else if constexpr (PAD_INSIDE) {
+        for (; g < g1; ++g) group(std::false_type{}, g + 1 < gs, g);
+    } else {
+        for (; g < gs; ++g) group(std::false_type{}, g + 1 < gs, g);
+        if constexpr (F::PAD_CHECK) {
+            const float P[GC][16] = {};
+            for (; g < g1; ++g) f.encode(n, g, P, q);
+        }
     }
     write_tag(blob, tag);
 }

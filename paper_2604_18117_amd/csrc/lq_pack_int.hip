@@ -82,6 +82,7 @@ struct PackIntResidual {
         else return *(const Raw*)(R + (size_t)j * K + k);
     }
     static constexpr double UNIT = 1.0;
+    static constexpr bool PAD_CHECK = GC == 2 && !FROMQ;
     __device__ void rval(const Raw& x, float (&v)[4]) const
     {
 #pragma unroll

@@ -102,3 +102,37 @@ def test_packing_runs_of_groups_and_unaligned_sources(oracle, family, g, bw, ag,
         assert np.array_equal(n(wv.pq)[rows], pk.pq)
     if family != "int":
         assert np.array_equal(n(wv.pe)[rows], pk.pe)
+
+
+@pytest.mark.parametrize("family,g,bw,ag", [("int", 64, 8, 0), ("int", 128, 4, 0), ("int", 64, 6, 64), ("mx", 32, 8, 32), ("mxb", 32, 8, 32),
+                                            ("mxb", 32, 6, 32), ("mxi", 32, 8, 32), ("mxi", 32, 4, 32)])
+@pytest.mark.parametrize("r", [0, 16, 32, 64, 96, 128])
+@pytest.mark.parametrize("from_q", [True, False])
+def test_packing_residual_of_quantised_and_given_factors(oracle, family, g, bw, ag, r, from_q):
+    """Runs of one scale group and of several, whose last chunk requests nothing up to rank 32; an odd number of chunks, which MX layouts pad
+    with one that is the last of its run or a run of its own."""
+    import torch
+    from paper_2604_18117_amd import binding as lq
+    from tests.gpu_util import n
+    if (family == "mx" and r == 96) or (family in ("mxb", "mxi") and r == 16):
+        pytest.skip("not a rank of this branch")
+    for N, K in ((64, 64), (192, 320), (4096, 4672)):
+        K = (K + g - 1) // g * g
+        rng = np.random.default_rng(N + r)
+        W, L, R = ((rng.standard_normal(s) * f).astype(np.float32) for s, f in (((N, K), 0.02), ((N, r), 0.03), ((r, K), 0.03)))
+        cfg = lq.make_config(N, K, r, family, g, bw, bw if family == "mxb" else 8, residual_from_quantized=from_q, a_group=ag)
+        dW, dL, dR = (torch.from_numpy(a).cuda() if a.size else None for a in (W, L, R))
+        wv = lq.lq_unpack_weights(cfg, lq.lq_pack_weights(cfg, dW, dL, dR))
+        rows = np.arange(0, N, 1 if N < 200 else 129)
+        args = (W[rows], L[rows] if r else None, R if r else None)
+        if family == "int":
+            pk = oracle.pack_int(*args, g, bw, residual_from_quantized=from_q, sint4_blocks=ag == 64)
+            assert np.array_equal(n(wv.sw)[rows], pk.sw) and np.array_equal(n(wv.pq)[rows], pk.pq), (N, K)
+            continue
+        pk = oracle.pack_mxi(*args, bw, residual_from_quantized=from_q) if family == "mxi" else \
+            oracle.pack_mx(*args, residual_from_quantized=from_q) if family == "mx" else oracle.pack_mxb(*args, residual_from_quantized=from_q, elem=bw)
+        assert np.array_equal(n(wv.pe)[rows], pk.pe), (N, K)
+        if family == "mxi":
+            assert np.array_equal(n(wv.pq)[rows], pk.pq), (N, K)
+        else:
+            assert np.array_equal(t_mxb.E2M1[n(wv.pq).view(np.uint8)[rows]], t_mxb.E2M1[pk.pc]), (N, K)
