@@ -251,10 +251,15 @@ hipError_t allow_lds(int bytes)
 
 // ---- device helpers ----------------------------------------------------------------------
 #if defined(__HIPCC__)
-// header of an activation blob, written by the first workgroup of the kernel that fills the blob
+// Header of an activation blob (32 bytes, 256-byte aligned), written by the first thread of the kernel that fills the blob, from scalar
+// registers.  Indexed by the thread, the words are a vector load from the kernel arguments, and the wait for it (700 to 1300
+// cycles) stood before everything else this workgroup does, which at 16 rows is the whole grid.
 __device__ __forceinline__ void write_tag(uint32_t* dst, const BlobTag& t)
 {
-    if (blockIdx.x == 0 && threadIdx.x < 8) dst[threadIdx.x] = t.w[threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ((uint4*)dst)[0] = make_uint4(t.w[0], t.w[1], t.w[2], t.w[3]);
+        ((uint4*)dst)[1] = make_uint4(t.w[4], t.w[5], t.w[6], t.w[7]);
+    }
 }
 __device__ __forceinline__ void panel_tile(int tile, int tilesM, int tilesN, int panel, int& tile_m, int& tile_n)
 {

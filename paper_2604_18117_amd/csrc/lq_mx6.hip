@@ -351,10 +351,17 @@ __global__ __launch_bounds__(256) void mx6_act_kernel(Mx6ActParams p)
                 *(v4i*)dst = v4i{(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
                 p.xe[m6_scale_offset(row, c64, q & 1, p.CQ)] = (uint8_t)E;
                 if (NJB > 0) {
+                    // (codes taken out at constant positions: an array indexed at run time is put into the LDS, whose address the compiler
+                    // forms from the workgroup size in the dispatch packet -- in host memory, read by every workgroup: rank 32, 4096 x 1152
+                    // 19.4 us a call, 300 x 1152 7.0; ranks 64 and 96 had it in scratch)
                     if (p.dbg_xb && row_ok && c64 < p.C64s) {
-                        uint32_t cw[8] = {c6[0], c6[1], c6[2], c6[3], c6[4], c6[5], 0u, 0u};
                         int8_t* o = p.dbg_xb + (size_t)row * p.K + (size_t)c * 128 + q * 32;
-                        for (int i = 0; i < 32; ++i) o[i] = (int8_t)fp6_get((const uint8_t*)cw, i);
+#pragma unroll
+                        for (int i = 0; i < 32; ++i) {
+                            const int w = 6 * i / 32, sh = 6 * i % 32;
+                            const uint32_t hi = sh > 26 ? c6[w + 1] << (32 - sh) : 0u;
+                            o[i] = (int8_t)(((c6[w] >> sh) | hi) & 63u);
+                        }
                     }
                     if (p.dbg_xbe && row_ok && c64 < p.C64s) p.dbg_xbe[(size_t)row * (p.K >> 5) + 4 * c + q] = (uint8_t)E;
                     const v8i a8 = {(int)c6[0], (int)c6[1], (int)c6[2], (int)c6[3], (int)c6[4], (int)c6[5], 0, 0};
