@@ -1,8 +1,12 @@
-"""Thin ctypes binding of liblq.so: argument marshalling only, same names as include/lq.h.
+"""Thin binding of liblq.so: argument marshalling only, same names as include/lq.h.
 
 PyTorch is used for device memory and the current stream, nothing else: every step of the
 path runs in the library's kernels.  Importing this module fails loudly when the HIP library
 has not been built (``python paper_2604_18117_amd/build.py``); there is no CPU fallback.
+
+The entry points of a program's loops (activation step, forward, hand-off, packing, calibration and rotation steps) hand their arguments to the
+native module ``_call`` (csrc/lq_call.cpp) as they are; it makes the call where they are of the ordinary kind (status >= 0) and does
+nothing otherwise (-1).  The checks and the ctypes call below each of them then decide, as for every other entry point.
 """
 from __future__ import annotations
 
@@ -18,6 +22,9 @@ _LIB_PATH = os.path.join(_HERE, "liblq.so")
 if not os.path.exists(_LIB_PATH):
     raise ImportError(f"{_LIB_PATH} is missing: build it with `python paper_2604_18117_amd/build.py`")
 _lib = C.CDLL(_LIB_PATH)
+if not os.path.exists(os.path.join(_HERE, "_call.so")):
+    raise ImportError(f"{_HERE}/_call.so is missing: build it with `python paper_2604_18117_amd/build.py`")
+from . import _call  # noqa: E402  (it links liblq.so)
 
 LQ_OK = 0
 LQ_ERR_NULL, LQ_ERR_SHAPE, LQ_ERR_UNSUPPORTED, LQ_ERR_ALIGN, LQ_ERR_BUFFER_TOO_SMALL, LQ_ERR_DEVICE, LQ_ERR_STALE_BLOB = range(1, 8)
@@ -33,6 +40,9 @@ class lq_config(C.Structure):
                 ("main_a", C.c_int32), ("main_w_group", C.c_int32), ("main_a_group", C.c_int32),
                 ("br_w", C.c_int32), ("br_a", C.c_int32), ("residual_from_quantized", C.c_int32),
                 ("x_dtype", C.c_int32), ("flags", C.c_int32)]
+
+
+_call.set_config_type(lq_config)
 
 
 class lq_act_debug(C.Structure):
@@ -198,6 +208,10 @@ def lq_act_sizes(cfg: lq_config, M: int) -> int:
 def lq_pack_weights(cfg: lq_config, W: torch.Tensor, L: Optional[torch.Tensor], R: Optional[torch.Tensor],
                     packed: Optional[torch.Tensor] = None) -> torch.Tensor:
     """W (N x K), L (N x r), R (r x K): fp32 CUDA tensors, contiguous.  Returns the packed blob."""
+    st = _call.pack_weights(cfg, W, L, R, packed)
+    if st >= 0:
+        _check(st, "lq_pack_weights")
+        return packed
     assert W.is_cuda and W.dtype == torch.float32 and W.is_contiguous() and tuple(W.shape) == (cfg.N, cfg.K)
     for t in (L, R):
         assert t is None or (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous())
@@ -223,6 +237,8 @@ def lq_quantize_act(cfg: lq_config, packed: torch.Tensor, X: torch.Tensor, act: 
                     debug: bool = False):
     """X: M x K CUDA tensor (fp32 or bf16, row stride may exceed K).  Returns the activation blob
     (and the parity taps when debug=True)."""
+    if not debug and _call.quantize_act(cfg, packed, X, act) == LQ_OK:
+        return act
     assert X.is_cuda and X.dim() == 2 and X.stride(1) == 1 and X.shape[1] == cfg.K
     assert X.dtype == (torch.bfloat16 if cfg.x_dtype == LQ_BF16 else torch.float32)
     M = X.shape[0]
@@ -259,6 +275,11 @@ class FwdDebug:
 def lq_linear_lowrank_fwd(cfg: lq_config, packed: torch.Tensor, act: torch.Tensor, M: int,
                           Y: Optional[torch.Tensor] = None, debug: bool = False, debug_acc: bool = True):
     """Returns Y (M x N bf16); with debug=True also the taps (acc only if debug_acc)."""
+    if not debug:
+        st = _call.linear_lowrank_fwd(cfg, packed, act, M, Y)
+        if st >= 0:
+            _check(st, "lq_linear_lowrank_fwd")
+            return Y
     if Y is None:
         Y = torch.empty((M, cfg.N), dtype=torch.bfloat16, device=act.device)
     assert Y.is_cuda and Y.dtype == torch.bfloat16 and Y.stride(1) == 1 and Y.shape == (M, cfg.N)
@@ -287,6 +308,10 @@ def lq_linear_lowrank_fwd_handoff(cfg: lq_config, packed: torch.Tensor, act: tor
                                   Y: Optional[torch.Tensor] = None):
     """The forward plus the quantized hand-off to a next layer (K = this N).  Returns (act_next, codes); Y (M x N bf16)
     is written only when given."""
+    st = _call.linear_lowrank_fwd_handoff(cfg, packed, act, M, next_cfg, act_next, codes, Y)
+    if st >= 0:
+        _check(st, "lq_linear_lowrank_fwd_handoff")
+        return act_next, codes
     if act_next is None:
         act_next = torch.empty(lq_act_sizes(next_cfg, M), dtype=torch.uint8, device=act.device)
     if codes is None:
@@ -303,6 +328,10 @@ def lq_linear_lowrank_fwd_handoff(cfg: lq_config, packed: torch.Tensor, act: tor
 def lq_branch_from_codes(next_cfg: lq_config, packed_next: torch.Tensor, codes: torch.Tensor, M: int,
                          act_next: torch.Tensor) -> torch.Tensor:
     """Completes act_next (the consumer's intermediate codes and scales) from the hand-off codes."""
+    st = _call.branch_from_codes(next_cfg, packed_next, codes, M, act_next)
+    if st >= 0:
+        _check(st, "lq_branch_from_codes")
+        return act_next
     _check(_lib.lq_branch_from_codes(C.byref(next_cfg), _ptr(packed_next), 0 if packed_next is None else packed_next.numel(),
                                      _ptr(codes), codes.numel(), M, _ptr(act_next),
                                      act_next.numel(), _stream()), "lq_branch_from_codes")
@@ -393,6 +422,9 @@ def lq_calib_init(cfg: lq_config, L: torch.Tensor, R: torch.Tensor, state: Optio
 def lq_calib_step(cfg: lq_config, W: torch.Tensor, state: torch.Tensor, step: int, lr: float = 1e-4, beta1: float = 0.9,
                   beta2: float = 0.999, eps: float = 1e-8, loss: Optional[torch.Tensor] = None) -> None:
     """One Adam step (step counts from 1); `loss`: optional 1-element fp32 CUDA tensor that receives the loss before the update."""
+    st = _call.calib_step(cfg, W, state, step, lr, beta1, beta2, eps, loss)
+    if st >= 0:
+        return _check(st, "lq_calib_step")
     assert W.is_cuda and W.dtype == torch.float32 and W.is_contiguous() and tuple(W.shape) == (cfg.N, cfg.K)
     ad = lq_adam(lr, beta1, beta2, eps)
     _check(_lib.lq_calib_step(C.byref(cfg), _ptr(W), _ptr(state), state.numel(), step, C.byref(ad), _ptr(loss),
@@ -440,6 +472,9 @@ def lq_rot_step(cfg: lq_config, L: torch.Tensor, R: torch.Tensor, state: torch.T
                 eps: float = 1e-8, q: float = 0.5, s: int = 2, grad_scale: float = 1.0,
                 loss: Optional[torch.Tensor] = None) -> None:
     """One Cayley-SGD step on Omega; `loss`: optional 1-element fp32 CUDA tensor that receives the loss before the update."""
+    st = _call.rot_step(cfg, L, R, state, lr, beta, eps, q, s, grad_scale, loss)
+    if st >= 0:
+        return _check(st, "lq_rot_step")
     _check_factors(cfg, L, R)
     opt = lq_cayley(lr, beta, eps, q, s, grad_scale)
     _check(_lib.lq_rot_step(C.byref(cfg), _ptr(L), _ptr(R), _ptr(state), state.numel(), C.byref(opt), _ptr(loss),

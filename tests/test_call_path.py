@@ -1,0 +1,115 @@
+"""The native half of the binding (`_call`): it makes the ordinary call and leaves everything else to the ctypes path, with the same results
+and the same errors."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2604_18117_amd import binding as lq
+
+FAST = ("quantize_act", "linear_lowrank_fwd", "linear_lowrank_fwd_handoff", "branch_from_codes", "pack_weights", "calib_step", "rot_step")
+
+
+def test_arguments_that_are_not_ordinary_are_left_alone():
+    cfg = lq.make_config(128, 128, 16)
+    cpu = torch.zeros(4, 128)
+    assert lq._call.quantize_act(cfg, cpu, cpu, cpu) == -1                    # CPU tensors
+    assert lq._call.quantize_act(cfg, None, cpu, None) == -1
+    assert lq._call.quantize_act(C.c_int(3), cpu, cpu, cpu) == -1             # not a configuration
+    assert lq._call.quantize_act(cfg, cpu, cpu) == -1                         # arguments missing
+    assert lq._call.linear_lowrank_fwd(cfg, cpu, cpu, 4.0, cpu) == -1
+    assert lq._call.pack_weights(cfg, "W", cpu, cpu, cpu) == -1
+    assert lq._call.rot_step(cfg, cpu, cpu, cpu, 0.5, 0.9, 1e-8, 0.5, 2, 1.0, None) == -1
+    assert lq._call.calib_step(cfg, cpu, cpu, 1, 1e-4, 0.9, 0.999, 1e-8, None) == -1
+    assert not C.pythonapi.PyErr_Occurred()
+    with pytest.raises(AssertionError):                                       # ... whose checks raise what they always did
+        lq.lq_quantize_act(cfg, cpu, cpu, act=cpu)
+
+
+def _work(monkeypatch, native):
+    """One pass of every entry point on seeded inputs; native: whether `_call` has to make the calls (or none of them)."""
+    made = []
+    for name in FAST:
+        real = getattr(lq._call, name)
+        monkeypatch.setattr(lq._call, name, (lambda *a, real=real, name=name: made.append((name, real(*a))) or made[-1][1]) if native else (lambda *a: -1))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+    out = []
+    N, K, r, M = 320, 192, 32, 37
+    c1 = lq.make_config(N, K, r, "mxi", 32, 4)
+    c2 = lq.make_config(192, N, r, "mxi", 32, 4)
+    blob = [torch.zeros(lq.lq_packed_sizes(c), dtype=torch.uint8, device="cuda") for c in (c1, c2)]
+    assert lq.lq_pack_weights(c1, normal(N, K), normal(N, r), normal(r, K), packed=blob[0]) is blob[0]
+    lq.lq_pack_weights(c2, normal(192, N), normal(192, r), normal(r, N), packed=blob[1])
+    X = torch.zeros(M, K + 64, dtype=torch.bfloat16, device="cuda")[:, :K]    # rows further apart than K
+    X.copy_(normal(M, K))
+    act, act2 = [torch.zeros(lq.lq_act_sizes(c, M), dtype=torch.uint8, device="cuda") for c in (c1, c2)]
+    codes = torch.zeros(lq.lq_handoff_sizes(c2, M), dtype=torch.uint8, device="cuda")
+    Y, Y1 = torch.zeros(M, 192, dtype=torch.bfloat16, device="cuda"), torch.zeros(M, N + 8, dtype=torch.bfloat16, device="cuda")[:, :N]
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):                                                # the calls go to the current stream
+        assert lq.lq_quantize_act(c1, blob[0], X, act=act) is act
+        lq.lq_linear_lowrank_fwd_handoff(c1, blob[0], act, M, c2, act_next=act2, codes=codes)
+        lq.lq_linear_lowrank_fwd_handoff(c1, blob[0], act, M, c2, act_next=act2, codes=codes, Y=Y1)
+        lq.lq_branch_from_codes(c2, blob[1], codes, M, act2)
+        assert lq.lq_linear_lowrank_fwd(c2, blob[1], act2, M, Y=Y) is Y
+    torch.cuda.current_stream().wait_stream(s)
+    out += [*blob, act, act2, codes, Y, Y1]
+    ci = lq.make_config(N, K, r, "int", 64, 8)
+    W, L, R = normal(N, K) * 0.02, normal(N, r) * 0.01, normal(r, K) * 0.01
+    loss = torch.zeros(1, device="cuda")
+    state = lq.lq_calib_init(ci, L, R)
+    lq.lq_calib_step(ci, W, state, 1, lr=1e-3, loss=loss)
+    lq.lq_calib_step(ci, W, state, 2)
+    out += [loss.clone(), *lq.lq_calib_unpack(ci, state, ("L", "R", "mL", "vR", "E")).values()]
+    rot = lq.lq_rot_init(ci)
+    lq.lq_rot_step(ci, L, R, rot, grad_scale=1e3, loss=loss)
+    out += [loss, *lq.lq_rot_unpack(ci, rot, ("Omega", "Mom", "E1")).values()]
+    torch.cuda.synchronize()
+    if native:
+        assert {n for n, st in made if st == 0} == set(FAST)
+    # errors: the same kind from both routes
+    for call, err in (((lambda: lq.lq_quantize_act(c1, blob[0], X.float(), act=act)), AssertionError),
+                      ((lambda: lq.lq_quantize_act(c1, blob[0], X[:, :-64], act=act)), AssertionError),
+                      ((lambda: lq.lq_quantize_act(c1, blob[0], X, act=act[:256])), lq.LqError),
+                      ((lambda: lq.lq_quantize_act(c1, blob[0][:256], X, act=act)), AssertionError),
+                      ((lambda: lq.lq_linear_lowrank_fwd(c2, blob[1], act2, M, Y=Y.float())), AssertionError),
+                      ((lambda: lq.lq_linear_lowrank_fwd(c2, blob[1], act2[:256], M, Y=Y)), lq.LqError),
+                      ((lambda: lq.lq_linear_lowrank_fwd(c2, blob[1], act2, M + 1, Y=Y)), AssertionError),
+                      ((lambda: lq.lq_pack_weights(c1, W.T, L, R, packed=blob[0])), AssertionError),
+                      ((lambda: lq.lq_rot_step(ci, L[:64], R, rot)), AssertionError),
+                      ((lambda: lq.lq_calib_step(ci, W, state[:256], 3)), lq.LqError)):
+        with pytest.raises(err):
+            call()
+    return out
+
+
+@pytest.mark.gpu
+def test_native_and_ctypes_route_do_the_same(monkeypatch):
+    for a, b in zip(_work(monkeypatch, True), _work(monkeypatch, False)):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+def test_wrapped_tensors_take_the_ctypes_route():
+    cfg = lq.make_config(128, 128, 16, "int", 64, 8)
+    W, L, R = torch.randn(128, 128, device="cuda"), torch.randn(128, 16, device="cuda"), torch.randn(16, 128, device="cuda")
+    packed = lq.lq_pack_weights(cfg, W, L, R)
+    X = torch.randn(8, 128, device="cuda").bfloat16()
+    act = torch.empty(lq.lq_act_sizes(cfg, 8), dtype=torch.uint8, device="cuda")
+
+    class Sub(torch.Tensor):
+        pass
+    assert lq._call.quantize_act(cfg, packed, X, act) == 0
+    assert lq._call.quantize_act(cfg, packed, torch.nn.Parameter(X), act) == 0
+    assert lq._call.quantize_act(cfg, packed, X.as_subclass(Sub), act) == -1
+    with torch.device("cuda"):                                                # a torch-function mode
+        assert lq._call.quantize_act(cfg, packed, X, act) == -1
+        lq.lq_quantize_act(cfg, packed, X, act=act)
+    seen = []
+    torch.vmap(lambda x: (seen.append(lq._call.quantize_act(cfg, packed, x, act)), x)[1])(torch.stack([X, X]))
+    assert seen == [-1]
