@@ -221,6 +221,25 @@ hipError_t launch_rot_unpack(const Dims& d, const uint8_t* state, const lq_rot_v
 
 int compute_units();  // of the current device
 
+// Form of the activation steps with a block-scaled floating-point branch (mxb_act_kernel, mx6_act_kernel; every form sums T in the same
+// order): 4 or 8 wavefronts per 16 rows, or 8 with a workgroup per 16 rows and 32 columns of the rank (2).  While every 16 rows have a compute
+// unit of their own the time is one workgroup's chain of 128-chunks, and, where compute units are left over, that of reading all of R through
+// one of them; beyond that 8 wavefronts deal the chunks less evenly (9 chunks of K = 1152: a second turn in which seven wait) and hold more
+// registers; so do they with few chunks.  us, forms 2 / 8 / 4, MXFP8: 64 x 4608 rank 128 9.1 / 13.2 / 15.4, 1024 x 1152 rank 128 5.1 / 6.7 / 6.9,
+// 2048 x 1152 rank 64 5.9 / 6.6 / 6.5, 3000 x 1152 rank 64 8.1 / 7.1 / 6.9, 4096 x 2240 rank 64 11.3 / 10.2 / 10.4, 4096 x 4608 rank 128 29.1 /
+// 19.3 / 20.7, 6001 x 2240 rank 64 16.5 / 16.3 / 15.7, 16384 x 1152 rank 128 41.9 / 27.1 / 21.5, 2 x 1152 rank 32 - / 4.1 / 4.3, 3000 x 512
+// rank 32 - / 5.3 / 4.5; MXFP6: 2048 x 512 rank 64 4.8 / 5.0 / 4.3, 1024 x 512 rank 128 4.7 / 5.5 / 4.8.  Rows held as fp32 spill at rank 128 with
+// 4 wavefronts (6001 x 1152, smoothed: 19.3 with 8, 21.2).
+static inline int mxb_act_form(int64_t Mp, int C128, int njb, bool fp32_rows)
+{
+    const int64_t groups = Mp / 16, cus = compute_units();
+    if (groups > cus) return njb >= 8 && fp32_rows ? 8 : 4;
+    const bool fits = groups * (njb / 2) <= cus;
+    if (C128 <= 5) return njb > 4 && fits ? 2 : 4;
+    if (njb > 2 && fits) return 2;
+    return C128 >= 12 || 4 * groups <= cus ? 8 : 4;
+}
+
 // Tile order of the forward kernels: panels of `panel` tile columns (256 channels each), row-major inside a panel; the
 // last panel may be narrower.  The workgroups resident on an XCD at one time then share few weight column blocks: with
 // all tile columns in flight at once, the weight codes of a wide layer (7.5 MB at 2240 x 6720) do not stay in the XCD's
@@ -256,7 +275,7 @@ hipError_t allow_lds(int bytes)
 // cycles) stood before everything else this workgroup does, which at 16 rows is the whole grid.
 __device__ __forceinline__ void write_tag(uint32_t* dst, const BlobTag& t)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         ((uint4*)dst)[0] = make_uint4(t.w[0], t.w[1], t.w[2], t.w[3]);
         ((uint4*)dst)[1] = make_uint4(t.w[4], t.w[5], t.w[6], t.w[7]);
     }

@@ -736,6 +736,12 @@ hipError_t launch_quantize_act_mx(const Dims& d, int x_dtype, const uint8_t* pac
 // k = 16q.. of each 64-half of the chunk, which is both the fragment position of the 4-bit main codes
 // and, as E4M3, bytes 0..15 / 16..31 of the lane's 8-bit MFMA operand.  A 32-block is shared by the
 // lane pair (q, q^1); the MFMA takes the scale of block q from lane (row, q), so lanes 1 and 2 swap.
+//
+// No scale spans more than a block, so the row is streamed, two chunks of X in flight per wavefront; the chunk's R is requested before its X
+// is coded and used after.  What bounds it: at one workgroup per compute unit the chain of a wavefront's chunks and the way of R (r K bytes)
+// through one compute unit, at more R's traffic from the L2 beside X's from memory (mxb_act_form has the forms and their times).  us a call,
+// four wavefronts with R a chunk ahead, values unpacked to fp32 and addresses in vector registers / this: 2 x 1152 rank 32 5.4 / 4.1, 300 x 1152
+// rank 64 6.6 / 5.0, 64 x 4608 rank 128 17.2 / 9.1, 6001 x 2240 rank 64 17.8 / 15.7, 16384 x 1152 rank 64 20.1 / 16.3, rank 128 32.7 / 21.5.
 // ---------------------------------------------------------------------------------------------
 struct MxbActParams {
     const void* X;
@@ -755,173 +761,249 @@ struct MxbActParams {
     uint32_t* tag_dst;
 };
 
-// BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32).
-template <bool BF16IN, int NJB, bool SM = false>
-__global__ __launch_bounds__(256) void mxb_act_kernel(MxbActParams p)
+// 16 values of a block and the block's scale -> 16 E4M3 bytes, nearest even, saturating at +-448 * 2^(E - 127): the scaled converters, from
+// bf16 pairs with both magnitudes limited first (they return NaN past the range), without unpacking a value.
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void mxfp8_codes16(const MxChunk<true>& ch, uint32_t E, uint32_t* out)
+{
+    const uint32_t l1 = ((E + 8u) << 7) | 0x60u, lim = l1 | (l1 << 16);
+    const float sc = e8m0_value(E);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        typedef short v2s __attribute__((ext_vector_type(2)));
+        v2s r = {0, 0};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t w = ch.w[2 * g + h];
+            const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, w & 0x7FFF7FFFu), __builtin_bit_cast(us2, lim)));
+            const v2bf v = __builtin_bit_cast(v2bf, (w & 0x80008000u) | m);
+            r = h ? __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(r, v, sc, true) : __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(r, v, sc, false);
+        }
+        out[g] = __builtin_bit_cast(uint32_t, r);
+    }
+}
+__device__ __forceinline__ void mxfp8_codes16(const MxChunk<false>& ch, uint32_t E, uint32_t* out)
+{
+    const float inv = e8m0_inverse(E);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        out[g] = fp8_quad(__fmul_rn(ch.get(4 * g), inv), __fmul_rn(ch.get(4 * g + 1), inv), __fmul_rn(ch.get(4 * g + 2), inv), __fmul_rn(ch.get(4 * g + 3), inv));
+}
+__device__ __forceinline__ void mxfp4_codes16(const MxChunk<true>& ch, float sc, uint32_t (&pk)[2])
+{
+#define LQ_CVT4(J) pk[(J) >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(pk[(J) >> 2], __builtin_bit_cast(v2bf, ch.w[J]), sc, (J) & 3)
+    LQ_CVT4(0); LQ_CVT4(1); LQ_CVT4(2); LQ_CVT4(3); LQ_CVT4(4); LQ_CVT4(5); LQ_CVT4(6); LQ_CVT4(7);
+#undef LQ_CVT4
+}
+__device__ __forceinline__ void mxfp4_codes16(const MxChunk<false>& ch, float sc, uint32_t (&pk)[2])
+{
+#define LQ_CVT4(J) pk[(J) >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk[(J) >> 2], ch.get(2 * (J)), ch.get(2 * (J) + 1), sc, (J) & 3)
+    LQ_CVT4(0); LQ_CVT4(1); LQ_CVT4(2); LQ_CVT4(3); LQ_CVT4(4); LQ_CVT4(5); LQ_CVT4(6); LQ_CVT4(7);
+#undef LQ_CVT4
+}
+__device__ __forceinline__ float mx_amax16(const MxChunk<true>& ch)  // |bf16| is monotonic in its low 15 bits: packed unsigned maximum, two values per instruction
+{
+    us2 m2 = {0, 0};
+#pragma unroll
+    for (int d = 0; d < 8; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, ch.w[d] & 0x7FFF7FFFu));
+    const uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
+    return __uint_as_float(mm << 16);
+}
+__device__ __forceinline__ float mx_amax16(const MxChunk<false>& ch)
+{
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(ch.get(i)));
+    return m;
+}
+
+// BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32); DBG: parity taps.
+template <bool BF16IN, int NJB, bool SM, int NW, bool DBG>
+__global__ __launch_bounds__(64 * NW, 2) void mxb_act_kernel(MxbActParams p)
 {
     write_tag(p.tag_dst, p.tag);
     constexpr bool BF16 = BF16IN && !SM;  // representation of a chunk in registers
     constexpr int NJA = NJB > 0 ? NJB : 1;
-    constexpr int PF = 2;  // 128-chunks in flight per wavefront: no scale spans more than a block, the row is streamed
-    __shared__ float s_acc[4][NJA][64][4];
+    constexpr int NS = 8, SW = NS / NW;  // T is eight sums, over the chunks c = 0 .. 7 mod 8, added in order; SW of them to a wavefront
+    __shared__ float s_acc[NS][NJA][64][4];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, q = lane >> 4;
     const int row = blockIdx.x * 16 + r16;
     const bool row_ok = row < p.M;
+    const uint32_t rowmask = row_ok ? ~0u : 0u;
     const int C64 = p.C64, C128 = p.C128;
+    const int njb = p.r >> 4, jb0 = (int)blockIdx.y * NJB;  // this workgroup's 16-column groups of the rank; the first one stores the main codes
+    const bool first = blockIdx.y == 0;
 
-    const int nmy = (C128 - wave + 3) >> 2;  // chunks of this wavefront: c = wave + 4 * ci, ci < nmy
-    MxChunk<BF16> xh[PF][2];
-    auto load_x = [&](MxChunk<BF16>& ch, size_t koff, bool ok) {
-        if constexpr (SM)
-            smooth_load<BF16IN, 16>(ch.v, p.X, (size_t)row * p.ldx + koff, p.rg + koff, ok);
-        else
-            ch.load(p.X, (size_t)row * p.ldx + koff, ok);
+    const int nmy = (C128 - wave + NW - 1) / NW;  // chunks of this wavefront: c = wave + NW * ci, ci < nmy
+    struct XSet { MxChunk<BF16> h[2]; };
+    XSet xs[2];
+    const size_t xrow = (size_t)(row_ok ? row : p.M - 1) * p.ldx + q * 16;
+    // (no branch around the loads, which would end the compiler's count of those in flight: past the end they are clamped, and not used)
+    auto load_x = [&](XSet& x, int ci) {
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            int c64 = 2 * (wave + NW * ci) + hh;
+            c64 = c64 < p.C64s ? c64 : p.C64s - 1;
+            if constexpr (SM)
+                smooth_load<BF16IN, 16>(x.h[hh].v, p.X, xrow + (size_t)c64 * 64, p.rg + (size_t)c64 * 64 + q * 16, true);
+            else
+                x.h[hh].load(p.X, xrow + (size_t)c64 * 64, true);
+        }
     };
+    v4f acc[SW][NJA];
 #pragma unroll
-    for (int i = 0; i < PF; ++i)
+    for (int i = 0; i < SW; ++i)
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-            load_x(xh[i][hh], (size_t)(wave + 4 * i) * 128 + hh * 64 + q * 16, row_ok && 2 * (wave + 4 * i) + hh < p.C64s);
-    // R fragments and their scale dwords: first chunk now, later ones one chunk ahead
-    v8i bvs[2][NJA];
-    int bss[2][NJA];
-    auto load_r8 = [&](int slot, int ci) {
-        int c = wave + 4 * ci;
-        c = c < C128 ? c : C128 - 1;  // clamped: a fragment past the end is fetched but not used
+        for (int jb = 0; jb < NJB; ++jb) acc[i][jb] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    // R, the codes and their scales go through descriptors (of R's sections and of this workgroup's block of 32 rows): a lane offset each and the
+    // chunk in a scalar register, instead of 64-bit addresses in vector registers, of which three wavefronts per SIMD have none to spare.
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    const int rblk = (int)(blockIdx.x >> 1);
+    const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc((void*)p.r8, 0, (int)((unsigned)C128 * njb * 2048u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_e = __builtin_amdgcn_make_buffer_rsrc((void*)p.re, 0, C128 * njb * 256, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_c = __builtin_amdgcn_make_buffer_rsrc(p.xc + (size_t)rblk * C64 * 1024, 0, C64 * 1024, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_s = __builtin_amdgcn_make_buffer_rsrc(p.xe + (size_t)rblk * p.CQ * 256, 0, p.CQ * 256, 0x00020000);
+    const int off_c = ((row & 31) + 32 * (q >> 1)) * 16 + (q & 1) * 8, off_s = ((row & 31) + 32 * (q >> 1)) * 4;
+    auto store_scales = [&](int c, uint32_t two) {  // of 64-chunks 2 c and 2 c + 1: neighbours in a dword
+        if ((q & 1) == 0) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)two, rs_s, off_s, (c >> 1) * 256 + (c & 1) * 2, 0);
+    };
+
+    // One chunk: request its R, code its X, request X of the chunk after the next (refill), multiply.
+    auto step = [&](auto slot, int ci, auto refill) {
+        constexpr int par = decltype(slot)::value, set = par % SW;  // (the chunks of a slot are those of one sum)
+        XSet& x = xs[par];
+        const int c = wave + NW * ci;
+        v8i bv[NJA];
+        int bs[NJA];
 #pragma unroll
         for (int jb = 0; jb < NJB; ++jb) {
-            bvs[slot][jb] = *(const v8i*)(p.r8 + ((size_t)((size_t)c * NJB + jb) * 64 + lane) * 32);
-            bss[slot][jb] = *(const int*)(p.re + ((size_t)((size_t)c * NJB + jb) * 64 + lane) * 4);
+            const u4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs_r, lane * 32, (c * njb + jb0 + jb) * 2048, 0);
+            const u4 hi = __builtin_amdgcn_raw_buffer_load_b128(rs_r, lane * 32 + 16, (c * njb + jb0 + jb) * 2048, 0);
+            bv[jb] = v8i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+            bs[jb] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_e, lane * 4, (c * njb + jb0 + jb) * 256, 0);
         }
-    };
-    load_r8(0, 0);
-
-    v4f acc[NJA];
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t x8[8], E4[2], Eh[2];
 #pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) acc[jb] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    for (int base = 0; base < nmy; base += PF) {
-#pragma unroll
-    for (int sl = 0; sl < PF; ++sl) {
-        const int ci = base + sl;
-        const int c = wave + 4 * ci;
-        load_r8((sl + 1) & 1, ci + 1);
-        if (ci < nmy) {  // wave-uniform
-            uint32_t x8[8];
-            uint32_t Eh[2];
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const MxChunk<BF16>& xc = xh[sl][hh];
-                float m = 0.f;
-                if constexpr (BF16) {
-                    us2 m2 = {0, 0};
-#pragma unroll
-                    for (int d = 0; d < 8; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, xc.w[d] & 0x7FFF7FFFu));
-                    const uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
-                    m = __uint_as_float(mm << 16);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(xc.get(i)));
-                }
-                const float ab = max_xor16(m);  // amax of the 32-block (lanes q, q^1)
-                // main codes: MXFP4
-                const uint32_t E4 = e8m0_of(ab);
-                const float sc = e8m0_value(E4);
+        for (int hh = 0; hh < 2; ++hh) {
+            const MxChunk<BF16>& xc = x.h[hh];
+            const int c64 = 2 * c + hh;
+            const uint32_t keep = c64 < p.C64s ? rowmask : 0u;  // (rows past M and the layout's padding chunk: amax and codes 0)
+            const float ab = __uint_as_float(__float_as_uint(max_xor16(mx_amax16(xc))) & keep);  // amax of the 32-block (lanes q, q^1)
+            E4[hh] = e8m0_of(ab);                        // main codes: MXFP4
+            if (first) {
                 uint32_t pk[2] = {0u, 0u};
-#define LQ_CVT4(J) pk[(J) >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk[(J) >> 2], xc.get(2 * (J)), xc.get(2 * (J) + 1), sc, (J) & 3)
-                if (ab != 0.0f) {
-                    LQ_CVT4(0); LQ_CVT4(1); LQ_CVT4(2); LQ_CVT4(3); LQ_CVT4(4); LQ_CVT4(5); LQ_CVT4(6); LQ_CVT4(7);
-                }
-#undef LQ_CVT4
-                const int c64 = 2 * c + hh;
-                uint8_t* dst = p.xc + ((size_t)((size_t)(row >> 5) * C64 + c64) * 64 + (row & 31) + 32 * (q >> 1)) * 16 + (q & 1) * 8;
-                *(uint2*)dst = make_uint2(pk[0], pk[1]);
-                if ((q & 1) == 0) p.xe[mx_scale_offset(row, c64, q >> 1, p.CQ)] = (uint8_t)E4;
-                // branch codes: MXFP8e4 of the same block
-                const uint32_t E8 = e8m0_of_fp8(ab);
-                const float inv8 = e8m0_inverse(E8);
-                Eh[hh] = E8;
+                mxfp4_codes16(xc, e8m0_value(E4[hh]), pk);
+                const uint32_t nz = ab != 0.0f ? ~0u : 0u;  // (a block of zeros has codes 0, also where the zeros are negative)
+                __builtin_amdgcn_raw_buffer_store_b64(u2{pk[0] & nz, pk[1] & nz}, rs_c, off_c, c64 * 1024, 0);
+            }
+            if constexpr (NJB > 0 || DBG) {              // branch codes: MXFP8e4 of the same block
+                Eh[hh] = e8m0_of_fp8(ab);
+                mxfp8_codes16(xc, Eh[hh], x8 + 4 * hh);
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    x8[4 * hh + g] = fp8_quad(__fmul_rn(xc.get(4 * g), inv8), __fmul_rn(xc.get(4 * g + 1), inv8),
-                                              __fmul_rn(xc.get(4 * g + 2), inv8), __fmul_rn(xc.get(4 * g + 3), inv8));
-                if (p.dbg_xb && row_ok && c64 < p.C64s)
+                for (int g = 0; g < 4; ++g) x8[4 * hh + g] &= keep;
+                if (DBG && p.dbg_xb && row_ok && c64 < p.C64s)
                     *(v4i*)(p.dbg_xb + (size_t)row * p.K + (size_t)c * 128 + hh * 64 + q * 16) =
                         v4i{(int)x8[4 * hh], (int)x8[4 * hh + 1], (int)x8[4 * hh + 2], (int)x8[4 * hh + 3]};
-                if (p.dbg_xbe && row_ok && c64 < p.C64s && (q & 1) == 0) p.dbg_xbe[(size_t)row * (p.K >> 5) + 4 * c + 2 * hh + (q >> 1)] = (uint8_t)E8;
-            }
-            if (NJB > 0) {
-                // lane q knows blocks (q>>1) [first half] and 2+(q>>1) [second half]; it must supply block q
-                const uint32_t send = (q == 1) ? Eh[1] : Eh[0];
-                const auto h32 = __builtin_amdgcn_permlane32_swap(send, send, false, false);  // the value of lane ^ 48, without the LDS
-                const uint32_t o32 = q < 2 ? h32[1] : h32[0];
-                const auto h16 = __builtin_amdgcn_permlane16_swap(o32, o32, false, false);
-                const uint32_t recv = (q & 1) ? h16[0] : h16[1];
-                const int sa = (int)((q == 0) ? Eh[0] : (q == 3) ? Eh[1] : recv);
-                const v8i a8 = {(int)x8[0], (int)x8[1], (int)x8[2], (int)x8[3], (int)x8[4], (int)x8[5], (int)x8[6], (int)x8[7]};
-#pragma unroll
-                for (int jb = 0; jb < NJB; ++jb)
-                    acc[jb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, bvs[sl & 1][jb], acc[jb], 0, 0, 0, sa, 0,
-                                                                            bss[sl & 1][jb]);
+                if (DBG && p.dbg_xbe && row_ok && c64 < p.C64s && (q & 1) == 0) p.dbg_xbe[(size_t)row * (p.K >> 5) + 4 * c + 2 * hh + (q >> 1)] = (uint8_t)Eh[hh];
             }
         }
-        // refill the slot with the chunk PF positions further on
+        if (first) store_scales(c, E4[0] | E4[1] << 8);
+        // (the codes are formed before the slot is filled again: moved down to their use they would keep both rows of X in registers)
+        if constexpr (NJB > 0) asm volatile("" : "+v"(x8[0]), "+v"(x8[1]), "+v"(x8[2]), "+v"(x8[3]), "+v"(x8[4]), "+v"(x8[5]), "+v"(x8[6]), "+v"(x8[7]));
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(refill)::value) {
+            load_x(x, ci + 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (NJB > 0) {
+            // lane q knows blocks (q>>1) [first half] and 2+(q>>1) [second half]; it must supply block q
+            const uint32_t send = (q == 1) ? Eh[1] : Eh[0];
+            const auto h32 = __builtin_amdgcn_permlane32_swap(send, send, false, false);  // the value of lane ^ 48, without the LDS
+            const uint32_t o32 = q < 2 ? h32[1] : h32[0];
+            const auto h16 = __builtin_amdgcn_permlane16_swap(o32, o32, false, false);
+            const uint32_t recv = (q & 1) ? h16[0] : h16[1];
+            const int sa = (int)((q == 0) ? Eh[0] : (q == 3) ? Eh[1] : recv);
+            const v8i a8 = {(int)x8[0], (int)x8[1], (int)x8[2], (int)x8[3], (int)x8[4], (int)x8[5], (int)x8[6], (int)x8[7]};
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-            load_x(xh[sl][hh], (size_t)(c + 4 * PF) * 128 + hh * 64 + q * 16, row_ok && 2 * (c + 4 * PF) + hh < p.C64s);
-    }
-    }
-    {   // padding 64-chunks of the last quad (at most one 128-chunk per wavefront): valid E8M0 bytes (2^0)
-        const int c = wave + 4 * nmy;
+            for (int jb = 0; jb < NJB; ++jb)
+                acc[set][jb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, bv[jb], acc[set][jb], 0, 0, 0, sa, 0, bs[jb]);
+            // (the products stay ahead of the next chunk's request of R: moved behind it they would hold both chunks' R in registers)
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-            if (2 * c + hh < 4 * p.CQ && (q & 1) == 0) p.xe[mx_scale_offset(row, 2 * c + hh, q >> 1, p.CQ)] = (uint8_t)127;
+            for (int jb = 0; jb < NJB; ++jb) asm volatile("" : "+v"(acc[set][jb]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    load_x(xs[0], 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_x(xs[1], 1);
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr std::integral_constant<int, 0> s0{};
+    constexpr std::integral_constant<int, 1> s1{};
+    int ci = 0;
+    for (; ci + 3 < nmy; ci += 2) {
+        step(s0, ci, std::true_type{});
+        step(s1, ci + 1, std::true_type{});
+    }
+    if (ci + 2 < nmy) {
+        step(s0, ci, std::true_type{});
+        step(s1, ci + 1, std::false_type{});
+        step(s0, ci + 2, std::false_type{});
+    } else {
+        if (ci < nmy) step(s0, ci, std::false_type{});
+        if (ci + 1 < nmy) step(s1, ci + 1, std::false_type{});
+    }
+    {   // padding 64-chunks of the last quad (at most one 128-chunk): valid E8M0 bytes (2^0)
+        const int c = wave + NW * nmy;
+        if (first && 2 * c < 4 * p.CQ) store_scales(c, 0x7F7Fu);
     }
     if (NJB == 0) return;
 
 #pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) *(v4f*)&s_acc[wave][jb][lane][0] = acc[jb];
-    __syncthreads();
-    // Sum over the wavefronts, re-quantise per token and per block of 32 along the rank: a block (two 16-column groups) to a
-    // wavefront.  The lane holds columns (2 bb + g) * 16 + lane%16 of the intermediate for token rows 4*q + i.
+    for (int i = 0; i < SW; ++i)
 #pragma unroll
-    for (int bb0 = 0; bb0 < (NJB + 1) / 2; bb0 += 4) {
-        const int bb = bb0 + wave;
-        if (bb >= (NJB + 1) / 2) break;  // wave-uniform
-        float T[2][4];
+        for (int jb = 0; jb < NJB; ++jb) *(v4f*)&s_acc[wave + NW * i][jb][lane][0] = acc[i][jb];
+    __syncthreads();
+    // The eight sums, re-quantised per token and per block of 32 along the rank: a task is a block (two 16-column groups) and two of a lane's
+    // four token rows.  The lane holds columns (2 bb + g) * 16 + lane%16 of the intermediate for token rows 4*q + i.
+    for (int task = wave; task < 2 * ((NJB + 1) / 2); task += NW) {
+        const int bb = task >> 1, half = task & 1;
+        float T[2][2];
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
             const int jb = 2 * bb + g;
-            v4f sum = *(const v4f*)&s_acc[0][jb][lane][0];
+            typedef float v2f __attribute__((ext_vector_type(2)));
+            v2f o[NS];
 #pragma unroll
-            for (int w = 1; w < 4; ++w) {
-                const v4f o = *(const v4f*)&s_acc[w][jb][lane][0];
+            for (int w = 0; w < NS; ++w) o[w] = *(const v2f*)&s_acc[w][jb][lane][2 * half];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) sum[i] = __fadd_rn(sum[i], o[i]);
-            }
+            for (int i = 0; i < 2; ++i) {
+                float sum = o[0][i];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                T[g][i] = sum[i];
-                const int grow = blockIdx.x * 16 + 4 * q + i;
-                if (grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = sum[i];
+                for (int w = 1; w < NS; ++w) sum = __fadd_rn(sum, o[w][i]);
+                T[g][i] = sum;
+                const int grow = blockIdx.x * 16 + 4 * q + 2 * half + i;
+                if (DBG && grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + (jb0 + jb) * 16 + r16] = sum;
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 2; ++i) {
             float tm = fmaxf(fabsf(T[0][i]), fabsf(T[1][i]));
             tm = max_row16(tm);
-            const int grow = blockIdx.x * 16 + 4 * q + i;
+            const int grow = blockIdx.x * 16 + 4 * q + 2 * half + i;
             const uint32_t E = e8m0_of_fp8(tm);
             const float inv = e8m0_inverse(E);
-            if (r16 == 0) p.te[mxb_scale_offset(grow, bb)] = (uint8_t)E;
+            if (r16 == 0) p.te[mxb_scale_offset(grow, (jb0 >> 1) + bb)] = (uint8_t)E;
 #pragma unroll
             for (int g = 0; g < 2; ++g)
-                p.tq8[mxb_frag8_offset(grow, (2 * bb + g) * 16 + r16, p.rp)] = (uint8_t)fp8_byte(__fmul_rn(T[g][i], inv));
+                p.tq8[mxb_frag8_offset(grow, (jb0 + 2 * bb + g) * 16 + r16, p.rp)] = (uint8_t)fp8_byte(__fmul_rn(T[g][i], inv));
         }
     }
-    if (wave != 3) return;
+    if (wave != NW - 1 || !first) return;
     // padding of the rank to a multiple of 64: zero codes, scale 2^0
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -932,11 +1014,21 @@ __global__ __launch_bounds__(256) void mxb_act_kernel(MxbActParams p)
     }
 }
 
+template <bool BF16, int NJB, bool SM, bool DBG>
+static hipError_t mxb_act_launch2(const MxbActParams& p, int64_t Mp, hipStream_t s)
+{
+    const dim3 rows((unsigned)(Mp / 16));
+    switch (mxb_act_form(Mp, p.C128, NJB, !BF16 || SM)) {
+        case 4: hipLaunchKernelGGL((mxb_act_kernel<BF16, NJB, SM, 4, DBG>), rows, dim3(256), 0, s, p); break;
+        case 8: hipLaunchKernelGGL((mxb_act_kernel<BF16, NJB, SM, 8, DBG>), rows, dim3(512), 0, s, p); break;
+        default: hipLaunchKernelGGL((mxb_act_kernel<BF16, NJB < 2 ? NJB : 2, SM, 8, DBG>), dim3(rows.x, NJB < 2 ? 1 : NJB / 2), dim3(512), 0, s, p); break;
+    }
+    return hipGetLastError();
+}
 template <bool BF16, int NJB, bool SM>
 static hipError_t mxb_act_launch(const MxbActParams& p, int64_t Mp, hipStream_t s)
 {
-    hipLaunchKernelGGL((mxb_act_kernel<BF16, NJB, SM>), dim3((unsigned)(Mp / 16)), dim3(256), 0, s, p);
-    return hipGetLastError();
+    return p.dbg_xb || p.dbg_xbe || p.dbg_T ? mxb_act_launch2<BF16, NJB, SM, true>(p, Mp, s) : mxb_act_launch2<BF16, NJB, SM, false>(p, Mp, s);
 }
 template <bool BF16, bool SM>
 static hipError_t mxb_act_rank2(const MxbActParams& p, int64_t Mp, hipStream_t s)

@@ -256,15 +256,47 @@ struct Mx6Block<false> {  // 32 fp32 values
     __device__ __forceinline__ float get(int i) const { return v[i]; }
 };
 
-// BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32).
-template <bool BF16IN, int NJB, bool SM = false>
-__global__ __launch_bounds__(256) void mx6_act_kernel(Mx6ActParams p)
+// The 32 values of a block and their scale -> FP4 codes (16 bytes) and FP6 codes (24 bytes).
+__device__ __forceinline__ void mx6_codes(const Mx6Block<true>& x, float sc, uint32_t (&pk)[4], v6u& c6, bool main_codes, bool branch)
+{
+    if (main_codes) {
+#define LQ_CVT4B(J) pk[(J) >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(pk[(J) >> 2], __builtin_bit_cast(v2bf, x.w[J]), sc, (J) & 3)
+        LQ_CVT4B(0); LQ_CVT4B(1); LQ_CVT4B(2); LQ_CVT4B(3); LQ_CVT4B(4); LQ_CVT4B(5); LQ_CVT4B(6); LQ_CVT4B(7);
+        LQ_CVT4B(8); LQ_CVT4B(9); LQ_CVT4B(10); LQ_CVT4B(11); LQ_CVT4B(12); LQ_CVT4B(13); LQ_CVT4B(14); LQ_CVT4B(15);
+#undef LQ_CVT4B
+    }
+    if (branch) {
+        v32bf h;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const v2bf two = __builtin_bit_cast(v2bf, x.w[j]);
+            h[2 * j] = two[0];
+            h[2 * j + 1] = two[1];
+        }
+        c6 = fp6_block_from_bf16(h, sc);
+    }
+}
+__device__ __forceinline__ void mx6_codes(const Mx6Block<false>& x, float sc, uint32_t (&pk)[4], v6u& c6, bool main_codes, bool branch)
+{
+    if (main_codes) {
+#define LQ_CVT4F(J) pk[(J) >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk[(J) >> 2], x.get(2 * (J)), x.get(2 * (J) + 1), sc, (J) & 3)
+        LQ_CVT4F(0); LQ_CVT4F(1); LQ_CVT4F(2); LQ_CVT4F(3); LQ_CVT4F(4); LQ_CVT4F(5); LQ_CVT4F(6); LQ_CVT4F(7);
+        LQ_CVT4F(8); LQ_CVT4F(9); LQ_CVT4F(10); LQ_CVT4F(11); LQ_CVT4F(12); LQ_CVT4F(13); LQ_CVT4F(14); LQ_CVT4F(15);
+#undef LQ_CVT4F
+    }
+    if (branch) c6 = fp6_block_from_f32(x.v, sc);
+}
+
+// BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32); DBG: parity taps.  The forms, the order of
+// T's sums and the way of the operands are those of mxb_act_kernel.
+template <bool BF16IN, int NJB, bool SM, int NW, bool DBG>
+__global__ __launch_bounds__(64 * NW, 2) void mx6_act_kernel(Mx6ActParams p)
 {
     write_tag(p.tag_dst, p.tag);
     constexpr bool BF16 = BF16IN && !SM;  // representation of a block in registers
     constexpr int NJA = NJB > 0 ? NJB : 1;
-    constexpr int PF = 2;  // 128-chunks in flight per wavefront
-    __shared__ float s_acc[4][NJA][64][4];
+    constexpr int NS = 8, SW = NS / NW;  // T is eight sums, over the chunks c = 0 .. 7 mod 8, added in order; SW of them to a wavefront
+    __shared__ float s_acc[NS][NJA][64][4];
     __shared__ float s_T[16][NJA * 16 + 1];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -272,170 +304,193 @@ __global__ __launch_bounds__(256) void mx6_act_kernel(Mx6ActParams p)
     const int row = blockIdx.x * 16 + r16;
     const bool row_ok = row < p.M;
     const int C128 = p.C128;
-    const int nmy = (C128 - wave + 3) >> 2;  // chunks of this wavefront: c = wave + 4 * ci, ci < nmy
+    const int njb = p.r >> 4, jb0 = (int)blockIdx.y * NJB;  // this workgroup's 16-column groups of the rank; the first one stores the main codes
+    const bool first = blockIdx.y == 0;
+    const int nmy = (C128 - wave + NW - 1) / NW;  // chunks of this wavefront: c = wave + NW * ci, ci < nmy
 
-    Mx6Block<BF16> xb[PF];
-    auto load_x = [&](Mx6Block<BF16>& blk, size_t koff, bool ok) {
+    Mx6Block<BF16> xs[2];
+    const size_t xrow = (size_t)(row_ok ? row : p.M - 1) * p.ldx;
+    auto load_x = [&](Mx6Block<BF16>& x, int ci) {  // (no branch around the loads: past the end they are clamped, and not used)
+        int b = 4 * (wave + NW * ci) + q;
+        b = b < 2 * p.C64s ? b : 2 * p.C64s - 1;
         if constexpr (SM)
-            smooth_load<BF16IN, 32>(blk.v, p.X, (size_t)row * p.ldx + koff, p.rg + koff, ok);
+            smooth_load<BF16IN, 32>(x.v, p.X, xrow + (size_t)b * 32, p.rg + (size_t)b * 32, true);
         else
-            blk.load(p.X, (size_t)row * p.ldx + koff, ok);
+            x.load(p.X, xrow + (size_t)b * 32, true);
     };
+    v4f acc[SW][NJA];
 #pragma unroll
-    for (int i = 0; i < PF; ++i) load_x(xb[i], (size_t)(wave + 4 * i) * 128 + q * 32, row_ok && 4 * (wave + 4 * i) + q < 2 * p.C64s);
-    v8i bvs[2][NJA];
-    int bss[2][NJA];
-    auto load_r = [&](int slot, int ci) {
-        int c = wave + 4 * ci;
-        c = c < C128 ? c : C128 - 1;  // clamped: a fragment past the end is fetched but not used
+    for (int i = 0; i < SW; ++i)
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb) acc[i][jb] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    const int rblk = (int)(blockIdx.x >> 1);
+    const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc((void*)p.rs, 0, (int)((unsigned)C128 * njb * 2048u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_e = __builtin_amdgcn_make_buffer_rsrc((void*)p.re, 0, C128 * njb * 256, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_c = __builtin_amdgcn_make_buffer_rsrc(p.xc + (size_t)rblk * p.C64 * 1024, 0, p.C64 * 1024, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_s = __builtin_amdgcn_make_buffer_rsrc(p.xe + (size_t)rblk * p.CQ * 256, 0, p.CQ * 256, 0x00020000);
+    // the lane's block is K block q & 1 of 64-chunk 2 c + (q >> 1)
+    const int off_c = ((row & 31) + 32 * (q & 1)) * 16 + (q >> 1) * 1024, off_s = ((row & 31) + 32 * (q & 1)) * 4 + (q >> 1);
+
+    // One chunk: request its R, code its X, request X of the chunk after the next (refill), multiply.
+    auto step = [&](auto slot, int ci, auto refill) {
+        constexpr int par = decltype(slot)::value, set = par % SW;  // (the chunks of a slot are those of one sum)
+        Mx6Block<BF16>& x = xs[par];
+        const int c = wave + NW * ci;
+        v8i bv[NJA];
+        int bs[NJA];
 #pragma unroll
         for (int jb = 0; jb < NJB; ++jb) {
-            bvs[slot][jb] = *(const v8i*)(p.rs + ((size_t)((size_t)c * NJB + jb) * 64 + lane) * 32);
-            bss[slot][jb] = *(const int*)(p.re + ((size_t)((size_t)c * NJB + jb) * 64 + lane) * 4);
+            const u4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs_r, lane * 32, (c * njb + jb0 + jb) * 2048, 0);
+            const u2 hi = __builtin_amdgcn_raw_buffer_load_b64(rs_r, lane * 32 + 16, (c * njb + jb0 + jb) * 2048, 0);
+            bv[jb] = v8i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], 0, 0};
+            bs[jb] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_e, lane * 4, (c * njb + jb0 + jb) * 256, 0);
         }
-    };
-    load_r(0, 0);
-
-    v4f acc[NJA];
+        __builtin_amdgcn_sched_barrier(0);
+        float m = 0.f;
+        if constexpr (BF16) {
+            us2 m2 = {0, 0};
 #pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) acc[jb] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    for (int base = 0; base < nmy; base += PF) {
+            for (int d = 0; d < 16; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, x.w[d] & 0x7FFF7FFFu));
+            const uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
+            m = __uint_as_float(mm << 16);
+        } else {
 #pragma unroll
-        for (int sl = 0; sl < PF; ++sl) {
-            const int ci = base + sl;
-            const int c = wave + 4 * ci;
-            load_r((sl + 1) & 1, ci + 1);
-            if (ci < nmy) {  // wave-uniform
-                const Mx6Block<BF16>& x = xb[sl];
-                float m = 0.f;
-                if constexpr (BF16) {
-                    us2 m2 = {0, 0};
+            for (int i = 0; i < 32; ++i) m = fmaxf(m, fabsf(x.get(i)));
+        }
+        if (!row_ok || 4 * c + q >= 2 * p.C64s) m = 0.f;  // (rows past M and the layout's padding chunk)
+        const uint32_t E = m6_e8m0_of(m), nz = m != 0.0f ? ~0u : 0u;  // (a block of zeros has codes 0, also where the zeros are negative)
+        uint32_t pk[4] = {0u, 0u, 0u, 0u};
+        v6u c6 = {0u, 0u, 0u, 0u, 0u, 0u};
+        mx6_codes(x, m6_e8m0_value(E), pk, c6, first, NJB > 0 || DBG);
+        if (first) {
+            __builtin_amdgcn_raw_buffer_store_b128(u4{pk[0] & nz, pk[1] & nz, pk[2] & nz, pk[3] & nz}, rs_c, off_c, c * 2048, 0);
+            __builtin_amdgcn_raw_buffer_store_b8((unsigned char)E, rs_s, off_s, (c >> 1) * 256 + (c & 1) * 2, 0);
+        }
 #pragma unroll
-                    for (int d = 0; d < 16; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, x.w[d] & 0x7FFF7FFFu));
-                    const uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
-                    m = __uint_as_float(mm << 16);
-                } else {
+        for (int i = 0; i < 6; ++i) c6[i] &= nz;
+        if constexpr (DBG) {  // (codes taken out at constant positions: an array indexed at run time ends up in the LDS or in scratch)
+            if (p.dbg_xb && row_ok && 4 * c + q < 2 * p.C64s) {
+                int8_t* o = p.dbg_xb + (size_t)row * p.K + (size_t)c * 128 + q * 32;
 #pragma unroll
-                    for (int i = 0; i < 32; ++i) m = fmaxf(m, fabsf(x.get(i)));
-                }
-                const uint32_t E = m6_e8m0_of(m);
-                const float sc = m6_e8m0_value(E);
-                uint32_t pk[4] = {0u, 0u, 0u, 0u};
-                v6u c6 = {0u, 0u, 0u, 0u, 0u, 0u};
-                if (m != 0.0f) {
-                    if constexpr (BF16) {
-#define LQ_CVT4B(J) pk[(J) >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(pk[(J) >> 2], __builtin_bit_cast(v2bf, x.w[J]), sc, (J) & 3)
-                        LQ_CVT4B(0); LQ_CVT4B(1); LQ_CVT4B(2); LQ_CVT4B(3); LQ_CVT4B(4); LQ_CVT4B(5); LQ_CVT4B(6); LQ_CVT4B(7);
-                        LQ_CVT4B(8); LQ_CVT4B(9); LQ_CVT4B(10); LQ_CVT4B(11); LQ_CVT4B(12); LQ_CVT4B(13); LQ_CVT4B(14); LQ_CVT4B(15);
-#undef LQ_CVT4B
-                        v32bf h;
-#pragma unroll
-                        for (int j = 0; j < 16; ++j) {
-                            const v2bf two = __builtin_bit_cast(v2bf, x.w[j]);
-                            h[2 * j] = two[0];
-                            h[2 * j + 1] = two[1];
-                        }
-                        c6 = fp6_block_from_bf16(h, sc);
-                    } else {
-#define LQ_CVT4F(J) pk[(J) >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk[(J) >> 2], x.get(2 * (J)), x.get(2 * (J) + 1), sc, (J) & 3)
-                        LQ_CVT4F(0); LQ_CVT4F(1); LQ_CVT4F(2); LQ_CVT4F(3); LQ_CVT4F(4); LQ_CVT4F(5); LQ_CVT4F(6); LQ_CVT4F(7);
-                        LQ_CVT4F(8); LQ_CVT4F(9); LQ_CVT4F(10); LQ_CVT4F(11); LQ_CVT4F(12); LQ_CVT4F(13); LQ_CVT4F(14); LQ_CVT4F(15);
-#undef LQ_CVT4F
-                        c6 = fp6_block_from_f32(x.v, sc);
-                    }
-                }
-                // the lane's block is K block q&1 of 64-chunk 2c + (q>>1)
-                const int c64 = 2 * c + (q >> 1);
-                uint8_t* dst = p.xc + ((size_t)((size_t)(row >> 5) * p.C64 + c64) * 64 + (row & 31) + 32 * (q & 1)) * 16;
-                *(v4i*)dst = v4i{(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
-                p.xe[m6_scale_offset(row, c64, q & 1, p.CQ)] = (uint8_t)E;
-                if (NJB > 0) {
-                    // (codes taken out at constant positions: an array indexed at run time is put into the LDS, whose address the compiler
-                    // forms from the workgroup size in the dispatch packet -- in host memory, read by every workgroup: rank 32, 4096 x 1152
-                    // 19.4 us a call, 300 x 1152 7.0; ranks 64 and 96 had it in scratch)
-                    if (p.dbg_xb && row_ok && c64 < p.C64s) {
-                        int8_t* o = p.dbg_xb + (size_t)row * p.K + (size_t)c * 128 + q * 32;
-#pragma unroll
-                        for (int i = 0; i < 32; ++i) {
-                            const int w = 6 * i / 32, sh = 6 * i % 32;
-                            const uint32_t hi = sh > 26 ? c6[w + 1] << (32 - sh) : 0u;
-                            o[i] = (int8_t)(((c6[w] >> sh) | hi) & 63u);
-                        }
-                    }
-                    if (p.dbg_xbe && row_ok && c64 < p.C64s) p.dbg_xbe[(size_t)row * (p.K >> 5) + 4 * c + q] = (uint8_t)E;
-                    const v8i a8 = {(int)c6[0], (int)c6[1], (int)c6[2], (int)c6[3], (int)c6[4], (int)c6[5], 0, 0};
-#pragma unroll
-                    for (int jb = 0; jb < NJB; ++jb)
-                        acc[jb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, bvs[sl & 1][jb], acc[jb], 2, 2, 0, (int)E, 0,
-                                                                                bss[sl & 1][jb]);
+                for (int i = 0; i < 32; ++i) {
+                    const int w = 6 * i / 32, sh = 6 * i % 32;
+                    const uint32_t hi = sh > 26 ? c6[w + 1] << (32 - sh) : 0u;
+                    o[i] = (int8_t)(((c6[w] >> sh) | hi) & 63u);
                 }
             }
-            load_x(xb[sl], (size_t)(c + 4 * PF) * 128 + q * 32, row_ok && 4 * (c + 4 * PF) + q < 2 * p.C64s);
+            if (p.dbg_xbe && row_ok && 4 * c + q < 2 * p.C64s) p.dbg_xbe[(size_t)row * (p.K >> 5) + 4 * c + q] = (uint8_t)E;
         }
+        // (the codes are formed before the slot is filled again: moved down to their use they would keep both rows of X in registers)
+        if constexpr (NJB > 0) asm volatile("" : "+v"(c6));
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(refill)::value) {
+            load_x(x, ci + 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (NJB > 0) {
+            const v8i a8 = {(int)c6[0], (int)c6[1], (int)c6[2], (int)c6[3], (int)c6[4], (int)c6[5], 0, 0};
+#pragma unroll
+            for (int jb = 0; jb < NJB; ++jb)
+                acc[set][jb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, bv[jb], acc[set][jb], 2, 2, 0, (int)E, 0, bs[jb]);
+            // (the products stay ahead of the next chunk's request of R: moved behind it they would hold both chunks' R in registers)
+#pragma unroll
+            for (int jb = 0; jb < NJB; ++jb) asm volatile("" : "+v"(acc[set][jb]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    load_x(xs[0], 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_x(xs[1], 1);
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr std::integral_constant<int, 0> s0{};
+    constexpr std::integral_constant<int, 1> s1{};
+    int ci = 0;
+    for (; ci + 3 < nmy; ci += 2) {
+        step(s0, ci, std::true_type{});
+        step(s1, ci + 1, std::true_type{});
     }
-    {   // padding 64-chunks of the last quad (at most one 128-chunk per wavefront): valid E8M0 bytes (2^0)
-        const int c = wave + 4 * nmy;
-        if (2 * c < 4 * p.CQ) p.xe[m6_scale_offset(row, 2 * c + (q >> 1), q & 1, p.CQ)] = (uint8_t)127;
+    if (ci + 2 < nmy) {
+        step(s0, ci, std::true_type{});
+        step(s1, ci + 1, std::false_type{});
+        step(s0, ci + 2, std::false_type{});
+    } else {
+        if (ci < nmy) step(s0, ci, std::false_type{});
+        if (ci + 1 < nmy) step(s1, ci + 1, std::false_type{});
+    }
+    {   // padding 64-chunks of the last quad (at most one 128-chunk): valid E8M0 bytes (2^0)
+        const int c = wave + NW * nmy;
+        if (first && 2 * c < 4 * p.CQ) __builtin_amdgcn_raw_buffer_store_b8((unsigned char)127, rs_s, off_s, (c >> 1) * 256 + (c & 1) * 2, 0);
     }
     if (NJB == 0) return;
 
 #pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) *(v4f*)&s_acc[wave][jb][lane][0] = acc[jb];
+    for (int i = 0; i < SW; ++i)
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb) *(v4f*)&s_acc[wave + NW * i][jb][lane][0] = acc[i][jb];
     __syncthreads();
-    // sum over the wavefronts, a 16-column group to a wavefront: lane holds column j = jb*16 + lane%16 of the intermediate
-    // for token rows 4*q + i
+    // the eight sums, a 16-column group and two of a lane's four token rows to a wavefront at a time: lane holds column j = jb*16 + lane%16 of
+    // the intermediate for token rows 4*q + i
+    for (int task = wave; task < 2 * NJB; task += NW) {
+        const int jb = task >> 1, half = task & 1;
+        typedef float v2f __attribute__((ext_vector_type(2)));
+        v2f o[NS];
 #pragma unroll
-    for (int jb0 = 0; jb0 < NJB; jb0 += 4) {
-        const int jb = jb0 + wave;
-        if (jb >= NJB) break;  // wave-uniform
-        v4f sum = *(const v4f*)&s_acc[0][jb][lane][0];
+        for (int w = 0; w < NS; ++w) o[w] = *(const v2f*)&s_acc[w][jb][lane][2 * half];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
-            const v4f o = *(const v4f*)&s_acc[w][jb][lane][0];
+        for (int i = 0; i < 2; ++i) {
+            float sum = o[0][i];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) sum[i] = __fadd_rn(sum[i], o[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            s_T[4 * q + i][jb * 16 + r16] = sum[i];
-            const int grow = blockIdx.x * 16 + 4 * q + i;
-            if (grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = sum[i];
+            for (int w = 1; w < NS; ++w) sum = __fadd_rn(sum, o[w][i]);
+            s_T[4 * q + 2 * half + i][jb * 16 + r16] = sum;
+            const int grow = blockIdx.x * 16 + 4 * q + 2 * half + i;
+            if (DBG && grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + (jb0 + jb) * 16 + r16] = sum;
         }
     }
     __syncthreads();
-    // re-quantise: one thread per (token row, block of 32 along the rank); blocks that pad the rank to a
-    // multiple of 64 get zero codes and scale 2^0
-    const int BRP = p.rp >> 5, BR = p.r >> 5;
-    if (tid < 16 * BRP) {
-        const int trow = tid / BRP, blk = tid % BRP;
+    // re-quantise: one thread per (token row, block of 32 along the rank); the first workgroup adds the blocks that pad the rank to a
+    // multiple of 64: zero codes and scale 2^0
+    const int own = NJB / 2, pad = first ? (p.rp >> 5) - (p.r >> 5) : 0;
+    if (tid < 16 * (own + pad)) {
+        const int trow = tid & 15, b = tid >> 4;
+        const int blk = b < own ? (jb0 >> 1) + b : (p.r >> 5) + b - own;
         const int grow = blockIdx.x * 16 + trow;
         float v[32];
         float a = 0.f;
         v6u c6 = {0u, 0u, 0u, 0u, 0u, 0u};
         uint32_t E = 127u;
-        if (blk < BR) {
+        if (b < own) {
             for (int i = 0; i < 32; ++i) {
-                v[i] = s_T[trow][32 * blk + i];
+                v[i] = s_T[trow][32 * b + i];
                 a = fmaxf(a, fabsf(v[i]));
             }
             E = m6_e8m0_of(a);
             if (a != 0.0f) c6 = fp6_block_from_f32(v, m6_e8m0_value(E));
         }
-        uint32_t* dst = (uint32_t*)(p.ts + mx6_lt_slot(grow, blk, p.rp));
-#pragma unroll
-        for (int i = 0; i < 6; ++i) dst[i] = c6[i];
-        dst[6] = 0u;
-        dst[7] = 0u;
+        uint4* dst = (uint4*)(p.ts + mx6_lt_slot(grow, blk, p.rp));
+        dst[0] = make_uint4(c6[0], c6[1], c6[2], c6[3]);
+        dst[1] = make_uint4(c6[4], c6[5], 0u, 0u);
         p.te[m6_lt_scale_offset(grow, blk)] = (uint8_t)E;
     }
 }
 
+template <bool BF16, int NJB, bool SM, bool DBG>
+static hipError_t mx6_act_launch2(const Mx6ActParams& p, int64_t Mp, hipStream_t s)
+{
+    const dim3 rows((unsigned)(Mp / 16));
+    switch (mxb_act_form(Mp, p.C128, NJB, !BF16 || SM)) {
+        case 4: hipLaunchKernelGGL((mx6_act_kernel<BF16, NJB, SM, 4, DBG>), rows, dim3(256), 0, s, p); break;
+        case 8: hipLaunchKernelGGL((mx6_act_kernel<BF16, NJB, SM, 8, DBG>), rows, dim3(512), 0, s, p); break;
+        default: hipLaunchKernelGGL((mx6_act_kernel<BF16, NJB < 2 ? NJB : 2, SM, 8, DBG>), dim3(rows.x, NJB < 2 ? 1 : NJB / 2), dim3(512), 0, s, p); break;
+    }
+    return hipGetLastError();
+}
 template <bool BF16, int NJB, bool SM>
 static hipError_t mx6_act_launch(const Mx6ActParams& p, int64_t Mp, hipStream_t s)
 {
-    hipLaunchKernelGGL((mx6_act_kernel<BF16, NJB, SM>), dim3((unsigned)(Mp / 16)), dim3(256), 0, s, p);
-    return hipGetLastError();
+    return p.dbg_xb || p.dbg_xbe || p.dbg_T ? mx6_act_launch2<BF16, NJB, SM, true>(p, Mp, s) : mx6_act_launch2<BF16, NJB, SM, false>(p, Mp, s);
 }
 template <bool BF16, bool SM>
 static hipError_t mx6_act_rank2(const Mx6ActParams& p, int64_t Mp, hipStream_t s)

@@ -209,3 +209,42 @@ def test_full_size_sampled_rows(oracle, name):
     rng = np.random.default_rng(1)
     rows = np.sort(np.concatenate([[0, layer.M - 1], rng.choice(layer.M, 14, replace=False)]))
     _compare(oracle, layer, X, W, L, R, rows=rows)
+
+
+# Every form of the activation step (4 or 8 wavefronts, one workgroup per 32 columns of the rank) and every length of a wavefront's run of
+# 128-chunks around its unrolled pairs: 3 chunks (a padding one among them) to 41, rows that end inside a group of 16.  Form 4 past a
+# group per compute unit is compared on its first rows.
+@pytest.mark.parametrize("elem", [8, 6])
+@pytest.mark.parametrize("K,r,xd", [(320, 64, "bf16"), (704, 128, "bf16"), (1088, 32, "bf16"), (2112, 96, "bf16"), (3200, 64, "bf16"), (5184, 32, "bf16"),
+                                    (1600, 128, "f32"), (640, 32, "f32"), (384, 0, "bf16")])
+def test_forms_of_the_activation_step(oracle, K, r, xd, elem):
+    from paper_2604_18117_amd import binding as lq
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    layer = wl.Layer("t", 37, K, 64, r, "mxb", 32, elem, elem, xd, seed=K + r)
+    X, W, L, R = wl.make_inputs(layer)
+    X[2, :] = -0.0                # blocks of zeros have codes 0, also where the zeros are negative
+    X[3, 32:64] = -0.0
+    X[3, 70] = -0.0               # (in other blocks a zero keeps its sign)
+    _compare(oracle, layer, X, W, L, R)
+    cfg = lq.config_for_layer(layer)
+    packed = lq.lq_pack_weights(cfg, *(torch.from_numpy(a).cuda() if r or a is W else None for a in (W, L, R)))
+
+    def blob(x, debug):
+        act = torch.full((lq.lq_act_sizes(cfg, x.shape[0]),), 0xFF, dtype=torch.uint8, device="cuda")
+        return lq.lq_quantize_act(cfg, packed, x, act=act, debug=debug)[0] if debug else lq.lq_quantize_act(cfg, packed, x, act=act)
+
+    def views(x, act):
+        v = lq.lq_unpack_act(cfg, act, x.shape[0])
+        return (v.xq, v.xe, v.tq, v.te) if r else (v.xq, v.xe)
+    Xd = wl.to_dev_x(X, xd)
+    want = blob(Xd, False)
+    assert torch.equal(want, blob(Xd, True))                           # with and without the parity taps
+    assert not bool(views(Xd, want)[0][2].any()) and not bool(views(Xd, want)[0][3, 32:64].any())
+    wide = torch.full((37, K + 64), float("nan"), dtype=Xd.dtype, device="cuda")
+    wide[:, :K] = Xd
+    assert torch.equal(blob(wide[:, :K], False), want)                 # rows further apart than K
+    for groups in (cus // 4 + 1, cus // 2 + 1, cus, cus + 1):
+        M = 16 * groups - 3
+        big = Xd.repeat((M + 36) // 37, 1)[:M].contiguous()
+        for a, b in zip(views(big, blob(big, False)), views(Xd, want)):
+            assert torch.equal(a[:37], b) and torch.equal(a[-(M % 37):] if M % 37 else a[-37:], b[:M % 37] if M % 37 else b), M
