@@ -400,7 +400,10 @@ hipError_t launch_unpack_act_mx(const Dims& d, const uint8_t* act, int64_t M, co
 
 // ---------------------------------------------------------------------------------------------
 // activation kernel: same decomposition as the INT one (16 token rows per workgroup, lane =
-// (row l%16, 16-value quarter l/16 of each 64-chunk), chunks dealt round-robin to 4 wavefronts)
+// (row l%16, 16-value quarter l/16 of each 64-chunk), chunks dealt round-robin to 4 or 8 wavefronts).
+// Bound: X's bytes, then, all workgroups in step, coding and the way to the re-quantised intermediate.  us a call, four wavefronts, one of them
+// re-quantising, and a clamp per value / this: 300 x 1152 rank 32 6.8 / 5.8, rank 128 7.9 / 6.5, 8192 x 4608 rank 128 42.3 / 36.4, smoothed 1000 x 4608
+// rank 64 28.4 / 14.6, 6001 x 2240 rank 64 21.6 / 16.5.
 // ---------------------------------------------------------------------------------------------
 struct MxActParams {
     const void* X;
@@ -459,308 +462,6 @@ struct MxChunk<false> {
     __device__ __forceinline__ float get(int i) const { return v[i]; }
 };
 
-// BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32).
-template <bool BF16IN, int MAXC, int NJB, bool SM = false>
-__global__ __launch_bounds__(256) void mx_act_kernel(MxActParams p)
-{
-    write_tag(p.tag_dst, p.tag);
-    constexpr bool BF16 = BF16IN && !SM;  // representation of the row in registers
-    __shared__ float s_amax[4][16];
-    __shared__ float s_sxb[16];
-    __shared__ float s_acc[4][NJB > 0 ? NJB : 1][64][4];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r16 = lane & 15, kq = lane >> 4;
-    const int row = blockIdx.x * 16 + r16;
-    const bool row_ok = row < p.M;
-    const int C64 = p.C64;
-
-    // MAXC = 0: rows too long for the registers are streamed twice through a two-chunk ring (amax pass, coding pass;
-    // the second read comes from the caches)
-    constexpr bool STREAM = MAXC == 0;
-    constexpr int NS = STREAM ? 2 : MAXC;   // chunk slots in registers
-    const int nmy = (C64 - wave + 3) >> 2;  // chunks of this wavefront: c = wave + 4 * ci, ci < nmy
-    MxChunk<BF16> xc[NS];
-    auto load_x = [&](MxChunk<BF16>& ch, int ci) {
-        const int c = wave + 4 * ci;
-        const size_t koff = (size_t)c * 64 + kq * 16;
-        const bool ok = row_ok && c < p.C64s;  // (a chunk of the layout past the row is coded from zeros)
-        if constexpr (SM)
-            smooth_load<BF16IN, 16>(ch.v, p.X, (size_t)row * p.ldx + koff, p.rg + koff, ok);
-        else
-            ch.load(p.X, (size_t)row * p.ldx + koff, ok);
-    };
-#pragma unroll
-    for (int ci = 0; ci < NS; ++ci) load_x(xc[ci], ci);
-
-    // Operands that do not depend on X are requested now (their latency overlaps the load of X):
-    // the Q2(R) fragments of the first chunk (later ones one chunk ahead, in the loop), R's scales.
-    constexpr int NJA = NJB > 0 ? NJB : 1;
-    v4i bvs[2][NJA];
-    auto load_r8 = [&](v4i (&dst)[NJA], int ci) {
-        int c = wave + 4 * ci;
-        c = c < C64 ? c : C64 - 1;  // clamped: a fragment past the end is fetched but not used
-#pragma unroll
-        for (int jb = 0; jb < NJB; ++jb) dst[jb] = *(const v4i*)(p.r8 + ((size_t)((size_t)c * NJB + jb) * 64 + lane) * 16);
-    };
-    load_r8(bvs[0], 0);
-    float srj[NJA];
-#pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) srj[jb] = p.sr[jb * 16 + r16];
-
-    // amax of the lane's 16 values per chunk (kept for the block scale when the row is resident) and of the whole row
-    auto amax16 = [&](const MxChunk<BF16>& ch) -> float {
-        if constexpr (BF16) {
-            // |bf16| is monotonic in its low 15 bits: packed unsigned 16-bit max, two values per op
-            us2 m2 = {0, 0};
-#pragma unroll
-            for (int d = 0; d < 8; ++d) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(us2, ch.w[d] & 0x7FFF7FFFu));
-            const uint32_t mm = m2[0] > m2[1] ? m2[0] : m2[1];
-            return __uint_as_float(mm << 16);
-        } else {
-            float m = 0.f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(ch.get(i)));
-            return m;
-        }
-    };
-    float a16[NS];
-    float a = 0.f;
-    if constexpr (STREAM) {
-        for (int ci0 = 0; ci0 < nmy; ci0 += 2) {
-#pragma unroll
-            for (int sl = 0; sl < 2; ++sl) {
-                a = fmaxf(a, amax16(xc[sl]));  // (a slot past the end holds zeros)
-                load_x(xc[sl], ci0 + sl + 2);
-            }
-        }
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) load_x(xc[sl], sl);  // second pass: the ring starts over
-    } else {
-#pragma unroll
-        for (int ci = 0; ci < NS; ++ci) {
-            a16[ci] = amax16(xc[ci]);
-            a = fmaxf(a, a16[ci]);
-        }
-    }
-    a = max_xor16(a);
-    a = max_xor32(a);
-    if (kq == 0) s_amax[wave][r16] = a;
-    __syncthreads();
-    a = fmaxf(fmaxf(s_amax[0][r16], s_amax[1][r16]), fmaxf(s_amax[2][r16], s_amax[3][r16]));
-    float sb, invb;
-    fp8_scales(a, &sb, &invb);
-    if (wave == 0 && kq == 0) {
-        s_sxb[r16] = sb;
-        if (p.dbg_sxb && row_ok) p.dbg_sxb[row] = sb;
-        if (NJB == 0) p.st[row] = 1.0f;
-    }
-
-    v4f acc[NJB > 0 ? NJB : 1];
-#pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) acc[jb] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    // one 64-chunk: MXFP4 codes and block scales, FP8 branch codes, skinny contraction (am: amax of the lane's 16 values)
-    auto code_chunk = [&](const MxChunk<BF16>& ch, const int c, const float am, const int bslot) {
-        // MXFP4: block of 32 = this lane's 16 values and its neighbour's (kq ^ 1)
-        const float ab = max_xor16(am);
-        const uint32_t E = e8m0_of(ab);
-        const float sc = e8m0_value(E);
-        uint32_t pk[2] = {0u, 0u};
-        uint32_t x8[4];
-#define LQ_CVT4(J) pk[(J) >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk[(J) >> 2], ch.get(2 * (J)), ch.get(2 * (J) + 1), sc, (J) & 3)
-        if (ab != 0.0f) {
-            LQ_CVT4(0); LQ_CVT4(1); LQ_CVT4(2); LQ_CVT4(3); LQ_CVT4(4); LQ_CVT4(5); LQ_CVT4(6); LQ_CVT4(7);
-        }
-#undef LQ_CVT4
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            x8[q] = fp8_quad(__fmul_rn(ch.get(4 * q), invb), __fmul_rn(ch.get(4 * q + 1), invb),
-                             __fmul_rn(ch.get(4 * q + 2), invb), __fmul_rn(ch.get(4 * q + 3), invb));
-        uint8_t* dst = p.xc + ((size_t)((size_t)(row >> 5) * C64 + c) * 64 + (row & 31) + 32 * (kq >> 1)) * 16 + (kq & 1) * 8;
-        *(uint2*)dst = make_uint2(pk[0], pk[1]);
-        if ((kq & 1) == 0) p.xe[mx_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)E;
-        if (p.dbg_xb && row_ok && c < p.C64s)
-            *(v4i*)(p.dbg_xb + (size_t)row * p.K + c * 64 + kq * 16) = v4i{(int)x8[0], (int)x8[1], (int)x8[2], (int)x8[3]};
-        if (NJB > 0) {
-            const long alo = (long)(((unsigned long)x8[1] << 32) | x8[0]);
-            const long ahi = (long)(((unsigned long)x8[3] << 32) | x8[2]);
-#pragma unroll
-            for (int jb = 0; jb < NJB; ++jb) {
-                const v4i bv = bvs[bslot][jb];
-                const long blo = (long)(((unsigned long)(uint32_t)bv[1] << 32) | (uint32_t)bv[0]);
-                const long bhi = (long)(((unsigned long)(uint32_t)bv[3] << 32) | (uint32_t)bv[2]);
-                acc[jb] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(alo, blo, acc[jb], 0, 0, 0);
-                acc[jb] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ahi, bhi, acc[jb], 0, 0, 0);
-            }
-        }
-    };
-    auto pad_chunk = [&](const int c) {  // padding chunk of the last quad: its scale bytes must be valid E8M0 values (2^0)
-        if (c >= C64 && c < 4 * p.CQ && (kq & 1) == 0) p.xe[mx_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)127;
-    };
-    if constexpr (STREAM) {
-        for (int ci0 = 0; ci0 < nmy; ci0 += 2) {
-#pragma unroll
-            for (int sl = 0; sl < 2; ++sl) {
-                const int ci = ci0 + sl, c = wave + 4 * ci;
-                load_r8(bvs[(sl + 1) & 1], ci + 1);
-                if (c < C64) code_chunk(xc[sl], c, amax16(xc[sl]), sl);  // wave-uniform
-                load_x(xc[sl], ci + 2);
-            }
-        }
-        pad_chunk(wave + 4 * nmy);
-    } else {
-#pragma unroll
-        for (int ci = 0; ci < NS; ++ci) {
-            const int c = wave + 4 * ci;
-            if (ci + 1 < NS) load_r8(bvs[(ci + 1) & 1], ci + 1);
-            if (c < C64) code_chunk(xc[ci], c, a16[ci], ci & 1);  // wave-uniform
-            else pad_chunk(c);
-        }
-    }
-    if (NJB == 0) return;
-
-#pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) *(v4f*)&s_acc[wave][jb][lane][0] = acc[jb];
-    __syncthreads();
-    if (wave != 0) return;
-
-    float T[NJB > 0 ? NJB : 1][4];
-    float tmax[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int jb = 0; jb < NJB; ++jb) {
-        v4f s = *(const v4f*)&s_acc[0][jb][lane][0];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) {
-            const v4f o = *(const v4f*)&s_acc[w][jb][lane][0];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] = __fadd_rn(s[i], o[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int tok = 4 * kq + i;
-            const float tv = __fmul_rn(__fmul_rn(s[i], s_sxb[tok]), srj[jb]);
-            T[jb][i] = tv;
-            tmax[i] = fmaxf(tmax[i], fabsf(tv));
-            const int grow = blockIdx.x * 16 + tok;
-            if (grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = tv;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        tmax[i] = max_row16(tmax[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int grow = blockIdx.x * 16 + 4 * kq + i;
-        float stv, invt;
-        fp8_scales(tmax[i], &stv, &invt);
-        if (r16 == 0) p.st[grow] = stv;
-#pragma unroll
-        for (int jb = 0; jb < NJB; ++jb) p.tq8[(size_t)grow * p.rp + jb * 16 + r16] = (uint8_t)fp8_byte(__fmul_rn(T[jb][i], invt));
-        for (int j = p.r + r16; j < p.rp; j += 16) p.tq8[(size_t)grow * p.rp + j] = 0;
-    }
-}
-
-template <bool BF16, int MAXC, int NJB, bool SM>
-static hipError_t mx_act_launch(const MxActParams& p, int64_t Mp, hipStream_t s)
-{
-    hipLaunchKernelGGL((mx_act_kernel<BF16, MAXC, NJB, SM>), dim3((unsigned)(Mp / 16)), dim3(256), 0, s, p);
-    return hipGetLastError();
-}
-template <bool BF16, int MAXC, bool SM = false>
-static hipError_t mx_act_rank(const MxActParams& p, int64_t Mp, hipStream_t s)
-{
-    switch (p.r) {
-        case 0: return mx_act_launch<BF16, MAXC, 0, SM>(p, Mp, s);
-        case 16: return mx_act_launch<BF16, MAXC, 1, SM>(p, Mp, s);
-        case 32: return mx_act_launch<BF16, MAXC, 2, SM>(p, Mp, s);
-        case 64: return mx_act_launch<BF16, MAXC, 4, SM>(p, Mp, s);
-        default: return mx_act_launch<BF16, MAXC, 8, SM>(p, Mp, s);
-    }
-}
-
-static hipError_t launch_quantize_act_mxb(const Dims& d, int x_dtype, const uint8_t* packed, const void* X, int64_t M,
-                                          int64_t ldx, uint8_t* act, const lq_act_debug* dbg, hipStream_t s);
-
-hipError_t launch_quantize_act_mx(const Dims& d, int x_dtype, const uint8_t* packed, const void* X, int64_t M,
-                                  int64_t ldx, uint8_t* act, const lq_act_debug* dbg, hipStream_t s)
-{
-    if (d.mxb_elem == 6) return launch_quantize_act_mx6(d, x_dtype, packed, X, M, ldx, act, dbg, s);
-    if (d.mxb) return launch_quantize_act_mxb(d, x_dtype, packed, X, M, ldx, act, dbg, s);
-    const PackedLayout pl = packed_layout(d);
-    const ActLayout al = act_layout(d, M);
-    MxActParams p;
-    p.tag = make_tag(d, LQ_BLOB_ACT, M);
-    p.tag_dst = (uint32_t*)act;
-    p.X = X;
-    p.ldx = ldx;
-    p.M = (int)M;
-    p.K = (int)d.Ks;
-    p.C64 = d.C64;
-    p.C64s = (int)(d.Ks / 64);
-    p.CQ = (d.C64 + 3) / 4;
-    p.r = d.r;
-    p.rp = d.rp;
-    p.r8 = packed + pl.off_rq;
-    p.sr = (const float*)(packed + pl.off_sr);
-    p.xc = act + al.off_xq;
-    p.xe = act + al.off_sx;
-    p.tq8 = act + al.off_tq;
-    p.st = (float*)(act + al.off_st);
-    p.dbg_xb = dbg ? dbg->xb : nullptr;
-    p.dbg_sxb = dbg ? dbg->sxb : nullptr;
-    p.dbg_T = dbg ? dbg->T : nullptr;
-    const int maxc = (d.C64 + 3) / 4;
-    p.rg = d.smooth ? (const float*)(packed + pl.off_rg) : nullptr;
-    // MAXC = 0: the streamed form, for rows that do not fit in registers (fp32 representation: K > 2304; bf16: K > 4608)
-    if (d.smooth) {
-        if (x_dtype == LQ_BF16)
-            return maxc <= 5 ? mx_act_rank<true, 5, true>(p, al.Mp, s) : maxc <= 9 ? mx_act_rank<true, 9, true>(p, al.Mp, s) : mx_act_rank<true, 0, true>(p, al.Mp, s);
-        return maxc <= 5 ? mx_act_rank<false, 5, true>(p, al.Mp, s) : maxc <= 9 ? mx_act_rank<false, 9, true>(p, al.Mp, s) : mx_act_rank<false, 0, true>(p, al.Mp, s);
-    }
-    if (x_dtype == LQ_BF16) {
-        if (maxc <= 5) return mx_act_rank<true, 5>(p, al.Mp, s);
-        if (maxc <= 9) return mx_act_rank<true, 9>(p, al.Mp, s);
-        if (maxc <= 18) return mx_act_rank<true, 18>(p, al.Mp, s);
-        return mx_act_rank<true, 0>(p, al.Mp, s);
-    }
-    if (maxc <= 5) return mx_act_rank<false, 5>(p, al.Mp, s);
-    if (maxc <= 9) return mx_act_rank<false, 9>(p, al.Mp, s);
-    return mx_act_rank<false, 0>(p, al.Mp, s);
-}
-
-// ---------------------------------------------------------------------------------------------
-// activation kernel with an MXFP8e4 branch.  Same decomposition as above, but K is walked in chunks
-// of 128 (= one v_mfma_scale_f32_16x16x128_f8f6f4): lane (row l%16, q = l/16) holds the 16 values
-// k = 16q.. of each 64-half of the chunk, which is both the fragment position of the 4-bit main codes
-// and, as E4M3, bytes 0..15 / 16..31 of the lane's 8-bit MFMA operand.  A 32-block is shared by the
-// lane pair (q, q^1); the MFMA takes the scale of block q from lane (row, q), so lanes 1 and 2 swap.
-//
-// No scale spans more than a block, so the row is streamed, two chunks of X in flight per wavefront; the chunk's R is requested before its X
-// is coded and used after.  What bounds it: at one workgroup per compute unit the chain of a wavefront's chunks and the way of R (r K bytes)
-// through one compute unit, at more R's traffic from the L2 beside X's from memory (mxb_act_form has the forms and their times).  us a call,
-// four wavefronts with R a chunk ahead, values unpacked to fp32 and addresses in vector registers / this: 2 x 1152 rank 32 5.4 / 4.1, 300 x 1152
-// rank 64 6.6 / 5.0, 64 x 4608 rank 128 17.2 / 9.1, 6001 x 2240 rank 64 17.8 / 15.7, 16384 x 1152 rank 64 20.1 / 16.3, rank 128 32.7 / 21.5.
-// ---------------------------------------------------------------------------------------------
-struct MxbActParams {
-    const void* X;
-    int64_t ldx;
-    int M, K, C64, C64s, CQ, C128, r, rp;  // K, C64s: the caller's row length and its 64-chunks; C64, C128: of the layout
-    const uint8_t* r8;
-    const uint8_t* re;
-    uint8_t* xc;
-    uint8_t* xe;
-    uint8_t* tq8;
-    uint8_t* te;
-    int8_t* dbg_xb;
-    uint8_t* dbg_xbe;
-    float* dbg_T;
-    const float* rg;  // reciprocals of the smoothing vector (smoothing variant only)
-    BlobTag tag;        // header of the activation blob (written by the first workgroup)
-    uint32_t* tag_dst;
-};
-
 // 16 values of a block and the block's scale -> 16 E4M3 bytes, nearest even, saturating at +-448 * 2^(E - 127): the scaled converters, from
 // bf16 pairs with both magnitudes limited first (they return NaN past the range), without unpacking a value.
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
@@ -816,6 +517,348 @@ __device__ __forceinline__ float mx_amax16(const MxChunk<false>& ch)
     for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(ch.get(i)));
     return m;
 }
+
+// BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32).
+template <bool BF16IN, int MAXC, int NJB, bool SM, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 1) void mx_act_kernel(MxActParams p)
+{
+    write_tag(p.tag_dst, p.tag);
+    constexpr bool BF16 = BF16IN && !SM;  // representation of the row in registers
+    constexpr int NJA = NJB > 0 ? NJB : 1;
+    constexpr int NSUM = 8, SW = NSUM / NW;  // T is eight sums, over the chunks c = 0 .. 7 mod 8, added in order; SW of them to a wavefront
+    __shared__ float s_amax[NW][16];
+    __shared__ float s_sxb[16];
+    __shared__ float s_acc[NSUM][NJA][64][4];
+    __shared__ float s_tmax[NW][16];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, kq = lane >> 4;
+    const int row = blockIdx.x * 16 + r16;
+    const bool row_ok = row < p.M;
+    const uint32_t rowmask = row_ok ? ~0u : 0u;
+    const int C64 = p.C64;
+
+    // MAXC = 0: rows too long for the registers are streamed twice through a two-chunk ring (amax pass, coding pass;
+    // the second read comes from the caches)
+    constexpr bool STREAM = MAXC == 0;
+    constexpr int NS = STREAM ? 2 : MAXC;        // chunk slots in registers
+    const int nmy = (C64 - wave + NW - 1) / NW;  // chunks of this wavefront: c = wave + NW * ci, ci < nmy
+    MxChunk<BF16> xc[NS];
+    const size_t xrow = (size_t)(row_ok ? row : p.M - 1) * p.ldx + kq * 16;
+    // (in the ring no branch stands around the loads, which would end the compiler's count of those in flight: past the end they are clamped,
+    // and masked where they are used)
+    auto load_x = [&](MxChunk<BF16>& ch, int ci) {
+        int c = wave + NW * ci;
+        const bool ok = STREAM || c < p.C64s;  // wave-uniform
+        c = c < p.C64s ? c : p.C64s - 1;
+        if (!ok) ch = MxChunk<BF16>{};
+        else if constexpr (SM)
+            smooth_load<BF16IN, 16>(ch.v, p.X, xrow + (size_t)c * 64, p.rg + (size_t)c * 64 + kq * 16, true);
+        else
+            ch.load(p.X, xrow + (size_t)c * 64, true);
+    };
+    auto keep_of = [&](int ci) { return wave + NW * ci < p.C64s ? rowmask : 0u; };  // (rows past M and chunks past the row: zeros)
+#pragma unroll
+    for (int ci = 0; ci < NS; ++ci) load_x(xc[ci], ci);
+
+    // Operands that do not depend on X are requested now (their latency overlaps the load of X):
+    // the Q2(R) fragments of the first chunk (later ones one chunk ahead, in the loop), R's scales.
+    v4i bvs[2][NJA];
+    auto load_r8 = [&](v4i (&dst)[NJA], int ci) {
+        int c = wave + NW * ci;
+        c = c < C64 ? c : C64 - 1;  // clamped: a fragment past the end is fetched but not used
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb) dst[jb] = *(const v4i*)(p.r8 + ((size_t)((size_t)c * NJB + jb) * 64 + lane) * 16);
+    };
+    load_r8(bvs[0], 0);
+    constexpr int PW = NJB <= 2 ? 1 : NW;        // wavefronts that re-quantise the intermediate
+    constexpr int NT = (NJA + PW - 1) / PW;      // 16-column groups each of them takes
+    float srj[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) srj[t] = NJB > 0 ? p.sr[(wave + PW * t < NJB ? wave + PW * t : 0) * 16 + r16] : 0.f;
+
+    // amax of the lane's 16 values per chunk (kept for the block scale when the row is resident) and of the whole row
+    float a16[NS];
+    float a = 0.f;
+    auto amax_chunk = [&](const MxChunk<BF16>& ch, int ci) { return __uint_as_float(__float_as_uint(mx_amax16(ch)) & keep_of(ci)); };
+    if constexpr (STREAM) {
+        for (int ci0 = 0; ci0 < nmy; ci0 += 2) {
+#pragma unroll
+            for (int sl = 0; sl < 2; ++sl) {
+                a = fmaxf(a, amax_chunk(xc[sl], ci0 + sl));
+                load_x(xc[sl], ci0 + sl + 2);
+            }
+        }
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) load_x(xc[sl], sl);  // second pass: the ring starts over
+    } else {
+#pragma unroll
+        for (int ci = 0; ci < NS; ++ci) {
+            a16[ci] = amax_chunk(xc[ci], ci);
+            a = fmaxf(a, a16[ci]);
+        }
+    }
+    a = max_xor16(a);
+    a = max_xor32(a);
+    if (kq == 0) s_amax[wave][r16] = a;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) a = fmaxf(a, s_amax[w][r16]);
+    float sb, invb;
+    fp8_scales(a, &sb, &invb);
+    if (wave == 0 && kq == 0) {
+        s_sxb[r16] = sb;
+        if (p.dbg_sxb && row_ok) p.dbg_sxb[row] = sb;
+        if (NJB == 0) p.st[row] = 1.0f;
+    }
+
+    v4f acc[SW][NJA];
+#pragma unroll
+    for (int i = 0; i < SW; ++i)
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb) acc[i][jb] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    // one 64-chunk: MXFP4 codes and block scales, FP8 branch codes, skinny contraction (am: amax of the lane's 16 values; odd: ci & 1)
+    auto code_chunk = [&](const MxChunk<BF16>& ch, const int c, const uint32_t keep, const float am, auto odd) {
+        // MXFP4: block of 32 = this lane's 16 values and its neighbour's (kq ^ 1)
+        const float ab = max_xor16(am);
+        const uint32_t E = e8m0_of(ab);
+        const uint32_t nz = ab != 0.0f ? ~0u : 0u;  // (a block of zeros has codes 0, also where the zeros are negative)
+        uint32_t pk[2] = {0u, 0u};
+        mxfp4_codes16(ch, e8m0_value(E), pk);
+        uint32_t x8[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {  // (at most 448 (1 + 2^-23) in magnitude: the converter's rounding saturates it)
+            const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(__fmul_rn(ch.get(4 * q), invb), __fmul_rn(ch.get(4 * q + 1), invb), 0, false);
+            x8[q] = keep & (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(__fmul_rn(ch.get(4 * q + 2), invb), __fmul_rn(ch.get(4 * q + 3), invb), lo, true);
+        }
+        uint8_t* dst = p.xc + ((size_t)((size_t)(row >> 5) * C64 + c) * 64 + (row & 31) + 32 * (kq >> 1)) * 16 + (kq & 1) * 8;
+        *(uint2*)dst = make_uint2(pk[0] & nz, pk[1] & nz);
+        if ((kq & 1) == 0) p.xe[mx_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)E;
+        if (p.dbg_xb && row_ok && c < p.C64s)
+            *(v4i*)(p.dbg_xb + (size_t)row * p.K + c * 64 + kq * 16) = v4i{(int)x8[0], (int)x8[1], (int)x8[2], (int)x8[3]};
+        if (NJB > 0) {
+            constexpr int par = decltype(odd)::value, set = par % SW;
+            const long alo = (long)(((unsigned long)x8[1] << 32) | x8[0]);
+            const long ahi = (long)(((unsigned long)x8[3] << 32) | x8[2]);
+#pragma unroll
+            for (int jb = 0; jb < NJB; ++jb) {
+                const v4i bv = bvs[par][jb];
+                const long blo = (long)(((unsigned long)(uint32_t)bv[1] << 32) | (uint32_t)bv[0]);
+                const long bhi = (long)(((unsigned long)(uint32_t)bv[3] << 32) | (uint32_t)bv[2]);
+                acc[set][jb] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(alo, blo, acc[set][jb], 0, 0, 0);
+                acc[set][jb] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ahi, bhi, acc[set][jb], 0, 0, 0);
+            }
+        }
+    };
+    auto pad_chunk = [&](const int c) {  // padding chunk of the last quad: its scale bytes must be valid E8M0 values (2^0)
+        if (c >= C64 && c < 4 * p.CQ && (kq & 1) == 0) p.xe[mx_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)127;
+    };
+    auto pair = [&](auto f) {  // f(0), f(1) with the argument as a compile-time constant
+        f(std::integral_constant<int, 0>{});
+        f(std::integral_constant<int, 1>{});
+    };
+    if constexpr (STREAM) {
+        for (int ci0 = 0; ci0 < nmy; ci0 += 2) {
+            pair([&](auto sl) {
+                const int ci = ci0 + decltype(sl)::value, c = wave + NW * ci;
+                load_r8(bvs[(decltype(sl)::value + 1) & 1], ci + 1);
+                MxChunk<BF16>& x = xc[decltype(sl)::value];
+                if (c < C64) code_chunk(x, c, keep_of(ci), amax_chunk(x, ci), sl);  // wave-uniform
+                load_x(x, ci + 2);
+            });
+        }
+        pad_chunk(wave + NW * nmy);
+    } else {
+#pragma unroll
+        for (int ci0 = 0; ci0 < NS; ci0 += 2) {
+            pair([&](auto sl) {
+                constexpr int par = decltype(sl)::value;
+                const int ci = ci0 + par, c = wave + NW * ci;
+                if (ci >= NS) return;
+                if (ci + 1 < NS) load_r8(bvs[par ^ 1], ci + 1);
+                if (c < C64) code_chunk(xc[ci], c, keep_of(ci), a16[ci], sl);  // wave-uniform
+                else pad_chunk(c);
+            });
+        }
+    }
+    if (NJB == 0) return;
+
+    // ---- the eight sums, dequantised and re-quantised per token.  Up to two 16-column groups: the first wavefront; more: wavefront w takes the
+    // groups w, w + NW, and the row maxima meet in LDS
+#pragma unroll
+    for (int i = 0; i < SW; ++i)
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb) *(v4f*)&s_acc[wave + NW * i][jb][lane][0] = acc[i][jb];
+    __syncthreads();
+    if (wave >= PW) return;
+
+    float T[NT][4];
+    float tmax[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int jb = wave + PW * t;
+        if (jb >= NJB) break;  // wave-uniform
+        v4f s = *(const v4f*)&s_acc[0][jb][lane][0];
+#pragma unroll
+        for (int w = 1; w < NSUM; ++w) {
+            const v4f o = *(const v4f*)&s_acc[w][jb][lane][0];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = __fadd_rn(s[i], o[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int tok = 4 * kq + i;
+            const float tv = __fmul_rn(__fmul_rn(s[i], s_sxb[tok]), srj[t]);
+            T[t][i] = tv;
+            tmax[i] = fmaxf(tmax[i], fabsf(tv));
+            const int grow = blockIdx.x * 16 + tok;
+            if (grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = tv;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        tmax[i] = max_row16(tmax[i]);
+    }
+    if constexpr (PW > 1) {
+        if (r16 == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s_tmax[wave][4 * kq + i] = tmax[i];
+        }
+        __syncthreads();  // (every wavefront: PW = NW)
+#pragma unroll
+        for (int w = 0; w < PW; ++w)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tmax[i] = fmaxf(tmax[i], s_tmax[w][4 * kq + i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int grow = blockIdx.x * 16 + 4 * kq + i;
+        float stv, invt;
+        fp8_scales(tmax[i], &stv, &invt);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int jb = wave + PW * t;
+            if (jb >= NJB) break;
+            p.tq8[(size_t)grow * p.rp + jb * 16 + r16] = (uint8_t)fp8_byte(__fmul_rn(T[t][i], invt));
+        }
+        if (wave == 0) {
+            if (r16 == 0) p.st[grow] = stv;
+            for (int j = p.r + r16; j < p.rp; j += 16) p.tq8[(size_t)grow * p.rp + j] = 0;
+        }
+    }
+}
+
+template <bool BF16, int MAXC, int NJB, bool SM, int NW>
+static hipError_t mx_act_launch(const MxActParams& p, int64_t Mp, hipStream_t s)
+{
+    hipLaunchKernelGGL((mx_act_kernel<BF16, MAXC, NJB, SM, NW>), dim3((unsigned)(Mp / 16)), dim3(64 * NW), 0, s, p);
+    return hipGetLastError();
+}
+template <bool BF16, int MAXC, bool SM, int NW>
+static hipError_t mx_act_rank(const MxActParams& p, int64_t Mp, hipStream_t s)
+{
+    switch (p.r) {
+        case 0: return mx_act_launch<BF16, MAXC, 0, SM, NW>(p, Mp, s);
+        case 16: return mx_act_launch<BF16, MAXC, 1, SM, NW>(p, Mp, s);
+        case 32: return mx_act_launch<BF16, MAXC, 2, SM, NW>(p, Mp, s);
+        case 64: return mx_act_launch<BF16, MAXC, 4, SM, NW>(p, Mp, s);
+        default: return mx_act_launch<BF16, MAXC, 8, SM, NW>(p, Mp, s);
+    }
+}
+template <bool BF16, bool SM>
+static hipError_t mx_act_len(const MxActParams& p, int64_t Mp, hipStream_t s)
+{
+    // Eight wavefronts while every 16 rows have a compute unit of their own (the time is one workgroup's chain: 2 x 1152 rank 32 4.5 us, four 5.1, 64 x
+    // 4608 rank 128 13.7, 15.6, 4096 x 2240 rank 64 10.5, 11.5), and for long rows where they hold the row in few enough registers for two
+    // workgroups to a compute unit, or four would have to stream it (8192 x 4608 rank 32 27.1, 28.8, rank 128 36.4, 40.0, 12000 x 2240 rank 16 19.7,
+    // 20.8, smoothed 6001 x 4608 rank 128 36.0, 45.1); four elsewhere (16384 x 1152 rank 128 26.4, 21.8, 8192 x 4608 rank 64 32.3, 29.0, smoothed
+    // 6001 x 2240 rank 64 18.3, 16.5, 16384 x 512 rank 32 10.8, 9.5).
+    const bool fp32_rows = !BF16 || SM;
+    const bool wide = Mp <= 16 * compute_units() || (p.C64 > 36 && (fp32_rows || p.r != 64)) || (!fp32_rows && p.r <= 32 && p.C64 > 20);
+    if (wide) {
+        const int mc = (p.C64 + 7) / 8;
+        if (mc <= 3) return mx_act_rank<BF16, 3, SM, 8>(p, Mp, s);
+        if (mc <= 5) return mx_act_rank<BF16, 5, SM, 8>(p, Mp, s);
+        if (mc <= 9) return mx_act_rank<BF16, 9, SM, 8>(p, Mp, s);
+        return mx_act_rank<BF16, 0, SM, 8>(p, Mp, s);
+    }
+    // MAXC = 0: the streamed form, for rows that do not fit in registers (fp32 representation: K > 2304; bf16: K > 4608)
+    const int mc = (p.C64 + 3) / 4;
+    if (mc <= 5) return mx_act_rank<BF16, 5, SM, 4>(p, Mp, s);
+    if (mc <= 9) return mx_act_rank<BF16, 9, SM, 4>(p, Mp, s);
+    if constexpr (BF16 && !SM) {
+        if (mc <= 18) return mx_act_rank<BF16, 18, SM, 4>(p, Mp, s);
+    }
+    return mx_act_rank<BF16, 0, SM, 4>(p, Mp, s);
+}
+
+static hipError_t launch_quantize_act_mxb(const Dims& d, int x_dtype, const uint8_t* packed, const void* X, int64_t M,
+                                          int64_t ldx, uint8_t* act, const lq_act_debug* dbg, hipStream_t s);
+
+hipError_t launch_quantize_act_mx(const Dims& d, int x_dtype, const uint8_t* packed, const void* X, int64_t M,
+                                  int64_t ldx, uint8_t* act, const lq_act_debug* dbg, hipStream_t s)
+{
+    if (d.mxb_elem == 6) return launch_quantize_act_mx6(d, x_dtype, packed, X, M, ldx, act, dbg, s);
+    if (d.mxb) return launch_quantize_act_mxb(d, x_dtype, packed, X, M, ldx, act, dbg, s);
+    const PackedLayout pl = packed_layout(d);
+    const ActLayout al = act_layout(d, M);
+    MxActParams p;
+    p.tag = make_tag(d, LQ_BLOB_ACT, M);
+    p.tag_dst = (uint32_t*)act;
+    p.X = X;
+    p.ldx = ldx;
+    p.M = (int)M;
+    p.K = (int)d.Ks;
+    p.C64 = d.C64;
+    p.C64s = (int)(d.Ks / 64);
+    p.CQ = (d.C64 + 3) / 4;
+    p.r = d.r;
+    p.rp = d.rp;
+    p.r8 = packed + pl.off_rq;
+    p.sr = (const float*)(packed + pl.off_sr);
+    p.xc = act + al.off_xq;
+    p.xe = act + al.off_sx;
+    p.tq8 = act + al.off_tq;
+    p.st = (float*)(act + al.off_st);
+    p.dbg_xb = dbg ? dbg->xb : nullptr;
+    p.dbg_sxb = dbg ? dbg->sxb : nullptr;
+    p.dbg_T = dbg ? dbg->T : nullptr;
+    p.rg = d.smooth ? (const float*)(packed + pl.off_rg) : nullptr;
+    if (d.smooth) return x_dtype == LQ_BF16 ? mx_act_len<true, true>(p, al.Mp, s) : mx_act_len<false, true>(p, al.Mp, s);
+    return x_dtype == LQ_BF16 ? mx_act_len<true, false>(p, al.Mp, s) : mx_act_len<false, false>(p, al.Mp, s);
+}
+
+// ---------------------------------------------------------------------------------------------
+// activation kernel with an MXFP8e4 branch.  Same decomposition as above, but K is walked in chunks
+// of 128 (= one v_mfma_scale_f32_16x16x128_f8f6f4): lane (row l%16, q = l/16) holds the 16 values
+// k = 16q.. of each 64-half of the chunk, which is both the fragment position of the 4-bit main codes
+// and, as E4M3, bytes 0..15 / 16..31 of the lane's 8-bit MFMA operand.  A 32-block is shared by the
+// lane pair (q, q^1); the MFMA takes the scale of block q from lane (row, q), so lanes 1 and 2 swap.
+//
+// No scale spans more than a block, so the row is streamed, two chunks of X in flight per wavefront; the chunk's R is requested before its X
+// is coded and used after.  What bounds it: at one workgroup per compute unit the chain of a wavefront's chunks and the way of R (r K bytes)
+// through one compute unit, at more R's traffic from the L2 beside X's from memory (mxb_act_form has the forms and their times).  us a call,
+// four wavefronts with R a chunk ahead, values unpacked to fp32 and addresses in vector registers / this: 2 x 1152 rank 32 5.4 / 4.1, 300 x 1152
+// rank 64 6.6 / 5.0, 64 x 4608 rank 128 17.2 / 9.1, 6001 x 2240 rank 64 17.8 / 15.7, 16384 x 1152 rank 64 20.1 / 16.3, rank 128 32.7 / 21.5.
+// ---------------------------------------------------------------------------------------------
+struct MxbActParams {
+    const void* X;
+    int64_t ldx;
+    int M, K, C64, C64s, CQ, C128, r, rp;  // K, C64s: the caller's row length and its 64-chunks; C64, C128: of the layout
+    const uint8_t* r8;
+    const uint8_t* re;
+    uint8_t* xc;
+    uint8_t* xe;
+    uint8_t* tq8;
+    uint8_t* te;
+    int8_t* dbg_xb;
+    uint8_t* dbg_xbe;
+    float* dbg_T;
+    const float* rg;  // reciprocals of the smoothing vector (smoothing variant only)
+    BlobTag tag;        // header of the activation blob (written by the first workgroup)
+    uint32_t* tag_dst;
+};
 
 // BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32); DBG: parity taps.
 template <bool BF16IN, int NJB, bool SM, int NW, bool DBG>

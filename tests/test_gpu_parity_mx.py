@@ -197,3 +197,36 @@ def test_forward_forms(oracle, fam, bw, M, K, N, r):
     X, W, L, R = wl.make_inputs(layer)
     rows = np.unique(np.concatenate([np.arange(M - 40, M), np.arange(0, M, 61)]))
     (_compare if fam == "mx" else mxb._compare)(oracle, layer, X, W, L, R, rows=rows)
+
+
+# Every form of the activation step (3, 5 or 9 chunks of 64 held by each of 8 wavefronts, 5, 9 or 18 by each of 4, and streamed rows), on both
+# sides of a group of 16 rows per compute unit, with a padding chunk, rows past the last and blocks of negative zeros.
+@pytest.mark.parametrize("K,r,xd,smooth", [(192, 64, "bf16", False), (1152, 128, "bf16", False), (1600, 16, "bf16", False), (2112, 64, "bf16", False),
+                                           (4544, 32, "bf16", False), (4608, 64, "bf16", False), (4672, 16, "bf16", False), (1152, 32, "f32", False),
+                                           (2560, 64, "f32", False), (4672, 128, "f32", False), (2368, 128, "bf16", True), (1344, 0, "bf16", True)])
+def test_forms_of_the_activation_step(oracle, K, r, xd, smooth):
+    from paper_2604_18117_amd import binding as lq
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    layer = wl.Layer("t", 37, K, 64, r, "mx", 32, 8, 8, xd, seed=K + r)
+    X, W, L, R = wl.make_inputs(layer)
+    X[2, :] = -0.0
+    X[3, 32:64] = -0.0
+    gamma = np.exp2(np.random.default_rng(K).integers(-3, 4, K)).astype(np.float32) if smooth else None
+    cfg = lq.config_for_layer(layer, smooth=smooth)
+    packed = lq.lq_pack_weights(cfg, *(torch.from_numpy(a).cuda() if r or a is W else None for a in (W, L, R)))
+    if smooth:
+        lq.lq_set_smoothing(cfg, packed, torch.from_numpy(gamma).cuda())
+    pk = oracle.pack_mx(W, L if r else None, R if r else None)
+    want = oracle.quantize_act_mx(oracle.smooth(X, gamma) if smooth else X, pk)
+    Xd = wl.to_dev_x(X, xd)
+    first = None
+    for M in (37, 16 * cus - 3, 16 * cus + 5):
+        big = Xd.repeat((M + 36) // 37, 1)[:M].contiguous()
+        v = lq.lq_unpack_act(cfg, lq.lq_quantize_act(cfg, packed, big, act=torch.full((lq.lq_act_sizes(cfg, M),), 0xFF, dtype=torch.uint8, device="cuda")), M)
+        xq = n(v.xq).view(np.uint8)
+        assert np.array_equal(E2M1[xq[:37]], E2M1[want.xc]) and np.array_equal(n(v.xe)[:37], want.xe), M
+        assert not xq[2].any() and not xq[3, 32:64].any()
+        got = [t.cpu() for t in ((v.xq, v.xe, v.tq, v.st) if r else (v.xq, v.xe))]
+        first = first or got
+        for a, b in zip(got, first):               # the same bits in every form and row
+            assert torch.equal(a, b.repeat(((M + 36) // 37,) + (1,) * (b.dim() - 1))[:M]), M
