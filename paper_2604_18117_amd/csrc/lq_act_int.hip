@@ -238,10 +238,9 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
 #pragma unroll
     for (int w = 0; w < NW; ++w) a = fmaxf(a, s_amax[w][r16]);
 
-    float s4, inv4, sb, invb;
-    scales(a, 7.0f, &s4, &inv4);
-    scales(a, p.qa, &sb, &invb);
-    if (wave == 0 && kq == 0) {
+    float inv4 = a == 0.0f ? 1.0f : 7.0f / a, invb = a == 0.0f ? 1.0f : p.qa / a;
+    if (wave == NW - 1 && kq == 0) {  // (the scales themselves: by the wavefront with the fewest chunks)
+        const float s4 = a == 0.0f ? 1.0f : a / 7.0f, sb = a == 0.0f ? 1.0f : a / p.qa;
         if constexpr (!GA) p.sx[row] = s4;
         s_sxb[r16] = sb;
         if (p.dbg_sxb && row_ok) p.dbg_sxb[row] = sb;
@@ -390,11 +389,15 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
 #pragma unroll
             for (int i = 0; i < 4; ++i) tmax[i] = fmaxf(tmax[i], s_tmax[w][4 * kq + i]);
     }
+    // (a row's maximum is in 16 lanes: lane i & 3 divides for row i and hands both factors to the others)
+    float sv, iv;
+    scales(r16 & 2 ? (r16 & 1 ? tmax[3] : tmax[2]) : (r16 & 1 ? tmax[1] : tmax[0]), p.qa, &sv, &iv);
+    const float st4[4] = {row16_lane<0>(sv), row16_lane<1>(sv), row16_lane<2>(sv), row16_lane<3>(sv)};
+    const float inv4t[4] = {row16_lane<0>(iv), row16_lane<1>(iv), row16_lane<2>(iv), row16_lane<3>(iv)};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int grow = blockIdx.x * 16 + 4 * kq + i;
-        float stv, invt;
-        scales(tmax[i], p.qa, &stv, &invt);
+        const float stv = st4[i], invt = inv4t[i];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int jb = wave + PW * t;
@@ -444,7 +447,9 @@ static hipError_t launch_len(const ActParams& p, int64_t Mp, hipStream_t s)
     // costs more than a second pass over a row of six chunks per wavefront (4096 x 2624 rank 128: streamed 23.7 us, in
     // registers 28.0; 2 x 2624 rank 16: 10.5, 13.6) and less than one over nine (1024 x 4608 rank 32: 27.3, 24.4).  The other types spill at
     // rank 128 alone, at most 29 registers, and are within 3 % of the streamed form or faster.
-    if (Mp <= 16 * compute_units()) {
+    // So they are where four would stream the row, but for smoothed fp32 rows (smoothed 8192 x 4608 rank 64 34.5 us, four 41.6, 12000 x 2560 rank 64 31.0,
+    // 36.9, fp32 6001 x 4480 44.8, 54.0).  Sixteen are slower at every size (64 x 1536 rank 64 7.0 us, eight 5.9, 2 x 1152 4.1, 3.7, 12 x 4480 9.1, 9.2).
+    if (Mp <= 16 * compute_units() || (p.C64 > 36 && p.C64 <= 72 && BF16 == SM)) {
         const int mc = (p.C64 + 7) / 8;
         if (mc <= 3) return launch_rank<BF16, 3, SM, 8>(p, Mp, s);
         if (mc <= 5) return launch_rank<BF16, 5, SM, 8>(p, Mp, s);

@@ -604,9 +604,9 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < NW; ++w) a = fmaxf(a, s_amax[w][r16]);
-    float sb, invb;
-    fp8_scales(a, &sb, &invb);
-    if (wave == 0 && kq == 0) {
+    const float invb = a == 0.0f ? 1.0f : 448.0f / a;
+    if (wave == NW - 1 && kq == 0) {  // (the scale itself: by the wavefront with the fewest chunks)
+        const float sb = a == 0.0f ? 1.0f : a / 448.0f;
         s_sxb[r16] = sb;
         if (p.dbg_sxb && row_ok) p.dbg_sxb[row] = sb;
         if (NJB == 0) p.st[row] = 1.0f;
@@ -731,11 +731,15 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 
 #pragma unroll
             for (int i = 0; i < 4; ++i) tmax[i] = fmaxf(tmax[i], s_tmax[w][4 * kq + i]);
     }
+    // (a row's maximum is in 16 lanes: lane i & 3 divides for row i and hands both factors to the others)
+    float sv, iv;
+    fp8_scales(r16 & 2 ? (r16 & 1 ? tmax[3] : tmax[2]) : (r16 & 1 ? tmax[1] : tmax[0]), &sv, &iv);
+    const float st4[4] = {row16_lane<0>(sv), row16_lane<1>(sv), row16_lane<2>(sv), row16_lane<3>(sv)};
+    const float inv4t[4] = {row16_lane<0>(iv), row16_lane<1>(iv), row16_lane<2>(iv), row16_lane<3>(iv)};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int grow = blockIdx.x * 16 + 4 * kq + i;
-        float stv, invt;
-        fp8_scales(tmax[i], &stv, &invt);
+        const float stv = st4[i], invt = inv4t[i];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int jb = wave + PW * t;

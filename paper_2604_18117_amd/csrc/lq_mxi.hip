@@ -434,7 +434,7 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
     constexpr int NJA = NJB > 0 ? NJB : 1;
     constexpr int KW = 4;                        // wavefronts along K: part of T's order of summation, the same in every form
     constexpr int NG = RPW * ROWG;               // groups of 16 rows per workgroup
-    constexpr int RCHUNK = NJB * 2048;           // bytes of R per 64-chunk
+    constexpr int RCHUNK = NJB * 2048;           // bytes of this workgroup's columns of R per 64-chunk
     constexpr int RBUF = KW * RCHUNK;            // ... per super-step
     constexpr bool STAGE = NJB > 0 && ROWG > 1;  // R goes through LDS
     constexpr int RED = NG * KW * NJA * 1024;    // partial sums of the wavefronts of a row group
@@ -449,6 +449,10 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
     const int C64 = p.C64;
     const int Mp = p.Mp;
     const int nss = (C64 + KW - 1) / KW;
+    // Small batches: a workgroup per 16 rows and 32 columns of the rank (grid.y); the first stores the main codes.  Every block of the intermediate
+    // is 32 columns, and no sum runs across them.
+    const int jb0 = STAGE ? 0 : (int)blockIdx.y * NJB, rchunk = STAGE ? RCHUNK : p.r * 128;  // bytes of all of R per 64-chunk
+    const bool first = STAGE || blockIdx.y == 0;
 
     // Rows past M count as zeros, chunks past the end are clamped and not used: the loads are unconditional (the wait
     // below counts them).  Groups past Mp (the last workgroup) are not stored.
@@ -478,7 +482,7 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
     constexpr int RI = RBUF / 1024 / (KW * ROWG);  // 1 KB instructions per wavefront, all of one chunk
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
     auto chunk_r = [&](int c) {  // R of one chunk (a descriptor for all of it would end at 4 GB: K = 2^24 at rank 128 has as much)
-        return __builtin_amdgcn_make_buffer_rsrc((void*)(p.rv + (size_t)c * RCHUNK), 0, RCHUNK, 0x00020000);
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(p.rv + (size_t)c * rchunk + jb0 * 2048), 0, RCHUNK, 0x00020000);
     };
     auto load_r = [&](int ss) {
         if constexpr (STAGE) {
@@ -567,8 +571,9 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
                 field = exp_field(ab);
                 // ---- main codes: MXINT4, clamp(rne(x * 2^(2-s)), +-7) by the FP6 converter
                 const float sc = f6_scale(field);
-                uint2 pk;
-                if constexpr (BF16) {
+                uint2 pk = {0u, 0u};
+                if (!first) {
+                } else if constexpr (BF16) {
                     const uint32_t l1 = f6_limit(field), l2 = l1 | (l1 >> 16);
                     uint32_t cw[8];
 #pragma unroll
@@ -583,7 +588,7 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
                 }
                 // lane (row, kq): half kq & 1 of block kq >> 1 of the chunk
                 uint8_t* dst = p.xq + ((size_t)((size_t)(row >> 5) * C64 + c) * 64 + (row & 31) + 32 * (kq >> 1)) * 16 + (kq & 1) * 8;
-                if (have && row0 + 16 * g < Mp) {
+                if (first && have && row0 + 16 * g < Mp) {
                     *(uint2*)dst = pk;
                     if ((kq & 1) == 0) p.xe[mxi_scale_offset(row, c, kq >> 1, p.CQ)] = (uint8_t)(field + 1u);
                 }
@@ -670,7 +675,7 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
     if (ss < nss) step(xs[0], ss);
     if constexpr (!FROMC) {   // padding chunks of the last quad: their scale bytes must be valid E8M0 values (2^0)
         const int c = C64 + wave;
-        if (c < 4 * p.CQ && (kq & 1) == 0) {
+        if (first && c < 4 * p.CQ && (kq & 1) == 0) {
 #pragma unroll
             for (int g = 0; g < RPW; ++g)
                 if (row0 + 16 * g < Mp) p.xe[mxi_scale_offset(row0 + 16 * g + r16, c, kq >> 1, p.CQ)] = (uint8_t)127;
@@ -709,7 +714,7 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
                 for (int i = 0; i < 4; ++i) {
                     T[h][i] = sum[i];
                     const int grow = rbase + 4 * kq + i;
-                    if (DBG && grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + (2 * bb + h) * 16 + r16] = sum[i];
+                    if (DBG && grow < p.M && p.dbg_T) p.dbg_T[(size_t)grow * p.r + (jb0 + 2 * bb + h) * 16 + r16] = sum[i];
                 }
             }
 #pragma unroll
@@ -718,11 +723,11 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
                 tm = max_row16(tm);
                 const int grow = rbase + 4 * kq + i;
                 const uint32_t field = exp_field(tm);
-                if (r16 == 0) p.te[(size_t)grow * BR + bb] = (uint8_t)field;
+                if (r16 == 0) p.te[(size_t)grow * BR + (jb0 >> 1) + bb] = (uint8_t)field;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const float v = mxint8_round(T[h][i], field);
-                    *(uint16_t*)(p.tv + mxi_lt_offset(grow, (2 * bb + h) * 16 + r16, p.rp)) = (uint16_t)(__float_as_uint(v) >> 16);
+                    *(uint16_t*)(p.tv + mxi_lt_offset(grow, (jb0 + 2 * bb + h) * 16 + r16, p.rp)) = (uint16_t)(__float_as_uint(v) >> 16);
                 }
             }
         }
@@ -765,7 +770,17 @@ static hipError_t mxi_act_launch2(const MxiActParams& p, hipStream_t s)
     switch (mxi_act_rows(p.r, p.K, p.Mp, FROMC)) {
         case 64: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 2, 2, DBG>), dim3((unsigned)((p.Mp + 63) / 64)), dim3(512), 0, s, p); break;
         case 32: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 2, DBG>), dim3((unsigned)(p.Mp / 32)), dim3(512), 0, s, p); break;
-        default: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 1, DBG>), dim3((unsigned)(p.Mp / 16)), dim3(256), 0, s, p); break;
+        default: {
+            // A workgroup per 32 columns of the rank while compute units are left over for them: R passes through a compute unit each (us, one / this:
+            // 300 x 1152 rank 128 7.1 / 5.1, 64 x 4608 rank 128 18.9 / 10.6, rank 64 12.9 / 12.3, 300 x 2240 fp32 rank 96 11.8 / 8.3, 2000 x 1152 rank 64
+            // 7.3 / 6.3; with two workgroups to a compute unit 2000 x 1152 rank 128 8.7 / 8.1, 3000 x 2240 rank 64 11.4 / 12.0, 3000 x 512 4.5 / 5.3).
+            constexpr int NB = NJB / 2;
+            if (NB > 1 && (int64_t)(p.Mp / 16) * NB <= compute_units())
+                hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB < 2 ? NJB : 2, SM, FROMC, 1, 1, DBG>), dim3((unsigned)(p.Mp / 16), NB > 0 ? NB : 1), dim3(256), 0, s, p);
+            else
+                hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 1, DBG>), dim3((unsigned)(p.Mp / 16)), dim3(256), 0, s, p);
+            break;
+        }
     }
     return hipGetLastError();
 }

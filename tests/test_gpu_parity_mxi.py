@@ -327,3 +327,39 @@ def test_outputs_do_not_depend_on_the_tiles(fam, g, bw, ag, K, N, ms):
     Y = [lq.lq_linear_lowrank_fwd(cfg, packed, lq.lq_quantize_act(cfg, packed, X[:m]), m).view(torch.int16) for m in ms]
     for m, y in zip(ms, Y):
         assert torch.equal(y, Y[-1][:m]), m
+
+
+# Small batches deal a group of 16 rows to a workgroup per 32 columns of the rank: the codes are those of one workgroup per group, from X and from
+# codes, on both sides of the line.
+@pytest.mark.parametrize("r,K,xd,smooth", [(64, 1152, "bf16", False), (96, 320, "f32", False), (128, 64, "bf16", False), (128, 1600, "bf16", True), (96, 4608, "bf16", False)])
+def test_workgroups_per_block_of_the_rank(r, K, xd, smooth):
+    from paper_2604_18117_amd import binding as lq
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(r + K)
+    W, L, R = (torch.randn(s, generator=gen, device="cuda") * f for s, f in (((64, K), 0.02), ((64, r), 0.1), ((r, K), 0.1)))
+    cfg = lq.make_config(64, K, r, "mxi", 32, 8, x_dtype=xd, smooth=smooth)
+    packed = lq.lq_pack_weights(cfg, W, L, R)
+    if smooth:
+        lq.lq_set_smoothing(cfg, packed, torch.rand(K, generator=gen, device="cuda") + 0.5)
+    groups = cus // (r // 32)                               # the last number of groups that are dealt so
+    X = torch.randn((16 * groups + 16, K), generator=gen, device="cuda")
+    X = X if xd == "f32" else X.bfloat16()
+    views = []
+    for m in (16 * groups + 16, 16 * groups - 3, 5):
+        act = lq.lq_quantize_act(cfg, packed, X[:m], act=torch.full((lq.lq_act_sizes(cfg, m),), 0xFF, dtype=torch.uint8, device="cuda"))
+        dbg = lq.lq_quantize_act(cfg, packed, X[:m], act=torch.full_like(act, 0xFF), debug=True)[0]
+        assert torch.equal(act, dbg), m
+        v = lq.lq_unpack_act(cfg, act, m)
+        views.append((v.xq, v.xe, v.tq, v.te))
+        if not smooth:
+            codes = torch.randint(0, 256, (lq.lq_handoff_sizes(cfg, m),), generator=torch.Generator(device="cuda").manual_seed(1), dtype=torch.uint8, device="cuda")
+            codes[(((m + 31) // 32 * 32) * K + 255) // 256 * 256:] = 120   # scale bytes
+            if m == 16 * groups + 16:
+                all_codes = codes
+            else:                                           # the same rows
+                codes[:m * K] = all_codes[:m * K]
+            vc = lq.lq_unpack_act(cfg, lq.lq_branch_from_codes(cfg, packed, codes, m, act.clone()), m)
+            views[-1] += (vc.tq, vc.te)
+        for a, b in zip(views[-1], views[0]):
+            assert torch.equal(a, b[:m]), m
