@@ -456,8 +456,7 @@ static hipError_t launch_len(const ActParams& p, int64_t Mp, hipStream_t s)
         if (mc <= 9 && (BF16 || !SM || mc > 6)) return launch_rank<BF16, 9, SM, 8>(p, Mp, s);
         return launch_rank<BF16, 0, SM, 8>(p, Mp, s);
     }
-    // MAXC = 0: the streamed kernel, for rows that do not fit in registers (fp32 representation: beyond 9 chunks per
-    // wavefront, K > 2304; bf16: beyond 18, K > 4608)
+    // MAXC = 0: the streamed kernel, for rows that do not fit in registers (K > 4608; smoothed fp32 rows beyond K = 2304)
     const int mc = (p.C64 + 3) / 4;
     if (mc <= 5) return launch_rank<BF16, 5, SM, 4>(p, Mp, s);
     if (mc <= 9) return launch_rank<BF16, 9, SM, 4>(p, Mp, s);

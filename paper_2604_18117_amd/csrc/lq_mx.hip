@@ -787,14 +787,14 @@ static hipError_t mx_act_len(const MxActParams& p, int64_t Mp, hipStream_t s)
         if (mc <= 9) return mx_act_rank<BF16, 9, SM, 8>(p, Mp, s);
         return mx_act_rank<BF16, 0, SM, 8>(p, Mp, s);
     }
-    // MAXC = 0: the streamed form, for rows that do not fit in registers (fp32 representation: K > 2304; bf16: K > 4608)
+    // MAXC = 0: the streamed form, for rows that do not fit in registers (K > 4608; rows held as fp32 beyond K = 2304 went to eight wavefronts above)
     const int mc = (p.C64 + 3) / 4;
     if (mc <= 5) return mx_act_rank<BF16, 5, SM, 4>(p, Mp, s);
-    if (mc <= 9) return mx_act_rank<BF16, 9, SM, 4>(p, Mp, s);
     if constexpr (BF16 && !SM) {
-        if (mc <= 18) return mx_act_rank<BF16, 18, SM, 4>(p, Mp, s);
+        if (mc > 18) return mx_act_rank<BF16, 0, SM, 4>(p, Mp, s);
+        if (mc > 9) return mx_act_rank<BF16, 18, SM, 4>(p, Mp, s);
     }
-    return mx_act_rank<BF16, 0, SM, 4>(p, Mp, s);
+    return mx_act_rank<BF16, 9, SM, 4>(p, Mp, s);
 }
 
 static hipError_t launch_quantize_act_mxb(const Dims& d, int x_dtype, const uint8_t* packed, const void* X, int64_t M,
