@@ -9,7 +9,9 @@
 //
 // Decomposition: a workgroup of NW = 4 or 8 wavefronts owns 16 token rows; lane l of every wavefront
 // works on row l%16 and on the 16-value quarter l/16 of each 64-deep K chunk, which is
-// exactly the A-operand layout of v_mfma_i32_16x16x64_i8.  The 64-chunks of K are dealt
+// exactly the A-operand layout of v_mfma_i32_16x16x64_i8.  In small batches a workgroup owns 16 / CS rows and the 16 rows of
+// the operand are CS chunks of each: a product per chunk, the other chunks' rows zeroed, leaves a row's sum spread over CS rows
+// of the result, which are added at the end (whole numbers: the same sum).  The 64-chunks of K are dealt
 // round-robin to the wavefronts, so a whole row block lives in registers between the
 // amax pass and the quantisation pass: X is read from HBM once.  Rows too long for that (MAXC = 0) are
 // streamed twice through a two-chunk ring instead: once for the amax, once for the codes (the second read
@@ -149,8 +151,17 @@ __device__ __forceinline__ void f6_codes16(const float (&v)[16], uint32_t (&out)
     out[2] = c[2];
 }
 
+// Chunks of R a wavefront of eight holds or has requested: what its registers leave, at most four (us, two / this: 2 x 1152 rank 16 3.9 / 3.5, 300 x
+// 1152 rank 32 5.3 / 4.9, 64 x 2240 rank 64 7.4 / 7.1, 71 x 4544 rank 128 13.7 / 13.3, with 16 rows to a workgroup).  With four wavefronts the workgroups of a
+// compute unit cover for each other and registers are better spent on them.
+constexpr int act_int_ring(bool bf16in, int maxc, int njb, bool sm, bool ga, int nw)
+{
+    const int rows = maxc * (bf16in && !sm && !ga ? 8 : 16), left = njb > 0 ? (208 - rows - 4 * njb) / (4 * njb) : 0;
+    return maxc == 0 || nw == 4 || (sm && !bf16in && maxc == 9) || left < 2 ? 2 : left < 4 ? left : 4;
+}
+
 // BF16IN: element type of X; SM: smoothing variant (X times stored reciprocals, row held as fp32).
-template <bool BF16IN, int MAXC, int NJB, bool SM, bool GA, int NW>
+template <bool BF16IN, int MAXC, int NJB, bool SM, bool GA, int NW, int CS>
 __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
 {
     write_tag(p.tag_dst, p.tag);
@@ -162,17 +173,19 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: with smoothing, whose row is fp32 in registers, 8192 x 2240 took 29.6 us with it in a vector register and takes 18.0
     const int r16 = lane & 15, kq = lane >> 4;
-    const int row = blockIdx.x * 16 + r16;
+    constexpr int RW = 16 / CS;                      // rows per workgroup; a wavefront's turn is CS chunks of them
+    const int cs = r16 / RW, row = blockIdx.x * RW + (r16 & (RW - 1));
     const bool row_ok = row < p.M;
     const int C64 = p.C64;
     constexpr int njb = NJB;  // rank / 16
 
     constexpr bool STREAM = MAXC == 0;
     constexpr int NS = STREAM ? 2 : MAXC;            // chunk slots in registers
-    const int nmy = (C64 - wave + NW - 1) / NW;      // chunks of this wavefront: c = wave + NW * ci, ci < nmy
+    const int nmy = (C64 - wave + NW - 1) / NW;      // (STREAM) chunks of this wavefront: c = wave + NW * ci, ci < nmy
+    static_assert(!STREAM || CS == 1, "the streamed form takes one chunk at a time");
     XChunk<BF16> xc[NS];
     auto load_x = [&](XChunk<BF16>& ch, int ci) {
-        const int c = wave + NW * ci;
+        const int c = CS * (wave + NW * ci) + cs;
         const size_t koff = (size_t)c * 64 + kq * 16;
         if constexpr (SM)
             load_smoothed<BF16IN>(ch, p.X, (size_t)row * p.ldx + koff, p.rg + (c < C64 ? koff : 0), row_ok && c < C64);
@@ -183,17 +196,20 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
     for (int ci = 0; ci < NS; ++ci) load_x(xc[ci], ci);
 
     // Operands that do not depend on X are requested now, so that their latency overlaps the
-    // load of X: the Q2(R) fragments of this wavefront's first chunk (later chunks are fetched one
-    // chunk ahead inside the loop) and the row scales of R.
+    // load of X: the Q2(R) fragments of this wavefront's first chunks (later ones are fetched RD - 1
+    // chunks ahead inside the loop) and the row scales of R.
     constexpr int NJA = NJB > 0 ? NJB : 1;
-    v4i bv[2][NJA];
-    auto load_rq = [&](v4i (&dst)[NJA], int ci) {
-        int c = wave + NW * ci;
+    constexpr int RD = act_int_ring(BF16IN, MAXC, NJB, SM, GA, NW);
+    v4i bv[RD][NJA];
+    auto load_rq = [&](v4i (&dst)[NJA], int t) {
+        int c = CS * (wave + NW * (t / CS)) + t % CS;
         c = c < C64 ? c : C64 - 1;  // clamped: a fragment past the end is fetched but not used
 #pragma unroll
         for (int jb = 0; jb < NJB; ++jb) dst[jb] = *(const v4i*)(p.rq + ((size_t)((size_t)c * NJB + jb) * 64 + lane) * 16);
     };
-    load_rq(bv[0], 0);
+#pragma unroll
+    for (int k = 0; k < RD - 1; ++k)
+        if (k < CS * NS) load_rq(bv[k], k);
     constexpr int PW = NJB <= 2 ? 1 : NW;        // wavefronts that re-quantise the intermediate
     constexpr int NT = (NJA + PW - 1) / PW;      // column blocks each of them takes
     float srj[NT];
@@ -233,6 +249,8 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
     }
     a = max_xor16(a);
     a = max_xor32(a);
+    if constexpr (CS > 1) a = max_dpp<0x128>(a);  // the row's other chunks: rotations within 16 lanes by 8 and by 4
+    if constexpr (CS > 2) a = max_dpp<0x124>(a);
     if (kq == 0) s_amax[wave][r16] = a;
     __syncthreads();
 #pragma unroll
@@ -253,7 +271,9 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
 
     const int rb = row >> 5;
     // one 64-chunk: main codes (and the block scale with SINT4 blocks), branch codes, skinny contraction
-    auto code_chunk = [&](const XChunk<BF16>& ch, const int c, const int bslot) {
+    auto code_chunk = [&](const XChunk<BF16>& ch, const int ci, const int bslot) {
+        const int c = CS * (wave + NW * ci) + cs;
+        const bool have = CS == 1 || c < C64;
         uint32_t pk[3];
         uint32_t xb4[4] = {0u, 0u, 0u, 0u};
         if constexpr (GA) {
@@ -273,7 +293,7 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
             ac = max_xor16(ac);
             ac = max_xor32(ac);
             const uint32_t bits = sint4_scale(ac, &inv4);
-            if (kq == 0) {
+            if (kq == 0 && have) {
                 p.sxg[sxg_index(row, c, p.tiles128)] = bits;
                 // row blocks of the last 128-row tile that do not exist: finite scales (the forward multiplies
                 // them by zero)
@@ -306,7 +326,7 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
         }
         // the lane's 16 codes are dwords 3*(kq&1) .. +2 of the forward lane (row % 32, K half kq/2): an aligned
         // 8-byte and a 4-byte store
-        {
+        if (have) {
             uint8_t* chunk = p.xq + ((size_t)rb * C64 + c) * F6_CHUNK;
             const int fl = (row & 31) + 32 * (kq >> 1);
             const bool odd = kq & 1;
@@ -315,13 +335,26 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
             *(uint2*)d8 = odd ? make_uint2(pk[1], pk[2]) : make_uint2(pk[0], pk[1]);
             *(uint32_t*)d4 = odd ? pk[0] : pk[2];
         }
-        if (p.dbg_xb && row_ok)
+        if (p.dbg_xb && row_ok && have)
             *(v4i*)(p.dbg_xb + (size_t)row * p.K + c * 64 + kq * 16) = v4i{(int)xb4[0], (int)xb4[1], (int)xb4[2], (int)xb4[3]};
         if (njb > 0) {
             const v4i av = {(int)xb4[0], (int)xb4[1], (int)xb4[2], (int)xb4[3]};
+            if constexpr (CS == 1) {
 #pragma unroll
-            for (int jb = 0; jb < NJB; ++jb)
-                acc[jb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, bv[bslot][jb], acc[jb], 0, 0, 0);
+                for (int jb = 0; jb < NJB; ++jb)
+                    acc[jb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, bv[bslot][jb], acc[jb], 0, 0, 0);
+            } else {
+                // a product per chunk, with zeros in the other chunks' rows
+#pragma unroll
+                for (int k = 0; k < CS; ++k) {
+                    const int t = CS * ci + k, m = cs == k ? ~0 : 0;
+                    if (t + RD - 1 < CS * NS) load_rq(bv[(t + RD - 1) % RD], t + RD - 1);
+                    const v4i am = {av[0] & m, av[1] & m, av[2] & m, av[3] & m};
+#pragma unroll
+                    for (int jb = 0; jb < NJB; ++jb)
+                        acc[jb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(am, bv[t % RD][jb], acc[jb], 0, 0, 0);
+                }
+            }
         }
     };
     if constexpr (STREAM) {
@@ -330,16 +363,15 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
             for (int sl = 0; sl < 2; ++sl) {
                 const int ci = ci0 + sl, c = wave + NW * ci;
                 load_rq(bv[(sl + 1) & 1], ci + 1);
-                if (c < C64) code_chunk(xc[sl], c, sl);  // wave-uniform
+                if (c < C64) code_chunk(xc[sl], ci, sl);  // wave-uniform
                 load_x(xc[sl], ci + 2);
             }
         }
     } else {
 #pragma unroll
         for (int ci = 0; ci < NS; ++ci) {
-            const int c = wave + NW * ci;
-            if (ci + 1 < NS) load_rq(bv[(ci + 1) & 1], ci + 1);
-            if (c < C64) code_chunk(xc[ci], c, ci & 1);  // wave-uniform
+            if (CS == 1 && ci + RD - 1 < NS) load_rq(bv[(ci + RD - 1) % RD], ci + RD - 1);
+            if (CS * (wave + NW * ci) < C64) code_chunk(xc[ci], ci, ci % RD);  // wave-uniform
         }
     }
     if (njb == 0) return;
@@ -351,7 +383,10 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
     __syncthreads();
     if (wave >= PW) return;
 
-    // lane holds column j = jb*16 + lane%16 and token rows 4*(lane/16) + i
+    // lane holds column j = jb*16 + lane%16 and token rows 4*(lane/16) + i; with several chunks to a turn, after their sum, rows 4 * (kq & TG - 1) + i,
+    // the same in 64 / (16 TG) lanes
+    constexpr int TG = 4 / CS;
+    const int tok0 = 4 * (kq & (TG - 1));
     float T[NT][4];
     float tmax[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -361,13 +396,20 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
         v4i s = *(const v4i*)&s_acc[0][jb][lane][0];
 #pragma unroll
         for (int w = 1; w < NW; ++w) s += *(const v4i*)&s_acc[w][jb][lane][0];
+        if constexpr (CS > 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (CS > 2) s[i] += __shfl_xor(s[i], 16);
+                s[i] += __shfl_xor(s[i], 32);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int tok = 4 * kq + i;
+            const int tok = tok0 + i;
             const float tv = __fmul_rn(__fmul_rn((float)s[i], s_sxb[tok]), srj[t]);
             T[t][i] = tv;
             tmax[i] = fmaxf(tmax[i], fabsf(tv));
-            const int grow = blockIdx.x * 16 + tok;
+            const int grow = blockIdx.x * RW + tok;
             if (grow < p.M) {
                 if (p.dbg_accT) p.dbg_accT[(size_t)grow * p.r + jb * 16 + r16] = s[i];
                 if (p.dbg_T) p.dbg_T[(size_t)grow * p.r + jb * 16 + r16] = tv;
@@ -394,9 +436,10 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
     scales(r16 & 2 ? (r16 & 1 ? tmax[3] : tmax[2]) : (r16 & 1 ? tmax[1] : tmax[0]), p.qa, &sv, &iv);
     const float st4[4] = {row16_lane<0>(sv), row16_lane<1>(sv), row16_lane<2>(sv), row16_lane<3>(sv)};
     const float inv4t[4] = {row16_lane<0>(iv), row16_lane<1>(iv), row16_lane<2>(iv), row16_lane<3>(iv)};
+    if (kq >= TG) return;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int grow = blockIdx.x * 16 + 4 * kq + i;
+        const int grow = blockIdx.x * RW + tok0 + i;
         const float stv = st4[i], invt = inv4t[i];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -411,35 +454,50 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
     }
 }
 
-template <bool BF16, int MAXC, int NJB, bool SM, bool GA, int NW>
+template <bool BF16, int MAXC, int NJB, bool SM, bool GA, int NW, int CS>
 static hipError_t launch_one(const ActParams& p, int64_t Mp, hipStream_t s)
 {
-    hipLaunchKernelGGL((act_int_kernel<BF16, MAXC, NJB, SM, GA, NW>), dim3((unsigned)(Mp / 16)), dim3(NW * 64), 0, s, p);
+    hipLaunchKernelGGL((act_int_kernel<BF16, MAXC, NJB, SM, GA, NW, CS>), dim3((unsigned)(Mp / 16 * CS)), dim3(NW * 64), 0, s, p);
     return hipGetLastError();
 }
 
-template <bool BF16, int MAXC, bool SM, bool GA, int NW>
+template <bool BF16, int MAXC, bool SM, bool GA, int NW, int CS>
 static hipError_t launch_rank2(const ActParams& p, int64_t Mp, hipStream_t s)
 {
     switch (p.r) {
-        case 0: return launch_one<BF16, MAXC, 0, SM, GA, NW>(p, Mp, s);
-        case 16: return launch_one<BF16, MAXC, 1, SM, GA, NW>(p, Mp, s);
-        case 32: return launch_one<BF16, MAXC, 2, SM, GA, NW>(p, Mp, s);
-        case 64: return launch_one<BF16, MAXC, 4, SM, GA, NW>(p, Mp, s);
-        case 96: return launch_one<BF16, MAXC, 6, SM, GA, NW>(p, Mp, s);
-        default: return launch_one<BF16, MAXC, 8, SM, GA, NW>(p, Mp, s);
+        case 0: return launch_one<BF16, MAXC, 0, SM, GA, NW, CS>(p, Mp, s);
+        case 16: return launch_one<BF16, MAXC, 1, SM, GA, NW, CS>(p, Mp, s);
+        case 32: return launch_one<BF16, MAXC, 2, SM, GA, NW, CS>(p, Mp, s);
+        case 64: return launch_one<BF16, MAXC, 4, SM, GA, NW, CS>(p, Mp, s);
+        case 96: return launch_one<BF16, MAXC, 6, SM, GA, NW, CS>(p, Mp, s);
+        default: return launch_one<BF16, MAXC, 8, SM, GA, NW, CS>(p, Mp, s);
     }
 }
 
-template <bool BF16, int MAXC, bool SM, int NW>
+template <bool BF16, int MAXC, bool SM, int NW, int CS = 1>
 static hipError_t launch_rank(const ActParams& p, int64_t Mp, hipStream_t s)
 {
-    return p.sxg ? launch_rank2<BF16, MAXC, SM, true, NW>(p, Mp, s) : launch_rank2<BF16, MAXC, SM, false, NW>(p, Mp, s);
+    return p.sxg ? launch_rank2<BF16, MAXC, SM, true, NW, CS>(p, Mp, s) : launch_rank2<BF16, MAXC, SM, false, NW, CS>(p, Mp, s);
 }
 
 template <bool BF16, bool SM>
 static hipError_t launch_len(const ActParams& p, int64_t Mp, hipStream_t s)
 {
+    // Four or eight rows to a workgroup while that leaves every workgroup a compute unit of its own: coding 16 rows, 136 instructions per chunk and
+    // wavefront, was the time of a small batch (us, 16 rows / this: 2 x 1152 rank 16 3.8 / 3.4, 300 x 1152 rank 32 4.9 / 4.3, 64 x 4608 rank 32 10.4 /
+    // 6.1, 71 x 4544 rank 128 13.2 / 9.8, SINT4 64 x 2240 rank 64 8.7 / 6.1, fp32 500 x 2240 rank 64 8.9 / 6.4; eight rows 2000 x 1152 rank 32 5.2 / 4.8,
+    // 2000 x 4608 rank 32 11.7 / 9.0, 2048 x 3072 rank 96 10.8 / 8.7).  Not for rows of at most a chunk per wavefront (700 x 320 rank 32 3.8 / 4.0, 1500 x 320 rank
+    // 128 5.2 / 5.6, 12 x 512 3.7 / 3.8), from rank 96 on two, where the few wavefronts with chunks wait for R (12 x 640 rank 128 5.1 / 5.5, 1500 x 768 5.9 / 6.0, 1500 x
+    // 1024 6.3 / 6.3, but 300 x 1152 6.3 / 5.9).
+    const bool few_rows = p.C64 > (p.r >= 96 ? 16 : 8);
+    if (few_rows && Mp <= 4 * compute_units()) {
+        if (p.C64 <= 32) return launch_rank<BF16, 1, SM, 8, 4>(p, Mp, s);
+        if (p.C64 <= 96) return launch_rank<BF16, 3, SM, 8, 4>(p, Mp, s);
+    }
+    if (few_rows && Mp <= 8 * compute_units()) {
+        if (p.C64 <= 48) return launch_rank<BF16, 3, SM, 8, 2>(p, Mp, s);
+        if (p.C64 <= 80) return launch_rank<BF16, 5, SM, 8, 2>(p, Mp, s);
+    }
     // Eight wavefronts to a workgroup while there is at most one workgroup per compute unit: the time is then one
     // workgroup's chain (64 x 4608: 12.8 -> 10.8 us, SINT4 64 x 2240: 11.1 -> 9.1, 4096 x 4608: 18.7 -> 16.6); with more
     // workgroups four are as fast or faster (8192 x 4608: 27.3 against 29.6, 16384 x 1152: 15.7 against 17.3).

@@ -401,7 +401,7 @@ def test_forward_forms_bit_exact(oracle, M, K, N, r, g, ag):
     assert torch.equal(run_gpu(layer, X, W, L, R, debug=True, debug_acc=False).Y, out_gpu.Y)
 
 
-# Activation step: eight wavefronts to a workgroup up to 4096 rows, four above; row lengths at the edges of the register forms (3, 5, 9 chunks
+# Activation step: eight wavefronts to a workgroup up to 4096 rows (of few rows each up to 2048: the next test), four above; row lengths at the edges of the register forms (3, 5, 9 chunks
 # per wavefront of eight, smoothed fp32 rows of 6 streamed; 5, 9, 18 of four; fp32 rows 9) and on the streamed form; every rank, fp32 input, SINT4 blocks, smoothing.
 @pytest.mark.parametrize("M,K,r,xd,ag,sm", [
     (50, 64, 16, "bf16", 0, False), (33, 1536, 16, "bf16", 0, False), (40, 1600, 96, "bf16", 64, False), (47, 2560, 128, "f32", 0, False),
@@ -426,6 +426,19 @@ def test_activation_forms_bit_exact(oracle, M, K, r, xd, ag, sm):
     if r:
         assert np.array_equal(n(av.tq)[rows], act.tq) and np.array_equal(n(av.st)[rows], act.st)
     assert np.array_equal(bf16_to_bits(g.Y)[rows], out.Y)
+
+
+# Activation step, rows per workgroup: four up to 1024 rows, eight up to 2048 (rows of more than eight chunks of 64, sixteen from rank 96 on), sixteen above; row counts at those
+# edges and row lengths at the edges of the register forms (1 and 3 turns of 32 chunks, 3 and 5 turns of 16, 3, 5 and 9 chunks of eight wavefronts), and streamed.
+@pytest.mark.parametrize("M,K,r,xd,ag,sm", [
+    (1, 576, 16, "bf16", 0, False), (3, 2048, 128, "f32", 0, True), (5, 2112, 96, "bf16", 64, True), (1024, 1088, 128, "bf16", 64, False), (1000, 1024, 96, "bf16", 0, False), (37, 6144, 64, "f32", 0, False),
+    (70, 5632, 128, "f32", 64, True), (1023, 1152, 0, "bf16", 0, True), (1025, 576, 64, "f32", 64, False), (1030, 3072, 128, "bf16", 0, False), (2048, 3136, 32, "bf16", 64, True),
+    (1100, 5120, 128, "f32", 0, True), (2047, 1088, 0, "f32", 0, False), (2048, 512, 64, "bf16", 0, False), (2049, 1536, 64, "f32", 64, True), (2050, 1600, 128, "bf16", 64, True),
+    (2055, 2560, 96, "f32", 0, False), (2060, 4608, 128, "bf16", 64, False), (2065, 2688, 32, "f32", 0, True), (2052, 3136, 64, "f32", 64, True),
+    (9, 6208, 32, "f32", 0, False), (21, 6208, 128, "bf16", 0, True), (1040, 5184, 64, "bf16", 64, False), (1060, 5184, 96, "f32", 0, True),
+])
+def test_rows_per_workgroup_of_the_activation_step(oracle, M, K, r, xd, ag, sm):
+    test_activation_forms_bit_exact(oracle, M, K, r, xd, ag, sm)
 
 
 # Residual of the pack step: runs of one and of several scale groups, every depth of the rank ring, factors as given and quantised.
