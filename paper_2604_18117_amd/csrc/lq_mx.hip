@@ -12,8 +12,8 @@
 //
 // Block scale exponent = (exponent field of the block amax) - 2, i.e. floor(log2 amax) - 2; elements
 // are converted by v_cvt_scalef32_pk_fp4_f32 (nearest even, saturating at +-6) and
-// v_cvt_pk_fp8_f32 (nearest even; inputs are clamped to +-448 first because the instruction
-// returns NaN, not 448, above 464).
+// v_cvt_pk_fp8_f32 or its scaled form (nearest even; they return NaN, not 448, above 464: inputs are
+// clamped to +-448 first where they can lie there, but for X of the FP8 branch, see mx_act_kernel).
 #include <type_traits>
 
 #include "lq_pack.h"
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 
         else
             ch.load(p.X, xrow + (size_t)c * 64, true);
     };
-    auto keep_of = [&](int ci) { return wave + NW * ci < p.C64s ? rowmask : 0u; };  // (rows past M and chunks past the row: zeros)
+    auto keep_of = [&](int ci, uint32_t m) { return wave + NW * ci < p.C64s ? m : 0u; };  // (rows past M and chunks past the row: zeros)
 #pragma unroll
     for (int ci = 0; ci < NS; ++ci) load_x(xc[ci], ci);
 
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 
     // amax of the lane's 16 values per chunk (kept for the block scale when the row is resident) and of the whole row
     float a16[NS];
     float a = 0.f;
-    auto amax_chunk = [&](const MxChunk<BF16>& ch, int ci) { return __uint_as_float(__float_as_uint(mx_amax16(ch)) & keep_of(ci)); };
+    auto amax_chunk = [&](const MxChunk<BF16>& ch, int ci) { return __uint_as_float(__float_as_uint(mx_amax16(ch)) & keep_of(ci, rowmask)); };
     if constexpr (STREAM) {
         for (int ci0 = 0; ci0 < nmy; ci0 += 2) {
 #pragma unroll
@@ -604,7 +604,14 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < NW; ++w) a = fmaxf(a, s_amax[w][r16]);
-    const float invb = a == 0.0f ? 1.0f : 448.0f / a;
+    // Codes of the branch are fl(x * 448 / a) through the scaled converter with scale 1: at most 448 (1 + 2^-23) in magnitude, which its rounding saturates.  Below
+    // 448 / FLT_MAX the factor is not finite and every value but zero saturates: 2^127 and a scale of 2^-40 take the smallest number past the range, where the
+    // converter returns NaN (0x7F and the sign), which is 448 without its last bit.
+    float invb = a == 0.0f ? 1.0f : 448.0f / a;
+    const bool tiny = invb > 3.402823466e38f;
+    const float cscale = tiny ? 0x1p-40f : 1.0f;
+    const uint32_t codemask = tiny ? rowmask & 0xFEFEFEFEu : rowmask;
+    invb = tiny ? 0x1p127f : invb;
     if (wave == NW - 1 && kq == 0) {  // (the scale itself: by the wavefront with the fewest chunks)
         const float sb = a == 0.0f ? 1.0f : a / 448.0f;
         s_sxb[r16] = sb;
@@ -628,9 +635,12 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 
         mxfp4_codes16(ch, e8m0_value(E), pk);
         uint32_t x8[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {  // (at most 448 (1 + 2^-23) in magnitude: the converter's rounding saturates it)
-            const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(__fmul_rn(ch.get(4 * q), invb), __fmul_rn(ch.get(4 * q + 1), invb), 0, false);
-            x8[q] = keep & (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(__fmul_rn(ch.get(4 * q + 2), invb), __fmul_rn(ch.get(4 * q + 3), invb), lo, true);
+        for (int q = 0; q < 4; ++q) {
+            typedef short v2s __attribute__((ext_vector_type(2)));
+            v2s c2 = {0, 0};
+            c2 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(c2, __fmul_rn(ch.get(4 * q), invb), __fmul_rn(ch.get(4 * q + 1), invb), cscale, false);
+            c2 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(c2, __fmul_rn(ch.get(4 * q + 2), invb), __fmul_rn(ch.get(4 * q + 3), invb), cscale, true);
+            x8[q] = keep & __builtin_bit_cast(uint32_t, c2);
         }
         uint8_t* dst = p.xc + ((size_t)((size_t)(row >> 5) * C64 + c) * 64 + (row & 31) + 32 * (kq >> 1)) * 16 + (kq & 1) * 8;
         *(uint2*)dst = make_uint2(pk[0] & nz, pk[1] & nz);
@@ -664,7 +674,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 
                 const int ci = ci0 + decltype(sl)::value, c = wave + NW * ci;
                 load_r8(bvs[(decltype(sl)::value + 1) & 1], ci + 1);
                 MxChunk<BF16>& x = xc[decltype(sl)::value];
-                if (c < C64) code_chunk(x, c, keep_of(ci), amax_chunk(x, ci), sl);  // wave-uniform
+                if (c < C64) code_chunk(x, c, keep_of(ci, codemask), amax_chunk(x, ci), sl);  // wave-uniform
                 load_x(x, ci + 2);
             });
         }
@@ -677,7 +687,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 
                 const int ci = ci0 + par, c = wave + NW * ci;
                 if (ci >= NS) return;
                 if (ci + 1 < NS) load_r8(bvs[par ^ 1], ci + 1);
-                if (c < C64) code_chunk(xc[ci], c, keep_of(ci), a16[ci], sl);  // wave-uniform
+                if (c < C64) code_chunk(xc[ci], c, keep_of(ci, codemask), a16[ci], sl);  // wave-uniform
                 else pad_chunk(c);
             });
         }

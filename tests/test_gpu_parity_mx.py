@@ -30,8 +30,9 @@ def _run_oracle(oracle, layer, X, W, L, R):
     return pk, act
 
 
-def _compare(oracle, layer, X, W, L, R, rows=None, gamma=None):
-    """rows: None = compare everything, else the sampled token rows (oracle sees only those)."""
+def _compare(oracle, layer, X, W, L, R, rows=None, gamma=None, branch_terms=False):
+    """rows: None = compare everything, else the sampled token rows (oracle sees only those).  branch_terms: the bound on y counts
+    the magnitudes of the branch's terms as it counts the main product's, for rows whose main codes are all zero (else they cover the branch's)."""
     g = run_gpu(layer, X, W, L, R, debug=True, debug_acc=False, gamma=gamma)
     Xo = X if rows is None else X[rows]
     if gamma is not None:                       # fused smoothing: the oracle quantises the smoothed input
@@ -86,6 +87,8 @@ def _compare(oracle, layer, X, W, L, R, rows=None, gamma=None):
     Xd = np.abs(E2M1[act.xc].astype(np.float64).reshape(Xo.shape[0], -1, 32)) * oracle.e8m0_decode(act.xe)[:, :, None]
     Wd = np.abs(E2M1[pk.pc].astype(np.float64).reshape(layer.N, -1, 32)) * oracle.e8m0_decode(pk.pe)[:, :, None]
     A = Xd.reshape(Xo.shape[0], -1) @ Wd.reshape(layer.N, -1).T          # sum of |terms| of the main product
+    if branch_terms:
+        A += (np.abs(f8[tq_gpu].astype(np.float64)) * st_gpu[:, None]) @ (np.abs(f8[pk.l8].astype(np.float64)) * pk.sl[:, None]).T
     bound = 2.0 ** -15 * (A + np.abs(out.ybr)) + 1e-30
     assert np.all(np.abs(y_gpu - out.y32) <= bound), f"y32 max excess {np.max(np.abs(y_gpu - out.y32) / bound)}"
     Yb = bf16_to_bits(g.Y)[sel]
@@ -227,6 +230,45 @@ def test_forms_of_the_activation_step(oracle, K, r, xd, smooth):
         assert np.array_equal(E2M1[xq[:37]], E2M1[want.xc]) and np.array_equal(n(v.xe)[:37], want.xe), M
         assert not xq[2].any() and not xq[3, 32:64].any()
         got = [t.cpu() for t in ((v.xq, v.xe, v.tq, v.st) if r else (v.xq, v.xe))]
+        first = first or got
+        for a, b in zip(got, first):               # the same bits in every form and row
+            assert torch.equal(a, b.repeat(((M + 36) // 37,) + (1,) * (b.dim() - 1))[:M]), M
+
+
+# Rows whose largest magnitude is about 448 / FLT_MAX = 1.32e-36 or less: 448 / amax is not finite there, every value but zero saturates.  The forms are
+# those of the test above; ordinary rows, one with every magnitude and rows with zeros stand in the same groups of 16.  R is scaled up so that T and Y are normal numbers.
+@pytest.mark.parametrize("K,r,xd,smooth", [(192, 64, "bf16", False), (1152, 128, "bf16", False), (1600, 16, "bf16", False), (2112, 64, "bf16", False),
+                                           (4544, 32, "bf16", False), (4608, 64, "bf16", False), (4672, 16, "bf16", False), (1152, 32, "f32", False),
+                                           (2560, 64, "f32", False), (4672, 128, "f32", False), (2368, 128, "bf16", True), (640, 16, "f32", True)])
+def test_rows_of_very_small_values(oracle, K, r, xd, smooth):
+    from paper_2604_18117_amd import binding as lq
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    layer = wl.Layer("t", 37, K, 64, r, "mx", 32, 8, 8, xd, seed=K + r)
+    X, W, L, R = wl.make_inputs(layer)
+    edge = np.float32(448.0) / np.finfo(np.float32).max
+    small = [1e-35, 2e-36, 1.4e-36, np.nextafter(edge, np.float32(1)), edge, np.nextafter(edge, np.float32(0)), 1.3e-36, 1e-36, 1e-37, 1.2e-38,
+             1e-38, 1e-39, 1e-40, 2.0 ** -133]
+    for i, a in enumerate(small):
+        X[i + 1] *= np.float32(2.0 ** -60) / np.abs(X[i + 1]).max()          # (in two steps: the quotient is below the normal numbers)
+        X[i + 1] = np.clip(X[i + 1] * np.float32(np.float64(a) * 2.0 ** 60), -a, a)
+        X[i + 1, i] = a
+    X[17], X[18] = X[8], X[9]                                                 # zeros beside 1e-36, 1e-37 and a subnormal
+    X[17, 1::3], X[18, 32:64], X[18, 64::2] = 0.0, -0.0, 0.0
+    X[19] = 0.0
+    X[19, 5], X[19, K - 1] = 1e-37, -2.0 ** -133
+    X[20] = np.where(np.arange(K) % 2, 1e-36, -1e-36)
+    if xd == "bf16":
+        X = wl.round_to_bf16(X)
+    R, W = R * np.float32(2.0 ** 115), W * np.float32(2.0 ** 115)
+    gamma = np.exp2(np.random.default_rng(K).integers(-3, 4, K)).astype(np.float32) if smooth else None
+    g = _compare(oracle, layer, X, W, L, R, gamma=gamma, branch_terms=True)
+    assert bool(torch.isfinite(g.Y).all())
+    Xd = wl.to_dev_x(X, xd)
+    first = None
+    for M in (37, 16 * cus - 3, 16 * cus + 5):
+        big = Xd.repeat((M + 36) // 37, 1)[:M].contiguous()
+        v = lq.lq_unpack_act(g.cfg, lq.lq_quantize_act(g.cfg, g.packed, big), M)
+        got = [t.cpu() for t in (v.xq, v.xe, v.tq, v.st)]
         first = first or got
         for a, b in zip(got, first):               # the same bits in every form and row
             assert torch.equal(a, b.repeat(((M + 36) // 37,) + (1,) * (b.dim() - 1))[:M]), M
