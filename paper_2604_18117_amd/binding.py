@@ -6,12 +6,14 @@ has not been built (``python paper_2604_18117_amd/build.py``); there is no CPU f
 
 The entry points of a program's loops (activation step, forward, hand-off, packing, calibration and rotation steps) hand their arguments to the
 native module ``_call`` (csrc/lq_call.cpp) as they are; it makes the call where they are of the ordinary kind (status >= 0) and does
-nothing otherwise (-1).  The checks and the ctypes call below each of them then decide, as for every other entry point.
+nothing otherwise (-1).  The checks and the ctypes call below each of them then decide, as for every other entry point.  ``_call`` belongs to
+one build of torch; where it cannot be loaded a warning says so and every call takes the ctypes route, which needs liblq.so alone.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -22,9 +24,20 @@ _LIB_PATH = os.path.join(_HERE, "liblq.so")
 if not os.path.exists(_LIB_PATH):
     raise ImportError(f"{_LIB_PATH} is missing: build it with `python paper_2604_18117_amd/build.py`")
 _lib = C.CDLL(_LIB_PATH)
-if not os.path.exists(os.path.join(_HERE, "_call.so")):
-    raise ImportError(f"{_HERE}/_call.so is missing: build it with `python paper_2604_18117_amd/build.py`")
-from . import _call  # noqa: E402  (it links liblq.so)
+
+
+class _CtypesOnly:
+    """In the place of ``_call`` where it cannot be loaded: makes no call."""
+
+    def __getattr__(self, name):
+        return lambda *args: -1
+
+
+try:
+    from . import _call  # (it links liblq.so and torch's libraries)
+except ImportError as e:
+    warnings.warn(f"_call.so cannot be loaded, calls take the slower ctypes route; build it with `python paper_2604_18117_amd/build.py` ({e})", RuntimeWarning)
+    _call = _CtypesOnly()
 
 LQ_OK = 0
 LQ_ERR_NULL, LQ_ERR_SHAPE, LQ_ERR_UNSUPPORTED, LQ_ERR_ALIGN, LQ_ERR_BUFFER_TOO_SMALL, LQ_ERR_DEVICE, LQ_ERR_STALE_BLOB = range(1, 8)

@@ -1,6 +1,9 @@
 """The native half of the binding (`_call`): it makes the ordinary call and leaves everything else to the ctypes path, with the same results
 and the same errors."""
 import ctypes as C
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -24,6 +27,36 @@ def test_arguments_that_are_not_ordinary_are_left_alone():
     assert not C.pythonapi.PyErr_Occurred()
     with pytest.raises(AssertionError):                                       # ... whose checks raise what they always did
         lq.lq_quantize_act(cfg, cpu, cpu, act=cpu)
+
+
+@pytest.mark.parametrize("call_so", ["absent", "of another build"])
+def test_the_binding_needs_the_library_alone(tmp_path, call_so):
+    """Without a `_call.so` that loads, the binding imports, says so, and works through ctypes with the same checks."""
+    pkg = os.path.dirname(os.path.abspath(lq.__file__))
+    copy = tmp_path / os.path.basename(pkg)
+    copy.mkdir()
+    for name in ("__init__.py", "binding.py", "liblq.so"):
+        os.symlink(os.path.join(pkg, name), copy / name)
+    if call_so != "absent":
+        (copy / "_call.so").write_bytes(b"no module")
+    p = subprocess.run([sys.executable, "-c", f"""
+import warnings, torch
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    from {copy.name} import binding as lq
+assert any("_call.so" in str(w.message) for w in seen), seen
+assert lq.__file__.startswith({str(tmp_path)!r}) and lq._call.quantize_act() == -1
+cfg = lq.make_config(128, 128, 16)
+assert lq.lq_packed_sizes(cfg) > 0
+x = torch.zeros(4, 128)
+for call in ((lambda: lq.lq_quantize_act(cfg, x, x, act=x)), (lambda: lq.lq_pack_weights(cfg, x, x, x, packed=x)), (lambda: lq.lq_calib_step(cfg, x, x, 1))):
+    try:
+        call()
+    except AssertionError:
+        continue
+    raise SystemExit("a call with CPU tensors was accepted")
+"""], cwd=tmp_path, capture_output=True, text=True)
+    assert p.returncode == 0, p.stderr
 
 
 def _work(monkeypatch, native):
