@@ -250,8 +250,13 @@ def lq_quantize_act(cfg: lq_config, packed: torch.Tensor, X: torch.Tensor, act: 
                     debug: bool = False):
     """X: M x K CUDA tensor (fp32 or bf16, row stride may exceed K).  Returns the activation blob
     (and the parity taps when debug=True)."""
-    if not debug and _call.quantize_act(cfg, packed, X, act) == LQ_OK:
-        return act
+    if not debug:
+        st = _call.quantize_act(cfg, packed, X, act)
+        if st == LQ_OK:
+            return act
+        if st > 0:
+            assert packed.numel() >= lq_packed_sizes(cfg)  # the library's own size check, as an assertion
+            _check(st, "lq_quantize_act")
     assert X.is_cuda and X.dim() == 2 and X.stride(1) == 1 and X.shape[1] == cfg.K
     assert X.dtype == (torch.bfloat16 if cfg.x_dtype == LQ_BF16 else torch.float32)
     M = X.shape[0]

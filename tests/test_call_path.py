@@ -59,6 +59,31 @@ for call in ((lambda: lq.lq_quantize_act(cfg, x, x, act=x)), (lambda: lq.lq_pack
     assert p.returncode == 0, p.stderr
 
 
+@pytest.mark.parametrize("status", [lq.LQ_OK, lq.LQ_ERR_DEVICE, lq.LQ_ERR_BUFFER_TOO_SMALL])
+def test_a_call_is_submitted_once(monkeypatch, status):
+    """What the native half reports is the call's outcome: a step whose launch failed is not launched again by the other route."""
+    cfg = lq.make_config(128, 128, 16)
+    x, packed = torch.zeros(4, 128, dtype=torch.bfloat16), torch.zeros(lq.lq_packed_sizes(cfg), dtype=torch.uint8)
+    state = torch.zeros(16)
+    calls = {"quantize_act": lambda: lq.lq_quantize_act(cfg, packed, x, act=packed), "pack_weights": lambda: lq.lq_pack_weights(cfg, x, x, x, packed=packed),
+             "linear_lowrank_fwd": lambda: lq.lq_linear_lowrank_fwd(cfg, packed, packed, 4, Y=x),
+             "linear_lowrank_fwd_handoff": lambda: lq.lq_linear_lowrank_fwd_handoff(cfg, packed, packed, 4, cfg, packed, packed),
+             "branch_from_codes": lambda: lq.lq_branch_from_codes(cfg, packed, packed, 4, packed), "calib_step": lambda: lq.lq_calib_step(cfg, x, state, 1),
+             "rot_step": lambda: lq.lq_rot_step(cfg, x, x, state)}
+    assert set(calls) == set(FAST)
+    for name, call in calls.items():
+        made = []
+        monkeypatch.setattr(lq._call, name, lambda *a: made.append("native") or status)
+        monkeypatch.setattr(lq._lib, "lq_" + name, lambda *a: made.append("ctypes") or lq.LQ_OK)
+        if status == lq.LQ_OK:
+            call()
+        else:
+            with pytest.raises(lq.LqError) as e:
+                call()
+            assert e.value.status == status
+        assert made == ["native"], name
+
+
 def _work(monkeypatch, native):
     """One pass of every entry point on seeded inputs; native: whether `_call` has to make the calls (or none of them)."""
     made = []
