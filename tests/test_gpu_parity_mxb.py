@@ -202,6 +202,31 @@ def test_packed_codes_over_the_whole_range_of_factor_scales(oracle, r, first, el
         assert np.array_equal(val[n(getattr(got, name)).view(np.uint8)], val[want]), name
 
 
+# Blocks of X at both ends of the scale bytes, in each form of the activation step's kernel.  Low: byte 0 (a subnormal 2^-127 as the converters' operand), with subnormal values, largest
+# magnitudes on both sides of where each format leaves byte 0, saturating values, and blocks of the smallest numbers; high: up to byte 246 (254 less the 8 of E4M3's
+# largest exponent; 252 with E2M3 and for the main codes).  The factors are scaled the other way so that T and Y are normal numbers.
+@pytest.mark.parametrize("elem", [8, 6])
+@pytest.mark.parametrize("end", ["low", "high"])
+@pytest.mark.parametrize("M,K,r,xd,smooth", [(40, 1152, 32, "bf16", False), (70, 1088, 128, "bf16", False), (4100, 192, 32, "bf16", False), (40, 1152, 64, "f32", False),
+                                             (40, 1152, 64, "bf16", True)])
+def test_codes_of_x_at_the_ends_of_its_range(oracle, M, K, r, xd, smooth, end, elem):
+    layer = wl.Layer("t", M, K, 64, r, "mxb", 32, elem, elem, xd, seed=M + K)
+    X, W, L, R = wl.make_inputs(layer)
+    rng = np.random.default_rng(elem + K)
+    blocks = X.reshape(M, K // 32, 32)
+    blocks /= np.abs(blocks).max(axis=2, keepdims=True)                  # largest magnitude 1
+    low = [-133, -130, -127, -126, -125, -124, -123, -121, -120, -119, -118, -117]
+    e = rng.choice(low if end == "low" else [127, 126, 125, 120, 119], size=(M, K // 32, 1))
+    top = rng.choice([1.0, 1.5, 1.75, 1.9375, 1.9921875], size=e.shape)  # (the last two saturate in both formats)
+    blocks[:] = (blocks * top * np.exp2(e.astype(np.float64))).astype(np.float32)
+    if xd == "bf16":
+        X = wl.round_to_bf16(X)
+    f = np.float32(2.0 ** (100 if end == "low" else -110))
+    gamma = np.exp2(rng.integers(0, 4, K) * (-1 if end == "low" else 1)).astype(np.float32) if smooth else None
+    rows = None if M < 100 else np.unique(np.concatenate([np.arange(40), np.arange(M - 20, M)]))
+    _compare(oracle, layer, X, W * f, L, R * f, rows=rows, gamma=gamma)
+
+
 @pytest.mark.parametrize("name", ["c5b_qkv", "c5b_fc2", "c5b6_qkv", "c5b6_fc2", "c4m_qkv"])
 def test_full_size_sampled_rows(oracle, name):
     layer = wl.LAYERS[name]
@@ -212,12 +237,12 @@ def test_full_size_sampled_rows(oracle, name):
 
 
 # Every form of the activation step (4 or 8 wavefronts, one workgroup per 32 columns of the rank) and every length of a wavefront's run of
-# 128-chunks around its unrolled pairs: 3 chunks (a padding one among them) to 41, rows that end inside a group of 16.  Form 4 past a
-# group per compute unit is compared on its first rows.
+# 128-chunks around its unrolled pairs: 3 chunks (a padding one among them) to 41, rows that end inside a group of 16, smoothed or not.
 @pytest.mark.parametrize("elem", [8, 6])
-@pytest.mark.parametrize("K,r,xd", [(320, 64, "bf16"), (704, 128, "bf16"), (1088, 32, "bf16"), (2112, 96, "bf16"), (3200, 64, "bf16"), (5184, 32, "bf16"),
-                                    (1600, 128, "f32"), (640, 32, "f32"), (384, 0, "bf16")])
-def test_forms_of_the_activation_step(oracle, K, r, xd, elem):
+@pytest.mark.parametrize("K,r,xd,smooth", [(320, 64, "bf16", False), (704, 128, "bf16", False), (1088, 32, "bf16", False), (2112, 96, "bf16", False), (3200, 64, "bf16", False),
+                                           (5184, 32, "bf16", False), (1600, 128, "f32", False), (640, 32, "f32", False), (384, 0, "bf16", False),
+                                           (1088, 32, "bf16", True), (2112, 96, "bf16", True), (1600, 128, "bf16", True), (3200, 64, "f32", True), (576, 0, "bf16", True)])
+def test_forms_of_the_activation_step(oracle, K, r, xd, smooth, elem):
     from paper_2604_18117_amd import binding as lq
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     layer = wl.Layer("t", 37, K, 64, r, "mxb", 32, elem, elem, xd, seed=K + r)
@@ -225,9 +250,12 @@ def test_forms_of_the_activation_step(oracle, K, r, xd, elem):
     X[2, :] = -0.0                # blocks of zeros have codes 0, also where the zeros are negative
     X[3, 32:64] = -0.0
     X[3, 70] = -0.0               # (in other blocks a zero keeps its sign)
-    _compare(oracle, layer, X, W, L, R)
-    cfg = lq.config_for_layer(layer)
+    gamma = np.exp2(np.random.default_rng(K).integers(-3, 4, K)).astype(np.float32) if smooth else None
+    _compare(oracle, layer, X, W, L, R, gamma=gamma)
+    cfg = lq.config_for_layer(layer, smooth=smooth)
     packed = lq.lq_pack_weights(cfg, *(torch.from_numpy(a).cuda() if r or a is W else None for a in (W, L, R)))
+    if smooth:
+        lq.lq_set_smoothing(cfg, packed, torch.from_numpy(gamma).cuda())
 
     def blob(x, debug):
         act = torch.full((lq.lq_act_sizes(cfg, x.shape[0]),), 0xFF, dtype=torch.uint8, device="cuda")
@@ -246,5 +274,5 @@ def test_forms_of_the_activation_step(oracle, K, r, xd, elem):
     for groups in (cus // 4 + 1, cus // 2 + 1, cus, cus + 1):
         M = 16 * groups - 3
         big = Xd.repeat((M + 36) // 37, 1)[:M].contiguous()
-        for a, b in zip(views(big, blob(big, False)), views(Xd, want)):
-            assert torch.equal(a[:37], b) and torch.equal(a[-(M % 37):] if M % 37 else a[-37:], b[:M % 37] if M % 37 else b), M
+        for a, b in zip(views(big, blob(big, False)), views(Xd, want)):   # every row
+            assert torch.equal(a, b.repeat((M + 36) // 37, 1)[:M]), M
