@@ -240,6 +240,13 @@ static inline int mxb_act_form(int64_t Mp, int C128, int njb, bool fp32_rows)
     return C128 >= 12 || 4 * groups <= cus ? 8 : 4;
 }
 
+// Rows of at most this many 128-chunks have a form of these kernels without a loop, whose wavefronts request the chunks that they have (one or none of
+// eight wavefronts, up to two of four) and nothing else.  The looped form requests two for each, clamped, because a branch around a request ends the
+// compiler's count of those in flight; at K = 128 that is X eight times over (us, looped / this: MXFP8 fp32 12327 x 128 rank 0 9.0 / 3.6, 16384 x 256 rank 0
+// 6.2 / 4.2, fp32 1500 x 640 rank 128 7.9 / 6.6; MXFP6 smoothed fp32 783 x 384 rank 96 7.7 / 4.4, 16384 x 640 rank 64 11.8 / 8.6).  With four wavefronts
+// every one has two chunks past the line; with eight it lies below K = 1152, where branches around the requests of a second chunk took 3 to 12 % longer.
+static constexpr int mxb_act_short(int wavefronts) { return wavefronts == 4 ? 7 : 8; }
+
 // Tile order of the forward kernels: panels of `panel` tile columns (256 channels each), row-major inside a panel; the
 // last panel may be narrower.  The workgroups resident on an XCD at one time then share few weight column blocks: with
 // all tile columns in flight at once, the weight codes of a wide layer (7.5 MB at 2240 x 6720) do not stay in the XCD's

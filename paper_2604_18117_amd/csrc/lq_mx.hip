@@ -874,8 +874,8 @@ struct MxbActParams {
     uint32_t* tag_dst;
 };
 
-// BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32); DBG: parity taps.
-template <bool BF16IN, int NJB, bool SM, int NW, bool DBG>
+// BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32); DBG: parity taps; SHORT: rows of few chunks (mxb_act_short).
+template <bool BF16IN, int NJB, bool SM, int NW, bool DBG, bool SHORT>
 __global__ __launch_bounds__(64 * NW, 2) void mxb_act_kernel(MxbActParams p)
 {
     write_tag(p.tag_dst, p.tag);
@@ -995,24 +995,33 @@ __global__ __launch_bounds__(64 * NW, 2) void mxb_act_kernel(MxbActParams p)
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    load_x(xs[0], 0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_x(xs[1], 1);
-    __builtin_amdgcn_sched_barrier(0);
     constexpr std::integral_constant<int, 0> s0{};
     constexpr std::integral_constant<int, 1> s1{};
-    int ci = 0;
-    for (; ci + 3 < nmy; ci += 2) {
-        step(s0, ci, std::true_type{});
-        step(s1, ci + 1, std::true_type{});
-    }
-    if (ci + 2 < nmy) {
-        step(s0, ci, std::true_type{});
-        step(s1, ci + 1, std::false_type{});
-        step(s0, ci + 2, std::false_type{});
+    if constexpr (SHORT) {
+        if (nmy > 0) {
+            load_x(xs[0], 0);
+            if (NW == 4 && nmy > 1) load_x(xs[1], 1);
+            step(s0, 0, std::false_type{});
+            if (NW == 4 && nmy > 1) step(s1, 1, std::false_type{});
+        }
     } else {
-        if (ci < nmy) step(s0, ci, std::false_type{});
-        if (ci + 1 < nmy) step(s1, ci + 1, std::false_type{});
+        load_x(xs[0], 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_x(xs[1], 1);
+        __builtin_amdgcn_sched_barrier(0);
+        int ci = 0;
+        for (; ci + 3 < nmy; ci += 2) {
+            step(s0, ci, std::true_type{});
+            step(s1, ci + 1, std::true_type{});
+        }
+        if (ci + 2 < nmy) {
+            step(s0, ci, std::true_type{});
+            step(s1, ci + 1, std::false_type{});
+            step(s0, ci + 2, std::false_type{});
+        } else {
+            if (ci < nmy) step(s0, ci, std::false_type{});
+            if (ci + 1 < nmy) step(s1, ci + 1, std::false_type{});
+        }
     }
     {   // padding 64-chunks of the last quad (at most one 128-chunk): valid E8M0 bytes (2^0)
         const int c = wave + NW * nmy;
@@ -1071,16 +1080,24 @@ __global__ __launch_bounds__(64 * NW, 2) void mxb_act_kernel(MxbActParams p)
     }
 }
 
+template <bool BF16, int NJB, bool SM, int NW, bool DBG>
+static hipError_t mxb_act_launch3(const MxbActParams& p, dim3 grid, hipStream_t s)
+{
+    if (!DBG && p.C128 <= mxb_act_short(NW))
+        hipLaunchKernelGGL((mxb_act_kernel<BF16, NJB, SM, NW, false, true>), grid, dim3(64 * NW), 0, s, p);
+    else
+        hipLaunchKernelGGL((mxb_act_kernel<BF16, NJB, SM, NW, DBG, false>), grid, dim3(64 * NW), 0, s, p);
+    return hipGetLastError();
+}
 template <bool BF16, int NJB, bool SM, bool DBG>
 static hipError_t mxb_act_launch2(const MxbActParams& p, int64_t Mp, hipStream_t s)
 {
     const dim3 rows((unsigned)(Mp / 16));
     switch (mxb_act_form(Mp, p.C128, NJB, !BF16 || SM)) {
-        case 4: hipLaunchKernelGGL((mxb_act_kernel<BF16, NJB, SM, 4, DBG>), rows, dim3(256), 0, s, p); break;
-        case 8: hipLaunchKernelGGL((mxb_act_kernel<BF16, NJB, SM, 8, DBG>), rows, dim3(512), 0, s, p); break;
-        default: hipLaunchKernelGGL((mxb_act_kernel<BF16, NJB < 2 ? NJB : 2, SM, 8, DBG>), dim3(rows.x, NJB < 2 ? 1 : NJB / 2), dim3(512), 0, s, p); break;
+        case 4: return mxb_act_launch3<BF16, NJB, SM, 4, DBG>(p, rows, s);
+        case 8: return mxb_act_launch3<BF16, NJB, SM, 8, DBG>(p, rows, s);
+        default: return mxb_act_launch3<BF16, NJB < 2 ? NJB : 2, SM, 8, DBG>(p, dim3(rows.x, NJB < 2 ? 1 : NJB / 2), s);
     }
-    return hipGetLastError();
 }
 template <bool BF16, int NJB, bool SM>
 static hipError_t mxb_act_launch(const MxbActParams& p, int64_t Mp, hipStream_t s)

@@ -289,7 +289,7 @@ __device__ __forceinline__ void mx6_codes(const Mx6Block<false>& x, float sc, ui
 
 // BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32); DBG: parity taps.  The forms, the order of
 // T's sums and the way of the operands are those of mxb_act_kernel.
-template <bool BF16IN, int NJB, bool SM, int NW, bool DBG>
+template <bool BF16IN, int NJB, bool SM, int NW, bool DBG, bool SHORT>
 __global__ __launch_bounds__(64 * NW, 2) void mx6_act_kernel(Mx6ActParams p)
 {
     write_tag(p.tag_dst, p.tag);
@@ -401,24 +401,33 @@ __global__ __launch_bounds__(64 * NW, 2) void mx6_act_kernel(Mx6ActParams p)
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    load_x(xs[0], 0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_x(xs[1], 1);
-    __builtin_amdgcn_sched_barrier(0);
     constexpr std::integral_constant<int, 0> s0{};
     constexpr std::integral_constant<int, 1> s1{};
-    int ci = 0;
-    for (; ci + 3 < nmy; ci += 2) {
-        step(s0, ci, std::true_type{});
-        step(s1, ci + 1, std::true_type{});
-    }
-    if (ci + 2 < nmy) {
-        step(s0, ci, std::true_type{});
-        step(s1, ci + 1, std::false_type{});
-        step(s0, ci + 2, std::false_type{});
+    if constexpr (SHORT) {
+        if (nmy > 0) {
+            load_x(xs[0], 0);
+            if (NW == 4 && nmy > 1) load_x(xs[1], 1);
+            step(s0, 0, std::false_type{});
+            if (NW == 4 && nmy > 1) step(s1, 1, std::false_type{});
+        }
     } else {
-        if (ci < nmy) step(s0, ci, std::false_type{});
-        if (ci + 1 < nmy) step(s1, ci + 1, std::false_type{});
+        load_x(xs[0], 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_x(xs[1], 1);
+        __builtin_amdgcn_sched_barrier(0);
+        int ci = 0;
+        for (; ci + 3 < nmy; ci += 2) {
+            step(s0, ci, std::true_type{});
+            step(s1, ci + 1, std::true_type{});
+        }
+        if (ci + 2 < nmy) {
+            step(s0, ci, std::true_type{});
+            step(s1, ci + 1, std::false_type{});
+            step(s0, ci + 2, std::false_type{});
+        } else {
+            if (ci < nmy) step(s0, ci, std::false_type{});
+            if (ci + 1 < nmy) step(s1, ci + 1, std::false_type{});
+        }
     }
     {   // padding 64-chunks of the last quad (at most one 128-chunk): valid E8M0 bytes (2^0)
         const int c = wave + NW * nmy;
@@ -476,16 +485,24 @@ __global__ __launch_bounds__(64 * NW, 2) void mx6_act_kernel(Mx6ActParams p)
     }
 }
 
+template <bool BF16, int NJB, bool SM, int NW, bool DBG>
+static hipError_t mx6_act_launch3(const Mx6ActParams& p, dim3 grid, hipStream_t s)
+{
+    if (!DBG && p.C128 <= mxb_act_short(NW))
+        hipLaunchKernelGGL((mx6_act_kernel<BF16, NJB, SM, NW, false, true>), grid, dim3(64 * NW), 0, s, p);
+    else
+        hipLaunchKernelGGL((mx6_act_kernel<BF16, NJB, SM, NW, DBG, false>), grid, dim3(64 * NW), 0, s, p);
+    return hipGetLastError();
+}
 template <bool BF16, int NJB, bool SM, bool DBG>
 static hipError_t mx6_act_launch2(const Mx6ActParams& p, int64_t Mp, hipStream_t s)
 {
     const dim3 rows((unsigned)(Mp / 16));
     switch (mxb_act_form(Mp, p.C128, NJB, !BF16 || SM)) {
-        case 4: hipLaunchKernelGGL((mx6_act_kernel<BF16, NJB, SM, 4, DBG>), rows, dim3(256), 0, s, p); break;
-        case 8: hipLaunchKernelGGL((mx6_act_kernel<BF16, NJB, SM, 8, DBG>), rows, dim3(512), 0, s, p); break;
-        default: hipLaunchKernelGGL((mx6_act_kernel<BF16, NJB < 2 ? NJB : 2, SM, 8, DBG>), dim3(rows.x, NJB < 2 ? 1 : NJB / 2), dim3(512), 0, s, p); break;
+        case 4: return mx6_act_launch3<BF16, NJB, SM, 4, DBG>(p, rows, s);
+        case 8: return mx6_act_launch3<BF16, NJB, SM, 8, DBG>(p, rows, s);
+        default: return mx6_act_launch3<BF16, NJB < 2 ? NJB : 2, SM, 8, DBG>(p, dim3(rows.x, NJB < 2 ? 1 : NJB / 2), s);
     }
-    return hipGetLastError();
 }
 template <bool BF16, int NJB, bool SM>
 static hipError_t mx6_act_launch(const Mx6ActParams& p, int64_t Mp, hipStream_t s)

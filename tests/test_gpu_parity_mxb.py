@@ -276,3 +276,27 @@ def test_forms_of_the_activation_step(oracle, K, r, xd, smooth, elem):
         big = Xd.repeat((M + 36) // 37, 1)[:M].contiguous()
         for a, b in zip(views(big, blob(big, False)), views(Xd, want)):   # every row
             assert torch.equal(a, b.repeat((M + 36) // 37, 1)[:M]), M
+
+
+# Rows of few 128-chunks have kernels of their own: lengths on both sides of their lines (7 chunks with four wavefronts, 8 with eight), one chunk to a
+# workgroup, an odd number of 64-chunks.  The kernels with parity taps, which the tests above check against the oracle, are the looped ones at every length: same bytes.
+@pytest.mark.parametrize("elem", [8, 6])
+@pytest.mark.parametrize("r,xd,smooth", [(0, "bf16", False), (32, "f32", True), (64, "bf16", False), (96, "f32", False), (128, "bf16", True)])
+def test_short_rows(r, xd, smooth, elem):
+    from paper_2604_18117_amd import binding as lq
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for K in (64, 128, 192, 512, 640, 832, 896, 960, 1024, 1088):
+        layer = wl.Layer("t", 37, K, 64, r, "mxb", 32, elem, elem, xd, seed=K + r)
+        X, W, L, R = wl.make_inputs(layer)
+        X[2, :] = -0.0
+        cfg = lq.config_for_layer(layer, smooth=smooth)
+        packed = lq.lq_pack_weights(cfg, *(torch.from_numpy(a).cuda() if r or a is W else None for a in (W, L, R)))
+        if smooth:
+            lq.lq_set_smoothing(cfg, packed, torch.from_numpy(np.random.default_rng(K).uniform(0.5, 2, K).astype(np.float32)).cuda())
+        Xd = wl.to_dev_x(X, xd)
+        for M in (37, 16 * (cus // 2) + 5, 16 * cus + 5):                 # eight wavefronts, a workgroup per 32 columns of the rank, four
+            big = Xd.repeat((M + 36) // 37, 1)[:M].contiguous()
+            act, tap = [torch.full((lq.lq_act_sizes(cfg, M),), 0xFF, dtype=torch.uint8, device="cuda") for _ in range(2)]
+            lq.lq_quantize_act(cfg, packed, big, act=act)
+            lq.lq_quantize_act(cfg, packed, big, act=tap, debug=True)
+            assert torch.equal(act, tap), (K, M)
