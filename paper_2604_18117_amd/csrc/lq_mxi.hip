@@ -426,7 +426,7 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)  // upper halv
 // FROMC: the branch half of the step alone, from the MXINT8 codes of a quantized hand-off (the producing layer's
 // epilogue has already written this layer's main codes and scales): 16 code bytes and a scale byte replace the 16 values
 // of X, code * 2^(s-6) is the dequantised bf16 element; the contraction and the re-quantisation are the same code.
-template <bool BF16IN, int NJB, bool SM, bool FROMC, int RPW, int ROWG, bool DBG>
+template <bool BF16IN, int NJB, bool SM, bool FROMC, int RPW, int ROWG, bool DBG, bool SPLIT>
 __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
 {
     write_tag(p.tag_dst, p.tag);
@@ -449,10 +449,11 @@ __global__ __launch_bounds__(ROWG * 256, 2) void mxi_act_kernel(MxiActParams p)
     const int C64 = p.C64;
     const int Mp = p.Mp;
     const int nss = (C64 + KW - 1) / KW;
-    // Small batches: a workgroup per 16 rows and 32 columns of the rank (grid.y); the first stores the main codes.  Every block of the intermediate
-    // is 32 columns, and no sum runs across them.
-    const int jb0 = STAGE ? 0 : (int)blockIdx.y * NJB, rchunk = STAGE ? RCHUNK : p.r * 128;  // bytes of all of R per 64-chunk
-    const bool first = STAGE || blockIdx.y == 0;
+    // SPLIT (small batches): a workgroup per 16 rows and 32 columns of the rank (grid.y); the first stores the main codes.  Every block of the intermediate
+    // is 32 columns, and no sum runs across them.  (A flag of the kernel's: decided at run time, the forms without it were up to 6 % slower, smoothed fp32 rows above all.)
+    if (SPLIT && row0 >= Mp) return;  // (grid.x is rounded up)
+    const int jb0 = SPLIT ? (int)blockIdx.y * NJB : 0, rchunk = SPLIT ? p.r * 128 : RCHUNK;  // bytes of all of R per 64-chunk
+    const bool first = !SPLIT || blockIdx.y == 0;
 
     // Rows past M count as zeros, chunks past the end are clamped and not used: the loads are unconditional (the wait
     // below counts them).  Groups past Mp (the last workgroup) are not stored.
@@ -768,17 +769,24 @@ template <bool BF16, int NJB, bool SM, bool FROMC, bool DBG>
 static hipError_t mxi_act_launch2(const MxiActParams& p, hipStream_t s)
 {
     switch (mxi_act_rows(p.r, p.K, p.Mp, FROMC)) {
-        case 64: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 2, 2, DBG>), dim3((unsigned)((p.Mp + 63) / 64)), dim3(512), 0, s, p); break;
-        case 32: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 2, DBG>), dim3((unsigned)(p.Mp / 32)), dim3(512), 0, s, p); break;
+        case 64: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 2, 2, DBG, false>), dim3((unsigned)((p.Mp + 63) / 64)), dim3(512), 0, s, p); break;
+        case 32: hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 2, DBG, false>), dim3((unsigned)(p.Mp / 32)), dim3(512), 0, s, p); break;
         default: {
             // A workgroup per 32 columns of the rank while compute units are left over for them: R passes through a compute unit each (us, one / this:
             // 300 x 1152 rank 128 7.1 / 5.1, 64 x 4608 rank 128 18.9 / 10.6, rank 64 12.9 / 12.3, 300 x 2240 fp32 rank 96 11.8 / 8.3, 2000 x 1152 rank 64
             // 7.3 / 6.3; with two workgroups to a compute unit 2000 x 1152 rank 128 8.7 / 8.1, 3000 x 2240 rank 64 11.4 / 12.0, 3000 x 512 4.5 / 5.3).
+            // Whole eights of row groups, so that the workgroups of a group are on one of the 8 XCDs and X is read from memory once (smoothed 600 x 6144 rank 64
+            // 24.8 us without, 20.8 unsplit, 18.6 so; 1500 x 4608 rank 64 13.7, 13.2, 11.8; 783 x 4608 rank 128 14.0, 17.0, 11.8).
             constexpr int NB = NJB / 2;
-            if (NB > 1 && (int64_t)(p.Mp / 16) * NB <= compute_units())
-                hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB < 2 ? NJB : 2, SM, FROMC, 1, 1, DBG>), dim3((unsigned)(p.Mp / 16), NB > 0 ? NB : 1), dim3(256), 0, s, p);
-            else
-                hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 1, DBG>), dim3((unsigned)(p.Mp / 16)), dim3(256), 0, s, p);
+            const unsigned groups = (unsigned)(p.Mp / 16);
+            if constexpr (NB > 1) {
+                if ((int64_t)groups * NB <= compute_units()) {
+                    const dim3 grid(groups > 8 ? (groups + 7) / 8 * 8 : groups, NB);
+                    hipLaunchKernelGGL((mxi_act_kernel<BF16, 2, SM, FROMC, 1, 1, DBG, true>), grid, dim3(256), 0, s, p);
+                    break;
+                }
+            }
+            hipLaunchKernelGGL((mxi_act_kernel<BF16, NJB, SM, FROMC, 1, 1, DBG, false>), dim3(groups), dim3(256), 0, s, p);
             break;
         }
     }

@@ -346,7 +346,7 @@ def test_workgroups_per_block_of_the_rank(r, K, xd, smooth):
     X = torch.randn((16 * groups + 16, K), generator=gen, device="cuda")
     X = X if xd == "f32" else X.bfloat16()
     views = []
-    for m in (16 * groups + 16, 16 * groups - 3, 5):
+    for m in (16 * groups + 16, 16 * groups - 3, 5, 167, 330):   # (the last two: a number of groups that is not a multiple of 8)
         act = lq.lq_quantize_act(cfg, packed, X[:m], act=torch.full((lq.lq_act_sizes(cfg, m),), 0xFF, dtype=torch.uint8, device="cuda"))
         dbg = lq.lq_quantize_act(cfg, packed, X[:m], act=torch.full_like(act, 0xFF), debug=True)[0]
         assert torch.equal(act, dbg), m
