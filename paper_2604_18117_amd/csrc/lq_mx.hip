@@ -518,9 +518,18 @@ __device__ __forceinline__ float mx_amax16(const MxChunk<false>& ch)
     return m;
 }
 
+// Wavefronts a SIMD is to hold.  Asked for one, the compiler keeps the eight sums of T beside the row's registers, and fewer workgroups fit than with four sums (us,
+// one / two: fp32 8447 x 128 rank 64 7.4 / 6.1, 12327 x 1280 20.8 / 18.9, smoothed 16384 x 1600 rank 128 37.9 / 28.8).  Four wavefronts at rank 128 spill for two
+// or are no faster (fp32 6125 x 1600 19.3 / 22.6, smoothed 6125 x 1280 11.6 / 12.1), but for smoothed rows of nine chunks and streamed ones.
+constexpr int mx_act_waves(int maxc, int njb, bool sm, int nw)
+{
+    if (nw == 4 && njb == 8) return maxc == 0 || (maxc == 9 && sm) ? 2 : 1;
+    return nw == 4 && maxc == 5 && njb == 1 ? 4 : 2;
+}
+
 // BF16IN: element type of X; SM: smoothing variant (X times the stored reciprocals, held as fp32).
 template <bool BF16IN, int MAXC, int NJB, bool SM, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 8 || (MAXC == 18 && NJB <= 4) ? 2 : 1) void mx_act_kernel(MxActParams p)
+__global__ __launch_bounds__(64 * NW, mx_act_waves(MAXC, NJB, SM, NW)) void mx_act_kernel(MxActParams p)
 {
     write_tag(p.tag_dst, p.tag);
     constexpr bool BF16 = BF16IN && !SM;  // representation of the row in registers
@@ -787,21 +796,26 @@ static hipError_t mx_act_len(const MxActParams& p, int64_t Mp, hipStream_t s)
     // 4608 rank 128 13.7, 15.6, 4096 x 2240 rank 64 10.5, 11.5), and for long rows where they hold the row in few enough registers for two
     // workgroups to a compute unit, or four would have to stream it (8192 x 4608 rank 32 27.1, 28.8, rank 128 36.4, 40.0, 12000 x 2240 rank 16 19.7,
     // 20.8, smoothed 6001 x 4608 rank 128 36.0, 45.1); four elsewhere (16384 x 1152 rank 128 26.4, 21.8, 8192 x 4608 rank 64 32.3, 29.0, smoothed
-    // 6001 x 2240 rank 64 18.3, 16.5, 16384 x 512 rank 32 10.8, 9.5).
+    // 6001 x 2240 rank 64 18.3, 16.5, 16384 x 512 rank 32 10.8, 9.5).  Rank 64 is not among the long rows of bf16: eight wavefronts take 145 registers there and one
+    // workgroup fits a compute unit, four (18 chunks each) 233 and two do; up to rank 32 eight take at most 122 and two fit, at rank 128 one fits either way.
     const bool fp32_rows = !BF16 || SM;
+    // Rows beyond K = 4608 are streamed (MAXC = 0): by eight wavefronts where a chain is the time, but for fp32 input, whose reads bound it (us, four / eight: 400 x 4736
+    // rank 32 bf16 16.0 / 15.6, fp32 23.2 / 25.8), and in a single part of a group (2 x 4736 fp32 13.1 / 11.9); by four beyond that, of which more
+    // workgroups fit (8447 x 4736 rank 32 41.9 / 44.3, rank 128 54.2 / 59.8, smoothed fp32 12327 x 4736 rank 64 106.4 / 125.7).
+    if (p.C64 > 72) {
+        const bool eight = p.M < 16 || (BF16 && Mp <= 16 * compute_units());
+        return eight ? mx_act_rank<BF16, 0, SM, 8>(p, Mp, s) : mx_act_rank<BF16, 0, SM, 4>(p, Mp, s);
+    }
     const bool wide = Mp <= 16 * compute_units() || (p.C64 > 36 && (fp32_rows || p.r != 64)) || (!fp32_rows && p.r <= 32 && p.C64 > 20);
     if (wide) {
         const int mc = (p.C64 + 7) / 8;
         if (mc <= 3) return mx_act_rank<BF16, 3, SM, 8>(p, Mp, s);
         if (mc <= 5) return mx_act_rank<BF16, 5, SM, 8>(p, Mp, s);
-        if (mc <= 9) return mx_act_rank<BF16, 9, SM, 8>(p, Mp, s);
-        return mx_act_rank<BF16, 0, SM, 8>(p, Mp, s);
+        return mx_act_rank<BF16, 9, SM, 8>(p, Mp, s);
     }
-    // MAXC = 0: the streamed form, for rows that do not fit in registers (K > 4608; rows held as fp32 beyond K = 2304 went to eight wavefronts above)
-    const int mc = (p.C64 + 3) / 4;
+    const int mc = (p.C64 + 3) / 4;  // (rows held as fp32 beyond K = 2304 went to eight wavefronts above)
     if (mc <= 5) return mx_act_rank<BF16, 5, SM, 4>(p, Mp, s);
     if constexpr (BF16 && !SM) {
-        if (mc > 18) return mx_act_rank<BF16, 0, SM, 4>(p, Mp, s);
         if (mc > 9) return mx_act_rank<BF16, 18, SM, 4>(p, Mp, s);
     }
     return mx_act_rank<BF16, 9, SM, 4>(p, Mp, s);

@@ -272,3 +272,26 @@ def test_rows_of_very_small_values(oracle, K, r, xd, smooth):
         first = first or got
         for a, b in zip(got, first):               # the same bits in every form and row
             assert torch.equal(a, b.repeat(((M + 36) // 37,) + (1,) * (b.dim() - 1))[:M]), M
+
+
+# Streamed rows, each type of input, by eight and by four wavefronts: a part of a group of 16 rows, on both sides of a group per compute unit, an odd number of
+# chunks and a padding one.  The same bits in every form.
+@pytest.mark.parametrize("K,r,xd,smooth", [(4672, 32, "f32", False), (4736, 64, "f32", True), (5184, 128, "bf16", True), (6144, 128, "bf16", False), (4736, 0, "bf16", True)])
+def test_streamed_rows(oracle, K, r, xd, smooth):
+    from paper_2604_18117_amd import binding as lq
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    layer = wl.Layer("t", 37, K, 64, r, "mx", 32, 8, 8, xd, seed=K + r)
+    X, W, L, R = wl.make_inputs(layer)
+    X[2, :] = -0.0
+    gamma = np.exp2(np.random.default_rng(K).integers(-3, 4, K)).astype(np.float32) if smooth else None
+    g = _compare(oracle, layer, X, W, L, R, gamma=gamma)
+    Xd = wl.to_dev_x(X, xd)
+    first = None
+    for M in (37, 9, 16 * cus - 3, 16 * cus + 5):
+        big = Xd.repeat((M + 36) // 37, 1)[:M].contiguous()
+        act = torch.full((lq.lq_act_sizes(g.cfg, M),), 0xFF, dtype=torch.uint8, device="cuda")
+        v = lq.lq_unpack_act(g.cfg, lq.lq_quantize_act(g.cfg, g.packed, big, act=act), M)
+        got = [t.cpu() for t in ((v.xq, v.xe, v.tq, v.st) if r else (v.xq, v.xe))]
+        first = first or got
+        for a, b in zip(got, first):
+            assert torch.equal(a, b.repeat(((M + 36) // 37,) + (1,) * (b.dim() - 1))[:M]), M
