@@ -153,9 +153,12 @@ __device__ __forceinline__ void f6_codes16(const float (&v)[16], uint32_t (&out)
 
 // Chunks of R a wavefront of eight holds or has requested: what its registers leave, at most four (us, two / this: 2 x 1152 rank 16 3.9 / 3.5, 300 x
 // 1152 rank 32 5.3 / 4.9, 64 x 2240 rank 64 7.4 / 7.1, 71 x 4544 rank 128 13.7 / 13.3, with 16 rows to a workgroup).  With four wavefronts the workgroups of a
-// compute unit cover for each other and registers are better spent on them.
-constexpr int act_int_ring(bool bf16in, int maxc, int njb, bool sm, bool ga, int nw)
+// compute unit cover for each other and registers are better spent on them.  Two as well from rank 96 on for rows of at most three chunks per wavefront, 16 of
+// which share a workgroup: most wavefronts have one or two, and R past them, requested and not used, held the others up (SINT4, four / two: 2 x
+// 1024 rank 128 6.9 / 6.3, 400 x 768 rank 128 6.9 / 6.2, 1024 x 256 rank 96 5.6 / 5.1, 400 x 640 rank 128 6.1 / 5.6).
+constexpr int act_int_ring(bool bf16in, int maxc, int njb, bool sm, bool ga, int nw, int cs)
 {
+    if (cs == 1 && maxc == 3 && njb >= 6) return 2;
     const int rows = maxc * (bf16in && !sm && !ga ? 8 : 16), left = njb > 0 ? (208 - rows - 4 * njb) / (4 * njb) : 0;
     return maxc == 0 || nw == 4 || (sm && !bf16in && maxc == 9) || left < 2 ? 2 : left < 4 ? left : 4;
 }
@@ -199,7 +202,7 @@ __global__ __launch_bounds__(NW * 64) void act_int_kernel(ActParams p)
     // load of X: the Q2(R) fragments of this wavefront's first chunks (later ones are fetched RD - 1
     // chunks ahead inside the loop) and the row scales of R.
     constexpr int NJA = NJB > 0 ? NJB : 1;
-    constexpr int RD = act_int_ring(BF16IN, MAXC, NJB, SM, GA, NW);
+    constexpr int RD = act_int_ring(BF16IN, MAXC, NJB, SM, GA, NW, CS);
     v4i bv[RD][NJA];
     auto load_rq = [&](v4i (&dst)[NJA], int t) {
         int c = CS * (wave + NW * (t / CS)) + t % CS;
