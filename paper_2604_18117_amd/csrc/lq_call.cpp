@@ -3,8 +3,8 @@
 // conversion of every argument: 2.7 us of a call beside the 2.6 us of its launch, more than the kernels of a small call take.
 //
 // A function returns the library's status when it has made the call, and -1, with nothing done, for every argument that is not of the
-// ordinary kind (no buffer given, another type, tensor subclasses and wrapped tensors, an active torch-function mode, a failed check); the binding
-// then goes through its own checks and ctypes, which raise what they raise.
+// ordinary kind (no buffer given, another type, tensor subclasses and wrapped tensors, an active torch-function mode, of which
+// torch.set_default_device is one, a failed check); the binding then goes through its own checks and ctypes, which raise what they raise.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
