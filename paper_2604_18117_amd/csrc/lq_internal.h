@@ -227,9 +227,11 @@ int compute_units();  // of the current device
 // one of them; beyond that 8 wavefronts deal the chunks less evenly (9 chunks of K = 1152: a second turn in which seven wait) and hold more
 // registers; so do they with few chunks.  us, forms 2 / 8 / 4, MXFP8: 64 x 4608 rank 128 9.1 / 13.2 / 15.4, 1024 x 1152 rank 128 5.1 / 6.7 / 6.9,
 // 2048 x 1152 rank 64 5.9 / 6.6 / 6.5, 3000 x 1152 rank 64 8.1 / 7.1 / 6.9, 4096 x 2240 rank 64 11.3 / 10.2 / 10.4, 4096 x 4608 rank 128 29.1 /
-// 19.3 / 20.7, 6001 x 2240 rank 64 16.5 / 16.3 / 15.7, 16384 x 1152 rank 128 41.9 / 27.1 / 21.5, 2 x 1152 rank 32 - / 4.1 / 4.3, 3000 x 512
-// rank 32 - / 5.3 / 4.5; MXFP6: 2048 x 512 rank 64 4.8 / 5.0 / 4.3, 1024 x 512 rank 128 4.7 / 5.5 / 4.8.  Rows held as fp32 spill at rank 128 with
-// 4 wavefronts (6001 x 1152, smoothed: 19.3 with 8, 21.2).
+// 19.3 / 20.7, 6001 x 2240 rank 64 16.5 / 16.3 / 15.7, 16384 x 1152 rank 128 41.9 / 27.1 / 21.5, 2 x 1152 rank 32 - / 4.1 / 4.3.  Rows held as fp32
+// spill at rank 128 with 4 wavefronts (6001 x 1152, smoothed: 19.3 with 8, 21.2).  The line at five chunks was drawn with short rows in the looped
+// form (mxb_act_short; 3000 x 512 rank 32 - / 5.3 / 4.5, MXFP6 2048 x 512 rank 64 4.8 / 5.0 / 4.3); in their own the forms are closer, and more
+// wavefronts ahead from 5 chunks and rank 64 on (- / 4.6 / 4.6, 4.1 / 4.2 / 4.3; 2048 x 640 rank 128 5.1 / 5.5 / 6.2, 300 x 640 rank 64 smoothed fp32
+// 5.2 / 5.2 / 6.1).
 static inline int mxb_act_form(int64_t Mp, int C128, int njb, bool fp32_rows)
 {
     const int64_t groups = Mp / 16, cus = compute_units();
